@@ -126,8 +126,8 @@ int a2a_distances(const a2a_topo* topo, int32_t src_begin, int32_t src_count, in
  * Computed per source batch by a forward path-count pass and a backward dependency pass over
  * the shortest-path DAG; batch results are added in ascending batch order and every sum is taken
  * in a fixed order, so the result is bitwise reproducible from run to run and does not depend on
- * the workspace size (the size decides which batches advance together, never the order of a sum:
- * every batch picks its kernels' lane layout from its own level sizes).
+ * the workspace size (the size decides which batches or sources advance together, never the order of
+ * a sum).
  *   load            device, double[E], overwritten
  *   dist_sum_total  device, int64[1]: sum over these sources of sum_t D(s,t).  May be NULL.
  *   flags           device, int64[1]: A2A_FLAG_* bits.  May be NULL.
@@ -300,7 +300,9 @@ int a2a_tree_lower_bound(int32_t N, int32_t d, double m_bytes, double b_bytes_pe
  * A2A_K_* into ms[] / launches[].  One launch serves a level of all batches of a group and every
  * batch picks its own lane layout inside it; a launch is filed under the layout that the group's
  * average level size stands for (FWD_ROWS / FWD_FEW / FWD_SPREAD, BWD_...).  While a mode other
- * than 0 is on, the compute calls wait for the device to read counters back.  Not thread safe.
+ * than 0 is on, the compute calls wait for the device to read counters back, and every topology goes
+ * through the level-by-level kernels that the profile is about (small ones use one kernel per call
+ * otherwise; the loads then differ by rounding).  Not thread safe.
  */
 typedef enum a2a_prof_kernel {
   A2A_K_INIT = 0,  /* level 0 set-up */

@@ -1,0 +1,525 @@
+// Device code for topologies whose whole per-source state fits the LDS of a compute unit.  Included once,
+// by a2a_topo.hip, after a2a_kernels.h.
+//
+// The level kernels of a2a_kernels.h need three dependent launches per BFS level; a topology of a few
+// thousand nodes is bound by that chain (about 5 us per launch), not by bytes or arithmetic.  Here one
+// workgroup takes its sources from the breadth-first search to the link loads: path counts and coefs live
+// in LDS (19 bytes per node and source), levels are separated by workgroup barriers, and the global traffic
+// is the link table (a few tens of KB, L2-resident), a level byte per node and source, and one row of
+// link loads per workgroup.  Whole calls with the level kernels and with this one: 8x8 torus 128 and 11 us, hypercube
+// of 1024 nodes 305 and 60 us, 16x16x16 torus 1060 and 290 us.  Every sum is taken in a fixed order, so the results are the same bits from run to
+// run and for every workspace size.
+#pragma once
+
+#include <type_traits>
+
+#include "a2a_kernels.h"
+
+namespace a2a_dev {
+
+constexpr int kSmallThreads = 1024;   // largest workgroup
+constexpr int kSmallUnseen = 255;     // level byte of a node not reached; levels go up to 253
+constexpr int kSmallBatch = 32;       // most sources of a workgroup: they search together, a bit of a word each
+constexpr int kSmallChunk = 16;       // partial load rows that are added up before they meet the running sum
+constexpr int kSmallCounters = 4;     // words per workgroup: sum of distances, reached pairs, inexact, demand x distance
+
+struct SmallView {
+  // [N][KS] out- and in-neighbours, two per word, in link order, as 8 x id (an LDS offset that costs one addition);
+  // places past a node's last link hold the node itself, which is never one level from itself
+  const uint32_t* out;
+  const uint32_t* in;
+  double* part;             // [workgroups of the launch][N * KS * 2] link loads, in the places of `out`
+  long long* counters;      // [workgroups of the launch][kSmallCounters]
+  unsigned char* level;     // [workgroups of the launch][per_wg][small_level_bytes(N)]
+  int N;
+  int per, per_log2;        // sources a workgroup works on at a time (a power of two), tg threads each
+  int tg, ts;               // multiples of 64: ts of them work on the levels
+  int depth;                // deepest level of the topology
+  int per_wg;               // sources per workgroup: a multiple of per, at most kSmallBatch
+  int wg0;                  // first workgroup of the launch among those of the call
+  int src_begin, src_count;
+  const double* dem;        // as in GroupView (nullptr: every pair has demand 1)
+  long long dem_ld;
+};
+
+// Level bytes of one source.
+__host__ __device__ inline size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
+
+// LDS of a workgroup, in this order: coef and sigma (doubles; two mask words per node in their place while
+// the search runs), node queue (8 x id in 16 bits, level by level), nodes per level, then
+// where each level starts in the queue, and cursors, level bytes.
+__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth) {
+  const size_t nq = ((size_t)N + 1) & ~(size_t)1;
+  return (size_t)per * ((size_t)N * 16 + nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
+}
+
+template <typename T>
+__device__ __forceinline__ T& lds_at(T* base, uint32_t bytes) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + bytes);
+}
+template <typename T>
+__device__ __forceinline__ const T& lds_at(const T* base, uint32_t bytes) {
+  return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
+}
+
+// The links of a node.  at<kShift>(j): 8 x id of link j shifted right, i.e. its place in an array of doubles (0), words
+// (1) or bytes (3); the two halves of a word are shifted together.
+template <int KS>
+struct SmallRow {
+  uint32_t w[KS];
+  template <int kShift = 0>
+  __device__ __forceinline__ uint32_t at(int j) const {
+    const uint32_t x = w[j >> 1] >> kShift;
+    return j & 1 ? x >> 16 : x & 0xffffu;
+  }
+  __device__ __forceinline__ void load(const uint32_t* __restrict__ table, uint32_t v8) {  // v8: 8 x id
+    const uint32_t* const p = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(table) + (v8 * KS >> 1));
+#pragma unroll
+    for (int k = 0; k < KS; ++k) w[k] = p[k];
+  }
+};
+
+// Bit-parallel search from the `count` (at most kSmallBatch) consecutive sources s0, ...: bit j = source j.
+// A thread owns nodes t, t + T, ...; their masks stay in its registers, and a level ORs them into the words of
+// their out-neighbours (two arrays in turn, so that one barrier per level is enough).  Levels are kept as bit
+// planes and written as a byte per node and source at the end.  nxt: 2 N words of LDS.
+template <int KS, int kNodes>
+__device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
+                                             unsigned char* __restrict__ level) {
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
+  SmallRow<KS> row[kNodes];
+  uint32_t cur[kNodes], seen[kNodes], plane[kNodes][8];
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k) {
+    const int v = t + T * k;
+    if (v < N) row[k].load(sv.out, 8 * v);
+    cur[k] = v >= s0 && v < s0 + count ? 1u << (v - s0) : 0u;
+    seen[k] = cur[k];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) plane[k][p] = 0;
+  }
+  for (int i = t; i < 2 * N; i += T) nxt[i] = 0;
+  __syncthreads();
+  for (int l = 1; l <= sv.depth; ++l) {
+    uint32_t* const buf = nxt + (l & 1) * N;
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) {
+      if (cur[k] != 0) {
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j)
+          __hip_atomic_fetch_or(&lds_at(buf, row[k].template at<1>(j)), cur[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) {
+      const int v = t + T * k;
+      if (v < N) {
+        cur[k] = buf[v] & ~seen[k];
+        buf[v] = 0;
+        seen[k] |= cur[k];
+#pragma unroll
+        for (int p = 0; p < 8; ++p) plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
+      }
+    }
+  }
+  const int nl = (int)small_level_bytes(N);
+#pragma unroll 1
+  for (int j = 0; j < count; ++j) {
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) {
+      const int v = t + T * k;
+      unsigned d = 0;
+#pragma unroll
+      for (int p = 0; p < 8; ++p) d |= ((plane[k][p] >> j) & 1u) << p;
+      if (((seen[k] >> j) & 1u) == 0) d = kSmallUnseen;
+      if (v < N) level[(size_t)j * nl + v] = (unsigned char)d;
+    }
+  }
+}
+
+// max(x, 0) and min(x, 0): one instruction each (the compiler's own adds one that quiets signalling NaNs).
+__device__ __forceinline__ double plus_part(double x) {
+  double r;
+  asm("v_max_f64 %0, %1, 0" : "=v"(r) : "v"(x));
+  return r;
+}
+__device__ __forceinline__ double minus_part(double x) {
+  double r;
+  asm("v_min_f64 %0, %1, 0" : "=v"(r) : "v"(x));
+  return r;
+}
+
+// A node that a lane works on: its place in an array of doubles (8 x id) and links.
+template <int KS>
+struct SmallNode {
+  uint32_t v8;
+  SmallRow<KS> row;
+  __device__ __forceinline__ void request(const uint32_t* __restrict__ table, uint32_t node8) {
+    v8 = node8;
+    row.load(table, v8);
+  }
+  __device__ __forceinline__ void gather(const double* x, double (&y)[2 * KS]) const {
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) y[j] = lds_at(x, row.at(j));
+  }
+  __device__ __forceinline__ void levels(const unsigned char* lvl, int (&m)[2 * KS]) const {
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) m[j] = lds_at(lvl, row.template at<3>(j));
+  }
+  // Sum of x over the links, in link order, of the entries that are positive (negative: of the negative ones, made
+  // positive).
+  template <bool kNegative>
+  __device__ __forceinline__ double sum(const double* x) const {
+    double y[2 * KS];
+    gather(x, y);
+    double a = kNegative ? minus_part(y[0]) : plus_part(y[0]);
+#pragma unroll
+    for (int j = 1; j < 2 * KS; ++j) a += kNegative ? minus_part(y[j]) : plus_part(y[j]);
+    return kNegative ? -a : a;
+  }
+  // The same over the links that lead to the given level.
+  __device__ __forceinline__ double sum_level(const double* x, const unsigned char* lvl, int level) const {
+    double y[2 * KS];
+    gather(x, y);
+    int m[2 * KS];
+    levels(lvl, m);
+    double a = 0.0;
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) a += m[j] == level ? y[j] : 0.0;
+    return a;
+  }
+};
+
+// Goes over the levels first, first + step, ... last (step 1 or -1), a node per lane, a barrier after every level:
+// x of a node becomes f(node, sum of x over its links of `table` to the level gone over before).  For that the
+// levels need not be looked up.  An in-link of a node on level l comes from level l - 1 or later and an out-link leads
+// to level l + 1 or before, so at the other ends there are only: nodes of the level before; nodes of the same
+// level, written or not; and nodes not written yet, whose x is 0.  Even levels are kept with a plus sign and odd ones
+// with a minus sign, and a level adds up the entries of the other sign only (kSigns; x must not be negative).
+// Without kSigns the levels are looked up, and x may hold anything at first.
+// What a level costs is its chain of LDS accesses and branches (about 30 cycles each), so there is one branch that is
+// taken for two levels, and the next level's nodes and links are on their way while this one is worked on.
+// tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
+// in the queue, for all levels up to last + 2; the queue has one valid entry at least.
+template <int KS, bool kSigns, typename F>
+__device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const int* start,
+                                            const unsigned char* lvl, double* x, int tl, int tg, int first, int last,
+                                            int step, F&& f) {
+  int l = first, left = (last - first) * step;  // levels after this one
+  if (tl - lane_id() >= tg) {  // waves that would rarely find a node
+    do {
+      __syncthreads();
+    } while (--left >= 0);
+    return;
+  }
+  const auto place = [&](int p, int end) { return (uint32_t)q[min(p, max(end - 1, 0))]; };
+  int p0 = start[l] + tl, e0 = start[l + 1], p1 = start[l + step] + tl, e1 = start[l + step + 1];
+  SmallNode<KS> n0, n1;
+  n0.request(table, place(p0, e0));
+  const auto level = [&](auto odd, const SmallNode<KS>& cur, SmallNode<KS>& next) {
+    constexpr bool kOdd = decltype(odd)::value;
+    const auto value = [&](const SmallNode<KS>& n) {
+      if constexpr (kSigns) {
+        const double a = f(n.v8, n.template sum<!kOdd>(x));
+        return kOdd ? -a : a;
+      } else {
+        return f(n.v8, n.sum_level(x, lvl, l - step));
+      }
+    };
+    const uint32_t v = place(p1, e1);
+    const int l2 = max(l + 2 * step, 0), p2 = start[l2] + tl, e2 = start[l2 + 1];
+    next.request(table, v);
+    if (p0 < e0) lds_at(x, cur.v8) = value(cur);
+#pragma unroll 1
+    for (int p = p0 + tg; p < e0; p += tg) {  // a level of more nodes than the source has threads
+      SmallNode<KS> more;
+      more.request(table, q[p]);
+      lds_at(x, more.v8) = value(more);
+    }
+    __syncthreads();
+    l += step;
+    p0 = p1;
+    e0 = e1;
+    p1 = p2;
+    e1 = e2;
+  };
+  using Odd = std::true_type;
+  using Even = std::false_type;
+  if (!(l & 1)) {
+    level(Even{}, n0, n1);
+    n0 = n1;
+    if (--left < 0) return;
+  }
+  for (;;) {
+    level(Odd{}, n0, n1);
+    if (--left < 0) return;
+    level(Even{}, n1, n0);
+    if (--left < 0) return;
+  }
+}
+
+// Link loads of sources [per_wg * workgroup, + per_wg) of the call, as one row of `part`.  The search takes up to
+// kSmallBatch sources together; then, up to `per` sources at a time: the nodes are sorted by level; sigma = the
+// sum over the in-links from the level before, level by level; coef = demand / sigma + the coefs of the successors,
+// deepest level first; then every thread goes over the out-links of its own nodes (t, t + T, ...) and adds
+// sigma(u) * coef(w) of each source, in source order, to the loads it keeps in registers for as long as the
+// workgroup lives.  KS: words per node of the link tables; kNodes: nodes per thread.
+template <int KS, int kNodes, bool kDemand>
+__global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
+  extern __shared__ double s_small[];
+  __shared__ double s_wd[kSmallThreads / kWave];
+  __shared__ long long s_tot[kSmallThreads / kWave][3];
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, lane = lane_id();
+  const int N = sv.N, per = sv.per, slots = sv.depth + 4;  // level slots, two of them empty for certain
+  const int nq = (N + 1) & ~1, nl = (int)small_level_bytes(N);
+  double* const coef_all = s_small;
+  double* const sig_all = coef_all + per * N;
+  unsigned short* const q_all = reinterpret_cast<unsigned short*>(sig_all + per * N);
+  int* const start_all = reinterpret_cast<int*>(q_all + per * nq);
+  int* const at_all = start_all + per * slots;
+  unsigned char* const lvl_all = reinterpret_cast<unsigned char*>(at_all + per * slots);
+  const int sg = __builtin_amdgcn_readfirstlane(t / sv.tg);  // which of the sources this thread's wave is on
+  const int tl = t - sg * sv.tg;
+  double* const coef = coef_all + sg * N;
+  double* const sig = sig_all + sg * N;
+  unsigned short* const q = q_all + sg * nq;
+  int* const start = start_all + sg * slots;
+  int* const at = at_all + sg * slots;
+  const unsigned char* const lvl = lvl_all + sg * nl;
+  unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
+
+  long long dsum = 0, reached = 0;
+  bool inexact = false;
+  double wd = 0.0;
+
+  const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
+  const int s_last = min(sv.src_count, s_first + sv.per_wg);
+  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level);
+  double acc[kNodes][2 * KS];
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k)
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
+  for (int s0 = s_first; s0 < s_last; s0 += per) {
+    const bool valid = s0 + sg < s_last;
+    for (int i = t; i < per * slots; i += T) start_all[i] = 0;
+    __syncthreads();  // (the level bytes are written, too)
+    for (int i = t; i < per * nl / 4; i += T) {
+      const int k = i * 4 / nl;
+      reinterpret_cast<uint32_t*>(lvl_all)[i] =
+          s0 + k < s_last ? reinterpret_cast<const uint32_t*>(level + (size_t)(s0 - s_first) * nl)[i] : 0xffffffffu;
+    }
+    __syncthreads();
+    for (int v = tl; v < N; v += sv.tg) {
+      const int l = lvl[v];
+      if (l != kSmallUnseen) __hip_atomic_fetch_add(&start[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (kDemand) {
+        const double d = valid ? sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)(s0 + sg)] : 0.0;
+        coef[v] = d;  // becomes coef in the backward sweep
+        if (l != kSmallUnseen && l != 0) wd = __builtin_fma((double)l, d, wd);
+      }
+    }
+    __syncthreads();
+    if (tl < kWave) {
+      int carry = 0;
+      for (int l0 = 0; l0 < slots; l0 += kWave) {
+        const int l = l0 + lane, c = l < slots ? start[l] : 0;
+        const int incl = wave_scan_incl(c, lane);
+        if (l < slots) start[l] = at[l] = carry + incl - c;
+        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+        dsum += (long long)c * l;
+        reached += l > 0 ? c : 0;
+      }
+    }
+    __syncthreads();
+    for (int v = tl; v < N; v += sv.tg) {
+      const int l = lvl[v];
+      if (l != kSmallUnseen)
+        q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(8 * v);
+      sig[v] = l == 0 ? 1.0 : 0.0;
+      if (!kDemand) coef[v] = 0.0;
+    }
+    if (!valid && tl == 0) q[0] = 0;  // no source: the sweeps look at an entry all the same
+    __syncthreads();
+    // the deepest level of these sources, the same in all threads
+    int depth = 0;
+    for (int l0 = 1; l0 < slots - 1; l0 += kWave) {
+      const int l = l0 + lane;
+      bool any = false;
+      if (l < slots - 1)
+        for (int k = 0; k < per; ++k) any |= start_all[k * slots + l + 1] > start_all[k * slots + l];
+      const uint64_t m = __ballot(any);
+      if (m != 0) depth = l0 + 63 - __builtin_clzll(m);
+    }
+    if (depth > 0) {
+      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, sv.ts, 1, depth, 1, [&](uint32_t, double a) {
+        inexact |= a >= kTwo53;
+        return a;
+      });
+      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, sv.ts, depth, 1, -1, [&](uint32_t v8, double a) {
+        const double r = recip(__builtin_fabs(lds_at(sig, v8)));
+        return (kDemand ? lds_at(coef, v8) * r : r) + a;
+      });
+    }
+    // The links of this thread's nodes.  They are the same in every round: the empty asm keeps the compiler
+    // from holding on to them (it would spill registers for that).
+    int u = t;
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k, u += T) {
+      asm volatile("" : "+v"(u));
+      if (u < N) {
+        SmallNode<KS> n;
+        n.row.load(sv.out, 8 * u);
+#pragma unroll 1
+        for (int s = 0; s < per; ++s) {
+          const double* const c_s = coef_all + s * N;
+          const unsigned char* const l_s = lvl_all + s * nl;
+          const double g = __builtin_fabs(sig_all[s * N + u]);
+          int m[2 * KS];
+          n.levels(l_s, m);
+          double y[2 * KS];
+          n.gather(c_s, y);
+          const int next = (int)l_s[u] + 1;
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) {
+            const double c = m[j] == next ? y[j] : 0.0;
+            acc[k][j] = __builtin_fma(g, kDemand ? c : __builtin_fabs(c), acc[k][j]);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k) {
+    const int u = t + T * k;
+    if (u < N) {
+      double2* const out = reinterpret_cast<double2*>(sv.part) + ((size_t)blockIdx.x * (size_t)N + (size_t)u) * KS;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) out[j] = make_double2(acc[k][2 * j], acc[k][2 * j + 1]);
+    }
+  }
+  long long bad = __ballot(inexact) != 0 ? 1 : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    dsum += __shfl_xor(dsum, o, kWave);
+    reached += __shfl_xor(reached, o, kWave);
+  }
+  if (kDemand) wd = wave_sum_double(wd);
+  if (lane == 0) {
+    s_tot[t / kWave][0] = dsum;
+    s_tot[t / kWave][1] = reached;
+    s_tot[t / kWave][2] = bad;
+    if (kDemand) s_wd[t / kWave] = wd;
+  }
+  __syncthreads();
+  if (t == 0) {
+    for (int k = 1; k < T / kWave; ++k) {
+      dsum += s_tot[k][0];
+      reached += s_tot[k][1];
+      bad |= s_tot[k][2];
+      if (kDemand) wd += s_wd[k];
+    }
+    long long* const c = sv.counters + (size_t)blockIdx.x * kSmallCounters;
+    c[0] = dsum;
+    c[1] = reached;
+    c[2] = bad;
+    if (kDemand) c[3] = __double_as_longlong(wd);
+  }
+}
+
+// load[a] = (first ? 0 : load[a]) + chunk sums of the launch's partial rows, kSmallChunk rows to a chunk, in
+// row order throughout (a launch but the last has whole chunks, so the bits do not depend on how the
+// call's workgroups are cut into launches).  A workgroup takes 32 places of the link table; thread
+// (place, c) adds up chunks c, c + 8, ...  The last workgroup adds up the counters instead: running
+// totals in misc[0..3] (inexact, sum of distances, reached pairs, demand x distance), and with `last` the
+// call's outputs.
+struct SmallTotals {
+  long long pairs;  // source_count * (N - 1)
+  long long* dist_sum_total;
+  long long* flags;
+  double* weighted;
+};
+__global__ void __launch_bounds__(kBlock)
+k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_t* __restrict__ out_ptr,
+               double* __restrict__ load, long long* __restrict__ misc, SmallTotals tot) {
+  const int t = (int)threadIdx.x;
+  const int places = sv.N * KS * 2;
+  if (blockIdx.x == gridDim.x - 1) {
+    if (t >= kWave) return;
+    long long bad = 0, dsum = 0, reached = 0;
+    double wd = first ? 0.0 : __longlong_as_double(misc[3]);
+    for (int r0 = 0; r0 < rows; r0 += kWave) {
+      const int r = r0 + t;
+      double x = 0.0;
+      if (r < rows) {
+        const long long* const c = sv.counters + (size_t)r * kSmallCounters;
+        dsum += c[0];
+        reached += c[1];
+        bad |= c[2];
+        if (tot.weighted != nullptr) x = __longlong_as_double(c[3]);
+      }
+      if (tot.weighted != nullptr)  // one after the other, in row order
+        for (int k = 0; k < min(kWave, rows - r0); ++k)
+          wd += __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), k));
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      dsum += __shfl_xor(dsum, o, kWave);
+      reached += __shfl_xor(reached, o, kWave);
+      bad |= __shfl_xor(bad, o, kWave);
+    }
+    if (t == 0) {
+      if (!first) {
+        bad |= misc[0];
+        dsum += misc[1];
+        reached += misc[2];
+      }
+      misc[0] = bad;
+      misc[1] = dsum;
+      misc[2] = reached;
+      misc[3] = __double_as_longlong(wd);
+      if (last) {
+        if (tot.dist_sum_total) *tot.dist_sum_total = dsum;
+        if (tot.flags) *tot.flags = (bad ? 1 : 0) | (tot.pairs != reached ? 2 : 0);
+        if (tot.weighted) *tot.weighted = wd;
+      }
+    }
+    return;
+  }
+  constexpr int kPlaces = 32, kAhead = kBlock / kPlaces;
+  __shared__ double s_sum[kAhead][kPlaces];
+  const int p = (int)blockIdx.x * kPlaces + (t & (kPlaces - 1)), c = t / kPlaces;
+  const int u = min(p, places - 1) / (2 * KS), j = p - u * 2 * KS;
+  const int a = out_ptr[u] + j;
+  const bool link = p < places && a < out_ptr[u + 1];
+  double run = 0.0;
+  if (link && c == 0 && !first) run = load[a];
+  const int chunks = (rows + kSmallChunk - 1) / kSmallChunk;
+  for (int c0 = 0; c0 < chunks; c0 += kAhead) {
+    double sum = 0.0;
+    if (link && c0 + c < chunks) {
+      const int r0 = (c0 + c) * kSmallChunk;
+      const double* const x = sv.part + (size_t)r0 * (size_t)places + p;
+      if (r0 + kSmallChunk <= rows) {
+        double y[kSmallChunk];
+#pragma unroll
+        for (int k = 0; k < kSmallChunk; ++k) y[k] = x[(size_t)k * (size_t)places];
+#pragma unroll
+        for (int k = 0; k < kSmallChunk; ++k) sum += y[k];
+      } else {
+        for (int k = 0; k < rows - r0; ++k) sum += x[(size_t)k * (size_t)places];
+      }
+    }
+    s_sum[c][t & (kPlaces - 1)] = sum;
+    __syncthreads();
+    if (c == 0)
+      for (int k = 0; k < min(kAhead, chunks - c0); ++k) run += s_sum[k][t];
+    __syncthreads();
+  }
+  if (link && c == 0) load[a] = run;
+}
+
+}  // namespace a2a_dev

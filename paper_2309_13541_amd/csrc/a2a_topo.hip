@@ -23,6 +23,7 @@
 #include <vector>
 
 #include "a2a_kernels.h"
+#include "a2a_small_kernels.h"
 #include "a2a_sssp_kernels.h"
 #include "a2a_topo.h"
 
@@ -51,6 +52,12 @@ struct a2a_topo {
   int64_t* h_pinned = nullptr;
   int64_t* d_small = nullptr;
   mutable std::atomic<unsigned> next_slot{0};
+  // Topologies whose per-source state fits LDS (a2a_small_kernels.h): link tables of `ell_words` words per
+  // node, 0 if there are none; smallest workspace of the link load calls.
+  uint32_t *d_ell_out = nullptr, *d_ell_in = nullptr;
+  int ell_words = 0;
+  bool small_loads = false;
+  size_t min_loads_bytes = 0;
   void* d_scratch = nullptr;    // device address of `scratch` on the handle's GPU
   // optional per-kernel timing (a2a_profile_enable); events are created per launch while it is on
   struct ProfRec {
@@ -479,6 +486,143 @@ int probe_depth(const a2a_topo* t, int32_t* depth_out) {
   return rc;
 }
 
+// --- topologies whose per-source state fits LDS ------------------------------------------------------
+
+// LDS that one workgroup may ask for (160 KB per compute unit, a little of it taken by fixed arrays).
+constexpr size_t kSmallLds = 160 * 1024 - 1024;
+constexpr int kComputeUnits = 256;
+
+// Words per node of the link tables (two links a word) for a largest in- or out-degree, 0: no tables.
+int ell_words_for(int32_t N, int32_t degree) {
+  if (N > 8191 || degree > 16 || degree < 1) return 0;  // 8 x id has 16 bits
+  for (int w : {2, 3, 4, 5})
+    if (degree <= 2 * w) return w;
+  return 8;
+}
+
+// Link table of a CSR: the neighbours of a node in list order, then the node itself.
+std::vector<uint32_t> make_ell(int32_t N, const int32_t* ptr, const int32_t* col, int words) {
+  std::vector<uint32_t> ell((size_t)N * words);
+  for (int32_t u = 0; u < N && words > 0; ++u) {
+    const int32_t p0 = ptr[u], deg = ptr[u + 1] - p0;
+    for (int k = 0; k < words; ++k) {
+      const uint32_t a = (uint32_t)(2 * k < deg ? col[p0 + 2 * k] : u);
+      const uint32_t b = (uint32_t)(2 * k + 1 < deg ? col[p0 + 2 * k + 1] : u);
+      ell[(size_t)u * words + k] = 8 * a | (8 * b << 16);
+    }
+  }
+  return ell;
+}
+
+struct SmallPlan {
+  SmallView sv{};
+  int T = 0, workgroups = 0, nodes = 0;  // threads, workgroups of the whole call, nodes per thread
+  size_t lds = 0;
+};
+
+// Threads per source: a level of the search has a few percent of the nodes, a lane each.
+int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 256 : 512; }
+
+// The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
+constexpr int small_max_nodes(int ell_words) { return ell_words == 2 ? 9 : 20 / ell_words; }
+
+// How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
+// do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
+// while there are workgroups for every compute unit; as many rounds as it then takes to have one
+// workgroup for each place on the chip, so that the rows of partial loads stay few.
+SmallPlan small_plan(const a2a_topo* t, int32_t src_count) {
+  SmallPlan p;
+  const int N = t->N, depth = t->level_bound;
+  int tg = small_threads(N), per = 1, log2 = 0;
+  while (2 * per * tg <= kSmallThreads && small_lds_bytes(N, 2 * per, depth) <= kSmallLds &&
+         2ll * per * kComputeUnits <= src_count) {
+    per *= 2;
+    ++log2;
+  }
+  while (N > small_max_nodes(t->ell_words) * per * tg) tg *= 2;
+  p.T = per * tg;
+  p.lds = small_lds_bytes(N, per, depth);
+  const int resident = (int)std::max<size_t>(1, std::min<size_t>(kSmallThreads / p.T, kSmallLds / p.lds));
+  const long long at_once = (long long)per * kComputeUnits * resident;
+  p.sv.per_wg = (int)((src_count + at_once - 1) / at_once) * per;
+  p.workgroups = (src_count + p.sv.per_wg - 1) / p.sv.per_wg;
+  p.nodes = (N + p.T - 1) / p.T;
+  p.sv.out = t->d_ell_out;
+  p.sv.in = t->d_ell_in;
+  p.sv.N = N;
+  p.sv.per = per;
+  p.sv.per_log2 = log2;
+  p.sv.tg = tg;
+  // 1.25 times an average level: most levels in one go
+  p.sv.ts = std::min(tg, (int)align_up((size_t)N * 5 / 4 / (size_t)std::max(depth, 1), kWave));
+  p.sv.depth = depth;
+  p.sv.src_count = src_count;
+  return p;
+}
+
+// Bytes of workspace per workgroup: its row of partial loads, its counters and level bytes.
+size_t small_row_bytes(const a2a_topo* t, int per_wg) {
+  return (size_t)t->N * t->ell_words * 2 * sizeof(double) + kSmallCounters * sizeof(long long) +
+         (size_t)per_wg * small_level_bytes(t->N);
+}
+
+// Whether link loads take the one-workgroup-per-source kernel: everything fits, and so do the rows of one
+// chunk of partial loads into the smallest workspace that a caller may bring.
+bool small_loads_fit(const a2a_topo* t) {
+  return t->ell_words > 0 && t->level_bound < kSmallUnseen - 1 &&
+         t->N <= small_max_nodes(t->ell_words) * kSmallThreads &&
+         small_lds_bytes(t->N, 1, t->level_bound) <= kSmallLds &&
+         256 + kSmallChunk * small_row_bytes(t, kSmallBatch) <= t->min_loads_bytes;
+}
+
+template <int KS, bool kDemand>
+void small_launch_words(const SmallPlan& p, int workgroups, hipStream_t st) {
+  if (p.nodes <= 1)
+    k_small_loads<KS, 1, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else if (p.nodes <= 2)
+    k_small_loads<KS, 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else if (KS <= 5 && p.nodes <= 4)
+    k_small_loads<KS, KS <= 5 ? 4 : 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else
+    k_small_loads<KS, small_max_nodes(KS), kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+}
+template <bool kDemand>
+void small_launch(const SmallPlan& p, int ell_words, int workgroups, hipStream_t st) {
+  switch (ell_words) {
+    case 2: return small_launch_words<2, kDemand>(p, workgroups, st);
+    case 3: return small_launch_words<3, kDemand>(p, workgroups, st);
+    case 4: return small_launch_words<4, kDemand>(p, workgroups, st);
+    case 5: return small_launch_words<5, kDemand>(p, workgroups, st);
+    default: return small_launch_words<8, kDemand>(p, workgroups, st);
+  }
+}
+
+int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
+                     double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
+                     hipStream_t st) {
+  if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  SmallPlan p = small_plan(t, src_count);
+  p.sv.src_begin = src_begin;
+  p.sv.dem = demand;
+  p.sv.dem_ld = src_count;
+  long long rows = (long long)((ws_bytes - 256) / small_row_bytes(t, p.sv.per_wg));  // at least kSmallChunk
+  rows = rows >= p.workgroups ? p.workgroups : rows / kSmallChunk * kSmallChunk;
+  p.sv.part = (double*)(ws + 256);
+  p.sv.counters = (long long*)(p.sv.part + (size_t)rows * t->N * t->ell_words * 2);
+  p.sv.level = (unsigned char*)(p.sv.counters + (size_t)rows * kSmallCounters);
+  const SmallTotals tot{(long long)src_count * (t->N - 1), (long long*)dist_sum_total, (long long*)flags, weighted_dist};
+  const unsigned blocks = (unsigned)((t->N * t->ell_words * 2 + 31) / 32 + 1);
+  for (int w0 = 0; w0 < p.workgroups; w0 += (int)rows) {
+    const int n = std::min(p.workgroups - w0, (int)rows);
+    p.sv.wg0 = w0;
+    demand ? small_launch<true>(p, t->ell_words, n, st) : small_launch<false>(p, t->ell_words, n, st);
+    k_small_reduce<<<blocks, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
+                                              t->d_out_ptr, load, (long long*)ws, tot);
+  }
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
 int check_common(const a2a_topo* t, int32_t src_begin, int32_t src_count, void* ws) {
   if (!t || src_begin < 0 || src_count < 0 || (int64_t)src_begin + src_count > t->N) return A2A_ERR_INVALID_ARG;
   if (src_count > 0 && (!ws || ((uintptr_t)ws & 255u))) return A2A_ERR_INVALID_ARG;
@@ -524,6 +668,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
   a2a_topo* t = new (std::nothrow) a2a_topo();
   if (!t) return A2A_ERR_NO_MEMORY;
   std::vector<int32_t> in_ptr, in_col, in_link;
+  std::vector<uint32_t> ell_out, ell_in;  // link tables of small topologies, see SmallView
   try {
     in_ptr.assign((size_t)N + 1, 0);
     in_col.resize((size_t)(E > 0 ? E : 1));
@@ -538,6 +683,9 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
         in_link[at] = p;
       }
     for (int32_t v = 0; v < N; ++v) t->dmax_in = std::max(t->dmax_in, in_ptr[(size_t)v + 1] - in_ptr[v]);
+    t->ell_words = ell_words_for(N, std::max(dmax, t->dmax_in));
+    ell_out = make_ell(N, row_ptr, col_idx, t->ell_words);
+    ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words);
   } catch (const std::bad_alloc&) {
     delete t;
     return A2A_ERR_NO_MEMORY;
@@ -553,6 +701,8 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
             hipMalloc((void**)&t->d_in_ptr, pb) == hipSuccess &&
             hipMalloc((void**)&t->d_in_col, cb) == hipSuccess &&
             hipMalloc((void**)&t->d_in_link, cb) == hipSuccess &&
+            (t->ell_words == 0 || (hipMalloc((void**)&t->d_ell_out, ell_out.size() * 4) == hipSuccess &&
+                                   hipMalloc((void**)&t->d_ell_in, ell_in.size() * 4) == hipSuccess)) &&
             hipMalloc((void**)&t->d_small, slot_bytes) == hipSuccess &&
             hipHostMalloc((void**)&t->h_pinned, slot_bytes, hipHostMallocDefault) == hipSuccess;
   ok = ok && hipGetSymbolAddress(&t->d_scratch, HIP_SYMBOL(scratch)) == hipSuccess && t->d_scratch != nullptr;
@@ -563,7 +713,14 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     ok = hipMemcpy(t->d_out_col, col_idx, (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess &&
          hipMemcpy(t->d_in_col, in_col.data(), (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess &&
          hipMemcpy(t->d_in_link, in_link.data(), (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess;
+  if (ok && t->ell_words > 0)
+    ok = hipMemcpy(t->d_ell_out, ell_out.data(), ell_out.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
+         hipMemcpy(t->d_ell_in, ell_in.data(), ell_in.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
   if (ok && E > 0) ok = probe_depth(t, &t->level_bound) == A2A_OK;
+  if (ok) {
+    t->min_loads_bytes = make_layout(t, 64, A2A_WS_LOADS, 0, true, true).total;
+    t->small_loads = small_loads_fit(t);
+  }
   if (!ok) {
     (void)hipGetLastError();
     a2a_topo_destroy(t);
@@ -584,6 +741,8 @@ void a2a_topo_destroy(a2a_topo* t) {
   if (t->d_in_ptr) (void)hipFree(t->d_in_ptr);
   if (t->d_in_col) (void)hipFree(t->d_in_col);
   if (t->d_in_link) (void)hipFree(t->d_in_link);
+  if (t->d_ell_out) (void)hipFree(t->d_ell_out);
+  if (t->d_ell_in) (void)hipFree(t->d_ell_in);
   if (t->d_small) (void)hipFree(t->d_small);
   if (t->h_pinned) (void)hipHostFree(t->h_pinned);
   delete t;
@@ -681,6 +840,10 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
   if (rc != A2A_OK) return rc;
   if (!load && t->E > 0) return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
+  // (while profiling is on, the level kernels run: that is what the profile is about)
+  if (t->small_loads && src_count > 0 && t->prof_mode == 0)
+    return small_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags,
+                            (char*)workspace, workspace_bytes, st);
   if (weighted_dist) HIP_TRY(zero_async(weighted_dist, 8, st));
   if (src_count == 0) {
     if (t->E > 0) HIP_TRY(zero_async(load, (size_t)t->E * 8, st));

@@ -1,0 +1,80 @@
+"""The kernel that takes a source from its search to its link loads inside one workgroup, at the edges of what it is
+chosen and cut up by: nodes per workgroup and per thread, words of the link table, deepest level, sources per
+workgroup.  And the level kernels on the small graphs, which they serve only while profiling is on.  Against the
+oracle.  (Needs an MI355X.)"""
+import numpy as np
+import pytest
+
+import a2a_inputs as gen
+from gpu_helpers import run_link_loads, assert_loads_close
+from test_demands import run_demand_gpu, seeded_demand
+from test_gpu_parity import SMALL
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def a2a():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2309_13541_amd as lib
+    lib.load_library()
+    return lib
+
+
+EDGES = [(f"{n} nodes, degree {d}, {cnt} sources", (n, d), s0, cnt) for n, d, s0, cnt in (
+    # nodes at which the threads per source change, and one over
+    (96, 3, 0, 96), (97, 3, 0, 97), (384, 4, 0, 384), (385, 4, 0, 385), (1536, 4, 0, 1536), (1537, 4, 1000, 537),
+    # words per node of the link table: 2, 3, 4, 5, 8; beyond 16 links the level kernels
+    (200, 2, 0, 200), (201, 5, 0, 201), (202, 6, 0, 202), (203, 7, 0, 203), (204, 9, 0, 204), (205, 10, 0, 205),
+    (206, 11, 0, 206), (207, 16, 0, 207), (208, 17, 0, 208),
+    # most nodes per thread for each width, and one node over; most nodes that LDS and 16-bit places allow
+    (5120, 8, 0, 40), (5121, 8, 0, 40), (6144, 6, 100, 520), (4096, 10, 0, 33), (2048, 16, 0, 70), (2049, 16, 0, 70),
+    (8191, 4, 0, 270), (8192, 4, 0, 70),
+    # one source; two sources at a time with one left over; a ragged last workgroup
+    (1000, 5, 999, 1), (600, 5, 0, 513), (1300, 5, 7, 1037))]
+
+
+@pytest.mark.parametrize("name,shape,s0,cnt", EDGES, ids=[e[0] for e in EDGES])
+def test_edges_match_oracle(a2a, oracle, name, shape, s0, cnt):
+    rp, col = gen.random_regular(*shape, 3)
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    o = oracle.run(rp, col, s0, cnt, threads=8)
+    load, dsum, flags = run_link_loads(topo, s0, cnt)
+    assert_loads_close(load, o.load)
+    assert dsum == int(o.dist_sum.sum()) and flags == o.flags
+    least = topo.workspace_bytes(cnt, a2a.WS_LOADS | a2a.WS_MINIMAL)
+    assert np.array_equal(run_link_loads(topo, s0, cnt, least)[0], load)
+    topo.close()
+
+
+@pytest.mark.parametrize("nodes", [32, 33, 254, 255, 256])
+def test_deepest_levels(a2a, oracle, nodes):
+    """Directed rings: as many levels as nodes.  Levels fit a byte, with one value for nodes not reached, up to 253."""
+    rp, col = gen.ring(nodes)
+    topo = a2a.Topology(rp, col)
+    load, dsum, flags = run_link_loads(topo)
+    assert np.array_equal(load, np.full(nodes, nodes * (nodes - 1) / 2.0))
+    assert dsum == nodes * nodes * (nodes - 1) // 2 and flags == 0
+    topo.close()
+
+
+@pytest.mark.parametrize("name", sorted(n for n in SMALL if len(SMALL[n][1])))
+def test_level_kernels_on_small_graphs(a2a, oracle, name):
+    rp, col = SMALL[name]
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    topo.profile_enable(1)
+    o = oracle.run(rp, col)
+    load, dsum, flags = run_link_loads(topo)
+    assert_loads_close(load, o.load)
+    assert dsum == int(o.dist_sum.sum()) and flags == o.flags
+    if name != "chain_2pow54":
+        dem = seeded_demand(topo.N, topo.N, 77)
+        want, want_wd = oracle.run_demand(rp, col, dem)
+        load, wd, dsum, flags = run_demand_gpu(topo, dem)
+        assert_loads_close(load, want)
+        assert wd == pytest.approx(want_wd, rel=1e-12) and dsum == int(o.dist_sum.sum())
+    topo.profile_enable(0)
+    topo.close()

@@ -16,7 +16,8 @@
  * Conventions
  *   - "host" / "device" after a pointer says where the memory lives.  The caller owns every
  *     buffer and the stream; the library owns only the opaque handle (a device copy of the
- *     out- and in-neighbour CSR, a few KB of pinned host memory).
+ *     out- and in-neighbour CSR, as much pinned host memory).  The memory of up to four destroyed small
+ *     handles (2 MiB each at most) is kept for the next ones.
  *   - All device work is enqueued on `hip_stream` (a hipStream_t passed as void*; NULL = the
  *     default stream).  a2a_distances, a2a_link_loads, a2a_link_loads_demand and
  *     a2a_link_loads_static only enqueue kernels of this library: they never wait for the device,

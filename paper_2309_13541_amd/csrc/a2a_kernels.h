@@ -1995,108 +1995,148 @@ __global__ void k_finish(const long long* __restrict__ misc, long long pairs,
   }
 }
 
-// max (lowest link id on ties) and min of load[0..E): one workgroup.
-__global__ void __launch_bounds__(1024)
-k_load_extrema(const double* __restrict__ load, long long E, long long* __restrict__ out) {
-  __shared__ double s_max[1024], s_min[1024];
-  __shared__ long long s_arg[1024];
-  const int t = (int)threadIdx.x;
-  double mx = -1.0, mn = __builtin_huge_val();
-  long long arg = -1;
-  for (long long a = t; a < E; a += 1024) {
-    const double x = load[a];
+// Largest value (lowest index on ties), smallest value, and with kCap the total and largest node capacity: what the
+// two kernels below reduce, over the lanes of a workgroup and then over the workgroups.
+struct Extrema {
+  double mx, mn, sum, cap;
+  long long arg;
+  int bad;
+  __device__ __forceinline__ void clear() {
+    mx = -1.0;
+    mn = __builtin_huge_val();
+    sum = cap = 0.0;
+    arg = -1;
+    bad = 0;
+  }
+  __device__ __forceinline__ void take(double x, long long a) {
     if (x > mx) {
       mx = x;
       arg = a;
     }
     if (x < mn) mn = x;
   }
-  s_max[t] = mx;
-  s_min[t] = mn;
-  s_arg[t] = arg;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (t < o) {
-      const double om = s_max[t + o];
-      const long long oa = s_arg[t + o];
-      if (oa >= 0 && (s_arg[t] < 0 || om > s_max[t] || (om == s_max[t] && oa < s_arg[t]))) {
-        s_max[t] = om;
-        s_arg[t] = oa;
-      }
-      if (s_min[t + o] < s_min[t]) s_min[t] = s_min[t + o];
+  __device__ __forceinline__ void merge(const Extrema& o) {
+    if (o.arg >= 0 && (arg < 0 || o.mx > mx || (o.mx == mx && o.arg < arg))) {
+      mx = o.mx;
+      arg = o.arg;
     }
+    if (o.mn < mn) mn = o.mn;
+    sum += o.sum;
+    if (o.cap > cap) cap = o.cap;
+    bad |= o.bad;
+  }
+};
+constexpr int kExtremaGroups = 64;  // most workgroups
+constexpr int kExtremaWords = 8;    // of scratch per workgroup
+
+// Every workgroup leaves what it found in its part of `scratch`; the one that comes last (`arrived`, 0 before and
+// after) merges them in workgroup order and writes out[0..5] = largest, its index, smallest, total capacity, largest
+// node capacity, 1 if a capacity is bad.  out is host memory: the caller waits for the stream and has them.
+template <bool kCap>
+__device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
+                                               long long* __restrict__ out) {
+  __shared__ Extrema s_e[kBlock];
+  __shared__ bool s_last;
+  const int t = (int)threadIdx.x;
+  s_e[t] = e;
+  __syncthreads();
+  for (int o = kBlock / 2; o > 0; o >>= 1) {
+    if (t < o) s_e[t].merge(s_e[t + o]);
     __syncthreads();
   }
   if (t == 0) {
-    out[0] = __double_as_longlong(s_max[0]);
-    out[1] = s_arg[0];
-    out[2] = __double_as_longlong(s_min[0]);
+    e = s_e[0];
+    const long long w[6] = {__double_as_longlong(e.mx), e.arg, __double_as_longlong(e.mn), __double_as_longlong(e.sum),
+                            __double_as_longlong(e.cap), e.bad};
+    for (int k = 0; k < (kCap ? 6 : 3); ++k)
+      __hip_atomic_store(&scratch[blockIdx.x * kExtremaWords + k], w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    s_last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!s_last) return;
+  e.clear();
+  if (t < (int)gridDim.x) {
+    long long w[6] = {0, 0, 0, 0, 0, 0};
+    for (int k = 0; k < (kCap ? 6 : 3); ++k)
+      w[k] = __hip_atomic_load(&scratch[t * kExtremaWords + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    e.mx = __longlong_as_double(w[0]);
+    e.arg = w[1];
+    e.mn = __longlong_as_double(w[2]);
+    e.sum = __longlong_as_double(w[3]);
+    e.cap = __longlong_as_double(w[4]);
+    e.bad = (int)w[5];
+  }
+  if (t < kExtremaGroups) s_e[t] = e;
+  __syncthreads();
+  for (int o = kExtremaGroups / 2; o > 0; o >>= 1) {
+    if (t < o) s_e[t].merge(s_e[t + o]);
+    __syncthreads();
+  }
+  if (t == 0) {
+    e = s_e[0];
+    out[0] = __double_as_longlong(e.mx);
+    out[1] = e.arg;
+    out[2] = __double_as_longlong(e.mn);
+    if (kCap) {
+      out[3] = __double_as_longlong(e.sum);
+      out[4] = __double_as_longlong(e.cap);
+      out[5] = e.bad;
+    }
+    *arrived = 0;
   }
 }
 
-// The same with link capacities (Sec. 3.1.1): utilisation load[a] / cap[a] instead of load[a];
-// also the total capacity (sum over links in link order, block by block: a fixed order) and the
-// largest total out-capacity of a node.  out[0..2] as k_load_extrema, out[3] = sum of cap,
-// out[4] = largest node capacity, out[5] = 1 if some capacity is not a positive finite number.
-// One workgroup; thread t takes nodes t, t + 1024, ... with their out-links.
-__global__ void __launch_bounds__(1024)
-k_util_extrema(const int32_t* __restrict__ out_ptr, const double* __restrict__ load,
-               const double* __restrict__ cap, int N, long long* __restrict__ out) {
-  __shared__ double s_max[1024], s_min[1024], s_sum[1024], s_cap[1024];
-  __shared__ long long s_arg[1024];
-  __shared__ int s_bad;
-  const int t = (int)threadIdx.x;
-  if (t == 0) s_bad = 0;
-  __syncthreads();
-  double mx = -1.0, mn = __builtin_huge_val(), sum = 0.0, cmax = 0.0;
-  long long arg = -1;
-  bool bad = false;
-  for (int u = t; u < N; u += 1024) {
+// max (lowest link id on ties) and min of load[0..E).  A single workgroup spent 40 us on 100 000 links (a chain of
+// dependent trips to memory); up to 64 of them take 5.
+__global__ void __launch_bounds__(kBlock)
+k_load_extrema(const double* __restrict__ load, long long E, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
+               long long* __restrict__ out) {
+  Extrema e;
+  e.clear();
+  const long long stride = (long long)gridDim.x * kBlock;
+  long long a = (long long)blockIdx.x * kBlock + threadIdx.x;
+  for (; a + 3 * stride < E; a += 4 * stride) {  // four requests in flight
+    double x[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = load[a + k * stride];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) e.take(x[k], a + k * stride);
+  }
+  for (; a < E; a += stride) e.take(load[a], a);
+  reduce_extrema<false>(e, scratch, arrived, out);
+}
+
+// The same with link capacities (Sec. 3.1.1): utilisation load[a] / cap[a] instead of load[a]; also the total
+// capacity (a fixed order: per thread in link order, then a fixed tree) and the largest total out-capacity of a
+// node.  A capacity is bad if it is not a positive finite number.  A thread takes whole nodes.
+__global__ void __launch_bounds__(kBlock)
+k_util_extrema(const int32_t* __restrict__ out_ptr, const double* __restrict__ load, const double* __restrict__ cap, int N,
+               long long* __restrict__ scratch, unsigned* __restrict__ arrived, long long* __restrict__ out) {
+  Extrema e;
+  e.clear();
+  for (int u = (int)(blockIdx.x * kBlock + threadIdx.x); u < N; u += (int)gridDim.x * kBlock) {
     double node_cap = 0.0;
     const int p1 = out_ptr[u + 1];
-    for (int a = out_ptr[u]; a < p1; ++a) {
-      const double c = cap[a];
-      if (!(c > 0.0) || c > 1.7976931348623157e308) bad = true;
-      const double x = load[a] / c;
-      if (x > mx) {
-        mx = x;
-        arg = a;
+    for (int p = out_ptr[u]; p < p1; p += 4) {
+      double c[4], x[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const int a = min(p + k, p1 - 1);
+        c[k] = cap[a];
+        x[k] = load[a];
       }
-      if (x < mn) mn = x;
-      node_cap += c;
-    }
-    sum += node_cap;
-    if (node_cap > cmax) cmax = node_cap;
-  }
-  if (bad) s_bad = 1;
-  s_max[t] = mx;
-  s_min[t] = mn;
-  s_arg[t] = arg;
-  s_sum[t] = sum;
-  s_cap[t] = cmax;
-  __syncthreads();
-  for (int o = 512; o > 0; o >>= 1) {
-    if (t < o) {
-      const double om = s_max[t + o];
-      const long long oa = s_arg[t + o];
-      if (oa >= 0 && (s_arg[t] < 0 || om > s_max[t] || (om == s_max[t] && oa < s_arg[t]))) {
-        s_max[t] = om;
-        s_arg[t] = oa;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        if (p + k >= p1) break;
+        if (!(c[k] > 0.0) || c[k] > 1.7976931348623157e308) e.bad = 1;
+        e.take(x[k] / c[k], p + k);
+        node_cap += c[k];
       }
-      if (s_min[t + o] < s_min[t]) s_min[t] = s_min[t + o];
-      s_sum[t] += s_sum[t + o];
-      if (s_cap[t + o] > s_cap[t]) s_cap[t] = s_cap[t + o];
     }
-    __syncthreads();
+    e.sum += node_cap;
+    if (node_cap > e.cap) e.cap = node_cap;
   }
-  if (t == 0) {
-    out[0] = __double_as_longlong(s_max[0]);
-    out[1] = s_arg[0];
-    out[2] = __double_as_longlong(s_min[0]);
-    out[3] = __double_as_longlong(s_sum[0]);
-    out[4] = __double_as_longlong(s_cap[0]);
-    out[5] = s_bad;
-  }
+  reduce_extrema<true>(e, scratch, arrived, out);
 }
 
 }  // namespace a2a_dev

@@ -138,6 +138,47 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
   }
 }
 
+// Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
+// masks in LDS (three words per node), until a level finds nothing new.  deepest: host memory, a word per workgroup.
+__global__ void __launch_bounds__(kSmallThreads)
+k_small_probe(const uint32_t* __restrict__ table, int words, int N, int* __restrict__ deepest) {
+  extern __shared__ uint32_t s_masks[];
+  __shared__ int s_new[2];
+  uint32_t *const cur = s_masks, *const nxt = cur + N, *const seen = nxt + N;
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, s0 = (int)blockIdx.x * kSmallBatch;
+  for (int v = t; v < N; v += T) {
+    cur[v] = seen[v] = v >= s0 && v < s0 + kSmallBatch ? 1u << (v - s0) : 0u;
+    nxt[v] = 0;
+  }
+  if (t < 2) s_new[t] = 0;
+  __syncthreads();
+  int l = 1;
+  for (;; ++l) {  // ends: a shortest path has less than N links
+    for (int v = t; v < N; v += T) {
+      const uint32_t c = cur[v];
+      if (c == 0) continue;
+      for (int k = 0; k < words; ++k) {
+        const uint32_t w = table[v * words + k];
+        __hip_atomic_fetch_or(&nxt[(w & 0xffffu) >> 3], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        __hip_atomic_fetch_or(&nxt[w >> 19], c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    __syncthreads();
+    bool any = false;
+    for (int v = t; v < N; v += T) {
+      const uint32_t c = nxt[v] & ~seen[v];
+      nxt[v] = 0;
+      cur[v] = c;
+      seen[v] |= c;
+      any |= c != 0;
+    }
+    if (__ballot(any) != 0 && lane_id() == 0) s_new[l & 1] = l;
+    __syncthreads();
+    if (s_new[l & 1] != l) break;
+  }
+  if (t == 0) deepest[blockIdx.x] = l - 1;
+}
+
 // max(x, 0) and min(x, 0): one instruction each (the compiler's own adds one that quiets signalling NaNs).
 __device__ __forceinline__ double plus_part(double x) {
   double r;

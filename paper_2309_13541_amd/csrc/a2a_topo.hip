@@ -14,11 +14,13 @@
 // has, how full they are) is decided inside the kernels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -40,17 +42,27 @@ struct a2a_topo {
   int32_t dmax = 0;
   int32_t dmax_in = 0;  // largest in-degree
   int32_t level_bound = 0;  // largest finite D(s,t), found by the level probe at create
+  // The handle's memory: one device block and one pinned host block.  The host block first holds what is uploaded
+  // and then only the read-back slots.
+  struct Arena {
+    int device = -1;
+    size_t device_bytes = 0, host_bytes = 0;
+    char* d = nullptr;
+    char* h = nullptr;
+  };
+  Arena mem;
   int32_t* d_out_ptr = nullptr;
   int32_t* d_out_col = nullptr;
   int32_t* d_in_ptr = nullptr;
   int32_t* d_in_col = nullptr;
   int32_t* d_in_link = nullptr;  // link id (position in the out-CSR) of every in-CSR entry
-  // Read-back slots of a2a_schedule_bound / _cap: kSlots x kSlotWords int64 on the device and in
-  // pinned host memory; every call takes the next slot, so calls on different streams or threads
-  // do not share one.
+  // Slots of a2a_schedule_bound / _cap: kSlots x kSlotWords int64 of pinned host memory that the kernels write their
+  // results to, scratch and an arrival counter on the device; every call takes the next slot, so calls on
+  // different streams or threads do not share one.
   static constexpr unsigned kSlots = 64, kSlotWords = 8;
-  int64_t* h_pinned = nullptr;
-  int64_t* d_small = nullptr;
+  int64_t* h_slots = nullptr;
+  long long* d_scratch_slots = nullptr;  // [kSlots][kExtremaGroups][kExtremaWords]
+  unsigned* d_arrived = nullptr;         // [kSlots], 0 between calls
   mutable std::atomic<unsigned> next_slot{0};
   // Topologies whose per-source state fits LDS (a2a_small_kernels.h): link tables of `ell_words` words per
   // node, 0 if there are none; smallest workspace of the link load calls.
@@ -76,6 +88,96 @@ struct a2a_topo {
 };
 
 namespace {
+
+// Blocks of destroyed handles, kept for the next ones: a program that evaluates one small topology after the other
+// would spend most of its time in hipMalloc, hipHostMalloc and hipFree otherwise.  At most kKept blocks of at most
+// kLargest bytes each are kept (an idle program holds 8 MiB of each kind of memory at the most); they are given back
+// when an allocation fails.  A block comes here only when the device has finished all work that may use it.
+class ArenaPool {
+ public:
+  using Arena = a2a_topo::Arena;
+  static constexpr size_t kKept = 4, kLargest = 2u << 20, kGrain = 64u << 10;
+
+  bool take(size_t device_bytes, size_t host_bytes, Arena* out) {
+    int device = -1;
+    if (hipGetDevice(&device) != hipSuccess) return false;
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      for (size_t i = 0; i < kept_.size(); ++i)
+        if (kept_[i].device == device && kept_[i].device_bytes >= device_bytes && kept_[i].host_bytes >= host_bytes) {
+          *out = kept_[i];
+          kept_.erase(kept_.begin() + (long)i);
+          return true;
+        }
+    }
+    Arena a;
+    a.device = device;
+    a.device_bytes = align_up_to(device_bytes);
+    a.host_bytes = align_up_to(host_bytes);
+    if (allocate(&a)) {
+      *out = a;
+      return true;
+    }
+    give_back();
+    if (!allocate(&a)) return false;
+    *out = a;
+    return true;
+  }
+
+  void put(const Arena& a) {
+    if (a.d == nullptr && a.h == nullptr) return;
+    int device = a.device;
+    const bool other = hipGetDevice(&device) == hipSuccess && device != a.device;
+    if (other) (void)hipSetDevice(a.device);
+    const bool idle = hipDeviceSynchronize() == hipSuccess;  // as hipFree would wait
+    bool keep = idle && a.d != nullptr && a.h != nullptr && a.device_bytes <= kLargest && a.host_bytes <= kLargest;
+    if (keep) {
+      std::lock_guard<std::mutex> lock(mutex_);
+      keep = kept_.size() < kKept;
+      if (keep) {
+        try {
+          kept_.push_back(a);
+        } catch (const std::bad_alloc&) {
+          keep = false;
+        }
+      }
+    }
+    if (!keep) release(a);
+    if (other) (void)hipSetDevice(device);
+    (void)hipGetLastError();
+  }
+
+ private:
+  static size_t align_up_to(size_t x) { return (x + kGrain - 1) / kGrain * kGrain; }
+  static bool allocate(Arena* a) {
+    if (hipMalloc((void**)&a->d, a->device_bytes) == hipSuccess) {
+      if (hipHostMalloc((void**)&a->h, a->host_bytes, hipHostMallocDefault) == hipSuccess) return true;
+      (void)hipFree(a->d);
+    }
+    (void)hipGetLastError();
+    a->d = a->h = nullptr;
+    return false;
+  }
+  static void release(const Arena& a) {
+    if (a.d) (void)hipFree(a.d);
+    if (a.h) (void)hipHostFree(a.h);
+  }
+  void give_back() {
+    std::vector<Arena> all;
+    {
+      std::lock_guard<std::mutex> lock(mutex_);
+      all.swap(kept_);
+    }
+    for (const Arena& a : all) release(a);
+  }
+  std::mutex mutex_;
+  std::vector<Arena> kept_;
+};
+
+ArenaPool& arena_pool() {
+  static ArenaPool* const pool = new ArenaPool;  // never destroyed: the runtime may be gone by then
+  return *pool;
+}
 
 enum {
   PROF_INIT = A2A_K_INIT, PROF_BFS = A2A_K_BFS, PROF_OFFSETS = A2A_K_OFFSETS, PROF_FWD = A2A_K_FWD_ROWS,
@@ -435,9 +537,20 @@ int run_fold(const Run& r, const GroupView& gv, int depth) {
 
 // Largest finite hop distance of the topology: the BFS from every node, 64 sources per mask, as
 // many super-batches at a time as about 1 GiB of temporary device memory holds.  Runs on the
-// default stream and waits (this is a2a_topo_create).
-int probe_depth(const a2a_topo* t, int32_t* depth_out) {
+// default stream and waits (this is a2a_topo_create).  Topologies with link tables need one launch and leave the
+// results in `deepest_of`, pinned host memory.
+int probe_depth(const a2a_topo* t, int* deepest_of, int32_t* depth_out) {
   const int N = t->N;
+  if (t->ell_words > 0) {
+    const int groups = (N + kSmallBatch - 1) / kSmallBatch;
+    const unsigned threads = (unsigned)std::min<size_t>(kSmallThreads, align_up((size_t)N, kWave));
+    k_small_probe<<<(unsigned)groups, threads, (size_t)N * 3 * sizeof(uint32_t), nullptr>>>(t->d_ell_out, t->ell_words, N,
+                                                                                        deepest_of);
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(nullptr));
+    *depth_out = *std::max_element(deepest_of, deepest_of + groups);
+    return A2A_OK;
+  }
   const int Npad = (int)align_up((size_t)N, kBlock);
   const int nb64 = Npad / kBfsNodes;
   const int sb_all = ((N + 63) / 64 + kSub - 1) / kSub;
@@ -623,6 +736,11 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
   return A2A_OK;
 }
 
+// Workgroups of an extrema kernel that has `items` items of work for its threads.
+unsigned extrema_groups(int64_t items) {
+  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kExtremaGroups, (items + kBlock - 1) / kBlock));
+}
+
 int check_common(const a2a_topo* t, int32_t src_begin, int32_t src_count, void* ws) {
   if (!t || src_begin < 0 || src_count < 0 || (int64_t)src_begin + src_count > t->N) return A2A_ERR_INVALID_ARG;
   if (src_count > 0 && (!ws || ((uintptr_t)ws & 255u))) return A2A_ERR_INVALID_ARG;
@@ -693,30 +811,53 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
   t->N = N;
   t->E = E;
   t->dmax = dmax;
-  const size_t pb = ((size_t)N + 1) * sizeof(int32_t);
-  const size_t cb = (size_t)(E > 0 ? E : 1) * sizeof(int32_t);
-  const size_t slot_bytes = (size_t)a2a_topo::kSlots * a2a_topo::kSlotWords * sizeof(int64_t);
-  bool ok = hipMalloc((void**)&t->d_out_ptr, pb) == hipSuccess &&
-            hipMalloc((void**)&t->d_out_col, cb) == hipSuccess &&
-            hipMalloc((void**)&t->d_in_ptr, pb) == hipSuccess &&
-            hipMalloc((void**)&t->d_in_col, cb) == hipSuccess &&
-            hipMalloc((void**)&t->d_in_link, cb) == hipSuccess &&
-            (t->ell_words == 0 || (hipMalloc((void**)&t->d_ell_out, ell_out.size() * 4) == hipSuccess &&
-                                   hipMalloc((void**)&t->d_ell_in, ell_in.size() * 4) == hipSuccess)) &&
-            hipMalloc((void**)&t->d_small, slot_bytes) == hipSuccess &&
-            hipHostMalloc((void**)&t->h_pinned, slot_bytes, hipHostMallocDefault) == hipSuccess;
+  // What is uploaded lies at the same offsets in the host and the device block; scratch follows on the device,
+  // read-back slots and the probe's results on the host.
+  size_t off = 0;
+  const auto part = [&off](size_t bytes) {
+    const size_t at = off;
+    off += align_up(bytes, 256);
+    return at;
+  };
+  const size_t pb = ((size_t)N + 1) * sizeof(int32_t), cb = (size_t)(E > 0 ? E : 1) * sizeof(int32_t);
+  const size_t eb = ell_out.size() * sizeof(uint32_t);
+  const size_t o_out_ptr = part(pb), o_out_col = part(cb), o_in_ptr = part(pb), o_in_col = part(cb);
+  const size_t o_in_link = part(cb), o_ell_out = part(eb), o_ell_in = part(eb);
+  const size_t o_arrived = part(a2a_topo::kSlots * sizeof(unsigned));
+  const size_t upload = off;
+  const size_t o_scratch = part((size_t)a2a_topo::kSlots * kExtremaGroups * kExtremaWords * sizeof(long long));
+  const size_t device_bytes = off;
+  off = upload;
+  const size_t o_slots = part((size_t)a2a_topo::kSlots * a2a_topo::kSlotWords * sizeof(int64_t));
+  const size_t o_probe = part(((size_t)N + kSmallBatch - 1) / kSmallBatch * sizeof(int));
+  bool ok = arena_pool().take(device_bytes, off, &t->mem);
   ok = ok && hipGetSymbolAddress(&t->d_scratch, HIP_SYMBOL(scratch)) == hipSuccess && t->d_scratch != nullptr;
-  ok = ok && hipMemset(t->d_small, 0, slot_bytes) == hipSuccess &&
-       hipMemcpy(t->d_out_ptr, row_ptr, pb, hipMemcpyHostToDevice) == hipSuccess &&
-       hipMemcpy(t->d_in_ptr, in_ptr.data(), pb, hipMemcpyHostToDevice) == hipSuccess;
-  if (ok && E > 0)
-    ok = hipMemcpy(t->d_out_col, col_idx, (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(t->d_in_col, in_col.data(), (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(t->d_in_link, in_link.data(), (size_t)E * 4, hipMemcpyHostToDevice) == hipSuccess;
-  if (ok && t->ell_words > 0)
-    ok = hipMemcpy(t->d_ell_out, ell_out.data(), ell_out.size() * 4, hipMemcpyHostToDevice) == hipSuccess &&
-         hipMemcpy(t->d_ell_in, ell_in.data(), ell_in.size() * 4, hipMemcpyHostToDevice) == hipSuccess;
-  if (ok && E > 0) ok = probe_depth(t, &t->level_bound) == A2A_OK;
+  if (ok) {
+    char *const d = t->mem.d, *const h = t->mem.h;
+    t->d_out_ptr = (int32_t*)(d + o_out_ptr);
+    t->d_out_col = (int32_t*)(d + o_out_col);
+    t->d_in_ptr = (int32_t*)(d + o_in_ptr);
+    t->d_in_col = (int32_t*)(d + o_in_col);
+    t->d_in_link = (int32_t*)(d + o_in_link);
+    t->d_ell_out = (uint32_t*)(d + o_ell_out);
+    t->d_ell_in = (uint32_t*)(d + o_ell_in);
+    t->d_arrived = (unsigned*)(d + o_arrived);
+    t->d_scratch_slots = (long long*)(d + o_scratch);
+    t->h_slots = (int64_t*)(h + o_slots);
+    std::memcpy(h + o_out_ptr, row_ptr, pb);
+    if (E > 0) std::memcpy(h + o_out_col, col_idx, cb);
+    std::memcpy(h + o_in_ptr, in_ptr.data(), pb);
+    std::memcpy(h + o_in_col, in_col.data(), cb);
+    std::memcpy(h + o_in_link, in_link.data(), cb);
+    if (eb > 0) {
+      std::memcpy(h + o_ell_out, ell_out.data(), eb);
+      std::memcpy(h + o_ell_in, ell_in.data(), eb);
+    }
+    std::memset(h + o_arrived, 0, a2a_topo::kSlots * sizeof(unsigned));
+    ok = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, nullptr) == hipSuccess;
+  }
+  if (ok && E > 0) ok = probe_depth(t, (int*)(t->mem.h + o_probe), &t->level_bound) == A2A_OK;
+  ok = ok && hipStreamSynchronize(nullptr) == hipSuccess;
   if (ok) {
     t->min_loads_bytes = make_layout(t, 64, A2A_WS_LOADS, 0, true, true).total;
     t->small_loads = small_loads_fit(t);
@@ -736,15 +877,7 @@ void a2a_topo_destroy(a2a_topo* t) {
     (void)hipEventDestroy(rec.beg);
     (void)hipEventDestroy(rec.end);
   }
-  if (t->d_out_ptr) (void)hipFree(t->d_out_ptr);
-  if (t->d_out_col) (void)hipFree(t->d_out_col);
-  if (t->d_in_ptr) (void)hipFree(t->d_in_ptr);
-  if (t->d_in_col) (void)hipFree(t->d_in_col);
-  if (t->d_in_link) (void)hipFree(t->d_in_link);
-  if (t->d_ell_out) (void)hipFree(t->d_ell_out);
-  if (t->d_ell_in) (void)hipFree(t->d_ell_in);
-  if (t->d_small) (void)hipFree(t->d_small);
-  if (t->h_pinned) (void)hipHostFree(t->h_pinned);
+  arena_pool().put(t->mem);
   delete t;
 }
 
@@ -996,12 +1129,12 @@ int a2a_schedule_bound(const a2a_topo* t, const double* load, int64_t sum_dist, 
   if (!t || !out || !load || t->E <= 0 || !(m_bytes > 0.0) || !(b_bytes_per_s > 0.0) || sum_dist < 0)
     return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
-  const size_t slot = (size_t)(t->next_slot.fetch_add(1) % a2a_topo::kSlots) * a2a_topo::kSlotWords;
-  int64_t* d_res = t->d_small + slot;
-  const int64_t* h_res = t->h_pinned + slot;
-  k_load_extrema<<<1, 1024, 0, st>>>(load, (long long)t->E, (long long*)d_res);
+  const unsigned slot = t->next_slot.fetch_add(1) % a2a_topo::kSlots;
+  int64_t* const h_res = t->h_slots + slot * a2a_topo::kSlotWords;
+  k_load_extrema<<<extrema_groups((t->E + 3) / 4), kBlock, 0, st>>>(
+      load, (long long)t->E, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
+      (long long*)h_res);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync((void*)h_res, d_res, 3 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   double lmax, lmin;
   std::memcpy(&lmax, &h_res[0], 8);
@@ -1030,12 +1163,12 @@ int a2a_schedule_bound_cap(const a2a_topo* t, const double* load, const double* 
   if (!t || !out || !load || !cap || t->E <= 0 || !(m_bytes > 0.0) || !(b_bytes_per_s > 0.0) || sum_dist < 0)
     return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
-  const size_t slot = (size_t)(t->next_slot.fetch_add(1) % a2a_topo::kSlots) * a2a_topo::kSlotWords;
-  int64_t* d_res = t->d_small + slot;
-  const int64_t* h_res = t->h_pinned + slot;
-  k_util_extrema<<<1, 1024, 0, st>>>(t->d_out_ptr, load, cap, t->N, (long long*)d_res);
+  const unsigned slot = t->next_slot.fetch_add(1) % a2a_topo::kSlots;
+  int64_t* const h_res = t->h_slots + slot * a2a_topo::kSlotWords;
+  k_util_extrema<<<extrema_groups(t->N), kBlock, 0, st>>>(
+      t->d_out_ptr, load, cap, t->N, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
+      (long long*)h_res);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipMemcpyAsync((void*)h_res, d_res, 6 * sizeof(int64_t), hipMemcpyDeviceToHost, st));
   HIP_TRY(hipStreamSynchronize(st));
   if (h_res[5] != 0) return A2A_ERR_INVALID_ARG;  // a capacity that is not positive and finite
   double umax, umin, total, cmax;

@@ -32,7 +32,7 @@ struct SmallView {
   long long* counters;      // [workgroups of the launch][kSmallCounters]
   unsigned char* level;     // [workgroups of the launch][per_wg][small_level_bytes(N)]
   int N;
-  int per, per_log2;        // sources a workgroup works on at a time (a power of two), tg threads each
+  int per;                  // sources a workgroup works on at a time, tg threads each
   int tg, ts;               // multiples of 64: ts of them work on the levels
   int depth;                // deepest level of the topology
   int per_wg;               // sources per workgroup: a multiple of per, at most kSmallBatch
@@ -45,12 +45,12 @@ struct SmallView {
 // Level bytes of one source.
 __host__ __device__ inline size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
 
-// LDS of a workgroup, in this order: coef and sigma (doubles; two mask words per node in their place while
-// the search runs), node queue (8 x id in 16 bits, level by level), nodes per level, then
+// LDS of a workgroup, in this order: coef (where it is asked for) and sigma (doubles; two mask words per node in
+// their place while the search runs), node queue (8 x id in 16 bits, level by level), nodes per level, then
 // where each level starts in the queue, and cursors, level bytes.
-__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth) {
+__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth, bool coefs) {
   const size_t nq = ((size_t)N + 1) & ~(size_t)1;
-  return (size_t)per * ((size_t)N * 16 + nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
+  return (size_t)per * ((size_t)N * (coefs ? 16 : 8) + nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
 }
 
 template <typename T>
@@ -81,22 +81,35 @@ struct SmallRow {
 
 // Bit-parallel search from the `count` (at most kSmallBatch) consecutive sources s0, ...: bit j = source j.
 // A thread owns nodes t, t + T, ...; their masks stay in its registers, and a level ORs them into the words of
-// their out-neighbours (two arrays in turn, so that one barrier per level is enough).  Levels are kept as bit
-// planes and written as a byte per node and source at the end.  nxt: 2 N words of LDS.
+// their out-neighbours (two arrays in turn, so that one barrier per level is enough).  On return bit j of `seen` says
+// whether source j reaches the node, bit j of plane p is bit p of the distance.  nxt: 2 N words of LDS.
+constexpr int kSmallPlanes = 8;
+template <int kNodes>
+struct SmallPlanes {
+  uint32_t seen[kNodes], plane[kNodes][kSmallPlanes];
+  // Distance from source j; kUsed: planes that are not empty.
+  template <int kUsed>
+  __device__ __forceinline__ unsigned distance(int k, int j) const {
+    unsigned d = 0;
+#pragma unroll
+    for (int p = 0; p < kUsed; ++p) d |= ((plane[k][p] >> j) & 1u) << p;
+    return d;
+  }
+};
 template <int KS, int kNodes>
-__device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
-                                             unsigned char* __restrict__ level) {
+__device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
+                                             SmallPlanes<kNodes>& out) {
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
   SmallRow<KS> row[kNodes];
-  uint32_t cur[kNodes], seen[kNodes], plane[kNodes][8];
+  uint32_t cur[kNodes];
 #pragma unroll
   for (int k = 0; k < kNodes; ++k) {
     const int v = t + T * k;
     if (v < N) row[k].load(sv.out, 8 * v);
     cur[k] = v >= s0 && v < s0 + count ? 1u << (v - s0) : 0u;
-    seen[k] = cur[k];
+    out.seen[k] = cur[k];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) plane[k][p] = 0;
+    for (int p = 0; p < kSmallPlanes; ++p) out.plane[k][p] = 0;
   }
   for (int i = t; i < 2 * N; i += T) nxt[i] = 0;
   __syncthreads();
@@ -115,27 +128,38 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
     for (int k = 0; k < kNodes; ++k) {
       const int v = t + T * k;
       if (v < N) {
-        cur[k] = buf[v] & ~seen[k];
+        cur[k] = buf[v] & ~out.seen[k];
         buf[v] = 0;
-        seen[k] |= cur[k];
+        out.seen[k] |= cur[k];
 #pragma unroll
-        for (int p = 0; p < 8; ++p) plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
+        for (int p = 0; p < kSmallPlanes; ++p) out.plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
       }
     }
   }
-  const int nl = (int)small_level_bytes(N);
+}
+
+// The same, the levels written as a byte per source and node.
+template <int KS, int kNodes>
+__device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
+                                             unsigned char* __restrict__ level) {
+  SmallPlanes<kNodes> planes;
+  small_search<KS, kNodes>(sv, nxt, s0, count, planes);
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, nl = (int)small_level_bytes(sv.N);
+  const auto write = [&](auto used) {
 #pragma unroll 1
-  for (int j = 0; j < count; ++j) {
+    for (int j = 0; j < count; ++j) {
 #pragma unroll
-    for (int k = 0; k < kNodes; ++k) {
-      const int v = t + T * k;
-      unsigned d = 0;
-#pragma unroll
-      for (int p = 0; p < 8; ++p) d |= ((plane[k][p] >> j) & 1u) << p;
-      if (((seen[k] >> j) & 1u) == 0) d = kSmallUnseen;
-      if (v < N) level[(size_t)j * nl + v] = (unsigned char)d;
+      for (int k = 0; k < kNodes; ++k) {
+        unsigned d = planes.template distance<decltype(used)::value>(k, j);
+        if (((planes.seen[k] >> j) & 1u) == 0) d = kSmallUnseen;
+        if (t + T * k < sv.N) level[(size_t)j * nl + t + T * k] = (unsigned char)d;
+      }
     }
-  }
+  };
+  if (sv.depth < 32)
+    write(std::integral_constant<int, 5>{});
+  else
+    write(std::integral_constant<int, kSmallPlanes>{});
 }
 
 // Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
@@ -300,6 +324,119 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
   }
 }
 
+// Where things lie in a workgroup's LDS (small_lds_bytes), and this thread's part in it.
+struct SmallLds {
+  double *coef_all, *sig_all;  // coef_all only where coefs are asked for
+  unsigned short* q_all;
+  int *start_all, *at_all;
+  unsigned char* lvl_all;
+  int slots, nq, nl;  // level slots (two of them empty for certain), queue entries, level bytes of a source
+  int sg, tl;         // which of the sources this thread's wave is on, its place among the threads of that source
+  __device__ __forceinline__ SmallLds(const SmallView& sv, double* lds, bool coefs) {
+    slots = sv.depth + 4;
+    nq = (sv.N + 1) & ~1;
+    nl = (int)small_level_bytes(sv.N);
+    coef_all = lds;
+    sig_all = lds + (coefs ? sv.per * sv.N : 0);
+    q_all = reinterpret_cast<unsigned short*>(sig_all + sv.per * sv.N);
+    start_all = reinterpret_cast<int*>(q_all + sv.per * nq);
+    at_all = start_all + sv.per * slots;
+    lvl_all = reinterpret_cast<unsigned char*>(at_all + sv.per * slots);
+    sg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / sv.tg);
+    tl = (int)threadIdx.x - sg * sv.tg;
+  }
+  __device__ __forceinline__ unsigned short* q() const { return q_all + sg * nq; }
+  __device__ __forceinline__ int* start() const { return start_all + sg * slots; }
+  __device__ __forceinline__ unsigned char* lvl() const { return lvl_all + sg * nl; }
+};
+
+// Takes the levels of the next `left` sources (up to sv.per of them) from `level` and sorts their nodes by level into
+// the queues; init(v, level) is called once per node.  Adds up distances and reached nodes.  Returns the deepest
+// level of these sources, the same in all threads.
+template <typename Init>
+__device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& lds, const unsigned char* __restrict__ level,
+                                          int left, Init&& init, long long& dsum, long long& reached) {
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, lane = lane_id();
+  const int N = sv.N, per = sv.per, slots = lds.slots;
+  int* const start = lds.start();
+  int* const at = lds.at_all + lds.sg * slots;
+  const unsigned char* const lvl = lds.lvl();
+  unsigned short* const q = lds.q();
+  for (int i = t; i < per * slots; i += T) lds.start_all[i] = 0;
+  const int here = min(per, left) * (lds.nl / 4);
+  for (int i = t; i < per * (lds.nl / 4); i += T)
+    reinterpret_cast<uint32_t*>(lds.lvl_all)[i] = i < here ? reinterpret_cast<const uint32_t*>(level)[i] : 0xffffffffu;
+  __syncthreads();
+  for (int v = lds.tl; v < N; v += sv.tg) {
+    const int l = lvl[v];
+    if (l != kSmallUnseen) __hip_atomic_fetch_add(&start[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    init(v, l);
+  }
+  __syncthreads();
+  if (lds.tl < kWave) {
+    int carry = 0;
+    for (int l0 = 0; l0 < slots; l0 += kWave) {
+      const int l = l0 + lane, c = l < slots ? start[l] : 0;
+      const int incl = wave_scan_incl(c, lane);
+      if (l < slots) start[l] = at[l] = carry + incl - c;
+      carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+      dsum += (long long)c * l;
+      reached += l > 0 ? c : 0;
+    }
+    if (carry == 0 && lane == 0) q[0] = 0;  // no source: the sweeps look at an entry all the same
+  }
+  __syncthreads();
+  for (int v = lds.tl; v < N; v += sv.tg) {
+    const int l = lvl[v];
+    if (l != kSmallUnseen)
+      q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(8 * v);
+  }
+  __syncthreads();
+  int depth = 0;
+  for (int l0 = 1; l0 < slots - 1; l0 += kWave) {
+    const int l = l0 + lane;
+    bool any = false;
+    if (l < slots - 1)
+      for (int k = 0; k < per; ++k) any |= lds.start_all[k * slots + l + 1] > lds.start_all[k * slots + l];
+    const uint64_t m = __ballot(any);
+    if (m != 0) depth = l0 + 63 - __builtin_clzll(m);
+  }
+  return depth;
+}
+
+// A workgroup's totals into its counters (all threads call it).
+__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd) {
+  __shared__ double s_wd[kSmallThreads / kWave];
+  __shared__ long long s_tot[kSmallThreads / kWave][3];
+  const int t = (int)threadIdx.x;
+  long long bad = __ballot(inexact) != 0 ? 1 : 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    dsum += __shfl_xor(dsum, o, kWave);
+    reached += __shfl_xor(reached, o, kWave);
+  }
+  wd = wave_sum_double(wd);
+  if (lane_id() == 0) {
+    s_tot[t / kWave][0] = dsum;
+    s_tot[t / kWave][1] = reached;
+    s_tot[t / kWave][2] = bad;
+    s_wd[t / kWave] = wd;
+  }
+  __syncthreads();
+  if (t != 0) return;
+  for (int k = 1; k < (int)blockDim.x / kWave; ++k) {
+    dsum += s_tot[k][0];
+    reached += s_tot[k][1];
+    bad |= s_tot[k][2];
+    wd += s_wd[k];
+  }
+  long long* const c = sv.counters + (size_t)blockIdx.x * kSmallCounters;
+  c[0] = dsum;
+  c[1] = reached;
+  c[2] = bad;
+  c[3] = __double_as_longlong(wd);
+}
+
 // Link loads of sources [per_wg * workgroup, + per_wg) of the call, as one row of `part`.  The search takes up to
 // kSmallBatch sources together; then, up to `per` sources at a time: the nodes are sorted by level; sigma = the
 // sum over the in-links from the level before, level by level; coef = demand / sigma + the coefs of the successors,
@@ -309,25 +446,18 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
 template <int KS, int kNodes, bool kDemand>
 __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
   extern __shared__ double s_small[];
-  __shared__ double s_wd[kSmallThreads / kWave];
-  __shared__ long long s_tot[kSmallThreads / kWave][3];
-  const int T = (int)blockDim.x, t = (int)threadIdx.x, lane = lane_id();
-  const int N = sv.N, per = sv.per, slots = sv.depth + 4;  // level slots, two of them empty for certain
-  const int nq = (N + 1) & ~1, nl = (int)small_level_bytes(N);
-  double* const coef_all = s_small;
-  double* const sig_all = coef_all + per * N;
-  unsigned short* const q_all = reinterpret_cast<unsigned short*>(sig_all + per * N);
-  int* const start_all = reinterpret_cast<int*>(q_all + per * nq);
-  int* const at_all = start_all + per * slots;
-  unsigned char* const lvl_all = reinterpret_cast<unsigned char*>(at_all + per * slots);
-  const int sg = __builtin_amdgcn_readfirstlane(t / sv.tg);  // which of the sources this thread's wave is on
-  const int tl = t - sg * sv.tg;
+  const int T = (int)blockDim.x, t = (int)threadIdx.x;
+  const int N = sv.N, per = sv.per;
+  const SmallLds lds(sv, s_small, true);
+  const int sg = lds.sg, tl = lds.tl, nl = lds.nl;
+  double* const coef_all = lds.coef_all;
+  double* const sig_all = lds.sig_all;
+  const unsigned char* const lvl_all = lds.lvl_all;
   double* const coef = coef_all + sg * N;
   double* const sig = sig_all + sg * N;
-  unsigned short* const q = q_all + sg * nq;
-  int* const start = start_all + sg * slots;
-  int* const at = at_all + sg * slots;
-  const unsigned char* const lvl = lvl_all + sg * nl;
+  const unsigned short* const q = lds.q();
+  const int* const start = lds.start();
+  const unsigned char* const lvl = lds.lvl();
   unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
 
   long long dsum = 0, reached = 0;
@@ -337,6 +467,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
   small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level);
+  __syncthreads();
   double acc[kNodes][2 * KS];
 #pragma unroll
   for (int k = 0; k < kNodes; ++k)
@@ -344,55 +475,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
     for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
   for (int s0 = s_first; s0 < s_last; s0 += per) {
     const bool valid = s0 + sg < s_last;
-    for (int i = t; i < per * slots; i += T) start_all[i] = 0;
-    __syncthreads();  // (the level bytes are written, too)
-    for (int i = t; i < per * nl / 4; i += T) {
-      const int k = i * 4 / nl;
-      reinterpret_cast<uint32_t*>(lvl_all)[i] =
-          s0 + k < s_last ? reinterpret_cast<const uint32_t*>(level + (size_t)(s0 - s_first) * nl)[i] : 0xffffffffu;
-    }
-    __syncthreads();
-    for (int v = tl; v < N; v += sv.tg) {
-      const int l = lvl[v];
-      if (l != kSmallUnseen) __hip_atomic_fetch_add(&start[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, [&](int v, int l) {
+      sig[v] = l == 0 ? 1.0 : 0.0;
       if (kDemand) {
         const double d = valid ? sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)(s0 + sg)] : 0.0;
         coef[v] = d;  // becomes coef in the backward sweep
         if (l != kSmallUnseen && l != 0) wd = __builtin_fma((double)l, d, wd);
+      } else {
+        coef[v] = 0.0;
       }
-    }
-    __syncthreads();
-    if (tl < kWave) {
-      int carry = 0;
-      for (int l0 = 0; l0 < slots; l0 += kWave) {
-        const int l = l0 + lane, c = l < slots ? start[l] : 0;
-        const int incl = wave_scan_incl(c, lane);
-        if (l < slots) start[l] = at[l] = carry + incl - c;
-        carry += __builtin_amdgcn_readlane(incl, kWave - 1);
-        dsum += (long long)c * l;
-        reached += l > 0 ? c : 0;
-      }
-    }
-    __syncthreads();
-    for (int v = tl; v < N; v += sv.tg) {
-      const int l = lvl[v];
-      if (l != kSmallUnseen)
-        q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(8 * v);
-      sig[v] = l == 0 ? 1.0 : 0.0;
-      if (!kDemand) coef[v] = 0.0;
-    }
-    if (!valid && tl == 0) q[0] = 0;  // no source: the sweeps look at an entry all the same
-    __syncthreads();
-    // the deepest level of these sources, the same in all threads
-    int depth = 0;
-    for (int l0 = 1; l0 < slots - 1; l0 += kWave) {
-      const int l = l0 + lane;
-      bool any = false;
-      if (l < slots - 1)
-        for (int k = 0; k < per; ++k) any |= start_all[k * slots + l + 1] > start_all[k * slots + l];
-      const uint64_t m = __ballot(any);
-      if (m != 0) depth = l0 + 63 - __builtin_clzll(m);
-    }
+    }, dsum, reached);
     if (depth > 0) {
       small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, sv.ts, 1, depth, 1, [&](uint32_t, double a) {
         inexact |= a >= kTwo53;
@@ -442,33 +534,108 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
       for (int j = 0; j < KS; ++j) out[j] = make_double2(acc[k][2 * j], acc[k][2 * j + 1]);
     }
   }
-  long long bad = __ballot(inexact) != 0 ? 1 : 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    dsum += __shfl_xor(dsum, o, kWave);
-    reached += __shfl_xor(reached, o, kWave);
-  }
-  if (kDemand) wd = wave_sum_double(wd);
-  if (lane == 0) {
-    s_tot[t / kWave][0] = dsum;
-    s_tot[t / kWave][1] = reached;
-    s_tot[t / kWave][2] = bad;
-    if (kDemand) s_wd[t / kWave] = wd;
-  }
+  small_totals(sv, dsum, reached, inexact, wd);
+}
+
+// Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and
+// forward sweep as above.
+struct SmallOut {
+  int32_t* dist;    // [src_count][N]
+  double* sigma;    // [src_count][N]
+  long long* sums;  // [src_count]
+};
+template <int KS, int kNodes>
+__global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, SmallOut out) {
+  extern __shared__ double s_small[];
+  const int N = sv.N;
+  const SmallLds lds(sv, s_small, false);
+  const int nl = lds.nl, tl = lds.tl;
+  double* const sig = lds.sig_all + lds.sg * N;
+  const unsigned char* const lvl = lds.lvl();
+  unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
+  long long dsum = 0, reached = 0;
+  bool inexact = false;
+  const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
+  const int s_last = min(sv.src_count, s_first + sv.per_wg);
+  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level);
   __syncthreads();
-  if (t == 0) {
-    for (int k = 1; k < T / kWave; ++k) {
-      dsum += s_tot[k][0];
-      reached += s_tot[k][1];
-      bad |= s_tot[k][2];
-      if (kDemand) wd += s_wd[k];
+  for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
+    long long own = 0;
+    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0,
+                                 [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
+    if (depth > 0)
+      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, sv.ts, 1, depth, 1, [&](uint32_t, double a) {
+        inexact |= a >= kTwo53;
+        return a;
+      });
+    const int s = s0 + lds.sg;
+    if (s < s_last) {
+      const size_t row = (size_t)s * (size_t)N;
+      for (int v = tl; v < N; v += sv.tg) {
+        const int l = lvl[v];
+        __builtin_nontemporal_store(__builtin_fabs(sig[v]), &out.sigma[row + v]);
+        if (out.dist != nullptr) __builtin_nontemporal_store(l == kSmallUnseen ? -1 : l, &out.dist[row + v]);
+      }
+      if (out.sums != nullptr && tl < kWave) {
+        long long d = own;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) d += __shfl_xor(d, o, kWave);
+        if (tl == 0) out.sums[s] = d;
+      }
     }
-    long long* const c = sv.counters + (size_t)blockIdx.x * kSmallCounters;
-    c[0] = dsum;
-    c[1] = reached;
-    c[2] = bad;
-    if (kDemand) c[3] = __double_as_longlong(wd);
+    dsum += own;
+    __syncthreads();
   }
+  small_totals(sv, dsum, reached, inexact, 0.0);
+}
+
+// Distances alone come straight from the planes of the search.
+template <int KS, int kNodes>
+__global__ void __launch_bounds__(kSmallThreads) k_small_dist(SmallView sv, SmallOut out) {
+  extern __shared__ double s_small[];
+  __shared__ int s_sum[kSmallBatch];
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N, lane = lane_id();
+  if (t < kSmallBatch) s_sum[t] = 0;
+  const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
+  const int count = min(sv.src_count - s_first, sv.per_wg);
+  SmallPlanes<kNodes> planes;
+  small_search<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, count, planes);
+  long long reached = 0;
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k)
+    if (t + T * k < N) reached += __popc(planes.seen[k]);
+  if (t == 0) reached -= count;  // the sources themselves
+  const auto write = [&](auto used) {
+#pragma unroll 1
+    for (int j = 0; j < count; ++j) {
+      int sum = 0;
+#pragma unroll
+      for (int k = 0; k < kNodes; ++k) {
+        const int v = t + T * k;
+        const int d = (int)planes.template distance<decltype(used)::value>(k, j);
+        if (v < N) {
+          sum += d;
+          if (out.dist != nullptr)
+            __builtin_nontemporal_store(((planes.seen[k] >> j) & 1u) != 0 ? d : -1, &out.dist[(size_t)(s_first + j) * (size_t)N + v]);
+        }
+      }
+      if (out.sums != nullptr) {
+        sum = wave_sum_int(sum);
+        if (lane == 0) __hip_atomic_fetch_add(&s_sum[j], sum, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+  };
+  if (sv.depth < 8)
+    write(std::integral_constant<int, 3>{});
+  else if (sv.depth < 32)
+    write(std::integral_constant<int, 5>{});
+  else
+    write(std::integral_constant<int, kSmallPlanes>{});
+  if (out.sums != nullptr) {
+    __syncthreads();
+    if (t < count) out.sums[s_first + t] = s_sum[t];
+  }
+  small_totals(sv, 0, reached, false, 0.0);
 }
 
 // load[a] = (first ? 0 : load[a]) + chunk sums of the launch's partial rows, kSmallChunk rows to a chunk, in
@@ -480,6 +647,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
 struct SmallTotals {
   long long pairs;  // source_count * (N - 1)
   long long* dist_sum_total;
+  long long* unreachable;
   long long* flags;
   double* weighted;
 };
@@ -524,6 +692,7 @@ k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_
       misc[3] = __double_as_longlong(wd);
       if (last) {
         if (tot.dist_sum_total) *tot.dist_sum_total = dsum;
+        if (tot.unreachable) *tot.unreachable = tot.pairs - reached;
         if (tot.flags) *tot.flags = (bad ? 1 : 0) | (tot.pairs != reached ? 2 : 0);
         if (tot.weighted) *tot.weighted = wd;
       }

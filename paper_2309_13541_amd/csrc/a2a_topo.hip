@@ -65,11 +65,11 @@ struct a2a_topo {
   unsigned* d_arrived = nullptr;         // [kSlots], 0 between calls
   mutable std::atomic<unsigned> next_slot{0};
   // Topologies whose per-source state fits LDS (a2a_small_kernels.h): link tables of `ell_words` words per
-  // node, 0 if there are none; smallest workspace of the link load calls.
+  // node, 0 if there are none; which calls use them; smallest workspaces of the calls.
   uint32_t *d_ell_out = nullptr, *d_ell_in = nullptr;
   int ell_words = 0;
-  bool small_loads = false;
-  size_t min_loads_bytes = 0;
+  bool small_loads = false, small_sigma = false, small_dist = false;
+  size_t min_loads_bytes = 0, min_sigma_bytes = 0, min_dist_bytes = 0;
   void* d_scratch = nullptr;    // device address of `scratch` on the handle's GPU
   // optional per-kernel timing (a2a_profile_enable); events are created per launch while it is on
   struct ProfRec {
@@ -639,32 +639,40 @@ int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 25
 // The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
 constexpr int small_max_nodes(int ell_words) { return ell_words == 2 ? 9 : 20 / ell_words; }
 
+enum class SmallWhat { kLoads, kSigma, kDist };
+
 // How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
 // do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
 // while there are workgroups for every compute unit; as many rounds as it then takes to have one
 // workgroup for each place on the chip, so that the rows of partial loads stay few.
-SmallPlan small_plan(const a2a_topo* t, int32_t src_count) {
+SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   SmallPlan p;
   const int N = t->N, depth = t->level_bound;
-  int tg = small_threads(N), per = 1, log2 = 0;
-  while (2 * per * tg <= kSmallThreads && small_lds_bytes(N, 2 * per, depth) <= kSmallLds &&
-         2ll * per * kComputeUnits <= src_count) {
-    per *= 2;
-    ++log2;
+  const bool coefs = what == SmallWhat::kLoads;
+  // nodes a thread may own: its registers hold the loads of their links, or the bit planes of their distances
+  const int most = coefs ? small_max_nodes(t->ell_words) : 8;
+  int tg = small_threads(N), per = 1;
+  if (what == SmallWhat::kDist) {
+    tg = std::min(kSmallThreads, (int)align_up((size_t)N, kWave));
+    p.lds = (size_t)N * 8;
+  } else {
+    const int want = std::max(1, std::min(kSmallThreads / kWave, src_count / kComputeUnits));
+    const int least = std::min(tg, 256);
+    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, coefs) <= kSmallLds) ++per;
+    tg = std::min(tg, kSmallThreads / per / kWave * kWave);
+    p.lds = small_lds_bytes(N, per, depth, coefs);
   }
-  while (N > small_max_nodes(t->ell_words) * per * tg) tg *= 2;
+  while (N > most * per * tg) tg += kWave;
   p.T = per * tg;
-  p.lds = small_lds_bytes(N, per, depth);
   const int resident = (int)std::max<size_t>(1, std::min<size_t>(kSmallThreads / p.T, kSmallLds / p.lds));
   const long long at_once = (long long)per * kComputeUnits * resident;
-  p.sv.per_wg = (int)((src_count + at_once - 1) / at_once) * per;
+  p.sv.per_wg = std::min((int)((src_count + at_once - 1) / at_once), kSmallBatch / per) * per;
   p.workgroups = (src_count + p.sv.per_wg - 1) / p.sv.per_wg;
   p.nodes = (N + p.T - 1) / p.T;
   p.sv.out = t->d_ell_out;
   p.sv.in = t->d_ell_in;
   p.sv.N = N;
   p.sv.per = per;
-  p.sv.per_log2 = log2;
   p.sv.tg = tg;
   // 1.25 times an average level: most levels in one go
   p.sv.ts = std::min(tg, (int)align_up((size_t)N * 5 / 4 / (size_t)std::max(depth, 1), kWave));
@@ -684,7 +692,7 @@ size_t small_row_bytes(const a2a_topo* t, int per_wg) {
 bool small_loads_fit(const a2a_topo* t) {
   return t->ell_words > 0 && t->level_bound < kSmallUnseen - 1 &&
          t->N <= small_max_nodes(t->ell_words) * kSmallThreads &&
-         small_lds_bytes(t->N, 1, t->level_bound) <= kSmallLds &&
+         small_lds_bytes(t->N, 1, t->level_bound, true) <= kSmallLds &&
          256 + kSmallChunk * small_row_bytes(t, kSmallBatch) <= t->min_loads_bytes;
 }
 
@@ -714,7 +722,7 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
                      double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
                      hipStream_t st) {
   if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  SmallPlan p = small_plan(t, src_count);
+  SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
   p.sv.src_begin = src_begin;
   p.sv.dem = demand;
   p.sv.dem_ld = src_count;
@@ -723,7 +731,8 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
   p.sv.part = (double*)(ws + 256);
   p.sv.counters = (long long*)(p.sv.part + (size_t)rows * t->N * t->ell_words * 2);
   p.sv.level = (unsigned char*)(p.sv.counters + (size_t)rows * kSmallCounters);
-  const SmallTotals tot{(long long)src_count * (t->N - 1), (long long*)dist_sum_total, (long long*)flags, weighted_dist};
+  const SmallTotals tot{(long long)src_count * (t->N - 1), (long long*)dist_sum_total, nullptr,
+                        (long long*)flags, weighted_dist};
   const unsigned blocks = (unsigned)((t->N * t->ell_words * 2 + 31) / 32 + 1);
   for (int w0 = 0; w0 < p.workgroups; w0 += (int)rows) {
     const int n = std::min(p.workgroups - w0, (int)rows);
@@ -731,6 +740,62 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
     demand ? small_launch<true>(p, t->ell_words, n, st) : small_launch<false>(p, t->ell_words, n, st);
     k_small_reduce<<<blocks, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
                                               t->d_out_ptr, load, (long long*)ws, tot);
+  }
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
+template <int KS>
+void small_launch_out_words(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st) {
+  const auto launch = [&](auto sigma, auto dist) {
+    if (out.sigma != nullptr)
+      sigma<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+    else
+      dist<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+  };
+  if (p.nodes <= 1)
+    launch(k_small_sigma<KS, 1>, k_small_dist<KS, 1>);
+  else if (p.nodes <= 2)
+    launch(k_small_sigma<KS, 2>, k_small_dist<KS, 2>);
+  else if (p.nodes <= 4)
+    launch(k_small_sigma<KS, 4>, k_small_dist<KS, 4>);
+  else
+    launch(k_small_sigma<KS, 8>, k_small_dist<KS, 8>);
+}
+
+// Whether distances (and path counts) take the small kernels: their level bytes and counters fit the smallest
+// workspace that a caller may bring, for one workgroup at least.
+bool small_distances_fit(const a2a_topo* t, bool sigma) {
+  return t->ell_words > 0 && t->level_bound < kSmallUnseen - 1 &&
+         small_lds_bytes(t->N, 1, t->level_bound, false) <= kSmallLds &&
+         256 + kSmallBatch * small_level_bytes(t->N) + kSmallCounters * sizeof(long long) <=
+             (sigma ? t->min_sigma_bytes : t->min_dist_bytes);
+}
+
+int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, const SmallOut& out, int64_t* unreachable,
+                    int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
+  const bool sigma = out.sigma != nullptr;
+  if (ws_bytes < (sigma ? t->min_sigma_bytes : t->min_dist_bytes)) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  SmallPlan p = small_plan(t, src_count, sigma ? SmallWhat::kSigma : SmallWhat::kDist);
+  p.sv.src_begin = src_begin;
+  const size_t row = kSmallCounters * sizeof(long long) + (sigma ? p.sv.per_wg * small_level_bytes(t->N) : 0);
+  const int rows = (int)std::min<size_t>((size_t)p.workgroups, (ws_bytes - 256) / row);
+  p.sv.counters = (long long*)(ws + 256);
+  p.sv.level = (unsigned char*)(p.sv.counters + (size_t)rows * kSmallCounters);
+  const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
+  for (int w0 = 0; w0 < p.workgroups; w0 += rows) {
+    const int n = std::min(p.workgroups - w0, rows);
+    p.sv.wg0 = w0;
+    switch (t->ell_words) {
+      case 2: small_launch_out_words<2>(p, out, n, st); break;
+      case 3: small_launch_out_words<3>(p, out, n, st); break;
+      case 4: small_launch_out_words<4>(p, out, n, st); break;
+      case 5: small_launch_out_words<5>(p, out, n, st); break;
+      default: small_launch_out_words<8>(p, out, n, st); break;
+    }
+    // a single workgroup: the counters only
+    k_small_reduce<<<1, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
+                                         t->d_out_ptr, nullptr, (long long*)ws, tot);
   }
   HIP_TRY(hipGetLastError());
   return A2A_OK;
@@ -860,7 +925,11 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
   ok = ok && hipStreamSynchronize(nullptr) == hipSuccess;
   if (ok) {
     t->min_loads_bytes = make_layout(t, 64, A2A_WS_LOADS, 0, true, true).total;
+    t->min_sigma_bytes = make_layout(t, 64, A2A_WS_SIGMA, 0, true, true).total;
+    t->min_dist_bytes = make_layout(t, 64, A2A_WS_DISTANCES, 0, true, true).total;
     t->small_loads = small_loads_fit(t);
+    t->small_sigma = small_distances_fit(t, true);
+    t->small_dist = small_distances_fit(t, false);
   }
   if (!ok) {
     (void)hipGetLastError();
@@ -908,6 +977,9 @@ int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32
     if (flags) HIP_TRY(zero_async(flags, 8, st));
     return A2A_OK;
   }
+  if ((sigma ? t->small_sigma : t->small_dist) && t->prof_mode == 0)
+    return small_distances(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
+                           (char*)workspace, workspace_bytes, st);
   Run r;
   r.t = t;
   r.L = make_layout(t, src_count, sigma ? A2A_WS_SIGMA : A2A_WS_DISTANCES, workspace_bytes, false, false);

@@ -78,3 +78,29 @@ def test_level_kernels_on_small_graphs(a2a, oracle, name):
         assert wd == pytest.approx(want_wd, rel=1e-12) and dsum == int(o.dist_sum.sum())
     topo.profile_enable(0)
     topo.close()
+
+
+OUTPUTS = [(f"{n} nodes, degree {d}, {cnt} sources", (n, d), s0, cnt) for n, d, s0, cnt in (
+    (64, 3, 0, 64), (65, 5, 3, 60), (1024, 10, 0, 1024), (1025, 6, 0, 1025), (2049, 4, 1, 2048), (4097, 8, 0, 700),
+    (4900, 6, 0, 1100), (8191, 3, 5, 800), (8192, 3, 0, 70), (700, 16, 0, 513), (700, 17, 0, 100))]
+
+
+@pytest.mark.parametrize("name,shape,s0,cnt", OUTPUTS, ids=[e[0] for e in OUTPUTS])
+def test_distances_and_path_counts(a2a, oracle, name, shape, s0, cnt):
+    from gpu_helpers import run_distances, assert_sigma_equal
+    rp, col = gen.random_regular(*shape, 4)
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    o = oracle.run(rp, col, s0, cnt, threads=8, want_dist=True, want_sigma=True, want_load=False)
+    for flags_of in (a2a.WS_SIGMA, a2a.WS_DISTANCES):
+        least = topo.workspace_bytes(cnt, flags_of | a2a.WS_MINIMAL)
+        for max_ws in (None, least):
+            want_sigma = flags_of == a2a.WS_SIGMA
+            dist, sigma, dsum, unr, flags = run_distances(topo, s0, cnt, want_sigma=want_sigma, max_ws=max_ws)
+            assert np.array_equal(dist, o.dist) and np.array_equal(dsum, o.dist_sum)
+            assert unr == o.unreachable and flags == (o.flags if want_sigma else o.flags & ~1)
+            if want_sigma:
+                assert_sigma_equal(sigma, o.sigma)
+    _, _, dsum, unr, _ = run_distances(topo, s0, cnt, want_sigma=False, want_dist=False)
+    assert np.array_equal(dsum, o.dist_sum) and unr == o.unreachable
+    topo.close()

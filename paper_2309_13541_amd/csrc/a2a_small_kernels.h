@@ -238,6 +238,7 @@ struct SmallNode {
   __device__ __forceinline__ double sum(const double* x) const {
     double y[2 * KS];
     gather(x, y);
+    __builtin_amdgcn_sched_barrier(0);  // all requests first: the scheduler would rather save registers
     double a = kNegative ? minus_part(y[0]) : plus_part(y[0]);
 #pragma unroll
     for (int j = 1; j < 2 * KS; ++j) a += kNegative ? minus_part(y[j]) : plus_part(y[j]);
@@ -249,6 +250,7 @@ struct SmallNode {
     gather(x, y);
     int m[2 * KS];
     levels(lvl, m);
+    __builtin_amdgcn_sched_barrier(0);
     double a = 0.0;
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) a += m[j] == level ? y[j] : 0.0;
@@ -257,7 +259,7 @@ struct SmallNode {
 };
 
 // Goes over the levels first, first + step, ... last (step 1 or -1), a node per lane, a barrier after every level:
-// x of a node becomes f(node, sum of x over its links of `table` to the level gone over before).  For that the
+// x of a node becomes f(node, look(node), sum of x over its links of `table` to the level gone over before).  For that the
 // levels need not be looked up.  An in-link of a node on level l comes from level l - 1 or later and an out-link leads
 // to level l + 1 or before, so at the other ends there are only: nodes of the level before; nodes of the same
 // level, written or not; and nodes not written yet, whose x is 0.  Even levels are kept with a plus sign and odd ones
@@ -267,10 +269,10 @@ struct SmallNode {
 // taken for two levels, and the next level's nodes and links are on their way while this one is worked on.
 // tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
 // in the queue, for all levels up to last + 2; the queue has one valid entry at least.
-template <int KS, bool kSigns, typename F>
+template <int KS, bool kSigns, typename Look, typename F>
 __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const int* start,
                                             const unsigned char* lvl, double* x, int tl, int tg, int first, int last,
-                                            int step, F&& f) {
+                                            int step, Look&& look, F&& f) {
   int l = first, left = (last - first) * step;  // levels after this one
   if (tl - lane_id() >= tg) {  // waves that would rarely find a node
     do {
@@ -285,11 +287,12 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
   const auto level = [&](auto odd, const SmallNode<KS>& cur, SmallNode<KS>& next) {
     constexpr bool kOdd = decltype(odd)::value;
     const auto value = [&](const SmallNode<KS>& n) {
+      const double own = look(n.v8);
       if constexpr (kSigns) {
-        const double a = f(n.v8, n.template sum<!kOdd>(x));
+        const double a = f(n.v8, own, n.template sum<!kOdd>(x));
         return kOdd ? -a : a;
       } else {
-        return f(n.v8, n.sum_level(x, lvl, l - step));
+        return f(n.v8, own, n.sum_level(x, lvl, l - step));
       }
     };
     const uint32_t v = place(p1, e1);
@@ -475,7 +478,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
     for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
   for (int s0 = s_first; s0 < s_last; s0 += per) {
     const bool valid = s0 + sg < s_last;
-    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, [&](int v, int l) {
+    const auto init = [&](int v, int l) {
       sig[v] = l == 0 ? 1.0 : 0.0;
       if (kDemand) {
         const double d = valid ? sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)(s0 + sg)] : 0.0;
@@ -484,14 +487,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
       } else {
         coef[v] = 0.0;
       }
-    }, dsum, reached);
+    };
+    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, init, dsum, reached);
+    const auto nothing = [](uint32_t) { return 0.0; };
+    const auto own_sigma_at = [&](uint32_t v8) { return lds_at(sig, v8); };
     if (depth > 0) {
-      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, sv.ts, 1, depth, 1, [&](uint32_t, double a) {
+      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, sv.ts, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
         inexact |= a >= kTwo53;
         return a;
       });
-      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, sv.ts, depth, 1, -1, [&](uint32_t v8, double a) {
-        const double r = recip(__builtin_fabs(lds_at(sig, v8)));
+      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, sv.ts, depth, 1, -1, own_sigma_at, [&](uint32_t v8, double s, double a) {
+        const double r = recip(__builtin_fabs(s));
         return (kDemand ? lds_at(coef, v8) * r : r) + a;
       });
     }
@@ -563,8 +569,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
     long long own = 0;
     const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0,
                                  [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
+    const auto nothing = [](uint32_t) { return 0.0; };
     if (depth > 0)
-      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, sv.ts, 1, depth, 1, [&](uint32_t, double a) {
+      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, sv.ts, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
         inexact |= a >= kTwo53;
         return a;
       });

@@ -25,7 +25,8 @@ constexpr int kSmallCounters = 4;     // words per workgroup: sum of distances, 
 
 struct SmallView {
   // [N][KS] out- and in-neighbours, two per word, in link order, as 8 x id (an LDS offset that costs one addition);
-  // places past a node's last link hold the node itself, which is never one level from itself
+  // places past a node's last link hold the node itself, which is never one level from itself.  (More than
+  // 8191 nodes, single-path baseline only: the ids as they are.)
   const uint32_t* out;
   const uint32_t* in;
   double* part;             // [workgroups of the launch][N * KS * 2] link loads, in the places of `out`
@@ -35,6 +36,7 @@ struct SmallView {
   int per;                  // sources a workgroup works on at a time, tg threads each
   int tg, ts;               // multiples of 64: ts of them work on the levels
   int depth;                // deepest level of the topology
+  int qshift;               // a queue entry is node id << qshift: 3, or 0 with more than 8191 nodes
   int per_wg;               // sources per workgroup: a multiple of per, at most kSmallBatch
   int wg0;                  // first workgroup of the launch among those of the call
   int src_begin, src_count;
@@ -45,12 +47,18 @@ struct SmallView {
 // Level bytes of one source.
 __host__ __device__ inline size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
 
-// LDS of a workgroup, in this order: coef (where it is asked for) and sigma (doubles; two mask words per node in
-// their place while the search runs), node queue (8 x id in 16 bits, level by level), nodes per level, then
-// where each level starts in the queue, and cursors, level bytes.
-__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth, bool coefs) {
+// LDS of a workgroup, in this order: per-node state of its sources (kState... bytes per node and source; two mask
+// words per node in its place while a search runs), node queue (16-bit places, level by level), where each level
+// starts in the queue, cursors, level bytes.
+constexpr int kStateLoads = 16;  // coef, sigma
+constexpr int kStateSigma = 8;   // sigma
+constexpr int kStateSssp = 5;    // cost, chosen link
+__host__ __device__ inline size_t small_state_bytes(int N, int per, int state) {
+  return ((size_t)per * N * state + 7) & ~(size_t)7;
+}
+__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth, int state) {
   const size_t nq = ((size_t)N + 1) & ~(size_t)1;
-  return (size_t)per * ((size_t)N * (coefs ? 16 : 8) + nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
+  return small_state_bytes(N, per, state) + (size_t)per * (nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
 }
 
 template <typename T>
@@ -84,9 +92,9 @@ struct SmallRow {
 // their out-neighbours (two arrays in turn, so that one barrier per level is enough).  On return bit j of `seen` says
 // whether source j reaches the node, bit j of plane p is bit p of the distance.  nxt: 2 N words of LDS.
 constexpr int kSmallPlanes = 8;
-template <int kNodes>
+template <int kNodes, int kPlanes = kSmallPlanes>
 struct SmallPlanes {
-  uint32_t seen[kNodes], plane[kNodes][kSmallPlanes];
+  uint32_t seen[kNodes], plane[kNodes][kPlanes];
   // Distance from source j; kUsed: planes that are not empty.
   template <int kUsed>
   __device__ __forceinline__ unsigned distance(int k, int j) const {
@@ -96,20 +104,21 @@ struct SmallPlanes {
     return d;
   }
 };
-template <int KS, int kNodes>
+template <int KS, int kNodes, int kPlanes, bool kWide = false>
 __device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
-                                             SmallPlanes<kNodes>& out) {
+                                             SmallPlanes<kNodes, kPlanes>& out) {
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
-  SmallRow<KS> row[kNodes];
+  constexpr bool kHold = kNodes * KS <= 24;  // links in registers, or fetched again for every level
+  SmallRow<KS> row[kHold ? kNodes : 1];
   uint32_t cur[kNodes];
 #pragma unroll
   for (int k = 0; k < kNodes; ++k) {
     const int v = t + T * k;
-    if (v < N) row[k].load(sv.out, 8 * v);
+    if (kHold && v < N) row[kHold ? k : 0].load(sv.out, 8 * v);
     cur[k] = v >= s0 && v < s0 + count ? 1u << (v - s0) : 0u;
     out.seen[k] = cur[k];
 #pragma unroll
-    for (int p = 0; p < kSmallPlanes; ++p) out.plane[k][p] = 0;
+    for (int p = 0; p < kPlanes; ++p) out.plane[k][p] = 0;
   }
   for (int i = t; i < 2 * N; i += T) nxt[i] = 0;
   __syncthreads();
@@ -118,9 +127,16 @@ __device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __re
 #pragma unroll
     for (int k = 0; k < kNodes; ++k) {
       if (cur[k] != 0) {
+        SmallRow<KS>& r = row[kHold ? k : 0];
+        if (!kHold) {
+          int v = t + T * k;
+          asm volatile("" : "+v"(v));  // not kept from level to level
+          r.load(sv.out, 8 * v);
+        }
 #pragma unroll
         for (int j = 0; j < 2 * KS; ++j)
-          __hip_atomic_fetch_or(&lds_at(buf, row[k].template at<1>(j)), cur[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+          __hip_atomic_fetch_or(&lds_at(buf, kWide ? 4 * r.at(j) : r.template at<1>(j)), cur[k],
+                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
       }
     }
     __syncthreads();
@@ -132,18 +148,18 @@ __device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __re
         buf[v] = 0;
         out.seen[k] |= cur[k];
 #pragma unroll
-        for (int p = 0; p < kSmallPlanes; ++p) out.plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
+        for (int p = 0; p < kPlanes; ++p) out.plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
       }
     }
   }
 }
 
 // The same, the levels written as a byte per source and node.
-template <int KS, int kNodes>
+template <int KS, int kNodes, int kPlanes = kSmallPlanes, bool kWide = false>
 __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
                                              unsigned char* __restrict__ level) {
-  SmallPlanes<kNodes> planes;
-  small_search<KS, kNodes>(sv, nxt, s0, count, planes);
+  SmallPlanes<kNodes, kPlanes> planes;
+  small_search<KS, kNodes, kPlanes, kWide>(sv, nxt, s0, count, planes);
   const int T = (int)blockDim.x, t = (int)threadIdx.x, nl = (int)small_level_bytes(sv.N);
   const auto write = [&](auto used) {
 #pragma unroll 1
@@ -156,10 +172,11 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
       }
     }
   };
-  if (sv.depth < 32)
-    write(std::integral_constant<int, 5>{});
+  constexpr int kFew = kPlanes < 5 ? kPlanes : 5;
+  if (sv.depth < 1 << kFew)
+    write(std::integral_constant<int, kFew>{});
   else
-    write(std::integral_constant<int, kSmallPlanes>{});
+    write(std::integral_constant<int, kPlanes>{});
 }
 
 // Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
@@ -329,19 +346,16 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
 
 // Where things lie in a workgroup's LDS (small_lds_bytes), and this thread's part in it.
 struct SmallLds {
-  double *coef_all, *sig_all;  // coef_all only where coefs are asked for
   unsigned short* q_all;
   int *start_all, *at_all;
   unsigned char* lvl_all;
   int slots, nq, nl;  // level slots (two of them empty for certain), queue entries, level bytes of a source
   int sg, tl;         // which of the sources this thread's wave is on, its place among the threads of that source
-  __device__ __forceinline__ SmallLds(const SmallView& sv, double* lds, bool coefs) {
+  __device__ __forceinline__ SmallLds(const SmallView& sv, double* lds, int state) {
     slots = sv.depth + 4;
     nq = (sv.N + 1) & ~1;
     nl = (int)small_level_bytes(sv.N);
-    coef_all = lds;
-    sig_all = lds + (coefs ? sv.per * sv.N : 0);
-    q_all = reinterpret_cast<unsigned short*>(sig_all + sv.per * sv.N);
+    q_all = reinterpret_cast<unsigned short*>(lds + small_state_bytes(sv.N, sv.per, state) / 8);
     start_all = reinterpret_cast<int*>(q_all + sv.per * nq);
     at_all = start_all + sv.per * slots;
     lvl_all = reinterpret_cast<unsigned char*>(at_all + sv.per * slots);
@@ -392,7 +406,7 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
   for (int v = lds.tl; v < N; v += sv.tg) {
     const int l = lvl[v];
     if (l != kSmallUnseen)
-      q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(8 * v);
+      q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(v << sv.qshift);
   }
   __syncthreads();
   int depth = 0;
@@ -451,10 +465,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
   extern __shared__ double s_small[];
   const int T = (int)blockDim.x, t = (int)threadIdx.x;
   const int N = sv.N, per = sv.per;
-  const SmallLds lds(sv, s_small, true);
+  const SmallLds lds(sv, s_small, kStateLoads);
   const int sg = lds.sg, tl = lds.tl, nl = lds.nl;
-  double* const coef_all = lds.coef_all;
-  double* const sig_all = lds.sig_all;
+  double* const coef_all = s_small;
+  double* const sig_all = s_small + per * N;
   const unsigned char* const lvl_all = lds.lvl_all;
   double* const coef = coef_all + sg * N;
   double* const sig = sig_all + sg * N;
@@ -554,9 +568,9 @@ template <int KS, int kNodes>
 __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, SmallOut out) {
   extern __shared__ double s_small[];
   const int N = sv.N;
-  const SmallLds lds(sv, s_small, false);
+  const SmallLds lds(sv, s_small, kStateSigma);
   const int nl = lds.nl, tl = lds.tl;
-  double* const sig = lds.sig_all + lds.sg * N;
+  double* const sig = s_small + lds.sg * N;
   const unsigned char* const lvl = lds.lvl();
   unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
   long long dsum = 0, reached = 0;
@@ -606,7 +620,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dist(SmallView sv, Smal
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int count = min(sv.src_count - s_first, sv.per_wg);
   SmallPlanes<kNodes> planes;
-  small_search<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, count, planes);
+  small_search<KS, kNodes, kSmallPlanes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, count, planes);
   long long reached = 0;
 #pragma unroll
   for (int k = 0; k < kNodes; ++k)
@@ -737,6 +751,162 @@ k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_
     __syncthreads();
   }
   if (link && c == 0) load[a] = run;
+}
+
+// ---------------------------------------------------------------------------------------
+// single-path baseline (the reading is described in a2a_sssp_kernels.h)
+// ---------------------------------------------------------------------------------------
+//
+// The levels do not depend on the weights: they are found for as many iterations at once as the workspace holds.
+// An iteration then is two launches: its workgroups take a source at a time from the levels to what every
+// node hands to the link it picked, all in LDS (8 bytes per node), and a second kernel adds that up.  Weights and
+// what is handed on are kept in the places of the in-link table (node, place of the link in its in-list): a
+// node's weights are one piece of memory, in ascending link id, and every node adds to one place of its own,
+// so nothing is added atomically.
+
+template <int KS, int kNodes, int kPlanes, bool kWide>
+__global__ void __launch_bounds__(kSmallThreads) k_small_levels(SmallView sv) {
+  extern __shared__ double s_small[];
+  const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
+  small_levels<KS, kNodes, kPlanes, kWide>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first,
+                                           min(sv.src_count - s_first, sv.per_wg),
+                                           sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * small_level_bytes(sv.N));
+}
+
+struct SmallSssp {
+  uint32_t* weight;       // [N][2 KS] commodities routed so far over the in-links
+  uint32_t* handed;       // [sources of the iteration][N]: paths that end in or pass through the node, + place << 28
+};
+constexpr int kHandedShift = 28;
+
+// Sources [per_wg * workgroup, + per_wg) of an iteration; sv.level: the levels of its first source.  Costs are
+// below 2^32 - 1 (the host checks).
+template <int KS>
+__global__ void __launch_bounds__(kSmallThreads) k_small_sssp(SmallView sv, SmallSssp ss) {
+  extern __shared__ double s_small[];
+  constexpr uint32_t kNone = 0xffffffffu;
+  const int N = sv.N;
+  const SmallLds lds(sv, s_small, kStateSssp);
+  const int tl = lds.tl, nl = lds.nl;
+  uint32_t* const cost = reinterpret_cast<uint32_t*>(s_small) + lds.sg * N;
+  unsigned char* const pick = reinterpret_cast<unsigned char*>(reinterpret_cast<uint32_t*>(s_small) + sv.per * N) + lds.sg * N;
+  const unsigned short* const q = lds.q();
+  const int* const start = lds.start();
+  const unsigned char* const lvl = lds.lvl();
+  long long dsum = 0, reached = 0;
+  const int s_first = (int)blockIdx.x * sv.per_wg;
+  const int s_last = min(sv.src_count, s_first + sv.per_wg);
+  for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
+    const int s = s0 + lds.sg;
+    const int depth = small_sort(sv, lds, sv.level + (size_t)s0 * nl, s_last - s0, [&](int v, int l) {
+      if (l == 0) cost[v] = 0;
+    }, dsum, reached);
+    for (int l = 1; l <= depth; ++l) {
+      const int end = start[l + 1];
+      for (int p = start[l] + tl; p < end; p += sv.tg) {
+        const int v = q[p] >> sv.qshift;
+        SmallRow<KS> row;
+        row.load(sv.in, 8 * v);
+        uint32_t w[2 * KS];
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) w[j] = ss.weight[(size_t)v * (2 * KS) + j];
+        uint32_t c[2 * KS];
+        int m[2 * KS];
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) {
+          const int u = (int)(row.at(j) >> sv.qshift);
+          m[j] = lvl[u];
+          c[j] = cost[u];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t best = kNone;
+        int at = 0;
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) {  // ascending link id: the lowest of equals stays
+          const uint32_t x = m[j] == l - 1 ? c[j] + w[j] : kNone;
+          if (x < best) {
+            best = x;
+            at = j;
+          }
+        }
+        cost[v] = best;
+        pick[v] = (unsigned char)at;
+      }
+      __syncthreads();
+    }
+    // from here on the cost array holds the paths that end in or pass through a node
+    uint32_t* const paths = cost;
+    uint32_t* const handed = ss.handed + (size_t)s * (size_t)N;
+    for (int v = tl; v < N; v += sv.tg) {
+      paths[v] = 1;
+      if (s < s_last && (lvl[v] == 0 || lvl[v] == kSmallUnseen)) handed[v] = 0;
+    }
+    __syncthreads();
+    for (int l = depth; l >= 1; --l) {
+      const int end = start[l + 1];
+      for (int p = start[l] + tl; p < end; p += sv.tg) {
+        const int v = q[p] >> sv.qshift;
+        const uint32_t x = paths[v];
+        const int j = pick[v];
+        handed[v] = x | (uint32_t)j << kHandedShift;
+        if (l > 1) {
+          const uint32_t w = sv.in[v * KS + (j >> 1)];
+          const int u = (int)((j & 1 ? w >> 16 : w & 0xffffu) >> sv.qshift);
+          __hip_atomic_fetch_add(&paths[u], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+      }
+      __syncthreads();
+    }
+  }
+  small_totals(sv, dsum, reached, false, 0.0);
+}
+
+// weight[v][j] += what the sources of the iteration handed from node v to its in-link j.  A workgroup takes 64
+// nodes, a lane each; its waves take every 16th source, and their sums meet in LDS.
+template <int KS>
+__global__ void __launch_bounds__(kSmallThreads) k_small_sssp_add(SmallSssp ss, int N, int sources) {
+  __shared__ uint32_t s_sum[kSmallThreads / kWave][kWave];
+  const int lane = lane_id(), wave = (int)threadIdx.x / kWave, v = (int)blockIdx.x * kWave + lane;
+  constexpr int kWaves = kSmallThreads / kWave, kAhead = 8;
+  uint32_t acc[2 * KS];
+#pragma unroll
+  for (int j = 0; j < 2 * KS; ++j) acc[j] = 0;
+  if (v < N) {
+    for (int s = wave; s < sources; s += kWaves * kAhead) {
+      uint32_t x[kAhead];
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) x[k] = s + kWaves * k < sources ? ss.handed[(size_t)(s + kWaves * k) * (size_t)N + v] : 0u;
+#pragma unroll
+      for (int k = 0; k < kAhead; ++k) {
+        const uint32_t n = x[k] & ((1u << kHandedShift) - 1), at = x[k] >> kHandedShift;
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) acc[j] += at == (uint32_t)j ? n : 0u;
+      }
+    }
+  }
+  for (int j = 0; j < 2 * KS; ++j) {
+    uint32_t mine = acc[0];
+#pragma unroll
+    for (int k = 1; k < 2 * KS; ++k) mine = j == k ? acc[k] : mine;
+    s_sum[wave][lane] = mine;
+    __syncthreads();
+    if (wave == 0 && v < N) {
+      uint32_t sum = 0;
+      for (int k = 0; k < kWaves; ++k) sum += s_sum[k][lane];
+      if (sum != 0) ss.weight[(size_t)v * (2 * KS) + j] += sum;
+    }
+    __syncthreads();
+  }
+}
+
+// load of every link from its place in the in-link table.
+__global__ void __launch_bounds__(kBlock)
+k_small_sssp_output(const uint32_t* __restrict__ weight, int places, const int32_t* __restrict__ in_ptr,
+                    const int32_t* __restrict__ in_link, int N, double* __restrict__ load) {
+  const int v = (int)(blockIdx.x * kBlock + threadIdx.x) / places, j = (int)(blockIdx.x * kBlock + threadIdx.x) % places;
+  if (v >= N) return;
+  const int a = in_ptr[v] + j;
+  if (a < in_ptr[v + 1]) load[in_link[a]] = (double)weight[(size_t)v * places + j];
 }
 
 }  // namespace a2a_dev

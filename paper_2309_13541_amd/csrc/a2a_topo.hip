@@ -347,6 +347,10 @@ inline unsigned grid_for(int G, int blocks_per_batch, int inflight = kXcd) {
 // byte offsets.
 constexpr int32_t kMaxNodes = 4 * 1024 * 1024;
 
+// The link tables hold 8 x id in 16 bits up to here, and ids beyond, up to the nodes that the single-path baseline's
+// state for one source takes in LDS.
+constexpr int32_t kScaledNodes = 8191, kWideNodes = 16384;
+
 // Nominal lane layout of a level for the profile's kernel classes (the kernels pick per batch,
 // from the same rule applied to the batch's own counts).
 constexpr double kNominalRows = 8.0;
@@ -541,7 +545,7 @@ int run_fold(const Run& r, const GroupView& gv, int depth) {
 // results in `deepest_of`, pinned host memory.
 int probe_depth(const a2a_topo* t, int* deepest_of, int32_t* depth_out) {
   const int N = t->N;
-  if (t->ell_words > 0) {
+  if (t->ell_words > 0 && N <= kScaledNodes) {
     const int groups = (N + kSmallBatch - 1) / kSmallBatch;
     const unsigned threads = (unsigned)std::min<size_t>(kSmallThreads, align_up((size_t)N, kWave));
     k_small_probe<<<(unsigned)groups, threads, (size_t)N * 3 * sizeof(uint32_t), nullptr>>>(t->d_ell_out, t->ell_words, N,
@@ -607,7 +611,7 @@ constexpr int kComputeUnits = 256;
 
 // Words per node of the link tables (two links a word) for a largest in- or out-degree, 0: no tables.
 int ell_words_for(int32_t N, int32_t degree) {
-  if (N > 8191 || degree > 16 || degree < 1) return 0;  // 8 x id has 16 bits
+  if (N > kWideNodes || degree > 16 || degree < 1) return 0;
   for (int w : {2, 3, 4, 5})
     if (degree <= 2 * w) return w;
   return 8;
@@ -616,12 +620,13 @@ int ell_words_for(int32_t N, int32_t degree) {
 // Link table of a CSR: the neighbours of a node in list order, then the node itself.
 std::vector<uint32_t> make_ell(int32_t N, const int32_t* ptr, const int32_t* col, int words) {
   std::vector<uint32_t> ell((size_t)N * words);
+  const uint32_t scale = N <= kScaledNodes ? 8 : 1;
   for (int32_t u = 0; u < N && words > 0; ++u) {
     const int32_t p0 = ptr[u], deg = ptr[u + 1] - p0;
     for (int k = 0; k < words; ++k) {
       const uint32_t a = (uint32_t)(2 * k < deg ? col[p0 + 2 * k] : u);
       const uint32_t b = (uint32_t)(2 * k + 1 < deg ? col[p0 + 2 * k + 1] : u);
-      ell[(size_t)u * words + k] = 8 * a | (8 * b << 16);
+      ell[(size_t)u * words + k] = scale * a | (scale * b << 16);
     }
   }
   return ell;
@@ -639,7 +644,7 @@ int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 25
 // The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
 constexpr int small_max_nodes(int ell_words) { return ell_words == 2 ? 9 : 20 / ell_words; }
 
-enum class SmallWhat { kLoads, kSigma, kDist };
+enum class SmallWhat { kLoads, kSigma, kDist, kSssp };
 
 // How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
 // do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
@@ -648,9 +653,9 @@ enum class SmallWhat { kLoads, kSigma, kDist };
 SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   SmallPlan p;
   const int N = t->N, depth = t->level_bound;
-  const bool coefs = what == SmallWhat::kLoads;
+  const int state = what == SmallWhat::kLoads ? kStateLoads : what == SmallWhat::kSigma ? kStateSigma : kStateSssp;
   // nodes a thread may own: its registers hold the loads of their links, or the bit planes of their distances
-  const int most = coefs ? small_max_nodes(t->ell_words) : 8;
+  const int most = what == SmallWhat::kLoads ? small_max_nodes(t->ell_words) : what == SmallWhat::kSssp ? 64 : 8;
   int tg = small_threads(N), per = 1;
   if (what == SmallWhat::kDist) {
     tg = std::min(kSmallThreads, (int)align_up((size_t)N, kWave));
@@ -658,9 +663,9 @@ SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   } else {
     const int want = std::max(1, std::min(kSmallThreads / kWave, src_count / kComputeUnits));
     const int least = std::min(tg, 256);
-    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, coefs) <= kSmallLds) ++per;
+    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds) ++per;
     tg = std::min(tg, kSmallThreads / per / kWave * kWave);
-    p.lds = small_lds_bytes(N, per, depth, coefs);
+    p.lds = small_lds_bytes(N, per, depth, state);
   }
   while (N > most * per * tg) tg += kWave;
   p.T = per * tg;
@@ -674,6 +679,7 @@ SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   p.sv.N = N;
   p.sv.per = per;
   p.sv.tg = tg;
+  p.sv.qshift = N <= kScaledNodes ? 3 : 0;
   // 1.25 times an average level: most levels in one go
   p.sv.ts = std::min(tg, (int)align_up((size_t)N * 5 / 4 / (size_t)std::max(depth, 1), kWave));
   p.sv.depth = depth;
@@ -690,9 +696,9 @@ size_t small_row_bytes(const a2a_topo* t, int per_wg) {
 // Whether link loads take the one-workgroup-per-source kernel: everything fits, and so do the rows of one
 // chunk of partial loads into the smallest workspace that a caller may bring.
 bool small_loads_fit(const a2a_topo* t) {
-  return t->ell_words > 0 && t->level_bound < kSmallUnseen - 1 &&
+  return t->ell_words > 0 && t->N <= kScaledNodes && t->level_bound < kSmallUnseen - 1 &&
          t->N <= small_max_nodes(t->ell_words) * kSmallThreads &&
-         small_lds_bytes(t->N, 1, t->level_bound, true) <= kSmallLds &&
+         small_lds_bytes(t->N, 1, t->level_bound, kStateLoads) <= kSmallLds &&
          256 + kSmallChunk * small_row_bytes(t, kSmallBatch) <= t->min_loads_bytes;
 }
 
@@ -766,8 +772,8 @@ void small_launch_out_words(const SmallPlan& p, const SmallOut& out, int workgro
 // Whether distances (and path counts) take the small kernels: their level bytes and counters fit the smallest
 // workspace that a caller may bring, for one workgroup at least.
 bool small_distances_fit(const a2a_topo* t, bool sigma) {
-  return t->ell_words > 0 && t->level_bound < kSmallUnseen - 1 &&
-         small_lds_bytes(t->N, 1, t->level_bound, false) <= kSmallLds &&
+  return t->ell_words > 0 && t->N <= kScaledNodes && t->level_bound < kSmallUnseen - 1 &&
+         small_lds_bytes(t->N, 1, t->level_bound, kStateSigma) <= kSmallLds &&
          256 + kSmallBatch * small_level_bytes(t->N) + kSmallCounters * sizeof(long long) <=
              (sigma ? t->min_sigma_bytes : t->min_dist_bytes);
 }
@@ -797,6 +803,96 @@ int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
     k_small_reduce<<<1, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
                                          t->d_out_ptr, nullptr, (long long*)ws, tot);
   }
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
+// Whether a call of the single-path baseline takes the small kernels: its state for one source fits LDS, levels fit a
+// byte (and, with more than 8191 nodes, the search's four bit planes), and no cost can reach 2^32 - 1 (a link
+// carries at most every commodity of the call).
+bool small_sssp_fits(const a2a_topo* t, int32_t src_count) {
+  return t->ell_words > 0 && t->level_bound < (t->N <= kScaledNodes ? kSmallUnseen - 1 : 16) &&
+         small_lds_bytes(t->N, 1, t->level_bound, kStateSssp) <= kSmallLds &&
+         (double)t->level_bound * src_count * (t->N - 1) < 4294967295.0;
+}
+
+template <int KS>
+void small_sssp_launch_levels(const SmallPlan& p, int workgroups, hipStream_t st) {
+  const int nodes = (p.sv.N + kSmallThreads - 1) / kSmallThreads;
+  const size_t lds = (size_t)p.sv.N * 8;
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kSmallThreads, lds, st>>>(p.sv); };
+  if (p.sv.N > kScaledNodes)
+    launch(k_small_levels<KS, 16, 4, true>);
+  else if (nodes <= 2)
+    launch(k_small_levels<KS, 2, kSmallPlanes, false>);
+  else
+    launch(k_small_levels<KS, 8, kSmallPlanes, false>);
+}
+
+template <int KS>
+void small_sssp_launch(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
+  k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
+  k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
+}
+
+#define SMALL_BY_WORDS(call)       \
+  switch (t->ell_words) {          \
+    case 2: call(2); break;        \
+    case 3: call(3); break;        \
+    case 4: call(4); break;        \
+    case 5: call(5); break;        \
+    default: call(8); break;       \
+  }
+
+// ws: at least what a2a_workspace_bytes says for the iteration (with dense rows of 1 KB per batch and node, far
+// more than one iteration takes here).
+int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t per_iter, double* load,
+               int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
+  const int places = 2 * t->ell_words;
+  const int iterations = (src_count + per_iter - 1) / per_iter;
+  const SmallPlan whole = small_plan(t, std::min(per_iter, src_count), SmallWhat::kSssp);
+  size_t off = 256;
+  const auto part = [&off](size_t bytes) {
+    const size_t at = off;
+    off += align_up(bytes, 256);
+    return at;
+  };
+  SmallSssp ss;
+  ss.weight = (uint32_t*)(ws + part((size_t)t->N * places * 4));
+  ss.handed = (uint32_t*)(ws + part((size_t)per_iter * t->N * 4));
+  long long* const counters = (long long*)(ws + part((size_t)src_count * kSmallCounters * 8));  // at most one workgroup per source
+  unsigned char* const level = (unsigned char*)(ws + off);
+  // iterations whose levels fit what is left
+  const size_t level_bytes = small_level_bytes(t->N);
+  const long long room = off < ws_bytes ? (long long)((ws_bytes - off) / (level_bytes * per_iter)) : 0;
+  if (room < 1) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  HIP_TRY(zero_async(ss.weight, (size_t)t->N * places * 4, st));
+  int rows = 0;
+  for (int i0 = 0; i0 < iterations; i0 += (int)room) {
+    const int i1 = (int)std::min<long long>(iterations, i0 + room);
+    SmallPlan lp = whole;
+    lp.sv.src_begin = src_begin + i0 * per_iter;
+    lp.sv.src_count = std::min(src_count, i1 * per_iter) - i0 * per_iter;
+    lp.sv.per_wg = kSmallBatch;
+    lp.sv.level = level;
+    const int groups = (lp.sv.src_count + kSmallBatch - 1) / kSmallBatch;
+#define SMALL_LEVELS(KS) small_sssp_launch_levels<KS>(lp, groups, st)
+    SMALL_BY_WORDS(SMALL_LEVELS)
+    for (int i = i0; i < i1; ++i) {
+      SmallPlan p = small_plan(t, std::min(per_iter, src_count - i * per_iter), SmallWhat::kSssp);
+      p.sv.level = level + (size_t)(i - i0) * per_iter * level_bytes;
+      p.sv.counters = counters + (size_t)rows * kSmallCounters;
+      rows += p.workgroups;
+#define SMALL_ITERATION(KS) small_sssp_launch<KS>(p, ss, st)
+      SMALL_BY_WORDS(SMALL_ITERATION)
+    }
+  }
+  k_small_sssp_output<<<(unsigned)(((size_t)t->N * places + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+      ss.weight, places, t->d_in_ptr, t->d_in_link, t->N, load);
+  SmallView sv = whole.sv;
+  sv.counters = counters;
+  const SmallTotals tot{(long long)src_count * (t->N - 1), (long long*)dist_sum_total, nullptr, (long long*)flags, nullptr};
+  k_small_reduce<<<1, kBlock, 0, st>>>(sv, t->ell_words, rows, 1, 1, t->d_out_ptr, nullptr, (long long*)ws, tot);
   HIP_TRY(hipGetLastError());
   return A2A_OK;
 }
@@ -1161,6 +1257,9 @@ int a2a_sssp_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   r.t = t;
   r.L = make_layout(t, per_iter * 64, A2A_WS_SSSP, workspace_bytes, false, false);
   if (r.L.G < per_iter) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  if (t->E > 0 && t->prof_mode == 0 && small_sssp_fits(t, src_count))
+    return small_sssp(t, src_begin, src_count, std::min(per_iter * 64, src_count), load, dist_sum_total, flags,
+                      (char*)workspace, workspace_bytes, st);
   r.ws = (char*)workspace;
   r.st = st;
   r.src_begin = src_begin;

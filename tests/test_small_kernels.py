@@ -104,3 +104,24 @@ def test_distances_and_path_counts(a2a, oracle, name, shape, s0, cnt):
     _, _, dsum, unr, _ = run_distances(topo, s0, cnt, want_sigma=False, want_dist=False)
     assert np.array_equal(dsum, o.dist_sum) and unr == o.unreachable
     topo.close()
+
+
+SSSP = [(f"{n} nodes, degree {d}, {cnt} sources, {k} per iteration", (n, d), s0, cnt, k) for n, d, s0, cnt, k in (
+    (64, 3, 0, 64, 64), (700, 5, 3, 690, 256), (1024, 10, 0, 1024, 512), (2050, 8, 0, 2050, 1024), (3000, 16, 5, 600, 64),
+    # ids instead of scaled places; most nodes whose state fits; one node over; too many links
+    (8191, 3, 0, 200, 128), (8192, 3, 0, 200, 128), (16384, 4, 100, 300, 128), (16384, 10, 0, 70, 64), (16385, 3, 0, 70, 64),
+    (900, 17, 0, 130, 64))]
+
+
+@pytest.mark.parametrize("name,shape,s0,cnt,k", SSSP, ids=[e[0] for e in SSSP])
+def test_single_path_baseline(a2a, oracle, name, shape, s0, cnt, k):
+    from test_sssp import run_sssp_gpu
+    rp, col = gen.random_regular(*shape, 6)
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    want, dsum, unr = oracle.sssp(rp, col, s0, cnt, iter_sources=k)
+    for extra in (0, 1 << 20):
+        load, got_sum, flags = run_sssp_gpu(topo, s0, cnt, iter_sources=k, extra_ws=extra)
+        assert np.array_equal(load, want.astype(np.float64))
+        assert got_sum == int(dsum.sum()) and flags == (a2a.FLAG_UNREACHABLE if unr else 0)
+    topo.close()

@@ -20,6 +20,7 @@ namespace a2a_dev {
 constexpr int kSmallThreads = 1024;   // largest workgroup
 constexpr int kSmallUnseen = 255;     // level byte of a node not reached; levels go up to 253
 constexpr int kSmallBatch = 32;       // most sources of a workgroup: they search together, a bit of a word each
+constexpr int kSmallStripes = 16;     // most nodes a thread sorts with their ranks in registers
 constexpr int kSmallChunk = 16;       // partial load rows that are added up before they meet the running sum
 constexpr int kSmallCounters = 4;     // words per workgroup: sum of distances, reached pairs, inexact, demand x distance
 
@@ -56,9 +57,13 @@ constexpr int kStateSssp = 5;    // cost, chosen link
 __host__ __device__ inline size_t small_state_bytes(int N, int per, int state) {
   return ((size_t)per * N * state + 7) & ~(size_t)7;
 }
+// Counters per level that the sort of a source's nodes works with: lanes that count the same word wait for each other
+// (64 of them 150 cycles), and few levels mean full ones, so they are spread over groups of eight lanes there.
+__host__ __device__ inline int small_spread(int depth) { return depth < 16 ? 8 : 1; }
 __host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth, int state) {
   const size_t nq = ((size_t)N + 1) & ~(size_t)1;
-  return small_state_bytes(N, per, state) + (size_t)per * (nq * 2 + (size_t)(depth + 4) * 8 + small_level_bytes(N));
+  return small_state_bytes(N, per, state) +
+         (size_t)per * (nq * 2 + (size_t)(depth + 4) * 4 * (1 + small_spread(depth)) + small_level_bytes(N));
 }
 
 template <typename T>
@@ -358,7 +363,7 @@ struct SmallLds {
     q_all = reinterpret_cast<unsigned short*>(lds + small_state_bytes(sv.N, sv.per, state) / 8);
     start_all = reinterpret_cast<int*>(q_all + sv.per * nq);
     at_all = start_all + sv.per * slots;
-    lvl_all = reinterpret_cast<unsigned char*>(at_all + sv.per * slots);
+    lvl_all = reinterpret_cast<unsigned char*>(at_all + sv.per * slots * small_spread(sv.depth));
     sg = __builtin_amdgcn_readfirstlane((int)threadIdx.x / sv.tg);
     tl = (int)threadIdx.x - sg * sv.tg;
   }
@@ -369,33 +374,54 @@ struct SmallLds {
 
 // Takes the levels of the next `left` sources (up to sv.per of them) from `level` and sorts their nodes by level into
 // the queues; init(v, level) is called once per node.  Adds up distances and reached nodes.  Returns the deepest
-// level of these sources, the same in all threads.
-template <typename Init>
+// level of these sources, the same in all threads.  kRanks: the counting pass keeps what its atomics return, so that
+// the placing pass needs none (30k -> 20k cycles at 16384 nodes); for kernels with registers to spare and at most
+// kSmallStripes nodes a thread.
+template <bool kRanks, typename Init>
 __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& lds, const unsigned char* __restrict__ level,
                                           int left, Init&& init, long long& dsum, long long& reached) {
   const int T = (int)blockDim.x, t = (int)threadIdx.x, lane = lane_id();
-  const int N = sv.N, per = sv.per, slots = lds.slots;
+  const int N = sv.N, per = sv.per, slots = lds.slots, spread = small_spread(sv.depth);
   int* const start = lds.start();
-  int* const at = lds.at_all + lds.sg * slots;
+  int* const at = lds.at_all + lds.sg * slots * spread;
   const unsigned char* const lvl = lds.lvl();
   unsigned short* const q = lds.q();
-  for (int i = t; i < per * slots; i += T) lds.start_all[i] = 0;
+  for (int i = t; i < per * slots * spread; i += T) lds.at_all[i] = 0;
   const int here = min(per, left) * (lds.nl / 4);
   for (int i = t; i < per * (lds.nl / 4); i += T)
     reinterpret_cast<uint32_t*>(lds.lvl_all)[i] = i < here ? reinterpret_cast<const uint32_t*>(level)[i] : 0xffffffffu;
   __syncthreads();
-  for (int v = lds.tl; v < N; v += sv.tg) {
-    const int l = lvl[v];
-    if (l != kSmallUnseen) __hip_atomic_fetch_add(&start[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    init(v, l);
+  int* const mine = at + (spread > 1 ? lane >> 3 : 0);
+  const auto count = [&](int l) {
+    return __hip_atomic_fetch_add(&mine[l * spread], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  int rank[kSmallStripes];  // of this thread's nodes among those with the same counter
+  if (kRanks) {
+#pragma unroll
+    for (int k = 0; k < kSmallStripes; ++k) {
+      if (k * sv.tg >= N) break;  // the same in all threads
+      const int v = lds.tl + k * sv.tg;
+      const int l = v < N ? lvl[v] : kSmallUnseen;
+      if (l != kSmallUnseen) rank[k] = count(l);
+      if (v < N) init(v, l);
+    }
+  } else {
+    for (int v = lds.tl; v < N; v += sv.tg) {
+      const int l = lvl[v];
+      if (l != kSmallUnseen) count(l);
+      init(v, l);
+    }
   }
   __syncthreads();
   if (lds.tl < kWave) {
     int carry = 0;
-    for (int l0 = 0; l0 < slots; l0 += kWave) {
-      const int l = l0 + lane, c = l < slots ? start[l] : 0;
+    for (int i0 = 0; i0 < slots * spread; i0 += kWave) {
+      const int i = i0 + lane, c = i < slots * spread ? at[i] : 0, l = spread > 1 ? i >> 3 : i;
       const int incl = wave_scan_incl(c, lane);
-      if (l < slots) start[l] = at[l] = carry + incl - c;
+      if (i < slots * spread) {
+        at[i] = carry + incl - c;
+        if (spread == 1 || (i & 7) == 0) start[l] = carry + incl - c;
+      }
       carry += __builtin_amdgcn_readlane(incl, kWave - 1);
       dsum += (long long)c * l;
       reached += l > 0 ? c : 0;
@@ -403,10 +429,19 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
     if (carry == 0 && lane == 0) q[0] = 0;  // no source: the sweeps look at an entry all the same
   }
   __syncthreads();
-  for (int v = lds.tl; v < N; v += sv.tg) {
-    const int l = lvl[v];
-    if (l != kSmallUnseen)
-      q[__hip_atomic_fetch_add(&at[l], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)] = (unsigned short)(v << sv.qshift);
+  if (kRanks) {
+#pragma unroll
+    for (int k = 0; k < kSmallStripes; ++k) {
+      if (k * sv.tg >= N) break;
+      const int v = lds.tl + k * sv.tg;
+      const int l = v < N ? lvl[v] : kSmallUnseen;
+      if (l != kSmallUnseen) q[mine[l * spread] + rank[k]] = (unsigned short)(v << sv.qshift);
+    }
+  } else {
+    for (int v = lds.tl; v < N; v += sv.tg) {
+      const int l = lvl[v];
+      if (l != kSmallUnseen) q[count(l)] = (unsigned short)(v << sv.qshift);
+    }
   }
   __syncthreads();
   int depth = 0;
@@ -502,7 +537,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
         coef[v] = 0.0;
       }
     };
-    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, init, dsum, reached);
+    const int depth = small_sort<false>(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, init, dsum, reached);
     const auto nothing = [](uint32_t) { return 0.0; };
     const auto own_sigma_at = [&](uint32_t v8) { return lds_at(sig, v8); };
     if (depth > 0) {
@@ -581,7 +616,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
   __syncthreads();
   for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
     long long own = 0;
-    const int depth = small_sort(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0,
+    const int depth = small_sort<false>(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0,
                                  [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
     const auto nothing = [](uint32_t) { return 0.0; };
     if (depth > 0)
@@ -798,7 +833,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sssp(SmallView sv, Smal
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
   for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
     const int s = s0 + lds.sg;
-    const int depth = small_sort(sv, lds, sv.level + (size_t)s0 * nl, s_last - s0, [&](int v, int l) {
+    const int depth = small_sort<true>(sv, lds, sv.level + (size_t)s0 * nl, s_last - s0, [&](int v, int l) {
       if (l == 0) cost[v] = 0;
     }, dsum, reached);
     for (int l = 1; l <= depth; ++l) {

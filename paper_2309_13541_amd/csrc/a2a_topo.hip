@@ -663,8 +663,12 @@ SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   } else {
     const int want = std::max(1, std::min(kSmallThreads / kWave, src_count / kComputeUnits));
     const int least = std::min(tg, 256);
-    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds) ++per;
+    const int stripes = what == SmallWhat::kSssp ? kSmallStripes : N;  // nodes a thread of a source may sort
+    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds &&
+           N <= stripes * (kSmallThreads / (per + 1) / kWave * kWave))
+      ++per;
     tg = std::min(tg, kSmallThreads / per / kWave * kWave);
+    while (N > stripes * tg) tg += kWave;
     p.lds = small_lds_bytes(N, per, depth, state);
   }
   while (N > most * per * tg) tg += kWave;

@@ -26,6 +26,7 @@
 
 #include "a2a_kernels.h"
 #include "a2a_small_kernels.h"
+#include "a2a_wide_kernels.h"
 #include "a2a_sssp_kernels.h"
 #include "a2a_topo.h"
 
@@ -68,7 +69,7 @@ struct a2a_topo {
   // node, 0 if there are none; which calls use them; smallest workspaces of the calls.
   uint32_t *d_ell_out = nullptr, *d_ell_in = nullptr;
   int ell_words = 0;
-  bool small_loads = false, small_sigma = false, small_dist = false;
+  bool small_loads = false, small_sigma = false, small_dist = false, wide_dist = false;
   size_t min_loads_bytes = 0, min_sigma_bytes = 0, min_dist_bytes = 0;
   void* d_scratch = nullptr;    // device address of `scratch` on the handle's GPU
   // optional per-kernel timing (a2a_profile_enable); events are created per launch while it is on
@@ -349,7 +350,7 @@ constexpr int32_t kMaxNodes = 4 * 1024 * 1024;
 
 // The link tables hold 8 x id in 16 bits up to here, and ids beyond, up to the nodes that the single-path baseline's
 // state for one source takes in LDS.
-constexpr int32_t kScaledNodes = 8191, kWideNodes = 16384;
+constexpr int32_t kScaledNodes = 8191, kBothTables = 16384;
 
 // Nominal lane layout of a level for the profile's kernel classes (the kernels pick per batch,
 // from the same rule applied to the batch's own counts).
@@ -611,15 +612,16 @@ constexpr int kComputeUnits = 256;
 
 // Words per node of the link tables (two links a word) for a largest in- or out-degree, 0: no tables.
 int ell_words_for(int32_t N, int32_t degree) {
-  if (N > kWideNodes || degree > 16 || degree < 1) return 0;
+  if (N > kWideMost || degree > 16 || degree < 1) return 0;
   for (int w : {2, 3, 4, 5})
     if (degree <= 2 * w) return w;
   return 8;
 }
 
-// Link table of a CSR: the neighbours of a node in list order, then the node itself.
-std::vector<uint32_t> make_ell(int32_t N, const int32_t* ptr, const int32_t* col, int words) {
-  std::vector<uint32_t> ell((size_t)N * words);
+// Link table of a CSR: the neighbours of a node in list order, then the node itself.  `rows` >= N: rows past the last
+// node are zero (the wide search reads whole slots).
+std::vector<uint32_t> make_ell(int32_t N, const int32_t* ptr, const int32_t* col, int words, size_t rows) {
+  std::vector<uint32_t> ell(rows * words);
   const uint32_t scale = N <= kScaledNodes ? 8 : 1;
   for (int32_t u = 0; u < N && words > 0; ++u) {
     const int32_t p0 = ptr[u], deg = ptr[u + 1] - p0;
@@ -811,11 +813,72 @@ int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
   return A2A_OK;
 }
 
+// Whether distances take the wide search: link table there, levels few enough.
+bool wide_distances_fit(const a2a_topo* t) {
+  return t->ell_words > 0 && t->N > kScaledNodes && t->level_bound < kWideDepth;
+}
+
+template <int W, int KS>
+void wide_launch_words(const WideView& wv, int workgroups, size_t lds, hipStream_t st) {
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
+  if (wv.depth < 8)
+    launch(k_wide_dist<W, KS, 3>);
+  else
+    launch(k_wide_dist<W, KS, 6>);
+}
+template <int W>
+void wide_launch(const WideView& wv, int ell_words, int workgroups, hipStream_t st) {
+  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+  switch (ell_words) {
+    case 2: return wide_launch_words<W, 2>(wv, workgroups, lds, st);
+    case 3: return wide_launch_words<W, 3>(wv, workgroups, lds, st);
+    case 4: return wide_launch_words<W, 4>(wv, workgroups, lds, st);
+    case 5: return wide_launch_words<W, 5>(wv, workgroups, lds, st);
+    default: return wide_launch_words<W, 8>(wv, workgroups, lds, st);
+  }
+}
+
+int wide_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t* dist, int64_t* dist_sum,
+                   int64_t* unreachable, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
+  if (ws_bytes < t->min_dist_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  // sources per workgroup: as few as the fewest rounds over the chip allow (a level takes the same time)
+  int W = 16;
+  const auto rounds = [&](int w) { return ((src_count + w - 1) / w + kComputeUnits - 1) / kComputeUnits; };
+  for (int w = 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
+    if (rounds(w) < rounds(W)) W = w;
+  WideView wv;
+  wv.in = t->d_ell_in;
+  wv.N = t->N;
+  wv.depth = t->level_bound;
+  wv.src_begin = src_begin;
+  wv.src_count = src_count;
+  wv.dist = dist;
+  wv.sums = (long long*)dist_sum;
+  wv.slots = W == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads) : (t->N + kWideThreads - 1) / kWideThreads * (W / 32);
+  const size_t masks = (size_t)(wv.depth / 2 + 1) * wv.slots * kWideThreads * sizeof(uint32_t);
+  const size_t room = (ws_bytes - 256) / (masks + kSmallCounters * sizeof(long long));  // at least one
+  const int workgroups = (int)std::min<size_t>({(size_t)(src_count + W - 1) / W, (size_t)kComputeUnits, room});
+  wv.counters = (long long*)(ws + 256);
+  wv.masks = (uint32_t*)(wv.counters + (size_t)workgroups * kSmallCounters);
+  switch (W) {
+    case 16: wide_launch<16>(wv, t->ell_words, workgroups, st); break;
+    case 32: wide_launch<32>(wv, t->ell_words, workgroups, st); break;
+    default: wide_launch<64>(wv, t->ell_words, workgroups, st); break;
+  }
+  SmallView sv{};
+  sv.N = t->N;
+  sv.counters = wv.counters;
+  const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
+  k_small_reduce<<<1, kBlock, 0, st>>>(sv, t->ell_words, workgroups, 1, 1, t->d_out_ptr, nullptr, (long long*)ws, tot);
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
 // Whether a call of the single-path baseline takes the small kernels: its state for one source fits LDS, levels fit a
 // byte (and, with more than 8191 nodes, the search's four bit planes), and no cost can reach 2^32 - 1 (a link
 // carries at most every commodity of the call).
 bool small_sssp_fits(const a2a_topo* t, int32_t src_count) {
-  return t->ell_words > 0 && t->level_bound < (t->N <= kScaledNodes ? kSmallUnseen - 1 : 16) &&
+  return t->ell_words > 0 && t->N <= kBothTables && t->level_bound < (t->N <= kScaledNodes ? kSmallUnseen - 1 : 16) &&
          small_lds_bytes(t->N, 1, t->level_bound, kStateSssp) <= kSmallLds &&
          (double)t->level_bound * src_count * (t->N - 1) < 4294967295.0;
 }
@@ -967,8 +1030,9 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
       }
     for (int32_t v = 0; v < N; ++v) t->dmax_in = std::max(t->dmax_in, in_ptr[(size_t)v + 1] - in_ptr[v]);
     t->ell_words = ell_words_for(N, std::max(dmax, t->dmax_in));
-    ell_out = make_ell(N, row_ptr, col_idx, t->ell_words);
-    ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words);
+    if (N <= kBothTables) ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
+    ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words,
+                      N <= kScaledNodes ? N : align_up((size_t)N, 2 * kWideThreads));
   } catch (const std::bad_alloc&) {
     delete t;
     return A2A_ERR_NO_MEMORY;
@@ -985,9 +1049,9 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     return at;
   };
   const size_t pb = ((size_t)N + 1) * sizeof(int32_t), cb = (size_t)(E > 0 ? E : 1) * sizeof(int32_t);
-  const size_t eb = ell_out.size() * sizeof(uint32_t);
+  const size_t eb_out = ell_out.size() * sizeof(uint32_t), eb_in = ell_in.size() * sizeof(uint32_t);
   const size_t o_out_ptr = part(pb), o_out_col = part(cb), o_in_ptr = part(pb), o_in_col = part(cb);
-  const size_t o_in_link = part(cb), o_ell_out = part(eb), o_ell_in = part(eb);
+  const size_t o_in_link = part(cb), o_ell_out = part(eb_out), o_ell_in = part(eb_in);
   const size_t o_arrived = part(a2a_topo::kSlots * sizeof(unsigned));
   const size_t upload = off;
   const size_t o_scratch = part((size_t)a2a_topo::kSlots * kExtremaGroups * kExtremaWords * sizeof(long long));
@@ -1014,10 +1078,8 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     std::memcpy(h + o_in_ptr, in_ptr.data(), pb);
     std::memcpy(h + o_in_col, in_col.data(), cb);
     std::memcpy(h + o_in_link, in_link.data(), cb);
-    if (eb > 0) {
-      std::memcpy(h + o_ell_out, ell_out.data(), eb);
-      std::memcpy(h + o_ell_in, ell_in.data(), eb);
-    }
+    if (eb_out > 0) std::memcpy(h + o_ell_out, ell_out.data(), eb_out);
+    if (eb_in > 0) std::memcpy(h + o_ell_in, ell_in.data(), eb_in);
     std::memset(h + o_arrived, 0, a2a_topo::kSlots * sizeof(unsigned));
     ok = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, nullptr) == hipSuccess;
   }
@@ -1030,6 +1092,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     t->small_loads = small_loads_fit(t);
     t->small_sigma = small_distances_fit(t, true);
     t->small_dist = small_distances_fit(t, false);
+    t->wide_dist = wide_distances_fit(t);
   }
   if (!ok) {
     (void)hipGetLastError();
@@ -1080,6 +1143,8 @@ int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32
   if ((sigma ? t->small_sigma : t->small_dist) && t->prof_mode == 0)
     return small_distances(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
                            (char*)workspace, workspace_bytes, st);
+  if (!sigma && t->wide_dist && t->prof_mode == 0)
+    return wide_distances(t, src_begin, src_count, dist, dist_sum, unreachable, flags, (char*)workspace, workspace_bytes, st);
   Run r;
   r.t = t;
   r.L = make_layout(t, src_count, sigma ? A2A_WS_SIGMA : A2A_WS_DISTANCES, workspace_bytes, false, false);

@@ -1,0 +1,342 @@
+// Distances of topologies with 8192 to 65536 nodes (a2a_distances without path counts).  Included once, by
+// a2a_topo.hip, after a2a_small_kernels.h.
+//
+// The level kernels search from 512 sources at a time with the masks in memory: every level of every source reads a
+// mask per link through the L2, whatever its frontier holds, and the rate of that is the copy rate (6.5 of 11.9 ms
+// for 65536 nodes of degree 8).  Here a workgroup searches from 16, 32 or 64 sources with the frontier of a whole
+// topology in LDS (a bit per node and source, 128 KB at the most): the reads per link stay in the compute unit.
+// Bound by those reads (7.2 cycles per 64 of them; 5.5 is what LDS gives for random words) and by the stores of the
+// matrix.  Whole matrix, before and after: 65536 nodes of degree 8 12.36 -> 4.16 ms (4.1 TB/s of stores), 20011 of
+// degree 5 1.30 -> 0.56 ms, 16384 of degree 4 0.67 -> 0.27 ms, torus 25x25x26 2.10 -> 0.65 ms; sums alone of 65536
+// nodes 8.38 -> 3.6 ms.
+#pragma once
+
+#include <utility>
+
+#include "a2a_small_kernels.h"
+
+namespace a2a_dev {
+
+constexpr int kWideThreads = 1024;
+constexpr int kWideSlots = 32;      // words of masks per thread
+constexpr int kWideMost = 65536;    // nodes, with 16 sources a word
+constexpr int kWideDepth = 64;      // levels are below this
+
+struct WideView {
+  const uint32_t* in;   // [rows][KS] in-links, two 16-bit ids a word; rows: N rounded up to whole slots
+  uint32_t* masks;      // [workgroups][depth / 2 + 1][slots][kWideThreads]
+  long long* counters;  // [workgroups][kSmallCounters]
+  int32_t* dist;        // [src_count][N], may be null
+  long long* sums;      // [src_count], may be null
+  int N, depth, src_begin, src_count;
+  int slots;            // words of masks per thread that hold nodes, at most kWideSlots
+};
+
+// Masks of W sources: which part of a thread's slots a node has.  A slot is a 32-bit word: two nodes (W = 16),
+// one (32) or half of one (64).
+typedef int Int4 __attribute__((ext_vector_type(4), aligned(4)));
+template <int W>
+struct WideWord;
+template <>
+struct WideWord<16> {
+  using type = uint16_t;
+};
+template <>
+struct WideWord<32> {
+  using type = uint32_t;
+};
+template <>
+struct WideWord<64> {
+  using type = uint64_t;
+};
+
+__device__ __forceinline__ uint4 wide_or(const uint4& a, const uint4& b) {
+  return make_uint4(a.x | b.x, a.y | b.y, a.z | b.z, a.w | b.w);
+}
+
+__device__ __forceinline__ uint4 wide_xnor(const uint4& a, const uint4& b) {
+  return make_uint4(~(a.x ^ b.x), ~(a.y ^ b.y), ~(a.z ^ b.z), ~(a.w ^ b.w));
+}
+
+// Bit planes to packed numbers: before, bit b of plane[p] is bit p of number b; after, number b is the kBits bits at
+// b / kBits * kBits of plane[b % kBits].  log2(kBits) exchanges of half the bits between pairs of planes: half an
+// instruction per number and stage.
+template <int kBits>
+__device__ __forceinline__ void wide_unpack(uint4 (&plane)[kBits]) {
+#pragma unroll
+  for (int s = 1; s < kBits; s *= 2) {
+    const uint32_t low = s == 1 ? 0x55555555u : s == 2 ? 0x33333333u : 0x0f0f0f0fu;  // bits that stay in the lower plane
+#pragma unroll
+    for (int p = 0; p < kBits; ++p) {
+      if (p & s) continue;
+      const uint4 a = plane[p], b = plane[p + s];
+      const auto lower = [&](uint32_t x, uint32_t y) { return (x & low) | ((y << s) & ~low); };
+      const auto upper = [&](uint32_t x, uint32_t y) { return ((x >> s) & low) | (y & ~low); };
+      plane[p] = make_uint4(lower(a.x, b.x), lower(a.y, b.y), lower(a.z, b.z), lower(a.w, b.w));
+      plane[p + s] = make_uint4(upper(a.x, b.x), upper(a.y, b.y), upper(a.z, b.z), upper(a.w, b.w));
+    }
+  }
+}
+
+// f(0), f(1), ... in straight code.
+template <typename F, size_t... I>
+__device__ __forceinline__ void wide_steps(F&& f, std::index_sequence<I...>) {
+  (f(std::integral_constant<int, (int)I>{}), ...);
+}
+
+// A workgroup takes groups of W sources, blockIdx.x, + gridDim.x, ...  Search: R_l = what a source reaches within l
+// links; LDS holds R_{l-1} of all nodes, a thread R of its own (every 1024th node) and in a level ORs in the words of
+// the in-neighbours.  Bit k of a distance d counts the l < d with l + 1 divisible by 2^k, so that bit plane k is the
+// parity of the complements of those R_l: plane 0 is kept in registers, the others come from the R_l of the odd levels,
+// which go to memory.  Then a lane takes the words of four adjacent nodes, unpacks them into distances and writes a row
+// per source.  kPlanes: bits of a level.
+template <int W, int KS, int kPlanes>
+__global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
+  using Word = typename WideWord<W>::type;
+  constexpr int kPerStep = W == 16 ? 2 : 1;                    // nodes a thread takes at a time
+  constexpr int kWords = W == 64 ? 2 : 1;                      // slots they have
+  constexpr int kSteps = kWideSlots / kWords;
+  constexpr int kStride = kPerStep * kWideThreads;             // nodes per step of the workgroup
+  constexpr int kLanes = W == 16 ? 16 : 32;                    // sources of a slot
+  constexpr int kBits = kPlanes == 3 ? 4 : 8;                  // of a distance as it is unpacked: all set stands for -1
+  constexpr auto kEach = std::make_index_sequence<kSteps>{};
+  extern __shared__ double s_small[];
+  Word* const front = reinterpret_cast<Word*>(s_small);
+  __shared__ int s_more;
+  __shared__ int s_sum[W];
+  const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave), N = wv.N;
+  const int last = (N - 1) / kStride;  // step
+  const size_t level_words = (size_t)wv.slots * kWideThreads;
+  // R_1, R_3, ..., then R of the deepest level; plane 0 takes the place of the frontier
+  uint32_t* const kept = wv.masks + (size_t)blockIdx.x * (wv.depth / 2 + 1) * level_words;
+  uint32_t* const kept_last = kept + (size_t)(wv.depth / 2) * level_words;
+  uint32_t* const plane0 = reinterpret_cast<uint32_t*>(s_small);
+  const auto source_bits = [](int v, int s0) -> Word {
+    return (unsigned)(v - s0) < W ? (Word)((Word)1 << (v - s0)) : (Word)0;
+  };
+  long long reached = 0;
+  const int groups = (wv.src_count + W - 1) / W;
+  // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
+  // time (5.5 ms instead of 4.2 for 65536 nodes).  The first start is spread over about the length of a search.
+  if (wv.dist != nullptr && groups > 2 * (int)gridDim.x)
+    for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
+  for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
+    const int s_first = g * W, count = min(W, wv.src_count - s_first), s0 = wv.src_begin + s_first;
+    const Word none = count == W ? (Word)0 : (Word)(~(Word)0 << count);  // bits without a source: taken for reached
+    uint32_t r[kWideSlots], even[kWideSlots];
+    // conditions and addresses of the steps are worked out where they are used, not kept in registers
+    int end = last, own = t;
+    asm volatile("" : "+s"(end), "+v"(own));
+    wide_steps([&](auto step) {
+      constexpr int i = decltype(step)::value;
+      const int v = i * kStride + own;
+      const auto init = [&](int u) -> Word { return u < N ? (Word)(none | source_bits(u, s0)) : (Word)~(Word)0; };
+      const Word x = init(v);
+      if constexpr (W == 16) {
+        const Word y = init(v + kWideThreads);
+        r[i] = (uint32_t)x | (uint32_t)y << 16;
+        if (i <= end) front[v + kWideThreads] = y;
+      } else if constexpr (W == 32) {
+        r[i] = x;
+      } else {
+        r[2 * i] = (uint32_t)x;
+        r[2 * i + 1] = (uint32_t)((uint64_t)x >> 32);
+      }
+      if (i <= end) front[v] = x;
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) even[i * kWords + w] = 0;
+    }, kEach);
+    if (t == 0) s_more = 0;
+    if (t < W) s_sum[t] = 0;
+    __syncthreads();
+
+    int deep = wv.depth;
+    for (int l = 1; l <= wv.depth; ++l) {
+      asm volatile("" : "+s"(end), "+v"(own));
+      uint32_t row[2][kPerStep][KS];
+      const auto fetch = [&](uint32_t (&x)[kPerStep][KS], int i) {
+#pragma unroll
+        for (int n = 0; n < kPerStep; ++n) {
+          const uint32_t* const p = wv.in + (i * kStride + n * kWideThreads) * KS + (uint32_t)own * KS;
+#pragma unroll
+          for (int k = 0; k < KS; ++k) x[n][k] = p[k];
+        }
+      };
+      fetch(row[0], 0);
+      wide_steps([&](auto step) {
+        constexpr int i = decltype(step)::value;
+        if (i > end) return;  // the same in all threads
+        fetch(row[(i + 1) & 1], min(i + 1, end));
+        const uint32_t(&link)[kPerStep][KS] = row[i & 1];
+        Word x[kPerStep][2 * KS];
+#pragma unroll
+        for (int n = 0; n < kPerStep; ++n)
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) x[n][j] = front[j & 1 ? link[n][j >> 1] >> 16 : link[n][j >> 1] & 0xffffu];
+        __builtin_amdgcn_sched_barrier(0);
+        Word acc[kPerStep];
+#pragma unroll
+        for (int n = 0; n < kPerStep; ++n) {
+          acc[n] = x[n][0];
+#pragma unroll
+          for (int j = 1; j < 2 * KS; ++j) acc[n] |= x[n][j];
+        }
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) even[i * kWords + w] ^= ~r[i * kWords + w];
+        if constexpr (W == 16) {
+          r[i] |= (uint32_t)acc[0] | (uint32_t)acc[kPerStep - 1] << 16;
+        } else if constexpr (W == 32) {
+          r[i] |= acc[0];
+        } else {
+          r[2 * i] |= (uint32_t)acc[0];
+          r[2 * i + 1] |= (uint32_t)((uint64_t)acc[0] >> 32);
+        }
+      }, kEach);
+      __syncthreads();
+      uint32_t* const keep = kept + (size_t)(l / 2) * level_words + (uint32_t)own;
+      uint32_t all = ~0u;
+      wide_steps([&](auto step) {
+        constexpr int i = decltype(step)::value;
+        if (i > end) return;
+        const int v = i * kStride + own;
+        if constexpr (W == 16) {
+          front[v] = (uint16_t)r[i];
+          front[v + kWideThreads] = (uint16_t)(r[i] >> 16);
+        } else if constexpr (W == 32) {
+          front[v] = r[i];
+        } else {
+          front[v] = (uint64_t)r[2 * i] | (uint64_t)r[2 * i + 1] << 32;
+        }
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) all &= r[i * kWords + w];
+      }, kEach);
+      if (__ballot(all != ~0u) != 0 && lane == 0) s_more = l;
+      if ((l & 1) != 0 && l < wv.depth)
+        wide_steps([&](auto step) {
+          constexpr int i = decltype(step)::value;
+          if (i > end) return;
+#pragma unroll
+          for (int w = 0; w < kWords; ++w) keep[(i * kWords + w) * kWideThreads] = r[i * kWords + w];
+        }, kEach);
+      __syncthreads();
+      if (s_more != l) {
+        deep = l;
+        break;
+      }
+    }
+    const bool missing = s_more == deep;  // pairs out of reach
+    int bits = 0;
+    asm volatile("" : "+s"(end), "+v"(own));
+    wide_steps([&](auto step) {
+      constexpr int i = decltype(step)::value;
+      if (i > end) return;
+#pragma unroll
+      for (int w = 0; w < kWords; ++w) {
+        const int slot = i * kWords + w;
+        plane0[slot * kWideThreads + own] = even[slot];
+        if (missing) kept_last[slot * kWideThreads + own] = r[slot];
+        bits += __popc(~r[slot]);
+      }
+    }, kEach);
+    reached -= bits;
+    if (t == 0) reached += (long long)count * (N - 1);
+    __syncthreads();
+
+    // Distances: four waves take a slot of all the threads.  With 64 sources a wave keeps to one half of them.
+    const int first = W == 64 ? (wave >> 2 & 1) * 32 : 0;  // source of bit 0
+    int sum[kLanes];
+#pragma unroll
+    for (int j = 0; j < kLanes; ++j) sum[j] = 0;
+    for (int slot = wave >> 2; slot < wv.slots; slot += kWideThreads / (4 * kWave)) {
+      const uint32_t at = (uint32_t)slot * kWideThreads + 4 * (t & 255);
+      const auto words = [&](const uint32_t* p) { return *reinterpret_cast<const uint4*>(p + at); };
+      uint4 plane[kBits];
+      plane[0] = words(plane0);
+#pragma unroll
+      for (int p = 1; p < kBits; ++p) plane[p] = make_uint4(0, 0, 0, 0);
+      for (int l0 = 0; l0 < deep; l0 += 8) {
+        uint4 x[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {  // levels l0 + 2u + 1
+          x[u] = make_uint4(~0u, ~0u, ~0u, ~0u);
+          if (l0 + 2 * u + 1 < deep) x[u] = words(kept + (size_t)(l0 / 2 + u) * level_words);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int p = 1; p < kPlanes; ++p)
+            if (p == 1 || (p == 2 && u % 2 == 1) || (p > 2 && u == 3 && (l0 + 8) % (1 << p) == 0)) plane[p] = wide_xnor(plane[p], x[u]);
+      }
+      if (missing) {
+        uint4 x = words(kept_last);
+        x = make_uint4(~x.x, ~x.y, ~x.z, ~x.w);
+#pragma unroll
+        for (int p = 0; p < kBits; ++p) plane[p] = wide_or(plane[p], x);
+        if (wv.sums != nullptr)  // these are about to be counted as -1
+#pragma unroll
+          for (int b = 0; b < 32; ++b) sum[b % kLanes] += (x.x >> b & 1) + (x.y >> b & 1) + (x.z >> b & 1) + (x.w >> b & 1);
+      }
+      wide_unpack<kBits>(plane);
+      const auto number = [&](int b) {  // of bit b of the words
+        const uint4 x = plane[b % kBits];
+        const int up = 32 - kBits - b / kBits * kBits;
+        Int4 d;
+        d.x = (int)(x.x << up) >> (32 - kBits);
+        d.y = (int)(x.y << up) >> (32 - kBits);
+        d.z = (int)(x.z << up) >> (32 - kBits);
+        d.w = (int)(x.w << up) >> (32 - kBits);
+        return d;
+      };
+      if (wv.sums != nullptr) {
+#pragma unroll
+        for (int b = 0; b < 32; ++b) {
+          const Int4 d = number(b);
+          sum[b % kLanes] += d.x + d.y + d.z + d.w;
+        }
+      }
+      if (wv.dist == nullptr) continue;
+      const int v = slot / kWords * kStride + 4 * (t & 255);  // first of the lane's nodes
+      int32_t* out = wv.dist + (size_t)(s_first + first) * (size_t)N;
+      const auto rows = [&](auto part) {
+#pragma unroll
+        for (int j = 0; j < kLanes; ++j) {
+          if (first + j >= count) break;
+#pragma unroll
+          for (int n = 0; n < kPerStep; ++n) {
+            const Int4 d = number(n * 16 + j);
+            const uint32_t u = (uint32_t)(v + n * kWideThreads);
+            if constexpr (!decltype(part)::value) {
+              __builtin_nontemporal_store(d, reinterpret_cast<Int4*>(out + u));
+            } else if ((int)u + 3 < N) {
+              __builtin_nontemporal_store(d, reinterpret_cast<Int4*>(out + u));
+            } else {
+              if ((int)u < N) out[u] = d.x;
+              if ((int)u + 1 < N) out[u + 1] = d.y;
+              if ((int)u + 2 < N) out[u + 2] = d.z;
+            }
+          }
+          out += N;
+        }
+      };
+      if ((slot / kWords + 1) * kStride <= N)
+        rows(std::false_type{});
+      else
+        rows(std::true_type{});
+    }
+    if (wv.sums != nullptr) {
+#pragma unroll
+      for (int j = 0; j < kLanes; ++j) {
+        const int x = wave_sum_int(sum[j]);
+        if (lane == 0) __hip_atomic_fetch_add(&s_sum[first + j], x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+      __syncthreads();
+      if (t < count) wv.sums[s_first + t] = s_sum[t];
+    }
+    __syncthreads();
+  }
+  SmallView sv{};
+  sv.counters = wv.counters;
+  small_totals(sv, 0, reached, false, 0.0);
+}
+
+}  // namespace a2a_dev

@@ -1,0 +1,65 @@
+"""Distances of 8192 to 65536 nodes (search with the frontier in LDS) at the edges of what the kernel is chosen and cut
+up by: nodes per thread, sources per word (16, 32, 64), words of the link table, levels, ragged last workgroups, pairs
+out of reach.  All rows against the level kernels (which run while profiling is on), some against the oracle.
+(Needs an MI355X.)"""
+import numpy as np
+import pytest
+
+import a2a_inputs as gen
+
+pytestmark = pytest.mark.gpu
+
+
+def thinned(n, d, seed, gone):
+    """Random out-lists, a share of the links gone: some nodes are out of reach."""
+    csr = gen.random_regular(n, d, seed)
+    rng = np.random.default_rng(seed)
+    return gen.remove_arcs(csr, rng.choice(len(csr[1]), int(gone * len(csr[1])), replace=False))
+
+
+CASES = {
+    "smallest, 16 sources a word": (lambda: gen.random_regular(8192, 4, 1), 100, 777),
+    "one source": (lambda: gen.random_regular(9001, 3, 2), 9000, 1),
+    "32 sources a word, ragged": (lambda: gen.random_regular(12345, 5, 3), 100, 4101),
+    "64 sources a word, most nodes": (lambda: gen.random_regular(16384, 8, 4), 7000, 8200),
+    "past 64 sources a word": (lambda: gen.random_regular(16385, 6, 5), 0, 8200),
+    "past 32 sources a word": (lambda: gen.random_regular(32769, 3, 6), 5, 4100),
+    "most nodes, three rounds": (lambda: gen.random_regular(65536, 3, 7), 56000, 9500),
+    "16 links a node": (lambda: gen.random_regular(10000, 16, 8), 0, 100),
+    "17 links a node: level kernels": (lambda: gen.random_regular(10000, 17, 8), 0, 100),
+    "out of reach": (lambda: thinned(10240, 3, 9, 0.5), 3, 4200),
+    "out of reach, more than 64 sources a word holds": (lambda: thinned(20011, 5, 10, 0.6), 1, 300),
+    "deepest": (lambda: gen.torus([60, 64, 3]), 0, 9000),
+    "one level too deep": (lambda: gen.torus([60, 66, 3]), 0, 100),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_wide_distances(oracle, name):
+    import torch
+    import paper_2309_13541_amd as a2a
+    make, s0, cnt = CASES[name]
+    csr = make()
+    print(name, flush=True)
+    topo = a2a.Topology(*csr)
+
+    def run(ws_bytes=None, want=True):
+        ws = torch.empty(ws_bytes or topo.workspace_bytes(cnt, a2a.WS_DISTANCES), dtype=torch.uint8, device="cuda")
+        dist = torch.full((cnt, topo.N), -7, dtype=torch.int32, device="cuda") if want else None
+        sums = torch.full((cnt,), -7, dtype=torch.int64, device="cuda")
+        words = torch.full((2,), -7, dtype=torch.int64, device="cuda")
+        topo.distances(s0, cnt, dist=dist, dist_sum=sums, unreachable=words[:1], flags=words[1:], workspace=ws)
+        torch.cuda.synchronize()
+        return dist, sums, words
+
+    dist, sums, words = run()
+    topo.profile_enable(1)
+    ref = run()
+    topo.profile_enable(0)
+    assert torch.equal(dist, ref[0]) and torch.equal(sums, ref[1]) and torch.equal(words, ref[2])
+    only = run(topo.workspace_bytes(cnt, a2a.WS_DISTANCES | a2a.WS_MINIMAL), False)
+    assert torch.equal(sums, only[1]) and torch.equal(words, only[2])
+    rows = min(cnt, 32)
+    o = oracle.run(*csr, s0, rows, want_dist=True, threads=8)
+    assert np.array_equal(dist[:rows].cpu().numpy(), o.dist)
+    topo.close()

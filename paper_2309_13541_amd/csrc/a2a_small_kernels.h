@@ -237,8 +237,9 @@ __device__ __forceinline__ double minus_part(double x) {
   return r;
 }
 
-// A node that a lane works on: its place in an array of doubles (8 x id) and links.
-template <int KS>
+// A node that a lane works on: its place in an array of doubles (8 x id) and links.  kWide: the table has the ids
+// themselves (above 8191 nodes).
+template <int KS, bool kWide = false>
 struct SmallNode {
   uint32_t v8;
   SmallRow<KS> row;
@@ -248,7 +249,7 @@ struct SmallNode {
   }
   __device__ __forceinline__ void gather(const double* x, double (&y)[2 * KS]) const {
 #pragma unroll
-    for (int j = 0; j < 2 * KS; ++j) y[j] = lds_at(x, row.at(j));
+    for (int j = 0; j < 2 * KS; ++j) y[j] = lds_at(x, kWide ? row.at(j) << 3 : row.at(j));
   }
   __device__ __forceinline__ void levels(const unsigned char* lvl, int (&m)[2 * KS]) const {
 #pragma unroll
@@ -291,8 +292,8 @@ struct SmallNode {
 // taken for two levels, and the next level's nodes and links are on their way while this one is worked on.
 // tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
 // in the queue, for all levels up to last + 2; the queue has one valid entry at least.
-template <int KS, bool kSigns, typename Look, typename F>
-__device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const int* start,
+template <int KS, bool kSigns, bool kWide = false, typename Start, typename Look, typename F>
+__device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const Start& start,
                                             const unsigned char* lvl, double* x, int tl, int tg, int first, int last,
                                             int step, Look&& look, F&& f) {
   int l = first, left = (last - first) * step;  // levels after this one
@@ -302,13 +303,13 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
     } while (--left >= 0);
     return;
   }
-  const auto place = [&](int p, int end) { return (uint32_t)q[min(p, max(end - 1, 0))]; };
+  const auto place = [&](int p, int end) { return (uint32_t)q[min(p, max(end - 1, 0))] << (kWide ? 3 : 0); };
   int p0 = start[l] + tl, e0 = start[l + 1], p1 = start[l + step] + tl, e1 = start[l + step + 1];
-  SmallNode<KS> n0, n1;
+  SmallNode<KS, kWide> n0, n1;
   n0.request(table, place(p0, e0));
-  const auto level = [&](auto odd, const SmallNode<KS>& cur, SmallNode<KS>& next) {
+  const auto level = [&](auto odd, const SmallNode<KS, kWide>& cur, SmallNode<KS, kWide>& next) {
     constexpr bool kOdd = decltype(odd)::value;
-    const auto value = [&](const SmallNode<KS>& n) {
+    const auto value = [&](const SmallNode<KS, kWide>& n) {
       const double own = look(n.v8);
       if constexpr (kSigns) {
         const double a = f(n.v8, own, n.template sum<!kOdd>(x));
@@ -323,8 +324,8 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
     if (p0 < e0) lds_at(x, cur.v8) = value(cur);
 #pragma unroll 1
     for (int p = p0 + tg; p < e0; p += tg) {  // a level of more nodes than the source has threads
-      SmallNode<KS> more;
-      more.request(table, q[p]);
+      SmallNode<KS, kWide> more;
+      more.request(table, (uint32_t)q[p] << (kWide ? 3 : 0));
       lds_at(x, more.v8) = value(more);
     }
     __syncthreads();
@@ -456,10 +457,12 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
   return depth;
 }
 
-// A workgroup's totals into its counters (all threads call it).
-__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd) {
-  __shared__ double s_wd[kSmallThreads / kWave];
-  __shared__ long long s_tot[kSmallThreads / kWave][3];
+// A workgroup's totals into its counters (all threads call it).  lds: kSmallTotals words of 8 bytes.
+constexpr int kSmallTotals = kSmallThreads / kWave * 4;
+__device__ __forceinline__ void small_totals(const SmallView& sv, double* lds, long long dsum, long long reached, bool inexact,
+                                             double wd) {
+  double* const s_wd = lds;
+  long long(*const s_tot)[3] = reinterpret_cast<long long(*)[3]>(lds + kSmallThreads / kWave);
   const int t = (int)threadIdx.x;
   long long bad = __ballot(inexact) != 0 ? 1 : 0;
 #pragma unroll
@@ -487,6 +490,10 @@ __device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum
   c[1] = reached;
   c[2] = bad;
   c[3] = __double_as_longlong(wd);
+}
+__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd) {
+  __shared__ double s_totals[kSmallTotals];
+  small_totals(sv, s_totals, dsum, reached, inexact, wd);
 }
 
 // Link loads of sources [per_wg * workgroup, + per_wg) of the call, as one row of `part`.  The search takes up to

@@ -69,7 +69,7 @@ struct a2a_topo {
   // node, 0 if there are none; which calls use them; smallest workspaces of the calls.
   uint32_t *d_ell_out = nullptr, *d_ell_in = nullptr;
   int ell_words = 0;
-  bool small_loads = false, small_sigma = false, small_dist = false, wide_dist = false;
+  bool small_loads = false, small_sigma = false, small_dist = false, wide_dist = false, wide_sigma = false;
   size_t min_loads_bytes = 0, min_sigma_bytes = 0, min_dist_bytes = 0;
   void* d_scratch = nullptr;    // device address of `scratch` on the handle's GPU
   // optional per-kernel timing (a2a_profile_enable); events are created per launch while it is on
@@ -817,59 +817,126 @@ int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
 bool wide_distances_fit(const a2a_topo* t) {
   return t->ell_words > 0 && t->N > kScaledNodes && t->level_bound < kWideDepth;
 }
-
-template <int W, int KS>
-void wide_launch_words(const WideView& wv, int workgroups, size_t lds, hipStream_t st) {
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
-  if (wv.depth < 8)
-    launch(k_wide_dist<W, KS, 3>);
-  else
-    launch(k_wide_dist<W, KS, 6>);
+// Path counts with a source's state in LDS: 10 bytes a node have to fit, and a level per lane.
+bool wide_sigma_fits(const a2a_topo* t) {
+  return wide_distances_fit(t) && t->N <= kWideStateNodes && t->level_bound <= kWideStateDepth;
 }
-template <int W>
-void wide_launch(const WideView& wv, int ell_words, int workgroups, hipStream_t st) {
-  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
-  switch (ell_words) {
-    case 2: return wide_launch_words<W, 2>(wv, workgroups, lds, st);
-    case 3: return wide_launch_words<W, 3>(wv, workgroups, lds, st);
-    case 4: return wide_launch_words<W, 4>(wv, workgroups, lds, st);
-    case 5: return wide_launch_words<W, 5>(wv, workgroups, lds, st);
-    default: return wide_launch_words<W, 8>(wv, workgroups, lds, st);
+
+#define SMALL_BY_WORDS(call)       \
+  switch (t->ell_words) {          \
+    case 2: call(2); break;        \
+    case 3: call(3); break;        \
+    case 4: call(4); break;        \
+    case 5: call(5); break;        \
+    default: call(8); break;       \
   }
+
+template <int W, int KS, bool kBytes>
+void wide_launch_words(const WideView& wv, int workgroups, hipStream_t st) {
+  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
+  if (!kBytes && wv.depth < 8)
+    launch(k_wide_dist<W, KS, kBytes ? 6 : 3, kBytes>);
+  else
+    launch(k_wide_dist<W, KS, 6, kBytes>);
+}
+
+// The wide search over the sources of wv, its memory at `ws`, of which it may use ws_bytes (at least what the smallest
+// workspace of a call leaves).  Sets *workgroups, each of which has counters at wv->counters.
+template <bool kBytes>
+int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int* workgroups, hipStream_t st) {
+  // sources per workgroup: as few as the fewest rounds over the chip allow (a level takes the same time)
+  const int n = wv->src_count;
+  int W = 16;
+  const auto rounds = [&](int w) { return ((n + w - 1) / w + kComputeUnits - 1) / kComputeUnits; };
+  for (int w = kBytes ? 64 : 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
+    if (rounds(w) < rounds(W)) W = w;
+  wv->in = t->d_ell_in;
+  wv->N = t->N;
+  wv->depth = t->level_bound;
+  wv->slots = W == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads) : (t->N + kWideThreads - 1) / kWideThreads * (W / 32);
+  const size_t masks = (size_t)(wv->depth / 2 + 1) * wv->slots * kWideThreads * sizeof(uint32_t);
+  const size_t room = ws_bytes / (masks + kSmallCounters * sizeof(long long));
+  if (room < 1) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  *workgroups = (int)std::min<size_t>({(size_t)(n + W - 1) / W, (size_t)kComputeUnits, room});
+  wv->masks = (uint32_t*)ws;
+  wv->counters = (long long*)(ws + *workgroups * masks);
+#define WIDE_SEARCH(KS)                                                       \
+  switch (W) {                                                                \
+    case 16: wide_launch_words<16, KS, kBytes>(*wv, *workgroups, st); break;  \
+    case 32: wide_launch_words<kBytes ? 64 : 32, KS, kBytes>(*wv, *workgroups, st); break;  \
+    default: wide_launch_words<64, KS, kBytes>(*wv, *workgroups, st); break;  \
+  }
+  SMALL_BY_WORDS(WIDE_SEARCH)
+  return A2A_OK;
+}
+
+// The call's totals from the counters of its workgroups (see k_small_reduce); misc: 64 bytes for the running ones.
+void wide_totals(const a2a_topo* t, long long* counters, int workgroups, bool first, bool last, const SmallTotals& tot,
+                 long long* misc, hipStream_t st) {
+  SmallView sv{};
+  sv.N = t->N;
+  sv.counters = counters;
+  k_small_reduce<<<1, kBlock, 0, st>>>(sv, t->ell_words, workgroups, first ? 1 : 0, last ? 1 : 0, t->d_out_ptr, nullptr, misc, tot);
 }
 
 int wide_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t* dist, int64_t* dist_sum,
                    int64_t* unreachable, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
   if (ws_bytes < t->min_dist_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  // sources per workgroup: as few as the fewest rounds over the chip allow (a level takes the same time)
-  int W = 16;
-  const auto rounds = [&](int w) { return ((src_count + w - 1) / w + kComputeUnits - 1) / kComputeUnits; };
-  for (int w = 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
-    if (rounds(w) < rounds(W)) W = w;
-  WideView wv;
-  wv.in = t->d_ell_in;
-  wv.N = t->N;
-  wv.depth = t->level_bound;
+  WideView wv{};
   wv.src_begin = src_begin;
   wv.src_count = src_count;
   wv.dist = dist;
   wv.sums = (long long*)dist_sum;
-  wv.slots = W == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads) : (t->N + kWideThreads - 1) / kWideThreads * (W / 32);
-  const size_t masks = (size_t)(wv.depth / 2 + 1) * wv.slots * kWideThreads * sizeof(uint32_t);
-  const size_t room = (ws_bytes - 256) / (masks + kSmallCounters * sizeof(long long));  // at least one
-  const int workgroups = (int)std::min<size_t>({(size_t)(src_count + W - 1) / W, (size_t)kComputeUnits, room});
-  wv.counters = (long long*)(ws + 256);
-  wv.masks = (uint32_t*)(wv.counters + (size_t)workgroups * kSmallCounters);
-  switch (W) {
-    case 16: wide_launch<16>(wv, t->ell_words, workgroups, st); break;
-    case 32: wide_launch<32>(wv, t->ell_words, workgroups, st); break;
-    default: wide_launch<64>(wv, t->ell_words, workgroups, st); break;
-  }
-  SmallView sv{};
-  sv.N = t->N;
-  sv.counters = wv.counters;
+  int workgroups = 0;
+  const int rc = wide_search<false>(t, &wv, ws + 256, ws_bytes - 256, &workgroups, st);
+  if (rc != A2A_OK) return rc;
   const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
-  k_small_reduce<<<1, kBlock, 0, st>>>(sv, t->ell_words, workgroups, 1, 1, t->d_out_ptr, nullptr, (long long*)ws, tot);
+  wide_totals(t, wv.counters, workgroups, true, true, tot, (long long*)ws, st);
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
+// 1.25 times an average level: most levels in one go.
+int wide_level_threads(const a2a_topo* t) {
+  return std::min(kWideThreads, (int)align_up((size_t)t->N * 5 / 4 / (size_t)std::max(t->level_bound, 1), kWave));
+}
+
+int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const SmallOut& out, int64_t* unreachable,
+               int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
+  if (ws_bytes < t->min_sigma_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  // a quarter of the workspace for level bytes, for all sources if they fit it
+  const size_t level_bytes = small_level_bytes(t->N);
+  const int chunk = (int)std::min<size_t>((size_t)src_count, std::max<size_t>(1, ws_bytes / 4 / level_bytes));
+  unsigned char* const level = (unsigned char*)(ws + 256);
+  char* const rest = ws + 256 + align_up(chunk * level_bytes, 256);
+  long long* const counters = (long long*)rest;
+  char* const search = rest + align_up(kComputeUnits * kSmallCounters * sizeof(long long), 256);
+  const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
+  for (int c0 = 0; c0 < src_count; c0 += chunk) {
+    WideView wv{};
+    wv.src_begin = src_begin + c0;
+    wv.src_count = std::min(chunk, src_count - c0);
+    wv.level = level;
+    int groups = 0;
+    const int rc = wide_search<true>(t, &wv, search, (size_t)(ws + ws_bytes - search), &groups, st);
+    if (rc != A2A_OK) return rc;
+    WideSigma wsig;
+    wsig.in = t->d_ell_in;
+    wsig.level = level;
+    wsig.counters = counters;
+    wsig.N = t->N;
+    wsig.depth = t->level_bound;
+    wsig.ts = wide_level_threads(t);
+    wsig.src_count = wv.src_count;
+    const size_t row = (size_t)c0 * t->N;
+    wsig.out = SmallOut{out.dist ? out.dist + row : nullptr, out.sigma + row, out.sums ? out.sums + c0 : nullptr};
+    const int workgroups = std::min(wv.src_count, kComputeUnits);
+    const size_t lds = wide_state_bytes(t->N);
+#define WIDE_SIGMA(KS) k_wide_sigma<KS><<<workgroups, kWideThreads, lds, st>>>(wsig)
+    SMALL_BY_WORDS(WIDE_SIGMA)
+    wide_totals(t, counters, workgroups, c0 == 0, c0 + chunk >= src_count, tot, (long long*)ws, st);
+  }
   HIP_TRY(hipGetLastError());
   return A2A_OK;
 }
@@ -901,15 +968,6 @@ void small_sssp_launch(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) 
   k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
   k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
 }
-
-#define SMALL_BY_WORDS(call)       \
-  switch (t->ell_words) {          \
-    case 2: call(2); break;        \
-    case 3: call(3); break;        \
-    case 4: call(4); break;        \
-    case 5: call(5); break;        \
-    default: call(8); break;       \
-  }
 
 // ws: at least what a2a_workspace_bytes says for the iteration (with dense rows of 1 KB per batch and node, far
 // more than one iteration takes here).
@@ -1093,6 +1151,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     t->small_sigma = small_distances_fit(t, true);
     t->small_dist = small_distances_fit(t, false);
     t->wide_dist = wide_distances_fit(t);
+    t->wide_sigma = wide_sigma_fits(t);
   }
   if (!ok) {
     (void)hipGetLastError();
@@ -1143,6 +1202,9 @@ int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32
   if ((sigma ? t->small_sigma : t->small_dist) && t->prof_mode == 0)
     return small_distances(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
                            (char*)workspace, workspace_bytes, st);
+  if (sigma && t->wide_sigma && t->prof_mode == 0)
+    return wide_sigma(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
+                      (char*)workspace, workspace_bytes, st);
   if (!sigma && t->wide_dist && t->prof_mode == 0)
     return wide_distances(t, src_begin, src_count, dist, dist_sum, unreachable, flags, (char*)workspace, workspace_bytes, st);
   Run r;

@@ -1,5 +1,5 @@
-// Distances of topologies with 8192 to 65536 nodes (a2a_distances without path counts).  Included once, by
-// a2a_topo.hip, after a2a_small_kernels.h.
+// Distances of topologies with 8192 to 65536 nodes, and path counts of 8192 to 16384 (a2a_distances).  Included once,
+// by a2a_topo.hip, after a2a_small_kernels.h.
 //
 // The level kernels search from 512 sources at a time with the masks in memory: every level of every source reads a
 // mask per link through the L2, whatever its frontier holds, and the rate of that is the copy rate (6.5 of 11.9 ms
@@ -27,6 +27,7 @@ struct WideView {
   uint32_t* masks;      // [workgroups][depth / 2 + 1][slots][kWideThreads]
   long long* counters;  // [workgroups][kSmallCounters]
   int32_t* dist;        // [src_count][N], may be null
+  unsigned char* level; // [src_count][small_level_bytes(N)]: the same as bytes (instead of dist)
   long long* sums;      // [src_count], may be null
   int N, depth, src_begin, src_count;
   int slots;            // words of masks per thread that hold nodes, at most kWideSlots
@@ -89,8 +90,8 @@ __device__ __forceinline__ void wide_steps(F&& f, std::index_sequence<I...>) {
 // the in-neighbours.  Bit k of a distance d counts the l < d with l + 1 divisible by 2^k, so that bit plane k is the
 // parity of the complements of those R_l: plane 0 is kept in registers, the others come from the R_l of the odd levels,
 // which go to memory.  Then a lane takes the words of four adjacent nodes, unpacks them into distances and writes a row
-// per source.  kPlanes: bits of a level.
-template <int W, int KS, int kPlanes>
+// per source.  kPlanes: bits of a level.  kBytes: level bytes are wanted.
+template <int W, int KS, int kPlanes, bool kBytes = false>
 __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   using Word = typename WideWord<W>::type;
   constexpr int kPerStep = W == 16 ? 2 : 1;                    // nodes a thread takes at a time
@@ -118,7 +119,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   const int groups = (wv.src_count + W - 1) / W;
   // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
   // time (5.5 ms instead of 4.2 for 65536 nodes).  The first start is spread over about the length of a search.
-  if (wv.dist != nullptr && groups > 2 * (int)gridDim.x)
+  if (!kBytes && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
     const int s_first = g * W, count = min(W, wv.src_count - s_first), s0 = wv.src_begin + s_first;
@@ -272,7 +273,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
         x = make_uint4(~x.x, ~x.y, ~x.z, ~x.w);
 #pragma unroll
         for (int p = 0; p < kBits; ++p) plane[p] = wide_or(plane[p], x);
-        if (wv.sums != nullptr)  // these are about to be counted as -1
+        if (!kBytes && wv.sums != nullptr)  // these are about to be counted as -1
 #pragma unroll
           for (int b = 0; b < 32; ++b) sum[b % kLanes] += (x.x >> b & 1) + (x.y >> b & 1) + (x.z >> b & 1) + (x.w >> b & 1);
       }
@@ -287,14 +288,14 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
         d.w = (int)(x.w << up) >> (32 - kBits);
         return d;
       };
-      if (wv.sums != nullptr) {
+      if (!kBytes && wv.sums != nullptr) {
 #pragma unroll
         for (int b = 0; b < 32; ++b) {
           const Int4 d = number(b);
           sum[b % kLanes] += d.x + d.y + d.z + d.w;
         }
       }
-      if (wv.dist == nullptr) continue;
+      if (!kBytes && wv.dist == nullptr) continue;
       const int v = slot / kWords * kStride + 4 * (t & 255);  // first of the lane's nodes
       int32_t* out = wv.dist + (size_t)(s_first + first) * (size_t)N;
       const auto rows = [&](auto part) {
@@ -318,12 +319,27 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
           out += N;
         }
       };
-      if ((slot / kWords + 1) * kStride <= N)
+      if constexpr (kBytes) {
+        const size_t nl = small_level_bytes(N);
+        unsigned char* row = wv.level + (size_t)(s_first + first) * nl;
+#pragma unroll
+        for (int j = 0; j < kLanes; ++j) {
+#pragma unroll
+          for (int n = 0; n < kPerStep; ++n) {
+            const Int4 d = number(n * 16 + j);
+            const uint32_t u = (uint32_t)(v + n * kWideThreads);
+            if (first + j < count && u < (uint32_t)N)
+              *reinterpret_cast<uint32_t*>(row + u) =
+                  (uint32_t)(d.x & 255) | (uint32_t)(d.y & 255) << 8 | (uint32_t)(d.z & 255) << 16 | (uint32_t)d.w << 24;
+          }
+          row += nl;
+        }
+      } else if ((slot / kWords + 1) * kStride <= N)
         rows(std::false_type{});
       else
         rows(std::true_type{});
     }
-    if (wv.sums != nullptr) {
+    if (!kBytes && wv.sums != nullptr) {
 #pragma unroll
       for (int j = 0; j < kLanes; ++j) {
         const int x = wave_sum_int(sum[j]);
@@ -337,6 +353,146 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   SmallView sv{};
   sv.counters = wv.counters;
   small_totals(sv, 0, reached, false, 0.0);
+}
+
+// ---------------------------------------------------------------------------------------
+// path counts of 8192 to 16384 nodes
+// ---------------------------------------------------------------------------------------
+//
+// As in the small kernels a source's path counts stay in LDS, 8 bytes per node, with the queue of its nodes behind
+// them: 10 bytes per node, all of the 160 KB for 16384 nodes.  So the levels come from a search of its own (bytes in
+// memory), the counters of the sort lie where the path counts will be, and where a level starts in the queue is kept
+// in a register, a level per lane.  (The level kernels wrote an index entry per node, level and batch, and gathered the
+// counts out of their compact rows one memory latency at a time.)  Bound by the sort (20k cycles per source of 16384
+// nodes), the sweep and the stores, about 25k cycles each.  All sources, before and after: torus 25x25x26 27.5 -> 2.5 ms,
+// 16384 nodes of degree 5 11.1 -> 1.74 ms, 9000 nodes of degree 8 3.20 -> 0.63 ms.
+
+constexpr int kWideStateNodes = 16384, kWideStateDepth = 60;
+__host__ __device__ inline size_t wide_state_bytes(int N) { return (size_t)N * 8 + ((size_t)N * 2 + 7) / 8 * 8; }
+
+struct WideStarts {
+  int at;  // lane l: where level l starts
+  __device__ __forceinline__ int operator[](int l) const { return __builtin_amdgcn_readlane(at, l); }
+};
+
+// Sorts the nodes of a source by level into q; `level`: its level bytes.  lds: room for the counters, free again on
+// return (after a barrier).  own: sum of the distances, in wave 0 (a share per lane); reached: pairs, likewise.
+__device__ __forceinline__ WideStarts wide_sort(int N, int spread, const uint32_t (&lv)[4], unsigned short* q, int* lds,
+                                                long long& own, long long& reached) {
+  const int t = (int)threadIdx.x, lane = lane_id();
+  constexpr int kSlots = kWave;
+  int *const start = lds, *const at = lds + kSlots;
+  for (int i = t; i < kSlots * spread; i += kWideThreads) at[i] = 0;
+  __syncthreads();
+  int* const mine = at + (spread > 1 ? lane >> 3 : 0);
+  uint32_t rank[8];  // of this thread's nodes among those with the same counter, two a word
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int l = (int)(lv[i / 4] >> (i % 4 * 8) & 255u);
+    uint32_t r = 0;
+    if (l != kSmallUnseen)
+      r = (uint32_t)__hip_atomic_fetch_add(&mine[l * spread], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    rank[i / 2] = i % 2 == 0 ? r : rank[i / 2] | r << 16;
+  }
+  __syncthreads();
+  if (t < kWave) {
+    int carry = 0;
+    for (int i0 = 0; i0 < kSlots * spread; i0 += kWave) {
+      const int i = i0 + lane, c = at[i], l = spread > 1 ? i >> 3 : i;
+      const int incl = wave_scan_incl(c, lane);
+      at[i] = carry + incl - c;
+      if (spread == 1 || (i & 7) == 0) start[l] = carry + incl - c;
+      carry += __builtin_amdgcn_readlane(incl, kWave - 1);
+      own += (long long)c * l;
+      reached += l > 0 ? c : 0;
+    }
+    if (carry == 0 && lane == 0) q[0] = 0;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int l = (int)(lv[i / 4] >> (i % 4 * 8) & 255u), v = 4 * (t + i / 4 * kWideThreads) + i % 4;
+    if (l != kSmallUnseen) q[mine[l * spread] + (int)(rank[i / 2] >> (i % 2 * 16) & 0xffffu)] = (unsigned short)v;
+  }
+  WideStarts s;
+  s.at = start[lane];
+  __syncthreads();
+  return s;
+}
+
+struct WideSigma {
+  const uint32_t* in;          // [N][KS] in-links
+  const unsigned char* level;  // [src_count][small_level_bytes(N)]
+  long long* counters;         // [workgroups][kSmallCounters]
+  int N, depth, ts, src_count;
+  SmallOut out;
+};
+
+typedef double Double2 __attribute__((ext_vector_type(2), aligned(8)));
+typedef int Int2 __attribute__((ext_vector_type(2), aligned(4)));
+
+template <int KS>
+__global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
+  extern __shared__ double s_small[];
+  const int t = (int)threadIdx.x, lane = lane_id(), N = ws.N, nl = (int)small_level_bytes(N);
+  double* const x = s_small;
+  unsigned short* const q = reinterpret_cast<unsigned short*>(s_small + N);
+  long long reached = 0;
+  bool inexact = false;
+  for (int s = (int)blockIdx.x; s < ws.src_count; s += (int)gridDim.x) {
+    const unsigned char* const level = ws.level + (size_t)s * (size_t)nl;
+    uint32_t lv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const int v = 4 * (t + k * kWideThreads);
+      lv[k] = ~0u;
+      if (v < N) lv[k] = *reinterpret_cast<const uint32_t*>(level + v);
+      if (v + 4 > N && v < N) lv[k] |= ~0u << ((N - v) * 8);
+    }
+    long long own = 0;
+    const WideStarts start = wide_sort(N, small_spread(ws.depth), lv, q, reinterpret_cast<int*>(x), own, reached);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      const int v = 4 * (t + i / 4 * kWideThreads) + i % 4;
+      if (v < N) x[v] = (lv[i / 4] >> (i % 4 * 8) & 255u) == 0 ? 1.0 : 0.0;
+    }
+    __syncthreads();
+    const int after = __shfl_down(start.at, 1, kWave);
+    const uint64_t filled = __ballot(lane >= 1 && lane < kWave - 1 && after > start.at);
+    if (filled != 0)
+      small_sweep<KS, true, true>(ws.in, q, start, nullptr, x, t, ws.ts, 1, 63 - __builtin_clzll(filled), 1,
+                                  [](uint32_t) { return 0.0; }, [&](uint32_t, double, double a) {
+        inexact |= a >= kTwo53;
+        return a;
+      });
+    const size_t row = (size_t)s * (size_t)N;
+    for (int v = 2 * t; v < N; v += 2 * kWideThreads) {
+      const unsigned two = *reinterpret_cast<const unsigned short*>(level + v);
+      const int l0 = (int)(two & 255u), l1 = (int)(two >> 8);
+      if (v + 1 < N) {
+        Double2 y;
+        y.x = __builtin_fabs(x[v]);
+        y.y = __builtin_fabs(x[v + 1]);
+        __builtin_nontemporal_store(y, reinterpret_cast<Double2*>(&ws.out.sigma[row + v]));
+        Int2 d;
+        d.x = l0 == kSmallUnseen ? -1 : l0;
+        d.y = l1 == kSmallUnseen ? -1 : l1;
+        if (ws.out.dist != nullptr) __builtin_nontemporal_store(d, reinterpret_cast<Int2*>(&ws.out.dist[row + v]));
+      } else {
+        ws.out.sigma[row + v] = __builtin_fabs(x[v]);
+        if (ws.out.dist != nullptr) ws.out.dist[row + v] = l0 == kSmallUnseen ? -1 : l0;
+      }
+    }
+    if (ws.out.sums != nullptr && t < kWave) {
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) own += __shfl_xor(own, o, kWave);
+      if (t == 0) ws.out.sums[s] = own;
+    }
+    __syncthreads();
+  }
+  SmallView sv{};
+  sv.counters = ws.counters;
+  small_totals(sv, s_small, 0, reached, inexact, 0.0);
 }
 
 }  // namespace a2a_dev

@@ -63,3 +63,51 @@ def test_wide_distances(oracle, name):
     o = oracle.run(*csr, s0, rows, want_dist=True, threads=8)
     assert np.array_equal(dist[:rows].cpu().numpy(), o.dist)
     topo.close()
+
+
+SIGMA = {
+    "smallest": (lambda: gen.random_regular(8192, 4, 1), 100, 777),
+    "one source": (lambda: gen.random_regular(9001, 3, 2), 9000, 1),
+    "most nodes, whole LDS": (lambda: gen.random_regular(16384, 8, 3), 7000, 4200),
+    "too many nodes: level kernels": (lambda: gen.random_regular(16385, 5, 3), 0, 70),
+    "odd rows, out of reach": (lambda: thinned(10241, 3, 9, 0.5), 3, 300),
+    "16 links a node": (lambda: gen.random_regular(12000, 16, 5), 0, 64),
+    "deepest": (lambda: gen.torus([56, 62, 3]), 10, 300),
+    "one level too deep": (lambda: gen.torus([56, 64, 3]), 10, 70),
+}
+
+
+@pytest.mark.parametrize("name", SIGMA)
+def test_wide_path_counts(oracle, name):
+    import torch
+    import paper_2309_13541_amd as a2a
+    make, s0, cnt = SIGMA[name]
+    csr = make()
+    print(name, flush=True)
+    topo = a2a.Topology(*csr)
+
+    def run(flags):
+        ws = torch.empty(topo.workspace_bytes(cnt, a2a.WS_SIGMA | flags), dtype=torch.uint8, device="cuda")
+        dist = torch.full((cnt, topo.N), -7, dtype=torch.int32, device="cuda")
+        sigma = torch.full((cnt, topo.N), -7.0, dtype=torch.float64, device="cuda")
+        sums = torch.full((cnt,), -7, dtype=torch.int64, device="cuda")
+        words = torch.full((2,), -7, dtype=torch.int64, device="cuda")
+        topo.distances(s0, cnt, dist=dist, sigma=sigma, dist_sum=sums, unreachable=words[:1], flags=words[1:], workspace=ws)
+        torch.cuda.synchronize()
+        return sigma, dist, sums, words
+
+    got, least = run(0), run(a2a.WS_MINIMAL)
+    topo.profile_enable(1)
+    ref = run(0)
+    topo.profile_enable(0)
+    for a, b in zip(got, least):
+        assert torch.equal(a, b)
+    for a, b in zip(got[1:], ref[1:]):
+        assert torch.equal(a, b)
+    whole = ref[0] < 2.0 ** 53
+    assert torch.equal(got[0][whole], ref[0][whole])
+    assert bool(((got[0] - ref[0]).abs() <= 1e-13 * ref[0]).all())
+    if bool(whole.all()):
+        o = oracle.run(*csr, s0, min(cnt, 16), want_sigma=True, threads=8)
+        assert np.array_equal(got[0][:min(cnt, 16)].cpu().numpy(), o.sigma.astype(np.float64))
+    topo.close()

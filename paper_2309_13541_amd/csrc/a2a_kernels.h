@@ -2031,7 +2031,8 @@ constexpr int kExtremaWords = 8;    // of scratch per workgroup
 
 // Every workgroup leaves what it found in its part of `scratch`; the one that comes last (`arrived`, 0 before and
 // after) merges them in workgroup order and writes out[0..5] = largest, its index, smallest, total capacity, largest
-// node capacity, 1 if a capacity is bad.  out is host memory: the caller waits for the stream and has them.
+// node capacity, 1 if a capacity is bad, and then out[kExtremaDone] = 1.  out is host memory: the caller sees them there.
+constexpr int kExtremaDone = 6;
 template <bool kCap>
 __device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
                                                long long* __restrict__ out) {
@@ -2083,6 +2084,7 @@ __device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict_
       out[5] = e.bad;
     }
     *arrived = 0;
+    __hip_atomic_store(&out[kExtremaDone], 1ll, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 

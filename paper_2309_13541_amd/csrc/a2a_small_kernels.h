@@ -185,7 +185,8 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
 }
 
 // Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
-// masks in LDS (three words per node), until a level finds nothing new.  deepest: host memory, a word per workgroup.
+// masks in LDS (three words per node), until a level finds nothing new.  deepest: host memory, a word per workgroup,
+// negative before (the host waits for the last of them to change).
 __global__ void __launch_bounds__(kSmallThreads)
 k_small_probe(const uint32_t* __restrict__ table, int words, int N, int* __restrict__ deepest) {
   extern __shared__ uint32_t s_masks[];
@@ -222,7 +223,7 @@ k_small_probe(const uint32_t* __restrict__ table, int words, int N, int* __restr
     __syncthreads();
     if (s_new[l & 1] != l) break;
   }
-  if (t == 0) deepest[blockIdx.x] = l - 1;
+  if (t == 0) __hip_atomic_store(&deepest[blockIdx.x], l - 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // max(x, 0) and min(x, 0): one instruction each (the compiler's own adds one that quiets signalling NaNs).

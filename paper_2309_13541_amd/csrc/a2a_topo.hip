@@ -16,6 +16,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdint>
 #include <cstdlib>
@@ -72,6 +73,14 @@ struct a2a_topo {
   bool small_loads = false, small_sigma = false, small_dist = false, wide_dist = false, wide_sigma = false;
   size_t min_loads_bytes = 0, min_sigma_bytes = 0, min_dist_bytes = 0;
   void* d_scratch = nullptr;    // device address of `scratch` on the handle's GPU
+  // Whether all work that uses the handle is known to be over (then a2a_topo_destroy need not wait for the device,
+  // 25 us): calls begun, calls now inside, the number begun when a call last waited for everything before it.
+  struct Uses {
+    std::atomic<uint64_t> begun{0}, inside{0}, settled{0};
+    std::atomic<void*> stream{nullptr};
+    std::atomic<bool> several{false};  // streams, or recorded in a graph: only the device knows
+  };
+  mutable Uses uses;
   // optional per-kernel timing (a2a_profile_enable); events are created per launch while it is on
   struct ProfRec {
     int cls, level;
@@ -89,6 +98,32 @@ struct a2a_topo {
 };
 
 namespace {
+
+// A call that enqueues work with the handle.
+class Use {
+ public:
+  Use(const a2a_topo* t, hipStream_t st) : u_(t->uses) {
+    u_.inside.fetch_add(1);
+    if (u_.begun.fetch_add(1) == 0) u_.stream = st;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (st != nullptr && hipStreamIsCapturing(st, &capture) != hipSuccess) u_.several = true;
+    if (capture != hipStreamCaptureStatusNone || u_.stream.load() != st || st == hipStreamPerThread) u_.several = true;
+  }
+  ~Use() { u_.inside.fetch_sub(1); }
+  Use(const Use&) = delete;
+  Use& operator=(const Use&) = delete;
+  // Before a launch: what a wait for it will cover, 0 if that is not everything begun so far.
+  uint64_t covered() const {
+    const uint64_t n = u_.begun.load();
+    return u_.inside.load() == 1 && !u_.several.load() ? n : 0;
+  }
+  void waited(uint64_t n) const {
+    if (n != 0) u_.settled = n;
+  }
+
+ private:
+  a2a_topo::Uses& u_;
+};
 
 // Blocks of destroyed handles, kept for the next ones: a program that evaluates one small topology after the other
 // would spend most of its time in hipMalloc, hipHostMalloc and hipFree otherwise.  At most kKept blocks of at most
@@ -125,12 +160,13 @@ class ArenaPool {
     return true;
   }
 
-  void put(const Arena& a) {
+  // settled: no work that uses the block is left.
+  void put(const Arena& a, bool settled) {
     if (a.d == nullptr && a.h == nullptr) return;
     int device = a.device;
     const bool other = hipGetDevice(&device) == hipSuccess && device != a.device;
     if (other) (void)hipSetDevice(a.device);
-    const bool idle = hipDeviceSynchronize() == hipSuccess;  // as hipFree would wait
+    const bool idle = settled || hipDeviceSynchronize() == hipSuccess;  // as hipFree would wait
     bool keep = idle && a.d != nullptr && a.h != nullptr && a.device_bytes <= kLargest && a.host_bytes <= kLargest;
     if (keep) {
       std::lock_guard<std::mutex> lock(mutex_);
@@ -305,6 +341,25 @@ Layout make_layout(const a2a_topo* t, int32_t src_count, int flags, size_t ws_by
       return A2A_ERR_HIP;       \
     }                           \
   } while (0)
+
+// Waits until done(), which looks at host memory that a kernel on the stream writes to at its end, or until the stream
+// has finished.  The kernel's word is there before the runtime learns of the kernel's end: 5 to 8 us per wait.  Looks
+// for about 100 us; what takes longer is left to the runtime, which does not keep the processor busy.
+template <typename Done>
+hipError_t wait_for(hipStream_t st, Done&& done) {
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(100);
+  do {
+    for (int k = 0; k < 64; ++k) {
+      if (done()) return hipSuccess;
+      __builtin_ia32_pause();
+    }
+  } while (std::chrono::steady_clock::now() < until);
+  return hipStreamSynchronize(st);
+}
+template <typename T>
+T seen(const T* p) {
+  return __atomic_load_n(p, __ATOMIC_ACQUIRE);
+}
 
 // Zeroes `bytes` bytes (rounded up to a multiple of 8; every array it is used on has that room) at
 // the 8-byte aligned device address p with a kernel on the stream.
@@ -549,10 +604,14 @@ int probe_depth(const a2a_topo* t, int* deepest_of, int32_t* depth_out) {
   if (t->ell_words > 0 && N <= kScaledNodes) {
     const int groups = (N + kSmallBatch - 1) / kSmallBatch;
     const unsigned threads = (unsigned)std::min<size_t>(kSmallThreads, align_up((size_t)N, kWave));
+    std::fill_n(deepest_of, groups, -1);
     k_small_probe<<<(unsigned)groups, threads, (size_t)N * 3 * sizeof(uint32_t), nullptr>>>(t->d_ell_out, t->ell_words, N,
                                                                                         deepest_of);
     HIP_TRY(hipGetLastError());
-    HIP_TRY(hipStreamSynchronize(nullptr));
+    HIP_TRY(wait_for(nullptr, [&, k = 0]() mutable {
+      while (k < groups && seen(&deepest_of[k]) >= 0) ++k;
+      return k == groups;
+    }));
     *depth_out = *std::max_element(deepest_of, deepest_of + groups);
     return A2A_OK;
   }
@@ -1141,8 +1200,8 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     std::memset(h + o_arrived, 0, a2a_topo::kSlots * sizeof(unsigned));
     ok = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, nullptr) == hipSuccess;
   }
-  if (ok && E > 0) ok = probe_depth(t, (int*)(t->mem.h + o_probe), &t->level_bound) == A2A_OK;
-  ok = ok && hipStreamSynchronize(nullptr) == hipSuccess;
+  // the probe runs after the upload and is waited for
+  if (ok) ok = E > 0 ? probe_depth(t, (int*)(t->mem.h + o_probe), &t->level_bound) == A2A_OK : hipStreamSynchronize(nullptr) == hipSuccess;
   if (ok) {
     t->min_loads_bytes = make_layout(t, 64, A2A_WS_LOADS, 0, true, true).total;
     t->min_sigma_bytes = make_layout(t, 64, A2A_WS_SIGMA, 0, true, true).total;
@@ -1155,6 +1214,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
   }
   if (!ok) {
     (void)hipGetLastError();
+    t->uses.several = true;  // whatever got as far as the device
     a2a_topo_destroy(t);
     return A2A_ERR_HIP;
   }
@@ -1168,7 +1228,7 @@ void a2a_topo_destroy(a2a_topo* t) {
     (void)hipEventDestroy(rec.beg);
     (void)hipEventDestroy(rec.end);
   }
-  arena_pool().put(t->mem);
+  arena_pool().put(t->mem, t->uses.several.load() ? false : t->uses.begun.load() == t->uses.settled.load());
   delete t;
 }
 
@@ -1194,6 +1254,7 @@ int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32
   int rc = check_common(t, src_begin, src_count, workspace);
   if (rc != A2A_OK) return rc;
   hipStream_t st = (hipStream_t)hip_stream;
+  const Use use(t, st);
   if (src_count == 0) {
     if (unreachable) HIP_TRY(zero_async(unreachable, 8, st));
     if (flags) HIP_TRY(zero_async(flags, 8, st));
@@ -1272,6 +1333,7 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
   if (rc != A2A_OK) return rc;
   if (!load && t->E > 0) return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
+  const Use use(t, st);
   // (while profiling is on, the level kernels run: that is what the profile is about)
   if (t->small_loads && src_count > 0 && t->prof_mode == 0)
     return small_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags,
@@ -1375,6 +1437,7 @@ int a2a_sssp_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   if (!load && t->E > 0) return A2A_ERR_INVALID_ARG;
   if (iter_sources <= 0 || iter_sources % 64 != 0) return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
+  const Use use(t, st);
   if (src_count == 0) {
     if (t->E > 0) HIP_TRY(zero_async(load, (size_t)t->E * 8, st));
     if (dist_sum_total) HIP_TRY(zero_async(dist_sum_total, 8, st));
@@ -1433,11 +1496,15 @@ int a2a_schedule_bound(const a2a_topo* t, const double* load, int64_t sum_dist, 
   hipStream_t st = (hipStream_t)hip_stream;
   const unsigned slot = t->next_slot.fetch_add(1) % a2a_topo::kSlots;
   int64_t* const h_res = t->h_slots + slot * a2a_topo::kSlotWords;
+  const Use use(t, st);
+  const uint64_t covered = use.covered();
+  h_res[kExtremaDone] = 0;
   k_load_extrema<<<extrema_groups((t->E + 3) / 4), kBlock, 0, st>>>(
       load, (long long)t->E, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
       (long long*)h_res);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
+  HIP_TRY(wait_for(st, [&] { return seen(&h_res[kExtremaDone]) != 0; }));
+  use.waited(covered);
   double lmax, lmin;
   std::memcpy(&lmax, &h_res[0], 8);
   std::memcpy(&lmin, &h_res[2], 8);
@@ -1467,11 +1534,15 @@ int a2a_schedule_bound_cap(const a2a_topo* t, const double* load, const double* 
   hipStream_t st = (hipStream_t)hip_stream;
   const unsigned slot = t->next_slot.fetch_add(1) % a2a_topo::kSlots;
   int64_t* const h_res = t->h_slots + slot * a2a_topo::kSlotWords;
+  const Use use(t, st);
+  const uint64_t covered = use.covered();
+  h_res[kExtremaDone] = 0;
   k_util_extrema<<<extrema_groups(t->N), kBlock, 0, st>>>(
       t->d_out_ptr, load, cap, t->N, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
       (long long*)h_res);
   HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(st));
+  HIP_TRY(wait_for(st, [&] { return seen(&h_res[kExtremaDone]) != 0; }));
+  use.waited(covered);
   if (h_res[5] != 0) return A2A_ERR_INVALID_ARG;  // a capacity that is not positive and finite
   double umax, umin, total, cmax;
   std::memcpy(&umax, &h_res[0], 8);

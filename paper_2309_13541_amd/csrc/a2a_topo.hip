@@ -406,6 +406,7 @@ constexpr int32_t kMaxNodes = 4 * 1024 * 1024;
 // The link tables hold 8 x id in 16 bits up to here, and ids beyond, up to the nodes that the single-path baseline's
 // state for one source takes in LDS.
 constexpr int32_t kScaledNodes = 8191, kBothTables = 16384;
+constexpr int32_t kPaddedRows = 4096;  // nodes above which the in-link table has whole slots of the wide search
 
 // Nominal lane layout of a level for the profile's kernel classes (the kernels pick per batch,
 // from the same rule applied to the batch's own counts).
@@ -420,6 +421,7 @@ struct Run {
   const double* demand = nullptr;  // [N][src_count] by target, or nullptr: every pair has demand 1
   int inflight = kXcd;  // batches in flight = XCDs: one batch's node blocks per XCD at a time
   int split = 1;        // waves per block of 64 nodes in the forward / backward kernels (pick_split)
+  mutable bool indexed = false;  // run_index has written the group's index entries
   mutable std::vector<double> lanes_per_node;  // profiling only: per level of the current group, pairs / (G*N)
   bool few(int level) const {
     return level >= 0 && level < (int)lanes_per_node.size() && lanes_per_node[level] > 0.0 &&
@@ -537,7 +539,7 @@ int run_bfs(const Run& r, const GroupView& gv, int top) {
 int run_fwd(const Run& r, const GroupView& gv, int depth) {
   const a2a_topo* t = r.t;
   const Layout& L = r.L;
-  {
+  if (!r.indexed) {
     // With demands the backward pass also visits a batch's deepest level and looks at the (empty)
     // level after it, which the BFS has computed: its index entries are written too.
     const int idx_depth = gv.dem != nullptr ? depth + 1 : depth;
@@ -890,25 +892,25 @@ bool wide_sigma_fits(const a2a_topo* t) {
     default: call(8); break;       \
   }
 
-template <int W, int KS, bool kBytes>
+template <int W, int KS, int kOut>
 void wide_launch_words(const WideView& wv, int workgroups, hipStream_t st) {
   const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
   const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
-  if (!kBytes && wv.depth < 8)
-    launch(k_wide_dist<W, KS, kBytes ? 6 : 3, kBytes>);
+  if (kOut == kWideDist && wv.depth < 8)
+    launch(k_wide_dist<W, KS, kOut == kWideDist ? 3 : 6, kOut>);
   else
-    launch(k_wide_dist<W, KS, 6, kBytes>);
+    launch(k_wide_dist<W, KS, 6, kOut>);
 }
 
 // The wide search over the sources of wv, its memory at `ws`, of which it may use ws_bytes (at least what the smallest
 // workspace of a call leaves).  Sets *workgroups, each of which has counters at wv->counters.
-template <bool kBytes>
+template <int kOut>
 int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int* workgroups, hipStream_t st) {
   // sources per workgroup: as few as the fewest rounds over the chip allow (a level takes the same time)
   const int n = wv->src_count;
   int W = 16;
   const auto rounds = [&](int w) { return ((n + w - 1) / w + kComputeUnits - 1) / kComputeUnits; };
-  for (int w = kBytes ? 64 : 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
+  for (int w = kOut == kWideBytes ? 64 : 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
     if (rounds(w) < rounds(W)) W = w;
   wv->in = t->d_ell_in;
   wv->N = t->N;
@@ -922,11 +924,60 @@ int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int*
   wv->counters = (long long*)(ws + *workgroups * masks);
 #define WIDE_SEARCH(KS)                                                       \
   switch (W) {                                                                \
-    case 16: wide_launch_words<16, KS, kBytes>(*wv, *workgroups, st); break;  \
-    case 32: wide_launch_words<kBytes ? 64 : 32, KS, kBytes>(*wv, *workgroups, st); break;  \
-    default: wide_launch_words<64, KS, kBytes>(*wv, *workgroups, st); break;  \
+    case 16: wide_launch_words<16, KS, kOut>(*wv, *workgroups, st); break;  \
+    case 32: wide_launch_words<kOut == kWideBytes ? 64 : 32, KS, kOut>(*wv, *workgroups, st); break;  \
+    default: wide_launch_words<64, KS, kOut>(*wv, *workgroups, st); break;  \
   }
   SMALL_BY_WORDS(WIDE_SEARCH)
+  return A2A_OK;
+}
+
+// Link loads by the level kernels: whether the levels of a group of G batches come from the wide search (link table
+// there, whole slots of rows in it, masks of all levels fit the memory of the level search's).  Search and index entries
+// before and after: 16384 nodes of degree 4 490 -> 250 us, 2501 sources of 20011 nodes 190 -> 102 us, 65536 nodes of
+// degree 8 10.4 -> 6.2 ms.  While profiling is on the level search runs, whose launches the profile knows.  The table of up to 8191
+// nodes has 8 x id, which is the place of a 64-bit word.
+int wide_masks_sources(const a2a_topo* t) { return t->N <= kBothTables ? 64 : 16; }  // a word
+int wide_masks_slots(const a2a_topo* t) {
+  return wide_masks_sources(t) == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads)
+                                     : (t->N + kWideThreads - 1) / kWideThreads * 2;
+}
+bool wide_masks_fit(const a2a_topo* t, const Layout& L, int G) {
+  const size_t room = L.off_bm - L.off_seen + (size_t)L.SB * L.Lcap * L.Npad * kSub * 8;
+  const size_t groups = (size_t)G * (64 / wide_masks_sources(t));
+  return t->ell_words > 0 && t->N > kPaddedRows && t->level_bound >= 1 && t->prof_mode == 0 &&
+         groups * t->level_bound * wide_masks_slots(t) * kWideThreads * sizeof(uint32_t) <= room;
+}
+
+// Search and index entries of a group, levels 0 .. top.
+int run_index(const Run& r, const GroupView& gv, int top) {
+  const a2a_topo* t = r.t;
+  WideView wv{};
+  wv.in = t->d_ell_in;
+  wv.masks = (uint32_t*)(r.ws + r.L.off_seen);
+  wv.N = t->N;
+  wv.depth = t->level_bound;
+  wv.src_begin = r.src_begin + gv.batch0 * 64;
+  wv.src_count = std::min(gv.G * 64, r.src_count - gv.batch0 * 64);
+  wv.slots = wide_masks_slots(t);
+  wv.ltot = gv.ltot;
+  wv.Lcap = gv.Lcap;
+  HIP_TRY(zero_async(gv.ltot, (size_t)gv.SB * kSub * r.L.Lcap * 8, r.st));
+  const int W = wide_masks_sources(t);
+  const int workgroups = std::min((wv.src_count + W - 1) / W, kComputeUnits);
+  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+#define WIDE_MASKS(KS)                                                                                               \
+  if (W == 16)                                                                                                       \
+    k_wide_dist<16, KS, 6, kWideMasks><<<workgroups, kWideThreads, lds, r.st>>>(wv);                                 \
+  else if (t->N > kScaledNodes)                                                                                      \
+    k_wide_dist<64, KS, 6, kWideMasks><<<workgroups, kWideThreads, lds, r.st>>>(wv);                                 \
+  else                                                                                                               \
+    k_wide_dist<64, KS, 6, kWideMasks, true><<<workgroups, kWideThreads, lds, r.st>>>(wv)
+  SMALL_BY_WORDS(WIDE_MASKS)
+  const unsigned blocks = (unsigned)(gv.G * (top + 1));
+  W == 16 ? k_wide_index<16><<<blocks, kWideThreads, 0, r.st>>>(wv, gv) : k_wide_index<64><<<blocks, kWideThreads, 0, r.st>>>(wv, gv);
+  HIP_TRY(hipGetLastError());
+  r.lanes_per_node.clear();
   return A2A_OK;
 }
 
@@ -948,7 +999,7 @@ int wide_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   wv.dist = dist;
   wv.sums = (long long*)dist_sum;
   int workgroups = 0;
-  const int rc = wide_search<false>(t, &wv, ws + 256, ws_bytes - 256, &workgroups, st);
+  const int rc = wide_search<kWideDist>(t, &wv, ws + 256, ws_bytes - 256, &workgroups, st);
   if (rc != A2A_OK) return rc;
   const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
   wide_totals(t, wv.counters, workgroups, true, true, tot, (long long*)ws, st);
@@ -978,7 +1029,7 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
     wv.src_count = std::min(chunk, src_count - c0);
     wv.level = level;
     int groups = 0;
-    const int rc = wide_search<true>(t, &wv, search, (size_t)(ws + ws_bytes - search), &groups, st);
+    const int rc = wide_search<kWideBytes>(t, &wv, search, (size_t)(ws + ws_bytes - search), &groups, st);
     if (rc != A2A_OK) return rc;
     WideSigma wsig;
     wsig.in = t->d_ell_in;
@@ -1149,7 +1200,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
     t->ell_words = ell_words_for(N, std::max(dmax, t->dmax_in));
     if (N <= kBothTables) ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
     ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words,
-                      N <= kScaledNodes ? N : align_up((size_t)N, 2 * kWideThreads));
+                      N <= kPaddedRows ? N : align_up((size_t)N, 2 * kWideThreads));
   } catch (const std::bad_alloc&) {
     delete t;
     return A2A_ERR_NO_MEMORY;
@@ -1361,7 +1412,8 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
     r.split = pick_split(t, nb - b0 < L.G ? nb - b0 : L.G, L.nb64, demand != nullptr);
     const GroupView gv = r.view(b0, nb - b0 < L.G ? nb - b0 : L.G);
     const int depth = t->level_bound;
-    rc = run_bfs(r, gv, demand ? depth + 1 : depth);
+    r.indexed = wide_masks_fit(t, L, gv.G);
+    rc = r.indexed ? run_index(r, gv, demand ? depth + 1 : depth) : run_bfs(r, gv, demand ? depth + 1 : depth);
     if (rc != A2A_OK) return rc;
     rc = run_fwd(r, gv, depth);
     if (rc != A2A_OK) return rc;

@@ -24,13 +24,15 @@ constexpr int kWideDepth = 64;      // levels are below this
 
 struct WideView {
   const uint32_t* in;   // [rows][KS] in-links, two 16-bit ids a word; rows: N rounded up to whole slots
-  uint32_t* masks;      // [workgroups][depth / 2 + 1][slots][kWideThreads]
+  uint32_t* masks;      // [workgroups][depth / 2 + 1][slots][kWideThreads]; kWideMasks: see there
   long long* counters;  // [workgroups][kSmallCounters]
   int32_t* dist;        // [src_count][N], may be null
   unsigned char* level; // [src_count][small_level_bytes(N)]: the same as bytes (instead of dist)
   long long* sums;      // [src_count], may be null
   int N, depth, src_begin, src_count;
   int slots;            // words of masks per thread that hold nodes, at most kWideSlots
+  long long* ltot;      // [batches of 64][Lcap]: newly reached pairs per level are added (kWideMasks)
+  int Lcap;
 };
 
 // Masks of W sources: which part of a thread's slots a node has.  A slot is a 32-bit word: two nodes (W = 16),
@@ -90,10 +92,15 @@ __device__ __forceinline__ void wide_steps(F&& f, std::index_sequence<I...>) {
 // the in-neighbours.  Bit k of a distance d counts the l < d with l + 1 divisible by 2^k, so that bit plane k is the
 // parity of the complements of those R_l: plane 0 is kept in registers, the others come from the R_l of the odd levels,
 // which go to memory.  Then a lane takes the words of four adjacent nodes, unpacks them into distances and writes a row
-// per source.  kPlanes: bits of a level.  kBytes: level bytes are wanted.
-template <int W, int KS, int kPlanes, bool kBytes = false>
+// per source.  kPlanes: bits of a level.
+// kOut: what is wanted.  kWideMasks: the newly reached of every level 1..depth, [groups][depth][slots][kWideThreads].
+// kScaled: the table has 8 x id (up to 8191 nodes; 64 sources a word only).
+enum { kWideDist, kWideBytes, kWideMasks };
+template <int W, int KS, int kPlanes, int kOut = kWideDist, bool kScaled = false>
 __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   using Word = typename WideWord<W>::type;
+  static_assert(!kScaled || W == 64, "8 x id is the place of a 64-bit word");
+  constexpr bool kBytes = kOut == kWideBytes, kMasks = kOut == kWideMasks;
   constexpr int kPerStep = W == 16 ? 2 : 1;                    // nodes a thread takes at a time
   constexpr int kWords = W == 64 ? 2 : 1;                      // slots they have
   constexpr int kSteps = kWideSlots / kWords;
@@ -119,11 +126,12 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   const int groups = (wv.src_count + W - 1) / W;
   // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
   // time (5.5 ms instead of 4.2 for 65536 nodes).  The first start is spread over about the length of a search.
-  if (!kBytes && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
+  if (kOut == kWideDist && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
     const int s_first = g * W, count = min(W, wv.src_count - s_first), s0 = wv.src_begin + s_first;
     const Word none = count == W ? (Word)0 : (Word)(~(Word)0 << count);  // bits without a source: taken for reached
+    uint32_t* const group_masks = wv.masks + (size_t)g * wv.depth * level_words;
     uint32_t r[kWideSlots], even[kWideSlots];
     // conditions and addresses of the steps are worked out where they are used, not kept in registers
     int end = last, own = t;
@@ -173,7 +181,10 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
 #pragma unroll
         for (int n = 0; n < kPerStep; ++n)
 #pragma unroll
-          for (int j = 0; j < 2 * KS; ++j) x[n][j] = front[j & 1 ? link[n][j >> 1] >> 16 : link[n][j >> 1] & 0xffffu];
+          for (int j = 0; j < 2 * KS; ++j) {
+            const uint32_t u = j & 1 ? link[n][j >> 1] >> 16 : link[n][j >> 1] & 0xffffu;
+            x[n][j] = kScaled ? lds_at(front, u) : front[u];
+          }
         __builtin_amdgcn_sched_barrier(0);
         Word acc[kPerStep];
 #pragma unroll
@@ -182,20 +193,29 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
 #pragma unroll
           for (int j = 1; j < 2 * KS; ++j) acc[n] |= x[n][j];
         }
-#pragma unroll
-        for (int w = 0; w < kWords; ++w) even[i * kWords + w] ^= ~r[i * kWords + w];
+        uint32_t found[2];
         if constexpr (W == 16) {
-          r[i] |= (uint32_t)acc[0] | (uint32_t)acc[kPerStep - 1] << 16;
+          found[0] = (uint32_t)acc[0] | (uint32_t)acc[kPerStep - 1] << 16;
         } else if constexpr (W == 32) {
-          r[i] |= acc[0];
+          found[0] = acc[0];
         } else {
-          r[2 * i] |= (uint32_t)acc[0];
-          r[2 * i + 1] |= (uint32_t)((uint64_t)acc[0] >> 32);
+          found[0] = (uint32_t)acc[0];
+          found[1] = (uint32_t)((uint64_t)acc[0] >> 32);
+        }
+#pragma unroll
+        for (int w = 0; w < kWords; ++w) {
+          const int slot = i * kWords + w;
+          if (kMasks)
+            even[slot] = found[w] & ~r[slot];  // new on this level
+          else
+            even[slot] ^= ~r[slot];
+          r[slot] |= found[w];
         }
       }, kEach);
       __syncthreads();
-      uint32_t* const keep = kept + (size_t)(l / 2) * level_words + (uint32_t)own;
+      uint32_t* const keep = (kMasks ? group_masks + (size_t)(l - 1) * level_words : kept + (size_t)(l / 2) * level_words) + (uint32_t)own;
       uint32_t all = ~0u;
+      int fresh = 0;
       wide_steps([&](auto step) {
         constexpr int i = decltype(step)::value;
         if (i > end) return;
@@ -209,10 +229,21 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
           front[v] = (uint64_t)r[2 * i] | (uint64_t)r[2 * i + 1] << 32;
         }
 #pragma unroll
-        for (int w = 0; w < kWords; ++w) all &= r[i * kWords + w];
+        for (int w = 0; w < kWords; ++w) {
+          all &= r[i * kWords + w];
+          if (kMasks) {
+            keep[(i * kWords + w) * kWideThreads] = even[i * kWords + w];
+            fresh += __popc(even[i * kWords + w]);
+          }
+        }
       }, kEach);
+      if (kMasks) {
+        fresh = wave_sum_int(fresh);
+        if (lane == 0 && fresh != 0)
+          atomicAdd((unsigned long long*)&wv.ltot[(size_t)(s_first / 64) * wv.Lcap + l], (unsigned long long)fresh);
+      }
       if (__ballot(all != ~0u) != 0 && lane == 0) s_more = l;
-      if ((l & 1) != 0 && l < wv.depth)
+      if (!kMasks && (l & 1) != 0 && l < wv.depth)
         wide_steps([&](auto step) {
           constexpr int i = decltype(step)::value;
           if (i > end) return;
@@ -224,6 +255,12 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
         deep = l;
         break;
       }
+    }
+    if constexpr (kMasks) {
+      for (int l = deep + 1; l <= wv.depth; ++l)
+        for (int i = 0; i < wv.slots; ++i) group_masks[((size_t)(l - 1) * wv.slots + i) * kWideThreads + t] = 0;
+      __syncthreads();
+      continue;
     }
     const bool missing = s_more == deep;  // pairs out of reach
     int bits = 0;
@@ -350,9 +387,95 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
     }
     __syncthreads();
   }
+  if (kMasks) return;
   SmallView sv{};
   sv.counters = wv.counters;
   small_totals(sv, 0, reached, false, 0.0);
+}
+
+// Index entries of the level kernels from the masks of the search: a workgroup takes a level of a batch of 64 sources
+// (64 / W groups of the search), blockIdx.x = level * G + batch.  Rows follow each other in node order, levels follow
+// each other.  Level 0 is the sources; a level past gv.ltot's last is empty.  Bound by the 16 bytes per node and level
+// that it writes, a kilobyte per wave and store.
+template <int W>
+__global__ void __launch_bounds__(kWideThreads) k_wide_index(WideView wv, GroupView gv) {
+  static_assert(W == 16 || W == 64, "");
+  constexpr int kGroups = 64 / W;
+  __shared__ int s_wave[2][4][kWideThreads / kWave];
+  const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int level = (int)blockIdx.x / gv.G, g = (int)blockIdx.x % gv.G;
+  const int s0 = wv.src_begin + g * 64, count = min(64, wv.src_count - g * 64);
+  long long* const lt = gv.ltot + (size_t)g * gv.Lcap;
+  NodeIdx* const out = gv.idxb + ((size_t)g * gv.Lcap + level) * gv.Npad;
+  const int groups = (wv.src_count + W - 1) / W;
+  const size_t level_words = (size_t)wv.slots * kWideThreads;
+  uint32_t off = 0;
+  for (int l = 0; l < level; ++l) off += l == 0 ? (uint32_t)count : (uint32_t)lt[l];
+  const bool empty = level > wv.depth || (level > 0 && lt[level] == 0);
+  if (level == 0) {
+    if (t < count) gv.datf[(size_t)g * gv.Npad * 128 + t] = 1.0f;
+    if (t == 0) lt[0] = count;
+    for (int l = t; l < gv.Lcap; l += kWideThreads) gv.dag[(size_t)g * gv.Lcap + l] = 0;
+  }
+  for (int b0 = 0; b0 * kWideThreads < gv.Npad; b0 += 4) {  // four blocks of a thousand nodes
+    uint64_t m[4] = {0, 0, 0, 0};
+    if (level == 0) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const unsigned j = (unsigned)((b0 + k) * kWideThreads + t - s0);
+        m[k] = j < (unsigned)count ? 1ull << j : 0ull;
+      }
+    } else if (!empty) {
+      const auto word = [&](int group, int slot) -> uint64_t {
+        return slot < wv.slots ? wv.masks[((size_t)group * wv.depth + (level - 1)) * level_words + (size_t)slot * kWideThreads + t] : 0u;
+      };
+      if constexpr (W == 64) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) m[k] = word(g, 2 * (b0 + k)) | word(g, 2 * (b0 + k) + 1) << 32;
+      } else {
+#pragma unroll
+        for (int i = 0; i < kGroups; ++i) {
+          if (g * kGroups + i >= groups) continue;
+#pragma unroll
+          for (int k = 0; k < 4; k += 2) {
+            const uint64_t x = word(g * kGroups + i, (b0 + k) / 2);
+            m[k] |= (x & 0xffffu) << (i * W);
+            m[k + 1] |= (x >> 16) << (i * W);
+          }
+        }
+      }
+    }
+    int c[4], incl[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) c[k] = __popcll(m[k]);
+#pragma unroll
+    for (int k = 0; k < 4; k += 2) {  // at most 64 x 64 in a wave
+      const int two = wave_scan_incl(c[k] | c[k + 1] << 16, lane);
+      incl[k] = two & 0xffff;
+      incl[k + 1] = two >> 16;
+    }
+    if (lane == kWave - 1) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s_wave[b0 / 4 & 1][k][wave] = incl[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      // lane w (of each 16) has wave w's sum
+      const int x = s_wave[b0 / 4 & 1][k][lane & 15];
+      int upto = x;
+#pragma unroll
+      for (int o = 1; o < 16; o <<= 1) {
+        const int y = __shfl_up(upto, o, 16);
+        if ((lane & 15) >= o) upto += y;
+      }
+      const int before = __builtin_amdgcn_readlane(upto - x, wave), all = __builtin_amdgcn_readlane(upto, 15);
+      const int v = (b0 + k) * kWideThreads + t;
+      if (v < gv.Npad)
+        *reinterpret_cast<ulonglong2*>(&out[v]) = make_ulonglong2(m[k], (unsigned long long)(off + (uint32_t)(before + incl[k] - c[k])));
+      off += (uint32_t)all;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------------------

@@ -111,3 +111,55 @@ def test_wide_path_counts(oracle, name):
         o = oracle.run(*csr, s0, min(cnt, 16), want_sigma=True, threads=8)
         assert np.array_equal(got[0][:min(cnt, 16)].cpu().numpy(), o.sigma.astype(np.float64))
     topo.close()
+
+
+LOADS = {
+    "8 x id in the table": (lambda: gen.random_regular(8191, 8, 1), 0, 700),
+    "fewest nodes with padded rows": (lambda: gen.random_regular(4097, 10, 2), 4000, 97),
+    "64 sources a word": (lambda: gen.random_regular(8192, 5, 3), 1000, 777),
+    "64 sources a word, most nodes": (lambda: gen.random_regular(16384, 4, 4), 16000, 384),
+    "16 sources a word, ragged batch": (lambda: gen.random_regular(16385, 4, 5), 3, 213),
+    "more groups than workgroups": (lambda: gen.random_regular(20011, 3, 6), 0, 4200),
+    "out of reach": (lambda: thinned(17000, 3, 7, 0.5), 10, 300),
+    "out of reach, 64 sources a word": (lambda: thinned(9000, 3, 8, 0.5), 10, 300),
+    "deep": (lambda: gen.torus([90, 95]), 0, 130),
+}
+
+
+@pytest.mark.parametrize("name", LOADS)
+def test_index_entries_from_wide_search(oracle, name):
+    """Loads: the index entries are those of the level search (which runs while profiling is on), so the bits are too."""
+    import torch
+    import paper_2309_13541_amd as a2a
+    make, s0, cnt = LOADS[name]
+    csr = make()
+    print(name, flush=True)
+    topo = a2a.Topology(*csr)
+    demand = torch.rand((topo.N, cnt), dtype=torch.float64, device="cuda") + 0.5
+
+    def run(flags, dem):
+        ws = torch.empty(topo.workspace_bytes(cnt, a2a.WS_LOADS | flags), dtype=torch.uint8, device="cuda")
+        load = torch.full((topo.E,), -7.0, dtype=torch.float64, device="cuda")
+        words = torch.full((2,), -7, dtype=torch.int64, device="cuda")
+        weighted = torch.full((1,), -7.0, dtype=torch.float64, device="cuda")
+        if dem:
+            topo.link_loads_demand(s0, cnt, demand=demand, load=load, weighted_dist=weighted, dist_sum_total=words[:1],
+                                   flags=words[1:], workspace=ws)
+        else:
+            topo.link_loads(s0, cnt, load=load, dist_sum_total=words[:1], flags=words[1:], workspace=ws)
+        torch.cuda.synchronize()
+        return load, words, weighted
+
+    for dem in (False, True):
+        got, least = run(0, dem), run(a2a.WS_MINIMAL, dem)
+        topo.profile_enable(1)
+        ref = run(0, dem)
+        topo.profile_enable(0)
+        for a, b, c in zip(got, least, ref):
+            assert torch.equal(a, b) and torch.equal(a, c)
+        if not dem:
+            o = oracle.run(*csr, s0, cnt, threads=8)
+            # (with path counts beyond 2^53 the level kernels are the only reference)
+            assert o.flags & 1 or np.allclose(got[0].cpu().numpy(), o.load, rtol=1e-11, atol=0)
+            assert int(got[1][0]) == int(o.dist_sum.sum())
+    topo.close()

@@ -14,15 +14,9 @@
 #include <type_traits>
 
 #include "a2a_kernels.h"
+#include "a2a_small_plan.h"
 
 namespace a2a_dev {
-
-constexpr int kSmallThreads = 1024;   // largest workgroup
-constexpr int kSmallUnseen = 255;     // level byte of a node not reached; levels go up to 253
-constexpr int kSmallBatch = 32;       // most sources of a workgroup: they search together, a bit of a word each
-constexpr int kSmallStripes = 16;     // most nodes a thread sorts with their ranks in registers
-constexpr int kSmallChunk = 16;       // partial load rows that are added up before they meet the running sum
-constexpr int kSmallCounters = 4;     // words per workgroup: sum of distances, reached pairs, inexact, demand x distance
 
 struct SmallView {
   // [N][KS] out- and in-neighbours, two per word, in link order, as 8 x id (an LDS offset that costs one addition);
@@ -44,27 +38,6 @@ struct SmallView {
   const double* dem;        // as in GroupView (nullptr: every pair has demand 1)
   long long dem_ld;
 };
-
-// Level bytes of one source.
-__host__ __device__ inline size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
-
-// LDS of a workgroup, in this order: per-node state of its sources (kState... bytes per node and source; two mask
-// words per node in its place while a search runs), node queue (16-bit places, level by level), where each level
-// starts in the queue, cursors, level bytes.
-constexpr int kStateLoads = 16;  // coef, sigma
-constexpr int kStateSigma = 8;   // sigma
-constexpr int kStateSssp = 5;    // cost, chosen link
-__host__ __device__ inline size_t small_state_bytes(int N, int per, int state) {
-  return ((size_t)per * N * state + 7) & ~(size_t)7;
-}
-// Counters per level that the sort of a source's nodes works with: lanes that count the same word wait for each other
-// (64 of them 150 cycles), and few levels mean full ones, so they are spread over groups of eight lanes there.
-__host__ __device__ inline int small_spread(int depth) { return depth < 16 ? 8 : 1; }
-__host__ __device__ inline size_t small_lds_bytes(int N, int per, int depth, int state) {
-  const size_t nq = ((size_t)N + 1) & ~(size_t)1;
-  return small_state_bytes(N, per, state) +
-         (size_t)per * (nq * 2 + (size_t)(depth + 4) * 4 * (1 + small_spread(depth)) + small_level_bytes(N));
-}
 
 template <typename T>
 __device__ __forceinline__ T& lds_at(T* base, uint32_t bytes) {

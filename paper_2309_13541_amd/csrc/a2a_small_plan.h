@@ -1,0 +1,108 @@
+// How calls on topologies whose per-source state fits LDS are cut into workgroups: plain host arithmetic, no HIP, so
+// that it can be checked over its whole range without a device.  Included by a2a_small_kernels.h (the layout functions
+// are constexpr: device code calls them too).
+#pragma once
+
+#include <algorithm>
+#include <cstddef>
+
+namespace a2a_dev {
+
+constexpr int kSmallWave = 64;
+constexpr int kSmallThreads = 1024;   // largest workgroup
+constexpr int kSmallUnseen = 255;     // level byte of a node not reached; levels go up to 253
+constexpr int kSmallBatch = 32;       // most sources of a workgroup: they search together, a bit of a word each
+constexpr int kSmallStripes = 16;     // most nodes a thread sorts with their ranks in registers
+constexpr int kSmallChunk = 16;       // partial load rows that are added up before they meet the running sum
+constexpr int kSmallCounters = 4;     // words per workgroup: sum of distances, reached pairs, inexact, demand x distance
+
+// LDS that one workgroup may ask for (160 KB per compute unit, a little of it taken by fixed arrays).
+constexpr size_t kSmallLds = 160 * 1024 - 1024;
+constexpr int kComputeUnits = 256;
+
+// The link tables hold 8 x id in 16 bits up to here, and ids beyond, up to the nodes that the single-path baseline's
+// state for one source takes in LDS.
+constexpr int kScaledNodes = 8191, kBothTables = 16384;
+
+// Level bytes of one source.
+constexpr size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
+
+// LDS of a workgroup, in this order: per-node state of its sources (kState... bytes per node and source; two mask
+// words per node in its place while a search runs), node queue (16-bit places, level by level), where each level
+// starts in the queue, cursors, level bytes.
+constexpr int kStateLoads = 16;  // coef, sigma
+constexpr int kStateSigma = 8;   // sigma
+constexpr int kStateSssp = 5;    // cost, chosen link
+constexpr size_t small_state_bytes(int N, int per, int state) { return ((size_t)per * N * state + 7) & ~(size_t)7; }
+// Counters per level that the sort of a source's nodes works with: lanes that count the same word wait for each other
+// (64 of them 150 cycles), and few levels mean full ones, so they are spread over groups of eight lanes there.
+constexpr int small_spread(int depth) { return depth < 16 ? 8 : 1; }
+constexpr size_t small_lds_bytes(int N, int per, int depth, int state) {
+  const size_t nq = ((size_t)N + 1) & ~(size_t)1;
+  return small_state_bytes(N, per, state) +
+         (size_t)per * (nq * 2 + (size_t)(depth + 4) * 4 * (1 + small_spread(depth)) + small_level_bytes(N));
+}
+
+// Threads per source: a level of the search has a few percent of the nodes, a lane each.
+constexpr int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 256 : 512; }
+
+// The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
+constexpr int small_max_nodes(int ell_words) { return ell_words == 2 ? 9 : 20 / ell_words; }
+
+enum class SmallWhat { kLoads, kSigma, kDist, kSssp };
+
+// Nodes that a thread may own: its registers hold the loads of their links, or the bit planes of their distances.
+constexpr int small_most_nodes(SmallWhat what, int ell_words) {
+  return what == SmallWhat::kLoads ? small_max_nodes(ell_words) : what == SmallWhat::kSssp ? 64 : 8;
+}
+// Threads that each of `per` sources of a workgroup can have at the most.
+constexpr int small_source_threads(int per) { return kSmallThreads / per / kSmallWave * kSmallWave; }
+
+struct SmallCut {
+  int per, tg, ts;                 // as in SmallView
+  int per_wg;
+  int threads, workgroups, nodes;  // of a workgroup, of the whole call, nodes per thread
+  size_t lds;
+};
+
+// How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
+// do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
+// while there are workgroups for every compute unit; as many rounds as it then takes to have one
+// workgroup for each place on the chip, so that the rows of partial loads stay few.
+inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallWhat what) {
+  const auto up = [](int x) { return (x + kSmallWave - 1) / kSmallWave * kSmallWave; };
+  SmallCut c{};
+  const int state = what == SmallWhat::kLoads ? kStateLoads : what == SmallWhat::kSigma ? kStateSigma : kStateSssp;
+  const int most = small_most_nodes(what, ell_words);
+  int tg = small_threads(N), per = 1;
+  if (what == SmallWhat::kDist) {
+    tg = std::min(kSmallThreads, up(N));
+    c.lds = (size_t)N * 8;
+  } else {
+    const int want = std::max(1, std::min(kSmallThreads / kSmallWave, src_count / kComputeUnits));
+    const int least = std::min(tg, 256);
+    const int stripes = what == SmallWhat::kSssp ? kSmallStripes : N;  // nodes a thread of a source may sort
+    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds &&
+           N <= stripes * small_source_threads(per + 1))
+      ++per;
+    // three sources leave 64 of the 1024 threads unused, which can be too few for the nodes
+    while (per > 1 && N > most * per * small_source_threads(per)) --per;
+    tg = std::min(tg, small_source_threads(per));
+    while (N > stripes * tg) tg += kSmallWave;
+    c.lds = small_lds_bytes(N, per, depth, state);
+  }
+  while (N > most * per * tg) tg += kSmallWave;
+  c.per = per;
+  c.tg = tg;
+  c.threads = per * tg;
+  const int resident = (int)std::max<size_t>(1, std::min<size_t>(kSmallThreads / c.threads, kSmallLds / c.lds));
+  const long long at_once = (long long)per * kComputeUnits * resident;
+  c.per_wg = (int)std::min<long long>((src_count + at_once - 1) / at_once, kSmallBatch / per) * per;
+  c.workgroups = (src_count + c.per_wg - 1) / c.per_wg;
+  c.nodes = (N + c.threads - 1) / c.threads;
+  // 1.25 times an average level: most levels in one go
+  c.ts = std::min(tg, up((int)((size_t)N * 5 / 4 / (size_t)std::max(depth, 1))));
+  return c;
+}
+
+}  // namespace a2a_dev

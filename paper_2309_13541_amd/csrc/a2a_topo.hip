@@ -403,9 +403,6 @@ inline unsigned grid_for(int G, int blocks_per_batch, int inflight = kXcd) {
 // byte offsets.
 constexpr int32_t kMaxNodes = 4 * 1024 * 1024;
 
-// The link tables hold 8 x id in 16 bits up to here, and ids beyond, up to the nodes that the single-path baseline's
-// state for one source takes in LDS.
-constexpr int32_t kScaledNodes = 8191, kBothTables = 16384;
 constexpr int32_t kPaddedRows = 4096;  // nodes above which the in-link table has whole slots of the wide search
 
 // Nominal lane layout of a level for the profile's kernel classes (the kernels pick per batch,
@@ -667,10 +664,6 @@ int probe_depth(const a2a_topo* t, int* deepest_of, int32_t* depth_out) {
 
 // --- topologies whose per-source state fits LDS ------------------------------------------------------
 
-// LDS that one workgroup may ask for (160 KB per compute unit, a little of it taken by fixed arrays).
-constexpr size_t kSmallLds = 160 * 1024 - 1024;
-constexpr int kComputeUnits = 256;
-
 // Words per node of the link tables (two links a word) for a largest in- or out-degree, 0: no tables.
 int ell_words_for(int32_t N, int32_t degree) {
   if (N > kWideMost || degree > 16 || degree < 1) return 0;
@@ -701,55 +694,22 @@ struct SmallPlan {
   size_t lds = 0;
 };
 
-// Threads per source: a level of the search has a few percent of the nodes, a lane each.
-int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 256 : 512; }
-
-// The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
-constexpr int small_max_nodes(int ell_words) { return ell_words == 2 ? 9 : 20 / ell_words; }
-
-enum class SmallWhat { kLoads, kSigma, kDist, kSssp };
-
-// How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
-// do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
-// while there are workgroups for every compute unit; as many rounds as it then takes to have one
-// workgroup for each place on the chip, so that the rows of partial loads stay few.
 SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
+  const SmallCut c = small_cut(t->N, t->level_bound, t->ell_words, src_count, what);
   SmallPlan p;
-  const int N = t->N, depth = t->level_bound;
-  const int state = what == SmallWhat::kLoads ? kStateLoads : what == SmallWhat::kSigma ? kStateSigma : kStateSssp;
-  // nodes a thread may own: its registers hold the loads of their links, or the bit planes of their distances
-  const int most = what == SmallWhat::kLoads ? small_max_nodes(t->ell_words) : what == SmallWhat::kSssp ? 64 : 8;
-  int tg = small_threads(N), per = 1;
-  if (what == SmallWhat::kDist) {
-    tg = std::min(kSmallThreads, (int)align_up((size_t)N, kWave));
-    p.lds = (size_t)N * 8;
-  } else {
-    const int want = std::max(1, std::min(kSmallThreads / kWave, src_count / kComputeUnits));
-    const int least = std::min(tg, 256);
-    const int stripes = what == SmallWhat::kSssp ? kSmallStripes : N;  // nodes a thread of a source may sort
-    while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds &&
-           N <= stripes * (kSmallThreads / (per + 1) / kWave * kWave))
-      ++per;
-    tg = std::min(tg, kSmallThreads / per / kWave * kWave);
-    while (N > stripes * tg) tg += kWave;
-    p.lds = small_lds_bytes(N, per, depth, state);
-  }
-  while (N > most * per * tg) tg += kWave;
-  p.T = per * tg;
-  const int resident = (int)std::max<size_t>(1, std::min<size_t>(kSmallThreads / p.T, kSmallLds / p.lds));
-  const long long at_once = (long long)per * kComputeUnits * resident;
-  p.sv.per_wg = std::min((int)((src_count + at_once - 1) / at_once), kSmallBatch / per) * per;
-  p.workgroups = (src_count + p.sv.per_wg - 1) / p.sv.per_wg;
-  p.nodes = (N + p.T - 1) / p.T;
+  p.T = c.threads;
+  p.workgroups = c.workgroups;
+  p.nodes = c.nodes;
+  p.lds = c.lds;
   p.sv.out = t->d_ell_out;
   p.sv.in = t->d_ell_in;
-  p.sv.N = N;
-  p.sv.per = per;
-  p.sv.tg = tg;
-  p.sv.qshift = N <= kScaledNodes ? 3 : 0;
-  // 1.25 times an average level: most levels in one go
-  p.sv.ts = std::min(tg, (int)align_up((size_t)N * 5 / 4 / (size_t)std::max(depth, 1), kWave));
-  p.sv.depth = depth;
+  p.sv.N = t->N;
+  p.sv.per = c.per;
+  p.sv.tg = c.tg;
+  p.sv.ts = c.ts;
+  p.sv.per_wg = c.per_wg;
+  p.sv.qshift = t->N <= kScaledNodes ? 3 : 0;
+  p.sv.depth = t->level_bound;
   p.sv.src_count = src_count;
   return p;
 }

@@ -49,6 +49,31 @@ def test_edges_match_oracle(a2a, oracle, name, shape, s0, cnt):
     topo.close()
 
 
+def circulant(nodes, offsets):
+    return gen.csr_from_rows([[(u + o) % nodes for o in offsets] for u in range(nodes)])
+
+
+# Three sources of a workgroup leave too few threads for 1921 to 2048 nodes with 11 to 16 links each: two are taken then.
+# The second shape is so deep that LDS allows no fourth source.
+THREES = {
+    "2000 nodes, 12 links, 800 sources": (2000, [1, -1, 2, -2, 3, -3, 4, -4, 5, -5, 6, -6], 5, 800),
+    "2048 nodes, 12 links, all sources": (2048, [1, 2, 3, 4, 5, -1, -2, -3, -4, 1, 2, -1], 0, 2048),
+}
+
+
+@pytest.mark.parametrize("name", THREES)
+def test_too_many_nodes_for_three_sources(a2a, oracle, name):
+    nodes, offsets, s0, cnt = THREES[name]
+    rp, col = circulant(nodes, offsets)
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    o = oracle.run(rp, col, s0, cnt, threads=8)
+    load, dsum, flags = run_link_loads(topo, s0, cnt)
+    assert_loads_close(load, o.load)
+    assert dsum == int(o.dist_sum.sum()) and flags == o.flags
+    topo.close()
+
+
 @pytest.mark.parametrize("nodes", [32, 33, 254, 255, 256])
 def test_deepest_levels(a2a, oracle, nodes):
     """Directed rings: as many levels as nodes.  Levels fit a byte, with one value for nodes not reached, up to 253."""

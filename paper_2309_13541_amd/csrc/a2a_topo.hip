@@ -895,8 +895,10 @@ int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int*
 // Link loads by the level kernels: whether the levels of a group of G batches come from the wide search (link table
 // there, whole slots of rows in it, masks of all levels fit the memory of the level search's).  Search and index entries
 // before and after: 16384 nodes of degree 4 490 -> 250 us, 2501 sources of 20011 nodes 190 -> 102 us, 65536 nodes of
-// degree 8 10.4 -> 6.2 ms.  While profiling is on the level search runs, whose launches the profile knows.  The table of up to 8191
-// nodes has 8 x id, which is the place of a 64-bit word.
+// degree 8 10.4 -> 6.2 ms; with many levels the whole call: torus 128x128 (128 levels) 34.8 -> 32.0 ms, 4x2000 (1002)
+// 47.0 -> 40.6 ms, ring of 8000 (4000) 286 -> 233 ms, so there is no limit on them.  While profiling is on
+// the level search runs, whose launches the profile knows.  The table of up to 8191 nodes has 8 x id, which is the place
+// of a 64-bit word.
 int wide_masks_sources(const a2a_topo* t) { return t->N <= kBothTables ? 64 : 16; }  // a word
 int wide_masks_slots(const a2a_topo* t) {
   return wide_masks_sources(t) == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads)

@@ -409,9 +409,14 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_index(WideView wv, GroupV
   NodeIdx* const out = gv.idxb + ((size_t)g * gv.Lcap + level) * gv.Npad;
   const int groups = (wv.src_count + W - 1) / W;
   const size_t level_words = (size_t)wv.slots * kWideThreads;
-  uint32_t off = 0;
-  for (int l = 0; l < level; ++l) off += l == 0 ? (uint32_t)count : (uint32_t)lt[l];
   const bool empty = level > wv.depth || (level > 0 && lt[level] == 0);
+  if (empty && level > 1 && lt[level - 1] == 0) return;  // past the batch's first empty level: nothing looks at it
+  // 64 levels at a time (one after the other, loads of a ring of 8000 nodes, 4000 levels, took 372 ms instead of 233, and
+  // 286 with the level search).  What is read here stays below a quarter of what is written.
+  uint32_t off = 0;
+  for (int l = lane; l < level; l += kWave) off += l == 0 ? (uint32_t)count : (uint32_t)lt[l];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) off += (uint32_t)__shfl_xor((int)off, o, kWave);
   if (level == 0) {
     if (t < count) gv.datf[(size_t)g * gv.Npad * 128 + t] = 1.0f;
     if (t == 0) lt[0] = count;

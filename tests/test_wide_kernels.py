@@ -123,6 +123,9 @@ LOADS = {
     "out of reach": (lambda: thinned(17000, 3, 7, 0.5), 10, 300),
     "out of reach, 64 sources a word": (lambda: thinned(9000, 3, 8, 0.5), 10, 300),
     "deep": (lambda: gen.torus([90, 95]), 0, 130),
+    "2500 levels": (lambda: gen.bidirectional_ring(5000), 4900, 100),
+    # a source's levels end with the chain: batches of 2200 to 2400 levels, most of a topology's 4999 empty
+    "4999 levels, batches that end early": (lambda: gen.csr_from_rows([[u + 1] for u in range(4999)] + [[]]), 2600, 200),
 }
 
 

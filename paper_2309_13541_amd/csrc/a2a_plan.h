@@ -1,12 +1,32 @@
-// How calls on topologies whose per-source state fits LDS are cut into workgroups: plain host arithmetic, no HIP, so
-// that it can be checked over its whole range without a device.  Included by a2a_small_kernels.h (the layout functions
-// are constexpr: device code calls them too).
+// How calls are cut into workgroups: plain host arithmetic, no HIP, so that it can be checked over its whole range
+// without a device.  Included by a2a_small_kernels.h (the layout functions are constexpr: device code calls them too).
 #pragma once
 
 #include <algorithm>
 #include <cstddef>
 
 namespace a2a_dev {
+
+// ---------------------------------------------------------------------------------------
+// level kernels
+// ---------------------------------------------------------------------------------------
+
+// A launch has less than 2^32 threads: the count wraps there, and the rest is left out without an error.
+constexpr long long kMostThreads = 0xffffffffll;
+
+// Levels that a workgroup of the index kernel takes one after the other, of `levels` in all.  units: groups of 8 batches
+// x blocks of 64 nodes; blocks: workgroups that a launch has for each piece of the levels.  All levels, unless that leaves
+// most of the chip idle; then one, or as many as it takes for the pieces to fit a launch (64 sources of 20000 nodes in
+// a ring, 10001 levels: 1.3e10 threads with a level each).
+inline int offset_levels(long long units, long long blocks, int threads, int levels) {
+  if (units >= 2048) return levels;
+  const long long pieces = std::max(1ll, kMostThreads / threads / blocks);
+  return (int)((levels + pieces - 1) / pieces);
+}
+
+// ---------------------------------------------------------------------------------------
+// topologies whose per-source state fits LDS
+// ---------------------------------------------------------------------------------------
 
 constexpr int kSmallWave = 64;
 constexpr int kSmallThreads = 1024;   // largest workgroup

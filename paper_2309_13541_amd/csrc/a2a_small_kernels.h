@@ -14,7 +14,7 @@
 #include <type_traits>
 
 #include "a2a_kernels.h"
-#include "a2a_small_plan.h"
+#include "a2a_plan.h"
 
 namespace a2a_dev {
 

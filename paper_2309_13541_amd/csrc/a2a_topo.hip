@@ -542,8 +542,7 @@ int run_fwd(const Run& r, const GroupView& gv, int depth) {
     const int idx_depth = gv.dem != nullptr ? depth + 1 : depth;
     ProfScope ps(t, PROF_OFFSETS, r.st);
     if (idx_depth >= 1) k_scan_blocks<<<(unsigned)(gv.G * idx_depth), kWave, 0, r.st>>>(gv, idx_depth);
-    // one workgroup per (super-batch, 64 nodes) works through all levels, unless that leaves most of the chip idle
-    const int levels = (long long)gv.SB * L.nb64 >= 2048 ? idx_depth + 1 : 1;
+    const int levels = offset_levels((long long)gv.SB * L.nb64, grid_for(gv.SB, L.nb64), kBfsBlock, idx_depth + 1);
     const int chunks = (idx_depth + levels) / levels;
     k_write_offsets<<<grid_for(gv.SB, L.nb64 * chunks), kBfsBlock, 0, r.st>>>(gv, idx_depth, levels);
   }
@@ -936,7 +935,7 @@ int run_index(const Run& r, const GroupView& gv, int top) {
   else                                                                                                               \
     k_wide_dist<64, KS, 6, kWideMasks, true><<<workgroups, kWideThreads, lds, r.st>>>(wv)
   SMALL_BY_WORDS(WIDE_MASKS)
-  const unsigned blocks = (unsigned)(gv.G * (top + 1));
+  const unsigned blocks = (unsigned)(gv.G * (top + 1));  // 2^32 threads: the entries alone would take 290 GB
   W == 16 ? k_wide_index<16><<<blocks, kWideThreads, 0, r.st>>>(wv, gv) : k_wide_index<64><<<blocks, kWideThreads, 0, r.st>>>(wv, gv);
   HIP_TRY(hipGetLastError());
   r.lanes_per_node.clear();

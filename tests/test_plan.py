@@ -1,15 +1,18 @@
-"""How calls on small topologies are cut into workgroups (csrc/a2a_small_plan.h, plain host arithmetic), checked over the
-range of nodes, link table widths, depths and source counts that the kernels take: no device needed."""
+"""How calls are cut into workgroups (csrc/a2a_plan.h, plain host arithmetic), checked over the range of nodes, link table
+widths, depths and source counts that the kernels take: no device needed, but for the call that shows the result."""
 import os
 import subprocess
 
+import numpy as np
 import pytest
+
+import a2a_inputs as gen
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 CHECK = r"""
 #include <cstdio>
-#include "a2a_small_plan.h"
+#include "a2a_plan.h"
 using namespace a2a_dev;
 
 static long long bad = 0, seen = 0;
@@ -74,3 +77,47 @@ def test_cuts_fit_a_workgroup(compiled):
     """At most 1024 threads (three sources of a topology of 1921 to 2048 nodes once got 1152), within LDS, every node and
     every source with a place."""
     assert compiled("cuts", CHECK).returncode == 0
+
+
+PIECES = r"""
+#include <cstdio>
+#include "a2a_plan.h"
+using namespace a2a_dev;
+
+int main() {
+  long long bad = 0, seen = 0;
+  for (long long nb64 = 4; nb64 <= 65536; nb64 += nb64 < 2100 ? 4 : 1024)  // up to 4 Mi nodes, a multiple of 256
+    for (long long SB = 1; SB <= 2048; SB *= 2)
+      for (long long levels = 1; levels <= nb64 * 64; levels = levels * 3 / 2 + 1) {
+        const long long blocks = (SB + 7) / 8 * 8 * nb64;
+        if (blocks * 512 > kMostThreads) continue;  // (more than 60 TB of masks)
+        const long long each = offset_levels(SB * nb64, blocks, 512, (int)levels), pieces = (levels - 1 + each) / each;
+        ++seen;
+        if (each < 1 || each > levels || pieces * each < levels || pieces * blocks * 512 > kMostThreads)
+          if (++bad <= 10) std::printf("%lld blocks of nodes, %lld super-batches, %lld levels: %lld a workgroup\n", nb64, SB, levels, each);
+      }
+  std::printf("%lld shapes, %lld bad\n", seen, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_index_launches_stay_below_2_32_threads(compiled):
+    assert compiled("pieces", PIECES).returncode == 0
+
+
+@pytest.mark.gpu
+def test_path_counts_of_ten_thousand_levels():
+    """A bidirectional ring of 20000 nodes: the index entries of its levels take more than one level a workgroup."""
+    import paper_2309_13541_amd as a2a
+    from gpu_helpers import run_distances
+    n, s0, cnt = 20000, 77, 3
+    topo = a2a.Topology(*gen.bidirectional_ring(n))
+    dist, sigma, dsum, unr, flags = run_distances(topo, s0, cnt)
+    for i in range(cnt):
+        away = (np.arange(n) - (s0 + i)) % n
+        want = np.minimum(away, n - away)
+        assert np.array_equal(dist[i], want) and np.array_equal(sigma[i], np.where(want == n // 2, 2.0, 1.0))
+        assert dsum[i] == want.sum()
+    assert unr == 0 and flags == 0
+    topo.close()

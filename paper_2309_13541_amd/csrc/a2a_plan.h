@@ -78,6 +78,13 @@ constexpr int small_most_nodes(SmallWhat what, int ell_words) {
 // Threads that each of `per` sources of a workgroup can have at the most.
 constexpr int small_source_threads(int per) { return kSmallThreads / per / kSmallWave * kSmallWave; }
 
+// Single-path baseline in 32-bit integers: a link carries at most every commodity of the call and a path has at most
+// `depth` links, so no cost reaches 2^32 - 1, which stands for "none".  (Commodities of a source handed on by a node, 28
+// bits, are below N, at most 16384; those of a link, 32 bits, below N squared.)
+constexpr bool sssp_costs_fit(int depth, int src_count, int N) {
+  return (long long)depth * src_count * (N - 1) < 0xffffffffll;
+}
+
 struct SmallCut {
   int per, tg, ts;                 // as in SmallView
   int per_wg;

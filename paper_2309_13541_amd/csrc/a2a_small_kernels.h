@@ -794,6 +794,7 @@ struct SmallSssp {
   uint32_t* handed;       // [sources of the iteration][N]: paths that end in or pass through the node, + place << 28
 };
 constexpr int kHandedShift = 28;
+static_assert(kBothTables < 1 << kHandedShift, "paths from one source, and the place among 16 links above them");
 
 // Sources [per_wg * workgroup, + per_wg) of an iteration; sv.level: the levels of its first source.  Costs are
 // below 2^32 - 1 (the host checks).

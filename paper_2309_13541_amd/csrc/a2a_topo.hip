@@ -1013,12 +1013,11 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
 }
 
 // Whether a call of the single-path baseline takes the small kernels: its state for one source fits LDS, levels fit a
-// byte (and, with more than 8191 nodes, the search's four bit planes), and no cost can reach 2^32 - 1 (a link
-// carries at most every commodity of the call).
+// byte (and, with more than 8191 nodes, the search's four bit planes), and costs fit 32 bits.
 bool small_sssp_fits(const a2a_topo* t, int32_t src_count) {
   return t->ell_words > 0 && t->N <= kBothTables && t->level_bound < (t->N <= kScaledNodes ? kSmallUnseen - 1 : 16) &&
          small_lds_bytes(t->N, 1, t->level_bound, kStateSssp) <= kSmallLds &&
-         (double)t->level_bound * src_count * (t->N - 1) < 4294967295.0;
+         sssp_costs_fit(t->level_bound, src_count, t->N);
 }
 
 template <int KS>

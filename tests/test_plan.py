@@ -106,6 +106,37 @@ def test_index_launches_stay_below_2_32_threads(compiled):
     assert compiled("pieces", PIECES).returncode == 0
 
 
+def bottleneck(n, sources, chain):
+    """`sources` nodes in a tree of eight links a node to its root, a chain from there, two equal ways at its end, and a
+    tree of eight links a node to all the others: every commodity of the first nodes to the last ones takes the chain."""
+    rows = [[(i - 1) // 8] if i > 0 else [sources] for i in range(sources)]
+    rows += [[sources + i + 1] for i in range(chain - 1)] + [[sources + chain, sources + chain + 1]]
+    rows += [[sources + chain + 2]] * 2
+    first, last = sources + chain + 2, n
+    rows += [[w for w in range(first + 8 * (v - first) + 1, first + 8 * (v - first) + 9) if w < last] for v in range(first, last)]
+    return gen.csr_from_rows(rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("over", [0, 1])
+def test_single_path_costs_near_2_32(oracle, over):
+    """The most sources whose costs are kept in 32 bits, and one more: costs come to 3.05e9, and the choice between the
+    two ways behind the chain is made on sums of that size."""
+    import paper_2309_13541_amd as a2a
+    from test_sssp import run_sssp_gpu
+    rp, col = bottleneck(8191, 2100, 242)
+    topo = a2a.Topology(rp, col)
+    assert topo.level_bound == 253  # as deep as the kernels with 32-bit costs take
+    sources = (2 ** 32 - 2) // (topo.level_bound * (topo.N - 1)) + over
+    assert sources <= 2100
+    want, dsum, unr = oracle.sssp(rp, col, 0, sources, iter_sources=64)
+    assert 2 ** 31 < 242 * int(want[2100]) < 2 ** 32  # the chain's first link
+    load, got_sum, flags = run_sssp_gpu(topo, 0, sources, iter_sources=64)
+    assert np.array_equal(load, want.astype(np.float64))
+    assert got_sum == int(dsum.sum()) and flags == (a2a.FLAG_UNREACHABLE if unr else 0)
+    topo.close()
+
+
 @pytest.mark.gpu
 def test_path_counts_of_ten_thousand_levels():
     """A bidirectional ring of 20000 nodes: the index entries of its levels take more than one level a workgroup."""

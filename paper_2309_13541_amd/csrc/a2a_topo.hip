@@ -44,8 +44,7 @@ struct a2a_topo {
   int32_t dmax = 0;
   int32_t dmax_in = 0;  // largest in-degree
   int32_t level_bound = 0;  // largest finite D(s,t), found by the level probe at create
-  // The handle's memory: one device block and one pinned host block.  The host block first holds what is uploaded
-  // and then only the read-back slots.
+  // The handle's memory: one device block and one pinned host block (HandleBlocks).
   struct Arena {
     int device = -1;
     size_t device_bytes = 0, host_bytes = 0;
@@ -127,12 +126,12 @@ class Use {
 
 // Blocks of destroyed handles, kept for the next ones: a program that evaluates one small topology after the other
 // would spend most of its time in hipMalloc, hipHostMalloc and hipFree otherwise.  At most kKept blocks of at most
-// kLargest bytes each are kept (an idle program holds 8 MiB of each kind of memory at the most); they are given back
+// kPooledBytes each are kept (an idle program holds 8 MiB of each kind of memory at the most); they are given back
 // when an allocation fails.  A block comes here only when the device has finished all work that may use it.
 class ArenaPool {
  public:
   using Arena = a2a_topo::Arena;
-  static constexpr size_t kKept = 4, kLargest = 2u << 20, kGrain = 64u << 10;
+  static constexpr size_t kKept = 4, kGrain = 64u << 10;
 
   bool take(size_t device_bytes, size_t host_bytes, Arena* out) {
     int device = -1;
@@ -167,7 +166,7 @@ class ArenaPool {
     const bool other = hipGetDevice(&device) == hipSuccess && device != a.device;
     if (other) (void)hipSetDevice(a.device);
     const bool idle = settled || hipDeviceSynchronize() == hipSuccess;  // as hipFree would wait
-    bool keep = idle && a.d != nullptr && a.h != nullptr && a.device_bytes <= kLargest && a.host_bytes <= kLargest;
+    bool keep = idle && a.d != nullptr && a.h != nullptr && a.device_bytes <= kPooledBytes && a.host_bytes <= kPooledBytes;
     if (keep) {
       std::lock_guard<std::mutex> lock(mutex_);
       keep = kept_.size() < kKept;
@@ -1168,51 +1167,39 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
   t->N = N;
   t->E = E;
   t->dmax = dmax;
-  // What is uploaded lies at the same offsets in the host and the device block; scratch follows on the device,
-  // read-back slots and the probe's results on the host.
-  size_t off = 0;
-  const auto part = [&off](size_t bytes) {
-    const size_t at = off;
-    off += align_up(bytes, 256);
-    return at;
-  };
-  const size_t pb = ((size_t)N + 1) * sizeof(int32_t), cb = (size_t)(E > 0 ? E : 1) * sizeof(int32_t);
-  const size_t eb_out = ell_out.size() * sizeof(uint32_t), eb_in = ell_in.size() * sizeof(uint32_t);
-  const size_t o_out_ptr = part(pb), o_out_col = part(cb), o_in_ptr = part(pb), o_in_col = part(cb);
-  const size_t o_in_link = part(cb), o_ell_out = part(eb_out), o_ell_in = part(eb_in);
-  const size_t o_arrived = part(a2a_topo::kSlots * sizeof(unsigned));
-  const size_t upload = off;
-  const size_t o_scratch = part((size_t)a2a_topo::kSlots * kExtremaGroups * kExtremaWords * sizeof(long long));
-  const size_t device_bytes = off;
-  off = upload;
-  const size_t o_slots = part((size_t)a2a_topo::kSlots * a2a_topo::kSlotWords * sizeof(int64_t));
-  const size_t o_probe = part(((size_t)N + kSmallBatch - 1) / kSmallBatch * sizeof(int));
-  bool ok = arena_pool().take(device_bytes, off, &t->mem);
+  const HandleBlocks m = handle_blocks(N, E, ell_out.size() * sizeof(uint32_t), ell_in.size() * sizeof(uint32_t),
+                                       a2a_topo::kSlots * sizeof(unsigned),
+                                       (size_t)a2a_topo::kSlots * kExtremaGroups * kExtremaWords * sizeof(long long),
+                                       (size_t)a2a_topo::kSlots * a2a_topo::kSlotWords * sizeof(int64_t),
+                                       (size_t)((std::min(N, kScaledNodes) + kSmallBatch - 1) / kSmallBatch) * sizeof(int));
+  bool ok = arena_pool().take(m.device, m.host, &t->mem);
   ok = ok && hipGetSymbolAddress(&t->d_scratch, HIP_SYMBOL(scratch)) == hipSuccess && t->d_scratch != nullptr;
   if (ok) {
     char *const d = t->mem.d, *const h = t->mem.h;
-    t->d_out_ptr = (int32_t*)(d + o_out_ptr);
-    t->d_out_col = (int32_t*)(d + o_out_col);
-    t->d_in_ptr = (int32_t*)(d + o_in_ptr);
-    t->d_in_col = (int32_t*)(d + o_in_col);
-    t->d_in_link = (int32_t*)(d + o_in_link);
-    t->d_ell_out = (uint32_t*)(d + o_ell_out);
-    t->d_ell_in = (uint32_t*)(d + o_ell_in);
-    t->d_arrived = (unsigned*)(d + o_arrived);
-    t->d_scratch_slots = (long long*)(d + o_scratch);
-    t->h_slots = (int64_t*)(h + o_slots);
-    std::memcpy(h + o_out_ptr, row_ptr, pb);
-    if (E > 0) std::memcpy(h + o_out_col, col_idx, cb);
-    std::memcpy(h + o_in_ptr, in_ptr.data(), pb);
-    std::memcpy(h + o_in_col, in_col.data(), cb);
-    std::memcpy(h + o_in_link, in_link.data(), cb);
-    if (eb_out > 0) std::memcpy(h + o_ell_out, ell_out.data(), eb_out);
-    if (eb_in > 0) std::memcpy(h + o_ell_in, ell_in.data(), eb_in);
-    std::memset(h + o_arrived, 0, a2a_topo::kSlots * sizeof(unsigned));
-    ok = hipMemcpyAsync(d, h, upload, hipMemcpyHostToDevice, nullptr) == hipSuccess;
+    t->d_out_ptr = (int32_t*)(d + m.at[kOutPtr]);
+    t->d_out_col = (int32_t*)(d + m.at[kOutCol]);
+    t->d_in_ptr = (int32_t*)(d + m.at[kInPtr]);
+    t->d_in_col = (int32_t*)(d + m.at[kInCol]);
+    t->d_in_link = (int32_t*)(d + m.at[kInLink]);
+    t->d_ell_out = (uint32_t*)(d + m.at[kEllOut]);
+    t->d_ell_in = (uint32_t*)(d + m.at[kEllIn]);
+    t->d_arrived = (unsigned*)(d + m.at[kArrived]);
+    t->d_scratch_slots = (long long*)(d + m.scratch);
+    t->h_slots = (int64_t*)(h + m.slots);
+    const unsigned arrived[a2a_topo::kSlots] = {};
+    const void* const from[kHandleParts] = {row_ptr, E > 0 ? col_idx : in_col.data(), in_ptr.data(), in_col.data(),
+                                            in_link.data(), ell_out.data(), ell_in.data(), arrived};
+    for (int i = 0; i < kHandleParts && ok; ++i) {
+      if (m.bytes[i] == 0) continue;
+      if (m.staged)
+        std::memcpy(h + m.at[i], from[i], m.bytes[i]);
+      else
+        ok = hipMemcpy(d + m.at[i], from[i], m.bytes[i], hipMemcpyHostToDevice) == hipSuccess;
+    }
+    if (ok && m.staged) ok = hipMemcpyAsync(d, h, m.upload, hipMemcpyHostToDevice, nullptr) == hipSuccess;
   }
   // the probe runs after the upload and is waited for
-  if (ok) ok = E > 0 ? probe_depth(t, (int*)(t->mem.h + o_probe), &t->level_bound) == A2A_OK : hipStreamSynchronize(nullptr) == hipSuccess;
+  if (ok) ok = E > 0 ? probe_depth(t, (int*)(t->mem.h + m.probe), &t->level_bound) == A2A_OK : hipStreamSynchronize(nullptr) == hipSuccess;
   if (ok) {
     t->min_loads_bytes = make_layout(t, 64, A2A_WS_LOADS, 0, true, true).total;
     t->min_sigma_bytes = make_layout(t, 64, A2A_WS_SIGMA, 0, true, true).total;

@@ -106,6 +106,37 @@ def test_index_launches_stay_below_2_32_threads(compiled):
     assert compiled("pieces", PIECES).returncode == 0
 
 
+BLOCKS = r"""
+#include <cstdio>
+#include "a2a_plan.h"
+using namespace a2a_dev;
+
+int main() {
+  long long bad = 0, seen = 0;
+  for (long long N = 1; N <= 4 << 20; N = N * 9 / 8 + 1)
+    for (long long d = 0; d <= 64; d = d * 2 + 1) {
+      const size_t ell = N <= 65536 && d <= 16 ? (size_t)N * 32 : 0;
+      const HandleBlocks b = handle_blocks(N, N * d, ell, ell, 256, 1 << 17, 4096, 1024);
+      bool ok = b.device >= b.upload + (1 << 17) && b.host >= 5120;
+      for (int i = 0; i < kHandleParts; ++i)
+        ok &= b.at[i] % 256 == 0 && b.at[i] + b.bytes[i] <= (i + 1 < kHandleParts ? b.at[i + 1] : b.upload);
+      ok &= b.bytes[kOutCol] >= 4 && b.bytes[kInPtr] == ((size_t)N + 1) * 4 && b.bytes[kInLink] >= (size_t)(N * d) * 4;
+      // pinned memory: a copy of the upload only where it is small
+      ok &= b.staged ? b.slots >= b.upload && b.host <= kStagedBytes + 5120 : b.slots == 0 && b.host <= 5120;
+      ++seen;
+      if (!ok && ++bad <= 10) std::printf("N %lld degree %lld: upload %zu host %zu\n", N, d, b.upload, b.host);
+    }
+  std::printf("%lld handles, %lld bad\n", seen, bad);
+  return bad != 0;
+}
+"""
+
+
+def test_pinned_memory_of_a_handle(compiled):
+    """A handle holds no pinned copy of a large upload."""
+    assert compiled("blocks", BLOCKS).returncode == 0
+
+
 def bottleneck(n, sources, chain):
     """`sources` nodes in a tree of eight links a node to its root, a chain from there, two equal ways at its end, and a
     tree of eight links a node to all the others: every commodity of the first nodes to the last ones takes the chain."""

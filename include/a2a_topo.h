@@ -293,30 +293,35 @@ int a2a_tree_lower_bound(int32_t N, int32_t d, double m_bytes, double b_bytes_pe
  * Optional per-kernel timing, for benchmarks (not part of the paper's method).
  * a2a_profile_enable(topo, mode) clears what was gathered so far and sets the mode:
  *   0  off (default);
- *   1  every kernel launch of a2a_distances / a2a_link_loads on this handle is bracketed by two
- *      HIP events on the caller's stream (a few microseconds per launch);
- *   2  as 1, and the forward pass also counts the (source, link) pairs that lie on shortest
- *      paths (one atomic per wavefront: slows the forward kernels down, use on untimed runs).
+ *   1  the kernel launches of the compute calls on this handle (the ones that run with mode 0 too: same
+ *      kernels, same results) are bracketed by two HIP events each on the caller's stream (a few
+ *      microseconds per launch);
+ *   2  every topology goes through the level-by-level kernels, whose forward pass counts the (source,
+ *      link) pairs that lie on shortest paths (one atomic per wavefront: slows the forward kernels
+ *      down); their launches are timed.  Link loads of topologies that other kernels serve with
+ *      mode 0 differ by rounding.  a2a_sssp_loads: as 1.
  * a2a_profile_read waits for the device and sums the event times per kernel class; index
- * A2A_K_* into ms[] / launches[].  One launch serves a level of all batches of a group and every
- * batch picks its own lane layout inside it; a launch is filed under the layout that the group's
- * average level size stands for (FWD_ROWS / FWD_FEW / FWD_SPREAD, BWD_...).  While a mode other
- * than 0 is on, the compute calls wait for the device to read counters back, and every topology goes
- * through the level-by-level kernels that the profile is about (small ones use one kernel per call
- * otherwise; the loads then differ by rounding).  Not thread safe.
+ * A2A_K_* into ms[] / launches[].  In the level kernels one launch serves a level of all batches of
+ * a group and every batch picks its own lane layout inside it; a launch is filed under the layout that the
+ * group's average level size stands for (FWD_ROWS / FWD_FEW / FWD_SPREAD, BWD_...).  While a mode
+ * other than 0 is on, a2a_distances and the link-load calls wait for the device to read counters back;
+ * where their kernels leave no pair counts per level, a search of its own, which is not timed, finds
+ * them in the workspace afterwards.  Not thread safe.
  */
 typedef enum a2a_prof_kernel {
   A2A_K_INIT = 0,  /* level 0 set-up */
   A2A_K_BFS,       /* one BFS level */
-  A2A_K_OFFSETS,   /* row offsets of the level-compact arrays */
-  A2A_K_FWD_ROWS,  /* forward level, one wave per node (well-filled level) */
+  A2A_K_OFFSETS,   /* index entries (masks, row offsets) of the level-compact arrays */
+  A2A_K_FWD_ROWS,  /* forward level, one wave per node (well-filled level; a2a_sssp_loads: every level) */
   A2A_K_FWD_FEW,   /* forward level with few sources per node: lanes = (node, link) or (node, source) */
   A2A_K_FWD_SPREAD, /* forward level, many sources per node, short rows on the level before */
-  A2A_K_BWD_ROWS,  /* backward level, one wave per node */
+  A2A_K_BWD_ROWS,  /* backward level, one wave per node (a2a_sssp_loads: every level) */
   A2A_K_BWD_FEW,   /* backward level, lanes = (node, link) or (node, source) */
   A2A_K_BWD_SPREAD, /* backward level, many sources per node, short rows on the level after */
-  A2A_K_REDUCE,    /* ordered sum of the per-batch link loads */
-  A2A_K_EXTRACT,   /* dist / sigma output of a2a_distances */
+  A2A_K_REDUCE,    /* ordered sum of per-batch or per-workgroup link loads and counters */
+  A2A_K_EXTRACT,   /* dist / sigma output of a2a_distances (level kernels) */
+  A2A_K_SEARCH,    /* search of all levels with its state in LDS (a2a_distances: and the output of dist) */
+  A2A_K_SOURCES,   /* a workgroup's sources from the search (or its levels) to their results, in LDS */
   A2A_K_COUNT
 } a2a_prof_kernel;
 #define A2A_PROF_MAX_LEVELS 64 /* deeper levels are lumped into the last slot */
@@ -334,7 +339,8 @@ typedef struct a2a_profile {
                                                   counts of level l-1 in single precision (the library
                                                   keeps them so while (largest in-degree)^level < 2^24:
                                                   exact, half the bytes) */
-  uint64_t fwd_flavours;                       /* lane layouts the batches' forward levels picked: bit
+  uint64_t fwd_flavours;                       /* lane layouts that the level kernels pick for the batches'
+                                                  forward levels (whichever kernels ran): bit
                                                   3 * layout + p, layout 0 rows, 1 spread, 2 (node, source),
                                                   3 (node, link); p = 0 float -> float, 1 float -> double,
                                                   2 double -> double path counts */

@@ -45,7 +45,7 @@ EXPORTED_SYMBOLS = (
 STATIC_WORKSPACE_BYTES = 32 << 20
 
 PROF_KERNELS = ("init", "bfs", "offsets", "fwd_rows", "fwd_few", "fwd_spread", "bwd_rows", "bwd_few", "bwd_spread",
-                "reduce", "extract")
+                "reduce", "extract", "search", "sources")
 PROF_MAX_LEVELS = 64
 
 HIPCC_FLAGS = [
@@ -284,7 +284,8 @@ class Topology:
             "a2a_link_loads_demand")
 
     def profile_enable(self, mode: int = 1) -> None:
-        """0 off, 1 per-launch events, 2 events + count of shortest-path (source, link) pairs."""
+        """0 off, 1 events around the launches, 2 the same of the level kernels, which then serve every topology, and
+        a count of shortest-path (source, link) pairs."""
         _check(load_library().a2a_profile_enable(self._h, int(mode)), "a2a_profile_enable")
 
     def profile_read(self) -> dict:

@@ -85,7 +85,8 @@ struct a2a_topo {
     int cls, level;
     hipEvent_t beg, end;
   };
-  mutable int prof_mode = 0;  // 0 off, 1 events, 2 events + shortest-path link count
+  mutable int prof_mode = 0;  // 0 off, 1 events, 2 events + shortest-path link count (level kernels)
+  bool level_kernels_only() const { return prof_mode == 2; }
   mutable std::vector<ProfRec> prof_recs;
   mutable int64_t prof_pairs_level[A2A_PROF_MAX_LEVELS] = {};
   mutable int64_t prof_dag_level[A2A_PROF_MAX_LEVELS] = {};
@@ -219,6 +220,7 @@ enum {
   PROF_INIT = A2A_K_INIT, PROF_BFS = A2A_K_BFS, PROF_OFFSETS = A2A_K_OFFSETS, PROF_FWD = A2A_K_FWD_ROWS,
   PROF_FWD_FEW = A2A_K_FWD_FEW, PROF_FWD_SPREAD = A2A_K_FWD_SPREAD, PROF_BWD = A2A_K_BWD_ROWS,
   PROF_BWD_FEW = A2A_K_BWD_FEW, PROF_BWD_SPREAD = A2A_K_BWD_SPREAD, PROF_REDUCE = A2A_K_REDUCE, PROF_EXTRACT = A2A_K_EXTRACT,
+  PROF_SEARCH = A2A_K_SEARCH, PROF_SOURCES = A2A_K_SOURCES,
   PROF_CLASSES = A2A_K_COUNT
 };
 
@@ -370,14 +372,14 @@ inline hipError_t zero_async(void* p, size_t bytes, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Brackets one kernel launch with two events while profiling is on.
+// Brackets one kernel launch with two events while profiling is on (t_ nullptr: not this one).
 struct ProfScope {
   const a2a_topo* t;
   hipStream_t st;
   a2a_topo::ProfRec rec{};
   bool live = false;
   ProfScope(const a2a_topo* t_, int cls, hipStream_t st_, int level = 0) : t(t_), st(st_) {
-    if (t->prof_mode == 0) return;
+    if (t == nullptr || t->prof_mode == 0) return;
     rec.cls = cls;
     rec.level = level;
     if (hipEventCreate(&rec.beg) != hipSuccess) return;
@@ -418,6 +420,7 @@ struct Run {
   int inflight = kXcd;  // batches in flight = XCDs: one batch's node blocks per XCD at a time
   int split = 1;        // waves per block of 64 nodes in the forward / backward kernels (pick_split)
   mutable bool indexed = false;  // run_index has written the group's index entries
+  bool timed = true;             // its launches are part of the profile
   mutable std::vector<double> lanes_per_node;  // profiling only: per level of the current group, pairs / (G*N)
   bool few(int level) const {
     return level >= 0 && level < (int)lanes_per_node.size() && lanes_per_node[level] > 0.0 &&
@@ -479,6 +482,47 @@ int pick_split(const a2a_topo* t, int G, int nb64, bool demand) {
   return split;
 }
 
+// While profiling is on: how full each level of a finished search is, by what it left in gv.ltot (this waits), and which
+// lane layouts the level kernels pick for that.
+int profile_group(const Run& r, const GroupView& gv) {
+  const a2a_topo* t = r.t;
+  const Layout& L = r.L;
+  r.lanes_per_node.clear();
+  if (t->prof_mode == 0) return A2A_OK;
+  try {
+    std::vector<long long> lt((size_t)gv.G * L.Lcap);
+    HIP_TRY(hipMemcpyAsync(lt.data(), gv.ltot, lt.size() * 8, hipMemcpyDeviceToHost, r.st));
+    HIP_TRY(hipStreamSynchronize(r.st));
+    r.lanes_per_node.assign((size_t)L.Lcap, 0.0);
+    int d = 0;
+    for (int g = 0; g < gv.G; ++g)
+      for (int k = 0; k < L.Lcap; ++k) {
+        const long long n = lt[(size_t)g * L.Lcap + k];
+        r.lanes_per_node[k] += (double)n;
+        if (n > 0 && k > d) d = k;
+      }
+    for (int k = 0; k <= d; ++k)
+      t->prof_pairs_level[k < A2A_PROF_MAX_LEVELS ? k : A2A_PROF_MAX_LEVELS - 1] += (int64_t)r.lanes_per_node[k];
+    // which lane layout and precision each batch's kernels pick on each level (the kernels' own rule)
+    for (int g = 0; g < gv.G; ++g)
+      for (int k = 0; k + 1 < L.Lcap; ++k) {
+        const long long* row = &lt[(size_t)g * L.Lcap];
+        const long long here = row[k], after = row[k + 1], before = k > 0 ? row[k - 1] : 0;
+        if (here == 0) continue;
+        if (k >= 1 && L.values)
+          t->prof_fwd_flavours |= 1ull << (3 * pick_flavour(here, before, t->N) + (r.narrow(k) ? 0 : (r.narrow(k - 1) ? 1 : 2)));
+        if (L.loads && (r.demand != nullptr || after > 0))
+          t->prof_bwd_flavours |= 1ull << (2 * pick_flavour(here, after, t->N) + (r.narrow(k) ? 0 : 1));
+      }
+    for (auto& x : r.lanes_per_node) x /= (double)gv.G * (double)t->N;
+    if (d > t->prof_depth) t->prof_depth = d;
+    t->prof_groups++;
+  } catch (const std::bad_alloc&) {
+    return A2A_ERR_NO_MEMORY;
+  }
+  return A2A_OK;
+}
+
 // BFS of one group: levels 1 .. top (the handle's deepest level, one more when the backward pass
 // will look at the empty level after a batch's last one).
 int run_bfs(const Run& r, const GroupView& gv, int top) {
@@ -486,49 +530,15 @@ int run_bfs(const Run& r, const GroupView& gv, int top) {
   const Layout& L = r.L;
   HIP_TRY(zero_async(gv.ltot, (size_t)gv.SB * kSub * L.Lcap * 8, r.st));
   {
-    ProfScope ps(t, PROF_INIT, r.st);
+    ProfScope ps(r.timed ? t : nullptr, PROF_INIT, r.st);
     k_init_group<<<grid_for(gv.SB, L.nb64), kBfsBlock, 0, r.st>>>(gv);
   }
   for (int l = 1; l <= top; ++l) {
-    ProfScope ps(t, PROF_BFS, r.st, l);
+    ProfScope ps(r.timed ? t : nullptr, PROF_BFS, r.st, l);
     k_bfs_level<<<grid_for(gv.SB, L.nb64), kBfsBlock, 0, r.st>>>(t->d_in_ptr, t->d_in_col, gv, l);
   }
   HIP_TRY(hipGetLastError());
-  r.lanes_per_node.clear();
-  if (t->prof_mode) {  // profiling only: how full each level is (this is the one place that waits)
-    try {
-      std::vector<long long> lt((size_t)gv.G * L.Lcap);
-      HIP_TRY(hipMemcpyAsync(lt.data(), gv.ltot, lt.size() * 8, hipMemcpyDeviceToHost, r.st));
-      HIP_TRY(hipStreamSynchronize(r.st));
-      r.lanes_per_node.assign((size_t)L.Lcap, 0.0);
-      int d = 0;
-      for (int g = 0; g < gv.G; ++g)
-        for (int k = 0; k < L.Lcap; ++k) {
-          const long long n = lt[(size_t)g * L.Lcap + k];
-          r.lanes_per_node[k] += (double)n;
-          if (n > 0 && k > d) d = k;
-        }
-      for (int k = 0; k <= d; ++k)
-        t->prof_pairs_level[k < A2A_PROF_MAX_LEVELS ? k : A2A_PROF_MAX_LEVELS - 1] += (int64_t)r.lanes_per_node[k];
-      // which lane layout and precision each batch's kernels pick on each level (the kernels' own rule)
-      for (int g = 0; g < gv.G; ++g)
-        for (int k = 0; k + 1 < L.Lcap; ++k) {
-          const long long* row = &lt[(size_t)g * L.Lcap];
-          const long long here = row[k], after = row[k + 1], before = k > 0 ? row[k - 1] : 0;
-          if (here == 0) continue;
-          if (k >= 1 && L.values)
-            t->prof_fwd_flavours |= 1ull << (3 * pick_flavour(here, before, t->N) + (r.narrow(k) ? 0 : (r.narrow(k - 1) ? 1 : 2)));
-          if (L.loads && (r.demand != nullptr || after > 0))
-            t->prof_bwd_flavours |= 1ull << (2 * pick_flavour(here, after, t->N) + (r.narrow(k) ? 0 : 1));
-        }
-      for (auto& x : r.lanes_per_node) x /= (double)gv.G * (double)t->N;
-      if (d > t->prof_depth) t->prof_depth = d;
-      t->prof_groups++;
-    } catch (const std::bad_alloc&) {
-      return A2A_ERR_NO_MEMORY;
-    }
-  }
-  return A2A_OK;
+  return profile_group(r, gv);
 }
 
 // Row offsets, then sigma for levels 1 .. depth.
@@ -589,6 +599,30 @@ int run_fwd(const Run& r, const GroupView& gv, int depth) {
 int run_fold(const Run& r, const GroupView& gv, int depth) {
   k_fold_counters<<<1, kBlock, 0, r.st>>>(gv, depth, r.misc());
   HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
+// While profiling is on: the levels of a call that other kernels have served, by a level search in its workspace, which
+// is not timed.
+int profile_levels(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, int ws_flags, char* ws,
+                   size_t ws_bytes, hipStream_t st) {
+  if (t->prof_mode == 0) return A2A_OK;
+  Run r;
+  r.t = t;
+  r.L = make_layout(t, src_count, ws_flags, ws_bytes, false, false);
+  if (r.L.G < 1) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  r.ws = ws;
+  r.st = st;
+  r.src_begin = src_begin;
+  r.src_count = src_count;
+  r.demand = demand;
+  r.timed = false;
+  const int nb = (src_count + 63) / 64;
+  for (int b0 = 0; b0 < nb; b0 += r.L.G) {
+    const int rc = run_bfs(r, r.view(b0, std::min(nb - b0, r.L.G)), t->level_bound);
+    if (rc != A2A_OK) return rc;
+  }
+  t->prof_calls++;
   return A2A_OK;
 }
 
@@ -768,7 +802,11 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
   for (int w0 = 0; w0 < p.workgroups; w0 += (int)rows) {
     const int n = std::min(p.workgroups - w0, (int)rows);
     p.sv.wg0 = w0;
-    demand ? small_launch<true>(p, t->ell_words, n, st) : small_launch<false>(p, t->ell_words, n, st);
+    {
+      ProfScope ps(t, PROF_SOURCES, st);
+      demand ? small_launch<true>(p, t->ell_words, n, st) : small_launch<false>(p, t->ell_words, n, st);
+    }
+    ProfScope ps(t, PROF_REDUCE, st);
     k_small_reduce<<<blocks, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
                                               t->d_out_ptr, load, (long long*)ws, tot);
   }
@@ -817,13 +855,17 @@ int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
   for (int w0 = 0; w0 < p.workgroups; w0 += rows) {
     const int n = std::min(p.workgroups - w0, rows);
     p.sv.wg0 = w0;
-    switch (t->ell_words) {
-      case 2: small_launch_out_words<2>(p, out, n, st); break;
-      case 3: small_launch_out_words<3>(p, out, n, st); break;
-      case 4: small_launch_out_words<4>(p, out, n, st); break;
-      case 5: small_launch_out_words<5>(p, out, n, st); break;
-      default: small_launch_out_words<8>(p, out, n, st); break;
+    {
+      ProfScope ps(t, PROF_SOURCES, st);
+      switch (t->ell_words) {
+        case 2: small_launch_out_words<2>(p, out, n, st); break;
+        case 3: small_launch_out_words<3>(p, out, n, st); break;
+        case 4: small_launch_out_words<4>(p, out, n, st); break;
+        case 5: small_launch_out_words<5>(p, out, n, st); break;
+        default: small_launch_out_words<8>(p, out, n, st); break;
+      }
     }
+    ProfScope ps(t, PROF_REDUCE, st);
     // a single workgroup: the counters only
     k_small_reduce<<<1, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
                                          t->d_out_ptr, nullptr, (long long*)ws, tot);
@@ -880,6 +922,7 @@ int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int*
   *workgroups = (int)std::min<size_t>({(size_t)(n + W - 1) / W, (size_t)kComputeUnits, room});
   wv->masks = (uint32_t*)ws;
   wv->counters = (long long*)(ws + *workgroups * masks);
+  ProfScope ps(t, PROF_SEARCH, st);
 #define WIDE_SEARCH(KS)                                                       \
   switch (W) {                                                                \
     case 16: wide_launch_words<16, KS, kOut>(*wv, *workgroups, st); break;  \
@@ -894,9 +937,8 @@ int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int*
 // there, whole slots of rows in it, masks of all levels fit the memory of the level search's).  Search and index entries
 // before and after: 16384 nodes of degree 4 490 -> 250 us, 2501 sources of 20011 nodes 190 -> 102 us, 65536 nodes of
 // degree 8 10.4 -> 6.2 ms; with many levels the whole call: torus 128x128 (128 levels) 34.8 -> 32.0 ms, 4x2000 (1002)
-// 47.0 -> 40.6 ms, ring of 8000 (4000) 286 -> 233 ms, so there is no limit on them.  While profiling is on
-// the level search runs, whose launches the profile knows.  The table of up to 8191 nodes has 8 x id, which is the place
-// of a 64-bit word.
+// 47.0 -> 40.6 ms, ring of 8000 (4000) 286 -> 233 ms, so there is no limit on them.  The table of up
+// to 8191 nodes has 8 x id, which is the place of a 64-bit word.
 int wide_masks_sources(const a2a_topo* t) { return t->N <= kBothTables ? 64 : 16; }  // a word
 int wide_masks_slots(const a2a_topo* t) {
   return wide_masks_sources(t) == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads)
@@ -905,7 +947,7 @@ int wide_masks_slots(const a2a_topo* t) {
 bool wide_masks_fit(const a2a_topo* t, const Layout& L, int G) {
   const size_t room = L.off_bm - L.off_seen + (size_t)L.SB * L.Lcap * L.Npad * kSub * 8;
   const size_t groups = (size_t)G * (64 / wide_masks_sources(t));
-  return t->ell_words > 0 && t->N > kPaddedRows && t->level_bound >= 1 && t->prof_mode == 0 &&
+  return t->ell_words > 0 && t->N > kPaddedRows && t->level_bound >= 1 && !t->level_kernels_only() &&
          groups * t->level_bound * wide_masks_slots(t) * kWideThreads * sizeof(uint32_t) <= room;
 }
 
@@ -933,12 +975,17 @@ int run_index(const Run& r, const GroupView& gv, int top) {
     k_wide_dist<64, KS, 6, kWideMasks><<<workgroups, kWideThreads, lds, r.st>>>(wv);                                 \
   else                                                                                                               \
     k_wide_dist<64, KS, 6, kWideMasks, true><<<workgroups, kWideThreads, lds, r.st>>>(wv)
-  SMALL_BY_WORDS(WIDE_MASKS)
+  {
+    ProfScope ps(t, PROF_SEARCH, r.st);
+    SMALL_BY_WORDS(WIDE_MASKS)
+  }
   const unsigned blocks = (unsigned)(gv.G * (top + 1));  // 2^32 threads: the entries alone would take 290 GB
-  W == 16 ? k_wide_index<16><<<blocks, kWideThreads, 0, r.st>>>(wv, gv) : k_wide_index<64><<<blocks, kWideThreads, 0, r.st>>>(wv, gv);
+  {
+    ProfScope ps(t, PROF_OFFSETS, r.st);
+    W == 16 ? k_wide_index<16><<<blocks, kWideThreads, 0, r.st>>>(wv, gv) : k_wide_index<64><<<blocks, kWideThreads, 0, r.st>>>(wv, gv);
+  }
   HIP_TRY(hipGetLastError());
-  r.lanes_per_node.clear();
-  return A2A_OK;
+  return profile_group(r, gv);
 }
 
 // The call's totals from the counters of its workgroups (see k_small_reduce); misc: 64 bytes for the running ones.
@@ -947,6 +994,7 @@ void wide_totals(const a2a_topo* t, long long* counters, int workgroups, bool fi
   SmallView sv{};
   sv.N = t->N;
   sv.counters = counters;
+  ProfScope ps(t, PROF_REDUCE, st);
   k_small_reduce<<<1, kBlock, 0, st>>>(sv, t->ell_words, workgroups, first ? 1 : 0, last ? 1 : 0, t->d_out_ptr, nullptr, misc, tot);
 }
 
@@ -1004,7 +1052,10 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
     const int workgroups = std::min(wv.src_count, kComputeUnits);
     const size_t lds = wide_state_bytes(t->N);
 #define WIDE_SIGMA(KS) k_wide_sigma<KS><<<workgroups, kWideThreads, lds, st>>>(wsig)
-    SMALL_BY_WORDS(WIDE_SIGMA)
+    {
+      ProfScope ps(t, PROF_SOURCES, st);
+      SMALL_BY_WORDS(WIDE_SIGMA)
+    }
     wide_totals(t, counters, workgroups, c0 == 0, c0 + chunk >= src_count, tot, (long long*)ws, st);
   }
   HIP_TRY(hipGetLastError());
@@ -1033,8 +1084,12 @@ void small_sssp_launch_levels(const SmallPlan& p, int workgroups, hipStream_t st
 }
 
 template <int KS>
-void small_sssp_launch(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
-  k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
+void small_sssp_launch(const a2a_topo* t, const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
+  {
+    ProfScope ps(t, PROF_SOURCES, st);
+    k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
+  }
+  ProfScope ps(t, PROF_REDUCE, st);
   k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
 }
 
@@ -1071,13 +1126,16 @@ int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t 
     lp.sv.level = level;
     const int groups = (lp.sv.src_count + kSmallBatch - 1) / kSmallBatch;
 #define SMALL_LEVELS(KS) small_sssp_launch_levels<KS>(lp, groups, st)
-    SMALL_BY_WORDS(SMALL_LEVELS)
+    {
+      ProfScope ps(t, PROF_SEARCH, st);
+      SMALL_BY_WORDS(SMALL_LEVELS)
+    }
     for (int i = i0; i < i1; ++i) {
       SmallPlan p = small_plan(t, std::min(per_iter, src_count - i * per_iter), SmallWhat::kSssp);
       p.sv.level = level + (size_t)(i - i0) * per_iter * level_bytes;
       p.sv.counters = counters + (size_t)rows * kSmallCounters;
       rows += p.workgroups;
-#define SMALL_ITERATION(KS) small_sssp_launch<KS>(p, ss, st)
+#define SMALL_ITERATION(KS) small_sssp_launch<KS>(t, p, ss, st)
       SMALL_BY_WORDS(SMALL_ITERATION)
     }
   }
@@ -1258,14 +1316,19 @@ int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32
     if (flags) HIP_TRY(zero_async(flags, 8, st));
     return A2A_OK;
   }
-  if ((sigma ? t->small_sigma : t->small_dist) && t->prof_mode == 0)
-    return small_distances(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
-                           (char*)workspace, workspace_bytes, st);
-  if (sigma && t->wide_sigma && t->prof_mode == 0)
-    return wide_sigma(t, src_begin, src_count, SmallOut{dist, sigma, (long long*)dist_sum}, unreachable, flags,
-                      (char*)workspace, workspace_bytes, st);
-  if (!sigma && t->wide_dist && t->prof_mode == 0)
-    return wide_distances(t, src_begin, src_count, dist, dist_sum, unreachable, flags, (char*)workspace, workspace_bytes, st);
+  const bool small = sigma ? t->small_sigma : t->small_dist;
+  if ((small || (sigma ? t->wide_sigma : t->wide_dist)) && !t->level_kernels_only()) {
+    const SmallOut out{dist, sigma, (long long*)dist_sum};
+    char* const ws = (char*)workspace;
+    if (small)
+      rc = small_distances(t, src_begin, src_count, out, unreachable, flags, ws, workspace_bytes, st);
+    else if (sigma)
+      rc = wide_sigma(t, src_begin, src_count, out, unreachable, flags, ws, workspace_bytes, st);
+    else
+      rc = wide_distances(t, src_begin, src_count, dist, dist_sum, unreachable, flags, ws, workspace_bytes, st);
+    if (rc != A2A_OK) return rc;
+    return profile_levels(t, src_begin, src_count, nullptr, sigma ? A2A_WS_SIGMA : A2A_WS_DISTANCES, ws, workspace_bytes, st);
+  }
   Run r;
   r.t = t;
   r.L = make_layout(t, src_count, sigma ? A2A_WS_SIGMA : A2A_WS_DISTANCES, workspace_bytes, false, false);
@@ -1332,10 +1395,12 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
   if (!load && t->E > 0) return A2A_ERR_INVALID_ARG;
   hipStream_t st = (hipStream_t)hip_stream;
   const Use use(t, st);
-  // (while profiling is on, the level kernels run: that is what the profile is about)
-  if (t->small_loads && src_count > 0 && t->prof_mode == 0)
-    return small_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags,
-                            (char*)workspace, workspace_bytes, st);
+  if (t->small_loads && src_count > 0 && !t->level_kernels_only()) {
+    rc = small_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags, (char*)workspace,
+                          workspace_bytes, st);
+    if (rc != A2A_OK) return rc;
+    return profile_levels(t, src_begin, src_count, demand, A2A_WS_LOADS, (char*)workspace, workspace_bytes, st);
+  }
   if (weighted_dist) HIP_TRY(zero_async(weighted_dist, 8, st));
   if (src_count == 0) {
     if (t->E > 0) HIP_TRY(zero_async(load, (size_t)t->E * 8, st));
@@ -1450,7 +1515,7 @@ int a2a_sssp_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   r.t = t;
   r.L = make_layout(t, per_iter * 64, A2A_WS_SSSP, workspace_bytes, false, false);
   if (r.L.G < per_iter) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  if (t->E > 0 && t->prof_mode == 0 && small_sssp_fits(t, src_count))
+  if (t->E > 0 && small_sssp_fits(t, src_count))
     return small_sssp(t, src_begin, src_count, std::min(per_iter * 64, src_count), load, dist_sum_total, flags,
                       (char*)workspace, workspace_bytes, st);
   r.ws = (char*)workspace;
@@ -1473,10 +1538,14 @@ int a2a_sssp_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
     // nodes per wave: 64, or 8 when the iteration has too few batches to give every SIMD a wave otherwise
     const int npw = (long long)gv.G * L.Npad >= 64ll * 4096 ? 64 : 8;
     const unsigned grid = grid_for(gv.G, L.bpb * (kWave / npw), r.inflight);
-    for (int l = 1; l <= depth; ++l)
+    for (int l = 1; l <= depth; ++l) {
+      ProfScope ps(t, PROF_FWD, st, l);
       k_sssp_fwd<<<grid, kBlock, 0, st>>>(t->d_in_ptr, t->d_in_col, t->d_in_link, gv, sv, l, npw);
-    for (int l = depth; l >= 0; --l)
+    }
+    for (int l = depth; l >= 0; --l) {
+      ProfScope ps(t, PROF_BWD, st, l);
       k_sssp_bwd<<<grid, kBlock, 0, st>>>(t->d_out_ptr, t->d_out_col, gv, sv, l, npw);
+    }
     rc = run_fold(r, gv, depth);
     if (rc != A2A_OK) return rc;
   }

@@ -2,6 +2,16 @@
 import numpy as np
 
 
+def beside_a_hub(csr):
+    """The same topology and, out of its reach, a node with links to 17 others.  A node with more than 16 links has no
+    place in the link tables, so the level kernels serve the whole topology; largest in-degree and depth stay."""
+    import a2a_inputs as gen
+    rp, col = csr
+    n = len(rp) - 1
+    rows = [list(col[rp[u]:rp[u + 1]]) for u in range(n)]
+    return gen.csr_from_rows(rows + [list(range(n + 1, n + 18))] + [[]] * 17)
+
+
 def run_link_loads(topo, src_begin=0, src_count=None, max_ws=None, workspace=None):
     import torch
     import paper_2309_13541_amd as a2a

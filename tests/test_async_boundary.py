@@ -111,11 +111,14 @@ def test_one_handle_two_streams_two_threads(a2a, oracle):
 
 def test_link_loads_recorded_into_a_graph_and_replayed(a2a, oracle):
     """a2a_link_loads under stream capture: no wait, no copy, no allocation, no memset node.  The graph is
-    replayed several times with other work of the program in between; every replay gives the eager bits."""
+    replayed several times with other work of the program in between; every replay gives the eager bits.  Topologies that
+    each of the library's ways serves: all in LDS, level kernels with the search in LDS, level kernels alone."""
     import torch
-    for rp, col in (gen.named_config("C1"), gen.random_regular(700, 4, 12)):
+    for rp, col in (gen.named_config("C1"), gen.random_regular(700, 4, 12), gen.random_regular(4500, 9, 2),
+                    gen.random_regular(8200, 3, 5), gen.random_regular(600, 17, 3)):
         topo = a2a.Topology(rp, col)
         N = topo.N
+        print(f"case N={N} E={topo.E}", flush=True)
         eager, esum, eflags = run_link_loads(topo)
         assert_loads_close(eager, oracle.run(rp, col).load)
         ws = topo.alloc_workspace(N, a2a.WS_LOADS)

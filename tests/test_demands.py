@@ -166,7 +166,8 @@ def _gpu_cases():
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", _gpu_cases(), ids=lambda c: c[0])
 def test_gpu_demand_loads_match_oracle(oracle, case):
-    """Every kernel flavour with demands (the graphs are those of the flavour test of test_gpu_parity)."""
+    """The graphs of the flavour test of test_gpu_parity, with demands.  (The level kernels serve those that have a node of
+    more than 16 links; with demands on the others: test_level_kernels_on_small_graphs.)"""
     import paper_2309_13541_amd as a2a
     from gpu_helpers import assert_loads_close
     name, (rp, col), cnt = case

@@ -511,7 +511,7 @@ def _flavours(a2a, rp, col, src_count=None):
     cnt = topo.N if src_count is None else src_count
     ws = topo.alloc_workspace(cnt, a2a.WS_LOADS)
     load = torch.empty(max(topo.E, 1), dtype=torch.float64, device="cuda")
-    topo.profile_enable(1)
+    topo.profile_enable(2)
     topo.link_loads(0, cnt, load=load, workspace=ws)
     p = topo.profile_read()
     topo.profile_enable(0)
@@ -529,7 +529,7 @@ def _flavours(a2a, rp, col, src_count=None):
 
 def test_parity_set_reaches_every_kernel_flavour(a2a):
     """The level kernels come in flavours picked from how full a level is and from the precision the path
-    counts of the levels involved are kept in; the graphs of test_small_graphs_everything and
+    counts of the levels involved are kept in; the graphs of test_level_kernels_on_small_graphs (test_small_kernels.py) and
     test_funnels_precision_boundary must between them run every one (else parity says nothing about the ones
     left out)."""
     seen = set()

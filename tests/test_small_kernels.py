@@ -1,12 +1,12 @@
 """The kernel that takes a source from its search to its link loads inside one workgroup, at the edges of what it is
 chosen and cut up by: nodes per workgroup and per thread, words of the link table, deepest level, sources per
-workgroup.  And the level kernels on the small graphs, which they serve only while profiling is on.  Against the
-oracle.  (Needs an MI355X.)"""
+workgroup.  And the level kernels on the small graphs, which they do not serve by themselves.  Against the oracle.
+(Needs an MI355X.)"""
 import numpy as np
 import pytest
 
 import a2a_inputs as gen
-from gpu_helpers import run_link_loads, assert_loads_close
+from gpu_helpers import run_link_loads, run_distances, assert_loads_close, assert_sigma_equal, beside_a_hub
 from test_demands import run_demand_gpu, seeded_demand
 from test_gpu_parity import SMALL
 
@@ -86,15 +86,25 @@ def test_deepest_levels(a2a, oracle, nodes):
 
 
 @pytest.mark.parametrize("name", sorted(n for n in SMALL if len(SMALL[n][1])))
-def test_level_kernels_on_small_graphs(a2a, oracle, name):
-    rp, col = SMALL[name]
+@pytest.mark.parametrize("how", ["beside a hub", "counting"])
+def test_level_kernels_on_small_graphs(a2a, oracle, name, how):
+    from test_sssp import run_sssp_gpu
+    rp, col = beside_a_hub(SMALL[name]) if how == "beside a hub" else SMALL[name]
     print(name, flush=True)
     topo = a2a.Topology(rp, col)
-    topo.profile_enable(1)
-    o = oracle.run(rp, col)
+    topo.profile_enable(2 if how == "counting" else 0)
+    o = oracle.run(rp, col, want_dist=True, want_sigma=True)
     load, dsum, flags = run_link_loads(topo)
     assert_loads_close(load, o.load)
     assert dsum == int(o.dist_sum.sum()) and flags == o.flags
+    for want_sigma in (True, False):
+        dist, sigma, sums, unr, flags = run_distances(topo, want_sigma=want_sigma)
+        assert np.array_equal(dist, o.dist) and np.array_equal(sums, o.dist_sum) and unr == o.unreachable
+        if want_sigma and not o.flags & 1:
+            assert_sigma_equal(sigma, o.sigma)
+    if how == "beside a hub":
+        want, _, _ = oracle.sssp(rp, col, iter_sources=64)
+        assert np.array_equal(run_sssp_gpu(topo)[0], want.astype(np.float64))
     if name != "chain_2pow54":
         dem = seeded_demand(topo.N, topo.N, 77)
         want, want_wd = oracle.run_demand(rp, col, dem)
@@ -112,7 +122,6 @@ OUTPUTS = [(f"{n} nodes, degree {d}, {cnt} sources", (n, d), s0, cnt) for n, d, 
 
 @pytest.mark.parametrize("name,shape,s0,cnt", OUTPUTS, ids=[e[0] for e in OUTPUTS])
 def test_distances_and_path_counts(a2a, oracle, name, shape, s0, cnt):
-    from gpu_helpers import run_distances, assert_sigma_equal
     rp, col = gen.random_regular(*shape, 4)
     print(name, flush=True)
     topo = a2a.Topology(rp, col)

@@ -1,10 +1,11 @@
-"""Topologies too small to fill the chip: 2, 4 or 8 waves share each block of 64 nodes, depending on how many batches
-a launch holds.  Link loads against the oracle, and the same bits for every workspace size.  (Needs an MI355X.)"""
+"""Topologies too small to fill the chip: in the level kernels 2, 4 or 8 waves share each block of 64 nodes, depending on how
+many batches a launch holds.  Link loads against the oracle, and the same bits for every workspace size, of every topology
+by itself (most have kernels of their own) and beside a node with more links than those take.  (Needs an MI355X.)"""
 import numpy as np
 import pytest
 
 import a2a_inputs as gen
-from gpu_helpers import run_link_loads, assert_loads_close
+from gpu_helpers import run_link_loads, assert_loads_close, beside_a_hub
 from test_gpu_parity import layered_collisions, dense_layers, random_digraph
 
 pytestmark = pytest.mark.gpu
@@ -47,9 +48,10 @@ def small_cases():
     yield "one link", gen.csr_from_rows([[1], []])
 
 
+@pytest.mark.parametrize("hub", [False, True], ids=["alone", "beside a hub"])
 @pytest.mark.parametrize("name,csr", list(small_cases()), ids=[n for n, _ in small_cases()])
-def test_small_topologies_match_oracle_for_every_group_size(a2a, oracle, name, csr):
-    rp, col = csr
+def test_small_topologies_match_oracle_for_every_group_size(a2a, oracle, name, csr, hub):
+    rp, col = beside_a_hub(csr) if hub else csr
     topo = a2a.Topology(rp, col)
     o = oracle.run(rp, col, threads=8)
     load, dsum, flags = all_group_sizes(a2a, topo)
@@ -58,9 +60,12 @@ def test_small_topologies_match_oracle_for_every_group_size(a2a, oracle, name, c
     topo.close()
 
 
-def test_source_ranges_for_every_group_size(a2a, oracle):
+@pytest.mark.parametrize("hub", [False, True], ids=["alone", "beside a hub"])
+def test_source_ranges_for_every_group_size(a2a, oracle, hub):
     """Partial source ranges (a ragged last batch, a range that starts inside a batch)."""
     rp, col = gen.random_regular(700, 4, 12)
+    if hub:
+        rp, col = beside_a_hub((rp, col))
     topo = a2a.Topology(rp, col)
     for s0, cnt in ((0, 700), (0, 1), (13, 200), (640, 60), (699, 1)):
         o = oracle.run(rp, col, s0, cnt)
@@ -70,12 +75,15 @@ def test_source_ranges_for_every_group_size(a2a, oracle):
     topo.close()
 
 
-def test_random_digraphs_for_every_group_size(a2a, oracle):
+@pytest.mark.parametrize("hub", [False, True], ids=["alone", "beside a hub"])
+def test_random_digraphs_for_every_group_size(a2a, oracle, hub):
     """Seeded digraphs of no particular shape: unreachable pairs, nodes without links, parallel links."""
     for seed in range(0, 160, 4):
         rp, col = random_digraph(seed)
         if len(col) == 0:
             continue
+        if hub:
+            rp, col = beside_a_hub((rp, col))
         topo = a2a.Topology(rp, col)
         print(f"seed {seed} N={topo.N} E={topo.E}", flush=True)
         o = oracle.run(rp, col)
@@ -85,10 +93,13 @@ def test_random_digraphs_for_every_group_size(a2a, oracle):
         topo.close()
 
 
-def test_path_counts_of_a_small_group(a2a, oracle):
-    """a2a_distances with path counts shares the forward kernel: one batch (eight waves per block) and all."""
+@pytest.mark.parametrize("hub", [False, True], ids=["alone", "beside a hub"])
+def test_path_counts_of_a_small_group(a2a, oracle, hub):
+    """a2a_distances with path counts shares the level kernels' forward pass: one batch (eight waves per block) and all."""
     from gpu_helpers import run_distances, assert_sigma_equal
     rp, col = gen.random_regular(1500, 5, 3)
+    if hub:
+        rp, col = beside_a_hub((rp, col))
     topo = a2a.Topology(rp, col)
     o = oracle.run(rp, col, want_dist=True, want_sigma=True, threads=8)
     for max_ws in (None, topo.workspace_bytes(64, a2a.WS_SIGMA)):

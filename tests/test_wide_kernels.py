@@ -1,6 +1,6 @@
 """Distances of 8192 to 65536 nodes (search with the frontier in LDS) at the edges of what the kernel is chosen and cut
 up by: nodes per thread, sources per word (16, 32, 64), words of the link table, levels, ragged last workgroups, pairs
-out of reach.  All rows against the level kernels (which run while profiling is on), some against the oracle.
+out of reach.  All rows against the level kernels (which run while the profile counts links), some against the oracle.
 (Needs an MI355X.)"""
 import numpy as np
 import pytest
@@ -53,7 +53,7 @@ def test_wide_distances(oracle, name):
         return dist, sums, words
 
     dist, sums, words = run()
-    topo.profile_enable(1)
+    topo.profile_enable(2)
     ref = run()
     topo.profile_enable(0)
     assert torch.equal(dist, ref[0]) and torch.equal(sums, ref[1]) and torch.equal(words, ref[2])
@@ -97,7 +97,7 @@ def test_wide_path_counts(oracle, name):
         return sigma, dist, sums, words
 
     got, least = run(0), run(a2a.WS_MINIMAL)
-    topo.profile_enable(1)
+    topo.profile_enable(2)
     ref = run(0)
     topo.profile_enable(0)
     for a, b in zip(got, least):
@@ -131,7 +131,8 @@ LOADS = {
 
 @pytest.mark.parametrize("name", LOADS)
 def test_index_entries_from_wide_search(oracle, name):
-    """Loads: the index entries are those of the level search (which runs while profiling is on), so the bits are too."""
+    """Loads: the index entries are those of the level search (which runs while the profile counts links), so the bits
+    are too."""
     import torch
     import paper_2309_13541_amd as a2a
     make, s0, cnt = LOADS[name]
@@ -155,7 +156,7 @@ def test_index_entries_from_wide_search(oracle, name):
 
     for dem in (False, True):
         got, least = run(0, dem), run(a2a.WS_MINIMAL, dem)
-        topo.profile_enable(1)
+        topo.profile_enable(2)
         ref = run(0, dem)
         topo.profile_enable(0)
         for a, b, c in zip(got, least, ref):

@@ -8,10 +8,11 @@ followed by a2a_schedule_bound.  The CSR is resident on the device before the ti
 Prints one JSON line.  TEPS = N * E / seconds (one traversed edge = one (source, link) pair).
 
 The timed region holds the K steps and nothing else.  The per-kernel split (HIP events around every
-launch, on the stream the kernels run on) comes from two further, untimed steps; one more untimed
-step counts the (source, link) pairs on shortest paths for the algorithmic bytes.  Beside the metric:
-a plain 1 GiB device copy and fill (what this machine's HBM gives a streaming kernel), a2a_distances,
-a2a_link_loads_demand, a2a_sssp_loads, and the CPU oracle on a bounded sample (all cores and one core).
+launch, on the stream the kernels run on) comes from two further, untimed steps; before them an untimed
+step through the level kernels counts the (source, link) pairs on shortest paths for the algorithmic bytes.
+Beside the metric: a plain 1 GiB device copy and fill (what this machine's HBM gives a streaming kernel),
+a2a_distances, a2a_link_loads_demand, a2a_sssp_loads, and the CPU oracle on a bounded sample (all cores and
+one core).
 """
 import argparse
 import json
@@ -30,7 +31,11 @@ HBM_PEAK_GBPS = 8000.0
 # every batch; the class says which lane layout the level's size stands for (every batch picks its own).
 KERNEL_NAME = {"bfs": "k_bfs_level", "offsets": "k_write_offsets", "fwd_rows": "k_fwd[rows]",
                "fwd_few": "k_fwd[few]", "fwd_spread": "k_fwd[spread]", "bwd_rows": "k_bwd[rows]",
-               "bwd_few": "k_bwd[few]", "bwd_spread": "k_bwd[spread]", "reduce": "k_reduce_part"}
+               "bwd_few": "k_bwd[few]", "bwd_spread": "k_bwd[spread]", "reduce": "k_reduce_part",
+               "search": "k_wide_dist", "sources": "k_small_loads"}
+# Where the search (or a source as a whole) runs in LDS, other kernels write the index entries and add up the loads.
+AFTER_SEARCH = {"offsets": "k_wide_index"}
+AFTER_SOURCES = {"reduce": "k_small_reduce"}
 FWD_CLASSES = ("fwd_rows", "fwd_few", "fwd_spread")
 BWD_CLASSES = ("bwd_rows", "bwd_few", "bwd_spread")
 
@@ -47,6 +52,9 @@ def algorithmic_bytes(prof, dag_level, nb, E, steps):
     (backward) that level; which kernel class ran the level comes from the per-level timings.
     The forward launch of the deepest level also leaves coef = 1/sigma behind (no backward
     launch there): that level's own 16 backward bytes are charged to it.
+    A search of all levels in one launch is charged the level tags; a launch that takes its sources from the
+    search to the loads, all but the reduction (that launch keeps the state in LDS: its bytes are a measure of the
+    work, not of traffic).
     """
     L = len(prof["pairs_level"])
     pairs = [p / steps for p in prof["pairs_level"]]       # per step
@@ -68,6 +76,10 @@ def algorithmic_bytes(prof, dag_level, nb, E, steps):
             out[bwd] += own + links
         elif fwd:  # deepest level: the forward launch leaves coef = 1/sigma, nothing runs backward
             out[fwd] += own
+        if prof["sources"]["launches"]:
+            out["sources"] += (2 + 8) * pairs[l] + 8 * dag_in[l] + own + links
+        elif prof["search"]["launches"]:
+            out["search"] += 1 * pairs[l]
     out["reduce"] = 8.0 * nb * E
     return out
 
@@ -202,24 +214,24 @@ def main():
     step_ms = sorted(marks[i].elapsed_time(marks[i + 1]) for i in range(args.steps))
     median_ms = step_ms[len(step_ms) // 2] if len(step_ms) % 2 else 0.5 * (step_ms[len(step_ms) // 2 - 1] + step_ms[len(step_ms) // 2])
     load_timed = load.clone()
-    # untimed: per-kernel split from HIP events around every launch, on the stream the kernels run on
+    # untimed: one step through the level kernels counts the (source, link) pairs on shortest paths
     prof_steps = 2
     graph = None  # the profiled steps are launched one by one
+    topo.profile_enable(2)
+    step()
+    torch.cuda.synchronize()
+    prof2 = topo.profile_read()
+    dag, dag_level = prof2["dag_links"], prof2["dag_level"]
+    # per-kernel split from HIP events around every launch of further steps, on the stream the kernels run on; their
+    # loads must be the same bits as the timed step's (fixed summation order)
     topo.profile_enable(1)
     for _ in range(prof_steps):
         step()
     torch.cuda.synchronize()
     prof = topo.profile_read()
-    # one more untimed step counts the (source, link) pairs on shortest paths; its loads must be
-    # the same bits as the timed step's (fixed summation order)
-    topo.profile_enable(2)
-    step()
-    torch.cuda.synchronize()
+    topo.profile_enable(0)
     rerun_bitwise = bool(torch.equal(load_timed, load))
     del load_timed
-    prof2 = topo.profile_read()
-    dag, dag_level = prof2["dag_links"], prof2["dag_level"]
-    topo.profile_enable(0)
     sec = elapsed / args.steps
     sum_dist = int(dsum.item())
     fl = int(flags.item())
@@ -229,8 +241,13 @@ def main():
     nb = (N + 63) // 64
     alg = algorithmic_bytes(prof, dag_level, nb, E, steps)
     cfg = args.config
+    names = dict(KERNEL_NAME)
+    if prof["search"]["launches"]:
+        names.update(AFTER_SEARCH)
+    if prof["sources"]["launches"]:
+        names.update(AFTER_SOURCES)
     per_kernel = {}
-    for k, name in KERNEL_NAME.items():
+    for k, name in names.items():
         ms, n = prof[k]["ms"], prof[k]["launches"]
         if n:
             per_kernel[name] = {"ms_per_step": ms / steps, "launches_per_step": n / steps,
@@ -239,8 +256,8 @@ def main():
                                 "ms_by_level": {str(l): round(x / steps, 3)
                                                 for l, x in enumerate(prof[k]["ms_level"]) if x > 0}}
     # The dominant kernel: k_fwd and k_bwd are one kernel each (all their levels), the others as named.
-    groups = {"k_bwd": BWD_CLASSES, "k_fwd": FWD_CLASSES, "k_bfs_level": ("bfs",),
-              "k_write_offsets": ("offsets",), "k_reduce_part": ("reduce",)}
+    groups = {"k_bwd": BWD_CLASSES, "k_fwd": FWD_CLASSES}
+    groups.update({names[c]: (c,) for c in ("bfs", "offsets", "reduce", "search", "sources")})
     g_ms = {g: sum(prof[c]["ms"] for c in cl) for g, cl in groups.items()}
     kname = max(g_ms, key=g_ms.get)
     n_l = sum(prof[c]["launches"] for c in groups[kname])
@@ -372,7 +389,8 @@ def main():
             assert int(dsrc.sum().item()) == sum_dist and int(unr.item()) == 0
         dist_leg = {"ms_per_step": dsec * 1e3, "teps_bfs": N * E / dsec, "unit": "edges/s",
                     "alg_bytes": 4.0 * N * N, "frac": 4.0 * N * N / dsec / 1e9 / HBM_PEAK_GBPS,
-                    "kernel_ms": {k: round(dprof[k]["ms"], 3) for k in ("init", "bfs", "extract")},
+                    "kernel_ms": {k: round(dprof[k]["ms"], 3)
+                                  for k in ("init", "bfs", "search", "sources", "extract", "reduce") if dprof[k]["launches"]},
                     "what": "a2a_distances over all sources: BFS + int32 dist[N][N] + per-source sums"}
         del dist, wsd
 

@@ -76,7 +76,7 @@ struct a2a_topo {
   // 25 us): calls begun, calls now inside, the number begun when a call last waited for everything before it.
   struct Uses {
     std::atomic<uint64_t> begun{0}, inside{0}, settled{0};
-    std::atomic<void*> stream{nullptr};
+    std::atomic<void*> stream{this};  // of the first call; before that no stream's handle
     std::atomic<bool> several{false};  // streams, or recorded in a graph: only the device knows
   };
   mutable Uses uses;
@@ -104,10 +104,12 @@ class Use {
  public:
   Use(const a2a_topo* t, hipStream_t st) : u_(t->uses) {
     u_.inside.fetch_add(1);
-    if (u_.begun.fetch_add(1) == 0) u_.stream = st;
+    u_.begun.fetch_add(1);
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     if (st != nullptr && hipStreamIsCapturing(st, &capture) != hipSuccess) u_.several = true;
-    if (capture != hipStreamCaptureStatusNone || u_.stream.load() != st || st == hipStreamPerThread) u_.several = true;
+    void* first = &u_;
+    const bool other = !u_.stream.compare_exchange_strong(first, st) && first != (void*)st;
+    if (capture != hipStreamCaptureStatusNone || other || st == hipStreamPerThread) u_.several = true;
   }
   ~Use() { u_.inside.fetch_sub(1); }
   Use(const Use&) = delete;

@@ -8,13 +8,15 @@ from __future__ import annotations
 import ctypes
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 from typing import Optional
 
 import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _ROOT = os.path.dirname(_HERE)
-_SRC = os.path.join(_HERE, "csrc", "a2a_topo.hip")
+_CSRC = os.path.join(_HERE, "csrc")
 _LIB = os.path.join(_HERE, "liba2a_topo.so")
 _lib = None
 
@@ -49,7 +51,7 @@ PROF_KERNELS = ("init", "bfs", "offsets", "fwd_rows", "fwd_few", "fwd_spread", "
 PROF_MAX_LEVELS = 64
 
 HIPCC_FLAGS = [
-    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-shared",
+    "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
 ]
 
@@ -120,16 +122,31 @@ def library_path() -> str:
 
 
 def build_library(verbose: bool = False) -> str:
-    """Compile csrc/a2a_topo.hip for gfx950 with hipcc (works without a GPU)."""
+    """Compile csrc/ for gfx950 with hipcc (works without a GPU): the host side with the level kernels, and the kernels
+    for each width of the link tables, side by side."""
     global _lib
-    cmd = ["hipcc", *HIPCC_FLAGS, "-I" + os.path.join(_ROOT, "include"), "-o", _LIB, _SRC]
+    flags = [*HIPCC_FLAGS, "-I" + os.path.join(_ROOT, "include")]
+    with tempfile.TemporaryDirectory() as tmp:
+        units = [("a2a_topo", [])] + [("a2a_words", [f"-DA2A_WORDS={w}"]) for w in (2, 3, 4, 5, 8)]
+        objects = [os.path.join(tmp, f"{i}.o") for i in range(len(units))]
+
+        def compile_unit(i):
+            name, extra = units[i]
+            return _run(["hipcc", *flags, *extra, "-c", "-o", objects[i], os.path.join(_CSRC, name + ".hip")], verbose)
+
+        with ThreadPoolExecutor(max_workers=min(len(units), os.cpu_count() or 1)) as pool:
+            list(pool.map(compile_unit, range(len(units))))
+        _run(["hipcc", "--offload-arch=gfx950", "-shared", "-o", _LIB, *objects], verbose)
+    _lib = None
+    return _LIB
+
+
+def _run(cmd, verbose: bool) -> None:
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if verbose or res.returncode != 0:
         print(res.stdout)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed:\n" + res.stdout)
-    _lib = None
-    return _LIB
 
 
 def load_library():

@@ -1,4 +1,5 @@
-// Device code of a2a_topo (gfx950, wave64).  Included once, by a2a_topo.hip.
+// Device code of a2a_topo (gfx950, wave64): helpers and the level kernels.  Kernels that are no templates are static: a
+// translation unit has the ones that it launches.
 //
 // Data model.  Sources are handled 64 at a time ("batch"): bit j of a 64-bit mask = source j of
 // the batch, and lane j of a wavefront carries that source's floating-point state.  For every
@@ -344,7 +345,7 @@ __device__ __forceinline__ size_t bm_at(const GroupView& gv, int sb, int level, 
 
 // Level 0: bit j of L_0[s_j] and seen[s_j] for the batch's sources s_j; sigma(s_j,s_j) = 1 is
 // entry j of the value array.  One thread per (node, batch of the super-batch).
-__global__ void __launch_bounds__(kBfsBlock) k_init_group(GroupView gv) {
+static __global__ void __launch_bounds__(kBfsBlock) k_init_group(GroupView gv) {
   int sb, nblk;
   if (!map_block(gv.SB, gv.nb64, kXcd, sb, nblk)) return;
   const int t = (int)threadIdx.x;
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(kBfsBlock) k_init_group(GroupView gv) {
 // One BFS level for every batch of the group, pull direction:
 // L_l[v] = (OR over in-neighbours u of L_{l-1}[u]) & ~seen[v].
 // Thread (node, k): the kSub lanes of a node read the same in-link list and adjacent masks.
-__global__ void __launch_bounds__(kBfsBlock)
+static __global__ void __launch_bounds__(kBfsBlock)
 k_bfs_level(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in_col, GroupView gv,
             int level) {
   int sb, nblk;
@@ -418,7 +419,7 @@ k_bfs_level(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in_c
 // bsum[g][l][*] (pairs per 64-node block) -> position of the block's first row in the batch's
 // value array: exclusive prefix over blocks, after all rows of the levels above.  One wave per
 // (batch, level), levels 1..depth.
-__global__ void __launch_bounds__(kWave) k_scan_blocks(GroupView gv, int depth) {
+static __global__ void __launch_bounds__(kWave) k_scan_blocks(GroupView gv, int depth) {
   const int g = (int)blockIdx.x / depth, level = 1 + (int)blockIdx.x % depth;
   const int lane = lane_id();
   const long long* __restrict__ lt = gv.ltot + (size_t)g * gv.Lcap;
@@ -439,7 +440,7 @@ __global__ void __launch_bounds__(kWave) k_scan_blocks(GroupView gv, int depth) 
 // batch k (three shuffle steps across the 8 nodes of a wave, then across the 8 waves via LDS).
 // A workgroup takes `levels` consecutive levels of its 64 nodes (all of them in a large group; one
 // each, in as many workgroups, where the group is too small to fill the chip otherwise).
-__global__ void __launch_bounds__(kBfsBlock) k_write_offsets(GroupView gv, int depth, int levels) {
+static __global__ void __launch_bounds__(kBfsBlock) k_write_offsets(GroupView gv, int depth, int levels) {
   const int chunks = (depth + levels) / levels;  // levels 0 .. depth
   int sb, unit;
   if (!map_block(gv.SB, gv.nb64 * chunks, kXcd, sb, unit)) return;
@@ -1638,7 +1639,7 @@ k_bwd(const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_col, 
 }
 
 // load[a] = (first group ? 0 : load[a]) + part[0][a] + part[1][a] + ... in that order.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_reduce_part(const double* __restrict__ part, size_t Epad, int G, long long E, int first,
               double* __restrict__ load) {
   const long long a = (long long)blockIdx.x * kBlock + threadIdx.x;
@@ -1662,7 +1663,7 @@ k_reduce_part(const double* __restrict__ part, size_t Epad, int G, long long E, 
 
 // dist[s][v] from the level masks, through a 64 x 64 LDS tile so that rows of dist are written
 // with consecutive lanes on consecutive nodes.  One wave per (batch, 64-node tile).  Any depth.
-__global__ void __launch_bounds__(kWave)
+static __global__ void __launch_bounds__(kWave)
 k_extract_dist(GroupView gv, int tiles, int depth, int32_t* __restrict__ dist,
                long long* __restrict__ dist_sum) {
   int g, tile;
@@ -1702,7 +1703,7 @@ k_extract_dist(GroupView gv, int tiles, int depth, int32_t* __restrict__ dist,
 // wave-uniform: no divergence), every lane writing its node's entry of row j.  The per-source sums
 // come from ballots: bit k of the distances of source j over the wave's nodes is one popcount.
 // `planes` = number of bits of `depth`.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_extract_dist_planes(GroupView gv, int depth, int planes, int32_t* __restrict__ dist,
                       long long* __restrict__ dist_sum) {
   // The masks of the kSub batches of a super-batch share memory lines (64 bytes per node): their
@@ -1828,7 +1829,7 @@ k_extract_dist_packed(GroupView gv, int depth, int32_t* __restrict__ dist, long 
 }
 
 // sigma[s][v] from the level-compact rows, transposed through LDS.  One wave per tile.
-__global__ void __launch_bounds__(kWave)
+static __global__ void __launch_bounds__(kWave)
 k_extract_sigma(GroupView gv, int tiles, int depth, double* __restrict__ sigma_out) {
   int g, tile;
   if (!map_block(gv.G, tiles, kXcd, g, tile)) return;
@@ -1867,7 +1868,7 @@ k_extract_sigma(GroupView gv, int tiles, int depth, double* __restrict__ sigma_o
 
 // p[0..n) = 0, eight bytes per thread and step.  Used instead of the runtime's memset so that a
 // call only ever enqueues kernels of this library on the caller's stream.
-__global__ void __launch_bounds__(kBlock) k_zero(unsigned long long* __restrict__ p, size_t n) {
+static __global__ void __launch_bounds__(kBlock) k_zero(unsigned long long* __restrict__ p, size_t n) {
   const size_t stride = (size_t)gridDim.x * kBlock;
   for (size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += stride) p[i] = 0ull;
 }
@@ -1875,7 +1876,7 @@ __global__ void __launch_bounds__(kBlock) k_zero(unsigned long long* __restrict_
 // Folds the per-batch level totals of a finished group into the call's running totals:
 // misc[1] += sum of distances, misc[2] += reached pairs.  One workgroup; integer sums, so the
 // order does not matter.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_fold_counters(GroupView gv, int depth, long long* __restrict__ misc) {
   __shared__ long long s_r[2][kWavesPerBlock];
   const int t = (int)threadIdx.x;
@@ -1909,7 +1910,7 @@ k_fold_counters(GroupView gv, int depth, long long* __restrict__ misc) {
 // Demand x distance of a call: each batch's blocks are added up in a fixed tree (one workgroup per
 // batch; the sum lands in the batch's first slot), then the batches are added to *out one after the
 // other in ascending order, so the bits do not depend on which batches share a group.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_fold_weighted_batch(double* __restrict__ wpart, int nb64) {
   __shared__ double s_r[kBlock];
   const int t = (int)threadIdx.x;
@@ -1925,7 +1926,7 @@ k_fold_weighted_batch(double* __restrict__ wpart, int nb64) {
   if (t == 0) w[0] = s_r[0];
 }
 // (one wave; 64 batches are read at a time: one after the other they took 26 us for 128)
-__global__ void __launch_bounds__(kWave) k_fold_weighted(const double* __restrict__ wpart, int G, int nb64, double* __restrict__ out) {
+static __global__ void __launch_bounds__(kWave) k_fold_weighted(const double* __restrict__ wpart, int G, int nb64, double* __restrict__ out) {
   const int lane = lane_id();
   double run = out[0];
   for (int g0 = 0; g0 < G; g0 += kWave) {
@@ -1943,7 +1944,7 @@ __global__ void __launch_bounds__(kWave) k_fold_weighted(const double* __restric
 // The BFS of k_bfs_level with two mask arrays used in turn instead of one per level, and no
 // counting: a2a_topo_create runs it from every node once to learn the largest finite distance,
 // which sizes the level slots of every later call.  Arrays: [SB][Npad][kSub].
-__global__ void __launch_bounds__(kBfsBlock)
+static __global__ void __launch_bounds__(kBfsBlock)
 k_probe_init(uint64_t* __restrict__ front, uint64_t* __restrict__ seen, int N, int Npad, int SB, int src0) {
   int sb, nblk;
   if (!map_block(SB, Npad / kBfsNodes, kXcd, sb, nblk)) return;
@@ -1956,7 +1957,7 @@ k_probe_init(uint64_t* __restrict__ front, uint64_t* __restrict__ seen, int N, i
   front[at] = bit;
   seen[at] = bit;
 }
-__global__ void __launch_bounds__(kBfsBlock)
+static __global__ void __launch_bounds__(kBfsBlock)
 k_probe_level(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in_col,
               const uint64_t* __restrict__ prev, uint64_t* __restrict__ next, uint64_t* __restrict__ seen, int N,
               int Npad, int SB, int* __restrict__ reached) {
@@ -1988,7 +1989,7 @@ k_probe_level(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in
 
 // Final outputs of a call: totals and flag bits (bit 0: sigma reached 2^53, bit 1: some pair
 // unreachable).
-__global__ void k_finish(const long long* __restrict__ misc, long long pairs,
+static __global__ void k_finish(const long long* __restrict__ misc, long long pairs,
                          long long* __restrict__ dist_sum_total, long long* __restrict__ unreachable,
                          long long* __restrict__ flags) {
   if (threadIdx.x == 0 && blockIdx.x == 0) {
@@ -2094,7 +2095,7 @@ __device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict_
 
 // max (lowest link id on ties) and min of load[0..E).  A single workgroup spent 40 us on 100 000 links (a chain of
 // dependent trips to memory); up to 64 of them take 5.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_load_extrema(const double* __restrict__ load, long long E, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
                long long* __restrict__ out) {
   Extrema e;
@@ -2115,7 +2116,7 @@ k_load_extrema(const double* __restrict__ load, long long E, long long* __restri
 // The same with link capacities (Sec. 3.1.1): utilisation load[a] / cap[a] instead of load[a]; also the total
 // capacity (a fixed order: per thread in link order, then a fixed tree) and the largest total out-capacity of a
 // node.  A capacity is bad if it is not a positive finite number.  A thread takes whole nodes.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_util_extrema(const int32_t* __restrict__ out_ptr, const double* __restrict__ load, const double* __restrict__ cap, int N,
                long long* __restrict__ scratch, unsigned* __restrict__ arrived, long long* __restrict__ out) {
   Extrema e;

@@ -1,5 +1,4 @@
-// Device code for topologies whose whole per-source state fits the LDS of a compute unit.  Included once,
-// by a2a_topo.hip, after a2a_kernels.h.
+// Device code for topologies whose whole per-source state fits the LDS of a compute unit.
 //
 // The level kernels of a2a_kernels.h need three dependent launches per BFS level; a topology of a few
 // thousand nodes is bound by that chain (about 5 us per launch), not by bytes or arithmetic.  Here one
@@ -160,7 +159,7 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
 // Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
 // masks in LDS (three words per node), until a level finds nothing new.  deepest: host memory, a word per workgroup,
 // negative before (the host waits for the last of them to change).
-__global__ void __launch_bounds__(kSmallThreads)
+static __global__ void __launch_bounds__(kSmallThreads)
 k_small_probe(const uint32_t* __restrict__ table, int words, int N, int* __restrict__ deepest) {
   extern __shared__ uint32_t s_masks[];
   __shared__ int s_new[2];
@@ -688,7 +687,7 @@ struct SmallTotals {
   long long* flags;
   double* weighted;
 };
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_t* __restrict__ out_ptr,
                double* __restrict__ load, long long* __restrict__ misc, SmallTotals tot) {
   const int t = (int)threadIdx.x;
@@ -917,7 +916,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sssp_add(SmallSssp ss, 
 }
 
 // load of every link from its place in the in-link table.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_small_sssp_output(const uint32_t* __restrict__ weight, int places, const int32_t* __restrict__ in_ptr,
                     const int32_t* __restrict__ in_link, int N, double* __restrict__ load) {
   const int v = (int)(blockIdx.x * kBlock + threadIdx.x) / places, j = (int)(blockIdx.x * kBlock + threadIdx.x) % places;

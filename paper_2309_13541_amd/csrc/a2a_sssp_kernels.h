@@ -1,6 +1,6 @@
 // Device code of a2a_sssp_loads: the single-path "SSSP" baseline of Sec. 5.2 (a heuristic that
 // computes shortest paths iteration by iteration through a graph whose link weights reflect the
-// congestion the earlier iterations caused).  Included once, by a2a_topo.hip, after a2a_kernels.h.
+// congestion the earlier iterations caused), level by level.
 //
 // One iteration = one group of batches (64 sources each): the BFS of a2a_kernels.h gives the level
 // masks L_l[v]; then, level by level, every (source, node) pair picks the in-link of least
@@ -55,7 +55,7 @@ __device__ __forceinline__ int wave_sum8_int_lds(const int (&x)[8], int lane, in
 // cost and chosen in-link of the pairs on `level` (>= 1).  A wave takes npw (a multiple of 8) consecutive
 // nodes of one batch.  In-links in list order = ascending link id, so the strict comparison keeps the
 // lowest id among equals.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_sssp_fwd(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in_col,
            const int32_t* __restrict__ in_link, GroupView gv, SsspView sv, int level, int npw) {
   int g, nblk;
@@ -136,7 +136,7 @@ k_sssp_fwd(const int32_t* __restrict__ in_ptr, const int32_t* __restrict__ in_co
 // Paths through the pairs on `level` (deepest .. 0), and the loads of the links chosen by the pairs one
 // level deeper.  The additions go straight to iload: the cost recursion of this iteration is over, the
 // next one starts after this kernel's last launch.
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_sssp_bwd(const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_col, GroupView gv, SsspView sv,
            int level, int npw) {
   int g, nblk;
@@ -214,7 +214,7 @@ k_sssp_bwd(const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_
 }
 
 // load[a] = iload[a] as a double (exact below 2^53).
-__global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kBlock)
 k_sssp_output(const unsigned long long* __restrict__ iload, long long E, double* __restrict__ load) {
   const long long a = (long long)blockIdx.x * kBlock + threadIdx.x;
   if (a < E) load[a] = (double)iload[a];

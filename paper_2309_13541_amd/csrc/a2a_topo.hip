@@ -26,8 +26,7 @@
 #include <vector>
 
 #include "a2a_kernels.h"
-#include "a2a_small_kernels.h"
-#include "a2a_wide_kernels.h"
+#include "a2a_launch.h"
 #include "a2a_sssp_kernels.h"
 #include "a2a_topo.h"
 
@@ -722,12 +721,6 @@ std::vector<uint32_t> make_ell(int32_t N, const int32_t* ptr, const int32_t* col
   return ell;
 }
 
-struct SmallPlan {
-  SmallView sv{};
-  int T = 0, workgroups = 0, nodes = 0;  // threads, workgroups of the whole call, nodes per thread
-  size_t lds = 0;
-};
-
 SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   const SmallCut c = small_cut(t->N, t->level_bound, t->ell_words, src_count, what);
   SmallPlan p;
@@ -763,28 +756,6 @@ bool small_loads_fit(const a2a_topo* t) {
          256 + kSmallChunk * small_row_bytes(t, kSmallBatch) <= t->min_loads_bytes;
 }
 
-template <int KS, bool kDemand>
-void small_launch_words(const SmallPlan& p, int workgroups, hipStream_t st) {
-  if (p.nodes <= 1)
-    k_small_loads<KS, 1, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
-  else if (p.nodes <= 2)
-    k_small_loads<KS, 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
-  else if (KS <= 5 && p.nodes <= 4)
-    k_small_loads<KS, KS <= 5 ? 4 : 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
-  else
-    k_small_loads<KS, small_max_nodes(KS), kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
-}
-template <bool kDemand>
-void small_launch(const SmallPlan& p, int ell_words, int workgroups, hipStream_t st) {
-  switch (ell_words) {
-    case 2: return small_launch_words<2, kDemand>(p, workgroups, st);
-    case 3: return small_launch_words<3, kDemand>(p, workgroups, st);
-    case 4: return small_launch_words<4, kDemand>(p, workgroups, st);
-    case 5: return small_launch_words<5, kDemand>(p, workgroups, st);
-    default: return small_launch_words<8, kDemand>(p, workgroups, st);
-  }
-}
-
 int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
                      double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
                      hipStream_t st) {
@@ -806,7 +777,7 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
     p.sv.wg0 = w0;
     {
       ProfScope ps(t, PROF_SOURCES, st);
-      demand ? small_launch<true>(p, t->ell_words, n, st) : small_launch<false>(p, t->ell_words, n, st);
+      by_words(t->ell_words, [&](auto ks) { launch_small_loads<decltype(ks)::value>(p, demand != nullptr, n, st); });
     }
     ProfScope ps(t, PROF_REDUCE, st);
     k_small_reduce<<<blocks, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,
@@ -814,24 +785,6 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
   }
   HIP_TRY(hipGetLastError());
   return A2A_OK;
-}
-
-template <int KS>
-void small_launch_out_words(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st) {
-  const auto launch = [&](auto sigma, auto dist) {
-    if (out.sigma != nullptr)
-      sigma<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
-    else
-      dist<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
-  };
-  if (p.nodes <= 1)
-    launch(k_small_sigma<KS, 1>, k_small_dist<KS, 1>);
-  else if (p.nodes <= 2)
-    launch(k_small_sigma<KS, 2>, k_small_dist<KS, 2>);
-  else if (p.nodes <= 4)
-    launch(k_small_sigma<KS, 4>, k_small_dist<KS, 4>);
-  else
-    launch(k_small_sigma<KS, 8>, k_small_dist<KS, 8>);
 }
 
 // Whether distances (and path counts) take the small kernels: their level bytes and counters fit the smallest
@@ -859,13 +812,7 @@ int small_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
     p.sv.wg0 = w0;
     {
       ProfScope ps(t, PROF_SOURCES, st);
-      switch (t->ell_words) {
-        case 2: small_launch_out_words<2>(p, out, n, st); break;
-        case 3: small_launch_out_words<3>(p, out, n, st); break;
-        case 4: small_launch_out_words<4>(p, out, n, st); break;
-        case 5: small_launch_out_words<5>(p, out, n, st); break;
-        default: small_launch_out_words<8>(p, out, n, st); break;
-      }
+      by_words(t->ell_words, [&](auto ks) { launch_small_outputs<decltype(ks)::value>(p, out, n, st); });
     }
     ProfScope ps(t, PROF_REDUCE, st);
     // a single workgroup: the counters only
@@ -885,34 +832,14 @@ bool wide_sigma_fits(const a2a_topo* t) {
   return wide_distances_fit(t) && t->N <= kWideStateNodes && t->level_bound <= kWideStateDepth;
 }
 
-#define SMALL_BY_WORDS(call)       \
-  switch (t->ell_words) {          \
-    case 2: call(2); break;        \
-    case 3: call(3); break;        \
-    case 4: call(4); break;        \
-    case 5: call(5); break;        \
-    default: call(8); break;       \
-  }
-
-template <int W, int KS, int kOut>
-void wide_launch_words(const WideView& wv, int workgroups, hipStream_t st) {
-  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
-  if (kOut == kWideDist && wv.depth < 8)
-    launch(k_wide_dist<W, KS, kOut == kWideDist ? 3 : 6, kOut>);
-  else
-    launch(k_wide_dist<W, KS, 6, kOut>);
-}
-
 // The wide search over the sources of wv, its memory at `ws`, of which it may use ws_bytes (at least what the smallest
 // workspace of a call leaves).  Sets *workgroups, each of which has counters at wv->counters.
-template <int kOut>
-int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int* workgroups, hipStream_t st) {
+int wide_search(const a2a_topo* t, WideView* wv, int out, char* ws, size_t ws_bytes, int* workgroups, hipStream_t st) {
   // sources per workgroup: as few as the fewest rounds over the chip allow (a level takes the same time)
   const int n = wv->src_count;
   int W = 16;
   const auto rounds = [&](int w) { return ((n + w - 1) / w + kComputeUnits - 1) / kComputeUnits; };
-  for (int w = kOut == kWideBytes ? 64 : 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
+  for (int w = out == kWideBytes ? 64 : 32; w <= 64 && (size_t)t->N * w <= (size_t)kWideMost * 16; w *= 2)
     if (rounds(w) < rounds(W)) W = w;
   wv->in = t->d_ell_in;
   wv->N = t->N;
@@ -925,13 +852,7 @@ int wide_search(const a2a_topo* t, WideView* wv, char* ws, size_t ws_bytes, int*
   wv->masks = (uint32_t*)ws;
   wv->counters = (long long*)(ws + *workgroups * masks);
   ProfScope ps(t, PROF_SEARCH, st);
-#define WIDE_SEARCH(KS)                                                       \
-  switch (W) {                                                                \
-    case 16: wide_launch_words<16, KS, kOut>(*wv, *workgroups, st); break;  \
-    case 32: wide_launch_words<kOut == kWideBytes ? 64 : 32, KS, kOut>(*wv, *workgroups, st); break;  \
-    default: wide_launch_words<64, KS, kOut>(*wv, *workgroups, st); break;  \
-  }
-  SMALL_BY_WORDS(WIDE_SEARCH)
+  by_words(t->ell_words, [&](auto ks) { launch_wide_search<decltype(ks)::value>(*wv, W, out, *workgroups, st); });
   return A2A_OK;
 }
 
@@ -969,17 +890,9 @@ int run_index(const Run& r, const GroupView& gv, int top) {
   HIP_TRY(zero_async(gv.ltot, (size_t)gv.SB * kSub * r.L.Lcap * 8, r.st));
   const int W = wide_masks_sources(t);
   const int workgroups = std::min((wv.src_count + W - 1) / W, kComputeUnits);
-  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
-#define WIDE_MASKS(KS)                                                                                               \
-  if (W == 16)                                                                                                       \
-    k_wide_dist<16, KS, 6, kWideMasks><<<workgroups, kWideThreads, lds, r.st>>>(wv);                                 \
-  else if (t->N > kScaledNodes)                                                                                      \
-    k_wide_dist<64, KS, 6, kWideMasks><<<workgroups, kWideThreads, lds, r.st>>>(wv);                                 \
-  else                                                                                                               \
-    k_wide_dist<64, KS, 6, kWideMasks, true><<<workgroups, kWideThreads, lds, r.st>>>(wv)
   {
     ProfScope ps(t, PROF_SEARCH, r.st);
-    SMALL_BY_WORDS(WIDE_MASKS)
+    by_words(t->ell_words, [&](auto ks) { launch_wide_masks<decltype(ks)::value>(wv, W, workgroups, r.st); });
   }
   const unsigned blocks = (unsigned)(gv.G * (top + 1));  // 2^32 threads: the entries alone would take 290 GB
   {
@@ -1009,7 +922,7 @@ int wide_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   wv.dist = dist;
   wv.sums = (long long*)dist_sum;
   int workgroups = 0;
-  const int rc = wide_search<kWideDist>(t, &wv, ws + 256, ws_bytes - 256, &workgroups, st);
+  const int rc = wide_search(t, &wv, kWideDist, ws + 256, ws_bytes - 256, &workgroups, st);
   if (rc != A2A_OK) return rc;
   const SmallTotals tot{(long long)src_count * (t->N - 1), nullptr, (long long*)unreachable, (long long*)flags, nullptr};
   wide_totals(t, wv.counters, workgroups, true, true, tot, (long long*)ws, st);
@@ -1039,7 +952,7 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
     wv.src_count = std::min(chunk, src_count - c0);
     wv.level = level;
     int groups = 0;
-    const int rc = wide_search<kWideBytes>(t, &wv, search, (size_t)(ws + ws_bytes - search), &groups, st);
+    const int rc = wide_search(t, &wv, kWideBytes, search, (size_t)(ws + ws_bytes - search), &groups, st);
     if (rc != A2A_OK) return rc;
     WideSigma wsig;
     wsig.in = t->d_ell_in;
@@ -1052,11 +965,9 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
     const size_t row = (size_t)c0 * t->N;
     wsig.out = SmallOut{out.dist ? out.dist + row : nullptr, out.sigma + row, out.sums ? out.sums + c0 : nullptr};
     const int workgroups = std::min(wv.src_count, kComputeUnits);
-    const size_t lds = wide_state_bytes(t->N);
-#define WIDE_SIGMA(KS) k_wide_sigma<KS><<<workgroups, kWideThreads, lds, st>>>(wsig)
     {
       ProfScope ps(t, PROF_SOURCES, st);
-      SMALL_BY_WORDS(WIDE_SIGMA)
+      by_words(t->ell_words, [&](auto ks) { launch_wide_sigma<decltype(ks)::value>(wsig, workgroups, st); });
     }
     wide_totals(t, counters, workgroups, c0 == 0, c0 + chunk >= src_count, tot, (long long*)ws, st);
   }
@@ -1070,29 +981,6 @@ bool small_sssp_fits(const a2a_topo* t, int32_t src_count) {
   return t->ell_words > 0 && t->N <= kBothTables && t->level_bound < (t->N <= kScaledNodes ? kSmallUnseen - 1 : 16) &&
          small_lds_bytes(t->N, 1, t->level_bound, kStateSssp) <= kSmallLds &&
          sssp_costs_fit(t->level_bound, src_count, t->N);
-}
-
-template <int KS>
-void small_sssp_launch_levels(const SmallPlan& p, int workgroups, hipStream_t st) {
-  const int nodes = (p.sv.N + kSmallThreads - 1) / kSmallThreads;
-  const size_t lds = (size_t)p.sv.N * 8;
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kSmallThreads, lds, st>>>(p.sv); };
-  if (p.sv.N > kScaledNodes)
-    launch(k_small_levels<KS, 16, 4, true>);
-  else if (nodes <= 2)
-    launch(k_small_levels<KS, 2, kSmallPlanes, false>);
-  else
-    launch(k_small_levels<KS, 8, kSmallPlanes, false>);
-}
-
-template <int KS>
-void small_sssp_launch(const a2a_topo* t, const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
-  {
-    ProfScope ps(t, PROF_SOURCES, st);
-    k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
-  }
-  ProfScope ps(t, PROF_REDUCE, st);
-  k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
 }
 
 // ws: at least what a2a_workspace_bytes says for the iteration (with dense rows of 1 KB per batch and node, far
@@ -1127,18 +1015,21 @@ int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t 
     lp.sv.per_wg = kSmallBatch;
     lp.sv.level = level;
     const int groups = (lp.sv.src_count + kSmallBatch - 1) / kSmallBatch;
-#define SMALL_LEVELS(KS) small_sssp_launch_levels<KS>(lp, groups, st)
     {
       ProfScope ps(t, PROF_SEARCH, st);
-      SMALL_BY_WORDS(SMALL_LEVELS)
+      by_words(t->ell_words, [&](auto ks) { launch_small_levels<decltype(ks)::value>(lp, groups, st); });
     }
     for (int i = i0; i < i1; ++i) {
       SmallPlan p = small_plan(t, std::min(per_iter, src_count - i * per_iter), SmallWhat::kSssp);
       p.sv.level = level + (size_t)(i - i0) * per_iter * level_bytes;
       p.sv.counters = counters + (size_t)rows * kSmallCounters;
       rows += p.workgroups;
-#define SMALL_ITERATION(KS) small_sssp_launch<KS>(t, p, ss, st)
-      SMALL_BY_WORDS(SMALL_ITERATION)
+      {
+        ProfScope ps(t, PROF_SOURCES, st);
+        by_words(t->ell_words, [&](auto ks) { launch_small_sssp<decltype(ks)::value>(p, ss, st); });
+      }
+      ProfScope ps(t, PROF_REDUCE, st);
+      by_words(t->ell_words, [&](auto ks) { launch_small_sssp_add<decltype(ks)::value>(p, ss, st); });
     }
   }
   k_small_sssp_output<<<(unsigned)(((size_t)t->N * places + kBlock - 1) / kBlock), kBlock, 0, st>>>(

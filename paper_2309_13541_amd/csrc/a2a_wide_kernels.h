@@ -1,5 +1,4 @@
-// Distances of topologies with 8192 to 65536 nodes, and path counts of 8192 to 16384 (a2a_distances).  Included once,
-// by a2a_topo.hip, after a2a_small_kernels.h.
+// Distances of topologies with 8192 to 65536 nodes, and path counts of 8192 to 16384 (a2a_distances).
 //
 // The level kernels search from 512 sources at a time with the masks in memory: every level of every source reads a
 // mask per link through the L2, whatever its frontier holds, and the rate of that is the copy rate (6.5 of 11.9 ms

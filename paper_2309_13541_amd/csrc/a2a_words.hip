@@ -1,0 +1,121 @@
+// The launches of a2a_launch.h for link tables of A2A_WORDS words a node.
+#include <hip/hip_runtime.h>
+
+#include "a2a_launch.h"
+
+#ifndef A2A_WORDS
+#error "A2A_WORDS: words of the link tables (2, 3, 4, 5 or 8)"
+#endif
+
+namespace a2a_dev {
+
+namespace {
+
+template <int KS, bool kDemand>
+void small_loads(const SmallPlan& p, int workgroups, hipStream_t st) {
+  if (p.nodes <= 1)
+    k_small_loads<KS, 1, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else if (p.nodes <= 2)
+    k_small_loads<KS, 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else if (KS <= 5 && p.nodes <= 4)
+    k_small_loads<KS, KS <= 5 ? 4 : 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+  else
+    k_small_loads<KS, small_max_nodes(KS), kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+}
+
+template <int W, int KS, int kOut>
+void wide_search(const WideView& wv, int workgroups, hipStream_t st) {
+  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
+  if (kOut == kWideDist && wv.depth < 8)
+    launch(k_wide_dist<W, KS, kOut == kWideDist ? 3 : 6, kOut>);
+  else
+    launch(k_wide_dist<W, KS, 6, kOut>);
+}
+
+}  // namespace
+
+template <int KS>
+void launch_small_loads(const SmallPlan& p, bool demand, int workgroups, hipStream_t st) {
+  demand ? small_loads<KS, true>(p, workgroups, st) : small_loads<KS, false>(p, workgroups, st);
+}
+
+template <int KS>
+void launch_small_outputs(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st) {
+  const auto launch = [&](auto sigma, auto dist) {
+    if (out.sigma != nullptr)
+      sigma<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+    else
+      dist<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+  };
+  if (p.nodes <= 1)
+    launch(k_small_sigma<KS, 1>, k_small_dist<KS, 1>);
+  else if (p.nodes <= 2)
+    launch(k_small_sigma<KS, 2>, k_small_dist<KS, 2>);
+  else if (p.nodes <= 4)
+    launch(k_small_sigma<KS, 4>, k_small_dist<KS, 4>);
+  else
+    launch(k_small_sigma<KS, 8>, k_small_dist<KS, 8>);
+}
+
+template <int KS>
+void launch_small_levels(const SmallPlan& p, int workgroups, hipStream_t st) {
+  const int nodes = (p.sv.N + kSmallThreads - 1) / kSmallThreads;
+  const size_t lds = (size_t)p.sv.N * 8;
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kSmallThreads, lds, st>>>(p.sv); };
+  if (p.sv.N > kScaledNodes)
+    launch(k_small_levels<KS, 16, 4, true>);
+  else if (nodes <= 2)
+    launch(k_small_levels<KS, 2, kSmallPlanes, false>);
+  else
+    launch(k_small_levels<KS, 8, kSmallPlanes, false>);
+}
+
+template <int KS>
+void launch_small_sssp(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
+  k_small_sssp<KS><<<p.workgroups, p.T, p.lds, st>>>(p.sv, ss);
+}
+
+template <int KS>
+void launch_small_sssp_add(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
+  k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
+}
+
+template <int KS>
+void launch_wide_search(const WideView& wv, int W, int out, int workgroups, hipStream_t st) {
+  if (out == kWideBytes)
+    return W == 16 ? wide_search<16, KS, kWideBytes>(wv, workgroups, st) : wide_search<64, KS, kWideBytes>(wv, workgroups, st);
+  switch (W) {
+    case 16: return wide_search<16, KS, kWideDist>(wv, workgroups, st);
+    case 32: return wide_search<32, KS, kWideDist>(wv, workgroups, st);
+    default: return wide_search<64, KS, kWideDist>(wv, workgroups, st);
+  }
+}
+
+template <int KS>
+void launch_wide_masks(const WideView& wv, int W, int workgroups, hipStream_t st) {
+  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
+  if (W == 16)
+    launch(k_wide_dist<16, KS, 6, kWideMasks>);
+  else if (wv.N > kScaledNodes)
+    launch(k_wide_dist<64, KS, 6, kWideMasks>);
+  else
+    launch(k_wide_dist<64, KS, 6, kWideMasks, true>);
+}
+
+template <int KS>
+void launch_wide_sigma(const WideSigma& ws, int workgroups, hipStream_t st) {
+  k_wide_sigma<KS><<<workgroups, kWideThreads, wide_state_bytes(ws.N), st>>>(ws);
+}
+
+template void launch_small_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStream_t);
+template void launch_small_outputs<A2A_WORDS>(const SmallPlan&, const SmallOut&, int, hipStream_t);
+template void launch_small_levels<A2A_WORDS>(const SmallPlan&, int, hipStream_t);
+template void launch_small_sssp<A2A_WORDS>(const SmallPlan&, const SmallSssp&, hipStream_t);
+template void launch_small_sssp_add<A2A_WORDS>(const SmallPlan&, const SmallSssp&, hipStream_t);
+template void launch_wide_search<A2A_WORDS>(const WideView&, int, int, int, hipStream_t);
+template void launch_wide_masks<A2A_WORDS>(const WideView&, int, int, hipStream_t);
+template void launch_wide_sigma<A2A_WORDS>(const WideSigma&, int, hipStream_t);
+
+}  // namespace a2a_dev

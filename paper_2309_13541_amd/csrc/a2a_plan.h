@@ -101,8 +101,10 @@ constexpr int kStateLoads = 16;  // coef, sigma
 constexpr int kStateSigma = 8;   // sigma
 constexpr int kStateSssp = 5;    // cost, chosen link
 constexpr size_t small_state_bytes(int N, int per, int state) { return ((size_t)per * N * state + 7) & ~(size_t)7; }
-// Counters per level that the sort of a source's nodes works with: lanes that count the same word wait for each other
-// (64 of them 150 cycles), and few levels mean full ones, so they are spread over groups of eight lanes there.
+// Counters per level that the sort of a source's nodes works with: lanes that count the same word wait for each other (an
+// add takes 180 cycles with 64 lanes on a word, 85 with eight, 57 with one), and few levels mean full ones, so they are
+// spread over groups of eight lanes there: single-path baseline of 16384 nodes 3.08 -> 2.60 ms, path counts of 2000 nodes
+// 52 -> 44 us.
 constexpr int small_spread(int depth) { return depth < 16 ? 8 : 1; }
 constexpr size_t small_lds_bytes(int N, int per, int depth, int state) {
   const size_t nq = ((size_t)N + 1) & ~(size_t)1;
@@ -110,7 +112,9 @@ constexpr size_t small_lds_bytes(int N, int per, int depth, int state) {
          (size_t)per * (nq * 2 + (size_t)(depth + 4) * 4 * (1 + small_spread(depth)) + small_level_bytes(N));
 }
 
-// Threads per source: a level of the search has a few percent of the nodes, a lane each.
+// Threads per source: a level of the sweeps has a few percent of the nodes, a lane each.  All sources of random topologies
+// of degree 4, us with 64, 128, 256, 512 threads: path counts of 160 nodes 12.7, 11.8, 11.5, 12.0 and of 385 nodes 19.2, 16.3,
+// 14.6, 14.8; loads of 700 nodes 40.9, 29.7, 29.0, 31.4 and of 4096 nodes 232, 232, 232, 188.
 constexpr int small_threads(int N) { return N <= 96 ? 64 : N <= 384 ? 128 : N <= 1536 ? 256 : 512; }
 
 // The loads of the links of a thread's nodes have to fit its registers: 40 doubles (36 with two words a node).
@@ -154,6 +158,8 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
     c.lds = (size_t)N * 8;
   } else {
     const int want = std::max(1, std::min(kSmallThreads / kSmallWave, src_count / kComputeUnits));
+    // fewest threads of a source that shares its workgroup: 1537 nodes of degree 4 take 50.9 us for their loads with 256,
+    // 57.9 with 128 and 59.4 with 512, a 40x40 torus 96, 93 and 129
     const int least = std::min(tg, 256);
     const int stripes = what == SmallWhat::kSssp ? kSmallStripes : N;  // nodes a thread of a source may sort
     while (per < want && (per + 1) * least <= kSmallThreads && small_lds_bytes(N, per + 1, depth, state) <= kSmallLds &&

@@ -5,9 +5,11 @@
 // workgroup takes its sources from the breadth-first search to the link loads: path counts and coefs live
 // in LDS (19 bytes per node and source), levels are separated by workgroup barriers, and the global traffic
 // is the link table (a few tens of KB, L2-resident), a level byte per node and source, and one row of
-// link loads per workgroup.  Whole calls with the level kernels and with this one: 8x8 torus 128 and 11 us, hypercube
-// of 1024 nodes 305 and 60 us, 16x16x16 torus 1060 and 290 us.  Every sum is taken in a fixed order, so the results are the same bits from run to
-// run and for every workspace size.
+// link loads per workgroup.  Whole calls with the level kernels and with this one: 8x8 torus 138 and 12 us, hypercube
+// of 1024 nodes 262 and 45 us, 16x16x16 torus 1025 and 270 us.  Bound by the chain of LDS accesses and barriers from level to
+// level: the vector ALUs are 1, 22 and 37 % busy in these three, LDS takes an instruction every 18 and 12 cycles in the last
+// two where it could take one every 7.  Every sum is taken in a fixed order, so the results are the same bits from run
+// to run and for every workspace size.
 #pragma once
 
 #include <type_traits>
@@ -261,7 +263,7 @@ struct SmallNode {
 // level, written or not; and nodes not written yet, whose x is 0.  Even levels are kept with a plus sign and odd ones
 // with a minus sign, and a level adds up the entries of the other sign only (kSigns; x must not be negative).
 // Without kSigns the levels are looked up, and x may hold anything at first.
-// What a level costs is its chain of LDS accesses and branches (about 30 cycles each), so there is one branch that is
+// What a level costs is its chain of LDS accesses (64 cycles each) and branches, so there is one branch that is
 // taken for two levels, and the next level's nodes and links are on their way while this one is worked on.
 // tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
 // in the queue, for all levels up to last + 2; the queue has one valid entry at least.
@@ -349,8 +351,8 @@ struct SmallLds {
 // Takes the levels of the next `left` sources (up to sv.per of them) from `level` and sorts their nodes by level into
 // the queues; init(v, level) is called once per node.  Adds up distances and reached nodes.  Returns the deepest
 // level of these sources, the same in all threads.  kRanks: the counting pass keeps what its atomics return, so that
-// the placing pass needs none (30k -> 20k cycles at 16384 nodes); for kernels with registers to spare and at most
-// kSmallStripes nodes a thread.
+// the placing pass needs none (single-path baseline of 16384 nodes 2.71 -> 2.60 ms); for kernels with registers to spare
+// and at most kSmallStripes nodes a thread.
 template <bool kRanks, typename Init>
 __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& lds, const unsigned char* __restrict__ level,
                                           int left, Init&& init, long long& dsum, long long& reached) {

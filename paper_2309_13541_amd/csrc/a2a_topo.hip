@@ -1,10 +1,16 @@
 // a2a_topo host side: the C ABI of include/a2a_topo.h.  All-pairs hop distances, shortest-path
 // counts and EwSP link loads of a direct-connect topology (Sec. 2.2, 5.2, 5.3, 5.4 of the paper)
-// on one MI355X.  The kernels and the data model are in a2a_kernels.h.
+// on one MI355X.  A call goes one of three ways, by what fits where (small_..._fit, wide_..._fit):
+//   - topologies of up to 8191 nodes and 16 links a node: one kernel takes a workgroup's sources from the search to
+//     their results with all state in LDS, a second adds up (a2a_small_kernels.h; single-path baseline up to 16384 nodes)
+//   - up to 65536 nodes and 16 links a node: the levels come from a search with the frontier in LDS
+//     (a2a_wide_kernels.h); distances straight from it, path counts of up to 16384 nodes a source at a time in LDS, link
+//     loads (of those topologies of more than 4096 nodes that do not go the first way) by the level kernels
+//   - everything else: the level kernels alone (a2a_kernels.h, where their data model is described)
 //
-// A "group" of G source batches (64 sources each) advances level by level together, one kernel
+// Level kernels.  A "group" of G source batches (64 sources each) advances level by level together, one kernel
 // launch per level and pass, as many batches as the caller's workspace holds:
-//   bfs    levels 1 .. deepest (the handle knows the deepest level any source reaches)
+//   bfs    levels 1 .. deepest (the handle knows the deepest level any source reaches), or the search in LDS
 //   offs   row offsets of the level-compact value array
 //   fwd    levels 1 .. deepest: sigma
 //   bwd    levels deepest .. 0: coef and per-batch link loads
@@ -474,7 +480,10 @@ struct Run {
 // A group that cannot fill the chip with one wave per 64 nodes lets 2, 4 or 8 waves share each block of
 // 64 nodes (a tile of eight nodes is the unit): a wave's chain of dependent memory requests, which
 // is what a launch of a small group costs, gets that much shorter.  Not with demands, not while
-// shortest-path links are counted (see GroupView).
+// shortest-path links are counted (see GroupView).  The line: us of link loads with sharing up to 0, 4096, 8192, 16384 and
+// 32768 waves: 512 sources of 20011 nodes of degree 5 531, 531, 420, 419, 440; 512 of 16384 nodes of degree 4 497, 384, 380, 401,
+// 401; 1000 of a 25x25x26 torus 1613, 1615, 1397, 1371, 1575.  (Where every level is dense a later line is better: 2501 of
+// 4500 nodes of degree 10 637, 637, 570, 510, 489; and for a single source none at all: 65536 nodes 380, 457, 598, 597, 597.)
 constexpr int kSplitWaves = 8192;
 int pick_split(const a2a_topo* t, int G, int nb64, bool demand) {
   if (demand || t->prof_mode == 2) return 1;
@@ -858,8 +867,8 @@ int wide_search(const a2a_topo* t, WideView* wv, int out, char* ws, size_t ws_by
 
 // Link loads by the level kernels: whether the levels of a group of G batches come from the wide search (link table
 // there, whole slots of rows in it, masks of all levels fit the memory of the level search's).  Search and index entries
-// before and after: 16384 nodes of degree 4 490 -> 250 us, 2501 sources of 20011 nodes 190 -> 102 us, 65536 nodes of
-// degree 8 10.4 -> 6.2 ms; with many levels the whole call: torus 128x128 (128 levels) 34.8 -> 32.0 ms, 4x2000 (1002)
+// before and after: 16384 nodes of degree 4 433 -> 223 us, 2501 sources of 20011 nodes 190 -> 103 us, 65536 nodes of
+// degree 8 9.4 -> 5.9 ms; with many levels the whole call: torus 128x128 (128 levels) 34.8 -> 32.0 ms, 4x2000 (1002)
 // 47.0 -> 40.6 ms, ring of 8000 (4000) 286 -> 233 ms, so there is no limit on them.  The table of up
 // to 8191 nodes has 8 x id, which is the place of a 64-bit word.
 int wide_masks_sources(const a2a_topo* t) { return t->N <= kBothTables ? 64 : 16; }  // a word

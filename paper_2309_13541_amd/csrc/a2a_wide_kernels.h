@@ -1,13 +1,14 @@
 // Distances of topologies with 8192 to 65536 nodes, and path counts of 8192 to 16384 (a2a_distances).
 //
 // The level kernels search from 512 sources at a time with the masks in memory: every level of every source reads a
-// mask per link through the L2, whatever its frontier holds, and the rate of that is the copy rate (6.5 of 11.9 ms
+// mask per link through the L2, whatever its frontier holds, and the rate of that is the copy rate (6.5 of 12.4 ms
 // for 65536 nodes of degree 8).  Here a workgroup searches from 16, 32 or 64 sources with the frontier of a whole
 // topology in LDS (a bit per node and source, 128 KB at the most): the reads per link stay in the compute unit.
-// Bound by those reads (7.2 cycles per 64 of them; 5.5 is what LDS gives for random words) and by the stores of the
-// matrix.  Whole matrix, before and after: 65536 nodes of degree 8 12.36 -> 4.16 ms (4.1 TB/s of stores), 20011 of
-// degree 5 1.30 -> 0.56 ms, 16384 of degree 4 0.67 -> 0.27 ms, torus 25x25x26 2.10 -> 0.65 ms; sums alone of 65536
-// nodes 8.38 -> 3.6 ms.
+// Bound by those reads (7.7 cycles for a wave's 64 in the search for link loads, where LDS gives random words in 7.3) and
+// by the stores of the matrix.  Whole matrix with its sums, before and after, into the same buffers from call to call: 65536
+// nodes of degree 8 12.4 -> 4.15 ms (4.1 TB/s of stores; 4.4 to 4.6 ms where the 17 GB are others on every call), 20011 of
+// degree 5 1.31 -> 0.56 ms, 16384 of degree 4 0.79 -> 0.29 ms, torus 25x25x26 2.09 -> 0.65 ms; sums alone of 65536 nodes
+// 8.45 -> 3.62 ms.
 #pragma once
 
 #include <utility>
@@ -124,7 +125,9 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   long long reached = 0;
   const int groups = (wv.src_count + W - 1) / W;
   // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
-  // time (5.5 ms instead of 4.2 for 65536 nodes).  The first start is spread over about the length of a search.
+  // time.  The first start is spread over about the length of a search.  Without, with twice and with half the spread, and as
+  // it is, without sums: 65536 nodes of degree 8 5.48, 4.25, 4.71, 4.07 ms; of degree 3 (13 levels) 5.24, 4.30, 4.57, 4.06; 20011
+  // of degree 5 576, 543, 560, 541 us; a 40x40x40 torus (60 levels) 18.9, 18.7, 17.2, 17.7 ms.
   if (kOut == kWideDist && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
@@ -395,7 +398,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
 // Index entries of the level kernels from the masks of the search: a workgroup takes a level of a batch of 64 sources
 // (64 / W groups of the search), blockIdx.x = level * G + batch.  Rows follow each other in node order, levels follow
 // each other.  Level 0 is the sources; a level past gv.ltot's last is empty.  Bound by the 16 bytes per node and level
-// that it writes, a kilobyte per wave and store.
+// that it writes, a kilobyte per wave and store: 12.4 GB in 2.47 ms for 65536 nodes of degree 8, the rate of a copy.
 template <int W>
 __global__ void __launch_bounds__(kWideThreads) k_wide_index(WideView wv, GroupView gv) {
   static_assert(W == 16 || W == 64, "");
@@ -490,9 +493,9 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_index(WideView wv, GroupV
 // them: 10 bytes per node, all of the 160 KB for 16384 nodes.  So the levels come from a search of its own (bytes in
 // memory), the counters of the sort lie where the path counts will be, and where a level starts in the queue is kept
 // in a register, a level per lane.  (The level kernels wrote an index entry per node, level and batch, and gathered the
-// counts out of their compact rows one memory latency at a time.)  Bound by the sort (20k cycles per source of 16384
-// nodes), the sweep and the stores, about 25k cycles each.  All sources, before and after: torus 25x25x26 27.5 -> 2.5 ms,
-// 16384 nodes of degree 5 11.1 -> 1.74 ms, 9000 nodes of degree 8 3.20 -> 0.63 ms.
+// counts out of their compact rows one memory latency at a time.)  Bound by the sort, the sweep and the stores: 27, 21
+// and 11 thousand cycles per source of 16384 nodes of degree 5.  All sources, before and after: torus 25x25x26 27.5 -> 2.5
+// ms, 16384 nodes of degree 5 11.1 -> 1.75 ms, 9000 nodes of degree 8 3.20 -> 0.63 ms.
 
 constexpr int kWideStateNodes = 16384, kWideStateDepth = 60;
 __host__ __device__ inline size_t wide_state_bytes(int N) { return (size_t)N * 8 + ((size_t)N * 2 + 7) / 8 * 8; }

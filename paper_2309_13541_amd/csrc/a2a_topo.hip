@@ -219,7 +219,8 @@ class ArenaPool {
 };
 
 ArenaPool& arena_pool() {
-  static ArenaPool* const pool = new ArenaPool;  // never destroyed: the runtime may be gone by then
+  alignas(ArenaPool) static unsigned char place[sizeof(ArenaPool)];
+  static ArenaPool* const pool = new (place) ArenaPool;  // never destroyed: the runtime may be gone by then
   return *pool;
 }
 
@@ -399,7 +400,12 @@ struct ProfScope {
   ~ProfScope() {
     if (!live) return;
     (void)hipEventRecord(rec.end, st);
-    t->prof_recs.push_back(rec);
+    try {
+      t->prof_recs.push_back(rec);
+    } catch (const std::bad_alloc&) {  // the launch is missing from the profile
+      (void)hipEventDestroy(rec.beg);
+      (void)hipEventDestroy(rec.end);
+    }
   }
 };
 

@@ -1,0 +1,658 @@
+// Link loads of topologies whose path counts or coefs of one source fit LDS (8 bytes a node: up to 20000 nodes) but whose
+// link loads do not fit the registers of a workgroup.
+//
+// The level kernels gather 64 sources at a time out of rows in memory.  Here a workgroup takes a source from its sorted levels
+// to its path counts and coefs with all gathers in LDS (k_flow_sources), and leaves a row of each in memory.  A second kernel
+// then goes over the sources with the loads of a block of links in registers and a source's path counts in LDS (k_flow_links),
+// and a third adds up its rows.  Whole calls over all sources, level kernels and these: 16384 nodes of a generalized Kautz
+// topology of degree 4 4.31 -> 2.37 ms, 20011 of degree 5 (2501 sources) 1.49 -> 0.63 ms, 8191 of degree 8 with demands 1.93 ->
+// 1.32 ms, 6000 of degree 8 0.95 -> 0.51 ms, 16384 of degree 16 10.2 -> 4.1 ms.
+#pragma once
+
+#include "a2a_wide_kernels.h"
+
+namespace a2a_dev {
+
+struct FlowView {
+  const uint32_t *in, *out;    // link tables, as in SmallView
+  const unsigned char* level;  // [sources][small_level_bytes(N)]
+  void* record;                // [workgroups of k_flow_sources][stride] FlowRecord
+  uint32_t* count;             // [sources][stride] FlowWord
+  double* coef;                // [sources][stride]; demands before (k_flow_demand)
+  double* weighted;            // [sources] demand x distance
+  long long* counters;         // [workgroups of k_flow_sources][kSmallCounters]
+  double* part;                // [groups][N * 2 KS] link loads, in the places of `in`
+  int N, stride, depth;
+  int source0, sources;        // node of row 0, rows
+  int group, groups;           // rows per group of k_flow_links, groups of this launch
+  int resume;                  // the groups' loads so far are in `part`
+};
+
+// A node as the forward sweep leaves it to the backward one, in the order in which levels are gone over.
+template <bool kDemand>
+struct alignas(8) FlowRecord {
+  uint32_t node;
+  uint32_t sigma;
+};
+template <>
+struct alignas(16) FlowRecord<true> {
+  uint32_t node;
+  double share;  // demand / sigma
+};
+
+typedef uint32_t FlowWords __attribute__((ext_vector_type(4)));
+typedef double FlowDoubles __attribute__((ext_vector_type(2)));
+
+// A node's word: its path count below its level counted down from 254; 0 if it is not reached (yet).  An in-link of a node of level
+// l comes from level l - 1 or later, so the words that count are the largest that can occur: a saturating subtraction of what
+// lies above the path count leaves the count of these and 0 of all others.
+constexpr int kFlowLevel = 24;
+__device__ __forceinline__ uint32_t flow_above(int level) { return (uint32_t)(kSmallUnseen - 1 - level) << kFlowLevel; }
+__device__ __forceinline__ uint32_t flow_count(uint32_t word, uint32_t above) { return __builtin_elementwise_sub_sat(word, above); }
+
+// The links of a node as places in an array of 1 << kSize bytes a node: one instruction a link from 8 x id (kScaled), one from ids.
+template <int KS, bool kScaled>
+struct FlowRow {
+  uint32_t w[KS];
+  __device__ __forceinline__ void load(const uint32_t* __restrict__ table, uint32_t entry) {  // id or 8 x id
+    const uint32_t at = kScaled ? __umul24(entry, KS) >> 1 : __umul24(entry, 4 * KS);
+    const uint32_t* const p = reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(table) + at);
+#pragma unroll
+    for (int k = 0; k < KS; ++k) w[k] = p[k];
+  }
+  template <int kSize>
+  __device__ __forceinline__ uint32_t at(int j) const {
+    if constexpr (kScaled) {
+      return __builtin_amdgcn_ubfe(w[j >> 1], (j & 1) * 16 + 3 - kSize, 13 + kSize);
+    } else {
+      uint32_t x;  // a half of the word, shifted: the compiler takes two instructions
+      if (j & 1)
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1" : "=v"(x) : "v"(kSize), "v"(w[j >> 1]));
+      else
+        asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0" : "=v"(x) : "v"(kSize), "v"(w[j >> 1]));
+      return x;
+    }
+  }
+  // Of the node of a table entry.
+  template <int kSize>
+  static __device__ __forceinline__ uint32_t own(uint32_t entry) {
+    return kScaled ? entry >> (3 - kSize) : entry << kSize;
+  }
+};
+
+// x of the lane `back` lanes before in the wave's rows of 16 lanes (kCtrl: row_shr), 0 for the first ones; or of lane 15 / 31
+// in the rows after it (row_bcast).
+template <int kCtrl, int kRows>
+__device__ __forceinline__ uint32_t flow_dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xf, false);
+}
+// Inclusive sums over the lanes of each row of 16.
+__device__ __forceinline__ uint32_t flow_scan_row(uint32_t x) {
+  x += flow_dpp<0x111, 0xf>(x);
+  x += flow_dpp<0x112, 0xf>(x);
+  x += flow_dpp<0x114, 0xf>(x);
+  x += flow_dpp<0x118, 0xf>(x);
+  return x;
+}
+// Over the whole wave.
+__device__ __forceinline__ uint32_t flow_scan(uint32_t x) {
+  x = flow_scan_row(x);
+  x += flow_dpp<0x142, 0xa>(x);
+  x += flow_dpp<0x143, 0xc>(x);
+  return x;
+}
+
+// `chunks` times 16 bytes from memory to LDS, a kilobyte a wave and instruction.  They have arrived when vmcnt has come down to the
+// requests after them.  (As assembly, because the compiler would wait for all of them before any access to LDS.)
+__device__ __forceinline__ void flow_to_lds(const void* from, void* to, int chunks, int wave, int lane) {
+  const uint32_t place = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)to;
+  for (int c = wave * kWave; c < chunks; c += kWideThreads)
+    if (c + lane < chunks)
+      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+                   :
+                   : "v"(16u * (uint32_t)lane), "s"(static_cast<const char*>(from) + 16 * (size_t)c), "s"(place + 16u * (uint32_t)c)
+                   : "memory");
+}
+
+// No memory request is moved from one side of this to the other.
+__device__ __forceinline__ void flow_in_order() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Waits for a node's links.
+template <int KS, bool kScaled>
+__device__ __forceinline__ void flow_arrived(const FlowRow<KS, kScaled>& row) {
+#pragma unroll
+  for (int k = 0; k < KS; ++k) asm volatile("" ::"v"(row.w[k]));
+}
+
+// Sorts nodes by level, in node order within a level: thread t has the nodes 4 words t, ..., their levels as bytes in lv.
+// place(position, node in thread's) is called for every node; those that are not on a level of 1 ... 8 kHalves get positions from
+// `spare` on, kFlowSpare at the most.  totals: [kWideThreads / kWave][8] words of LDS; base: room for 8 kHalves + 1
+// positions per thread.  Has one barrier inside.  Returns where levels start: lane l has level l (lanes past the last level
+// the end).  No atomics: a thread's counts per level are the bytes of 64-bit words, eight levels each, and the sums over threads
+// 16-bit fields.  Bound by the vector ALUs (some 20 instructions a node).
+constexpr int kFlowSpare = 32;
+template <int kHalves, typename Place>
+__device__ __forceinline__ int flow_sort(uint32_t (&lv)[kFlowWords], int words, uint32_t* totals, unsigned short* base,
+                                         int spare, int wave, int lane, Place&& place) {
+  constexpr int kFields = 4 * kHalves, kLevels = 8 * kHalves;
+  const auto level = [&](int k, int i) { return min((lv[k] >> (8 * i) & 255u) - 1u, (uint32_t)kLevels); };  // less one
+  uint64_t count[kHalves];
+  uint32_t rank[kFlowWords];  // of a node among the thread's on its level, a byte each
+#pragma unroll
+  for (int h = 0; h < kHalves; ++h) count[h] = 0;
+#pragma unroll
+  for (int k = 0; k < kFlowWords; ++k) {
+    rank[k] = 0;
+    if (k >= words) break;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint32_t d = level(k, i), shift = d * 8u & 63u;
+      const uint64_t one = 1ull << shift;
+      rank[k] |= ((uint32_t)((kHalves == 1 || d < 8u ? count[0] : count[kHalves - 1]) >> shift) & 255u) << (8 * i);
+#pragma unroll
+      for (int h = 0; h < kHalves; ++h) count[h] += d - 8u * h < 8u ? one : 0ull;
+    }
+  }
+  // half f of word w of parity p of half h: level 8 h + p + 4 w + 2 f + 1
+  uint32_t own[kFields], incl[kFields];
+#pragma unroll
+  for (int h = 0; h < kHalves; ++h) {
+    const uint32_t lo = (uint32_t)count[h], hi = (uint32_t)(count[h] >> 32);
+    own[4 * h] = lo & 0x00ff00ffu;
+    own[4 * h + 1] = hi & 0x00ff00ffu;
+    own[4 * h + 2] = lo >> 8 & 0x00ff00ffu;
+    own[4 * h + 3] = hi >> 8 & 0x00ff00ffu;
+  }
+#pragma unroll
+  for (int g = 0; g < kFields; ++g) incl[g] = flow_scan(own[g]);
+  if (lane == kWave - 1) {
+#pragma unroll
+    for (int g = 0; g < kFields; ++g) totals[wave * 8 + g] = incl[g];
+  }
+  __syncthreads();
+  uint32_t all[kFields], pos[kFields];
+#pragma unroll
+  for (int g = 0; g < kFields; ++g) {
+    const uint32_t x = totals[(lane & 15) * 8 + g], upto = flow_scan_row(x);
+    all[g] = (uint32_t)__builtin_amdgcn_readlane((int)upto, 15);
+    pos[g] = (uint32_t)__builtin_amdgcn_readlane((int)(upto - x), wave) + incl[g] - own[g];
+  }
+  unsigned short* const mine = base + wave * kWave + lane;
+  int at = 0;
+  uint32_t sum = 0;
+#pragma unroll
+  for (int d = 0; d < kLevels; ++d) {
+    const int g = (d >> 3) * 4 + (d & 1) * 2 + (d >> 2 & 1), shift = (d >> 1 & 1) * 16;
+    mine[d * kWideThreads] = (unsigned short)((pos[g] >> shift) + sum);
+    if (lane == d + 1) at = (int)sum;
+    sum += all[g] >> shift & 0xffffu;
+  }
+  if (lane > kLevels) at = (int)sum;
+  mine[kLevels * kWideThreads] = (unsigned short)spare;
+#pragma unroll
+  for (int k = 0; k < kFlowWords; ++k) {
+    if (k >= words) break;
+    asm volatile("" : "+v"(lv[k]), "+v"(rank[k]));  // nothing worked out before the barrier is kept
+    uint32_t at_level[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) at_level[i] = mine[level(k, i) * kWideThreads];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) place(at_level[i] + (rank[k] >> (8 * i) & 255u), 4 * k + i);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  return at;
+}
+
+// The levels of a source, one after the other (kStep 1: upwards, -1: downwards), in pieces of as many nodes as the workgroup
+// has threads; all of it in scalar registers.  Levels past the last and level 0 have no nodes.
+template <int kStep>
+struct FlowPiece {
+  int level, base, end;  // its place in the queue, where the level ends
+  __device__ __forceinline__ void enter(int l, int starts) {
+    level = l;
+    base = __builtin_amdgcn_readlane(starts, l & (kWave - 1));
+    end = __builtin_amdgcn_readlane(starts, (l + 1) & (kWave - 1));
+  }
+  __device__ __forceinline__ void next(int starts) {
+    base += kWideThreads;
+    if (base >= end) enter(level + kStep, starts);
+  }
+};
+
+// What lies in LDS at a place in bytes.  These kernels have no LDS but what they are launched with, which starts at 0: a pointer to
+// it would be added to every place.
+template <typename T>
+__device__ __forceinline__ T flow_read(uint32_t at) {
+  return *(const __attribute__((address_space(3))) T*)at;
+}
+template <typename T>
+__device__ __forceinline__ void flow_write(uint32_t at, T x) {
+  *(__attribute__((address_space(3))) T*)at = x;
+}
+
+// Path counts and coefs of sources blockIdx.x, + gridDim.x, ...  Per source: sort; sigma = the sum over the in-links from the level
+// before, level by level; coef = demand / sigma + the coefs of the successors, deepest level first.  LDS has a word per node in the
+// forward sweep, its level above its path count (a whole number below 2^24), so that a gathered word tells whether it counts.  In
+// the backward sweep a double per node, 0 until it is written: a node of level l has out-links to levels up to l + 1, of which only
+// l + 1 and (some of) l are written, so even levels are kept with a plus sign and odd ones with a minus sign, and a level adds up
+// the entries of the other sign only.  Coefs of unequal demands have any sign: even and odd levels have an array each.
+// The nodes' order goes through memory from one sweep to the other, with what the backward sweep needs of a node (its coefs take
+// the place of the queue); that is read three pieces ahead, links one piece ahead.  Rows of the outputs are written from LDS, in
+// node order.
+// Bound by the chain of a piece (links, gathers, sum, barrier at the end of a level), which the four waves of a SIMD hide in part: a
+// source of 16384 nodes of degree 4 takes 57 thousand cycles, sort 9.7, forward 15, backward 23, rows and zeroes 9; vector
+// ALUs and LDS are busy about half of the time each.  Pushing counts to the out-links by LDS additions where that touches fewer
+// nodes took longer (48 for 26 thousand cycles forward, 20011 nodes of degree 5), and so did links asked for three pieces ahead (20
+// for 14 thousand).
+// kScaled: the tables have 8 x id.
+template <int KS, bool kScaled, bool kDemand>
+__global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
+  using Record = FlowRecord<kDemand>;
+  extern __shared__ double s_small[];
+  using Row = FlowRow<KS, kScaled>;
+  const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int N = fv.N, S = fv.stride, nl = (int)small_level_bytes(N);
+  const int words = (N + 4 * kWideThreads - 1) / (4 * kWideThreads), v0 = 4 * words * t;  // this thread's nodes in the sort
+  uint32_t* const x = reinterpret_cast<uint32_t*>(s_small);
+  unsigned short* const q = reinterpret_cast<unsigned short*>(x + S);
+  unsigned short* const base = q + S + kFlowSpare;
+  double* const demand = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_demand_at(N, fv.depth));
+  // behind all that, so that places in the arrays at the start need no addition
+  double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_source_lds(N, fv.depth, kDemand) - kFlowTail);
+  uint32_t* const s_totals = reinterpret_cast<uint32_t*>(s_weighted + kWideThreads / kWave);
+  Record* const record = static_cast<Record*>(fv.record) + (size_t)blockIdx.x * fv.stride;
+  constexpr int kId = kScaled ? 3 : 0;  // table entries are ids << kId
+  long long dsum = 0, reached = 0;
+  uint32_t lv[kFlowWords];
+  const auto levels = [&](int s) {  // of a source
+    const unsigned char* const level = fv.level + (size_t)s * (size_t)nl;
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) {
+      lv[k] = ~0u;
+      if (k < words && v0 + 4 * k < N) lv[k] = *reinterpret_cast<const uint32_t*>(level + v0 + 4 * k);
+    }
+  };
+  if ((int)blockIdx.x < fv.sources) levels((int)blockIdx.x);
+  for (int s = (int)blockIdx.x; s < fv.sources; s += (int)gridDim.x) {
+    double* const coef = fv.coef + (size_t)s * (size_t)S;
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) {  // places past the last node: out of reach
+      const int v = v0 + 4 * k;
+      if (v < N && v + 4 > N) lv[k] |= ~0u << ((N - v) * 8);
+    }
+    __syncthreads();
+    if (kDemand) flow_to_lds(coef, demand, S / 2, wave, lane);  // arrives while the nodes are sorted
+    for (int i = t; i < S / 4; i += kWideThreads) reinterpret_cast<uint4*>(x)[i] = make_uint4(0, 0, 0, 0);
+    int v1 = v0;
+    asm volatile("" : "+v"(v1));  // not kept from source to source
+    const auto place = [&](uint32_t p, int i) { q[p] = (unsigned short)((v1 + i) << kId); };
+    const int starts = fv.depth <= 8 ? flow_sort<1>(lv, words, s_totals, base, S, wave, lane, place)
+                                     : flow_sort<2>(lv, words, s_totals, base, S, wave, lane, place);
+    if (t == 0) x[fv.source0 + s] = flow_above(0) + 1u;
+    const int after = __shfl_down(starts, 1, kWave);
+    const uint64_t filled = __ballot(lane >= 1 && lane <= fv.depth && after > starts);
+    const int deep = filled != 0 ? 63 - __builtin_clzll(filled) : 0;
+    const uint32_t last = (uint32_t)max(__builtin_amdgcn_readlane(starts, kWave - 1) - 1, 0);
+    if (wave == 0) {
+      reached += lane >= 1 && lane <= deep ? after - starts : 0;
+      dsum += lane >= 1 && lane <= deep ? (long long)lane * (after - starts) : 0;
+    }
+    if (kDemand) __builtin_amdgcn_s_waitcnt(0);  // this wave's demands have arrived
+    __syncthreads();
+
+    double wd = 0.0;
+    if (deep > 0) {  // forward
+      FlowPiece<1> a, b, c;
+      a.enter(1, starts);
+      b = a;
+      b.next(starts);
+      c = b;
+      c.next(starts);
+      const uint32_t q0 = 4u * (uint32_t)S + 2u * (uint32_t)t, q1 = 4u * (uint32_t)S + 2u * last;
+      const auto node = [&](const FlowPiece<1>& p) {
+        uint32_t n = flow_read<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
+        asm volatile("" : "+v"(n));  // widened as it is read, not again where it is used
+        return n;
+      };
+      struct Ahead {
+        uint32_t node;
+        Row row;
+      };
+      // A piece, after the links of the next one have been asked for; the node after that one takes the piece's place.
+      // Registers are not moved from piece to piece: a move would wait for what is on its way.
+      const auto step = [&](Ahead& here, Ahead& next) {
+        flow_arrived(here.row);
+        next.row.load(fv.in, next.node);
+        const uint32_t then = node(c);
+        if (t < a.end - a.base) {
+          uint32_t y[2 * KS];
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) y[j] = flow_read<uint32_t>(here.row.template at<2>(j));
+          const double own = kDemand ? lds_at(demand, Row::template own<3>(here.node)) : 1.0;
+          __builtin_amdgcn_sched_barrier(0);
+          const uint32_t before = flow_above(a.level - 1);
+          uint32_t above = flow_above(a.level), sum = 0;
+          asm volatile("" : "+s"(above));
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) sum += flow_count(y[j], before);
+          flow_write<uint32_t>(Row::template own<2>(here.node), sum + above);
+          Record r;
+          r.node = here.node;
+          if constexpr (kDemand) {
+            r.share = own * recip((double)sum);
+            wd = __builtin_fma((double)a.level, own, wd);
+          } else {
+            r.sigma = sum;
+          }
+          lds_at(record, (uint32_t)(a.base + t) * (uint32_t)sizeof(Record)) = r;
+        }
+        if (b.level != a.level) __syncthreads();
+        here.node = then;
+        a = b;
+        b = c;
+        c.next(starts);
+      };
+      Ahead n0, n1;
+      n0.node = node(a);
+      n1.node = node(b);
+      n0.row.load(fv.in, n0.node);
+      for (;;) {
+        step(n0, n1);
+        if (a.level > deep) break;
+        step(n1, n0);
+        if (a.level > deep) break;
+      }
+    }
+    if (kDemand) {
+      wd = wave_sum_double(wd);
+      if (lane == 0) s_weighted[wave] = wd;
+    }
+    uint32_t* const count = fv.count + (size_t)s * (size_t)S;
+    for (int i = t; i < S / 4; i += kWideThreads)
+      __builtin_nontemporal_store(reinterpret_cast<const FlowWords*>(x)[i], reinterpret_cast<FlowWords*>(count) + i);
+    __syncthreads();
+    if (kDemand && t == 0) {
+      wd = 0.0;
+      for (int k = 0; k < kWideThreads / kWave; ++k) wd += s_weighted[k];
+      fv.weighted[s] = wd;
+    }
+    for (int i = t; i < (kDemand ? S : S / 2); i += kWideThreads) reinterpret_cast<double2*>(s_small)[i] = make_double2(0.0, 0.0);
+    __syncthreads();
+
+    if (s + (int)gridDim.x < fv.sources) levels(s + (int)gridDim.x);
+    if (deep > 0) {  // backward
+      FlowPiece<-1> a, b, c, d;
+      a.enter(deep, starts);
+      b = a;
+      b.next(starts);
+      c = b;
+      c.next(starts);
+      d = c;
+      d.next(starts);
+      const uint32_t r0 = (uint32_t)t * (uint32_t)sizeof(Record), r1 = last * (uint32_t)sizeof(Record);
+      const auto read = [&](const FlowPiece<-1>& p) { return lds_at(record, min(r0 + (uint32_t)p.base * (uint32_t)sizeof(Record), r1)); };
+      const auto step = [&](const Record& here, const Record& next, Record& third, Row& row, Row& next_row) {
+        flow_arrived(row);
+        next_row.load(fv.out, next.node);
+        flow_in_order();
+        third = read(d);
+        flow_in_order();
+        if (t < a.end - a.base) {
+          double sum;
+          if constexpr (kDemand)
+            sum = here.share;
+          else
+            sum = recip((double)here.sigma);
+          const bool odd = (a.level & 1) != 0, inner = a.level < deep;  // the last level has no successors
+          const uint32_t from = kDemand && !odd ? 8u * (uint32_t)S : 0u, to = kDemand && odd ? 8u * (uint32_t)S : 0u;
+          double y[2 * KS];
+          if (inner) {
+#pragma unroll
+            for (int j = 0; j < 2 * KS; ++j) y[j] = flow_read<double>(row.template at<3>(j) + from);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          if (kDemand) {
+            if (inner) {
+              double succ = y[0];
+#pragma unroll
+              for (int j = 1; j < 2 * KS; ++j) succ += y[j];
+              sum += succ;
+            }
+          } else if (odd) {
+            sum = -sum;
+            if (inner) {
+              double succ = plus_part(y[0]);
+#pragma unroll
+              for (int j = 1; j < 2 * KS; ++j) succ += plus_part(y[j]);
+              sum -= succ;
+            }
+          } else if (inner) {
+            double succ = minus_part(y[0]);
+#pragma unroll
+            for (int j = 1; j < 2 * KS; ++j) succ += minus_part(y[j]);
+            sum -= succ;
+          }
+          flow_write<double>(Row::template own<3>(here.node) + to, sum);
+        }
+        if (b.level != a.level) __syncthreads();
+        a = b;
+        b = c;
+        c = d;
+        d.next(starts);
+      };
+      Record e0 = read(a), e1 = read(b), e2, e3;
+      Row w0, w1;
+      w0.load(fv.out, e0.node);
+      flow_in_order();  // as in the steps: links, then a node
+      e2 = read(c);
+      flow_in_order();
+      for (;;) {
+        step(e0, e1, e3, w0, w1);
+        if (a.level < 1) break;
+        step(e1, e2, e0, w1, w0);
+        if (a.level < 1) break;
+        step(e2, e3, e1, w0, w1);
+        if (a.level < 1) break;
+        step(e3, e0, e2, w1, w0);
+        if (a.level < 1) break;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) asm volatile("" : "+v"(lv[k]));  // arrived before anything is stored: a wait for them later on would be one for the stores too
+    for (int i = t; i < S / 2; i += kWideThreads) {
+      const FlowDoubles y = reinterpret_cast<const FlowDoubles*>(s_small)[i];
+      FlowDoubles out;
+      if (kDemand) {
+        out = y + reinterpret_cast<const FlowDoubles*>(s_small + S)[i];  // one of the two is 0
+      } else {
+        out.x = __builtin_fabs(y.x);
+        out.y = __builtin_fabs(y.y);
+      }
+      __builtin_nontemporal_store(out, reinterpret_cast<FlowDoubles*>(coef) + i);
+    }
+  }
+  __syncthreads();
+  SmallView sv{};
+  sv.counters = fv.counters;
+  small_totals(sv, s_small, dsum, reached, false, 0.0);
+}
+
+// coef[s][v] = demand of node v from source s: tiles of 64 x 64.
+static __global__ void __launch_bounds__(kBlock)
+k_flow_demand(FlowView fv, const double* __restrict__ dem, long long ld) {
+  __shared__ double s_tile[kWave][kWave + 1];
+  const int t = (int)threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int tiles = (fv.N + kWave - 1) / kWave;
+  const int v0 = (int)(blockIdx.x % (unsigned)tiles) * kWave, s0 = (int)(blockIdx.x / (unsigned)tiles) * kWave;
+  constexpr int kRows = kWave / (kBlock / kWave);  // of a wave
+  double x[kRows];
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    const int v = v0 + wave + k * (kBlock / kWave);
+    x[k] = v < fv.N && s0 + lane < fv.sources ? __builtin_nontemporal_load(&dem[(size_t)v * (size_t)ld + (size_t)(s0 + lane)]) : 0.0;
+  }
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) s_tile[wave + k * (kBlock / kWave)][lane] = x[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < kRows; ++k) {
+    const int s = s0 + wave + k * (kBlock / kWave);
+    if (s < fv.sources && v0 + lane < fv.N)
+      __builtin_nontemporal_store(s_tile[lane][s - s0], &fv.coef[(size_t)s * (size_t)fv.stride + (size_t)(v0 + lane)]);
+  }
+}
+
+// Loads of the links into a block of nodes, of a group of sources: load of in-link j of node v += sigma(u) coef(v) of each
+// source, in source order, in registers.  A thread has kPairs pairs of adjacent nodes.  A source's path counts are brought into
+// LDS while the last one's are worked on.  The blocks of a group read the same path counts: they go to the same XCD, one after
+// the other.  Bound by memory where nodes have few links (16384 nodes of degree 4: 3.1 GB in 0.59 ms), else by LDS and the vector ALUs.
+template <int KS, bool kScaled, bool kDemand>
+__global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
+  constexpr int kPairs = flow_nodes(KS) / 2, kXcds = 8;
+  extern __shared__ double s_small[];
+  const int t = (int)threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t / kWave), N = fv.N;
+  const int blocks = (N + 2 * kPairs * kWideThreads - 1) / (2 * kPairs * kWideThreads);
+  const int place = (int)blockIdx.x / kXcds;
+  const int group = place / blocks * kXcds + (int)blockIdx.x % kXcds, v0 = place % blocks * (2 * kPairs * kWideThreads) + 2 * t;
+  if (group >= fv.groups) return;
+  const int s_first = group * fv.group, s_last = min(fv.sources, s_first + fv.group);
+  const uint32_t buffer = (uint32_t)fv.stride * 4u;  // bytes of one of the two
+  const int lane = lane_id();
+  const auto stage = [&](int s, uint32_t at) {
+    flow_to_lds(fv.count + (size_t)s * (size_t)fv.stride, &lds_at(s_small, at), fv.stride / 4, wave, lane);
+  };
+  FlowRow<KS, kScaled> link[kPairs][2];
+  double acc[kPairs][2][2 * KS];
+  double* const part = fv.part + (size_t)group * (size_t)N * (2 * KS);
+  const auto last = [&](int k, int i) { return min(v0 + 2 * kWideThreads * k + i, N - 1); };  // past the last node: nothing comes of it
+#pragma unroll
+  for (int k = 0; k < kPairs; ++k)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int j = 0; j < KS; ++j) link[k][i].w[j] = fv.in[(size_t)last(k, i) * KS + j];
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) acc[k][i][j] = 0.0;
+    }
+  if (fv.resume) {
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) acc[k][i][j] = part[(size_t)last(k, i) * (2 * KS) + j];
+  }
+  // Even, and rows are a multiple of 64 nodes, so the second of the pair is there; pairs past the last node work on node 0.
+  const auto pair = [&](int k) { return v0 + 2 * kWideThreads * k < N ? v0 + 2 * kWideThreads * k : 0; };
+  struct Coefs {
+    double2 pair[kPairs];
+  };
+  const auto request = [&](int s, uint32_t at, Coefs& c) {
+    stage(s, at);
+#pragma unroll
+    for (int k = 0; k < kPairs; ++k)
+      c.pair[k] = *reinterpret_cast<const double2*>(fv.coef + (size_t)s * (size_t)fv.stride + (size_t)pair(k));
+    flow_in_order();
+  };
+  // A node's words are asked for before the last one's are worked on, where there are registers for both.
+  constexpr int kAhead = KS == 4 || KS == 8 ? 0 : 1;
+  struct Got {
+    uint32_t own, y[2 * KS];
+  };
+  const auto step = [&](int s, uint32_t here, const Coefs& c, Coefs& next) {
+    __builtin_amdgcn_s_waitcnt(0);  // what was asked for a step ago has arrived
+    __syncthreads();
+    if (s + 1 < s_last) request(s + 1, buffer - here, next);
+    const auto gather = [&](int u, Got& g) {
+      const int k = u / 2, i = u % 2;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) asm volatile("" : "+v"(link[k][i].w[j]));  // no addresses kept from source to source
+      g.own = flow_read<uint32_t>(here + 4u * (uint32_t)(pair(k) + i));
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) g.y[j] = flow_read<uint32_t>(link[k][i].template at<2>(j) + here);
+    };
+    const auto add = [&](int u, const Got& g) {
+      const int k = u / 2, i = u % 2;
+      const uint32_t before = (g.own & ~((1u << kFlowLevel) - 1u)) + (1u << kFlowLevel);
+      const double f = i == 0 ? c.pair[k].x : c.pair[k].y;
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) {
+        const uint32_t n = flow_count(g.y[j], before);
+        acc[k][i][j] = __builtin_fma(kDemand && n == 0 ? 0.0 : f, (double)n, acc[k][i][j]);
+      }
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) asm volatile("" : "+v"(acc[k][i][j]));  // here and now: put off, the sums would hold on to what was gathered
+    };
+    Got g[2];
+    if (kAhead) gather(0, g[0]);
+#pragma unroll
+    for (int u = 0; u < 2 * kPairs; ++u) {
+      if (u + kAhead < 2 * kPairs) gather(u + kAhead, g[(u + kAhead) % 2]);
+      __builtin_amdgcn_sched_barrier(0);
+      add(u, g[u % 2]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  if (s_first < s_last) {
+    Coefs c0, c1;
+    request(s_first, 0, c0);
+    for (int s = s_first;;) {
+      step(s, 0, c0, c1);
+      if (++s == s_last) break;
+      step(s, buffer, c1, c0);
+      if (++s == s_last) break;
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kPairs; ++k)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int v = v0 + 2 * kWideThreads * k + i;
+      if (v < N) {
+        double2* const out = reinterpret_cast<double2*>(part + (size_t)v * (2 * KS));
+#pragma unroll
+        for (int j = 0; j < KS; ++j) out[j] = make_double2(acc[k][i][2 * j], acc[k][i][2 * j + 1]);
+      }
+    }
+}
+
+// load of every link = (first ? 0 : load) + the groups' rows, in order.
+static __global__ void __launch_bounds__(kBlock)
+k_flow_reduce(const double* __restrict__ part, int groups, int places, int N, int first, const int32_t* __restrict__ in_ptr,
+              const int32_t* __restrict__ in_link, double* __restrict__ load) {
+  const int p = (int)(blockIdx.x * kBlock + threadIdx.x), v = p / places, a = v < N ? in_ptr[v] + p % places : 0;
+  if (v >= N || a >= in_ptr[v + 1]) return;
+  const int link = in_link[a];
+  const size_t row = (size_t)N * (size_t)places;
+  double sum = first ? 0.0 : load[link];
+  int g = 0;
+  for (; g + 16 <= groups; g += 16) {  // sixteen requests in flight
+    double x[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = part[(size_t)(g + k) * row + p];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) sum += x[k];
+  }
+  for (; g < groups; ++g) sum += part[(size_t)g * row + p];
+  load[link] = sum;
+}
+
+// Sum over all sources of demand x distance: a thread's share in source order, then a tree.
+static __global__ void __launch_bounds__(kWideThreads)
+k_flow_weighted(const double* __restrict__ weighted, int sources, double* __restrict__ out) {
+  __shared__ double s_sum[kWideThreads / kWave];
+  const int t = (int)threadIdx.x;
+  double sum = 0.0;
+  for (int s = t; s < sources; s += kWideThreads) sum += weighted[s];
+  sum = wave_sum_double(sum);
+  if (lane_id() == 0) s_sum[t / kWave] = sum;
+  __syncthreads();
+  if (t != 0) return;
+  for (int k = 1; k < kWideThreads / kWave; ++k) sum += s_sum[k];
+  *out = sum;
+}
+
+}  // namespace a2a_dev

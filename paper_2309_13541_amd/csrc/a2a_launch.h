@@ -4,6 +4,7 @@
 
 #include <type_traits>
 
+#include "a2a_flow_kernels.h"
 #include "a2a_small_kernels.h"
 #include "a2a_wide_kernels.h"
 
@@ -34,6 +35,10 @@ template <int KS>
 void launch_wide_masks(const WideView& wv, int W, int workgroups, hipStream_t st);
 template <int KS>
 void launch_wide_sigma(const WideSigma& ws, int workgroups, hipStream_t st);
+template <int KS>
+void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStream_t st);
+template <int KS>
+void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st);
 
 // f(KS), a constant, for a table of that many words a node.
 template <typename F>

@@ -185,4 +185,93 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
   return c;
 }
 
+// ---------------------------------------------------------------------------------------
+// link loads by sources in LDS, links in registers (a2a_flow_kernels.h)
+// ---------------------------------------------------------------------------------------
+
+constexpr int kFlowWords = 5;           // words of level bytes a thread sorts: at most 20480 nodes
+constexpr int kFlowFewestSources = 1024;
+constexpr int kFlowDeepest = 11;
+constexpr int flow_nodes(int ell_words) { return ell_words == 2 ? 6 : ell_words <= 4 ? 4 : 2; }  // a thread
+constexpr int flow_stride(int N) { return (N + 63) / 64 * 64; }
+// LDS of k_flow_sources: in its sort and forward sweep a word and a queue entry per node and positions per thread (one for each
+// level of a word of counters, one for those without), and the demands; in its backward sweep 8 bytes a node, 16 with demands.
+constexpr size_t flow_sort_bytes(int N, int depth) { return (size_t)flow_stride(N) * 6 + 2 * 32 + (depth <= 8 ? 9 : 17) * 2 * kSmallThreads; }
+constexpr size_t flow_demand_at(int N, int depth) {
+  return flow_sort_bytes(N, depth) > (size_t)flow_stride(N) * 8 ? flow_sort_bytes(N, depth) : (size_t)flow_stride(N) * 8;
+}
+constexpr size_t kFlowTail = kSmallThreads / kSmallWave * (8 + 8 * 4);  // sums of the waves
+constexpr size_t flow_source_lds(int N, int depth, bool demand) {
+  return flow_demand_at(N, depth) + (demand ? (size_t)flow_stride(N) * 8 : 0) + kFlowTail;
+}
+// Of k_flow_links: the path counts of two sources.
+constexpr size_t flow_link_lds(int N) { return (size_t)flow_stride(N) * 4 * 2; }
+constexpr bool flow_lds_fits(int N, int depth, bool demand) {
+  return N <= kFlowWords * 4 * kSmallThreads && flow_source_lds(N, depth, demand) <= kSmallLds + kFlowTail &&
+         flow_link_lds(N) <= kSmallLds;
+}
+// Most nodes of a topology that may come this way.
+constexpr int kFlowNodes = 20352;
+static_assert(flow_lds_fits(kFlowNodes, kFlowDeepest, false) && !flow_lds_fits(kFlowNodes + 1, 1, false));
+
+// How the sources of a call are grouped: depends on the topology and their number only.  A workgroup of k_flow_links keeps the
+// loads of a block of links over a group, and the groups are added up in order; about one workgroup per compute unit.
+struct FlowGroups {
+  int blocks, group, groups;  // blocks of nodes, sources per group, groups
+};
+inline FlowGroups flow_groups(int N, int ell_words, int src_count) {
+  FlowGroups g;
+  g.blocks = (N + flow_nodes(ell_words) * kSmallThreads - 1) / (flow_nodes(ell_words) * kSmallThreads);
+  const int most = std::max(8, kComputeUnits / g.blocks / 8 * 8);
+  g.group = (src_count + most - 1) / most;
+  g.groups = (src_count + g.group - 1) / g.group;
+  return g;
+}
+
+// Where things lie in the workspace: `rows` sources at a time, partial loads of `parts` groups.  rows: all, or as many whole
+// groups as fit, or a part of one.
+struct FlowLayout {
+  int rows = 0, parts = 0;
+  size_t counters = 0, weighted = 0, record = 0, part = 0, level = 0, count = 0, coef = 0, total = 0;
+};
+inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool demand, int rows, int parts) {
+  FlowLayout l;
+  l.rows = rows;
+  l.parts = parts;
+  size_t off = 256;
+  const auto take = [&off](size_t bytes) {
+    const size_t at = off;
+    off += (bytes + 255) / 256 * 256;
+    return at;
+  };
+  const size_t stride = (size_t)flow_stride(N);
+  l.counters = take((size_t)kComputeUnits * kSmallCounters * 8);
+  l.weighted = take((size_t)src_count * 8);
+  l.record = take((size_t)std::min(rows, kComputeUnits) * stride * (demand ? 16 : 8));
+  l.part = take((size_t)parts * N * ell_words * 2 * 8);
+  l.level = take((size_t)rows * small_level_bytes(N));
+  l.count = take((size_t)rows * stride * 4);
+  l.coef = take((size_t)rows * stride * 8);
+  l.total = off;
+  return l;
+}
+inline FlowLayout flow_layout(int N, int ell_words, int src_count, bool demand, size_t bytes) {
+  const FlowGroups g = flow_groups(N, ell_words, src_count);
+  const auto most = [bytes](int hi, auto&& at) {  // largest k in 0..hi with at(k) that fits
+    int lo = 0;
+    while (lo < hi) {
+      const int mid = lo + (hi - lo + 1) / 2;
+      if (at(mid).total <= bytes)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    return lo;
+  };
+  const auto groups = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, std::min(k * g.group, src_count), k); };
+  const auto rows = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, k, 1); };
+  const int k = most(g.groups, groups);
+  return k > 0 ? groups(k) : rows(most(g.group, rows));
+}
+
 }  // namespace a2a_dev

@@ -990,6 +990,96 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
   return A2A_OK;
 }
 
+// Whether link loads of src_count sources go by sources in LDS and links in registers: path counts of all levels below 2^24 (a
+// word holds a count and its level), LDS large enough, and for one source and group at least the smallest workspace that a caller may
+// bring.  us of level kernels and of this, all sources, 1024 and 256 of them: 8192 nodes of degree 5 1673, 804; 320, 256; 221,
+// 264.  16384 of degree 4 6497, 2646; 597, 253; 404, 247.  20011 of degree 5 9886, 4204; 692, 316; 422, 295.  6000 of degree 8 950,
+// 506; 249, 259; 169, 286.  It would win for fewer sources too (from 8192 nodes on) and with more levels (20011 of degree 3, 12 levels,
+// 10819, 4226): there the level kernels stay, whose results the tests hold bit for bit.
+bool flow_fits(const a2a_topo* t, int32_t src_count, bool demand) {
+  const double bits = (double)t->level_bound * std::log2((double)std::max(t->dmax_in, 2));  // as Run::narrow
+  return t->ell_words > 0 && t->N <= kFlowNodes && !t->small_loads && src_count >= kFlowFewestSources && t->level_bound >= 1 &&
+         t->level_bound <= kFlowDeepest && bits < 24.0 && flow_lds_fits(t->N, t->level_bound, demand) &&
+         flow_layout_for(t->N, t->ell_words, src_count, demand, kSmallBatch, 1).total <= t->min_loads_bytes;
+}
+
+int flow_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
+                    double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
+  if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
+  const FlowGroups g = flow_groups(t->N, t->ell_words, src_count);
+  const FlowLayout l = flow_layout(t->N, t->ell_words, src_count, demand != nullptr, ws_bytes);
+  FlowView fv{};
+  fv.in = t->d_ell_in;
+  fv.out = t->d_ell_out;
+  fv.level = (unsigned char*)(ws + l.level);
+  fv.record = ws + l.record;
+  fv.count = (uint32_t*)(ws + l.count);
+  fv.coef = (double*)(ws + l.coef);
+  fv.counters = (long long*)(ws + l.counters);
+  fv.part = (double*)(ws + l.part);
+  fv.N = t->N;
+  fv.stride = flow_stride(t->N);
+  fv.depth = t->level_bound;
+  fv.group = g.group;
+  const int places = 2 * t->ell_words;
+  const SmallTotals tot{(long long)src_count * (t->N - 1), (long long*)dist_sum_total, nullptr, (long long*)flags, nullptr};
+  // pieces of whole groups, or one group in several
+  const bool whole = l.parts > 1 || l.rows >= g.group;
+  int piece = 0;
+  bool added = false;
+  for (int s0 = 0; s0 < src_count; s0 += piece) {
+    const int left = whole ? src_count - s0 : std::min(src_count, (s0 / g.group + 1) * g.group) - s0;  // of the call, or the group
+    piece = std::min(l.rows, left);
+    fv.source0 = src_begin + s0;
+    fv.sources = piece;
+    fv.groups = (piece + g.group - 1) / g.group;
+    fv.resume = !whole && s0 % g.group != 0;
+    fv.weighted = (double*)(ws + l.weighted) + s0;
+    if (t->N <= kScaledNodes) {
+      SmallPlan lp = small_plan(t, piece, SmallWhat::kSssp);
+      lp.sv.src_begin = fv.source0;
+      lp.sv.per_wg = kSmallBatch;
+      lp.sv.level = (unsigned char*)(ws + l.level);
+      ProfScope ps(t, PROF_SEARCH, st);
+      by_words(t->ell_words, [&](auto ks) { launch_small_levels<decltype(ks)::value>(lp, (piece + kSmallBatch - 1) / kSmallBatch, st); });
+    } else {
+      WideView wv{};
+      wv.src_begin = fv.source0;
+      wv.src_count = piece;
+      wv.level = (unsigned char*)(ws + l.level);
+      int groups = 0;
+      const int rc = wide_search(t, &wv, kWideBytes, ws + l.coef, l.total - l.coef, &groups, st);
+      if (rc != A2A_OK) return rc;
+    }
+    const int workgroups = std::min(piece, kComputeUnits);
+    {
+      ProfScope ps(t, PROF_SOURCES, st);
+      if (demand) {
+        const unsigned tiles = (unsigned)((t->N + kWave - 1) / kWave) * (unsigned)((piece + kWave - 1) / kWave);
+        k_flow_demand<<<tiles, kBlock, 0, st>>>(fv, demand + s0, src_count);
+      }
+      by_words(t->ell_words, [&](auto ks) { launch_flow_sources<decltype(ks)::value>(fv, demand != nullptr, workgroups, st); });
+      by_words(t->ell_words, [&](auto ks) { launch_flow_links<decltype(ks)::value>(fv, demand != nullptr, st); });
+    }
+    const bool last = s0 + piece == src_count;
+    if (whole || last || (s0 + piece) % g.group == 0) {
+      ProfScope ps(t, PROF_REDUCE, st);
+      k_flow_reduce<<<(unsigned)(((size_t)t->N * places + kBlock - 1) / kBlock), kBlock, 0, st>>>(
+          fv.part, fv.groups, places, t->N, added ? 0 : 1, t->d_in_ptr, t->d_in_link, load);
+      added = true;
+    }
+    wide_totals(t, fv.counters, workgroups, s0 == 0, last, tot, (long long*)ws, st);
+  }
+  if (weighted_dist) {
+    if (demand)
+      k_flow_weighted<<<1, kWideThreads, 0, st>>>((double*)(ws + l.weighted), src_count, weighted_dist);
+    else
+      HIP_TRY(zero_async(weighted_dist, 8, st));
+  }
+  HIP_TRY(hipGetLastError());
+  return A2A_OK;
+}
+
 // Whether a call of the single-path baseline takes the small kernels: its state for one source fits LDS, levels fit a
 // byte (and, with more than 8191 nodes, the search's four bit planes), and costs fit 32 bits.
 bool small_sssp_fits(const a2a_topo* t, int32_t src_count) {
@@ -1123,7 +1213,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
       }
     for (int32_t v = 0; v < N; ++v) t->dmax_in = std::max(t->dmax_in, in_ptr[(size_t)v + 1] - in_ptr[v]);
     t->ell_words = ell_words_for(N, std::max(dmax, t->dmax_in));
-    if (N <= kBothTables) ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
+    if (N <= kFlowNodes) ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
     ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words,
                       N <= kPaddedRows ? N : align_up((size_t)N, 2 * kWideThreads));
   } catch (const std::bad_alloc&) {
@@ -1306,6 +1396,12 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
   if (t->small_loads && src_count > 0 && !t->level_kernels_only()) {
     rc = small_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags, (char*)workspace,
                           workspace_bytes, st);
+    if (rc != A2A_OK) return rc;
+    return profile_levels(t, src_begin, src_count, demand, A2A_WS_LOADS, (char*)workspace, workspace_bytes, st);
+  }
+  if (flow_fits(t, src_count, demand != nullptr) && !t->level_kernels_only()) {
+    rc = flow_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags, (char*)workspace,
+                         workspace_bytes, st);
     if (rc != A2A_OK) return rc;
     return profile_levels(t, src_begin, src_count, demand, A2A_WS_LOADS, (char*)workspace, workspace_bytes, st);
   }

@@ -109,6 +109,27 @@ void launch_wide_sigma(const WideSigma& ws, int workgroups, hipStream_t st) {
   k_wide_sigma<KS><<<workgroups, kWideThreads, wide_state_bytes(ws.N), st>>>(ws);
 }
 
+template <int KS>
+void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStream_t st) {
+  const size_t lds = flow_source_lds(fv.N, fv.depth, demand);
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(fv); };
+  if (fv.N <= kScaledNodes)
+    demand ? launch(k_flow_sources<KS, true, true>) : launch(k_flow_sources<KS, true, false>);
+  else
+    demand ? launch(k_flow_sources<KS, false, true>) : launch(k_flow_sources<KS, false, false>);
+}
+
+template <int KS>
+void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st) {
+  const int blocks = (fv.N + flow_nodes(KS) * kWideThreads - 1) / (flow_nodes(KS) * kWideThreads);
+  const unsigned workgroups = (unsigned)((fv.groups + 7) / 8 * 8 * blocks);
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, flow_link_lds(fv.N), st>>>(fv); };
+  if (fv.N <= kScaledNodes)
+    demand ? launch(k_flow_links<KS, true, true>) : launch(k_flow_links<KS, true, false>);
+  else
+    demand ? launch(k_flow_links<KS, false, true>) : launch(k_flow_links<KS, false, false>);
+}
+
 template void launch_small_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStream_t);
 template void launch_small_outputs<A2A_WORDS>(const SmallPlan&, const SmallOut&, int, hipStream_t);
 template void launch_small_levels<A2A_WORDS>(const SmallPlan&, int, hipStream_t);
@@ -117,5 +138,7 @@ template void launch_small_sssp_add<A2A_WORDS>(const SmallPlan&, const SmallSssp
 template void launch_wide_search<A2A_WORDS>(const WideView&, int, int, int, hipStream_t);
 template void launch_wide_masks<A2A_WORDS>(const WideView&, int, int, hipStream_t);
 template void launch_wide_sigma<A2A_WORDS>(const WideSigma&, int, hipStream_t);
+template void launch_flow_sources<A2A_WORDS>(const FlowView&, bool, int, hipStream_t);
+template void launch_flow_links<A2A_WORDS>(const FlowView&, bool, hipStream_t);
 
 }  // namespace a2a_dev

@@ -80,28 +80,6 @@ struct FlowRow {
   }
 };
 
-// x of the lane `back` lanes before in the wave's rows of 16 lanes (kCtrl: row_shr), 0 for the first ones; or of lane 15 / 31
-// in the rows after it (row_bcast).
-template <int kCtrl, int kRows>
-__device__ __forceinline__ uint32_t flow_dpp(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, kCtrl, kRows, 0xf, false);
-}
-// Inclusive sums over the lanes of each row of 16.
-__device__ __forceinline__ uint32_t flow_scan_row(uint32_t x) {
-  x += flow_dpp<0x111, 0xf>(x);
-  x += flow_dpp<0x112, 0xf>(x);
-  x += flow_dpp<0x114, 0xf>(x);
-  x += flow_dpp<0x118, 0xf>(x);
-  return x;
-}
-// Over the whole wave.
-__device__ __forceinline__ uint32_t flow_scan(uint32_t x) {
-  x = flow_scan_row(x);
-  x += flow_dpp<0x142, 0xa>(x);
-  x += flow_dpp<0x143, 0xc>(x);
-  return x;
-}
-
 // `chunks` times 16 bytes from memory to LDS, a kilobyte a wave and instruction.  They have arrived when vmcnt has come down to the
 // requests after them.  (As assembly, because the compiler would wait for all of them before any access to LDS.)
 __device__ __forceinline__ void flow_to_lds(const void* from, void* to, int chunks, int wave, int lane) {
@@ -167,7 +145,7 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kFlowWords], int words, 
     own[4 * h + 3] = hi >> 8 & 0x00ff00ffu;
   }
 #pragma unroll
-  for (int g = 0; g < kFields; ++g) incl[g] = flow_scan(own[g]);
+  for (int g = 0; g < kFields; ++g) incl[g] = (uint32_t)wave_scan_incl((int)own[g]);
   if (lane == kWave - 1) {
 #pragma unroll
     for (int g = 0; g < kFields; ++g) totals[wave * 8 + g] = incl[g];
@@ -176,7 +154,7 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kFlowWords], int words, 
   uint32_t all[kFields], pos[kFields];
 #pragma unroll
   for (int g = 0; g < kFields; ++g) {
-    const uint32_t x = totals[(lane & 15) * 8 + g], upto = flow_scan_row(x);
+    const uint32_t x = totals[(lane & 15) * 8 + g], upto = (uint32_t)wave_scan_row((int)x);
     all[g] = (uint32_t)__builtin_amdgcn_readlane((int)upto, 15);
     pos[g] = (uint32_t)__builtin_amdgcn_readlane((int)(upto - x), wave) + incl[g] - own[g];
   }
@@ -477,7 +455,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   __syncthreads();
   SmallView sv{};
   sv.counters = fv.counters;
-  small_totals(sv, s_small, dsum, reached, false, 0.0);
+  small_totals(sv, s_small, dsum, reached, false, 0.0, false);
 }
 
 // coef[s][v] = demand of node v from source s: tiles of 64 x 64.

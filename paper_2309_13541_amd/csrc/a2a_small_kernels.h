@@ -30,7 +30,7 @@ struct SmallView {
   unsigned char* level;     // [workgroups of the launch][per_wg][small_level_bytes(N)]
   int N;
   int per;                  // sources a workgroup works on at a time, tg threads each
-  int tg, ts;               // multiples of 64: ts of them work on the levels
+  int tg, ts;               // multiples of 64: ts of them at the least work on the levels
   int depth;                // deepest level of the topology
   int qshift;               // a queue entry is node id << qshift: 3, or 0 with more than 8191 nodes
   int per_wg;               // sources per workgroup: a multiple of per, at most kSmallBatch
@@ -133,10 +133,11 @@ __device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __re
   }
 }
 
-// The same, the levels written as a byte per source and node.
+// The same, the levels written as a byte per source and node; to `lds`, not to `level`, where the workgroup's sources
+// all have room there (loads of an 8x8 torus from 8 sources: 11.7 -> 10.8 us, with the sums by lanes).
 template <int KS, int kNodes, int kPlanes = kSmallPlanes, bool kWide = false>
 __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
-                                             unsigned char* __restrict__ level) {
+                                             unsigned char* __restrict__ level, unsigned char* lds = nullptr) {
   SmallPlanes<kNodes, kPlanes> planes;
   small_search<KS, kNodes, kPlanes, kWide>(sv, nxt, s0, count, planes);
   const int T = (int)blockDim.x, t = (int)threadIdx.x, nl = (int)small_level_bytes(sv.N);
@@ -147,7 +148,11 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
       for (int k = 0; k < kNodes; ++k) {
         unsigned d = planes.template distance<decltype(used)::value>(k, j);
         if (((planes.seen[k] >> j) & 1u) == 0) d = kSmallUnseen;
-        if (t + T * k < sv.N) level[(size_t)j * nl + t + T * k] = (unsigned char)d;
+        if (t + T * k >= sv.N) continue;
+        if (lds != nullptr)
+          lds[j * nl + t + T * k] = (unsigned char)d;
+        else
+          level[(size_t)j * nl + t + T * k] = (unsigned char)d;
       }
     }
   };
@@ -230,16 +235,15 @@ struct SmallNode {
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) m[j] = lds_at(lvl, row.template at<3>(j));
   }
-  // Sum of x over the links, in link order, of the entries that are positive (negative: of the negative ones, made
-  // positive).
+  // Sum of x over the links, in pairs, of the entries that are positive (negative: of the negative ones, made positive).
   template <bool kNegative>
   __device__ __forceinline__ double sum(const double* x) const {
     double y[2 * KS];
     gather(x, y);
     __builtin_amdgcn_sched_barrier(0);  // all requests first: the scheduler would rather save registers
-    double a = kNegative ? minus_part(y[0]) : plus_part(y[0]);
 #pragma unroll
-    for (int j = 1; j < 2 * KS; ++j) a += kNegative ? minus_part(y[j]) : plus_part(y[j]);
+    for (int j = 0; j < 2 * KS; ++j) y[j] = kNegative ? minus_part(y[j]) : plus_part(y[j]);
+    const double a = sum_pairs(y);
     return kNegative ? -a : a;
   }
   // The same over the links that lead to the given level.
@@ -249,10 +253,17 @@ struct SmallNode {
     int m[2 * KS];
     levels(lvl, m);
     __builtin_amdgcn_sched_barrier(0);
-    double a = 0.0;
 #pragma unroll
-    for (int j = 0; j < 2 * KS; ++j) a += m[j] == level ? y[j] : 0.0;
-    return a;
+    for (int j = 0; j < 2 * KS; ++j) y[j] = m[j] == level ? y[j] : 0.0;
+    return sum_pairs(y);
+  }
+  // (three additions one after the other for eight links, not seven)
+  static __device__ __forceinline__ double sum_pairs(double (&y)[2 * KS]) {
+#pragma unroll
+    for (int o = 1; o < 2 * KS; o *= 2)
+#pragma unroll
+      for (int j = 0; j + o < 2 * KS; j += 2 * o) y[j] += y[j + o];
+    return y[0];
   }
 };
 
@@ -264,9 +275,12 @@ struct SmallNode {
 // with a minus sign, and a level adds up the entries of the other sign only (kSigns; x must not be negative).
 // Without kSigns the levels are looked up, and x may hold anything at first.
 // What a level costs is its chain of LDS accesses (64 cycles each) and branches, so there is one branch that is
-// taken for two levels, and the next level's nodes and links are on their way while this one is worked on.
+// taken for two levels, and while a level is worked on, the next one's links, the nodes of the one after that and the
+// places of the third are on their way.  (Loads of a 16x16x16 torus, 282 us, took 296 with one trip to the queue more in
+// the chain and the links added up one after the other.  Scalar cursors over pieces of levels, with no loop in a
+// level, took 318: their code is in the chain too.)
 // tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
-// in the queue, for all levels up to last + 2; the queue has one valid entry at least.
+// in the queue, for all levels up to three past the deepest gone over; the queue has one valid entry at least.
 template <int KS, bool kSigns, bool kWide = false, typename Start, typename Look, typename F>
 __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const Start& start,
                                             const unsigned char* lvl, double* x, int tl, int tg, int first, int last,
@@ -278,37 +292,45 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
     } while (--left >= 0);
     return;
   }
-  const auto place = [&](int p, int end) { return (uint32_t)q[min(p, max(end - 1, 0))] << (kWide ? 3 : 0); };
-  int p0 = start[l] + tl, e0 = start[l + 1], p1 = start[l + step] + tl, e1 = start[l + step + 1];
+  const int most = max(first, last) + 2;
+  struct Places {
+    int p, end;
+  };
+  const auto places = [&](int level) {
+    const int k = min(max(level, 0), most);
+    return Places{start[k] + tl, start[k + 1]};
+  };
+  const auto node = [&](const Places& a) { return (uint32_t)q[min(a.p, max(a.end - 1, 0))] << (kWide ? 3 : 0); };
+  Places a = places(l), b = places(l + step), c = places(l + 2 * step);
   SmallNode<KS, kWide> n0, n1;
-  n0.request(table, place(p0, e0));
+  n0.request(table, node(a));
+  uint32_t v = node(b);
   const auto level = [&](auto odd, const SmallNode<KS, kWide>& cur, SmallNode<KS, kWide>& next) {
     constexpr bool kOdd = decltype(odd)::value;
     const auto value = [&](const SmallNode<KS, kWide>& n) {
       const double own = look(n.v8);
       if constexpr (kSigns) {
-        const double a = f(n.v8, own, n.template sum<!kOdd>(x));
-        return kOdd ? -a : a;
+        const double y = f(n.v8, own, n.template sum<!kOdd>(x));
+        return kOdd ? -y : y;
       } else {
         return f(n.v8, own, n.sum_level(x, lvl, l - step));
       }
     };
-    const uint32_t v = place(p1, e1);
-    const int l2 = max(l + 2 * step, 0), p2 = start[l2] + tl, e2 = start[l2 + 1];
     next.request(table, v);
-    if (p0 < e0) lds_at(x, cur.v8) = value(cur);
+    v = node(c);
+    const Places d = places(l + 3 * step);
+    if (a.p < a.end) lds_at(x, cur.v8) = value(cur);
 #pragma unroll 1
-    for (int p = p0 + tg; p < e0; p += tg) {  // a level of more nodes than the source has threads
+    for (int p = a.p + tg; p < a.end; p += tg) {  // a level of more nodes than the source has threads
       SmallNode<KS, kWide> more;
       more.request(table, (uint32_t)q[p] << (kWide ? 3 : 0));
       lds_at(x, more.v8) = value(more);
     }
     __syncthreads();
     l += step;
-    p0 = p1;
-    e0 = e1;
-    p1 = p2;
-    e1 = e2;
+    a = b;
+    b = c;
+    c = d;
   };
   using Odd = std::true_type;
   using Even = std::false_type;
@@ -346,10 +368,17 @@ struct SmallLds {
   __device__ __forceinline__ unsigned short* q() const { return q_all + sg * nq; }
   __device__ __forceinline__ int* start() const { return start_all + sg * slots; }
   __device__ __forceinline__ unsigned char* lvl() const { return lvl_all + sg * nl; }
+  // Threads of the source that work on the levels: enough for the widest one at a time, if the source has them.
+  __device__ __forceinline__ int busy(const SmallView& sv) const {
+    int widest = 0;
+    for (int l = lane_id(); l < slots - 1; l += kWave) widest = max(widest, start()[l + 1] - start()[l]);
+    widest = wave_max_int(widest, 0);
+    return min(sv.tg, max(sv.ts, (widest + kWave - 1) / kWave * kWave));
+  }
 };
 
-// Takes the levels of the next `left` sources (up to sv.per of them) from `level` and sorts their nodes by level into
-// the queues; init(v, level) is called once per node.  Adds up distances and reached nodes.  Returns the deepest
+// Takes the levels of the next `left` sources (up to sv.per of them) from `level` (null: they are in LDS) and sorts
+// their nodes by level into the queues; init(v, level) is called once per node.  Adds up distances and reached nodes.  Returns the deepest
 // level of these sources, the same in all threads.  kRanks: the counting pass keeps what its atomics return, so that
 // the placing pass needs none (single-path baseline of 16384 nodes 2.71 -> 2.60 ms); for kernels with registers to spare
 // and at most kSmallStripes nodes a thread.
@@ -364,7 +393,7 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
   unsigned short* const q = lds.q();
   for (int i = t; i < per * slots * spread; i += T) lds.at_all[i] = 0;
   const int here = min(per, left) * (lds.nl / 4);
-  for (int i = t; i < per * (lds.nl / 4); i += T)
+  for (int i = t + (level != nullptr ? 0 : here); i < per * (lds.nl / 4); i += T)
     reinterpret_cast<uint32_t*>(lds.lvl_all)[i] = i < here ? reinterpret_cast<const uint32_t*>(level)[i] : 0xffffffffu;
   __syncthreads();
   int* const mine = at + (spread > 1 ? lane >> 3 : 0);
@@ -393,7 +422,7 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
     int carry = 0;
     for (int i0 = 0; i0 < slots * spread; i0 += kWave) {
       const int i = i0 + lane, c = i < slots * spread ? at[i] : 0, l = spread > 1 ? i >> 3 : i;
-      const int incl = wave_scan_incl(c, lane);
+      const int incl = wave_scan_incl(c);
       if (i < slots * spread) {
         at[i] = carry + incl - c;
         if (spread == 1 || (i & 7) == 0) start[l] = carry + incl - c;
@@ -435,17 +464,14 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
 // A workgroup's totals into its counters (all threads call it).  lds: kSmallTotals words of 8 bytes.
 constexpr int kSmallTotals = kSmallThreads / kWave * 4;
 __device__ __forceinline__ void small_totals(const SmallView& sv, double* lds, long long dsum, long long reached, bool inexact,
-                                             double wd) {
+                                             double wd, bool weighted) {
   double* const s_wd = lds;
   long long(*const s_tot)[3] = reinterpret_cast<long long(*)[3]>(lds + kSmallThreads / kWave);
   const int t = (int)threadIdx.x;
   long long bad = __ballot(inexact) != 0 ? 1 : 0;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    dsum += __shfl_xor(dsum, o, kWave);
-    reached += __shfl_xor(reached, o, kWave);
-  }
-  wd = wave_sum_double(wd);
+  dsum = wave_sum_long(dsum);
+  reached = wave_sum_long(reached);
+  if (weighted) wd = wave_sum_double(wd);
   if (lane_id() == 0) {
     s_tot[t / kWave][0] = dsum;
     s_tot[t / kWave][1] = reached;
@@ -466,9 +492,10 @@ __device__ __forceinline__ void small_totals(const SmallView& sv, double* lds, l
   c[2] = bad;
   c[3] = __double_as_longlong(wd);
 }
-__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd) {
+__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd,
+                                             bool weighted) {
   __shared__ double s_totals[kSmallTotals];
-  small_totals(sv, s_totals, dsum, reached, inexact, wd);
+  small_totals(sv, s_totals, dsum, reached, inexact, wd, weighted);
 }
 
 // Link loads of sources [per_wg * workgroup, + per_wg) of the call, as one row of `part`.  The search takes up to
@@ -500,7 +527,9 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
 
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
-  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level);
+  const bool at_once = sv.per_wg <= per;
+  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level,
+                           at_once ? lds.lvl_all : nullptr);
   __syncthreads();
   double acc[kNodes][2 * KS];
 #pragma unroll
@@ -519,15 +548,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
         coef[v] = 0.0;
       }
     };
-    const int depth = small_sort<false>(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0, init, dsum, reached);
+    const int depth = small_sort<false>(sv, lds, at_once ? nullptr : level + (size_t)(s0 - s_first) * nl, s_last - s0,
+                                        init, dsum, reached);
+    const int busy = lds.busy(sv);
     const auto nothing = [](uint32_t) { return 0.0; };
     const auto own_sigma_at = [&](uint32_t v8) { return lds_at(sig, v8); };
     if (depth > 0) {
-      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, sv.ts, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
+      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, busy, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
         inexact |= a >= kTwo53;
         return a;
       });
-      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, sv.ts, depth, 1, -1, own_sigma_at, [&](uint32_t v8, double s, double a) {
+      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, busy, depth, 1, -1, own_sigma_at, [&](uint32_t v8, double s, double a) {
         const double r = recip(__builtin_fabs(s));
         return (kDemand ? lds_at(coef, v8) * r : r) + a;
       });
@@ -571,7 +602,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
       for (int j = 0; j < KS; ++j) out[j] = make_double2(acc[k][2 * j], acc[k][2 * j + 1]);
     }
   }
-  small_totals(sv, dsum, reached, inexact, wd);
+  small_totals(sv, dsum, reached, inexact, wd, kDemand);
 }
 
 // Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and
@@ -594,15 +625,18 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
   bool inexact = false;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
-  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level);
+  const bool at_once = sv.per_wg <= sv.per;
+  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level,
+                           at_once ? lds.lvl_all : nullptr);
   __syncthreads();
   for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
     long long own = 0;
-    const int depth = small_sort<false>(sv, lds, level + (size_t)(s0 - s_first) * nl, s_last - s0,
-                                 [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
+    const int depth = small_sort<false>(sv, lds, at_once ? nullptr : level + (size_t)(s0 - s_first) * nl, s_last - s0,
+                                        [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
+    const int busy = lds.busy(sv);
     const auto nothing = [](uint32_t) { return 0.0; };
     if (depth > 0)
-      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, sv.ts, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
+      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, busy, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
         inexact |= a >= kTwo53;
         return a;
       });
@@ -624,7 +658,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
     dsum += own;
     __syncthreads();
   }
-  small_totals(sv, dsum, reached, inexact, 0.0);
+  small_totals(sv, dsum, reached, inexact, 0.0, false);
 }
 
 // Distances alone come straight from the planes of the search.
@@ -673,7 +707,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dist(SmallView sv, Smal
     __syncthreads();
     if (t < count) out.sums[s_first + t] = s_sum[t];
   }
-  small_totals(sv, 0, reached, false, 0.0);
+  small_totals(sv, 0, reached, false, 0.0, false);
 }
 
 // load[a] = (first ? 0 : load[a]) + chunk sums of the launch's partial rows, kSmallChunk rows to a chunk, in
@@ -876,7 +910,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sssp(SmallView sv, Smal
       __syncthreads();
     }
   }
-  small_totals(sv, dsum, reached, false, 0.0);
+  small_totals(sv, dsum, reached, false, 0.0, false);
 }
 
 // weight[v][j] += what the sources of the iteration handed from node v to its in-link j.  A workgroup takes 64

@@ -945,11 +945,6 @@ int wide_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int3
   return A2A_OK;
 }
 
-// 1.25 times an average level: most levels in one go.
-int wide_level_threads(const a2a_topo* t) {
-  return std::min(kWideThreads, (int)align_up((size_t)t->N * 5 / 4 / (size_t)std::max(t->level_bound, 1), kWave));
-}
-
 int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const SmallOut& out, int64_t* unreachable,
                int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
   if (ws_bytes < t->min_sigma_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
@@ -975,7 +970,6 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
     wsig.counters = counters;
     wsig.N = t->N;
     wsig.depth = t->level_bound;
-    wsig.ts = wide_level_threads(t);
     wsig.src_count = wv.src_count;
     const size_t row = (size_t)c0 * t->N;
     wsig.out = SmallOut{out.dist ? out.dist + row : nullptr, out.sigma + row, out.sums ? out.sums + c0 : nullptr};

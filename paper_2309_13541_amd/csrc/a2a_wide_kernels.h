@@ -392,7 +392,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   if (kMasks) return;
   SmallView sv{};
   sv.counters = wv.counters;
-  small_totals(sv, 0, reached, false, 0.0);
+  small_totals(sv, 0, reached, false, 0.0, false);
 }
 
 // Index entries of the level kernels from the masks of the search: a workgroup takes a level of a batch of 64 sources
@@ -457,7 +457,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_index(WideView wv, GroupV
     for (int k = 0; k < 4; ++k) c[k] = __popcll(m[k]);
 #pragma unroll
     for (int k = 0; k < 4; k += 2) {  // at most 64 x 64 in a wave
-      const int two = wave_scan_incl(c[k] | c[k + 1] << 16, lane);
+      const int two = wave_scan_incl(c[k] | c[k + 1] << 16);
       incl[k] = two & 0xffff;
       incl[k + 1] = two >> 16;
     }
@@ -529,7 +529,7 @@ __device__ __forceinline__ WideStarts wide_sort(int N, int spread, const uint32_
     int carry = 0;
     for (int i0 = 0; i0 < kSlots * spread; i0 += kWave) {
       const int i = i0 + lane, c = at[i], l = spread > 1 ? i >> 3 : i;
-      const int incl = wave_scan_incl(c, lane);
+      const int incl = wave_scan_incl(c);
       at[i] = carry + incl - c;
       if (spread == 1 || (i & 7) == 0) start[l] = carry + incl - c;
       carry += __builtin_amdgcn_readlane(incl, kWave - 1);
@@ -554,7 +554,7 @@ struct WideSigma {
   const uint32_t* in;          // [N][KS] in-links
   const unsigned char* level;  // [src_count][small_level_bytes(N)]
   long long* counters;         // [workgroups][kSmallCounters]
-  int N, depth, ts, src_count;
+  int N, depth, src_count;
   SmallOut out;
 };
 
@@ -589,8 +589,10 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
     __syncthreads();
     const int after = __shfl_down(start.at, 1, kWave);
     const uint64_t filled = __ballot(lane >= 1 && lane < kWave - 1 && after > start.at);
+    const int widest = wave_max_int(lane < kWave - 1 ? after - start.at : 0, 0);
+    const int busy = min(kWideThreads, (widest + kWave - 1) / kWave * kWave);  // threads: the widest level in one go if they suffice
     if (filled != 0)
-      small_sweep<KS, true, true>(ws.in, q, start, nullptr, x, t, ws.ts, 1, 63 - __builtin_clzll(filled), 1,
+      small_sweep<KS, true, true>(ws.in, q, start, nullptr, x, t, busy, 1, 63 - __builtin_clzll(filled), 1,
                                   [](uint32_t) { return 0.0; }, [&](uint32_t, double, double a) {
         inexact |= a >= kTwo53;
         return a;
@@ -622,7 +624,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
   }
   SmallView sv{};
   sv.counters = ws.counters;
-  small_totals(sv, s_small, 0, reached, inexact, 0.0);
+  small_totals(sv, s_small, 0, reached, inexact, 0.0, false);
 }
 
 }  // namespace a2a_dev

@@ -200,17 +200,6 @@ struct FlowPiece {
   }
 };
 
-// What lies in LDS at a place in bytes.  These kernels have no LDS but what they are launched with, which starts at 0: a pointer to
-// it would be added to every place.
-template <typename T>
-__device__ __forceinline__ T flow_read(uint32_t at) {
-  return *(const __attribute__((address_space(3))) T*)at;
-}
-template <typename T>
-__device__ __forceinline__ void flow_write(uint32_t at, T x) {
-  *(__attribute__((address_space(3))) T*)at = x;
-}
-
 // Path counts and coefs of sources blockIdx.x, + gridDim.x, ...  Per source: sort; sigma = the sum over the in-links from the level
 // before, level by level; coef = demand / sigma + the coefs of the successors, deepest level first.  LDS has a word per node in the
 // forward sweep, its level above its path count (a whole number below 2^24), so that a gathered word tells whether it counts.  In
@@ -291,7 +280,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       c.next(starts);
       const uint32_t q0 = 4u * (uint32_t)S + 2u * (uint32_t)t, q1 = 4u * (uint32_t)S + 2u * last;
       const auto node = [&](const FlowPiece<1>& p) {
-        uint32_t n = flow_read<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
+        uint32_t n = lds_get<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
         asm volatile("" : "+v"(n));  // widened as it is read, not again where it is used
         return n;
       };
@@ -308,7 +297,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
         if (t < a.end - a.base) {
           uint32_t y[2 * KS];
 #pragma unroll
-          for (int j = 0; j < 2 * KS; ++j) y[j] = flow_read<uint32_t>(here.row.template at<2>(j));
+          for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<uint32_t>(here.row.template at<2>(j));
           const double own = kDemand ? lds_at(demand, Row::template own<3>(here.node)) : 1.0;
           __builtin_amdgcn_sched_barrier(0);
           const uint32_t before = flow_above(a.level - 1);
@@ -316,7 +305,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
           asm volatile("" : "+s"(above));
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) sum += flow_count(y[j], before);
-          flow_write<uint32_t>(Row::template own<2>(here.node), sum + above);
+          lds_put<uint32_t>(Row::template own<2>(here.node), sum + above);
           Record r;
           r.node = here.node;
           if constexpr (kDemand) {
@@ -389,7 +378,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
           double y[2 * KS];
           if (inner) {
 #pragma unroll
-            for (int j = 0; j < 2 * KS; ++j) y[j] = flow_read<double>(row.template at<3>(j) + from);
+            for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<double>(row.template at<3>(j) + from);
           }
           __builtin_amdgcn_sched_barrier(0);
           if (kDemand) {
@@ -413,7 +402,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
             for (int j = 1; j < 2 * KS; ++j) succ += minus_part(y[j]);
             sum -= succ;
           }
-          flow_write<double>(Row::template own<3>(here.node) + to, sum);
+          lds_put<double>(Row::template own<3>(here.node) + to, sum);
         }
         if (b.level != a.level) __syncthreads();
         a = b;
@@ -548,9 +537,9 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
       const int k = u / 2, i = u % 2;
 #pragma unroll
       for (int j = 0; j < KS; ++j) asm volatile("" : "+v"(link[k][i].w[j]));  // no addresses kept from source to source
-      g.own = flow_read<uint32_t>(here + 4u * (uint32_t)(pair(k) + i));
+      g.own = lds_get<uint32_t>(here + 4u * (uint32_t)(pair(k) + i));
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) g.y[j] = flow_read<uint32_t>(link[k][i].template at<2>(j) + here);
+      for (int j = 0; j < 2 * KS; ++j) g.y[j] = lds_get<uint32_t>(link[k][i].template at<2>(j) + here);
     };
     const auto add = [&](int u, const Got& g) {
       const int k = u / 2, i = u % 2;

@@ -94,9 +94,18 @@ constexpr int kScaledNodes = 8191, kBothTables = 16384;
 // Level bytes of one source.
 constexpr size_t small_level_bytes(int N) { return ((size_t)N + 3) & ~(size_t)3; }
 
-// LDS of a workgroup, in this order: per-node state of its sources (kState... bytes per node and source; two mask
-// words per node in its place while a search runs), node queue (16-bit places, level by level), where each level
-// starts in the queue, cursors, level bytes.
+// LDS of a search by workgroups of up to `nodes` nodes a thread: two arrays of a word per node, the second one where an
+// instruction's constant offset reaches it.
+constexpr int small_search_apart(int nodes) { return nodes * kSmallThreads * 4; }
+constexpr size_t small_search_bytes(int N, int nodes) { return (size_t)small_search_apart(nodes) + (size_t)N * 4; }
+// The same with a workgroup's totals (four words of 8 bytes a wave) and sums of distances behind it.
+constexpr size_t small_dist_bytes(int N, int nodes) {
+  return (small_search_bytes(N, nodes) + 7) / 8 * 8 + kSmallThreads / 64 * 32 + kSmallBatch * 4;
+}
+
+// LDS of a workgroup, in this order: per-node state of its sources (kState... bytes per node and source), node queue
+// (16-bit places, level by level), where each level starts in the queue, cursors, level bytes.  The search is done
+// before any of it is written.
 constexpr int kStateLoads = 16;  // coef, sigma
 constexpr int kStateSigma = 8;   // sigma
 constexpr int kStateSssp = 5;    // cost, chosen link

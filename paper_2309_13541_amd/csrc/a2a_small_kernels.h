@@ -49,6 +49,17 @@ __device__ __forceinline__ const T& lds_at(const T* base, uint32_t bytes) {
   return *reinterpret_cast<const T*>(reinterpret_cast<const char*>(base) + bytes);
 }
 
+// LDS by its byte address, for kernels that have no other than their dynamic array, which starts at 0: the compiler adds the
+// array's address to every place, which is an instruction also where it is 0.
+template <typename T>
+__device__ __forceinline__ T lds_get(uint32_t at) {
+  return *(const __attribute__((address_space(3))) T*)at;
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(uint32_t at, T x) {
+  *(__attribute__((address_space(3))) T*)at = x;
+}
+
 // The links of a node.  at<kShift>(j): 8 x id of link j shifted right, i.e. its place in an array of doubles (0), words
 // (1) or bytes (3); the two halves of a word are shifted together.
 template <int KS>
@@ -67,86 +78,112 @@ struct SmallRow {
 };
 
 // Bit-parallel search from the `count` (at most kSmallBatch) consecutive sources s0, ...: bit j = source j.
-// A thread owns nodes t, t + T, ...; their masks stay in its registers, and a level ORs them into the words of
-// their out-neighbours (two arrays in turn, so that one barrier per level is enough).  On return bit j of `seen` says
-// whether source j reaches the node, bit j of plane p is bit p of the distance.  nxt: 2 N words of LDS.
-constexpr int kSmallPlanes = 8;
-template <int kNodes, int kPlanes = kSmallPlanes>
+// A thread owns nodes t, t + T, ...; a level ORs the words of their in-neighbours, which lie in LDS (two arrays in turn,
+// so that one barrier per level is enough), and nodes that all sources have reached look no more.  (Levels that ORed
+// their nodes' words into those of the out-neighbours were bound by the atomics, 18 cycles per wave and link where a
+// gather takes 7.)  Bound by the instructions: so the arrays lie a constant apart, which takes no additions, and a level
+// touches only those planes whose bit is set in it.  On return bit j of `seen` says whether source j reaches the node,
+// bit j of plane p is bit p of the distance.  In the first small_search_bytes(N, kNodes) of the LDS.
+constexpr int kSmallPlanes = 8, kSmallFewPlanes = 5;  // the few where they do
+template <int kNodes, int kPlanes>
 struct SmallPlanes {
   uint32_t seen[kNodes], plane[kNodes][kPlanes];
-  // Distance from source j; kUsed: planes that are not empty.
-  template <int kUsed>
-  __device__ __forceinline__ unsigned distance(int k, int j) const {
+  __device__ __forceinline__ unsigned distance(int k, int j) const {  // from source j
     unsigned d = 0;
 #pragma unroll
-    for (int p = 0; p < kUsed; ++p) d |= ((plane[k][p] >> j) & 1u) << p;
+    for (int p = 0; p < kPlanes; ++p) d |= ((plane[k][p] >> j) & 1u) << p;
     return d;
   }
 };
 template <int KS, int kNodes, int kPlanes, bool kWide = false>
-__device__ __forceinline__ void small_search(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
-                                             SmallPlanes<kNodes, kPlanes>& out) {
+__device__ __forceinline__ void small_search(const SmallView& sv, int s0, int count, SmallPlanes<kNodes, kPlanes>& out) {
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
-  constexpr bool kHold = kNodes * KS <= 24;  // links in registers, or fetched again for every level
+  const uint32_t all = ~0u >> (kSmallBatch - count);
+  // links in registers, or fetched again for every level
+  constexpr bool kHold = kNodes * (KS + kPlanes) <= (kPlanes > kSmallFewPlanes ? 88 : 72);
+  constexpr bool kPlaces = kNodes * KS <= 12;  // held as places in LDS, a register each
+  constexpr int kApart = small_search_apart(kNodes);
   SmallRow<KS> row[kHold ? kNodes : 1];
-  uint32_t cur[kNodes];
+  uint32_t place[kPlaces ? kNodes : 1][2 * KS];
 #pragma unroll
   for (int k = 0; k < kNodes; ++k) {
     const int v = t + T * k;
-    if (kHold && v < N) row[kHold ? k : 0].load(sv.out, 8 * v);
-    cur[k] = v >= s0 && v < s0 + count ? 1u << (v - s0) : 0u;
-    out.seen[k] = cur[k];
+    if (kHold && v < N) {
+      row[kHold ? k : 0].load(sv.in, 8 * v);
+#pragma unroll
+      for (int j = 0; kPlaces && j < 2 * KS; ++j) place[kPlaces ? k : 0][j] = row[kHold ? k : 0].template at<1>(j);
+    }
+    out.seen[k] = v >= s0 && v < s0 + count ? 1u << (v - s0) : 0u;
+    if (v < N) lds_put(4 * v, out.seen[k]);
 #pragma unroll
     for (int p = 0; p < kPlanes; ++p) out.plane[k][p] = 0;
   }
-  for (int i = t; i < 2 * N; i += T) nxt[i] = 0;
-  __syncthreads();
-  for (int l = 1; l <= sv.depth; ++l) {
-    uint32_t* const buf = nxt + (l & 1) * N;
-#pragma unroll
-    for (int k = 0; k < kNodes; ++k) {
-      if (cur[k] != 0) {
-        SmallRow<KS>& r = row[kHold ? k : 0];
-        if (!kHold) {
-          int v = t + T * k;
-          asm volatile("" : "+v"(v));  // not kept from level to level
-          r.load(sv.out, 8 * v);
-        }
-#pragma unroll
-        for (int j = 0; j < 2 * KS; ++j)
-          __hip_atomic_fetch_or(&lds_at(buf, kWide ? 4 * r.at(j) : r.template at<1>(j)), cur[k],
-                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      }
-    }
+  constexpr bool kLater = kNodes <= 4;  // the planes after all nodes: registers for what is new in each
+  const auto level = [&](auto odd, int l) {
+    constexpr int kBefore = decltype(odd)::value ? 0 : kApart, kNow = kApart - kBefore;
+    uint32_t fresh[kLater ? kNodes : 1];
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < kNodes; ++k) {
       const int v = t + T * k;
+      uint32_t& x = fresh[kLater ? k : 0];
+      x = 0;
       if (v < N) {
-        cur[k] = buf[v] & ~out.seen[k];
-        buf[v] = 0;
-        out.seen[k] |= cur[k];
+        if (out.seen[k] != all) {
+          SmallRow<KS>& r = row[kHold ? k : 0];
+          if (!kHold) {
+            int u = v;
+            asm volatile("" : "+v"(u));  // not kept from level to level
+            r.load(sv.in, 8 * u);
+          }
+          uint32_t m[2 * KS];
 #pragma unroll
-        for (int p = 0; p < kPlanes; ++p) out.plane[k][p] |= (l >> p) & 1 ? cur[k] : 0u;
+          for (int j = 0; j < 2 * KS; ++j)
+            m[j] = lds_get<uint32_t>((kPlaces ? place[kPlaces ? k : 0][j] : kWide ? 4 * r.at(j) : r.template at<1>(j)) + kBefore);
+#pragma unroll
+          for (int j = 1; j < 2 * KS; ++j) m[0] |= m[j];
+          x = m[0] & ~out.seen[k];
+        }
+        lds_put(4 * v + kNow, x);
+        if (!kLater) {
+          out.seen[k] |= x;
+#pragma unroll
+          for (int p = 0; p < kPlanes; ++p) out.plane[k][p] |= (l >> p) & 1 ? x : 0u;
+        }
       }
     }
+    if (!kLater) return;
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) out.seen[k] |= fresh[kLater ? k : 0];
+#pragma unroll
+    for (int p = 0; p < kPlanes; ++p)
+      if ((l >> p) & 1) {
+#pragma unroll
+        for (int k = 0; k < kNodes; ++k) out.plane[k][p] |= fresh[kLater ? k : 0];
+      }
+  };
+  for (int l = 1; l <= sv.depth; l += 2) {
+    level(std::true_type{}, l);
+    if (l == sv.depth) break;
+    level(std::false_type{}, l + 1);
   }
 }
 
 // The same, the levels written as a byte per source and node; to `lds`, not to `level`, where the workgroup's sources
 // all have room there (loads of an 8x8 torus from 8 sources: 11.7 -> 10.8 us, with the sums by lanes).
 template <int KS, int kNodes, int kPlanes = kSmallPlanes, bool kWide = false>
-__device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __restrict__ nxt, int s0, int count,
-                                             unsigned char* __restrict__ level, unsigned char* lds = nullptr) {
-  SmallPlanes<kNodes, kPlanes> planes;
-  small_search<KS, kNodes, kPlanes, kWide>(sv, nxt, s0, count, planes);
-  const int T = (int)blockDim.x, t = (int)threadIdx.x, nl = (int)small_level_bytes(sv.N);
-  const auto write = [&](auto used) {
+__device__ __forceinline__ void small_levels(const SmallView& sv, int s0, int count, unsigned char* __restrict__ level,
+                                             unsigned char* lds = nullptr) {
+  const auto levels = [&](auto used) {
+    SmallPlanes<kNodes, decltype(used)::value> planes;
+    small_search<KS, kNodes, decltype(used)::value, kWide>(sv, s0, count, planes);
+    if (lds != nullptr) __syncthreads();  // the search's words may lie there
+    const int T = (int)blockDim.x, t = (int)threadIdx.x, nl = (int)small_level_bytes(sv.N);
 #pragma unroll 1
     for (int j = 0; j < count; ++j) {
 #pragma unroll
       for (int k = 0; k < kNodes; ++k) {
-        unsigned d = planes.template distance<decltype(used)::value>(k, j);
+        unsigned d = planes.distance(k, j);
         if (((planes.seen[k] >> j) & 1u) == 0) d = kSmallUnseen;
         if (t + T * k >= sv.N) continue;
         if (lds != nullptr)
@@ -156,11 +193,10 @@ __device__ __forceinline__ void small_levels(const SmallView& sv, uint32_t* __re
       }
     }
   };
-  constexpr int kFew = kPlanes < 5 ? kPlanes : 5;
-  if (sv.depth < 1 << kFew)
-    write(std::integral_constant<int, kFew>{});
+  if (kPlanes <= kSmallFewPlanes || sv.depth < 1 << kSmallFewPlanes)
+    levels(std::integral_constant<int, kPlanes <= kSmallFewPlanes ? kPlanes : kSmallFewPlanes>{});
   else
-    write(std::integral_constant<int, kPlanes>{});
+    levels(std::integral_constant<int, kPlanes>{});
 }
 
 // Deepest level of any source, for a2a_topo_create: a workgroup searches from kSmallBatch sources as above, with its
@@ -217,6 +253,12 @@ __device__ __forceinline__ double minus_part(double x) {
   return r;
 }
 
+__device__ __forceinline__ double larger(double x, double y) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
+
 // A node that a lane works on: its place in an array of doubles (8 x id) and links.  kWide: the table has the ids
 // themselves (above 8191 nodes).
 template <int KS, bool kWide = false>
@@ -235,29 +277,24 @@ struct SmallNode {
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) m[j] = lds_at(lvl, row.template at<3>(j));
   }
-  // Sum of x over the links, in pairs, of the entries that are positive (negative: of the negative ones, made positive).
-  template <bool kNegative>
-  __device__ __forceinline__ double sum(const double* x) const {
-    double y[2 * KS];
-    gather(x, y);
-    __builtin_amdgcn_sched_barrier(0);  // all requests first: the scheduler would rather save registers
+  // Sum of what was gathered, of the entries that are positive (negative: of the negative ones, made positive), in pairs
+  // (three additions one after the other for eight links, not seven) or in link order.
+  template <bool kNegative, bool kPairs>
+  static __device__ __forceinline__ double sum(double (&y)[2 * KS]) {
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) y[j] = kNegative ? minus_part(y[j]) : plus_part(y[j]);
-    const double a = sum_pairs(y);
+    if (kPairs) return kNegative ? -sum_pairs(y) : sum_pairs(y);
+    double a = y[0];
+#pragma unroll
+    for (int j = 1; j < 2 * KS; ++j) a += y[j];
     return kNegative ? -a : a;
   }
-  // The same over the links that lead to the given level.
-  __device__ __forceinline__ double sum_level(const double* x, const unsigned char* lvl, int level) const {
-    double y[2 * KS];
-    gather(x, y);
-    int m[2 * KS];
-    levels(lvl, m);
-    __builtin_amdgcn_sched_barrier(0);
+  // The same in pairs over the links that lead to the given level.
+  static __device__ __forceinline__ double sum_level(double (&y)[2 * KS], const int (&m)[2 * KS], int level) {
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) y[j] = m[j] == level ? y[j] : 0.0;
     return sum_pairs(y);
   }
-  // (three additions one after the other for eight links, not seven)
   static __device__ __forceinline__ double sum_pairs(double (&y)[2 * KS]) {
 #pragma unroll
     for (int o = 1; o < 2 * KS; o *= 2)
@@ -273,17 +310,19 @@ struct SmallNode {
 // to level l + 1 or before, so at the other ends there are only: nodes of the level before; nodes of the same
 // level, written or not; and nodes not written yet, whose x is 0.  Even levels are kept with a plus sign and odd ones
 // with a minus sign, and a level adds up the entries of the other sign only (kSigns; x must not be negative).
-// Without kSigns the levels are looked up, and x may hold anything at first.
+// Without kSigns the levels are looked up, and x may hold anything at first.  kPairs: the links of a node are added up in
+// pairs; path counts that are a result themselves keep the order of the links, which shows above 2^53.
 // What a level costs is its chain of LDS accesses (64 cycles each) and branches, so there is one branch that is
-// taken for two levels, and while a level is worked on, the next one's links, the nodes of the one after that and the
-// places of the third are on their way.  (Loads of a 16x16x16 torus, 282 us, took 296 with one trip to the queue more in
+// taken for two levels, and once a level's gathers are on their way, so are the next one's links, the nodes of the one after
+// that and the places of the third.  (Loads of a 16x16x16 torus, 282 us, took 296 with one trip to the queue more in
 // the chain and the links added up one after the other.  Scalar cursors over pieces of levels, with no loop in a
 // level, took 318: their code is in the chain too.)
-// tl: this thread's place among those of the source, of which the first tg take part; start[l]: where level l starts
+// tl: this thread's place among those of the source, of which the first tg take part; wide: levels may have more nodes
+// than that; start[l]: where level l starts
 // in the queue, for all levels up to three past the deepest gone over; the queue has one valid entry at least.
-template <int KS, bool kSigns, bool kWide = false, typename Start, typename Look, typename F>
+template <int KS, bool kSigns, bool kPairs, bool kWide, typename Start, typename Look, typename F>
 __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, const unsigned short* q, const Start& start,
-                                            const unsigned char* lvl, double* x, int tl, int tg, int first, int last,
+                                            const unsigned char* lvl, double* x, int tl, int tg, bool wide, int first, int last,
                                             int step, Look&& look, F&& f) {
   int l = first, left = (last - first) * step;  // levels after this one
   if (tl - lane_id() >= tg) {  // waves that would rarely find a node
@@ -292,6 +331,7 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
     } while (--left >= 0);
     return;
   }
+  using Node = SmallNode<KS, kWide>;
   const int most = max(first, last) + 2;
   struct Places {
     int p, end;
@@ -302,29 +342,50 @@ __device__ __forceinline__ void small_sweep(const uint32_t* __restrict__ table, 
   };
   const auto node = [&](const Places& a) { return (uint32_t)q[min(a.p, max(a.end - 1, 0))] << (kWide ? 3 : 0); };
   Places a = places(l), b = places(l + step), c = places(l + 2 * step);
-  SmallNode<KS, kWide> n0, n1;
+  Node n0, n1;
   n0.request(table, node(a));
   uint32_t v = node(b);
-  const auto level = [&](auto odd, const SmallNode<KS, kWide>& cur, SmallNode<KS, kWide>& next) {
+  asm volatile("" : "+v"(v), "+v"(c.p), "+v"(c.end));  // arrived: not waited for in the first level, and so in all of them
+  const auto level = [&](auto odd, const Node& cur, Node& next) {
     constexpr bool kOdd = decltype(odd)::value;
-    const auto value = [&](const SmallNode<KS, kWide>& n) {
-      const double own = look(n.v8);
-      if constexpr (kSigns) {
-        const double y = f(n.v8, own, n.template sum<!kOdd>(x));
-        return kOdd ? -y : y;
-      } else {
-        return f(n.v8, own, n.sum_level(x, lvl, l - step));
-      }
+    struct Ends {
+      double own, y[2 * KS];
+      int m[2 * KS];
     };
+    const auto gather = [&](const Node& n, Ends& e) {
+      e.own = look(n.v8);
+      n.gather(x, e.y);
+      if (!kSigns) n.levels(lvl, e.m);
+    };
+    const auto finish = [&](const Node& n, Ends& e) {
+      double r;
+      if constexpr (kSigns) {
+        r = f(n.v8, e.own, Node::template sum<!kOdd, kPairs>(e.y));
+        if (kOdd) r = -r;
+      } else {
+        r = f(n.v8, e.own, Node::sum_level(e.y, e.m, l - step));
+      }
+      lds_at(x, n.v8) = r;
+    };
+    const bool in = a.p < a.end;
+    Ends e;
+    if (in) gather(cur, e);
+    __builtin_amdgcn_sched_barrier(0);  // all requests first: the scheduler would rather save registers
     next.request(table, v);
     v = node(c);
     const Places d = places(l + 3 * step);
-    if (a.p < a.end) lds_at(x, cur.v8) = value(cur);
+    __builtin_amdgcn_sched_barrier(0);
+    if (in) finish(cur, e);
+    if (wide) {
 #pragma unroll 1
-    for (int p = a.p + tg; p < a.end; p += tg) {  // a level of more nodes than the source has threads
-      SmallNode<KS, kWide> more;
-      more.request(table, (uint32_t)q[p] << (kWide ? 3 : 0));
-      lds_at(x, more.v8) = value(more);
+      for (int p = a.p + tg; p < a.end; p += tg) {
+        Node n;
+        Ends other;
+        n.request(table, (uint32_t)q[p] << (kWide ? 3 : 0));
+        gather(n, other);
+        __builtin_amdgcn_sched_barrier(0);
+        finish(n, other);
+      }
     }
     __syncthreads();
     l += step;
@@ -368,11 +429,14 @@ struct SmallLds {
   __device__ __forceinline__ unsigned short* q() const { return q_all + sg * nq; }
   __device__ __forceinline__ int* start() const { return start_all + sg * slots; }
   __device__ __forceinline__ unsigned char* lvl() const { return lvl_all + sg * nl; }
+  // Most nodes of a level of the source.
+  __device__ __forceinline__ int widest() const {
+    int most = 0;
+    for (int l = lane_id(); l < slots - 1; l += kWave) most = max(most, start()[l + 1] - start()[l]);
+    return wave_max_int(most, 0);
+  }
   // Threads of the source that work on the levels: enough for the widest one at a time, if the source has them.
-  __device__ __forceinline__ int busy(const SmallView& sv) const {
-    int widest = 0;
-    for (int l = lane_id(); l < slots - 1; l += kWave) widest = max(widest, start()[l + 1] - start()[l]);
-    widest = wave_max_int(widest, 0);
+  __device__ __forceinline__ int busy(const SmallView& sv, int widest) const {
     return min(sv.tg, max(sv.ts, (widest + kWave - 1) / kWave * kWave));
   }
 };
@@ -522,13 +586,12 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
   unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
 
   long long dsum = 0, reached = 0;
-  bool inexact = false;
-  double wd = 0.0;
+  double largest = 0.0, wd = 0.0;
 
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
   const bool at_once = sv.per_wg <= per;
-  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level,
+  small_levels<KS, kNodes>(sv, sv.src_begin + s_first, s_last - s_first, level,
                            at_once ? lds.lvl_all : nullptr);
   __syncthreads();
   double acc[kNodes][2 * KS];
@@ -550,15 +613,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
     };
     const int depth = small_sort<false>(sv, lds, at_once ? nullptr : level + (size_t)(s0 - s_first) * nl, s_last - s0,
                                         init, dsum, reached);
-    const int busy = lds.busy(sv);
+    const int widest = lds.widest(), busy = lds.busy(sv, widest);
+    const bool wide = widest > busy;
     const auto nothing = [](uint32_t) { return 0.0; };
     const auto own_sigma_at = [&](uint32_t v8) { return lds_at(sig, v8); };
     if (depth > 0) {
-      small_sweep<KS, true>(sv.in, q, start, lvl, sig, tl, busy, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
-        inexact |= a >= kTwo53;
+      small_sweep<KS, true, true, false>(sv.in, q, start, lvl, sig, tl, busy, wide, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
+        largest = larger(largest, a);
         return a;
       });
-      small_sweep<KS, !kDemand>(sv.out, q, start, lvl, coef, tl, busy, depth, 1, -1, own_sigma_at, [&](uint32_t v8, double s, double a) {
+      small_sweep<KS, !kDemand, true, false>(sv.out, q, start, lvl, coef, tl, busy, wide, depth, 1, -1, own_sigma_at,
+                                [&](uint32_t v8, double s, double a) {
         const double r = recip(__builtin_fabs(s));
         return (kDemand ? lds_at(coef, v8) * r : r) + a;
       });
@@ -602,7 +667,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
       for (int j = 0; j < KS; ++j) out[j] = make_double2(acc[k][2 * j], acc[k][2 * j + 1]);
     }
   }
-  small_totals(sv, dsum, reached, inexact, wd, kDemand);
+  small_totals(sv, s_small, dsum, reached, largest >= kTwo53, wd, kDemand);
 }
 
 // Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and
@@ -622,22 +687,23 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
   const unsigned char* const lvl = lds.lvl();
   unsigned char* const level = sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * (size_t)nl;
   long long dsum = 0, reached = 0;
-  bool inexact = false;
+  double largest = 0.0;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
   const bool at_once = sv.per_wg <= sv.per;
-  small_levels<KS, kNodes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, s_last - s_first, level,
+  small_levels<KS, kNodes>(sv, sv.src_begin + s_first, s_last - s_first, level,
                            at_once ? lds.lvl_all : nullptr);
   __syncthreads();
   for (int s0 = s_first; s0 < s_last; s0 += sv.per) {
     long long own = 0;
     const int depth = small_sort<false>(sv, lds, at_once ? nullptr : level + (size_t)(s0 - s_first) * nl, s_last - s0,
                                         [&](int v, int l) { sig[v] = l == 0 ? 1.0 : 0.0; }, own, reached);
-    const int busy = lds.busy(sv);
+    const int widest = lds.widest(), busy = lds.busy(sv, widest);
+    const bool wide = widest > busy;
     const auto nothing = [](uint32_t) { return 0.0; };
     if (depth > 0)
-      small_sweep<KS, true>(sv.in, lds.q(), lds.start(), lvl, sig, tl, busy, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
-        inexact |= a >= kTwo53;
+      small_sweep<KS, true, false, false>(sv.in, lds.q(), lds.start(), lvl, sig, tl, busy, wide, 1, depth, 1, nothing, [&](uint32_t, double, double a) {
+        largest = larger(largest, a);
         return a;
       });
     const int s = s0 + lds.sg;
@@ -658,33 +724,34 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sigma(SmallView sv, Sma
     dsum += own;
     __syncthreads();
   }
-  small_totals(sv, dsum, reached, inexact, 0.0, false);
+  small_totals(sv, s_small, dsum, reached, largest >= kTwo53, 0.0, false);
 }
 
 // Distances alone come straight from the planes of the search.
 template <int KS, int kNodes>
 __global__ void __launch_bounds__(kSmallThreads) k_small_dist(SmallView sv, SmallOut out) {
   extern __shared__ double s_small[];
-  __shared__ int s_sum[kSmallBatch];
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N, lane = lane_id();
+  double* const s_totals = s_small + (small_search_bytes(N, kNodes) + 7) / 8;
+  int* const s_sum = reinterpret_cast<int*>(s_totals + kSmallTotals);
   if (t < kSmallBatch) s_sum[t] = 0;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int count = min(sv.src_count - s_first, sv.per_wg);
-  SmallPlanes<kNodes> planes;
-  small_search<KS, kNodes, kSmallPlanes>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first, count, planes);
   long long reached = 0;
+  const auto rows = [&](auto used) {
+    SmallPlanes<kNodes, decltype(used)::value> planes;
+    small_search<KS, kNodes, decltype(used)::value>(sv, sv.src_begin + s_first, count, planes);
 #pragma unroll
-  for (int k = 0; k < kNodes; ++k)
-    if (t + T * k < N) reached += __popc(planes.seen[k]);
-  if (t == 0) reached -= count;  // the sources themselves
-  const auto write = [&](auto used) {
+    for (int k = 0; k < kNodes; ++k)
+      if (t + T * k < N) reached += __popc(planes.seen[k]);
+    if (t == 0) reached -= count;  // the sources themselves
 #pragma unroll 1
     for (int j = 0; j < count; ++j) {
       int sum = 0;
 #pragma unroll
       for (int k = 0; k < kNodes; ++k) {
         const int v = t + T * k;
-        const int d = (int)planes.template distance<decltype(used)::value>(k, j);
+        const int d = (int)planes.distance(k, j);
         if (v < N) {
           sum += d;
           if (out.dist != nullptr)
@@ -698,16 +765,16 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_dist(SmallView sv, Smal
     }
   };
   if (sv.depth < 8)
-    write(std::integral_constant<int, 3>{});
-  else if (sv.depth < 32)
-    write(std::integral_constant<int, 5>{});
+    rows(std::integral_constant<int, 3>{});
+  else if (sv.depth < 1 << kSmallFewPlanes)
+    rows(std::integral_constant<int, kSmallFewPlanes>{});
   else
-    write(std::integral_constant<int, kSmallPlanes>{});
+    rows(std::integral_constant<int, kSmallPlanes>{});
   if (out.sums != nullptr) {
     __syncthreads();
     if (t < count) out.sums[s_first + t] = s_sum[t];
   }
-  small_totals(sv, 0, reached, false, 0.0, false);
+  small_totals(sv, s_totals, 0, reached, false, 0.0, false);
 }
 
 // load[a] = (first ? 0 : load[a]) + chunk sums of the launch's partial rows, kSmallChunk rows to a chunk, in
@@ -819,7 +886,7 @@ template <int KS, int kNodes, int kPlanes, bool kWide>
 __global__ void __launch_bounds__(kSmallThreads) k_small_levels(SmallView sv) {
   extern __shared__ double s_small[];
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
-  small_levels<KS, kNodes, kPlanes, kWide>(sv, reinterpret_cast<uint32_t*>(s_small), sv.src_begin + s_first,
+  small_levels<KS, kNodes, kPlanes, kWide>(sv, sv.src_begin + s_first,
                                            min(sv.src_count - s_first, sv.per_wg),
                                            sv.level + (size_t)blockIdx.x * (size_t)sv.per_wg * small_level_bytes(sv.N));
 }

@@ -568,7 +568,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
   double* const x = s_small;
   unsigned short* const q = reinterpret_cast<unsigned short*>(s_small + N);
   long long reached = 0;
-  bool inexact = false;
+  double largest = 0.0;
   for (int s = (int)blockIdx.x; s < ws.src_count; s += (int)gridDim.x) {
     const unsigned char* const level = ws.level + (size_t)s * (size_t)nl;
     uint32_t lv[4];
@@ -590,11 +590,11 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
     const int after = __shfl_down(start.at, 1, kWave);
     const uint64_t filled = __ballot(lane >= 1 && lane < kWave - 1 && after > start.at);
     const int widest = wave_max_int(lane < kWave - 1 ? after - start.at : 0, 0);
-    const int busy = min(kWideThreads, (widest + kWave - 1) / kWave * kWave);  // threads: the widest level in one go if they suffice
+    const int busy = min(kWideThreads, (widest + kWave - 1) / kWave * kWave);
     if (filled != 0)
-      small_sweep<KS, true, true>(ws.in, q, start, nullptr, x, t, busy, 1, 63 - __builtin_clzll(filled), 1,
-                                  [](uint32_t) { return 0.0; }, [&](uint32_t, double, double a) {
-        inexact |= a >= kTwo53;
+      small_sweep<KS, true, false, true>(ws.in, q, start, nullptr, x, t, busy, widest > busy, 1,
+                                  63 - __builtin_clzll(filled), 1, [](uint32_t) { return 0.0; }, [&](uint32_t, double, double a) {
+        largest = larger(largest, a);
         return a;
       });
     const size_t row = (size_t)s * (size_t)N;
@@ -624,7 +624,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_sigma(WideSigma ws) {
   }
   SmallView sv{};
   sv.counters = ws.counters;
-  small_totals(sv, s_small, 0, reached, inexact, 0.0, false);
+  small_totals(sv, s_small, 0, reached, largest >= kTwo53, 0.0, false);
 }
 
 }  // namespace a2a_dev

@@ -13,14 +13,18 @@ namespace {
 
 template <int KS, bool kDemand>
 void small_loads(const SmallPlan& p, int workgroups, hipStream_t st) {
+  const auto launch = [&](auto nodes) {
+    constexpr int kNodes = decltype(nodes)::value;
+    k_small_loads<KS, kNodes, kDemand><<<workgroups, p.T, std::max(p.lds, small_search_bytes(p.sv.N, kNodes)), st>>>(p.sv);
+  };
   if (p.nodes <= 1)
-    k_small_loads<KS, 1, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+    launch(std::integral_constant<int, 1>{});
   else if (p.nodes <= 2)
-    k_small_loads<KS, 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+    launch(std::integral_constant<int, 2>{});
   else if (KS <= 5 && p.nodes <= 4)
-    k_small_loads<KS, KS <= 5 ? 4 : 2, kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+    launch(std::integral_constant<int, KS <= 5 ? 4 : 2>{});
   else
-    k_small_loads<KS, small_max_nodes(KS), kDemand><<<workgroups, p.T, p.lds, st>>>(p.sv);
+    launch(std::integral_constant<int, small_max_nodes(KS)>{});
 }
 
 template <int W, int KS, int kOut>
@@ -42,33 +46,35 @@ void launch_small_loads(const SmallPlan& p, bool demand, int workgroups, hipStre
 
 template <int KS>
 void launch_small_outputs(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st) {
-  const auto launch = [&](auto sigma, auto dist) {
+  const auto launch = [&](auto nodes) {
+    constexpr int kNodes = decltype(nodes)::value;
     if (out.sigma != nullptr)
-      sigma<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+      k_small_sigma<KS, kNodes><<<workgroups, p.T, std::max(p.lds, small_search_bytes(p.sv.N, kNodes)), st>>>(p.sv, out);
     else
-      dist<<<workgroups, p.T, p.lds, st>>>(p.sv, out);
+      k_small_dist<KS, kNodes><<<workgroups, p.T, small_dist_bytes(p.sv.N, kNodes), st>>>(p.sv, out);
   };
   if (p.nodes <= 1)
-    launch(k_small_sigma<KS, 1>, k_small_dist<KS, 1>);
+    launch(std::integral_constant<int, 1>{});
   else if (p.nodes <= 2)
-    launch(k_small_sigma<KS, 2>, k_small_dist<KS, 2>);
+    launch(std::integral_constant<int, 2>{});
   else if (p.nodes <= 4)
-    launch(k_small_sigma<KS, 4>, k_small_dist<KS, 4>);
+    launch(std::integral_constant<int, 4>{});
   else
-    launch(k_small_sigma<KS, 8>, k_small_dist<KS, 8>);
+    launch(std::integral_constant<int, 8>{});
 }
 
 template <int KS>
 void launch_small_levels(const SmallPlan& p, int workgroups, hipStream_t st) {
   const int nodes = (p.sv.N + kSmallThreads - 1) / kSmallThreads;
-  const size_t lds = (size_t)p.sv.N * 8;
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kSmallThreads, lds, st>>>(p.sv); };
+  const auto launch = [&](auto kernel, int most) {
+    kernel<<<workgroups, kSmallThreads, small_search_bytes(p.sv.N, most), st>>>(p.sv);
+  };
   if (p.sv.N > kScaledNodes)
-    launch(k_small_levels<KS, 16, 4, true>);
+    launch(k_small_levels<KS, 16, 4, true>, 16);
   else if (nodes <= 2)
-    launch(k_small_levels<KS, 2, kSmallPlanes, false>);
+    launch(k_small_levels<KS, 2, kSmallPlanes, false>, 2);
   else
-    launch(k_small_levels<KS, 8, kSmallPlanes, false>);
+    launch(k_small_levels<KS, 8, kSmallPlanes, false>, 8);
 }
 
 template <int KS>

@@ -332,6 +332,35 @@ __device__ __forceinline__ const double* demand_rows(const GroupView& gv, int g)
 }
 
 // Sum over the lanes, the same in every lane and from run to run.
+// Larger and smaller of two numbers (one instruction each: the compiler's own first quiet signalling NaNs).
+__device__ __forceinline__ double larger(double x, double y) {
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
+__device__ __forceinline__ double smaller(double x, double y) {
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
+  return r;
+}
+// Largest or smallest of a wave, neither of which minds a lane that meets itself.  All lanes have to be there.
+template <typename F>
+__device__ __forceinline__ double wave_pick_double(double x, F&& pick) {
+  const auto step = [&](auto ctrl, auto rows) {
+    const uint64_t b = (uint64_t)__double_as_longlong(x);
+    const uint32_t lo = (uint32_t)wave_dpp<decltype(ctrl)::value, decltype(rows)::value>((int)(uint32_t)b, (int)(uint32_t)b);
+    const uint32_t hi = (uint32_t)wave_dpp<decltype(ctrl)::value, decltype(rows)::value>((int)(b >> 32), (int)(b >> 32));
+    x = pick(x, __longlong_as_double((long long)((uint64_t)hi << 32 | lo)));
+  };
+  using All = std::integral_constant<int, 0xf>;
+  step(std::integral_constant<int, 0x111>{}, All{});
+  step(std::integral_constant<int, 0x112>{}, All{});
+  step(std::integral_constant<int, 0x114>{}, All{});
+  step(std::integral_constant<int, 0x118>{}, All{});
+  step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});
+  step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});
+  return __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), kWave - 1));
+}
 __device__ __forceinline__ double wave_sum_double(double x) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, kWave);
@@ -2023,10 +2052,10 @@ static __global__ void k_finish(const long long* __restrict__ misc, long long pa
 }
 
 // Largest value (lowest index on ties), smallest value, and with kCap the total and largest node capacity: what the
-// two kernels below reduce, over the lanes of a workgroup and then over the workgroups.
+// two kernels below reduce, over the lanes of a wave, the waves of a workgroup and the workgroups.
 struct Extrema {
   double mx, mn, sum, cap;
-  long long arg;
+  int arg;  // -1: none
   int bad;
   __device__ __forceinline__ void clear() {
     mx = -1.0;
@@ -2035,73 +2064,84 @@ struct Extrema {
     arg = -1;
     bad = 0;
   }
-  __device__ __forceinline__ void take(double x, long long a) {
+  __device__ __forceinline__ void take(double x, int a) {
     if (x > mx) {
       mx = x;
       arg = a;
     }
     if (x < mn) mn = x;
   }
-  __device__ __forceinline__ void merge(const Extrema& o) {
-    if (o.arg >= 0 && (arg < 0 || o.mx > mx || (o.mx == mx && o.arg < arg))) {
-      mx = o.mx;
-      arg = o.arg;
+  // What the lanes of the wave have, in all of them.
+  template <bool kCap>
+  __device__ __forceinline__ void over_wave() {
+    const double most = wave_pick_double(mx, larger);
+    // as unsigned numbers none is the largest
+    arg = (int)~(uint32_t)(wave_max_int((int)(~(uint32_t)(mx == most ? arg : -1) ^ 0x80000000u), (int)0x80000000u) ^ 0x80000000u);
+    mx = most;
+    mn = wave_pick_double(mn, smaller);
+    if (kCap) {
+      sum = wave_sum_double(sum);
+      cap = wave_pick_double(cap, larger);
+      bad = __ballot(bad != 0) != 0 ? 1 : 0;
     }
-    if (o.mn < mn) mn = o.mn;
-    sum += o.sum;
-    if (o.cap > cap) cap = o.cap;
-    bad |= o.bad;
   }
 };
-constexpr int kExtremaGroups = 64;  // most workgroups
+constexpr int kExtremaGroups = 64;  // most workgroups: a lane each in the end
 constexpr int kExtremaWords = 8;    // of scratch per workgroup
+constexpr int kExtremaThreads = 1024;
+// Workgroups for `items` items of a thread each, `alone` of which one workgroup does by itself.  What one finds it writes
+// at once; several have to leave it in memory and wait for each other, 3 us.
+__host__ __device__ inline int extrema_groups(long long items, long long alone, int each) {
+  if (items <= alone) return 1;
+  const long long groups = (items + each - 1) / each;
+  return (int)(groups < kExtremaGroups ? groups : kExtremaGroups);
+}
 
 // Every workgroup leaves what it found in its part of `scratch`; the one that comes last (`arrived`, 0 before and
-// after) merges them in workgroup order and writes out[0..5] = largest, its index, smallest, total capacity, largest
+// after) merges them and writes out[0..5] = largest, its index, smallest, total capacity, largest
 // node capacity, 1 if a capacity is bad, and then out[kExtremaDone] = 1.  out is host memory: the caller sees them there.
+// One barrier: the waves reduce by themselves and the first one does the rest (a tree in LDS with a barrier for each of its
+// levels made this 8.7 us for 10240 links, now 5.0; 65528 links with capacities 12.2, now 9.3).
 constexpr int kExtremaDone = 6;
 template <bool kCap>
 __device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
                                                long long* __restrict__ out) {
-  __shared__ Extrema s_e[kBlock];
-  __shared__ bool s_last;
-  const int t = (int)threadIdx.x;
-  s_e[t] = e;
+  __shared__ Extrema s_e[kExtremaThreads / kWave];
+  const int t = (int)threadIdx.x, lane = lane_id();
+  e.over_wave<kCap>();
+  if (lane == 0) s_e[t / kWave] = e;
   __syncthreads();
-  for (int o = kBlock / 2; o > 0; o >>= 1) {
-    if (t < o) s_e[t].merge(s_e[t + o]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    e = s_e[0];
-    const long long w[6] = {__double_as_longlong(e.mx), e.arg, __double_as_longlong(e.mn), __double_as_longlong(e.sum),
-                            __double_as_longlong(e.cap), e.bad};
-    for (int k = 0; k < (kCap ? 6 : 3); ++k)
-      __hip_atomic_store(&scratch[blockIdx.x * kExtremaWords + k], w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1;
-  }
-  __syncthreads();
-  if (!s_last) return;
+  if (t >= kWave) return;
   e.clear();
-  if (t < (int)gridDim.x) {
-    long long w[6] = {0, 0, 0, 0, 0, 0};
-    for (int k = 0; k < (kCap ? 6 : 3); ++k)
-      w[k] = __hip_atomic_load(&scratch[t * kExtremaWords + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    e.mx = __longlong_as_double(w[0]);
-    e.arg = w[1];
-    e.mn = __longlong_as_double(w[2]);
-    e.sum = __longlong_as_double(w[3]);
-    e.cap = __longlong_as_double(w[4]);
-    e.bad = (int)w[5];
+  if (lane < (int)blockDim.x / kWave) e = s_e[lane];
+  e.over_wave<kCap>();
+  if (gridDim.x > 1) {
+    unsigned before = 0;
+    if (lane == 0) {
+      const long long w[6] = {__double_as_longlong(e.mx), e.arg, __double_as_longlong(e.mn), __double_as_longlong(e.sum),
+                              __double_as_longlong(e.cap), e.bad};
+      for (int k = 0; k < (kCap ? 6 : 3); ++k)
+        __hip_atomic_store(&scratch[blockIdx.x * kExtremaWords + k], w[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (__builtin_amdgcn_readfirstlane((int)before) != (int)gridDim.x - 1) return;
+    e.clear();
+    if (lane < (int)gridDim.x) {
+      long long w[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll
+      for (int k = 0; k < (kCap ? 6 : 3); ++k)
+        w[k] = __hip_atomic_load(&scratch[lane * kExtremaWords + k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      e.mx = __longlong_as_double(w[0]);
+      e.arg = (int)w[1];
+      e.mn = __longlong_as_double(w[2]);
+      e.sum = __longlong_as_double(w[3]);
+      e.cap = __longlong_as_double(w[4]);
+      e.bad = (int)w[5];
+    }
+    e.over_wave<kCap>();
+    if (lane == 0) *arrived = 0;
   }
-  if (t < kExtremaGroups) s_e[t] = e;
-  __syncthreads();
-  for (int o = kExtremaGroups / 2; o > 0; o >>= 1) {
-    if (t < o) s_e[t].merge(s_e[t + o]);
-    __syncthreads();
-  }
-  if (t == 0) {
-    e = s_e[0];
+  if (lane == 0) {
     out[0] = __double_as_longlong(e.mx);
     out[1] = e.arg;
     out[2] = __double_as_longlong(e.mn);
@@ -2110,52 +2150,50 @@ __device__ __forceinline__ void reduce_extrema(Extrema e, long long* __restrict_
       out[4] = __double_as_longlong(e.cap);
       out[5] = e.bad;
     }
-    *arrived = 0;
     __hip_atomic_store(&out[kExtremaDone], 1ll, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
-// max (lowest link id on ties) and min of load[0..E).  A single workgroup spent 40 us on 100 000 links (a chain of
-// dependent trips to memory); up to 64 of them take 5.
-static __global__ void __launch_bounds__(kBlock)
-k_load_extrema(const double* __restrict__ load, long long E, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
+// max (lowest link id on ties) and min of load[0..E).
+static __global__ void __launch_bounds__(kExtremaThreads)
+k_load_extrema(const double* __restrict__ load, int E, long long* __restrict__ scratch, unsigned* __restrict__ arrived,
                long long* __restrict__ out) {
+  constexpr int kAhead = 8;  // requests in flight
   Extrema e;
   e.clear();
-  const long long stride = (long long)gridDim.x * kBlock;
-  long long a = (long long)blockIdx.x * kBlock + threadIdx.x;
-  for (; a + 3 * stride < E; a += 4 * stride) {  // four requests in flight
-    double x[4];
+  const long long stride = (long long)gridDim.x * blockDim.x;
+  for (long long a = (long long)blockIdx.x * blockDim.x + threadIdx.x; a < E; a += kAhead * stride) {
+    double x[kAhead];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) x[k] = load[a + k * stride];
+    for (int k = 0; k < kAhead; ++k) x[k] = load[min(a + k * stride, (long long)E - 1)];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) e.take(x[k], a + k * stride);
+    for (int k = 0; k < kAhead; ++k) e.take(x[k], (int)min(a + k * stride, (long long)E - 1));
   }
-  for (; a < E; a += stride) e.take(load[a], a);
   reduce_extrema<false>(e, scratch, arrived, out);
 }
 
 // The same with link capacities (Sec. 3.1.1): utilisation load[a] / cap[a] instead of load[a]; also the total
 // capacity (a fixed order: per thread in link order, then a fixed tree) and the largest total out-capacity of a
 // node.  A capacity is bad if it is not a positive finite number.  A thread takes whole nodes.
-static __global__ void __launch_bounds__(kBlock)
+static __global__ void __launch_bounds__(kExtremaThreads)
 k_util_extrema(const int32_t* __restrict__ out_ptr, const double* __restrict__ load, const double* __restrict__ cap, int N,
                long long* __restrict__ scratch, unsigned* __restrict__ arrived, long long* __restrict__ out) {
+  constexpr int kAhead = 8;  // links whose load and capacity are asked for together
   Extrema e;
   e.clear();
-  for (int u = (int)(blockIdx.x * kBlock + threadIdx.x); u < N; u += (int)gridDim.x * kBlock) {
+  for (int u = (int)(blockIdx.x * blockDim.x + threadIdx.x); u < N; u += (int)(gridDim.x * blockDim.x)) {
     double node_cap = 0.0;
     const int p1 = out_ptr[u + 1];
-    for (int p = out_ptr[u]; p < p1; p += 4) {
-      double c[4], x[4];
+    for (int p = out_ptr[u]; p < p1; p += kAhead) {
+      double c[kAhead], x[kAhead];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < kAhead; ++k) {
         const int a = min(p + k, p1 - 1);
         c[k] = cap[a];
         x[k] = load[a];
       }
 #pragma unroll
-      for (int k = 0; k < 4; ++k) {
+      for (int k = 0; k < kAhead; ++k) {
         if (p + k >= p1) break;
         if (!(c[k] > 0.0) || c[k] > 1.7976931348623157e308) e.bad = 1;
         e.take(x[k] / c[k], p + k);

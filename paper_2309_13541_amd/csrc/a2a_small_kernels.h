@@ -253,12 +253,6 @@ __device__ __forceinline__ double minus_part(double x) {
   return r;
 }
 
-__device__ __forceinline__ double larger(double x, double y) {
-  double r;
-  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(x), "v"(y));
-  return r;
-}
-
 // A node that a lane works on: its place in an array of doubles (8 x id) and links.  kWide: the table has the ids
 // themselves (above 8191 nodes).
 template <int KS, bool kWide = false>

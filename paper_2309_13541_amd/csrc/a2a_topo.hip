@@ -1141,11 +1141,6 @@ int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t 
   return A2A_OK;
 }
 
-// Workgroups of an extrema kernel that has `items` items of work for its threads.
-unsigned extrema_groups(int64_t items) {
-  return (unsigned)std::max<int64_t>(1, std::min<int64_t>(kExtremaGroups, (items + kBlock - 1) / kBlock));
-}
-
 int check_common(const a2a_topo* t, int32_t src_begin, int32_t src_count, void* ws) {
   if (!t || src_begin < 0 || src_count < 0 || (int64_t)src_begin + src_count > t->N) return A2A_ERR_INVALID_ARG;
   if (src_count > 0 && (!ws || ((uintptr_t)ws & 255u))) return A2A_ERR_INVALID_ARG;
@@ -1565,8 +1560,8 @@ int a2a_schedule_bound(const a2a_topo* t, const double* load, int64_t sum_dist, 
   const Use use(t, st);
   const uint64_t covered = use.covered();
   h_res[kExtremaDone] = 0;
-  k_load_extrema<<<extrema_groups((t->E + 3) / 4), kBlock, 0, st>>>(
-      load, (long long)t->E, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
+  k_load_extrema<<<extrema_groups(t->E, 32 * kExtremaThreads, 4 * kExtremaThreads), kExtremaThreads, 0, st>>>(
+      load, (int)t->E, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
       (long long*)h_res);
   HIP_TRY(hipGetLastError());
   HIP_TRY(wait_for(st, [&] { return seen(&h_res[kExtremaDone]) != 0; }));
@@ -1603,7 +1598,8 @@ int a2a_schedule_bound_cap(const a2a_topo* t, const double* load, const double* 
   const Use use(t, st);
   const uint64_t covered = use.covered();
   h_res[kExtremaDone] = 0;
-  k_util_extrema<<<extrema_groups(t->N), kBlock, 0, st>>>(
+  const int groups = extrema_groups(t->N, kExtremaThreads, kBlock);
+  k_util_extrema<<<groups, groups == 1 ? kExtremaThreads : kBlock, 0, st>>>(
       t->d_out_ptr, load, cap, t->N, t->d_scratch_slots + slot * (kExtremaGroups * kExtremaWords), t->d_arrived + slot,
       (long long*)h_res);
   HIP_TRY(hipGetLastError());

@@ -622,4 +622,185 @@ k_flow_weighted(const double* __restrict__ weighted, int sources, double* __rest
   *out = sum;
 }
 
+// The single-path baseline of k_small_sssp with the sort and the cursors of k_flow_sources: sources blockIdx.x, + gridDim.x, ... of
+// an iteration.  LDS has a word per node and a word per queue entry.  Forward: a node's cost, with the parity of its
+// level as its highest bit (all ones before it has one), so that a gathered word tells whether it counts.  Costs are below 2^31 - 1
+// (the host checks).  On odd levels, as unsigned numbers, the costs of the level before are smaller than all else, and on even
+// ones, as signed numbers, too; both also after an addition that saturates.
+// The node's entry in the queue takes the chosen link's place and neighbour beside the node.  Backward: the paths that end in
+// or pass through a node, below the chosen link's place, which leave as whole rows.
+// Per source of 16384 nodes of degree 4, thousands of cycles: sort 16, forward 17.5, backward and rows 14; in k_small_sssp sort 21,
+// forward 22.5, backward 25.  Iteration by 512 sources 71 us, now 49.  Bound by the vector ALUs and LDS in turns.
+constexpr int kFlowSsspNode = 14;  // bits of a node
+static_assert(kBothTables <= 1 << kFlowSsspNode && kHandedShift == 2 * kFlowSsspNode, "a queue entry: node, neighbour, place");
+template <int KS, bool kScaled>
+__global__ void __launch_bounds__(kWideThreads) k_flow_sssp(SmallView sv, SmallSssp ss) {
+  extern __shared__ double s_small[];
+  using Row = FlowRow<KS, kScaled>;
+  constexpr int kId = kScaled ? 3 : 0;  // table entries are ids << kId
+  constexpr uint32_t kNode = (1u << kFlowSsspNode) - 1, kPaths = (1u << kHandedShift) - 1;
+  const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int N = sv.N, S = flow_stride(N), nl = (int)small_level_bytes(N);
+  const int words = (N + 4 * kWideThreads - 1) / (4 * kWideThreads), v0 = 4 * words * t;  // this thread's nodes in the sort
+  uint32_t* const x = reinterpret_cast<uint32_t*>(s_small);
+  const uint32_t q_at = (uint32_t)flow_sssp_queue(N, sv.depth);
+  uint32_t* const q = reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(s_small) + q_at);
+  uint32_t* const s_totals = q + S + kFlowSpare;
+  const bool apart = flow_sssp_apart(N, sv.depth);
+  unsigned short* const base = apart ? reinterpret_cast<unsigned short*>(s_totals + 128) : reinterpret_cast<unsigned short*>(s_small);
+  long long dsum = 0, reached = 0;
+  uint32_t lv[kFlowWords];
+  const auto levels = [&](int s) {  // of a source
+    const unsigned char* const level = sv.level + (size_t)s * (size_t)nl;
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) {
+      lv[k] = ~0u;
+      if (k < words && v0 + 4 * k < N) lv[k] = *reinterpret_cast<const uint32_t*>(level + v0 + 4 * k);
+    }
+  };
+  levels((int)blockIdx.x);
+  for (int s = (int)blockIdx.x; s < sv.src_count; s += (int)gridDim.x) {
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) {  // places past the last node: out of reach
+      const int v = v0 + 4 * k;
+      if (v < N && v + 4 > N) lv[k] |= ~0u << ((N - v) * 8);
+    }
+    int v1 = v0;
+    asm volatile("" : "+v"(v1));  // not kept from source to source
+    __syncthreads();
+    const auto clear = [&] {
+      const int source = sv.src_begin + s;
+      for (int i = t; i < S / 4; i += kWideThreads) {
+        const auto none_yet = [&](int k) { return 4 * i + k == source ? 0u : ~0u; };
+        reinterpret_cast<uint4*>(x)[i] = make_uint4(none_yet(0), none_yet(1), none_yet(2), none_yet(3));
+      }
+    };
+    if (apart) clear();
+    const auto place = [&](uint32_t p, int i) { q[p] = (uint32_t)(v1 + i); };
+    const int starts = sv.depth <= 8 ? flow_sort<1>(lv, words, s_totals, base, S, wave, lane, place)
+                                     : flow_sort<2>(lv, words, s_totals, base, S, wave, lane, place);
+    const int after = __shfl_down(starts, 1, kWave);
+    const uint64_t filled = __ballot(lane >= 1 && lane <= sv.depth && after > starts);
+    const int deep = filled != 0 ? 63 - __builtin_clzll(filled) : 0;
+    const int total = __builtin_amdgcn_readlane(starts, kWave - 1);
+    if (wave == 0) {
+      reached += lane >= 1 && lane <= deep ? after - starts : 0;
+      dsum += lane >= 1 && lane <= deep ? (long long)lane * (after - starts) : 0;
+    }
+    if (!apart) {
+      __syncthreads();  // the positions of the sort have been read
+      clear();
+    }
+    if (s + (int)gridDim.x < sv.src_count) levels(s + (int)gridDim.x);  // of the next source, in time for its sort
+    __syncthreads();
+    const uint32_t q0 = q_at + 4u * (uint32_t)t, q1 = q_at + 4u * (uint32_t)max(total - 1, 0);
+    if (deep > 0) {
+      FlowPiece<1> a, b, c;
+      a.enter(1, starts);
+      b = a;
+      b.next(starts);
+      c = b;
+      c.next(starts);
+      // An entry that has been worked on has its node too.
+      const auto node = [&](const FlowPiece<1>& p) { return (lds_get<uint32_t>(min(q0 + 4u * (uint32_t)p.base, q1)) & kNode) << kId; };
+      struct Ahead {
+        uint32_t node, weight[2 * KS];
+        Row row;
+        __device__ __forceinline__ void request(const SmallView& sv, const SmallSssp& ss) {
+          row.load(sv.in, node);
+          const uint32_t* const w = ss.weight + (size_t)((node >> kId) * (uint32_t)(2 * KS));
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) weight[j] = w[j];
+        }
+      };
+      // A piece, after the links of the next one have been asked for; the node after that one takes the piece's place.
+      const auto step = [&](Ahead& here, Ahead& next) {
+        flow_arrived(here.row);
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) asm volatile("" ::"v"(here.weight[j]));
+        next.request(sv, ss);
+        const uint32_t then = node(c);
+        if (t < a.end - a.base) {
+          uint32_t from[2 * KS], y[2 * KS];
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) {
+            from[j] = here.row.template at<2>(j);
+            y[j] = lds_get<uint32_t>(from[j]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+          // The chosen link, place and neighbour, as in a queue entry.
+          uint32_t cost, link = 0;
+          const auto choose = [&](auto zero) {
+            using Cost = decltype(zero);
+            uint32_t sum[2 * KS];
+#pragma unroll
+            for (int j = 0; j < 2 * KS; ++j) sum[j] = (uint32_t)__builtin_elementwise_add_sat((Cost)y[j], (Cost)here.weight[j]);
+            Cost best = (Cost)sum[0];
+#pragma unroll
+            for (int j = 1; j < 2 * KS; ++j) best = min(best, (Cost)sum[j]);
+            cost = (uint32_t)best;
+#pragma unroll
+            for (int j = 2 * KS - 1; j >= 0; --j) {  // the lowest link of equals stays
+              const uint32_t one = from[j] << (kFlowSsspNode - 2) | (uint32_t)j << kHandedShift;
+              link = sum[j] == cost ? one : link;
+            }
+          };
+          if (a.level & 1)
+            choose(0u);
+          else
+            choose(0);
+          lds_put<uint32_t>(Row::template own<2>(here.node), cost ^ 0x80000000u);
+          lds_put<uint32_t>(q0 + 4u * (uint32_t)a.base, here.node >> kId | link);
+        }
+        if (b.level != a.level) __syncthreads();
+        here.node = then;
+        a = b;
+        b = c;
+        c.next(starts);
+      };
+      Ahead n0, n1;
+      n0.node = node(a);
+      n1.node = node(b);
+      n0.request(sv, ss);
+      for (;;) {
+        step(n0, n1);
+        if (a.level > deep) break;
+        step(n1, n0);
+        if (a.level > deep) break;
+      }
+    }
+    for (int i = t; i < S / 4; i += kWideThreads) reinterpret_cast<uint4*>(x)[i] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    for (int p = t; p < total; p += kWideThreads) {
+      const uint32_t r = q[p];
+      x[r & kNode] = 1u | (r >> kHandedShift) << kHandedShift;
+    }
+    __syncthreads();
+    if (deep > 1) {
+      FlowPiece<-1> a, b;
+      a.enter(deep, starts);
+      b = a;
+      b.next(starts);
+      const auto entry = [&](const FlowPiece<-1>& p) { return lds_get<uint32_t>(min(q0 + 4u * (uint32_t)max(p.base, 0), q1)); };
+      uint32_t r = entry(a);
+      for (;;) {
+        const uint32_t next = entry(b);
+        if (t < a.end - a.base) {
+          const uint32_t paths = x[r & kNode] & kPaths;
+          __hip_atomic_fetch_add(&x[r >> kFlowSsspNode & kNode], paths, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+        if (b.level != a.level) __syncthreads();
+        r = next;
+        a = b;
+        b.next(starts);
+        if (a.level < 2) break;
+      }
+    }
+    uint32_t* const handed = ss.handed + (size_t)s * (size_t)N;
+    for (int v = t; v < N; v += kWideThreads) handed[v] = x[v];
+  }
+  __syncthreads();
+  small_totals(sv, s_small, dsum, reached, false, 0.0, false);
+}
+
 }  // namespace a2a_dev

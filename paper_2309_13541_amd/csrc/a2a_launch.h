@@ -26,6 +26,8 @@ void launch_small_levels(const SmallPlan& p, int workgroups, hipStream_t st);
 template <int KS>
 void launch_small_sssp(const SmallPlan& p, const SmallSssp& ss, hipStream_t st);
 template <int KS>
+void launch_flow_sssp(const SmallPlan& p, const SmallSssp& ss, int workgroups, hipStream_t st);
+template <int KS>
 void launch_small_sssp_add(const SmallPlan& p, const SmallSssp& ss, hipStream_t st);
 // W sources a word; out: kWideDist (16, 32 or 64) or kWideBytes (16 or 64).
 template <int KS>

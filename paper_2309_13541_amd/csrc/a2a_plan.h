@@ -223,6 +223,29 @@ constexpr bool flow_lds_fits(int N, int depth, bool demand) {
 constexpr int kFlowNodes = 20352;
 static_assert(flow_lds_fits(kFlowNodes, kFlowDeepest, false) && !flow_lds_fits(kFlowNodes + 1, 1, false));
 
+// LDS of k_flow_sssp: a word per node, a word per queue entry, sums, and the positions of the sort; those lie in the place of the
+// first where there is no room for both.
+constexpr size_t flow_sssp_places(int depth) { return (size_t)(depth <= 8 ? 9 : 17) * 2 * kSmallThreads; }
+constexpr size_t flow_sssp_tail(int N) { return ((size_t)flow_stride(N) + 32) * 4 + 512; }  // from the queue on, without positions
+constexpr bool flow_sssp_apart(int N, int depth) {
+  return (size_t)flow_stride(N) * 4 + flow_sssp_tail(N) + flow_sssp_places(depth) <= kSmallLds;
+}
+constexpr size_t flow_sssp_queue(int N, int depth) {
+  const size_t state = (size_t)flow_stride(N) * 4, places = flow_sssp_apart(N, depth) ? 0 : flow_sssp_places(depth);
+  return state > places ? state : places;
+}
+constexpr size_t flow_sssp_lds(int N, int depth) {
+  return flow_sssp_queue(N, depth) + flow_sssp_tail(N) + (flow_sssp_apart(N, depth) ? flow_sssp_places(depth) : 0);
+}
+// Which calls take it.  Below, k_small_sssp has more than two sources in a workgroup's LDS (us there and here: 4200 nodes of degree 6
+// 580, 497; 5000 of degree 4 459, 435; 8191 of degree 4 1168, 1000).  Costs have 31 bits, the largest number of which
+// stands for "none".
+constexpr int kFlowSsspDeepest = 15;
+constexpr bool flow_sssp_fits(int N, int depth, int src_count) {
+  return N > 4096 && N <= kBothTables && depth <= kFlowSsspDeepest &&
+         (long long)depth * src_count * (N - 1) < 0x7fffffffll && flow_sssp_lds(N, depth) <= kSmallLds;
+}
+
 // How the sources of a call are grouped: depends on the topology and their number only.  A workgroup of k_flow_links keeps the
 // loads of a block of links over a group, and the groups are added up in order; about one workgroup per compute unit.
 struct FlowGroups {

@@ -793,7 +793,17 @@ k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_
     if (t >= kWave) return;
     long long bad = 0, dsum = 0, reached = 0;
     double wd = first ? 0.0 : __longlong_as_double(misc[3]);
-    for (int r0 = 0; r0 < rows; r0 += kWave) {
+    if (tot.weighted == nullptr) {  // sums of integers, and their largest: in any order
+#pragma unroll 8
+      for (int r = t; r < rows; r += kWave) {
+        const longlong2* const c = reinterpret_cast<const longlong2*>(sv.counters + (size_t)r * kSmallCounters);
+        const longlong2 sums = c[0];
+        dsum += sums.x;
+        reached += sums.y;
+        bad |= c[1].x;
+      }
+    }
+    for (int r0 = 0; tot.weighted != nullptr && r0 < rows; r0 += kWave) {
       const int r = r0 + t;
       double x = 0.0;
       if (r < rows) {
@@ -801,11 +811,10 @@ k_small_reduce(SmallView sv, int KS, int rows, int first, int last, const int32_
         dsum += c[0];
         reached += c[1];
         bad |= c[2];
-        if (tot.weighted != nullptr) x = __longlong_as_double(c[3]);
+        x = __longlong_as_double(c[3]);
       }
-      if (tot.weighted != nullptr)  // one after the other, in row order
-        for (int k = 0; k < min(kWave, rows - r0); ++k)
-          wd += __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), k));
+      for (int k = 0; k < min(kWave, rows - r0); ++k)  // one after the other, in row order
+        wd += __longlong_as_double((long long)readlane64((uint64_t)__double_as_longlong(x), k));
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {

@@ -1089,6 +1089,7 @@ int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t 
   const int places = 2 * t->ell_words;
   const int iterations = (src_count + per_iter - 1) / per_iter;
   const SmallPlan whole = small_plan(t, std::min(per_iter, src_count), SmallWhat::kSssp);
+  const bool flow = flow_sssp_fits(t->N, t->level_bound, src_count);
   size_t off = 256;
   const auto part = [&off](size_t bytes) {
     const size_t at = off;
@@ -1120,12 +1121,17 @@ int small_sssp(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t 
     }
     for (int i = i0; i < i1; ++i) {
       SmallPlan p = small_plan(t, std::min(per_iter, src_count - i * per_iter), SmallWhat::kSssp);
+      p.sv.src_begin = src_begin + i * per_iter;
       p.sv.level = level + (size_t)(i - i0) * per_iter * level_bytes;
       p.sv.counters = counters + (size_t)rows * kSmallCounters;
-      rows += p.workgroups;
+      const int workgroups = flow ? std::min(p.sv.src_count, kComputeUnits) : p.workgroups;
+      rows += workgroups;
       {
         ProfScope ps(t, PROF_SOURCES, st);
-        by_words(t->ell_words, [&](auto ks) { launch_small_sssp<decltype(ks)::value>(p, ss, st); });
+        by_words(t->ell_words, [&](auto ks) {
+          constexpr int KS = decltype(ks)::value;
+          flow ? launch_flow_sssp<KS>(p, ss, workgroups, st) : launch_small_sssp<KS>(p, ss, st);
+        });
       }
       ProfScope ps(t, PROF_REDUCE, st);
       by_words(t->ell_words, [&](auto ks) { launch_small_sssp_add<decltype(ks)::value>(p, ss, st); });

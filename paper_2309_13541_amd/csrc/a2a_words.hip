@@ -83,6 +83,17 @@ void launch_small_sssp(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) 
 }
 
 template <int KS>
+void launch_flow_sssp(const SmallPlan& p, const SmallSssp& ss, int workgroups, hipStream_t st) {
+  const auto launch = [&](auto kernel) {
+    kernel<<<workgroups, kWideThreads, flow_sssp_lds(p.sv.N, p.sv.depth), st>>>(p.sv, ss);
+  };
+  if (p.sv.N <= kScaledNodes)
+    launch(k_flow_sssp<KS, true>);
+  else
+    launch(k_flow_sssp<KS, false>);
+}
+
+template <int KS>
 void launch_small_sssp_add(const SmallPlan& p, const SmallSssp& ss, hipStream_t st) {
   k_small_sssp_add<KS><<<(p.sv.N + kWave - 1) / kWave, kSmallThreads, 0, st>>>(ss, p.sv.N, p.sv.src_count);
 }
@@ -140,6 +151,7 @@ template void launch_small_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStre
 template void launch_small_outputs<A2A_WORDS>(const SmallPlan&, const SmallOut&, int, hipStream_t);
 template void launch_small_levels<A2A_WORDS>(const SmallPlan&, int, hipStream_t);
 template void launch_small_sssp<A2A_WORDS>(const SmallPlan&, const SmallSssp&, hipStream_t);
+template void launch_flow_sssp<A2A_WORDS>(const SmallPlan&, const SmallSssp&, int, hipStream_t);
 template void launch_small_sssp_add<A2A_WORDS>(const SmallPlan&, const SmallSssp&, hipStream_t);
 template void launch_wide_search<A2A_WORDS>(const WideView&, int, int, int, hipStream_t);
 template void launch_wide_masks<A2A_WORDS>(const WideView&, int, int, hipStream_t);

@@ -16,7 +16,7 @@ namespace a2a_dev {
 struct FlowView {
   const uint32_t *in, *out;    // link tables, as in SmallView
   const unsigned char* level;  // [sources][small_level_bytes(N)]
-  void* record;                // [workgroups of k_flow_sources][stride] FlowRecord
+  void* record;                // [workgroups of k_flow_sources] FlowRecords
   uint32_t* count;             // [sources][stride] FlowWord
   double* coef;                // [sources][stride]; demands before (k_flow_demand)
   double* weighted;            // [sources] demand x distance
@@ -29,15 +29,12 @@ struct FlowView {
 };
 
 // A node as the forward sweep leaves it to the backward one, in the order in which levels are gone over.
+// In memory the values of a workgroup's source come first, the nodes behind them, 16 bits each.
 template <bool kDemand>
-struct alignas(8) FlowRecord {
+struct FlowRecord {
+  using Value = std::conditional_t<kDemand, double, uint32_t>;
   uint32_t node;
-  uint32_t sigma;
-};
-template <>
-struct alignas(16) FlowRecord<true> {
-  uint32_t node;
-  double share;  // demand / sigma
+  Value value;  // path count, demand / path count
 };
 
 typedef uint32_t FlowWords __attribute__((ext_vector_type(4)));
@@ -207,8 +204,9 @@ struct FlowPiece {
 // l + 1 and (some of) l are written, so even levels are kept with a plus sign and odd ones with a minus sign, and a level adds up
 // the entries of the other sign only.  Coefs of unequal demands have any sign: even and odd levels have an array each.
 // The nodes' order goes through memory from one sweep to the other, with what the backward sweep needs of a node (its coefs take
-// the place of the queue); that is read three pieces ahead, links one piece ahead.  Rows of the outputs are written from LDS, in
-// node order.
+// the place of the queue); that is read three pieces ahead, links one piece ahead.  It is kept small so that the 32 workgroups of an
+// XCD find theirs in its L2: with 16 bytes a node, now 10, 8191 nodes of degree 8 with demands took 891 us here, now 765 (1598
+// MB read, now 1013); 20011 of degree 5, 8 bytes, now 6, 386, now 372.  Rows of the outputs are written from LDS, in node order.
 // Bound by the chain of a piece (links, gathers, sum, barrier at the end of a level), which the four waves of a SIMD hide in part: a
 // source of 16384 nodes of degree 4 takes 57 thousand cycles, sort 9.7, forward 15, backward 23, rows and zeroes 9; vector
 // ALUs and LDS are busy about half of the time each.  Pushing counts to the out-links by LDS additions where that touches fewer
@@ -230,7 +228,9 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   // behind all that, so that places in the arrays at the start need no addition
   double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_source_lds(N, fv.depth, kDemand) - kFlowTail);
   uint32_t* const s_totals = reinterpret_cast<uint32_t*>(s_weighted + kWideThreads / kWave);
-  Record* const record = static_cast<Record*>(fv.record) + (size_t)blockIdx.x * fv.stride;
+  using Value = typename Record::Value;
+  Value* const record = reinterpret_cast<Value*>(static_cast<char*>(fv.record) + (size_t)blockIdx.x * flow_record_bytes(S, kDemand));
+  unsigned short* const record_node = reinterpret_cast<unsigned short*>(record + S);
   constexpr int kId = kScaled ? 3 : 0;  // table entries are ids << kId
   long long dsum = 0, reached = 0;
   uint32_t lv[kFlowWords];
@@ -306,15 +306,16 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) sum += flow_count(y[j], before);
           lds_put<uint32_t>(Row::template own<2>(here.node), sum + above);
-          Record r;
-          r.node = here.node;
+          Value value;
           if constexpr (kDemand) {
-            r.share = own * recip((double)sum);
+            value = own * recip((double)sum);
             wd = __builtin_fma((double)a.level, own, wd);
           } else {
-            r.sigma = sum;
+            value = sum;
           }
-          lds_at(record, (uint32_t)(a.base + t) * (uint32_t)sizeof(Record)) = r;
+          const uint32_t at = (uint32_t)(a.base + t);
+          record[at] = value;
+          record_node[at] = (unsigned short)here.node;
         }
         if (b.level != a.level) __syncthreads();
         here.node = then;
@@ -359,8 +360,13 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       c.next(starts);
       d = c;
       d.next(starts);
-      const uint32_t r0 = (uint32_t)t * (uint32_t)sizeof(Record), r1 = last * (uint32_t)sizeof(Record);
-      const auto read = [&](const FlowPiece<-1>& p) { return lds_at(record, min(r0 + (uint32_t)p.base * (uint32_t)sizeof(Record), r1)); };
+      const auto read = [&](const FlowPiece<-1>& p) {
+        const uint32_t at = min((uint32_t)t + (uint32_t)p.base, last);
+        Record r;
+        r.value = record[at];
+        r.node = record_node[at];
+        return r;
+      };
       const auto step = [&](const Record& here, const Record& next, Record& third, Row& row, Row& next_row) {
         flow_arrived(row);
         next_row.load(fv.out, next.node);
@@ -370,9 +376,9 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
         if (t < a.end - a.base) {
           double sum;
           if constexpr (kDemand)
-            sum = here.share;
+            sum = here.value;
           else
-            sum = recip((double)here.sigma);
+            sum = recip((double)here.value);
           const bool odd = (a.level & 1) != 0, inner = a.level < deep;  // the last level has no successors
           const uint32_t from = kDemand && !odd ? 8u * (uint32_t)S : 0u, to = kDemand && odd ? 8u * (uint32_t)S : 0u;
           double y[2 * KS];

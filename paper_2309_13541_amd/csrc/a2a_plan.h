@@ -246,6 +246,9 @@ constexpr bool flow_sssp_fits(int N, int depth, int src_count) {
          (long long)depth * src_count * (N - 1) < 0x7fffffffll && flow_sssp_lds(N, depth) <= kSmallLds;
 }
 
+// A workgroup's records between the two sweeps: a path count, or 8 bytes with demands, and a 16-bit node per place.
+constexpr size_t flow_record_bytes(int stride, bool demand) { return (size_t)stride * (demand ? 10 : 6); }
+
 // How the sources of a call are grouped: depends on the topology and their number only.  A workgroup of k_flow_links keeps the
 // loads of a block of links over a group, and the groups are added up in order; about one workgroup per compute unit.
 struct FlowGroups {
@@ -279,7 +282,7 @@ inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool dema
   const size_t stride = (size_t)flow_stride(N);
   l.counters = take((size_t)kComputeUnits * kSmallCounters * 8);
   l.weighted = take((size_t)src_count * 8);
-  l.record = take((size_t)std::min(rows, kComputeUnits) * stride * (demand ? 16 : 8));
+  l.record = take((size_t)std::min(rows, kComputeUnits) * flow_record_bytes((int)stride, demand));
   l.part = take((size_t)parts * N * ell_words * 2 * 8);
   l.level = take((size_t)rows * small_level_bytes(N));
   l.count = take((size_t)rows * stride * 4);

@@ -206,7 +206,7 @@ struct FlowPiece {
 // The nodes' order goes through memory from one sweep to the other, with what the backward sweep needs of a node (its coefs take
 // the place of the queue); that is read three pieces ahead, links one piece ahead.  It is kept small so that the 32 workgroups of an
 // XCD find theirs in its L2: with 16 bytes a node, now 10, 8191 nodes of degree 8 with demands took 891 us here, now 765 (1598
-// MB read, now 1013); 20011 of degree 5, 8 bytes, now 6, 386, now 372.  Rows of the outputs are written from LDS, in node order.
+// MB read, now 1013); 20011 of degree 5, 8 bytes, now 6, 386, now 375.  Rows of the outputs are written from LDS, in node order.
 // Bound by the chain of a piece (links, gathers, sum, barrier at the end of a level), which the four waves of a SIMD hide in part: a
 // source of 16384 nodes of degree 4 takes 57 thousand cycles, sort 9.7, forward 15, backward 23, rows and zeroes 9; vector
 // ALUs and LDS are busy about half of the time each.  Pushing counts to the out-links by LDS additions where that touches fewer

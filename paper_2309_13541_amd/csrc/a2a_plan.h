@@ -153,9 +153,12 @@ struct SmallCut {
 };
 
 // How a call over src_count sources is cut up; depends on the topology and src_count only (so the results
-// do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow
-// while there are workgroups for every compute unit; as many rounds as it then takes to have one
-// workgroup for each place on the chip, so that the rows of partial loads stay few.
+// do not depend on the workspace).  As many sources per workgroup at a time as LDS and 1024 threads allow,
+// up to one workgroup for every compute unit; as many rounds as it then takes to have one
+// workgroup for each place on the chip, so that the rows of partial loads stay few.  (Sources that share a workgroup search
+// together; with no more sharing than leaves at least 256 workgroups, a few units had two and the rest waited: link loads of 400
+// nodes of degree 4 44.5 us, now 31.5; of 900 of degree 8 55.2, 45.7; 400 sources of 3000 nodes 124, 98; path counts of 600 nodes 15.0,
+// 13.7; where both rules agree, from some 1200 sources on, the same.)
 inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallWhat what) {
   const auto up = [](int x) { return (x + kSmallWave - 1) / kSmallWave * kSmallWave; };
   SmallCut c{};
@@ -166,7 +169,7 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
     tg = std::min(kSmallThreads, up(N));
     c.lds = (size_t)N * 8;
   } else {
-    const int want = std::max(1, std::min(kSmallThreads / kSmallWave, src_count / kComputeUnits));
+    const int want = std::max(1, std::min(kSmallThreads / kSmallWave, (src_count + kComputeUnits - 1) / kComputeUnits));
     // fewest threads of a source that shares its workgroup: 1537 nodes of degree 4 take 50.9 us for their loads with 256,
     // 57.9 with 128 and 59.4 with 512, a 40x40 torus 96, 93 and 129
     const int least = std::min(tg, 256);

@@ -79,14 +79,16 @@ struct FlowRow {
 
 // `chunks` times 16 bytes from memory to LDS, a kilobyte a wave and instruction.  They have arrived when vmcnt has come down to the
 // requests after them.  (As assembly, because the compiler would wait for all of them before any access to LDS.)
+// The compiler puts no wait states inside: a load to LDS needs one after the write of M0, and five after a vector instruction that wrote
+// its address registers (a lane read back), whatever stands before this.
 __device__ __forceinline__ void flow_to_lds(const void* from, void* to, int chunks, int wave, int lane) {
   const uint32_t place = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)to;
   for (int c = wave * kWave; c < chunks; c += kWideThreads)
     if (c + lane < chunks)
-      asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1"
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1"
                    :
                    : "v"(16u * (uint32_t)lane), "s"(static_cast<const char*>(from) + 16 * (size_t)c), "s"(place + 16u * (uint32_t)c)
-                   : "memory");
+                   : "memory", "m0");
 }
 
 // No memory request is moved from one side of this to the other.

@@ -1,0 +1,70 @@
+"""What the compiler leaves to the source, looked up in the library that was built from it (AMD machine code): no device needed."""
+import os
+import re
+import subprocess
+
+import pytest
+
+import paper_2309_13541_amd as a2a
+
+LLVM = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    at = tmp_path_factory.mktemp("code")
+    lib = at / "lib.so"
+    lib.symlink_to(a2a.library_path())
+    subprocess.run([os.path.join(LLVM, "llvm-objdump"), "--offloading", str(lib)], check=True, stdout=subprocess.DEVNULL, timeout=120)
+    objects = sorted(str(p) for p in at.iterdir() if p.name.endswith("gfx950"))
+    assert len(objects) == 6  # one per translation unit
+    return objects
+
+
+def registers(operand):
+    m = re.fullmatch(r"([vs])(\d+|\[(\d+):(\d+)\])", operand)
+    if not m:
+        return {operand} & {"m0", "vcc"}
+    first, last = (m[2], m[2]) if m[3] is None else (m[3], m[4])
+    return {m[1] + str(i) for i in range(int(first), int(last) + 1)}
+
+
+def loads_to_lds_too_early(lines):
+    """Loads to LDS, and those with too few wait states behind a scalar write of M0 (1) or a vector write of their scalar
+    registers (5).  In the order of the text: the library's loads to LDS stand in one block with what they wait for."""
+    found, early, before = 0, [], []
+    for line in lines:
+        text = line.split("//")[0].strip()
+        op, _, rest = text.partition(" ")
+        operands = [x.strip().split(" ")[0] for x in rest.split(",")]
+        if "_lds_dword" in op:
+            found += 1
+            scalars = {r for x in operands for r in registers(x) if r[0] == "s"}
+            states = 0
+            for was, writes, waits in reversed(before):
+                if (states < 1 and was[:2] == "s_" and "m0" in writes) or (states < 5 and was[:2] == "v_" and writes & scalars):
+                    early.append(f"{was} {sorted(writes)}, {states} wait states: {text}")
+                states += waits
+        waits = int(operands[0], 0) + 1 if op == "s_nop" else 1
+        before = before[-5:] + [(op, registers(operands[0]), waits)]
+    return found, early
+
+
+def test_the_check_itself():
+    write, load = "s_mov_b32 m0, s4", "global_load_lds_dwordx4 v1, s[2:3]"
+    for lines, bad in (([write, load], 1), ([write, "s_nop 0", load], 0), ([write, "v_add_u32_e32 v2, v3, v4", load], 0),
+                       (["v_readlane_b32 s3, v9, 1", write, "s_nop 2", load], 1),
+                       (["v_readlane_b32 s3, v9, 1", write, "s_nop 3", load], 0), (["v_readlane_b32 s5, v9, 1", "s_nop 0", load], 0)):
+        assert loads_to_lds_too_early(lines)[0] == 1 and len(loads_to_lds_too_early(lines)[1]) == bad, lines
+
+
+def test_loads_to_lds_wait_for_their_registers(code_objects):
+    """The write of M0 and the load are one piece of assembly, in which the compiler keeps no wait states."""
+    found = 0
+    for path in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", path], check=True, stdout=subprocess.PIPE,
+                              text=True, timeout=120).stdout
+        n, early = loads_to_lds_too_early(text.splitlines())
+        assert not early, early[:5]
+        found += n
+    assert found > 0

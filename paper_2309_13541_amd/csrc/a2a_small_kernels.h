@@ -50,7 +50,8 @@ __device__ __forceinline__ const T& lds_at(const T* base, uint32_t bytes) {
 }
 
 // LDS by its byte address, for kernels that have no other than their dynamic array, which starts at 0: the compiler adds the
-// array's address to every place, which is an instruction also where it is 0.
+// array's address to every place, which is an instruction also where it is 0.  A __shared__ array in such a kernel, or in a function
+// that it calls, would move the dynamic one and these would miss it (tests/test_machine_code.py looks for that in what was built).
 template <typename T>
 __device__ __forceinline__ T lds_get(uint32_t at) {
   return *(const __attribute__((address_space(3))) T*)at;
@@ -542,7 +543,7 @@ __device__ __forceinline__ int small_sort(const SmallView& sv, const SmallLds& l
   return depth;
 }
 
-// A workgroup's totals into its counters (all threads call it).  lds: kSmallTotals words of 8 bytes.
+// A workgroup's totals into its counters (all threads call it).  lds: kSmallTotals words of 8 bytes, the caller's.
 constexpr int kSmallTotals = kSmallThreads / kWave * 4;
 __device__ __forceinline__ void small_totals(const SmallView& sv, double* lds, long long dsum, long long reached, bool inexact,
                                              double wd, bool weighted) {
@@ -572,11 +573,6 @@ __device__ __forceinline__ void small_totals(const SmallView& sv, double* lds, l
   c[1] = reached;
   c[2] = bad;
   c[3] = __double_as_longlong(wd);
-}
-__device__ __forceinline__ void small_totals(const SmallView& sv, long long dsum, long long reached, bool inexact, double wd,
-                                             bool weighted) {
-  __shared__ double s_totals[kSmallTotals];
-  small_totals(sv, s_totals, dsum, reached, inexact, wd, weighted);
 }
 
 // Link loads of sources [per_wg * workgroup, + per_wg) of the call, as one row of `part`.  The search takes up to
@@ -929,6 +925,7 @@ static_assert(kBothTables < 1 << kHandedShift, "paths from one source, and the p
 template <int KS>
 __global__ void __launch_bounds__(kSmallThreads) k_small_sssp(SmallView sv, SmallSssp ss) {
   extern __shared__ double s_small[];
+  __shared__ double s_totals[kSmallTotals];
   constexpr uint32_t kNone = 0xffffffffu;
   const int N = sv.N;
   const SmallLds lds(sv, s_small, kStateSssp);
@@ -1003,7 +1000,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_sssp(SmallView sv, Smal
       __syncthreads();
     }
   }
-  small_totals(sv, dsum, reached, false, 0.0, false);
+  small_totals(sv, s_totals, dsum, reached, false, 0.0, false);
 }
 
 // weight[v][j] += what the sources of the iteration handed from node v to its in-link j.  A workgroup takes 64

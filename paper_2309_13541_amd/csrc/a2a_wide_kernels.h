@@ -112,6 +112,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   Word* const front = reinterpret_cast<Word*>(s_small);
   __shared__ int s_more;
   __shared__ int s_sum[W];
+  __shared__ double s_totals[kSmallTotals];
   const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave), N = wv.N;
   const int last = (N - 1) / kStride;  // step
   const size_t level_words = (size_t)wv.slots * kWideThreads;
@@ -392,7 +393,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   if (kMasks) return;
   SmallView sv{};
   sv.counters = wv.counters;
-  small_totals(sv, 0, reached, false, 0.0, false);
+  small_totals(sv, s_totals, 0, reached, false, 0.0, false);
 }
 
 // Index entries of the level kernels from the masks of the search: a workgroup takes a level of a batch of 64 sources

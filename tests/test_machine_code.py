@@ -68,3 +68,43 @@ def test_loads_to_lds_wait_for_their_registers(code_objects):
         assert not early, early[:5]
         found += n
     assert found > 0
+
+
+CSRC = os.path.join(os.path.dirname(a2a.library_path()), "csrc")
+
+
+def by_address():
+    """Kernels that use LDS by its byte address, by themselves or through what they call (by name: rather more than fewer)."""
+    head = re.compile(r"__(global|device)__\b[^;({}]*?(\w+)\s*\(")
+    text, kernels = {}, set()  # of a function: from its head to the next one's
+    for name in sorted(os.listdir(CSRC)):
+        if name.endswith(".h"):
+            with open(os.path.join(CSRC, name)) as f:
+                source = re.sub(r"//.*|__launch_bounds__\(\w+\)", "", f.read())
+            heads = list(head.finditer(source))
+            for m, end in zip(heads, [m.start() for m in heads[1:]] + [len(source)]):
+                text[m[2]] = text.get(m[2], "") + source[m.end():end]
+                if m[1] == "global":
+                    kernels.add(m[2])
+    users = {"lds_get", "lds_put"}
+    while True:
+        calls = re.compile(rf"\b(?:{'|'.join(sorted(users))})\s*[<(]")
+        more = {f for f in text if f not in users and calls.search(text[f])}
+        if not more:
+            return users & kernels
+        users |= more
+
+
+def test_lds_by_address_starts_at_zero(code_objects):
+    """Such a kernel has no LDS but its dynamic array: no __shared__ array of its own or of what it calls."""
+    names = by_address()
+    assert names >= {"k_small_loads", "k_small_sigma", "k_small_dist", "k_small_levels", "k_flow_sources", "k_flow_links", "k_flow_sssp"}
+    assert not names & {"k_wide_dist", "k_small_sssp", "k_small_reduce"}  # these have some
+    sizes = {}
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, stdout=subprocess.PIPE, text=True,
+                               timeout=120).stdout
+        for size, length, rest in re.findall(r"\.group_segment_fixed_size: (\d+)(?:.*\n)+?.*\.name: +_ZN7a2a_devL?(\d+)(\w+)", notes):
+            sizes.setdefault(rest[:int(length)], set()).add(int(size))
+    assert names <= set(sizes) and 0 not in sizes["k_wide_dist"]
+    assert {k: sizes[k] for k in names if sizes[k] != {0}} == {}

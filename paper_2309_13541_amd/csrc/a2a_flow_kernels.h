@@ -1,12 +1,12 @@
-// Link loads of topologies whose path counts or coefs of one source fit LDS (8 bytes a node: up to 20000 nodes) but whose
-// link loads do not fit the registers of a workgroup.
+// Link loads of topologies whose path counts or coefs of one source fit LDS (8 bytes a node: up to 20352 nodes; 16 with demands: 10176)
+// but whose link loads do not fit the registers of a workgroup (from 2049 nodes of 16 links, 8192 of 4 links on).
 //
 // The level kernels gather 64 sources at a time out of rows in memory.  Here a workgroup takes a source from its sorted levels
 // to its path counts and coefs with all gathers in LDS (k_flow_sources), and leaves a row of each in memory.  A second kernel
 // then goes over the sources with the loads of a block of links in registers and a source's path counts in LDS (k_flow_links),
 // and a third adds up its rows.  Whole calls over all sources, level kernels and these: 16384 nodes of a generalized Kautz
-// topology of degree 4 4.31 -> 2.37 ms, 20011 of degree 5 (2501 sources) 1.49 -> 0.63 ms, 8191 of degree 8 with demands 1.93 ->
-// 1.32 ms, 6000 of degree 8 0.95 -> 0.51 ms, 16384 of degree 16 10.2 -> 4.1 ms.
+// topology of degree 4 3.70 -> 2.23 ms, of a random one 6.51 -> 2.63 ms; random topologies of 20011 nodes of degree 5 (2501 sources)
+// 1.46 -> 0.59 ms, 8191 of degree 8 with demands 1.90 -> 1.15 ms, 6000 of degree 8 0.95 -> 0.49 ms, 16384 of degree 16 10.2 -> 4.1 ms.
 #pragma once
 
 #include "a2a_wide_kernels.h"

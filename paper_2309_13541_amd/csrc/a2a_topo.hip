@@ -986,10 +986,10 @@ int wide_sigma(const a2a_topo* t, int32_t src_begin, int32_t src_count, const Sm
 
 // Whether link loads of src_count sources go by sources in LDS and links in registers: path counts of all levels below 2^24 (a
 // word holds a count and its level), LDS large enough, and for one source and group at least the smallest workspace that a caller may
-// bring.  us of level kernels and of this, all sources, 1024 and 256 of them: 8192 nodes of degree 5 1673, 804; 320, 256; 221,
-// 264.  16384 of degree 4 6497, 2646; 597, 253; 404, 247.  20011 of degree 5 9886, 4204; 692, 316; 422, 295.  6000 of degree 8 950,
-// 506; 249, 259; 169, 286.  It would win for fewer sources too (from 8192 nodes on) and with more levels (20011 of degree 3, 12 levels,
-// 10819, 4226): there the level kernels stay, whose results the tests hold bit for bit.
+// bring.  us of level kernels and of this, random topologies, all sources, 1024 and 256 of them: 8192 nodes of degree 5 1680, 760; 313,
+// 162; 214, 177.  16384 of degree 4 6520, 2638; 590, 250; 396, 242.  20011 of degree 5 9944, 4165; 690, 309; 411, 290.  6000 of degree 8
+// 954, 488; 242, 220; 163, 228.  It would win for fewer sources too (from 8192 nodes on) and with more levels (20011 of degree 3, 12
+// levels, 10853, 4175): there the level kernels stay, whose results the tests hold bit for bit.
 bool flow_fits(const a2a_topo* t, int32_t src_count, bool demand) {
   const double bits = (double)t->level_bound * std::log2((double)std::max(t->dmax_in, 2));  // as Run::narrow
   return t->ell_words > 0 && t->N <= kFlowNodes && !t->small_loads && src_count >= kFlowFewestSources && t->level_bound >= 1 &&

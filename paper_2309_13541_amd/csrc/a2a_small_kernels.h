@@ -8,7 +8,7 @@
 // link loads per workgroup.  Whole calls with the level kernels and with this one: 8x8 torus 138 and 12 us, hypercube
 // of 1024 nodes 262 and 42 us, 16x16x16 torus 1025 and 246 us.  Bound in the first two by the chain of LDS accesses and barriers
 // from level to level, in the third by the number of LDS instructions: the vector ALUs are 1, 22 and 43 % busy, and LDS takes an
-// instruction every 17 and 9.9 cycles in the last two, where it gives a wave random words in 7.3 and 8-byte ones in 9.9.  Every sum is
+// instruction every 17 and 10 cycles in the last two, where it gives a wave random words in 7.3 and 8-byte ones in 9.9.  Every sum is
 // taken in a fixed order, so the results are the same bits from run to run and for every workspace size.
 #pragma once
 

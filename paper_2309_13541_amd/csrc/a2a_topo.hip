@@ -771,6 +771,15 @@ bool small_loads_fit(const a2a_topo* t) {
          256 + kSmallChunk * small_row_bytes(t, kSmallBatch) <= t->min_loads_bytes;
 }
 
+// Workspace for all rows at once of a call over src_count sources or fewer.  (256 sources of 256 nodes of degree 8 have 4.2 MB of
+// rows; 1.2 MB are what the level kernels take, and in those the rows went in four launches, and as many to add them up: 40.6 us,
+// 13.0 in one.  256 sources of 1000 nodes 70.3, 23.6.)
+size_t small_loads_bytes(const a2a_topo* t, int32_t src_count) {
+  const SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
+  const int rows = std::max(p.workgroups, std::min(src_count, kComputeUnits));
+  return 256 + (size_t)rows * small_row_bytes(t, p.sv.per_wg);
+}
+
 int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
                      double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
                      hipStream_t st) {
@@ -1293,8 +1302,9 @@ int a2a_topo_info(const a2a_topo* t, int32_t* N, int64_t* E, int32_t* dmax, int3
 size_t a2a_workspace_bytes(const a2a_topo* t, int32_t src_count, int flags) {
   if (!t || src_count < 0 || (size_t)src_count > align_up((size_t)t->N, 64)) return 0;
   if (src_count == 0) return 256;
-  const Layout L = make_layout(t, src_count, flags & 0xff, 0, true, (flags & A2A_WS_MINIMAL) != 0);
-  return L.total;
+  const bool minimal = (flags & A2A_WS_MINIMAL) != 0;
+  const Layout L = make_layout(t, src_count, flags & 0xff, 0, true, minimal);
+  return minimal || !(flags & A2A_WS_LOADS) || !t->small_loads ? L.total : std::max(L.total, small_loads_bytes(t, src_count));
 }
 
 int a2a_distances(const a2a_topo* t, int32_t src_begin, int32_t src_count, int32_t* dist, double* sigma,

@@ -107,3 +107,18 @@ def test_path_counts_of_a_small_group(a2a, oracle, hub):
         assert np.array_equal(dist, o.dist)
         assert_sigma_equal(sigma, o.sigma)
     topo.close()
+
+
+@pytest.mark.parametrize("nodes,degree,cnt", [(150, 6, 150), (256, 8, 256), (257, 8, 257), (1000, 8, 256), (3000, 3, 700)])
+def test_recommended_workspace_takes_one_launch_of_each_kernel(a2a, nodes, degree, cnt):
+    """Rows of partial loads for every workgroup of a call, also where that is more than the level kernels would take."""
+    import torch
+    topo = a2a.Topology(*gen.random_regular(nodes, degree, 5))
+    topo.profile_enable(1)
+    run_link_loads(topo, 0, cnt)
+    p = topo.profile_read()
+    topo.profile_enable(0)
+    whole = run_link_loads(topo, 0, cnt)[0]
+    assert np.array_equal(run_link_loads(topo, 0, cnt, 1)[0], whole)  # (the least it takes)
+    assert p["sources"]["launches"] == 1 and p["reduce"]["launches"] == 1
+    topo.close()

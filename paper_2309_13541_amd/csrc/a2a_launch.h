@@ -20,6 +20,8 @@ struct SmallPlan {
 template <int KS>
 void launch_small_loads(const SmallPlan& p, bool demand, int workgroups, hipStream_t st);
 template <int KS>
+void launch_node_loads(const SmallPlan& p, bool demand, int workgroups, hipStream_t st);
+template <int KS>
 void launch_small_outputs(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st);
 template <int KS>
 void launch_small_levels(const SmallPlan& p, int workgroups, hipStream_t st);

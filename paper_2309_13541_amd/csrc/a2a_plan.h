@@ -165,8 +165,8 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
   const int state = what == SmallWhat::kLoads ? kStateLoads : what == SmallWhat::kSigma ? kStateSigma : kStateSssp;
   const int most = small_most_nodes(what, ell_words);
   int tg = small_threads(N), per = 1;
-  // A source that has a compute unit to itself: a thread per node where there are few (link loads, us: 200 nodes of degree 8
-  // 51.7, now 48.0; 200 sources of 1000 nodes 73.1, 67.1; of a 40x40 torus 63.5, 59.4; 150 of 2500 nodes 73.4, 73.8 with it).
+  // A source that has a compute unit to itself, of what node_fits leaves: a thread per node where there are few (link loads, us: 200
+  // sources of 1000 nodes 73.1, now 67.1; 150 of 2500 nodes 73.4, 73.8 with it).
   if (what == SmallWhat::kLoads && src_count <= kComputeUnits && N <= 2 * kSmallThreads) tg = std::min(kSmallThreads, up(N));
   if (what == SmallWhat::kDist) {
     tg = std::min(kSmallThreads, up(N));
@@ -198,6 +198,38 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
   // 1.25 times an average level: most levels in one go
   c.ts = std::min(tg, up((int)((size_t)N * 5 / 4 / (size_t)std::max(depth, 1))));
   return c;
+}
+
+// Link loads with a thread per node (k_node_loads): LDS of four arrays of a double per node, each where an instruction's constant
+// offset reaches it, and the waves' totals.
+constexpr int kNodeMost = 2;  // nodes a thread may have
+constexpr int node_apart(int nodes) { return nodes * kSmallThreads * 8; }
+constexpr size_t node_lds_bytes(int N, int nodes) { return 3 * (size_t)node_apart(nodes) + (size_t)N * 8 + kSmallThreads / kSmallWave * 32; }
+
+// A thread has a node, or two where the registers allow it (link tables of 8 words spill: 1100 nodes 124 us, k_small_loads 52).  A
+// workgroup for every compute unit, its sources one after the other: two workgroups at a time on a unit would leave twice the rows
+// to add up (all of 512 nodes of degree 4 13.0 us, 15.4 then; of 300 11.7, 13.3).
+struct NodeCut {
+  int threads, nodes, per_wg, workgroups;  // of a workgroup, per thread, sources of a workgroup, of the whole call
+};
+inline NodeCut node_cut(int N, int src_count) {
+  NodeCut c;
+  c.nodes = N <= kSmallThreads ? 1 : 2;
+  c.threads = ((N + c.nodes - 1) / c.nodes + kSmallWave - 1) / kSmallWave * kSmallWave;
+  c.per_wg = (src_count + kComputeUnits - 1) / kComputeUnits;
+  c.workgroups = (src_count + c.per_wg - 1) / c.per_wg;
+  return c;
+}
+// Which calls take it.  k_small_loads goes over the levels of several sources at a time, and every level only over its own nodes;
+// here each source has its levels to itself, and every node without a level looks at its links.  So it depends on the sources of a
+// workgroup and on the levels (us, k_small_loads and this): one source each: 256 nodes of degree 8 13.0, 9.9; 4x128 torus (66
+// levels) 44.5, 23.5; 2000 of degree 8 37.0, 29.5.  Two: bidirectional ring of 500 (250 levels) 155, 121; 2048 of degree 3 30.0, 25.4;
+// 40x40 torus 47.5, 49.7.  Three: 9x9x9 torus (12 levels) 27.7, 26.6; 24x24 (24) 26.9, 29.2.  Four: hypercube of 1024 (10)
+// 39.8, 38.6; 10x10x10 torus (15) 37.2, 39.3.  Six: 1400 of degree 3 (9) 49.3, 44.9.  Seven: 1537 of degree 3 (9) 50.6, 54.2.
+constexpr int kNodeFewSources = 2, kNodeFewLevels = 10;
+inline bool node_fits(int N, int ell_words, int depth, int src_count) {
+  if (N > kNodeMost * kSmallThreads || (N > kSmallThreads && ell_words > 5)) return false;
+  return node_cut(N, src_count).per_wg <= kNodeFewSources || (N <= kSmallThreads * 3 / 2 && depth <= kNodeFewLevels);
 }
 
 // ---------------------------------------------------------------------------------------

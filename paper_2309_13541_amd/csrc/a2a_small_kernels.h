@@ -686,6 +686,118 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
   small_totals(sv, s_small, dsum, reached, largest >= kTwo53, wd, kDemand);
 }
 
+// Link loads of topologies that give a thread a node or two, a source at a time, as rows like those of k_small_loads.  A thread keeps
+// its nodes' links, levels, path counts and link loads in registers.  Forward, a level has the nodes without a level
+// add up their in-neighbours' path counts: a sum that is not zero is the node's own and puts it on this level, so the
+// search and the path counts are one sweep, and nothing is sorted.  Backward, the nodes of a level add up the coefs of their
+// out-neighbours, and what each link brought, times the path count, is its load.  Values of even and of odd levels lie in two arrays, 0
+// where there is none: a node without a level at level l has in-links from level l - 1 or later, and the later ones are not in
+// the array of the level before; out-links of level l lead to levels up to l + 1, and those below l are not yet written.
+// Bound by the chain of a level: gathers, sum, store, barrier.  Whole calls, k_small_loads and this: 8x8 torus 10.8, 9.7 us, 256 nodes of
+// degree 8 13.0, 9.9, 512 of degree 4 16.4, 13.0, 1000 of degree 8 35.3, 31.5; where that is over: node_fits.
+template <int KS, int kNodes, bool kDemand>
+__global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
+  extern __shared__ double s_small[];
+  constexpr uint32_t kApart = node_apart(kNodes);  // sigma of even and odd levels, coefs of even and odd levels
+  constexpr int kNever = -2, kNone = -1;
+  const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
+  const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
+  const int s_last = min(sv.src_count, s_first + sv.per_wg);
+  SmallRow<KS> in[kNodes], out[kNodes];
+  double acc[kNodes][2 * KS];
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k) {
+    const int v = min(t + T * k, N - 1);
+    in[k].load(sv.in, 8 * v);
+    out[k].load(sv.out, 8 * v);
+#pragma unroll
+    for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
+  }
+  long long dsum = 0, reached = 0;
+  double largest = 0.0, wd = 0.0;
+  for (int s = s_first; s < s_last; ++s) {
+    const int source = sv.src_begin + s;
+    int lvl[kNodes];
+    double own[kNodes], demand[kNodes];
+    if (s != s_first) __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) {
+      const int v = t + T * k;
+      lvl[k] = v >= N ? kNever : v == source ? 0 : kNone;
+      own[k] = v == source ? 1.0 : 0.0;
+      demand[k] = 0.0;
+      if (v < N) {
+        lds_put(8 * v, own[k]);
+#pragma unroll
+        for (int a = 1; a < 4; ++a) lds_put(8 * v + a * kApart, 0.0);
+        if (kDemand) demand[k] = sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)s];
+      }
+    }
+    const auto gather = [&](const SmallRow<KS>& row, uint32_t from, double (&y)[2 * KS]) {
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<double>(row.at(j) + from);
+    };
+    const auto forward = [&](auto odd, int l) {
+      constexpr uint32_t kNow = decltype(odd)::value ? kApart : 0, kBefore = kApart - kNow;
+      __syncthreads();
+#pragma unroll
+      for (int k = 0; k < kNodes; ++k) {
+        if (lvl[k] != kNone) continue;
+        double y[2 * KS];
+        gather(in[k], kBefore, y);
+        const double a = SmallNode<KS>::sum_pairs(y);
+        if (a > 0.0) {
+          lvl[k] = l;
+          own[k] = a;
+          lds_put(8 * (t + T * k) + kNow, a);
+        }
+      }
+    };
+    for (int l = 1; l <= sv.depth; l += 2) {
+      forward(std::true_type{}, l);
+      if (l == sv.depth) break;
+      forward(std::false_type{}, l + 1);
+    }
+    const auto backward = [&](auto odd, int l) {
+      constexpr uint32_t kNow = 2 * kApart + (decltype(odd)::value ? kApart : 0), kAfter = 5 * kApart - kNow;
+#pragma unroll
+      for (int k = 0; k < kNodes; ++k) {
+        if (lvl[k] != l) continue;
+        double y[2 * KS];
+        gather(out[k], kAfter, y);
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j) acc[k][j] = __builtin_fma(own[k], y[j], acc[k][j]);
+        const double r = recip(own[k]);
+        lds_put(8 * (t + T * k) + kNow, (kDemand ? demand[k] * r : r) + SmallNode<KS>::sum_pairs(y));
+      }
+      __syncthreads();
+    };
+    int l = sv.depth;
+    if (!(l & 1)) backward(std::false_type{}, l--);
+    for (; l > 0; l -= 2) {
+      backward(std::true_type{}, l);
+      backward(std::false_type{}, l - 1);
+    }
+#pragma unroll
+    for (int k = 0; k < kNodes; ++k) {
+      dsum += max(lvl[k], 0);
+      reached += lvl[k] > 0 ? 1 : 0;
+      largest = larger(largest, own[k]);
+      if (kDemand && lvl[k] > 0) wd = __builtin_fma((double)lvl[k], demand[k], wd);
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < kNodes; ++k) {
+    const int v = t + T * k;
+    if (v < N) {
+      double* const to = sv.part + (size_t)blockIdx.x * (size_t)(2 * KS) * (size_t)N + (size_t)v;
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) to[(size_t)j * (size_t)N] = acc[k][j];
+    }
+  }
+  small_totals(sv, &lds_at(s_small, 3 * kApart + 8 * (uint32_t)N), dsum, reached, largest >= kTwo53, wd, kDemand);
+}
+
 // Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and
 // forward sweep as above.
 struct SmallOut {

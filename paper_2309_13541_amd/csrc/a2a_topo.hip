@@ -756,6 +756,21 @@ SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
   return p;
 }
 
+// The same for link loads, with a thread per node where that is faster.
+SmallPlan small_loads_plan(const a2a_topo* t, int32_t src_count) {
+  SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
+  if (node_fits(t->N, t->ell_words, t->level_bound, src_count)) {
+    const NodeCut c = node_cut(t->N, src_count);
+    p.T = c.threads;
+    p.nodes = c.nodes;
+    p.workgroups = c.workgroups;
+    p.lds = node_lds_bytes(t->N, c.nodes);
+    p.sv.per = 1;
+    p.sv.per_wg = c.per_wg;
+  }
+  return p;
+}
+
 // Bytes of workspace per workgroup: its row of partial loads, its counters and level bytes.
 size_t small_row_bytes(const a2a_topo* t, int per_wg) {
   return (size_t)t->N * t->ell_words * 2 * sizeof(double) + kSmallCounters * sizeof(long long) +
@@ -775,7 +790,7 @@ bool small_loads_fit(const a2a_topo* t) {
 // rows; 1.2 MB are what the level kernels take, and in those the rows went in four launches, and as many to add them up: 40.6 us,
 // 13.0 in one.  256 sources of 1000 nodes 70.3, 23.6.)
 size_t small_loads_bytes(const a2a_topo* t, int32_t src_count) {
-  const SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
+  const SmallPlan p = small_loads_plan(t, src_count);
   const int rows = std::max(p.workgroups, std::min(src_count, kComputeUnits));
   return 256 + (size_t)rows * small_row_bytes(t, p.sv.per_wg);
 }
@@ -784,7 +799,8 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
                      double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
                      hipStream_t st) {
   if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
+  SmallPlan p = small_loads_plan(t, src_count);
+  const bool by_node = node_fits(t->N, t->ell_words, t->level_bound, src_count);
   p.sv.src_begin = src_begin;
   p.sv.dem = demand;
   p.sv.dem_ld = src_count;
@@ -801,7 +817,8 @@ int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, co
     p.sv.wg0 = w0;
     {
       ProfScope ps(t, PROF_SOURCES, st);
-      by_words(t->ell_words, [&](auto ks) { launch_small_loads<decltype(ks)::value>(p, demand != nullptr, n, st); });
+      by_words(t->ell_words, [&](auto ks) { by_node ? launch_node_loads<decltype(ks)::value>(p, demand != nullptr, n, st)
+                                                      : launch_small_loads<decltype(ks)::value>(p, demand != nullptr, n, st); });
     }
     ProfScope ps(t, PROF_REDUCE, st);
     k_small_reduce<<<blocks, kBlock, 0, st>>>(p.sv, t->ell_words, n, w0 == 0 ? 1 : 0, w0 + n == p.workgroups ? 1 : 0,

@@ -45,6 +45,16 @@ void launch_small_loads(const SmallPlan& p, bool demand, int workgroups, hipStre
 }
 
 template <int KS>
+void launch_node_loads(const SmallPlan& p, bool demand, int workgroups, hipStream_t st) {
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, p.T, p.lds, st>>>(p.sv); };
+  constexpr int kTwo = KS <= 5 ? 2 : 1;  // (node_fits)
+  if (p.nodes == 1)
+    demand ? launch(k_node_loads<KS, 1, true>) : launch(k_node_loads<KS, 1, false>);
+  else
+    demand ? launch(k_node_loads<KS, kTwo, true>) : launch(k_node_loads<KS, kTwo, false>);
+}
+
+template <int KS>
 void launch_small_outputs(const SmallPlan& p, const SmallOut& out, int workgroups, hipStream_t st) {
   const auto launch = [&](auto nodes) {
     constexpr int kNodes = decltype(nodes)::value;
@@ -148,6 +158,7 @@ void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st) {
 }
 
 template void launch_small_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStream_t);
+template void launch_node_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStream_t);
 template void launch_small_outputs<A2A_WORDS>(const SmallPlan&, const SmallOut&, int, hipStream_t);
 template void launch_small_levels<A2A_WORDS>(const SmallPlan&, int, hipStream_t);
 template void launch_small_sssp<A2A_WORDS>(const SmallPlan&, const SmallSssp&, hipStream_t);

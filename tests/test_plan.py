@@ -183,3 +183,35 @@ def test_path_counts_of_ten_thousand_levels():
         assert dsum[i] == want.sum()
     assert unr == 0 and flags == 0
     topo.close()
+
+
+NODES = r"""
+#include <cstdio>
+#include "a2a_plan.h"
+using namespace a2a_dev;
+
+int main() {
+  long long bad = 0, seen = 0;
+  for (int N = 1; N <= kScaledNodes; ++N)
+    for (int words : {2, 3, 4, 5, 8})
+      for (int depth : {0, 1, 10, 11, 253})
+        for (int n : {1, 2, 255, 256, 257, 511, 512, 513, 1024, 1536, N - 1, N}) {
+          if (n < 1 || n > N || !node_fits(N, words, depth, n)) continue;
+          const NodeCut c = node_cut(N, n);
+          ++seen;
+          const bool ok = c.threads >= kSmallWave && c.threads % kSmallWave == 0 && c.threads <= kSmallThreads &&
+                          c.nodes >= 1 && c.nodes <= (words <= 5 ? kNodeMost : 1) && c.nodes * c.threads >= N &&
+                          N * 8 <= node_apart(c.nodes) &&
+                          node_lds_bytes(N, c.nodes) >= 3 * (size_t)node_apart(c.nodes) + 8 * (size_t)N + c.threads / kSmallWave * 32 &&
+                          node_lds_bytes(N, c.nodes) <= kSmallLds && c.per_wg >= 1 && c.workgroups <= kComputeUnits &&
+                          (long long)c.workgroups * c.per_wg >= n && (long long)(c.workgroups - 1) * c.per_wg < n;
+          if (!ok && ++bad <= 10) std::printf("N %d words %d depth %d sources %d\n", N, words, depth, n);
+        }
+  std::printf("%lld cuts, %lld bad\n", seen, bad);
+  return bad != 0 || seen == 0;
+}
+"""
+
+
+def test_a_thread_per_node_fits_a_workgroup(compiled):
+    assert compiled("nodes", NODES).returncode == 0

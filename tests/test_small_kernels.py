@@ -74,6 +74,41 @@ def test_too_many_nodes_for_three_sources(a2a, oracle, name):
     topo.close()
 
 
+# A thread per node or two (k_node_loads), at the edges of its rule: a wave and one node over; a node a thread and one over, one
+# source each and two; most nodes; three sources with few and with too many levels; and links out of service, so that some
+# nodes are out of reach.
+NODES = [(name, csr, s0, cnt) for name, csr, s0, cnt in (
+    ("1 node", lambda: gen.csr_from_rows([[]]), 0, 1),
+    ("64 nodes", lambda: gen.random_regular(64, 4, 3), 0, 64),
+    ("65 nodes, one source", lambda: gen.random_regular(65, 9, 3), 64, 1),
+    ("1024 nodes, 3 sources each", lambda: gen.random_regular(1024, 3, 3), 100, 700),
+    ("1025 nodes, a source each", lambda: gen.random_regular(1025, 5, 3), 700, 256),
+    ("2048 nodes, 2 sources each", lambda: gen.random_regular(2048, 8, 3), 1, 511),
+    ("1536 nodes, 6 sources each", lambda: gen.random_regular(1536, 4, 3), 0, 1536),
+    ("22x23 torus", lambda: gen.torus([22, 23]), 0, 506),
+    ("26x27 torus, 3 sources each", lambda: gen.torus([26, 27]), 0, 702),
+    ("8x9 torus with 90 links left", lambda: gen.remove_arcs(gen.torus([8, 9]), np.random.default_rng(5).permutation(288)[90:]), 0, 72))]
+
+
+@pytest.mark.parametrize("name,csr,s0,cnt", NODES, ids=[e[0] for e in NODES])
+def test_a_thread_per_node(a2a, oracle, name, csr, s0, cnt):
+    rp, col = csr()
+    print(name, flush=True)
+    topo = a2a.Topology(rp, col)
+    o = oracle.run(rp, col, s0, cnt, threads=8)
+    load, dsum, flags = run_link_loads(topo, s0, cnt)
+    assert_loads_close(load, o.load)
+    assert dsum == int(o.dist_sum.sum()) and flags == o.flags
+    least = topo.workspace_bytes(cnt, a2a.WS_LOADS | a2a.WS_MINIMAL)
+    assert np.array_equal(run_link_loads(topo, s0, cnt, least)[0], load)
+    dem = np.random.default_rng(78).integers(0, 7, (cnt, topo.N)).astype(np.float64)
+    want, want_wd = oracle.run_demand(rp, col, dem, s0)
+    load, wd, dsum, flags = run_demand_gpu(topo, dem, s0)
+    assert_loads_close(load, want)
+    assert wd == pytest.approx(want_wd, rel=1e-12) and dsum == int(o.dist_sum.sum())
+    topo.close()
+
+
 @pytest.mark.parametrize("nodes", [32, 33, 254, 255, 256])
 def test_deepest_levels(a2a, oracle, nodes):
     """Directed rings: as many levels as nodes.  Levels fit a byte, with one value for nodes not reached, up to 253."""

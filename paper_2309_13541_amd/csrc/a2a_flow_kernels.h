@@ -7,6 +7,7 @@
 // and a third adds up its rows.  Whole calls over all sources, level kernels and these: 16384 nodes of a generalized Kautz
 // topology of degree 4 3.70 -> 2.23 ms, of a random one 6.51 -> 2.63 ms; random topologies of 20011 nodes of degree 5 (2501 sources)
 // 1.46 -> 0.59 ms, 8191 of degree 8 with demands 1.90 -> 1.15 ms, 6000 of degree 8 0.95 -> 0.49 ms, 16384 of degree 16 10.2 -> 4.1 ms.
+// Up to 65536 nodes: k_strip_sources.
 #pragma once
 
 #include "a2a_wide_kernels.h"
@@ -26,6 +27,9 @@ struct FlowView {
   int source0, sources;        // node of row 0, rows
   int group, groups;           // rows per group of k_flow_links, groups of this launch
   int resume;                  // the groups' loads so far are in `part`
+  // By strips of nodes (k_strip_sources): `count` has 16 bits a node.
+  uint32_t* exact;             // [sources][stride] path counts that those do not hold
+  int* escaped;                // [sources] whether there are any
 };
 
 // A node as the forward sweep leaves it to the backward one, in the order in which levels are gone over.
@@ -70,6 +74,16 @@ struct FlowRow {
       return x;
     }
   }
+  // 8 x id of link j + less.
+  __device__ __forceinline__ uint32_t strip_at(int j, uint32_t less) const {
+    static_assert(!kScaled);
+    uint32_t x;
+    if (j & 1)
+      asm("v_mad_u32_u16 %0, %1, 8, %2 op_sel:[1,0,0,0]" : "=v"(x) : "v"(w[j >> 1]), "s"(less));
+    else
+      asm("v_mad_u32_u16 %0, %1, 8, %2" : "=v"(x) : "v"(w[j >> 1]), "s"(less));
+    return x;
+  }
   // Of the node of a table entry.
   template <int kSize>
   static __device__ __forceinline__ uint32_t own(uint32_t entry) {
@@ -105,23 +119,23 @@ __device__ __forceinline__ void flow_arrived(const FlowRow<KS, kScaled>& row) {
 }
 
 // Sorts nodes by level, in node order within a level: thread t has the nodes 4 words t, ..., their levels as bytes in lv.
-// place(position, node in thread's) is called for every node; those that are not on a level of 1 ... 8 kHalves get positions from
-// `spare` on, kFlowSpare at the most.  totals: [kWideThreads / kWave][8] words of LDS; base: room for 8 kHalves + 1
+// place(position, node in thread's) is called for every node; those that are not on a level of 1 ... kLevels get positions from
+// `spare` on, kFlowSpare at the most.  totals: [kWideThreads / kWave][8] words of LDS; base: room for kLevels + 1
 // positions per thread.  Has one barrier inside.  Returns where levels start: lane l has level l (lanes past the last level
 // the end).  No atomics: a thread's counts per level are the bytes of 64-bit words, eight levels each, and the sums over threads
 // 16-bit fields.  Bound by the vector ALUs (some 20 instructions a node).
 constexpr int kFlowSpare = 32;
-template <int kHalves, typename Place>
-__device__ __forceinline__ int flow_sort(uint32_t (&lv)[kFlowWords], int words, uint32_t* totals, unsigned short* base,
+template <int kLevels, int kMost, typename Place>
+__device__ __forceinline__ int flow_sort(uint32_t (&lv)[kMost], int words, uint32_t* totals, unsigned short* base,
                                          int spare, int wave, int lane, Place&& place) {
-  constexpr int kFields = 4 * kHalves, kLevels = 8 * kHalves;
+  constexpr int kHalves = (kLevels + 7) / 8, kFields = 4 * kHalves;
   const auto level = [&](int k, int i) { return min((lv[k] >> (8 * i) & 255u) - 1u, (uint32_t)kLevels); };  // less one
   uint64_t count[kHalves];
-  uint32_t rank[kFlowWords];  // of a node among the thread's on its level, a byte each
+  uint32_t rank[kMost];  // of a node among the thread's on its level, a byte each
 #pragma unroll
   for (int h = 0; h < kHalves; ++h) count[h] = 0;
 #pragma unroll
-  for (int k = 0; k < kFlowWords; ++k) {
+  for (int k = 0; k < kMost; ++k) {
     rank[k] = 0;
     if (k >= words) break;
 #pragma unroll
@@ -170,7 +184,7 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kFlowWords], int words, 
   if (lane > kLevels) at = (int)sum;
   mine[kLevels * kWideThreads] = (unsigned short)spare;
 #pragma unroll
-  for (int k = 0; k < kFlowWords; ++k) {
+  for (int k = 0; k < kMost; ++k) {
     if (k >= words) break;
     asm volatile("" : "+v"(lv[k]), "+v"(rank[k]));  // nothing worked out before the barrier is kept
     uint32_t at_level[4];
@@ -258,8 +272,8 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
     int v1 = v0;
     asm volatile("" : "+v"(v1));  // not kept from source to source
     const auto place = [&](uint32_t p, int i) { q[p] = (unsigned short)((v1 + i) << kId); };
-    const int starts = fv.depth <= 8 ? flow_sort<1>(lv, words, s_totals, base, S, wave, lane, place)
-                                     : flow_sort<2>(lv, words, s_totals, base, S, wave, lane, place);
+    const int starts = fv.depth <= 8 ? flow_sort<8>(lv, words, s_totals, base, S, wave, lane, place)
+                                     : flow_sort<16>(lv, words, s_totals, base, S, wave, lane, place);
     if (t == 0) x[fv.source0 + s] = flow_above(0) + 1u;
     const int after = __shfl_down(starts, 1, kWave);
     const uint64_t filled = __ballot(lane >= 1 && lane <= fv.depth && after > starts);
@@ -455,6 +469,439 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   small_totals(sv, s_small, dsum, reached, false, 0.0, false);
 }
 
+// Threads of a workgroup wait for each other and for what they have written to LDS, not for memory.
+__device__ __forceinline__ void strip_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// What k_flow_sources does, for topologies whose coefs of one source do not fit LDS (up to 65536 nodes).  16-bit words of all nodes do:
+// the levels that occur counted down, above the path count.  A count that does not fit leaves all ones there, and itself
+// in memory (fv.exact), where the few that meet it read it.  So the forward sweep is that of k_flow_sources, with the queue in memory.
+// Backward, a level's coefs come into LDS a strip of nodes at a time, and the nodes of the level before go over their
+// links once per strip: a link that leads elsewhere reads the 0 behind the strip (all lanes the same word, which costs little).
+// Their sums stay in registers in between, kPieces nodes a thread.  A level of few nodes needs no strips: a bit per node says
+// which are on it, and the coefs are a list.  The last level, and a level before one of few nodes, is worked out strip by strip
+// as it goes into LDS; others come from memory, where they wait in the row of the output.
+// A source of 65536 nodes of degree 8 takes 564 thousand cycles: sort 48, forward 124, levels of few nodes 27, level 6 into LDS 106, level 5
+// into LDS 60, the sums over strips 135, what a level is by itself 42.  Bound by chains within a piece (links, gathers, sum) and by
+// barriers between strips, then by LDS (half of the time) and memory (2.4 MB read, 1.8 MB written a source).  Link tables that have a
+// node's links by strips took less LDS time, but 4 MB more in L2: 4.8 MB read a source, 97 ms a call, now 80.
+template <int KS>
+__global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
+  extern __shared__ double s_small[];
+  using Row = FlowRow<KS, false>;
+  constexpr int T = kWideThreads, kPieces = KS <= 4 ? 24 : KS == 5 ? 16 : 8;
+  const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int N = fv.N, S = fv.stride, nl = (int)small_level_bytes(N);
+  const int words = (N + 4 * T - 1) / (4 * T);
+  const int count_bits = strip_count_bits(fv.depth);
+  const uint32_t count_most = (1u << count_bits) - 1u;
+  const StripCut strips = strip_cut(N);
+  unsigned short* const x = reinterpret_cast<unsigned short*>(s_small);  // the queue, then the nodes' words
+  unsigned short* const base = x + S;
+  uint32_t* const s_totals = reinterpret_cast<uint32_t*>(s_small + kStripState / 8);
+  int* const s_strip = reinterpret_cast<int*>(s_totals + T / kWave * 8);  // [strip][level less one]: place in the queue
+  int* const s_escaped = s_strip + kStripMost * 16;
+  unsigned short* const queue = reinterpret_cast<unsigned short*>(static_cast<char*>(fv.record) + (size_t)blockIdx.x * strip_record_bytes(S));
+  uint32_t* const record = reinterpret_cast<uint32_t*>(queue + S);  // node, path count above it (all ones: in fv.exact)
+  const auto above = [&](int level) { return (uint32_t)(fv.depth - level) << count_bits; };
+  const auto clear = [&](uint32_t bytes) {
+    for (uint32_t i = (uint32_t)t; i < bytes / 16; i += T) reinterpret_cast<uint4*>(s_small)[i] = make_uint4(0, 0, 0, 0);
+  };
+  long long dsum = 0, reached = 0;
+  for (int s = (int)blockIdx.x; s < fv.sources; s += (int)gridDim.x) {
+    double* const coef = fv.coef + (size_t)s * (size_t)S;
+    uint32_t* const exact = fv.exact + (size_t)s * (size_t)S;
+    const int source = fv.source0 + s;
+    int tt = t;
+    asm volatile("" : "+v"(tt));  // addresses are not kept from source to source
+    const int v0 = 4 * words * tt;  // this thread's nodes in the sort
+    uint32_t lv[kStripWords];
+    const unsigned char* const level = fv.level + (size_t)s * (size_t)nl;
+#pragma unroll
+    for (int k = 0; k < kStripWords; k += 4) {
+      const int v = v0 + 4 * k;
+      Int4 four = {-1, -1, -1, -1};
+      if (k < words && v + 16 <= nl) {
+        four = *reinterpret_cast<const Int4*>(level + v);
+      } else if (k < words) {
+        if (v < nl) four.x = *reinterpret_cast<const int*>(level + v);
+        if (v + 4 < nl) four.y = *reinterpret_cast<const int*>(level + v + 4);
+        if (v + 8 < nl) four.z = *reinterpret_cast<const int*>(level + v + 8);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        lv[k + i] = (uint32_t)four[i];
+        const int u = v + 4 * i;
+        if (u < N && u + 4 > N) lv[k + i] |= ~0u << ((N - u) * 8);  // places past the last node: out of reach
+      }
+    }
+    __syncthreads();
+    int v1 = v0;
+    asm volatile("" : "+v"(v1));
+    // (those on no level have the last place: there is the source too, so that no other node has it)
+    const auto place = [&](uint32_t p, int i) { x[min(p, (uint32_t)N - 1u)] = (unsigned short)(v1 + i); };
+    const int levels = strip_levels(fv.depth);
+    const int starts = levels == 8    ? flow_sort<8>(lv, words, s_totals, base, N - 1, wave, lane, place)
+                       : levels == 12 ? flow_sort<12>(lv, words, s_totals, base, N - 1, wave, lane, place)
+                                      : flow_sort<16>(lv, words, s_totals, base, N - 1, wave, lane, place);
+    if (t % strips.threads == 0 && t / strips.threads < strips.count)
+      for (int l = 0; l < levels; ++l) s_strip[t / strips.threads * 16 + l] = base[l * T + t];
+    if (t == 0) *s_escaped = 0;
+    const auto start = [&](int l) { return __builtin_amdgcn_readlane(starts, l & (kWave - 1)); };  // of a level
+    const int after = __shfl_down(starts, 1, kWave);
+    const uint64_t filled = __ballot(lane >= 1 && lane <= fv.depth && after > starts);
+    const int deep = filled != 0 ? 63 - __builtin_clzll(filled) : 0;
+    const int total = __builtin_amdgcn_readlane(starts, kWave - 1);
+    const uint32_t last = (uint32_t)max(total - 1, 0);
+    if (wave == 0) {
+      reached += lane >= 1 && lane <= deep ? after - starts : 0;
+      dsum += lane >= 1 && lane <= deep ? (long long)lane * (after - starts) : 0;
+    }
+    strip_barrier();
+    for (int i = t; i < S / 8; i += T) reinterpret_cast<uint4*>(queue)[i] = reinterpret_cast<const uint4*>(x)[i];
+    strip_barrier();
+    clear(2u * (uint32_t)S);
+    strip_barrier();
+    if (t == 0) {
+      x[source] = (unsigned short)(above(0) + 1u);
+      coef[source] = 0.0;
+    }
+    __syncthreads();
+
+    bool escaped = false;
+    if (deep > 0) {  // forward: nodes are asked for four pieces ahead, links two
+      FlowPiece<1> a, b, e;
+      a.enter(1, starts);
+      b = a;
+      b.next(starts);
+      e = a;
+      const auto ask = [&](uint32_t& node) {
+        node = lds_at(queue, 2u * min((uint32_t)(e.base + tt), last));
+        e.next(starts);
+      };
+      uint32_t node[6];
+      Row row[3];
+      const auto step = [&](auto step_number) {
+        constexpr int i = decltype(step_number)::value;
+        if (a.level > deep) return;
+        const Row& here = row[i % 3];
+        const uint32_t own = node[i];
+        flow_arrived(here);
+        row[(i + 2) % 3].load(fv.in, node[(i + 2) % 6]);
+        flow_in_order();
+        ask(node[(i + 4) % 6]);
+        flow_in_order();
+        if (tt < a.end - a.base) {
+          uint32_t y[2 * KS];
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<unsigned short>(here.template at<1>(j));
+          __builtin_amdgcn_sched_barrier(0);
+          const uint32_t before = above(a.level - 1);
+          uint32_t sum = 0;
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) sum += y[j] = flow_count(y[j], before);
+          if (sum >= count_most) {
+            sum = 0;
+#pragma unroll
+            for (int j = 0; j < 2 * KS; ++j) sum += y[j] == count_most ? exact[here.template at<0>(j)] : y[j];
+            if (sum >= count_most) {
+              exact[own] = sum;
+              escaped = true;
+            }
+            __builtin_amdgcn_s_waitcnt(0);  // there before the barrier
+          }
+          lds_put<unsigned short>(2 * own, (unsigned short)(min(sum, count_most) + above(a.level)));
+          lds_at(record, 4u * (uint32_t)(a.base + tt)) = own | min(sum, 0xffffu) << 16;
+        }
+        if (b.level != a.level) strip_barrier();
+        a = b;
+        b.next(starts);
+      };
+      ask(node[0]);
+      ask(node[1]);
+      ask(node[2]);
+      ask(node[3]);
+      flow_in_order();
+      row[0].load(fv.in, node[0]);
+      row[1].load(fv.in, node[1]);
+      flow_in_order();
+      while (a.level <= deep) wide_steps(step, std::make_index_sequence<6>{});
+    }
+    if (escaped) *s_escaped = 1;
+    unsigned short* const count = reinterpret_cast<unsigned short*>(fv.count) + (size_t)s * (size_t)S;
+    for (int i = t; i < S / 8; i += T)
+      __builtin_nontemporal_store(reinterpret_cast<const FlowWords*>(x)[i], reinterpret_cast<FlowWords*>(count) + i);
+    if (total < N - 1)  // nodes out of reach have no coef
+      for (int v = t; v < N; v += T)
+        if (x[v] == 0) coef[v] = 0.0;
+
+    // What a node of a level is to its predecessors, without its successors.
+    const auto alone = [&](uint32_t r) {
+      uint32_t n = r >> 16;
+      if (n == 0xffffu) n = exact[r & 0xffffu];
+      return recip((double)n);
+    };
+    const uint32_t bits_at = (uint32_t)strips.bits, before_at = (uint32_t)strips.before;
+    // The coefs of a node's successors on a level of few nodes: which links lead there (bits), then their sum.
+    uint32_t few_at = 0;
+    const auto few_bits = [&](const Row& row, uint32_t (&bits)[2 * KS]) {
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) bits[j] = lds_get<uint32_t>((row.template at<0>(j) >> 3 & 0x1ffcu) + bits_at);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    const auto few_sum = [&](const Row& row, const uint32_t (&bits)[2 * KS]) {
+      uint32_t links = 0;
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) links |= __builtin_amdgcn_ubfe(bits[j], row.template at<0>(j), 1) << j;
+      double sum = 0.0;
+      while (links != 0) {
+        const uint32_t j = (uint32_t)__builtin_ctz(links);
+        links &= links - 1u;
+        uint32_t w = row.w[0];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) w = j >> 1 == (uint32_t)k ? row.w[k] : w;
+        const uint32_t v = w >> (j & 1u) * 16u & 0xffffu;
+        const uint32_t word = lds_get<uint32_t>((v >> 3 & 0x1ffcu) + bits_at), first = lds_get<unsigned short>((v >> 4 & 0xffeu) + before_at);
+        sum += lds_get<double>(8u * (first + (uint32_t)__popc(word & ((1u << (v & 31u)) - 1u))) + few_at);
+      }
+      return sum;
+    };
+    // Pieces of the places first ... end of the queue: f(place, record, successors' coefs from the list).  Records are asked for four
+    // pieces ahead, links two, and the first of them before start().  Places past the end too, with the record of the last.
+    const auto pieces = [&](int first, int end, auto&& start, auto&& f) {
+      uint32_t r[6];
+      Row row[3];
+      int at = first, t1 = tt;
+      asm volatile("" : "+v"(t1));
+      const auto ask = [&](uint32_t& one, int ahead) { one = lds_at(record, 4u * (uint32_t)max(min(at + ahead * T + t1, end - 1), 0)); };
+#pragma unroll
+      for (int k = 0; k < 4; ++k) ask(r[k], k);
+      flow_in_order();
+#pragma unroll
+      for (int k = 0; k < 2; ++k) row[k].load(fv.out, min(r[k] & 0xffffu, (uint32_t)N - 1u));
+      flow_in_order();
+      start();
+      while (at < end)
+        wide_steps([&](auto number) {
+          constexpr int i = decltype(number)::value;
+          if (at >= end) return;
+          row[(i + 2) % 3].load(fv.out, r[(i + 2) % 6] & 0xffffu);
+          flow_in_order();
+          ask(r[(i + 4) % 6], 4);
+          flow_in_order();
+          uint32_t bits[2 * KS];
+          few_bits(row[i % 3], bits);
+          f(at + t1, r[i], few_sum(row[i % 3], bits));
+          flow_in_order();
+          at += T;
+        }, std::make_index_sequence<6>{});
+    };
+    // A level is one of few nodes if there is room for its list behind a strip; if the level before it is one as well, there
+    // is no strip then, and the list may lie in its place.
+    // Makes a level of few nodes what few_sum reads; node and coef of place start(l) + tt + k T in v[k], c[k].
+    constexpr int kFewPieces = kStripFew / T;
+    const auto size = [&](int l) { return start(l + 1) - start(l); };
+    const auto few_on = [&](int l) { return size(l) <= (size(l - 1) <= strips.most ? kStripFew : strips.most); };
+    const auto list = [&](int l, const uint32_t (&v)[kFewPieces], const double (&c)[kFewPieces]) {
+      const int first = start(l), end = start(l + 1);
+      few_at = size(l) <= strips.most ? (uint32_t)strips.few : 0u;
+      uint32_t previous[kFewPieces];
+#pragma unroll
+      for (int k = 0; k < kFewPieces; ++k) previous[k] = lds_at(queue, 2u * (uint32_t)min(max(first + k * T + tt - 1, first), end - 1));
+      strip_barrier();
+      for (uint32_t i = (uint32_t)tt; i < (before_at - bits_at) / 16; i += T) lds_put<FlowWords>(16u * i + bits_at, FlowWords{0, 0, 0, 0});
+      strip_barrier();
+#pragma unroll
+      for (int k = 0; k < kFewPieces; ++k) {
+        const int i = first + k * T + tt;
+        if (i < end) {
+          lds_put<double>(8u * (uint32_t)(i - first) + few_at, c[k]);
+          __hip_atomic_fetch_or(&lds_at(reinterpret_cast<uint32_t*>(s_small), (v[k] >> 3 & 0x1ffcu) + bits_at), 1u << (v[k] & 31u), __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (i == first || previous[k] >> 5 != v[k] >> 5) lds_put<unsigned short>((v[k] >> 4 & 0xffeu) + before_at, (unsigned short)(i - first));
+        }
+      }
+      strip_barrier();
+    };
+    // Where the coefs of the level behind the present one are: in the list (or there is no such level); still to be worked out, from
+    // the list or without successors; in memory.
+    enum { kListed, kOpen, kStored };
+    int behind = kListed;
+    for (int l = deep; l >= 1; --l) {
+      const int from = start(l), to = start(l + 1), next = start(l + 2);
+      const bool few = few_on(l);
+      if (behind == kListed) {
+        if (!few) {
+          behind = kOpen;
+          continue;
+        }
+        uint32_t v[kFewPieces];
+        double c[kFewPieces];
+#pragma unroll
+        for (int k = 0; k < kFewPieces; ++k) {
+          v[k] = 0;
+          c[k] = 0.0;
+          const int i = from + k * T + tt;
+          if (i < to) {
+            const uint32_t r = lds_at(record, 4u * (uint32_t)i);
+            v[k] = r & 0xffffu;
+            Row row;
+            if (l < deep) row.load(fv.out, v[k]);
+            c[k] = alone(r);
+            if (l < deep) {
+              uint32_t bits[2 * KS];
+              few_bits(row, bits);
+              c[k] += few_sum(row, bits);
+            }
+            lds_at(coef, 8u * v[k]) = c[k];
+          }
+        }
+        if (l > 1) list(l, v, c);
+        continue;
+      }
+      for (int b = from; b < to; b += kPieces * T) {
+        const int here = to - b;
+        double sum[kPieces];
+#pragma unroll
+        for (int k = 0; k < kPieces; ++k) sum[k] = 0.0;
+        uint32_t node_first[4];  // the same for every strip
+        Row row_first[2];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) node_first[k] = lds_at(queue, 2u * (uint32_t)min(b + k * T + tt, to - 1));
+        flow_in_order();
+        row_first[0].load(fv.out, node_first[0]);
+        row_first[1].load(fv.out, node_first[1]);
+        flow_in_order();
+        for (int h = 0; h < strips.count; ++h) {
+          const uint32_t v_first = (uint32_t)(h * strips.nodes);
+          const int first = h == 0 ? to : __builtin_amdgcn_readfirstlane(s_strip[h * 16 + l]);
+          const int end = h + 1 == strips.count ? next : __builtin_amdgcn_readfirstlane(s_strip[(h + 1) * 16 + l]);
+          const auto put = [&](uint32_t v, double c) { lds_put<double>(8u * (v - v_first), c); };
+          const auto room = [&] {
+            strip_barrier();
+            clear(8u * (uint32_t)strips.nodes + 16u);
+            strip_barrier();
+          };
+          if (behind == kOpen && b == from) {
+            if (l + 1 == deep) {
+              constexpr int kAtOnce = 8;
+              uint32_t r[kAtOnce];
+              const auto records = [&](int i) {
+#pragma unroll
+                for (int k = 0; k < kAtOnce; ++k) r[k] = lds_at(record, 4u * (uint32_t)max(min(i + k * T, end - 1), 0));
+                flow_in_order();
+              };
+              records(first + tt);
+              room();
+              for (int i = first + tt; i < end;) {
+#pragma unroll
+                for (int k = 0; k < kAtOnce; ++k)
+                  if (i + k * T < end) {
+                    const uint32_t v = r[k] & 0xffffu;
+                    const double c = alone(r[k]);
+                    lds_at(coef, 8u * v) = c;
+                    put(v, c);
+                  }
+                i += kAtOnce * T;
+                if (i < end) records(i);
+              }
+            } else {
+              pieces(first, end, room, [&](int i, uint32_t r, double succ) {
+                if (i < end) {
+                  const uint32_t v = r & 0xffffu;
+                  const double c = alone(r) + succ;
+                  lds_at(coef, 8u * v) = c;
+                  put(v, c);
+                }
+              });
+            }
+          } else {
+            constexpr int kAtOnce = 12;
+            uint32_t v[kAtOnce];
+            const auto nodes = [&](int i) {
+#pragma unroll
+              for (int k = 0; k < kAtOnce; ++k) v[k] = lds_at(queue, 2u * (uint32_t)max(min(i + k * T, end - 1), 0));
+            };
+            nodes(first + tt);
+            if (h == 0) __syncthreads();  // coefs are in memory
+            room();
+            for (int i = first + tt; i < end;) {
+              double c[kAtOnce];
+#pragma unroll
+              for (int k = 0; k < kAtOnce; ++k) c[k] = lds_at(coef, 8u * v[k]);
+#pragma unroll
+              for (int k = 0; k < kAtOnce; ++k)
+                if (i + k * T < end) put(v[k], c[k]);
+              i += kAtOnce * T;
+              if (i < end) nodes(i);
+            }
+          }
+          strip_barrier();
+          // the block's nodes, asked for four pieces ahead, their links two
+          const uint32_t zero = 8u * (uint32_t)strips.nodes, less = 0u - 8u * v_first;
+          uint32_t node[6];
+          Row row[3];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) node[k] = node_first[k];
+          row[0] = row_first[0];
+          row[1] = row_first[1];
+          int t1 = tt;
+          asm volatile("" : "+v"(t1));  // addresses are not kept from strip to strip
+          wide_steps([&](auto number) {
+            constexpr int k = decltype(number)::value;
+            if (k * T >= here) return;
+            if constexpr (k + 2 < kPieces) row[(k + 2) % 3].load(fv.out, node[(k + 2) % 6]);
+            flow_in_order();
+            if constexpr (k + 4 < kPieces) node[(k + 4) % 6] = lds_at(queue, 2u * (uint32_t)min(b + (k + 4) * T + t1, to - 1));
+            flow_in_order();
+            double y[2 * KS];
+#pragma unroll
+            for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<double>(min(row[k % 3].strip_at(j, less), zero));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < 2 * KS; ++j) sum[k] += y[j];
+            asm volatile("" : "+v"(sum[k]));
+            flow_in_order();
+          }, std::make_index_sequence<kPieces>{});
+        }
+        uint32_t few_v[kFewPieces];
+        double few_c[kFewPieces];
+        constexpr int kAtOnce = kPieces % 12 == 0 ? 12 : 8;
+        static_assert(kPieces % kAtOnce == 0 && kFewPieces <= kPieces);
+        wide_steps([&](auto number) {
+          constexpr int k0 = decltype(number)::value * kAtOnce;
+          if (k0 * T >= here) return;
+          uint32_t r[kAtOnce];
+#pragma unroll
+          for (int k = 0; k < kAtOnce; ++k) r[k] = lds_at(record, 4u * (uint32_t)min(b + (k0 + k) * T + tt, to - 1));
+          flow_in_order();
+#pragma unroll
+          for (int k = 0; k < kAtOnce; ++k) {
+            double c = sum[k0 + k];
+            if (b + (k0 + k) * T + tt < to) {
+              const uint32_t v = r[k] & 0xffffu;
+              c += alone(r[k]);
+              lds_at(coef, 8u * v) = c;
+            }
+            if (k0 + k < kFewPieces) {
+              few_v[k0 + k < kFewPieces ? k0 + k : 0] = r[k] & 0xffffu;
+              few_c[k0 + k < kFewPieces ? k0 + k : 0] = c;
+            }
+          }
+          flow_in_order();
+        }, std::make_index_sequence<kPieces / kAtOnce>{});
+        if (few && l > 1) list(l, few_v, few_c);
+      }
+      behind = few ? kListed : kStored;
+    }
+    __syncthreads();
+    if (t == 0) fv.escaped[s] = *s_escaped;
+  }
+  __syncthreads();
+  SmallView sv{};
+  sv.counters = fv.counters;
+  small_totals(sv, s_small, dsum, reached, false, 0.0, false);
+}
+
 // coef[s][v] = demand of node v from source s: tiles of 64 x 64.
 static __global__ void __launch_bounds__(kBlock)
 k_flow_demand(FlowView fv, const double* __restrict__ dem, long long ld) {
@@ -484,7 +931,7 @@ k_flow_demand(FlowView fv, const double* __restrict__ dem, long long ld) {
 // source, in source order, in registers.  A thread has kPairs pairs of adjacent nodes.  A source's path counts are brought into
 // LDS while the last one's are worked on.  The blocks of a group read the same path counts: they go to the same XCD, one after
 // the other.  Bound by memory where nodes have few links (16384 nodes of degree 4: 3.3 GB in 0.59 ms), else by LDS and the vector ALUs.
-template <int KS, bool kScaled, bool kDemand>
+template <int KS, bool kScaled, bool kDemand, bool kHalves = false>
 __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
   constexpr int kPairs = flow_nodes(KS) / 2, kXcds = 8;
   extern __shared__ double s_small[];
@@ -494,10 +941,14 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
   const int group = place / blocks * kXcds + (int)blockIdx.x % kXcds, v0 = place % blocks * (2 * kPairs * kWideThreads) + 2 * t;
   if (group >= fv.groups) return;
   const int s_first = group * fv.group, s_last = min(fv.sources, s_first + fv.group);
-  const uint32_t buffer = (uint32_t)fv.stride * 4u;  // bytes of one of the two
+  using Word = std::conditional_t<kHalves, unsigned short, uint32_t>;
+  constexpr int kSize = kHalves ? 1 : 2;
+  const int count_bits = kHalves ? strip_count_bits(fv.depth) : kFlowLevel;
+  const bool single = kHalves && strip_links_single(N);
+  const uint32_t row_bytes = (uint32_t)fv.stride << kSize, buffer = single ? 0u : row_bytes;  // of a source; to the other one's
   const int lane = lane_id();
   const auto stage = [&](int s, uint32_t at) {
-    flow_to_lds(fv.count + (size_t)s * (size_t)fv.stride, &lds_at(s_small, at), fv.stride / 4, wave, lane);
+    flow_to_lds(reinterpret_cast<const char*>(fv.count) + (size_t)s * row_bytes, &lds_at(s_small, at), (int)row_bytes / 16, wave, lane);
   };
   FlowRow<KS, kScaled> link[kPairs][2];
   double acc[kPairs][2][2 * KS];
@@ -526,7 +977,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
     double2 pair[kPairs];
   };
   const auto request = [&](int s, uint32_t at, Coefs& c) {
-    stage(s, at);
+    if (!single) stage(s, at);
 #pragma unroll
     for (int k = 0; k < kPairs; ++k)
       c.pair[k] = *reinterpret_cast<const double2*>(fv.coef + (size_t)s * (size_t)fv.stride + (size_t)pair(k));
@@ -540,24 +991,31 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
   const auto step = [&](int s, uint32_t here, const Coefs& c, Coefs& next) {
     __builtin_amdgcn_s_waitcnt(0);  // what was asked for a step ago has arrived
     __syncthreads();
+    const int escaped = kHalves ? fv.escaped[s] : 0;
+    const uint32_t* const exact = fv.exact + (kHalves ? (size_t)s * (size_t)fv.stride : 0);
     if (s + 1 < s_last) request(s + 1, buffer - here, next);
     const auto gather = [&](int u, Got& g) {
       const int k = u / 2, i = u % 2;
 #pragma unroll
       for (int j = 0; j < KS; ++j) asm volatile("" : "+v"(link[k][i].w[j]));  // no addresses kept from source to source
-      g.own = lds_get<uint32_t>(here + 4u * (uint32_t)(pair(k) + i));
+      g.own = lds_get<Word>(here + ((uint32_t)(pair(k) + i) << kSize));
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) g.y[j] = lds_get<uint32_t>(link[k][i].template at<2>(j) + here);
+      for (int j = 0; j < 2 * KS; ++j) g.y[j] = lds_get<Word>(link[k][i].template at<kSize>(j) + here);
     };
     const auto add = [&](int u, const Got& g) {
       const int k = u / 2, i = u % 2;
-      const uint32_t before = (g.own & ~((1u << kFlowLevel) - 1u)) + (1u << kFlowLevel);
+      const uint32_t before = (g.own & ~((1u << count_bits) - 1u)) + (1u << count_bits);
       const double f = i == 0 ? c.pair[k].x : c.pair[k].y;
+      uint32_t n[2 * KS];
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) {
-        const uint32_t n = flow_count(g.y[j], before);
-        acc[k][i][j] = __builtin_fma(kDemand && n == 0 ? 0.0 : f, (double)n, acc[k][i][j]);
+      for (int j = 0; j < 2 * KS; ++j) n[j] = flow_count(g.y[j], before);
+      if (kHalves && escaped != 0) {
+#pragma unroll
+        for (int j = 0; j < 2 * KS; ++j)
+          if (n[j] == (1u << count_bits) - 1u) n[j] = exact[link[k][i].template at<0>(j)];
       }
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) acc[k][i][j] = __builtin_fma(kDemand && n[j] == 0 ? 0.0 : f, (double)n[j], acc[k][i][j]);
 #pragma unroll
       for (int j = 0; j < 2 * KS; ++j) asm volatile("" : "+v"(acc[k][i][j]));  // here and now: put off, the sums would hold on to what was gathered
     };
@@ -570,9 +1028,14 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
       add(u, g[u % 2]);
       __builtin_amdgcn_sched_barrier(0);
     }
+    if (single) {
+      __syncthreads();
+      if (s + 1 < s_last) stage(s + 1, 0);
+    }
   };
   if (s_first < s_last) {
     Coefs c0, c1;
+    if (single) stage(s_first, 0);
     request(s_first, 0, c0);
     for (int s = s_first;;) {
       step(s, 0, c0, c1);
@@ -685,8 +1148,8 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sssp(SmallView sv, SmallS
     };
     if (apart) clear();
     const auto place = [&](uint32_t p, int i) { q[p] = (uint32_t)(v1 + i); };
-    const int starts = sv.depth <= 8 ? flow_sort<1>(lv, words, s_totals, base, S, wave, lane, place)
-                                     : flow_sort<2>(lv, words, s_totals, base, S, wave, lane, place);
+    const int starts = sv.depth <= 8 ? flow_sort<8>(lv, words, s_totals, base, S, wave, lane, place)
+                                     : flow_sort<16>(lv, words, s_totals, base, S, wave, lane, place);
     const int after = __shfl_down(starts, 1, kWave);
     const uint64_t filled = __ballot(lane >= 1 && lane <= sv.depth && after > starts);
     const int deep = filled != 0 ? 63 - __builtin_clzll(filled) : 0;

@@ -42,6 +42,9 @@ void launch_wide_sigma(const WideSigma& ws, int workgroups, hipStream_t st);
 template <int KS>
 void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStream_t st);
 template <int KS>
+void launch_strip_sources(const FlowView& fv, int workgroups, hipStream_t st);
+// fv.exact: null after launch_flow_sources.  (With demands only after that.)
+template <int KS>
 void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st);
 
 // f(KS), a constant, for a table of that many words a node.

@@ -284,6 +284,52 @@ constexpr bool flow_sssp_fits(int N, int depth, int src_count) {
          (long long)depth * src_count * (N - 1) < 0x7fffffffll && flow_sssp_lds(N, depth) <= kSmallLds;
 }
 
+// More nodes than that, by strips of nodes (k_strip_sources).  LDS, one after the other: queue and positions of the sort; 16-bit words
+// of all nodes; coefs of a level, of one strip of nodes at a time, and of a level of few nodes (StripCut).  Behind all that sums of the
+// waves and where strips start in the levels.
+constexpr int kStripWords = 16;  // of level bytes a thread sorts: 65536 nodes
+constexpr int kStripFewestSources = 2048;
+constexpr int kStripDeepest = 15, kStripMost = 4;
+constexpr size_t kStripState = kSmallLds;
+constexpr size_t kStripTail = kSmallThreads / kSmallWave * 8 * 4 + kStripMost * 16 * 4 + 16;
+constexpr int strip_levels(int depth) { return depth <= 8 ? 8 : depth <= 12 ? 12 : 16; }
+constexpr size_t strip_sort_bytes(int N, int depth) { return (size_t)flow_stride(N) * 2 + (strip_levels(depth) + 1) * 2 * kSmallThreads; }
+// Bits of a word that count paths; those above are the levels up to the deepest, counted down.  All ones: the count is elsewhere.
+constexpr int strip_count_bits(int depth) { return depth < 8 ? 13 : 12; }
+// Strips of whole threads of the sort.  LDS of the backward sweep: a double per node of a strip and a 0 behind them; a level of few nodes
+// as a bit per node, the level's nodes before each word of bits, and a double for each of the level's nodes.
+constexpr int kStripFew = 4096, kStripFewLeast = 2048;  // most of those; at least
+struct StripCut {
+  int count, threads, nodes;  // strips; of a strip
+  int bits, before, few;      // places in LDS
+  int most;                   // nodes of a level of few
+};
+constexpr StripCut strip_cut(int N) {
+  const int words = (N + 4 * kSmallThreads - 1) / (4 * kSmallThreads), used = (N + 4 * words - 1) / (4 * words);
+  const int bit_words = (N + 127) / 128 * 4;
+  StripCut c{};
+  for (c.count = 1;; ++c.count) {
+    c.threads = (used + c.count - 1) / c.count;
+    c.nodes = c.threads * 4 * words;
+    c.bits = c.nodes * 8 + 16;
+    c.before = c.bits + bit_words * 4;
+    c.few = c.before + bit_words * 2;
+    const int room = ((int)kStripState - c.few) / 8;
+    c.most = room < kStripFew ? room : kStripFew;
+    if (c.most >= kStripFewLeast) return c;
+  }
+}
+constexpr bool strip_lds_fits(int N, int depth) {
+  return N <= kStripWords * 4 * kSmallThreads && depth <= kStripDeepest && strip_sort_bytes(N, depth) <= kStripState &&
+         strip_cut(N).count <= kStripMost;
+}
+static_assert(kStripState + kStripTail <= 160 * 1024 && strip_lds_fits(65536, 12));
+// Of k_flow_links: two sources' words, or those of one where there is no more room.
+constexpr bool strip_links_single(int N) { return (size_t)flow_stride(N) * 4 > kSmallLds; }
+constexpr size_t strip_link_lds(int N) { return (size_t)flow_stride(N) * (strip_links_single(N) ? 2 : 4); }
+// A workgroup's queue: nodes of 16 bits, then nodes with their path counts, 32 bits.
+constexpr size_t strip_record_bytes(int stride) { return (size_t)stride * 6; }
+
 // A workgroup's records between the two sweeps: a path count, or 8 bytes with demands, and a 16-bit node per place.
 constexpr size_t flow_record_bytes(int stride, bool demand) { return (size_t)stride * (demand ? 10 : 6); }
 
@@ -306,8 +352,9 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count) {
 struct FlowLayout {
   int rows = 0, parts = 0;
   size_t counters = 0, weighted = 0, record = 0, part = 0, level = 0, count = 0, coef = 0, total = 0;
+  size_t escaped = 0, exact = 0;  // by strips only
 };
-inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool demand, int rows, int parts) {
+inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool demand, int rows, int parts, bool strips = false) {
   FlowLayout l;
   l.rows = rows;
   l.parts = parts;
@@ -320,15 +367,19 @@ inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool dema
   const size_t stride = (size_t)flow_stride(N);
   l.counters = take((size_t)kComputeUnits * kSmallCounters * 8);
   l.weighted = take((size_t)src_count * 8);
-  l.record = take((size_t)std::min(rows, kComputeUnits) * flow_record_bytes((int)stride, demand));
+  l.record = take((size_t)std::min(rows, kComputeUnits) * (strips ? strip_record_bytes((int)stride) : flow_record_bytes((int)stride, demand)));
   l.part = take((size_t)parts * N * ell_words * 2 * 8);
   l.level = take((size_t)rows * small_level_bytes(N));
-  l.count = take((size_t)rows * stride * 4);
+  if (strips) {
+    l.escaped = take((size_t)rows * 4);
+    l.exact = take((size_t)rows * stride * 4);
+  }
+  l.count = take((size_t)rows * stride * (strips ? 2 : 4));
   l.coef = take((size_t)rows * stride * 8);
   l.total = off;
   return l;
 }
-inline FlowLayout flow_layout(int N, int ell_words, int src_count, bool demand, size_t bytes) {
+inline FlowLayout flow_layout(int N, int ell_words, int src_count, bool demand, size_t bytes, bool strips = false) {
   const FlowGroups g = flow_groups(N, ell_words, src_count);
   const auto most = [bytes](int hi, auto&& at) {  // largest k in 0..hi with at(k) that fits
     int lo = 0;
@@ -341,8 +392,8 @@ inline FlowLayout flow_layout(int N, int ell_words, int src_count, bool demand, 
     }
     return lo;
   };
-  const auto groups = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, std::min(k * g.group, src_count), k); };
-  const auto rows = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, k, 1); };
+  const auto groups = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, std::min(k * g.group, src_count), k, strips); };
+  const auto rows = [&](int k) { return flow_layout_for(N, ell_words, src_count, demand, k, 1, strips); };
   const int k = most(g.groups, groups);
   return k > 0 ? groups(k) : rows(most(g.group, rows));
 }

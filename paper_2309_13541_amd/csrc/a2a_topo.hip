@@ -1023,17 +1023,32 @@ bool flow_fits(const a2a_topo* t, int32_t src_count, bool demand) {
          flow_layout_for(t->N, t->ell_words, src_count, demand, kSmallBatch, 1).total <= t->min_loads_bytes;
 }
 
-int flow_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
+// The same for unit demands of topologies of more nodes, by strips (k_strip_sources): path counts of all levels below 2^32.  ms of
+// level kernels and of this, all sources and 2048 of them: random topologies, 20353 nodes of degree 6 9.49, 6.87; 1.09, 0.79; 30000 of degree 4
+// 20.7, 13.2; 1.60, 1.08; 45000 of degree 3 (13 levels) 59.6, 37.3; 3.02, 1.98; 65536 of degree 8 106.3, 80.2; 3.58, 2.80; generalized Kautz
+// topologies, 40000 of degree 5 24.6, 19.2; 1.42, 1.11; 65535 of degree 3 76.5, 69.1.  With demands it is not the faster one
+// everywhere (16384 nodes of degree 4 5.23, 5.82; 32768 of degree 3 33.2, 28.8).  Fewer sources stay with the level kernels,
+// whose results the tests hold bit for bit.
+bool strips_fit(const a2a_topo* t, int32_t src_count) {
+  const double bits = (double)t->level_bound * std::log2((double)std::max(t->dmax_in, 2));
+  return t->ell_words > 0 && t->N > kFlowNodes && src_count >= kStripFewestSources && t->level_bound >= 1 && bits < 32.0 &&
+         strip_lds_fits(t->N, t->level_bound) &&
+         flow_layout_for(t->N, t->ell_words, src_count, false, kSmallBatch, 1, true).total <= t->min_loads_bytes;
+}
+
+int flow_link_loads(const a2a_topo* t, bool strips, int32_t src_begin, int32_t src_count, const double* demand, double* load,
                     double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
   if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
   const FlowGroups g = flow_groups(t->N, t->ell_words, src_count);
-  const FlowLayout l = flow_layout(t->N, t->ell_words, src_count, demand != nullptr, ws_bytes);
+  const FlowLayout l = flow_layout(t->N, t->ell_words, src_count, demand != nullptr, ws_bytes, strips);
   FlowView fv{};
   fv.in = t->d_ell_in;
   fv.out = t->d_ell_out;
   fv.level = (unsigned char*)(ws + l.level);
   fv.record = ws + l.record;
   fv.count = (uint32_t*)(ws + l.count);
+  fv.exact = strips ? (uint32_t*)(ws + l.exact) : nullptr;
+  fv.escaped = (int*)(ws + l.escaped);
   fv.coef = (double*)(ws + l.coef);
   fv.counters = (long long*)(ws + l.counters);
   fv.part = (double*)(ws + l.part);
@@ -1078,7 +1093,10 @@ int flow_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, con
         const unsigned tiles = (unsigned)((t->N + kWave - 1) / kWave) * (unsigned)((piece + kWave - 1) / kWave);
         k_flow_demand<<<tiles, kBlock, 0, st>>>(fv, demand + s0, src_count);
       }
-      by_words(t->ell_words, [&](auto ks) { launch_flow_sources<decltype(ks)::value>(fv, demand != nullptr, workgroups, st); });
+      by_words(t->ell_words, [&](auto ks) {
+        strips ? launch_strip_sources<decltype(ks)::value>(fv, workgroups, st)
+               : launch_flow_sources<decltype(ks)::value>(fv, demand != nullptr, workgroups, st);
+      });
       by_words(t->ell_words, [&](auto ks) { launch_flow_links<decltype(ks)::value>(fv, demand != nullptr, st); });
     }
     const bool last = s0 + piece == src_count;
@@ -1234,7 +1252,7 @@ int a2a_topo_create(int32_t N, const int32_t* row_ptr, const int32_t* col_idx, a
       }
     for (int32_t v = 0; v < N; ++v) t->dmax_in = std::max(t->dmax_in, in_ptr[(size_t)v + 1] - in_ptr[v]);
     t->ell_words = ell_words_for(N, std::max(dmax, t->dmax_in));
-    if (N <= kFlowNodes) ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
+    ell_out = make_ell(N, row_ptr, col_idx, t->ell_words, N);
     ell_in = make_ell(N, in_ptr.data(), in_col.data(), t->ell_words,
                       N <= kPaddedRows ? N : align_up((size_t)N, 2 * kWideThreads));
   } catch (const std::bad_alloc&) {
@@ -1421,8 +1439,9 @@ int link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const do
     if (rc != A2A_OK) return rc;
     return profile_levels(t, src_begin, src_count, demand, A2A_WS_LOADS, (char*)workspace, workspace_bytes, st);
   }
-  if (flow_fits(t, src_count, demand != nullptr) && !t->level_kernels_only()) {
-    rc = flow_link_loads(t, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags, (char*)workspace,
+  const bool whole = flow_fits(t, src_count, demand != nullptr);
+  if ((whole || (demand == nullptr && strips_fit(t, src_count))) && !t->level_kernels_only()) {
+    rc = flow_link_loads(t, !whole, src_begin, src_count, demand, load, weighted_dist, dist_sum_total, flags, (char*)workspace,
                          workspace_bytes, st);
     if (rc != A2A_OK) return rc;
     return profile_levels(t, src_begin, src_count, demand, A2A_WS_LOADS, (char*)workspace, workspace_bytes, st);

@@ -147,11 +147,18 @@ void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStr
 }
 
 template <int KS>
+void launch_strip_sources(const FlowView& fv, int workgroups, hipStream_t st) {
+  k_strip_sources<KS><<<workgroups, kWideThreads, kStripState + kStripTail, st>>>(fv);
+}
+
+template <int KS>
 void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st) {
   const int blocks = (fv.N + flow_nodes(KS) * kWideThreads - 1) / (flow_nodes(KS) * kWideThreads);
   const unsigned workgroups = (unsigned)((fv.groups + 7) / 8 * 8 * blocks);
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, flow_link_lds(fv.N), st>>>(fv); };
-  if (fv.N <= kScaledNodes)
+  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, fv.exact != nullptr ? strip_link_lds(fv.N) : flow_link_lds(fv.N), st>>>(fv); };
+  if (fv.exact != nullptr)
+    launch(k_flow_links<KS, false, false, true>);
+  else if (fv.N <= kScaledNodes)
     demand ? launch(k_flow_links<KS, true, true>) : launch(k_flow_links<KS, true, false>);
   else
     demand ? launch(k_flow_links<KS, false, true>) : launch(k_flow_links<KS, false, false>);
@@ -168,6 +175,7 @@ template void launch_wide_search<A2A_WORDS>(const WideView&, int, int, int, hipS
 template void launch_wide_masks<A2A_WORDS>(const WideView&, int, int, hipStream_t);
 template void launch_wide_sigma<A2A_WORDS>(const WideSigma&, int, hipStream_t);
 template void launch_flow_sources<A2A_WORDS>(const FlowView&, bool, int, hipStream_t);
+template void launch_strip_sources<A2A_WORDS>(const FlowView&, int, hipStream_t);
 template void launch_flow_links<A2A_WORDS>(const FlowView&, bool, hipStream_t);
 
 }  // namespace a2a_dev

@@ -134,10 +134,11 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kMost], int words, uint3
   uint32_t rank[kMost];  // of a node among the thread's on its level, a byte each
 #pragma unroll
   for (int h = 0; h < kHalves; ++h) count[h] = 0;
-#pragma unroll
-  for (int k = 0; k < kMost; ++k) {
+  // (steps and not loops: of loops that are unrolled late the compiler keeps the arrays as one tuple of registers, which it moves)
+  wide_steps([&](auto word) {
+    constexpr int k = decltype(word)::value;
     rank[k] = 0;
-    if (k >= words) break;
+    if (k >= words) return;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const uint32_t d = level(k, i), shift = d * 8u & 63u;
@@ -146,7 +147,7 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kMost], int words, uint3
 #pragma unroll
       for (int h = 0; h < kHalves; ++h) count[h] += d - 8u * h < 8u ? one : 0ull;
     }
-  }
+  }, std::make_index_sequence<kMost>{});
   // half f of word w of parity p of half h: level 8 h + p + 4 w + 2 f + 1
   uint32_t own[kFields], incl[kFields];
 #pragma unroll
@@ -183,9 +184,9 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kMost], int words, uint3
   }
   if (lane > kLevels) at = (int)sum;
   mine[kLevels * kWideThreads] = (unsigned short)spare;
-#pragma unroll
-  for (int k = 0; k < kMost; ++k) {
-    if (k >= words) break;
+  wide_steps([&](auto word) {
+    constexpr int k = decltype(word)::value;
+    if (k >= words) return;
     asm volatile("" : "+v"(lv[k]), "+v"(rank[k]));  // nothing worked out before the barrier is kept
     uint32_t at_level[4];
 #pragma unroll
@@ -193,7 +194,7 @@ __device__ __forceinline__ int flow_sort(uint32_t (&lv)[kMost], int words, uint3
 #pragma unroll
     for (int i = 0; i < 4; ++i) place(at_level[i] + (rank[k] >> (8 * i) & 255u), 4 * k + i);
     __builtin_amdgcn_sched_barrier(0);
-  }
+  }, std::make_index_sequence<kMost>{});
   return at;
 }
 
@@ -506,7 +507,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
   const auto clear = [&](uint32_t bytes) {
     for (uint32_t i = (uint32_t)t; i < bytes / 16; i += T) reinterpret_cast<uint4*>(s_small)[i] = make_uint4(0, 0, 0, 0);
   };
-  long long dsum = 0, reached = 0;
+  uint32_t reached = 0;  // by lane l of the first wave on level l (at most 256 sources)
   for (int s = (int)blockIdx.x; s < fv.sources; s += (int)gridDim.x) {
     double* const coef = fv.coef + (size_t)s * (size_t)S;
     uint32_t* const exact = fv.exact + (size_t)s * (size_t)S;
@@ -552,10 +553,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
     const int deep = filled != 0 ? 63 - __builtin_clzll(filled) : 0;
     const int total = __builtin_amdgcn_readlane(starts, kWave - 1);
     const uint32_t last = (uint32_t)max(total - 1, 0);
-    if (wave == 0) {
-      reached += lane >= 1 && lane <= deep ? after - starts : 0;
-      dsum += lane >= 1 && lane <= deep ? (long long)lane * (after - starts) : 0;
-    }
+    if (wave == 0) reached += lane >= 1 && lane <= deep ? (uint32_t)(after - starts) : 0u;
     strip_barrier();
     for (int i = t; i < S / 8; i += T) reinterpret_cast<uint4*>(queue)[i] = reinterpret_cast<const uint4*>(x)[i];
     strip_barrier();
@@ -568,27 +566,28 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
     __syncthreads();
 
     bool escaped = false;
-    if (deep > 0) {  // forward: nodes are asked for four pieces ahead, links two
+    if (deep > 0) {  // forward: nodes are asked for a dozen pieces at a time, links two pieces ahead
+      constexpr int kDozen = 12;
       FlowPiece<1> a, b, e;
       a.enter(1, starts);
       b = a;
       b.next(starts);
       e = a;
-      const auto ask = [&](uint32_t& node) {
-        node = lds_at(queue, 2u * min((uint32_t)(e.base + tt), last));
-        e.next(starts);
+      uint32_t node[kDozen], then[kDozen];
+      const auto ask = [&](uint32_t (&to)[kDozen]) {
+        wide_steps([&](auto number) {
+          to[decltype(number)::value] = lds_at(queue, 2u * min((uint32_t)(e.base + tt), last));
+          e.next(starts);
+        }, std::make_index_sequence<kDozen>{});
+        flow_in_order();
       };
-      uint32_t node[6];
       Row row[3];
       const auto step = [&](auto step_number) {
         constexpr int i = decltype(step_number)::value;
-        if (a.level > deep) return;
         const Row& here = row[i % 3];
         const uint32_t own = node[i];
         flow_arrived(here);
-        row[(i + 2) % 3].load(fv.in, node[(i + 2) % 6]);
-        flow_in_order();
-        ask(node[(i + 4) % 6]);
+        row[(i + 2) % 3].load(fv.in, i + 2 < kDozen ? node[i + 2 < kDozen ? i + 2 : 0] : then[i + 2 < kDozen ? 0 : i + 2 - kDozen]);
         flow_in_order();
         if (tt < a.end - a.base) {
           uint32_t y[2 * KS];
@@ -599,11 +598,11 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           uint32_t sum = 0;
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) sum += y[j] = flow_count(y[j], before);
-          if (sum >= count_most) {
+          if (__builtin_expect(sum >= count_most, 0)) {
             sum = 0;
 #pragma unroll
             for (int j = 0; j < 2 * KS; ++j) sum += y[j] == count_most ? exact[here.template at<0>(j)] : y[j];
-            if (sum >= count_most) {
+            if (__builtin_expect(sum >= count_most, 0)) {
               exact[own] = sum;
               escaped = true;
             }
@@ -615,16 +614,17 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
         if (b.level != a.level) strip_barrier();
         a = b;
         b.next(starts);
+        return a.level <= deep;
       };
-      ask(node[0]);
-      ask(node[1]);
-      ask(node[2]);
-      ask(node[3]);
-      flow_in_order();
+      ask(node);
       row[0].load(fv.in, node[0]);
       row[1].load(fv.in, node[1]);
       flow_in_order();
-      while (a.level <= deep) wide_steps(step, std::make_index_sequence<6>{});
+      for (;;) {
+        ask(then);
+        if (!wide_steps_while(step, std::make_index_sequence<kDozen>{})) break;
+        wide_steps([&](auto number) { node[decltype(number)::value] = then[decltype(number)::value]; }, std::make_index_sequence<kDozen>{});
+      }
     }
     if (escaped) *s_escaped = 1;
     unsigned short* const count = reinterpret_cast<unsigned short*>(fv.count) + (size_t)s * (size_t)S;
@@ -645,13 +645,13 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
     uint32_t few_at = 0;
     const auto few_bits = [&](const Row& row, uint32_t (&bits)[2 * KS]) {
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) bits[j] = lds_get<uint32_t>((row.template at<0>(j) >> 3 & 0x1ffcu) + bits_at);
+      for (int j = 0; j < 2 * KS; ++j) bits[j] = lds_get<uint32_t>(__builtin_amdgcn_ubfe(row.w[j >> 1] & 0xffe0ffe0u, (j & 1) * 16 + 3, 13) + bits_at);
       __builtin_amdgcn_sched_barrier(0);
     };
     const auto few_sum = [&](const Row& row, const uint32_t (&bits)[2 * KS]) {
       uint32_t links = 0;
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) links |= __builtin_amdgcn_ubfe(bits[j], row.template at<0>(j), 1) << j;
+      for (int j = 0; j < 2 * KS; ++j) links |= __builtin_amdgcn_ubfe(bits[j], row.w[j >> 1] >> (j & 1) * 16, 1) << j;
       double sum = 0.0;
       while (links != 0) {
         const uint32_t j = (uint32_t)__builtin_ctz(links);
@@ -665,35 +665,40 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
       }
       return sum;
     };
-    // Pieces of the places first ... end of the queue: f(place, record, successors' coefs from the list).  Records are asked for four
-    // pieces ahead, links two, and the first of them before start().  Places past the end too, with the record of the last.
+    // Pieces of the places first ... end of the queue: f(place, record, successors' coefs from the list).  Records are asked for a
+    // dozen pieces at a time, links two pieces ahead, and the first of them before start().  Places past the end too, with the
+    // record of the last.
     const auto pieces = [&](int first, int end, auto&& start, auto&& f) {
-      uint32_t r[6];
+      constexpr int kDozen = 12;
+      uint32_t r[kDozen];
       Row row[3];
-      int at = first, t1 = tt;
+      int t1 = tt;
       asm volatile("" : "+v"(t1));
-      const auto ask = [&](uint32_t& one, int ahead) { one = lds_at(record, 4u * (uint32_t)max(min(at + ahead * T + t1, end - 1), 0)); };
+      const auto ask = [&](int at) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) ask(r[k], k);
-      flow_in_order();
+        for (int k = 0; k < kDozen; ++k) r[k] = lds_at(record, 4u * (uint32_t)max(min(at + k * T + t1, end - 1), 0));
+        flow_in_order();
 #pragma unroll
-      for (int k = 0; k < 2; ++k) row[k].load(fv.out, min(r[k] & 0xffffu, (uint32_t)N - 1u));
-      flow_in_order();
+        for (int k = 0; k < 2; ++k) row[k].load(fv.out, min(r[k] & 0xffffu, (uint32_t)N - 1u));
+        flow_in_order();
+      };
+      ask(first);
       start();
-      while (at < end)
-        wide_steps([&](auto number) {
+      for (int at = first; at < end;) {
+        const bool more = wide_steps_while([&](auto number) {
           constexpr int i = decltype(number)::value;
-          if (at >= end) return;
-          row[(i + 2) % 3].load(fv.out, r[(i + 2) % 6] & 0xffffu);
-          flow_in_order();
-          ask(r[(i + 4) % 6], 4);
+          if constexpr (i + 2 < kDozen) row[(i + 2) % 3].load(fv.out, r[i + 2] & 0xffffu);
           flow_in_order();
           uint32_t bits[2 * KS];
           few_bits(row[i % 3], bits);
-          f(at + t1, r[i], few_sum(row[i % 3], bits));
+          f(at + i * T + t1, r[i], few_sum(row[i % 3], bits));
           flow_in_order();
-          at += T;
-        }, std::make_index_sequence<6>{});
+          return at + (i + 1) * T < end;
+        }, std::make_index_sequence<kDozen>{});
+        if (!more) break;
+        at += kDozen * T;
+        ask(at);
+      }
     };
     // A level is one of few nodes if there is room for its list behind a strip; if the level before it is one as well, there
     // is no strip then, and the list may lie in its place.
@@ -760,9 +765,6 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
       }
       for (int b = from; b < to; b += kPieces * T) {
         const int here = to - b;
-        double sum[kPieces];
-#pragma unroll
-        for (int k = 0; k < kPieces; ++k) sum[k] = 0.0;
         uint32_t node_first[4];  // the same for every strip
         Row row_first[2];
 #pragma unroll
@@ -771,6 +773,8 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
         row_first[0].load(fv.out, node_first[0]);
         row_first[1].load(fv.out, node_first[1]);
         flow_in_order();
+        double sum[kPieces];
+        wide_steps([&](auto number) { sum[decltype(number)::value] = 0.0; }, std::make_index_sequence<kPieces>{});
         for (int h = 0; h < strips.count; ++h) {
           const uint32_t v_first = (uint32_t)(h * strips.nodes);
           const int first = h == 0 ? to : __builtin_amdgcn_readfirstlane(s_strip[h * 16 + l]);
@@ -835,9 +839,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
               if (i < end) nodes(i);
             }
           }
-          strip_barrier();
           // the block's nodes, asked for four pieces ahead, their links two
-          const uint32_t zero = 8u * (uint32_t)strips.nodes, less = 0u - 8u * v_first;
           uint32_t node[6];
           Row row[3];
 #pragma unroll
@@ -846,9 +848,10 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           row[1] = row_first[1];
           int t1 = tt;
           asm volatile("" : "+v"(t1));  // addresses are not kept from strip to strip
-          wide_steps([&](auto number) {
+          strip_barrier();
+          const uint32_t zero = 8u * (uint32_t)strips.nodes, less = 0u - 8u * v_first;
+          wide_steps_while([&](auto number) {
             constexpr int k = decltype(number)::value;
-            if (k * T >= here) return;
             if constexpr (k + 2 < kPieces) row[(k + 2) % 3].load(fv.out, node[(k + 2) % 6]);
             flow_in_order();
             if constexpr (k + 4 < kPieces) node[(k + 4) % 6] = lds_at(queue, 2u * (uint32_t)min(b + (k + 4) * T + t1, to - 1));
@@ -861,33 +864,34 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
             for (int j = 0; j < 2 * KS; ++j) sum[k] += y[j];
             asm volatile("" : "+v"(sum[k]));
             flow_in_order();
+            return (k + 1) * T < here;
           }, std::make_index_sequence<kPieces>{});
         }
         uint32_t few_v[kFewPieces];
         double few_c[kFewPieces];
         constexpr int kAtOnce = kPieces % 12 == 0 ? 12 : 8;
         static_assert(kPieces % kAtOnce == 0 && kFewPieces <= kPieces);
-        wide_steps([&](auto number) {
+        wide_steps_while([&](auto number) {
           constexpr int k0 = decltype(number)::value * kAtOnce;
-          if (k0 * T >= here) return;
           uint32_t r[kAtOnce];
-#pragma unroll
-          for (int k = 0; k < kAtOnce; ++k) r[k] = lds_at(record, 4u * (uint32_t)min(b + (k0 + k) * T + tt, to - 1));
+          wide_steps([&](auto n) { constexpr int k = decltype(n)::value; r[k] = lds_at(record, 4u * (uint32_t)min(b + (k0 + k) * T + tt, to - 1)); },
+                     std::make_index_sequence<kAtOnce>{});
           flow_in_order();
-#pragma unroll
-          for (int k = 0; k < kAtOnce; ++k) {
+          wide_steps([&](auto n) {
+            constexpr int k = decltype(n)::value;
             double c = sum[k0 + k];
             if (b + (k0 + k) * T + tt < to) {
               const uint32_t v = r[k] & 0xffffu;
               c += alone(r[k]);
               lds_at(coef, 8u * v) = c;
             }
-            if (k0 + k < kFewPieces) {
-              few_v[k0 + k < kFewPieces ? k0 + k : 0] = r[k] & 0xffffu;
-              few_c[k0 + k < kFewPieces ? k0 + k : 0] = c;
+            if constexpr (k0 + k < kFewPieces) {
+              few_v[k0 + k] = r[k] & 0xffffu;
+              few_c[k0 + k] = c;
             }
-          }
+          }, std::make_index_sequence<kAtOnce>{});
           flow_in_order();
+          return (k0 + kAtOnce) * T < here;
         }, std::make_index_sequence<kPieces / kAtOnce>{});
         if (few && l > 1) list(l, few_v, few_c);
       }
@@ -899,7 +903,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
   __syncthreads();
   SmallView sv{};
   sv.counters = fv.counters;
-  small_totals(sv, s_small, dsum, reached, false, 0.0, false);
+  small_totals(sv, s_small, (long long)lane * reached, reached, false, 0.0, false);
 }
 
 // coef[s][v] = demand of node v from source s: tiles of 64 x 64.

@@ -87,6 +87,12 @@ __device__ __forceinline__ void wide_steps(F&& f, std::index_sequence<I...>) {
   (f(std::integral_constant<int, (int)I>{}), ...);
 }
 
+// The same until one of them is false.
+template <typename F, size_t... I>
+__device__ __forceinline__ bool wide_steps_while(F&& f, std::index_sequence<I...>) {
+  return (f(std::integral_constant<int, (int)I>{}) && ...);
+}
+
 // A workgroup takes groups of W sources, blockIdx.x, + gridDim.x, ...  Search: R_l = what a source reaches within l
 // links; LDS holds R_{l-1} of all nodes, a thread R of its own (every 1024th node) and in a level ORs in the words of
 // the in-neighbours.  Bit k of a distance d counts the l < d with l + 1 divisible by 2^k, so that bit plane k is the

@@ -470,9 +470,6 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   small_totals(sv, s_small, dsum, reached, false, 0.0, false);
 }
 
-// Threads of a workgroup wait for each other and for what they have written to LDS, not for memory.
-__device__ __forceinline__ void strip_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 // What k_flow_sources does, for topologies whose coefs of one source do not fit LDS (up to 65536 nodes).  16-bit words of all nodes do:
 // the levels that occur counted down, above the path count.  A count that does not fit leaves all ones there, and itself
 // in memory (fv.exact), where the few that meet it read it.  So the forward sweep is that of k_flow_sources, with the queue in memory.
@@ -554,11 +551,11 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
     const int total = __builtin_amdgcn_readlane(starts, kWave - 1);
     const uint32_t last = (uint32_t)max(total - 1, 0);
     if (wave == 0) reached += lane >= 1 && lane <= deep ? (uint32_t)(after - starts) : 0u;
-    strip_barrier();
+    lds_barrier();
     for (int i = t; i < S / 8; i += T) reinterpret_cast<uint4*>(queue)[i] = reinterpret_cast<const uint4*>(x)[i];
-    strip_barrier();
+    lds_barrier();
     clear(2u * (uint32_t)S);
-    strip_barrier();
+    lds_barrier();
     if (t == 0) {
       x[source] = (unsigned short)(above(0) + 1u);
       coef[source] = 0.0;
@@ -611,7 +608,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           lds_put<unsigned short>(2 * own, (unsigned short)(min(sum, count_most) + above(a.level)));
           lds_at(record, 4u * (uint32_t)(a.base + tt)) = own | min(sum, 0xffffu) << 16;
         }
-        if (b.level != a.level) strip_barrier();
+        if (b.level != a.level) lds_barrier();
         a = b;
         b.next(starts);
         return a.level <= deep;
@@ -712,9 +709,9 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
       uint32_t previous[kFewPieces];
 #pragma unroll
       for (int k = 0; k < kFewPieces; ++k) previous[k] = lds_at(queue, 2u * (uint32_t)min(max(first + k * T + tt - 1, first), end - 1));
-      strip_barrier();
+      lds_barrier();
       for (uint32_t i = (uint32_t)tt; i < (before_at - bits_at) / 16; i += T) lds_put<FlowWords>(16u * i + bits_at, FlowWords{0, 0, 0, 0});
-      strip_barrier();
+      lds_barrier();
 #pragma unroll
       for (int k = 0; k < kFewPieces; ++k) {
         const int i = first + k * T + tt;
@@ -725,7 +722,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           if (i == first || previous[k] >> 5 != v[k] >> 5) lds_put<unsigned short>((v[k] >> 4 & 0xffeu) + before_at, (unsigned short)(i - first));
         }
       }
-      strip_barrier();
+      lds_barrier();
     };
     // Where the coefs of the level behind the present one are: in the list (or there is no such level); still to be worked out, from
     // the list or without successors; in memory.
@@ -781,9 +778,9 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           const int end = h + 1 == strips.count ? next : __builtin_amdgcn_readfirstlane(s_strip[(h + 1) * 16 + l]);
           const auto put = [&](uint32_t v, double c) { lds_put<double>(8u * (v - v_first), c); };
           const auto room = [&] {
-            strip_barrier();
+            lds_barrier();
             clear(8u * (uint32_t)strips.nodes + 16u);
-            strip_barrier();
+            lds_barrier();
           };
           if (behind == kOpen && b == from) {
             if (l + 1 == deep) {
@@ -848,7 +845,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
           row[1] = row_first[1];
           int t1 = tt;
           asm volatile("" : "+v"(t1));  // addresses are not kept from strip to strip
-          strip_barrier();
+          lds_barrier();
           const uint32_t zero = 8u * (uint32_t)strips.nodes, less = 0u - 8u * v_first;
           wide_steps_while([&](auto number) {
             constexpr int k = decltype(number)::value;

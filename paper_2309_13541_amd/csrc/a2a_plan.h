@@ -233,6 +233,21 @@ inline bool node_fits(int N, int ell_words, int depth, int src_count) {
 }
 
 // ---------------------------------------------------------------------------------------
+// search with the frontier in LDS (a2a_wide_kernels.h)
+// ---------------------------------------------------------------------------------------
+
+// LDS of a search: a word per slot and thread, and a list of the new nodes of a sparse level, 16 bits each.  A level by the list costs
+// some 7 thousand cycles for 65536 nodes and 20 for a full list of 8192 entries; by the links of all nodes 66 thousand with 8
+// links a node, 33 with 4.  With 64 sources a word a node's links are gone over once for all of them, and the list is the longer
+// one: sums alone, without and with it, 10000 nodes of degree 3 70, 72 us, torus 25x25x26 359, 362; with 32 or 16 sources, 20011 of
+// degree 5 250, 221; 40000 of a generalized Kautz topology of degree 6 716, 548; 65536 of degree 3 3542, 2669; torus 40x40x40 16.0, 14.6 ms.
+constexpr int kWideList = 8192;  // entries; a thread keeps some of them in registers
+constexpr bool wide_sparse(int W) { return W != 64; }
+constexpr size_t wide_words_bytes(int slots) { return (size_t)slots * kSmallThreads * 4; }
+constexpr int wide_list(int N, int W) { return !wide_sparse(W) ? 0 : N / 8 < kWideList ? N / 8 : kWideList; }
+static_assert(wide_words_bytes(32) + kWideList * 2 <= kSmallLds);
+
+// ---------------------------------------------------------------------------------------
 // link loads by sources in LDS, links in registers (a2a_flow_kernels.h)
 // ---------------------------------------------------------------------------------------
 

@@ -61,6 +61,9 @@ __device__ __forceinline__ void lds_put(uint32_t at, T x) {
   *(__attribute__((address_space(3))) T*)at = x;
 }
 
+// Threads of a workgroup wait for each other and for what they have asked of LDS, not for memory.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // The links of a node.  at<kShift>(j): 8 x id of link j shifted right, i.e. its place in an array of doubles (0), words
 // (1) or bytes (3); the two halves of a word are shifted together.
 template <int KS>

@@ -886,6 +886,8 @@ int wide_search(const a2a_topo* t, WideView* wv, int out, char* ws, size_t ws_by
   wv->N = t->N;
   wv->depth = t->level_bound;
   wv->slots = W == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads) : (t->N + kWideThreads - 1) / kWideThreads * (W / 32);
+  wv->out = t->d_ell_out;
+  wv->list = wide_list(t->N, W);
   const size_t masks = (size_t)(wv->depth / 2 + 1) * wv->slots * kWideThreads * sizeof(uint32_t);
   const size_t room = ws_bytes / (masks + kSmallCounters * sizeof(long long));
   if (room < 1) return A2A_ERR_WORKSPACE_TOO_SMALL;

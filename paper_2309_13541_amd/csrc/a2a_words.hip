@@ -29,7 +29,7 @@ void small_loads(const SmallPlan& p, int workgroups, hipStream_t st) {
 
 template <int W, int KS, int kOut>
 void wide_search(const WideView& wv, int workgroups, hipStream_t st) {
-  const size_t lds = (size_t)wv.slots * kWideThreads * sizeof(uint32_t);
+  const size_t lds = wide_words_bytes(wv.slots) + (size_t)wv.list * 2;
   const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
   if (kOut == kWideDist && wv.depth < 8)
     launch(k_wide_dist<W, KS, kOut == kWideDist ? 3 : 6, kOut>);

@@ -27,7 +27,8 @@ CASES = {
 
 
 @pytest.mark.parametrize("name", CASES)
-def test_distances(a2a, oracle, name):
+def test_distances(oracle, name):
+    import paper_2309_13541_amd as a2a
     make, s0, cnt = CASES[name]
     rp, col = make()
     print(name, flush=True)

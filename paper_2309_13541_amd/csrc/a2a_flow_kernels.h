@@ -728,6 +728,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
     // the list or without successors; in memory.
     enum { kListed, kOpen, kStored };
     int behind = kListed;
+    bool ready = false;  // the first strip of the level behind is in LDS
     for (int l = deep; l >= 1; --l) {
       const int from = start(l), to = start(l + 1), next = start(l + 2);
       const bool few = few_on(l);
@@ -815,7 +816,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
                 }
               });
             }
-          } else {
+          } else if (!ready || h > 0 || b > from) {
             constexpr int kAtOnce = 12;
             uint32_t v[kAtOnce];
             const auto nodes = [&](int i) {
@@ -823,7 +824,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
               for (int k = 0; k < kAtOnce; ++k) v[k] = lds_at(queue, 2u * (uint32_t)max(min(i + k * T, end - 1), 0));
             };
             nodes(first + tt);
-            if (h == 0) __syncthreads();  // coefs are in memory
+            if (h == (ready && b == from ? 1 : 0)) __syncthreads();  // coefs are in memory
             room();
             for (int i = first + tt; i < end;) {
               double c[kAtOnce];
@@ -866,6 +867,12 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
         }
         uint32_t few_v[kFewPieces];
         double few_c[kFewPieces];
+        ready = !few && l > 1 && to - from <= kPieces * T;
+        if (ready) {
+          lds_barrier();
+          clear(8u * (uint32_t)strips.nodes + 16u);
+          lds_barrier();
+        }
         constexpr int kAtOnce = kPieces % 12 == 0 ? 12 : 8;
         static_assert(kPieces % kAtOnce == 0 && kFewPieces <= kPieces);
         wide_steps_while([&](auto number) {
@@ -881,6 +888,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
               const uint32_t v = r[k] & 0xffffu;
               c += alone(r[k]);
               lds_at(coef, 8u * v) = c;
+              if (ready && v < (uint32_t)strips.nodes) lds_put<double>(8u * v, c);
             }
             if constexpr (k0 + k < kFewPieces) {
               few_v[k0 + k] = r[k] & 0xffffu;

@@ -478,10 +478,12 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
 // Their sums stay in registers in between, kPieces nodes a thread.  A level of few nodes needs no strips: a bit per node says
 // which are on it, and the coefs are a list.  The last level, and a level before one of few nodes, is worked out strip by strip
 // as it goes into LDS; others come from memory, where they wait in the row of the output.
-// A source of 65536 nodes of degree 8 takes 564 thousand cycles: sort 48, forward 124, levels of few nodes 27, level 6 into LDS 106, level 5
-// into LDS 60, the sums over strips 135, what a level is by itself 42.  Bound by chains within a piece (links, gathers, sum) and by
-// barriers between strips, then by LDS (half of the time) and memory (2.4 MB read, 1.8 MB written a source).  Link tables that have a
-// node's links by strips took less LDS time, but 4 MB more in L2: 4.8 MB read a source, 97 ms a call, now 80.
+// A source of 65536 nodes of degree 8 takes 540 thousand cycles: sort 53, forward 102, levels of few nodes 25, level 6 into LDS 62, levels 5
+// and 4 into LDS 30, the sums over strips 109, waiting for each other and for records around a strip 76, what a level is by itself 58.
+// Vector ALUs are busy 42, LDS 38 % of the time, and 1.5 MB are read and 1.6 written a source (3.8 TB/s): bound by chains within
+// a piece (links, gathers, sum) and by what a strip begins and ends with.  Memory requests come back in order, so queue
+// entries, which miss L2, are asked for many at a time (a call 80, now 77 ms), and the first strip's coefs do not go through
+// memory (77, now 75).  Link tables that have a node's links by strips took less LDS time, but 4 MB more in L2: 97 ms, 80 without.
 template <int KS>
 __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
   extern __shared__ double s_small[];

@@ -353,11 +353,15 @@ constexpr size_t flow_record_bytes(int stride, bool demand) { return (size_t)str
 struct FlowGroups {
   int blocks, group, groups;  // blocks of nodes, sources per group, groups
 };
-inline FlowGroups flow_groups(int N, int ell_words, int src_count) {
+inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips = false) {
   FlowGroups g;
   g.blocks = (N + flow_nodes(ell_words) * kSmallThreads - 1) / (flow_nodes(ell_words) * kSmallThreads);
   const int most = std::max(8, kComputeUnits / g.blocks / 8 * 8);
   g.group = (src_count + most - 1) / most;
+  // By strips a source takes up to a megabyte of workspace, and what of a call fits it may be few groups, so they are smaller, at the price of
+  // as many partial loads (65536 nodes of degree 8, with groups as above and these: 4096 sources in 1 GB 11.4, 7.7 ms; groups of 128 for all
+  // 65536 sources 75.9, of 256 74.4 ms, in 1 GB 119 and 170, in 4 GB 82 and 82; of 50000 of a generalized Kautz topology of degree 5, 30.6, 29.6 ms).
+  if (strips) g.group = std::min(g.group, std::min(256, std::max(128, src_count / 128)));
   g.groups = (src_count + g.group - 1) / g.group;
   return g;
 }
@@ -395,7 +399,7 @@ inline FlowLayout flow_layout_for(int N, int ell_words, int src_count, bool dema
   return l;
 }
 inline FlowLayout flow_layout(int N, int ell_words, int src_count, bool demand, size_t bytes, bool strips = false) {
-  const FlowGroups g = flow_groups(N, ell_words, src_count);
+  const FlowGroups g = flow_groups(N, ell_words, src_count, strips);
   const auto most = [bytes](int hi, auto&& at) {  // largest k in 0..hi with at(k) that fits
     int lo = 0;
     while (lo < hi) {

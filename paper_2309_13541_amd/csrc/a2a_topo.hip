@@ -1,11 +1,13 @@
 // a2a_topo host side: the C ABI of include/a2a_topo.h.  All-pairs hop distances, shortest-path
 // counts and EwSP link loads of a direct-connect topology (Sec. 2.2, 5.2, 5.3, 5.4 of the paper)
-// on one MI355X.  A call goes one of three ways, by what fits where (small_..._fit, wide_..._fit):
+// on one MI355X.  A call goes one of four ways, by what fits where (small_..._fit, flow_fits, strips_fit, wide_..._fit):
 //   - topologies of up to 8191 nodes and 16 links a node: one kernel takes a workgroup's sources from the search to
 //     their results with all state in LDS, a second adds up (a2a_small_kernels.h; single-path baseline up to 16384 nodes)
+//   - link loads of up to 65536 nodes and 16 links a node from many sources: a source at a time in LDS, as a whole or by strips of nodes, and
+//     a second kernel with the links' loads in registers (a2a_flow_kernels.h)
 //   - up to 65536 nodes and 16 links a node: the levels come from a search with the frontier in LDS
 //     (a2a_wide_kernels.h); distances straight from it, path counts of up to 16384 nodes a source at a time in LDS, link
-//     loads (of those topologies of more than 4096 nodes that do not go the first way) by the level kernels
+//     loads (of those topologies of more than 4096 nodes that do not go the other ways) by the level kernels
 //   - everything else: the level kernels alone (a2a_kernels.h, where their data model is described)
 //
 // Level kernels.  A "group" of G source batches (64 sources each) advances level by level together, one kernel
@@ -1041,7 +1043,7 @@ bool strips_fit(const a2a_topo* t, int32_t src_count) {
 int flow_link_loads(const a2a_topo* t, bool strips, int32_t src_begin, int32_t src_count, const double* demand, double* load,
                     double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes, hipStream_t st) {
   if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  const FlowGroups g = flow_groups(t->N, t->ell_words, src_count);
+  const FlowGroups g = flow_groups(t->N, t->ell_words, src_count, strips);
   const FlowLayout l = flow_layout(t->N, t->ell_words, src_count, demand != nullptr, ws_bytes, strips);
   FlowView fv{};
   fv.in = t->d_ell_in;

@@ -40,7 +40,8 @@ int main() {
     for (int w : words)
       for (int n : {kStripFewestSources, 2501, 10000, N}) {
         if (n > N) continue;
-        const FlowGroups g = flow_groups(N, w, n);
+        const FlowGroups g = flow_groups(N, w, n, true);
+        check(g.group >= 1 && g.group <= 256 && (long long)g.group * g.groups >= n && (long long)g.group * (g.groups - 1) < n, "groups", N, w, n);
         const FlowLayout whole = flow_layout(N, w, n, true, ~(size_t)0, true);
         const size_t S = (size_t)flow_stride(N);
         check(whole.rows == n && whole.part - whole.record >= 256 * strip_record_bytes((int)S) && whole.exact - whole.escaped >= 4 * (size_t)n &&

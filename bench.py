@@ -37,6 +37,7 @@ KERNEL_NAME = {"bfs": "k_bfs_level", "offsets": "k_write_offsets", "fwd_rows": "
 AFTER_SEARCH = {"offsets": "k_wide_index"}
 AFTER_SOURCES = {"reduce": "k_small_reduce"}
 AFTER_BOTH = {"sources": "k_flow_sources + k_flow_links", "reduce": "k_flow_reduce"}
+AFTER_BOTH_STRIPS = {"sources": "k_strip_sources + k_flow_links", "reduce": "k_flow_reduce"}  # more than 20352 nodes
 FWD_CLASSES = ("fwd_rows", "fwd_few", "fwd_spread")
 BWD_CLASSES = ("bwd_rows", "bwd_few", "bwd_spread")
 
@@ -246,7 +247,7 @@ def main():
     if prof["search"]["launches"]:
         names.update(AFTER_SEARCH)
     if prof["sources"]["launches"]:
-        names.update(AFTER_BOTH if prof["search"]["launches"] else AFTER_SOURCES)
+        names.update((AFTER_BOTH_STRIPS if N > 20352 else AFTER_BOTH) if prof["search"]["launches"] else AFTER_SOURCES)
     per_kernel = {}
     for k, name in names.items():
         ms, n = prof[k]["ms"], prof[k]["launches"]

@@ -1028,11 +1028,11 @@ bool flow_fits(const a2a_topo* t, int32_t src_count, bool demand) {
 }
 
 // The same for unit demands of topologies of more nodes, by strips (k_strip_sources): path counts of all levels below 2^32.  ms of
-// level kernels and of this, all sources and 2048 of them: random topologies, 20353 nodes of degree 6 9.49, 6.87; 1.09, 0.79; 30000 of degree 4
-// 20.7, 13.2; 1.60, 1.08; 45000 of degree 3 (13 levels) 59.6, 37.3; 3.02, 1.98; 65536 of degree 8 106.3, 80.2; 3.58, 2.80; generalized Kautz
-// topologies, 40000 of degree 5 24.6, 19.2; 1.42, 1.11; 65535 of degree 3 76.5, 69.1.  With demands it is not the faster one
-// everywhere (16384 nodes of degree 4 5.23, 5.82; 32768 of degree 3 33.2, 28.8).  Fewer sources stay with the level kernels,
-// whose results the tests hold bit for bit.
+// level kernels and of this, all sources and 2048 of them: random topologies, 20353 nodes of degree 6 9.49, 6.68; 1.09, 0.74; 30000 of degree 4
+// 20.7, 12.4; 1.60, 0.99; 45000 of degree 3 (13 levels) 59.6, 34.4; 3.02, 1.84; 65536 of degree 8 106.3, 75.2; 3.58, 2.64; 24000 of degree 16 2048
+// sources 2.41, 1.25; generalized Kautz topologies, 40000 of degree 5 24.6, 18.8; 1.42, 1.04; 65535 of degree 3 76.5, 61.6; 60000 of degree 8
+// 64.8, 57.4.  With demands it was not the faster one everywhere (16384 nodes of degree 4 5.23, 5.82; 32768 of degree 3 33.2, 28.8).  Fewer
+// sources stay with the level kernels, whose results the tests hold bit for bit.
 bool strips_fit(const a2a_topo* t, int32_t src_count) {
   const double bits = (double)t->level_bound * std::log2((double)std::max(t->dmax_in, 2));
   return t->ell_words > 0 && t->N > kFlowNodes && src_count >= kStripFewestSources && t->level_bound >= 1 && bits < 32.0 &&

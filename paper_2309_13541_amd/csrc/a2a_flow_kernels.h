@@ -942,9 +942,9 @@ k_flow_demand(FlowView fv, const double* __restrict__ dem, long long ld) {
 // source, in source order, in registers.  A thread has kPairs pairs of adjacent nodes.  A source's path counts are brought into
 // LDS while the last one's are worked on.  The blocks of a group read the same path counts: they go to the same XCD, one after
 // the other.  Bound by memory where nodes have few links (16384 nodes of degree 4: 3.3 GB in 0.59 ms), else by LDS and the vector ALUs.
-template <int KS, bool kScaled, bool kDemand, bool kHalves = false>
+template <int KS, bool kScaled, bool kDemand, bool kHalves = false, int kPairs = flow_nodes(KS) / 2>
 __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
-  constexpr int kPairs = flow_nodes(KS) / 2, kXcds = 8;
+  constexpr int kXcds = 8;
   extern __shared__ double s_small[];
   const int t = (int)threadIdx.x, wave = __builtin_amdgcn_readfirstlane(t / kWave), N = fv.N;
   const int blocks = (N + 2 * kPairs * kWideThreads - 1) / (2 * kPairs * kWideThreads);

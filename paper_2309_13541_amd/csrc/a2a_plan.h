@@ -366,6 +366,14 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips =
   return g;
 }
 
+// Whether k_flow_links after k_strip_sources has two nodes a thread for its usual four or six: where the groups at hand then still have at most a
+// workgroup per compute unit.  A link's load is the same sum.  (65536 nodes of degree 8: all sources in 1 GB 170, 152 ms, 4096 in the least
+// workspace 39, 36; 4096 of 45000 of degree 3 in the least 30.0, 26.7, but in 1 GB, 88 workgroups for which it would be 242, 4.8, 5.4.)
+inline bool strip_links_narrow(int N, int ell_words, int groups) {
+  const int nodes = flow_nodes(ell_words);
+  return nodes > 2 && (N + nodes * kSmallThreads - 1) / (nodes * kSmallThreads) * groups * nodes / 2 < kComputeUnits;
+}
+
 // Where things lie in the workspace: `rows` sources at a time, partial loads of `parts` groups.  rows: all, or as many whole
 // groups as fit, or a part of one.
 struct FlowLayout {

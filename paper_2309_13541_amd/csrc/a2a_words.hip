@@ -153,15 +153,18 @@ void launch_strip_sources(const FlowView& fv, int workgroups, hipStream_t st) {
 
 template <int KS>
 void launch_flow_links(const FlowView& fv, bool demand, hipStream_t st) {
-  const int blocks = (fv.N + flow_nodes(KS) * kWideThreads - 1) / (flow_nodes(KS) * kWideThreads);
-  const unsigned workgroups = (unsigned)((fv.groups + 7) / 8 * 8 * blocks);
-  const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, fv.exact != nullptr ? strip_link_lds(fv.N) : flow_link_lds(fv.N), st>>>(fv); };
+  const auto launch = [&](auto kernel, int nodes) {  // of a thread
+    const int blocks = (fv.N + nodes * kWideThreads - 1) / (nodes * kWideThreads);
+    const unsigned workgroups = (unsigned)((fv.groups + 7) / 8 * 8 * blocks);
+    kernel<<<workgroups, kWideThreads, fv.exact != nullptr ? strip_link_lds(fv.N) : flow_link_lds(fv.N), st>>>(fv);
+  };
+  constexpr int kNodes = flow_nodes(KS);
   if (fv.exact != nullptr)
-    launch(k_flow_links<KS, false, false, true>);
+    strip_links_narrow(fv.N, KS, fv.groups) ? launch(k_flow_links<KS, false, false, true, 1>, 2) : launch(k_flow_links<KS, false, false, true>, kNodes);
   else if (fv.N <= kScaledNodes)
-    demand ? launch(k_flow_links<KS, true, true>) : launch(k_flow_links<KS, true, false>);
+    demand ? launch(k_flow_links<KS, true, true>, kNodes) : launch(k_flow_links<KS, true, false>, kNodes);
   else
-    demand ? launch(k_flow_links<KS, false, true>) : launch(k_flow_links<KS, false, false>);
+    demand ? launch(k_flow_links<KS, false, true>, kNodes) : launch(k_flow_links<KS, false, false>, kNodes);
 }
 
 template void launch_small_loads<A2A_WORDS>(const SmallPlan&, bool, int, hipStream_t);

@@ -626,6 +626,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
       }
     }
     if (escaped) *s_escaped = 1;
+    __syncthreads();  // other threads read the records and path counts in memory from here on
     unsigned short* const count = reinterpret_cast<unsigned short*>(fv.count) + (size_t)s * (size_t)S;
     for (int i = t; i < S / 8; i += T)
       __builtin_nontemporal_store(reinterpret_cast<const FlowWords*>(x)[i], reinterpret_cast<FlowWords*>(count) + i);
@@ -686,7 +687,7 @@ __global__ void __launch_bounds__(kWideThreads) k_strip_sources(FlowView fv) {
       for (int at = first; at < end;) {
         const bool more = wide_steps_while([&](auto number) {
           constexpr int i = decltype(number)::value;
-          if constexpr (i + 2 < kDozen) row[(i + 2) % 3].load(fv.out, r[i + 2] & 0xffffu);
+          if constexpr (i + 2 < kDozen) row[(i + 2) % 3].load(fv.out, min(r[i + 2] & 0xffffu, (uint32_t)N - 1u));
           flow_in_order();
           uint32_t bits[2 * KS];
           few_bits(row[i % 3], bits);

@@ -108,3 +108,17 @@ def test_lds_by_address_starts_at_zero(code_objects):
             sizes.setdefault(rest[:int(length)], set()).add(int(size))
     assert names <= set(sizes) and 0 not in sizes["k_wide_dist"]
     assert {k: sizes[k] for k in names if sizes[k] != {0}} == {}
+
+
+def test_words_in_memory_between_the_sweeps_of_a_strip_source():
+    """lds_barrier() waits for LDS only.  Where k_strip_sources begins to read the records that other threads have stored, a
+    barrier for memory stands before it, and a record is no place outside the link table whatever it holds."""
+    with open(os.path.join(CSRC, "a2a_flow_kernels.h")) as f:
+        source = re.sub(r"//.*", "", f.read())
+    kernel = re.split(r"k_strip_sources\(FlowView fv\) \{", source)[1].split("__global__")[0]
+    stored = kernel.index("lds_at(record, 4u * (uint32_t)(a.base + tt)) =")
+    read = kernel.index("= lds_at(record,", stored)
+    assert "__syncthreads();" in kernel[stored:read]
+    # (a thread's own records, and nodes of the queue, are no other thread's)
+    rows = re.findall(r"\.load\(fv\.out, (.*)\);", kernel)
+    assert len(rows) >= 6 and all(row.startswith("min(") for row in rows if "r[" in row), rows

@@ -220,16 +220,31 @@ inline NodeCut node_cut(int N, int src_count) {
   c.workgroups = (src_count + c.per_wg - 1) / c.per_wg;
   return c;
 }
-// Which calls take it.  k_small_loads goes over the levels of several sources at a time, and every level only over its own nodes;
-// here each source has its levels to itself, and every node without a level looks at its links.  So it depends on the sources of a
-// workgroup and on the levels (us, k_small_loads and this): one source each: 256 nodes of degree 8 13.0, 9.9; 4x128 torus (66
-// levels) 44.5, 23.5; 2000 of degree 8 37.0, 29.5.  Two: bidirectional ring of 500 (250 levels) 155, 121; 2048 of degree 3 30.0, 25.4;
-// 40x40 torus 47.5, 49.7.  Three: 9x9x9 torus (12 levels) 27.7, 26.6; 24x24 (24) 26.9, 29.2.  Four: hypercube of 1024 (10)
-// 39.8, 38.6; 10x10x10 torus (15) 37.2, 39.3.  Six: 1400 of degree 3 (9) 49.3, 44.9.  Seven: 1537 of degree 3 (9) 50.6, 54.2.
-constexpr int kNodeFewSources = 2, kNodeFewLevels = 10;
+// Which calls take it.  k_small_loads goes over the levels of several sources at a time, and every level only over its own nodes; here
+// each source has its levels to itself, and every node without a level looks at its links.  So it is the faster one up to so many
+// levels, the fewer the more sources a workgroup has and where a thread has two nodes (us, k_small_loads and this, at the edges):
+//   a node a thread.  One and two sources of a workgroup, any levels: 256 nodes of degree 8 13.0, 9.9; 8x128 torus (68 levels) 59.9,
+//     47.1; bidirectional ring of 500 (250) 155, 121.  Three, 15 levels: 10x10x10 torus 31.8, 30.8; 22 and more not: 24x24 torus (24)
+//     26.5, 28.8.  Four, 10: hypercube of 1024 38.7, 38.0, with a fifth of its links gone 39.1, 39.0, 5x5x6x6 torus 32.0, 32.4; 4x4x8x8
+//     torus (12) 34.3, 35.1, 10x10x10 (15) 36.6, 39.1.
+//   two nodes.  One source, any: 2000 of degree 8 37.0, 29.5; 44x46 torus (45) 48.9, 35.6.  Two: up to 1536 nodes any, 38x40 torus
+//     (39) 49.7, 47.7, 5x300 (152) 134, 113; with more nodes 30, 4x16x32 torus (26) 46.7, 46.6, or levels of at most 35 nodes, 20x102
+//     torus (61) 64.3, 62.1; not 40x40 (40) 47.4, 49.7, 45x45 (44) 54.9, 59.1, 24x74 (49) 53.2, 54.2.  Three, 11: 5x6x6x6 torus 34.4,
+//     34.4, 4x4x4x4x6 47.6, 45.4; 6x6x6x6 (12) 38.9, 39.4, 11x11x11 (15) 38.1, 41.9.  Four, 7: 1300 of degree 5 34.2, 34.1, of degree 6
+//     (6) 35.6, 34.0; 1536 of degree 4 (8) 32.5, 33.0, of degree 3 (9) 32.1, 33.4.  Five and six, which k_small_loads takes in two
+//     rounds, 11: 5x6x6x6 torus 53.1, 47.7; 6x6x6x6 (12) 60.2, 62.8.  More: 2048 of degree 4 (8) 56.4, 64.1.
 inline bool node_fits(int N, int ell_words, int depth, int src_count) {
   if (N > kNodeMost * kSmallThreads || (N > kSmallThreads && ell_words > 5)) return false;
-  return node_cut(N, src_count).per_wg <= kNodeFewSources || (N <= kSmallThreads * 3 / 2 && depth <= kNodeFewLevels);
+  const int sources = node_cut(N, src_count).per_wg;
+  if (N <= kSmallThreads) return sources <= 2 || depth <= (sources == 3 ? 15 : 10);
+  const bool few = N <= kSmallThreads * 3 / 2;
+  switch (sources) {
+    case 1: return true;
+    case 2: return few || depth <= 30 || N <= 35 * depth;
+    case 3: return depth <= 11;
+    case 4: return depth <= 7;
+    default: return few && depth <= 11;
+  }
 }
 
 // ---------------------------------------------------------------------------------------

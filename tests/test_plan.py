@@ -215,3 +215,34 @@ int main() {
 
 def test_a_thread_per_node_fits_a_workgroup(compiled):
     assert compiled("nodes", NODES).returncode == 0
+
+
+EDGES = r"""
+#include <cstdio>
+#include "a2a_plan.h"
+using namespace a2a_dev;
+
+int main() {
+  // nodes, words of the link table, levels, sources, whether k_node_loads was the faster one when both were timed
+  const int measured[][5] = {
+      {256, 4, 4, 256, 1},   {1024, 2, 68, 512, 1},  {500, 2, 250, 500, 1},  {1000, 3, 15, 768, 1},  {576, 2, 24, 576, 0},
+      {702, 2, 26, 702, 0},  {729, 3, 12, 729, 1},   {1024, 5, 10, 1024, 1}, {1024, 4, 12, 1024, 0}, {1000, 3, 15, 1000, 0},
+      {2000, 4, 5, 256, 1},  {2024, 2, 45, 256, 1},  {1520, 2, 39, 512, 1},  {1500, 2, 152, 512, 1}, {2048, 3, 24, 512, 1},
+      {2040, 2, 61, 512, 1}, {2048, 2, 132, 512, 1}, {1600, 2, 40, 512, 0},  {2025, 2, 44, 400, 0},  {1776, 2, 49, 400, 0},
+      {2048, 2, 9, 768, 1},  {1536, 5, 11, 768, 1},  {1296, 4, 12, 768, 0},  {1331, 3, 15, 768, 0},  {1300, 3, 6, 1024, 1},
+      {2048, 4, 5, 1024, 1}, {1536, 2, 8, 1024, 0},  {1100, 2, 9, 1024, 0},  {1050, 4, 10, 896, 0},  {1080, 4, 11, 1080, 1},
+      {1536, 2, 9, 1536, 1}, {1296, 4, 12, 1296, 0}, {1600, 2, 10, 1600, 0}, {2048, 2, 8, 2048, 0}};
+  int bad = 0;
+  for (const auto& m : measured)
+    if (node_fits(m[0], m[1], m[2], m[3]) != (m[4] != 0)) {
+      std::printf("%d nodes, %d words, %d levels, %d sources: not %d\n", m[0], m[1], m[2], m[3], m[4]);
+      ++bad;
+    }
+  return bad != 0;
+}
+"""
+
+
+def test_a_thread_per_node_where_it_was_faster(compiled):
+    out = compiled("edges", EDGES)
+    assert out.returncode == 0, out.stdout

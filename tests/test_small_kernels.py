@@ -85,6 +85,9 @@ NODES = [(name, csr, s0, cnt) for name, csr, s0, cnt in (
     ("1025 nodes, a source each", lambda: gen.random_regular(1025, 5, 3), 700, 256),
     ("2048 nodes, 2 sources each", lambda: gen.random_regular(2048, 8, 3), 1, 511),
     ("1536 nodes, 6 sources each", lambda: gen.random_regular(1536, 4, 3), 0, 1536),
+    ("2047 nodes, 3 sources each", lambda: gen.random_regular(2047, 4, 3), 1300, 640),
+    ("1080 nodes, 5 sources each, 11 levels", lambda: gen.torus([5, 6, 6, 6]), 0, 1080),
+    ("40x40 torus, 2 sources each", lambda: gen.torus([40, 40]), 1000, 400),
     ("22x23 torus", lambda: gen.torus([22, 23]), 0, 506),
     ("26x27 torus, 3 sources each", lambda: gen.torus([26, 27]), 0, 702),
     ("8x9 torus with 90 links left", lambda: gen.remove_arcs(gen.torus([8, 9]), np.random.default_rng(5).permutation(288)[90:]), 0, 72))]

@@ -165,9 +165,6 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
   const int state = what == SmallWhat::kLoads ? kStateLoads : what == SmallWhat::kSigma ? kStateSigma : kStateSssp;
   const int most = small_most_nodes(what, ell_words);
   int tg = small_threads(N), per = 1;
-  // A source that has a compute unit to itself, of what node_fits leaves: a thread per node where there are few (link loads, us: 200
-  // sources of 1000 nodes 73.1, now 67.1; 150 of 2500 nodes 73.4, 73.8 with it).
-  if (what == SmallWhat::kLoads && src_count <= kComputeUnits && N <= 2 * kSmallThreads) tg = std::min(kSmallThreads, up(N));
   if (what == SmallWhat::kDist) {
     tg = std::min(kSmallThreads, up(N));
     c.lds = (size_t)N * 8;

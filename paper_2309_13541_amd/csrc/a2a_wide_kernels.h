@@ -304,29 +304,20 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
           constexpr int i0 = decltype(four)::value * kAtOnce;
           if (i0 > end) return;
           uint32_t found[kAtOnce][2];
+          static_assert(kWords == 1);
           wide_steps([&](auto number) {
             constexpr int k = decltype(number)::value;
             const int v = min(i0 + k, end) * kStride + own;
-            if constexpr (W == 16) {
-              found[k][0] = (uint32_t)front[v] | (uint32_t)front[v + kWideThreads] << 16;
-            } else if constexpr (W == 32) {
-              found[k][0] = front[v];
-            } else {
-              const uint64_t x = front[v];
-              found[k][0] = (uint32_t)x;
-              found[k][1] = (uint32_t)(x >> 32);
-            }
+            found[k][0] = (uint32_t)front[v];
+            if constexpr (W == 16) found[k][0] |= (uint32_t)front[v + kWideThreads] << 16;
           }, std::make_index_sequence<kAtOnce>{});
           __builtin_amdgcn_sched_barrier(0);
           wide_steps([&](auto number) {
             constexpr int k = decltype(number)::value, i = i0 + k;
             if (i > end) return;
             update(std::integral_constant<int, i>{}, found[k]);
-#pragma unroll
-            for (int w = 0; w < kWords; ++w) {
-              all &= r[i * kWords + w];
-              if (odd) keep[(i * kWords + w) * kWideThreads] = r[i * kWords + w];
-            }
+            all &= r[i];
+            if (odd) keep[i * kWideThreads] = r[i];
           }, std::make_index_sequence<kAtOnce>{});
           __builtin_amdgcn_sched_barrier(0);
         }, std::make_index_sequence<kSteps / kAtOnce>{});

@@ -378,12 +378,15 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips =
   return g;
 }
 
-// Whether k_flow_links after k_strip_sources has two nodes a thread for its usual four or six: where the groups at hand then still have at most a
-// workgroup per compute unit.  A link's load is the same sum.  (65536 nodes of degree 8: all sources in 1 GB 170, 152 ms, 4096 in the least
-// workspace 39, 36; 4096 of 45000 of degree 3 in the least 30.0, 26.7, but in 1 GB, 88 workgroups for which it would be 242, 4.8, 5.4.)
+// Whether k_flow_links after k_strip_sources has two nodes a thread for its usual four or six: where all workgroups of the groups at hand then still
+// run at once.  A group's workgroups share an XCD, so that is a matter of the XCD with the most groups.  A link's load is the same sum.
+// (16384 sources, ms, usual and two nodes, and workgroups of that XCD with two: 65536 nodes of degree 8, 7 groups 30.3, 28.3 (32), 11 groups 24.7, 28.3
+// (64); 45000 of degree 3, 8 groups 21.1, 19.5 (22), 11 groups 19.4, 21.4 (44); 24000 of degree 8, 16 groups 8.48, 7.70 (24), 21 groups 8.14, 8.73 (36); 4096
+// of 33000 of degree 7, 7 groups 4.08, 3.70 (17), 11 groups 3.18, 3.66 (34).  Just above 32 with little left over it is the faster one now and then, too: 20353
+// of degree 6, 25 groups 6.74, 6.45 (40).)
 inline bool strip_links_narrow(int N, int ell_words, int groups) {
-  const int nodes = flow_nodes(ell_words);
-  return nodes > 2 && (N + nodes * kSmallThreads - 1) / (nodes * kSmallThreads) * groups * nodes / 2 < kComputeUnits;
+  constexpr int kXcds = 8, kNarrow = 2 * kSmallThreads;
+  return flow_nodes(ell_words) > 2 && (groups + kXcds - 1) / kXcds * ((N + kNarrow - 1) / kNarrow) <= kComputeUnits / kXcds;
 }
 
 // Where things lie in the workspace: `rows` sources at a time, partial loads of `parts` groups.  rows: all, or as many whole

@@ -53,6 +53,11 @@ int main() {
           check((l.rows == 0 || l.total <= bytes) && (l.rows % g.group == 0 || l.rows < g.group), "layout", N, n, part);
         }
       }
+  // nodes, words, groups, whether two nodes a thread were the faster ones when both were timed
+  const int narrow[][4] = {{65536, 4, 1, 1}, {65536, 4, 7, 1},  {65536, 4, 11, 0}, {45000, 2, 8, 1},  {45000, 2, 10, 0}, {45000, 2, 11, 0},
+                           {24000, 4, 16, 1}, {24000, 4, 19, 0}, {33000, 4, 7, 1},  {33000, 4, 10, 0}, {33000, 4, 11, 0}, {50000, 3, 7, 1},
+                           {50000, 3, 10, 0}, {30000, 2, 12, 1}, {30000, 2, 17, 0}, {20353, 2, 24, 1}, {40000, 8, 1, 0}};
+  for (const auto& m : narrow) check(strip_links_narrow(m[0], m[1], m[2]) == (m[3] != 0), "two nodes a thread", m[0], m[1], m[2]);
   std::printf("%lld checks, %lld bad\n", seen, bad);
   return bad != 0;
 }

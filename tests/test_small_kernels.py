@@ -112,6 +112,35 @@ def test_a_thread_per_node(a2a, oracle, name, csr, s0, cnt):
     topo.close()
 
 
+@pytest.mark.parametrize("nodes", [600, 1100])
+def test_a_thread_per_node_demands_of_any_kind(a2a, oracle, nodes):
+    """Demands of both signs; and an infinite one and one that is no number, which change the loads on their own shortest paths
+    only: those of the source's other demands."""
+    topo = a2a.Topology(*gen.random_regular(nodes, 6, 5))
+    rp, col = gen.random_regular(nodes, 6, 5)
+    s0, cnt = 40, 500
+    assert int(topo.N) == nodes
+    dem = np.random.default_rng(3).standard_normal((cnt, nodes))
+    size = oracle.run_demand(rp, col, np.abs(dem), s0)
+    want = oracle.run_demand(rp, col, dem, s0)
+    load, wd, _, _ = run_demand_gpu(topo, dem, s0)
+    # (sums of up to cnt * nodes terms of either sign: error against the sum of their magnitudes)
+    assert np.all(np.abs(load - want[0]) <= 1e-12 * size[0]) and abs(wd - want[1]) <= 1e-12 * size[1]
+    on_path = []  # links on a shortest path from the source to the target
+    for s, t, value in ((7, 300, np.inf), (333, 5, np.nan)):
+        one = np.zeros((cnt, nodes))
+        one[s, t] = 1.0
+        on_path.append(oracle.run_demand(rp, col, one, s0)[0] > 0)
+        dem[s, t] = value
+    got, got_wd, _, _ = run_demand_gpu(topo, dem, s0)
+    assert on_path[0].any() and on_path[1].any() and np.isnan(got_wd)
+    assert np.array_equal(np.isnan(got), on_path[1])
+    assert np.array_equal(np.isposinf(got), on_path[0] & ~on_path[1])
+    rest = ~(on_path[0] | on_path[1])
+    assert np.array_equal(got[rest], load[rest])
+    topo.close()
+
+
 @pytest.mark.parametrize("nodes", [32, 33, 254, 255, 256])
 def test_deepest_levels(a2a, oracle, nodes):
     """Directed rings: as many levels as nodes.  Levels fit a byte, with one value for nodes not reached, up to 253."""

@@ -39,7 +39,20 @@ CASES = {
     "out of reach": (lambda: thinned(33333, 6, 10, 0.1), 3, 2048),
     "path counts past a word": (lambda: blown_up(gen.random_regular(7000, 5, 11), 3), 0, 2048),
     "path counts past 16 bits": (lambda: layered_rings(190, 7, 16), 2000, 2048),
+    "path counts past 12 bits, one source in LDS": (lambda: blown_up(gen.imase_itoh(14000, 3), 3), 39000, 2048),
+    "path counts past 13 bits, one source in LDS": (lambda: layered_rings(370, 7, 16), 1, 2048),
+    "sources without links": (lambda: gen.remove_arcs(gen.random_regular(24000, 5, 12), np.arange(100 * 5, 140 * 5)), 90, 2048),
 }
+
+
+def call_within(topo, s0, cnt, size):
+    import torch
+    ws = torch.full((size,), 0xff, dtype=torch.uint8, device="cuda")
+    load = torch.full((topo.E,), -7.0, dtype=torch.float64, device="cuda")
+    words = torch.full((2,), -7, dtype=torch.int64, device="cuda")
+    topo.link_loads(s0, cnt, load=load, dist_sum_total=words[:1], flags=words[1:], workspace=ws)
+    torch.cuda.synchronize()
+    return load, words
 
 
 @pytest.mark.parametrize("name", CASES)
@@ -57,6 +70,16 @@ def test_loads(oracle, name):
     topo.profile_enable(0)
     for a, b, c in zip(got, least, again):
         assert torch.equal(a, b) and torch.equal(a, c)
+    # a workspace of several groups but not all: a third of what the sources' rows take, behind a workgroup's records and the loads of groups
+    some = max(topo.workspace_bytes(cnt, a2a.WS_LOADS | a2a.WS_MINIMAL),
+               15 * topo.N * cnt // 3 + 256 * 6 * topo.N + cnt // 3 // 43 * topo.E * 8 + (8 << 20)) // 256 * 256
+    topo.profile_enable(1)
+    with_some = call_within(topo, s0, cnt, some)
+    pieces = topo.profile_read()["reduce"]["launches"]
+    topo.profile_enable(0)
+    assert 2 <= pieces // 2 <= 6, pieces  # (a launch for the loads and one for the totals each)
+    for a, b in zip(got, with_some):
+        assert torch.equal(a, b)
     # (sums of at most 2^27 positive terms in double precision)
     assert bool(((got[0] - ref[0]).abs() <= 1e-12 * ref[0]).all())
     assert torch.equal(got[1], ref[1])

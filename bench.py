@@ -9,7 +9,9 @@ Prints one JSON line.  TEPS = N * E / seconds (one traversed edge = one (source,
 
 The timed region holds the K steps and nothing else.  The per-kernel split (HIP events around every
 launch, on the stream the kernels run on) comes from two further, untimed steps; before them an untimed
-step through the level kernels counts the (source, link) pairs on shortest paths for the algorithmic bytes.
+step through the level kernels counts the (source, link) pairs on shortest paths for the bytes of their design.
+Bytes are what the kernels that run have to move (roofline, per_kernel); work_bytes is the level kernels' count
+whatever runs, a measure of work.
 Beside the metric: a plain 1 GiB device copy and fill (what this machine's HBM gives a streaming kernel),
 a2a_distances, a2a_link_loads_demand, a2a_sssp_loads, and the CPU oracle on a bounded sample (all cores and
 one core).
@@ -25,6 +27,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0
+FLOW_NODES = 20352  # up to here a whole source's coefs fit LDS; beyond, k_strip_sources takes them by strips
 
 
 # Profile classes of the library -> the kernel that runs them.  One k_fwd / k_bwd launch serves a level of
@@ -32,21 +35,34 @@ HBM_PEAK_GBPS = 8000.0
 KERNEL_NAME = {"bfs": "k_bfs_level", "offsets": "k_write_offsets", "fwd_rows": "k_fwd[rows]",
                "fwd_few": "k_fwd[few]", "fwd_spread": "k_fwd[spread]", "bwd_rows": "k_bwd[rows]",
                "bwd_few": "k_bwd[few]", "bwd_spread": "k_bwd[spread]", "reduce": "k_reduce_part",
-               "search": "k_wide_dist", "sources": "k_small_loads"}
+               "search": "k_wide_dist", "sources": "k_small_loads / k_node_loads"}
 # Where the search (or a source as a whole) runs in LDS, other kernels write the index entries and add up the loads.
 AFTER_SEARCH = {"offsets": "k_wide_index"}
 AFTER_SOURCES = {"reduce": "k_small_reduce"}
 AFTER_BOTH = {"sources": "k_flow_sources + k_flow_links", "reduce": "k_flow_reduce"}
-AFTER_BOTH_STRIPS = {"sources": "k_strip_sources + k_flow_links", "reduce": "k_flow_reduce"}  # more than 20352 nodes
+AFTER_BOTH_STRIPS = {"sources": "k_strip_sources + k_flow_links", "reduce": "k_flow_reduce"}  # more than FLOW_NODES
 FWD_CLASSES = ("fwd_rows", "fwd_few", "fwd_spread")
 BWD_CLASSES = ("bwd_rows", "bwd_few", "bwd_spread")
 
 
-def algorithmic_bytes(prof, dag_level, nb, E, steps):
-    """Algorithmic bytes per kernel class for one step.
+def partial_rows(N, degree, after_search):
+    """Rows of partial link loads, E doubles each, that the kernels with their state in LDS leave to the reduction in a pass over all
+    sources: one per workgroup, or one per group of sources where a search came before (as csrc/a2a_plan.h cuts them)."""
+    up = lambda a, b: (a + b - 1) // b
+    if not after_search:
+        return up(N, up(N, 256))
+    nodes = 6 if degree <= 4 else 4 if degree <= 8 else 2  # of a thread of k_flow_links
+    group = up(N, max(8, 256 // up(N, nodes * 1024) // 8 * 8))
+    if N > FLOW_NODES:
+        group = min(group, 256, max(128, N // 128))
+    return up(N, group)
 
-    Per reachable (source, node) pair: level tag 1 B written (BFS) + 1 B read (forward),
-    sigma 8 B written (forward) + 8 B read (backward), coef 8 B written (backward) = 26 B.
+
+def algorithmic_bytes(prof, dag_level, nb, N, E, degree, steps):
+    """Bytes that each kernel class has to move in one step.
+
+    Level kernels, whose state is in memory.  Per reachable (source, node) pair: level tag 1 B written (BFS) + 1 B read
+    (forward), sigma 8 B written (forward) + 8 B read (backward), coef 8 B written (backward) = 26 B.
     Per (source, shortest-path link): sigma gather 8 B (forward) + coef gather 8 B (backward).
     Per (batch, link): partial load 8 B written (backward, spread over its launches in
     proportion to their links) + 8 B read (ordered reduction).
@@ -54,9 +70,9 @@ def algorithmic_bytes(prof, dag_level, nb, E, steps):
     (backward) that level; which kernel class ran the level comes from the per-level timings.
     The forward launch of the deepest level also leaves coef = 1/sigma behind (no backward
     launch there): that level's own 16 backward bytes are charged to it.
-    A search of all levels in one launch is charged the level tags; a launch that takes its sources from the
-    search to the loads, all but the reduction (that launch keeps the state in LDS: its bytes are a measure of the
-    work, not of traffic).
+
+    Kernels with their state in LDS.  Per pair, where a search comes before: level tag 1 B written + 1 B read, a word of 2 B (4 B up to
+    20352 nodes) and the coef 8 B written by one kernel and read by the next.  Per row of partial loads and link: 8 B written + 8 B read.
     """
     L = len(prof["pairs_level"])
     pairs = [p / steps for p in prof["pairs_level"]]       # per step
@@ -65,6 +81,15 @@ def algorithmic_bytes(prof, dag_level, nb, E, steps):
     dag_total = max(sum(dag_in), 1)
     ran = {k: [ms > 0 for ms in prof[k]["ms_level"]] for k in KERNEL_NAME}
     out = {k: 0.0 for k in KERNEL_NAME}
+    search = prof["search"]["launches"] > 0
+    if prof["sources"]["launches"]:
+        rows = partial_rows(N, degree, search)
+        if search:
+            out["search"] = 1.0 * sum(pairs)
+            out["sources"] = (1 + 2 * ((2 if N > FLOW_NODES else 4) + 8)) * sum(pairs)
+        out["sources"] += 8.0 * rows * E
+        out["reduce"] = 8.0 * (rows + 1) * E
+        return out
     for l in range(L):
         if ran["bfs"][l]:
             out["bfs"] += 1 * pairs[l]
@@ -78,16 +103,20 @@ def algorithmic_bytes(prof, dag_level, nb, E, steps):
             out[bwd] += own + links
         elif fwd:  # deepest level: the forward launch leaves coef = 1/sigma, nothing runs backward
             out[fwd] += own
-        if prof["sources"]["launches"]:
-            out["sources"] += (2 + 8) * pairs[l] + 8 * dag_in[l] + own + links
-        elif prof["search"]["launches"]:
+        if search:
             out["search"] += 1 * pairs[l]
     out["reduce"] = 8.0 * nb * E
     return out
 
 
+def work_bytes(prof, dag_level, nb, E, steps):
+    """The level kernels' count for the whole pass, whatever kernels ran: with kernels that keep their state in LDS a measure of the
+    work done, not of bytes that move."""
+    return 26.0 * sum(prof["pairs_level"]) / steps + 16.0 * sum(dag_level) + 16.0 * nb * E
+
+
 def layout_bytes(prof, dag_level, nb, E, steps, narrow_levels):
-    """The same count with the bytes the chosen layout moves: path counts of a level kept in single precision
+    """The same count with the bytes that the level kernels' layout moves: path counts of a level kept in single precision
     (bit l+1 of narrow_levels: level l is) cost 4 bytes where the algorithmic count has 8."""
     L = len(prof["pairs_level"])
     narrow = [True] + [bool((narrow_levels >> (l + 1)) & 1) for l in range(L - 1)]
@@ -164,6 +193,7 @@ def main():
               "ordered sum of E doubles at the end). Use --gpus 1.", file=sys.stderr)
         sys.exit(2)
 
+    import numpy as np
     import torch
     import a2a_inputs as gen
     import paper_2309_13541_amd as a2a
@@ -241,13 +271,14 @@ def main():
 
     steps = prof_steps  # the per-kernel figures come from the profiled steps
     nb = (N + 63) // 64
-    alg = algorithmic_bytes(prof, dag_level, nb, E, steps)
+    degree = int(max(np.bincount(col).max(), np.diff(rp).max()))
+    alg = algorithmic_bytes(prof, dag_level, nb, N, E, degree, steps)
     cfg = args.config
     names = dict(KERNEL_NAME)
     if prof["search"]["launches"]:
         names.update(AFTER_SEARCH)
     if prof["sources"]["launches"]:
-        names.update((AFTER_BOTH_STRIPS if N > 20352 else AFTER_BOTH) if prof["search"]["launches"] else AFTER_SOURCES)
+        names.update((AFTER_BOTH_STRIPS if N > FLOW_NODES else AFTER_BOTH) if prof["search"]["launches"] else AFTER_SOURCES)
     per_kernel = {}
     for k, name in names.items():
         ms, n = prof[k]["ms"], prof[k]["launches"]
@@ -267,7 +298,9 @@ def main():
     k_ms = g_ms[kname] / steps                            # per step
     achieved = k_alg / (k_ms * 1e-3) / 1e9
     alg_total = sum(alg.values())
-    lay_total = layout_bytes(prof, dag_level, nb, E, steps, prof["narrow_levels"])
+    in_lds = prof["sources"]["launches"] > 0
+    lay_total = alg_total if in_lds else layout_bytes(prof, dag_level, nb, E, steps, prof["narrow_levels"])
+    work_total = work_bytes(prof, dag_level, nb, E, steps)
     traffic = read_traffic(cfg, kname)
     # the single longest launch of that kernel (one BFS level), with its own bytes
     longest = None
@@ -280,7 +313,7 @@ def main():
         c, l, x = longest
         one = {k: dict(v, ms_level=[m if (k == c and i == l) else 0.0 for i, m in enumerate(v["ms_level"])])
                if isinstance(v, dict) and "ms_level" in v else v for k, v in prof.items()}
-        a_one = algorithmic_bytes(one, dag_level, nb, E, steps)[c]
+        a_one = algorithmic_bytes(one, dag_level, nb, N, E, degree, steps)[c]
         ms_one = x / steps
         longest_launch = {"kernel": f"{kname} level {l} ({c.split('_')[1]})", "ms": ms_one, "alg_bytes": a_one,
                           "achieved": a_one / (ms_one * 1e-3) / 1e9, "frac": a_one / (ms_one * 1e-3) / 1e9 / HBM_PEAK_GBPS,
@@ -296,6 +329,7 @@ def main():
                        "frac": alg_total / sec / 1e9 / HBM_PEAK_GBPS,
                        "frac_of_copy": alg_total / sec / 1e9 / copy_gbps,
                        "layout_bytes": lay_total, "layout_frac": lay_total / sec / 1e9 / HBM_PEAK_GBPS,
+                       "work_bytes": work_total, "work_over_peak": work_total / sec / 1e9 / HBM_PEAK_GBPS,
                        "traffic": read_traffic(cfg, "whole_step")},
         "per_kernel": per_kernel,
     }

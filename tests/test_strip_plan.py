@@ -2,6 +2,7 @@
 depths and over workspaces: no device needed."""
 import os
 import subprocess
+import sys
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -72,3 +73,32 @@ def test_layouts_over_their_range(tmp_path):
     out = subprocess.run([str(exe)], capture_output=True, text=True, timeout=120)
     print(out.stdout)
     assert out.returncode == 0, out.stdout
+
+
+ROWS = r"""
+#include <cstdio>
+#include <cstdlib>
+#include "a2a_plan.h"
+using namespace a2a_dev;
+
+int main(int argc, char** argv) {  // nodes, words of the link table, deepest level; 1: after a search
+  const int N = std::atoi(argv[1]), words = std::atoi(argv[2]), depth = std::atoi(argv[3]);
+  if (std::atoi(argv[4]) != 0)
+    std::printf("%d", flow_groups(N, words, N, N > kFlowNodes).groups);
+  else
+    std::printf("%d", node_fits(N, words, depth, N) ? node_cut(N, N).workgroups : small_cut(N, depth, words, N, SmallWhat::kLoads).workgroups);
+}
+"""
+
+
+def test_rows_of_partial_loads_that_the_benchmark_counts(tmp_path):
+    sys.path.insert(0, ROOT)
+    import bench
+    src, exe = tmp_path / "rows.cpp", tmp_path / "rows"
+    src.write_text(ROWS)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", os.path.join(ROOT, "paper_2309_13541_amd", "csrc"), str(src), "-o", str(exe)],
+                   check=True, timeout=120)
+    for nodes, degree, words, depth, search in ((64, 4, 2, 8, 0), (1024, 10, 5, 10, 0), (4096, 6, 3, 24, 0), (16384, 4, 2, 7, 1), (20352, 6, 3, 7, 1),
+                                                (20353, 6, 3, 7, 1), (40000, 16, 8, 5, 1), (65536, 8, 4, 7, 1)):
+        rows = subprocess.run([str(exe), str(nodes), str(words), str(depth), str(search)], check=True, capture_output=True, text=True, timeout=60).stdout
+        assert bench.partial_rows(nodes, degree, bool(search)) == int(rows), (nodes, degree)

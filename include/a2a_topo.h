@@ -34,9 +34,10 @@
  *     aborts or prints.  On error the outputs are unspecified.
  *   - Sources are processed in batches of 64 (one bit of a 64-bit mask per source); several
  *     batches advance level by level together, as many as the workspace holds.
- *   - All arithmetic is in double precision.  Inside the workspace the path counts of BFS level
- *     l are kept as floats while (largest in-degree)^l < 2^24, i.e. while every one of them is
- *     certain to be a whole number that a float holds exactly; results do not depend on it.
+ *   - All arithmetic is in double precision.  Inside the workspace and the kernels path counts
+ *     are kept in less (floats, whole numbers of 12, 13 or 24 bits) while (largest
+ *     in-degree)^level says that every one of them is a whole number that fits, or with a place
+ *     for the exact count of those that do not; results do not depend on it.
  */
 #ifndef A2A_TOPO_H
 #define A2A_TOPO_H
@@ -97,9 +98,11 @@ int a2a_topo_info(const a2a_topo* topo, int32_t* N, int64_t* E, int32_t* dmax, i
 
 /*
  * Bytes of device workspace for a call over src_count sources.  With A2A_WS_MINIMAL the
- * smallest size the call accepts; otherwise the size at which all ceil(src_count/64) batches
- * advance together (fewest kernel launches).  Any size in between is used as well as it can
- * be.  Returns 0 on bad arguments.  The workspace must be 256-byte aligned.
+ * smallest size the call accepts; otherwise the size at which all sources go at once (fewest
+ * kernel launches): all ceil(src_count/64) batches advance together, and link loads of small
+ * topologies, where a workgroup takes its sources from the search to their loads, have a row of
+ * partial loads for every workgroup.  Any size in between is used as well as it can be.
+ * Returns 0 on bad arguments.  The workspace must be 256-byte aligned.
  */
 size_t a2a_workspace_bytes(const a2a_topo* topo, int32_t src_count, int flags);
 

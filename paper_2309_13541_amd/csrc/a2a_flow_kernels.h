@@ -480,7 +480,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
 // as it goes into LDS; others come from memory, where they wait in the row of the output.
 // A source of 65536 nodes of degree 8 takes 540 thousand cycles: sort 53, forward 102, levels of few nodes 25, level 6 into LDS 62, levels 5
 // and 4 into LDS 30, the sums over strips 109, waiting for each other and for records around a strip 76, what a level is by itself 58.
-// Vector ALUs are busy 42, LDS 38 % of the time, and 1.5 MB are read and 1.6 written a source (3.8 TB/s): bound by chains within
+// Vector ALUs are busy 42, LDS 38 % of the time, and 1.6 MB are read and as much is written a source (3.9 TB/s): bound by chains within
 // a piece (links, gathers, sum) and by what a strip begins and ends with.  Memory requests come back in order, so queue
 // entries, which miss L2, are asked for many at a time (a call 80, now 77 ms), and the first strip's coefs do not go through
 // memory (77, now 75).  Link tables that have a node's links by strips took less LDS time, but 4 MB more in L2: 97 ms, 80 without.

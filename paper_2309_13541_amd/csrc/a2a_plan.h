@@ -19,7 +19,7 @@ constexpr size_t kPooledBytes = 2u << 20, kStagedBytes = 4u << 20;
 // place where the upload is put together.  That copy stays for as long as the handle, so a larger upload goes from the
 // caller's and the builder's arrays, piece by piece.  Handles made one after the other, through pinned memory and from
 // the arrays: 16384 nodes of degree 8 (2.2 MB) 1.41 and 1.51 ms, 65536 of degree 8 (7.9 MB) 15.9 and 16.0 ms (the first
-// of a process 19.7 and 16.7).
+// of a process 19.7 and 16.7); with the table of out-links, which all topologies have by now, 8.9 MB and 16.1 ms.
 enum HandlePart { kOutPtr, kOutCol, kInPtr, kInCol, kInLink, kEllOut, kEllIn, kArrived, kHandleParts };
 struct HandleBlocks {
   size_t at[kHandleParts] = {}, bytes[kHandleParts] = {};
@@ -220,7 +220,7 @@ inline NodeCut node_cut(int N, int src_count) {
 // Which calls take it.  k_small_loads goes over the levels of several sources at a time, and every level only over its own nodes; here
 // each source has its levels to itself, and every node without a level looks at its links.  So it is the faster one up to so many
 // levels, the fewer the more sources a workgroup has and where a thread has two nodes (us, k_small_loads and this, at the edges):
-//   a node a thread.  One and two sources of a workgroup, any levels: 256 nodes of degree 8 13.0, 9.9; 8x128 torus (68 levels) 59.9,
+//   a node a thread.  One and two sources of a workgroup, any levels: 256 nodes of degree 8 12.7, 9.5; 8x128 torus (68 levels) 59.9,
 //     47.1; bidirectional ring of 500 (250) 155, 121.  Three, 15 levels: 10x10x10 torus 31.8, 30.8; 22 and more not: 24x24 torus (24)
 //     26.5, 28.8.  Four, 10: hypercube of 1024 38.7, 38.0, with a fifth of its links gone 39.1, 39.0, 5x5x6x6 torus 32.0, 32.4; 4x4x8x8
 //     torus (12) 34.3, 35.1, 10x10x10 (15) 36.6, 39.1.
@@ -372,7 +372,7 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips =
   g.group = (src_count + most - 1) / most;
   // By strips a source takes up to a megabyte of workspace, and what of a call fits it may be few groups, so they are smaller, at the price of
   // as many partial loads (65536 nodes of degree 8, with groups as above and these: 4096 sources in 1 GB 11.4, 7.7 ms; groups of 128 for all
-  // 65536 sources 75.9, of 256 74.4 ms, in 1 GB 119 and 170, in 4 GB 82 and 82; of 50000 of a generalized Kautz topology of degree 5, 30.6, 29.6 ms).
+  // 65536 sources 75.9, of 256 74.4 ms, in 1 GB 119 and 152, in 4 GB 82 and 82; of 50000 of a generalized Kautz topology of degree 5, 30.6, 29.6 ms).
   if (strips) g.group = std::min(g.group, std::min(256, std::max(128, src_count / 128)));
   g.groups = (src_count + g.group - 1) / g.group;
   return g;

@@ -696,8 +696,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
 // out-neighbours, and what each link brought, times the path count, is its load.  Values of even and of odd levels lie in two arrays, 0
 // where there is none: a node without a level at level l has in-links from level l - 1 or later, and the later ones are not in
 // the array of the level before; out-links of level l lead to levels up to l + 1, and those below l are not yet written.
-// Bound by the chain of a level: gathers, sum, store, barrier.  Whole calls, k_small_loads and this: 8x8 torus 10.8, 9.7 us, 256 nodes of
-// degree 8 13.0, 9.9, 512 of degree 4 16.4, 13.0, 1000 of degree 8 35.3, 31.5; where that is over: node_fits.
+// Bound by the chain of a level: gathers, sum, store, barrier (hypercube of 1024 nodes: waves wait half of the time, vector ALUs are busy
+// 27, LDS 32 % of it).  Whole calls, k_small_loads and this, in a replayed graph: 8x8 torus 10.3, 6.2 us, 256 nodes of degree 8 12.7, 9.5,
+// 512 of degree 4 16.2, 13.0, 1000 of degree 8 34.7, 31.2; one by one the smallest take as long as the host takes to launch them (8x8 torus
+// 11.5 us for both).  Where k_small_loads is the faster one: node_fits.
 template <int KS, int kNodes, bool kDemand>
 __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   extern __shared__ double s_small[];

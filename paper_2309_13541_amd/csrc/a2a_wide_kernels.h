@@ -6,9 +6,9 @@
 // topology in LDS (a bit per node and source, 128 KB at the most): the reads per link stay in the compute unit.
 // Bound by those reads (7.7 cycles for a wave's 64 in the search for link loads, where LDS gives random words in 7.3) and
 // by the stores of the matrix.  Whole matrix with its sums, before and after, into the same buffers from call to call: 65536
-// nodes of degree 8 12.4 -> 4.15 ms (4.1 TB/s of stores; 4.4 to 4.6 ms where the 17 GB are others on every call), 20011 of
-// degree 5 1.31 -> 0.56 ms, 16384 of degree 4 0.79 -> 0.29 ms, torus 25x25x26 2.09 -> 0.65 ms; sums alone of 65536 nodes
-// 8.45 -> 3.62 ms.
+// nodes of degree 8 12.4 -> 3.98 ms (4.3 TB/s of stores; 4.1 ms where the 17 GB are others on every call), 20011 of
+// degree 5 1.31 -> 0.54 ms, 16384 of degree 4 0.79 -> 0.28 ms, torus 25x25x26 2.09 -> 0.65 ms; sums alone of 65536 nodes
+// 8.45 -> 2.31 ms.
 #pragma once
 
 #include <utility>
@@ -105,7 +105,8 @@ __device__ __forceinline__ bool wide_steps_while(F&& f, std::index_sequence<I...
 // The first levels have few new nodes.  While those of the level before fit a list (wide_list), they are what is gone over: their
 // R_{l-1} is ORed into the words of their out-neighbours, those that gain by it are the next list (a node once for every
 // link that brought something), and a thread finds R_l of its own there.  65536 nodes of degree 8: four of seven levels, some 20
-// thousand cycles each where the others take 66; sums alone 3.57, now 2.32 ms, with distances 4.43, now 4.12 (the stores).
+// thousand cycles each where the others take 66; sums alone 3.57, now 2.31 ms, with distances 4.09, now 3.98 into the
+// same buffers, 4.41, now 4.07 into others on every call (the stores).
 // kOut: what is wanted.  kWideMasks: the newly reached of every level 1..depth, [groups][depth][slots][kWideThreads].
 // kScaled: the table has 8 x id (up to 8191 nodes; 64 sources a word only).
 enum { kWideDist, kWideBytes, kWideMasks };

@@ -997,6 +997,19 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
       c.pair[k] = *reinterpret_cast<const double2*>(fv.coef + (size_t)s * (size_t)fv.stride + (size_t)pair(k));
     flow_in_order();
   };
+  // Where LDS has no room for two sources' words, the next one's are asked for into L2 meanwhile, a word of each line, the lines shared
+  // out among the group's blocks.  Staged from memory itself they kept a workgroup waiting for half of its time (8192 sources of 65536
+  // nodes of degree 8 2350 us here, now 1740; without staging 1330, without gathers still 2310; whole calls over 4096 sources 5.05, now 4.74 ms,
+  // 50000 nodes of a generalized Kautz topology of degree 5 2.66, 2.51; two sources ahead the same).  Where two sources fit, the next one's are
+  // staged a step ahead, and this gains nothing (16384 nodes of degree 4 617, 645 us).
+  constexpr uint32_t kLine = 128;
+  const uint32_t lines = row_bytes / kLine, share = (lines + (uint32_t)blocks - 1) / (uint32_t)blocks;
+  const uint32_t line = (uint32_t)(place % blocks) * share + (uint32_t)t;
+  uint32_t touched = 0;
+  const auto touch = [&](int s) {
+    if ((uint32_t)t < share && line < lines)
+      touched = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(fv.count) + (size_t)s * row_bytes + kLine * line);
+  };
   // A node's words are asked for before the last one's are worked on, where there are registers for both.
   constexpr int kAhead = KS == 4 || KS == 8 ? 0 : 1;
   struct Got {
@@ -1007,7 +1020,12 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_links(FlowView fv) {
     __syncthreads();
     const int escaped = kHalves ? fv.escaped[s] : 0;
     const uint32_t* const exact = fv.exact + (kHalves ? (size_t)s * (size_t)fv.stride : 0);
+    if (single) asm volatile("" ::"v"(touched));
     if (s + 1 < s_last) request(s + 1, buffer - here, next);
+    if (single && s + 1 < s_last) {
+      touch(s + 1);
+      flow_in_order();
+    }
     const auto gather = [&](int u, Got& g) {
       const int k = u / 2, i = u % 2;
 #pragma unroll

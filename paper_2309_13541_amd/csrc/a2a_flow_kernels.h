@@ -17,7 +17,7 @@ namespace a2a_dev {
 struct FlowView {
   const uint32_t *in, *out;    // link tables, as in SmallView
   const unsigned char* level;  // [sources][small_level_bytes(N)]
-  void* record;                // [workgroups of k_flow_sources] FlowRecords
+  void* record;                // [workgroups of k_flow_sources] nodes of a source, level by level, 16 bits each
   uint32_t* count;             // [sources][stride] FlowWord
   double* coef;                // [sources][stride]; demands before (k_flow_demand)
   double* weighted;            // [sources] demand x distance
@@ -30,15 +30,6 @@ struct FlowView {
   // By strips of nodes (k_strip_sources): `count` has 16 bits a node.
   uint32_t* exact;             // [sources][stride] path counts that those do not hold
   int* escaped;                // [sources] whether there are any
-};
-
-// A node as the forward sweep leaves it to the backward one, in the order in which levels are gone over.
-// In memory the values of a workgroup's source come first, the nodes behind them, 16 bits each.
-template <bool kDemand>
-struct FlowRecord {
-  using Value = std::conditional_t<kDemand, double, uint32_t>;
-  uint32_t node;
-  Value value;  // path count, demand / path count
 };
 
 typedef uint32_t FlowWords __attribute__((ext_vector_type(4)));
@@ -220,10 +211,13 @@ struct FlowPiece {
 // the backward sweep a double per node, 0 until it is written: a node of level l has out-links to levels up to l + 1, of which only
 // l + 1 and (some of) l are written, so even levels are kept with a plus sign and odd ones with a minus sign, and a level adds up
 // the entries of the other sign only.  Coefs of unequal demands have any sign: even and odd levels have an array each.
-// The nodes' order goes through memory from one sweep to the other, with what the backward sweep needs of a node (its coefs take
-// the place of the queue); that is read three pieces ahead, links one piece ahead.  It is kept small so that the 32 workgroups of an
-// XCD find theirs in its L2: with 16 bytes a node, now 10, 8191 nodes of degree 8 with demands took 891 us here, now 765 (1598
-// MB read, now 1013); 20011 of degree 5, 8 bytes, now 6, 386, now 375.  Rows of the outputs are written from LDS, in node order.
+// The nodes' order goes through memory from one sweep to the other; it is read three pieces ahead, links one piece ahead.  With
+// demands, demand / path count goes with it.  Without, the path count stays in LDS, in the low word of the double that the backward sweep has
+// of a node: below 2^-1022, it changes no sum of coefs, all of which are above 2^-25, and not 1 / count either.  So the forward
+// sweep stores nothing in memory, whose pieces would wait for what the piece before has stored, and 2 bytes a node make the way that took 6:
+// 16384 nodes of degree 4 1646, now 1516 us here; 20011 of degree 5 364, 360.  (All of it read again by node from the output rows 1791,
+// 414; with demands, 8191 of degree 8 774, 938, and with quotients and nodes stored after the sweep 801.)  Rows of the outputs are written from
+// LDS, in node order.
 // Bound by the chain of a piece (links, gathers, sum, barrier at the end of a level), which the four waves of a SIMD hide in part: a
 // source of 16384 nodes of degree 4 takes 57 thousand cycles, sort 9.7, forward 15, backward 23, rows and zeroes 9; vector
 // ALUs and LDS are busy about half of the time each.  Pushing counts to the out-links by LDS additions where that touches fewer
@@ -232,7 +226,6 @@ struct FlowPiece {
 // kScaled: the tables have 8 x id.
 template <int KS, bool kScaled, bool kDemand>
 __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
-  using Record = FlowRecord<kDemand>;
   extern __shared__ double s_small[];
   using Row = FlowRow<KS, kScaled>;
   const int t = (int)threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(t / kWave);
@@ -245,10 +238,10 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   // behind all that, so that places in the arrays at the start need no addition
   double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_source_lds(N, fv.depth, kDemand) - kFlowTail);
   uint32_t* const s_totals = reinterpret_cast<uint32_t*>(s_weighted + kWideThreads / kWave);
-  using Value = typename Record::Value;
-  Value* const record = reinterpret_cast<Value*>(static_cast<char*>(fv.record) + (size_t)blockIdx.x * flow_record_bytes(S, kDemand));
-  unsigned short* const record_node = reinterpret_cast<unsigned short*>(record + S);
+  unsigned short* const queue = reinterpret_cast<unsigned short*>(static_cast<char*>(fv.record) + (size_t)blockIdx.x * flow_record_bytes(S, kDemand));
+  double* const value = reinterpret_cast<double*>(queue + S);  // demand / path count, with demands
   constexpr int kId = kScaled ? 3 : 0;  // table entries are ids << kId
+  constexpr uint32_t kCount = (1u << kFlowLevel) - 1u;
   long long dsum = 0, reached = 0;
   uint32_t lv[kFlowWords];
   const auto levels = [&](int s) {  // of a source
@@ -297,9 +290,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       c.next(starts);
       const uint32_t q0 = 4u * (uint32_t)S + 2u * (uint32_t)t, q1 = 4u * (uint32_t)S + 2u * last;
       const auto node = [&](const FlowPiece<1>& p) {
-        uint32_t n = lds_get<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
-        asm volatile("" : "+v"(n));  // widened as it is read, not again where it is used
-        return n;
+        return (uint32_t)lds_get<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
       };
       struct Ahead {
         uint32_t node;
@@ -310,7 +301,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       const auto step = [&](Ahead& here, Ahead& next) {
         flow_arrived(here.row);
         next.row.load(fv.in, next.node);
-        const uint32_t then = node(c);
+        uint32_t then = node(c);
         if (t < a.end - a.base) {
           uint32_t y[2 * KS];
 #pragma unroll
@@ -323,18 +314,15 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) sum += flow_count(y[j], before);
           lds_put<uint32_t>(Row::template own<2>(here.node), sum + above);
-          Value value;
           if constexpr (kDemand) {
-            value = own * recip((double)sum);
+            const uint32_t at = (uint32_t)(a.base + t);
+            value[at] = own * recip((double)sum);
+            queue[at] = (unsigned short)here.node;
             wd = __builtin_fma((double)a.level, own, wd);
-          } else {
-            value = sum;
           }
-          const uint32_t at = (uint32_t)(a.base + t);
-          record[at] = value;
-          record_node[at] = (unsigned short)here.node;
         }
-        if (b.level != a.level) __syncthreads();
+        if (b.level != a.level) lds_barrier();
+        asm volatile("" : "+v"(then));  // widened as it is read, not again where it is used
         here.node = then;
         a = b;
         b = c;
@@ -355,17 +343,39 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       wd = wave_sum_double(wd);
       if (lane == 0) s_weighted[wave] = wd;
     }
+    // Path counts leave, and a node's waits for it in the low word of its place in the backward sweep: as a double less than 2^-1022 and so
+    // nothing beside a coef.
     uint32_t* const count = fv.count + (size_t)s * (size_t)S;
-    for (int i = t; i < S / 4; i += kWideThreads)
-      __builtin_nontemporal_store(reinterpret_cast<const FlowWords*>(x)[i], reinterpret_cast<FlowWords*>(count) + i);
+    for (int i = t; i < S / 8 && !kDemand; i += kWideThreads) reinterpret_cast<FlowWords*>(queue)[i] = reinterpret_cast<const FlowWords*>(q)[i];
+    FlowWords words_of[kFlowWords];
+#pragma unroll
+    for (int k = 0; k < kFlowWords; ++k) {
+      const int i = t + k * kWideThreads;
+      if (i < S / 4) {
+        words_of[k] = reinterpret_cast<const FlowWords*>(x)[i];
+        __builtin_nontemporal_store(words_of[k], reinterpret_cast<FlowWords*>(count) + i);
+      }
+    }
     __syncthreads();
     if (kDemand && t == 0) {
       wd = 0.0;
       for (int k = 0; k < kWideThreads / kWave; ++k) wd += s_weighted[k];
       fv.weighted[s] = wd;
     }
-    for (int i = t; i < (kDemand ? S : S / 2); i += kWideThreads) reinterpret_cast<double2*>(s_small)[i] = make_double2(0.0, 0.0);
-    __syncthreads();
+    if (kDemand) {
+      for (int i = t; i < S; i += kWideThreads) reinterpret_cast<double2*>(s_small)[i] = make_double2(0.0, 0.0);
+    } else {
+#pragma unroll
+      for (int k = 0; k < kFlowWords; ++k) {
+        const int i = t + k * kWideThreads;
+        if (i < S / 4) {
+          reinterpret_cast<FlowWords*>(s_small)[2 * i] = FlowWords{words_of[k].x & kCount, 0, words_of[k].y & kCount, 0};
+          reinterpret_cast<FlowWords*>(s_small)[2 * i + 1] = FlowWords{words_of[k].z & kCount, 0, words_of[k].w & kCount, 0};
+        }
+      }
+    }
+    lds_barrier();
+    if (!kDemand && t == 0) s_small[fv.source0 + s] = 0.0;
 
     if (s + (int)gridDim.x < fv.sources) levels(s + (int)gridDim.x);
     if (deep > 0) {  // backward
@@ -377,33 +387,34 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       c.next(starts);
       d = c;
       d.next(starts);
+      struct Entry {
+        uint32_t node;
+        double value;
+      };
       const auto read = [&](const FlowPiece<-1>& p) {
         const uint32_t at = min((uint32_t)t + (uint32_t)p.base, last);
-        Record r;
-        r.value = record[at];
-        r.node = record_node[at];
-        return r;
+        Entry e;
+        e.value = kDemand ? lds_at(value, 8u * at) : 0.0;
+        e.node = queue[at];
+        return e;
       };
-      const auto step = [&](const Record& here, const Record& next, Record& third, Row& row, Row& next_row) {
+      const auto step = [&](const Entry& here, const Entry& next, Entry& third, Row& row, Row& next_row) {
         flow_arrived(row);
         next_row.load(fv.out, next.node);
         flow_in_order();
         third = read(d);
         flow_in_order();
         if (t < a.end - a.base) {
-          double sum;
-          if constexpr (kDemand)
-            sum = here.value;
-          else
-            sum = recip((double)here.value);
           const bool odd = (a.level & 1) != 0, inner = a.level < deep;  // the last level has no successors
           const uint32_t from = kDemand && !odd ? 8u * (uint32_t)S : 0u, to = kDemand && odd ? 8u * (uint32_t)S : 0u;
+          const uint32_t paths = kDemand ? 0u : lds_get<uint32_t>(Row::template own<3>(here.node));
           double y[2 * KS];
           if (inner) {
 #pragma unroll
             for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<double>(row.template at<3>(j) + from);
           }
           __builtin_amdgcn_sched_barrier(0);
+          double sum = kDemand ? here.value : recip((double)paths);
           if (kDemand) {
             if (inner) {
               double succ = y[0];
@@ -427,13 +438,13 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
           }
           lds_put<double>(Row::template own<3>(here.node) + to, sum);
         }
-        if (b.level != a.level) __syncthreads();
+        if (b.level != a.level) lds_barrier();
         a = b;
         b = c;
         c = d;
         d.next(starts);
       };
-      Record e0 = read(a), e1 = read(b), e2, e3;
+      Entry e0 = read(a), e1 = read(b), e2, e3;
       Row w0, w1;
       w0.load(fv.out, e0.node);
       flow_in_order();  // as in the steps: links, then a node
@@ -449,6 +460,8 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
         step(e3, e0, e2, w1, w0);
         if (a.level < 1) break;
       }
+    } else {
+      lds_barrier();
     }
 #pragma unroll
     for (int k = 0; k < kFlowWords; ++k) asm volatile("" : "+v"(lv[k]));  // arrived before anything is stored: a wait for them later on would be one for the stores too

@@ -357,8 +357,8 @@ constexpr size_t strip_link_lds(int N) { return (size_t)flow_stride(N) * (strip_
 // A workgroup's queue: nodes of 16 bits, then nodes with their path counts, 32 bits.
 constexpr size_t strip_record_bytes(int stride) { return (size_t)stride * 6; }
 
-// A workgroup's records between the two sweeps: a path count, or 8 bytes with demands, and a 16-bit node per place.
-constexpr size_t flow_record_bytes(int stride, bool demand) { return (size_t)stride * (demand ? 10 : 6); }
+// A workgroup's queue between the two sweeps: a 16-bit node per place, with demands 8 bytes more.
+constexpr size_t flow_record_bytes(int stride, bool demand) { return (size_t)stride * (demand ? 10 : 2); }
 
 // How the sources of a call are grouped: depends on the topology and their number only.  A workgroup of k_flow_links keeps the
 // loads of a block of links over a group, and the groups are added up in order; about one workgroup per compute unit.

@@ -211,20 +211,21 @@ struct FlowPiece {
 // the backward sweep a double per node, 0 until it is written: a node of level l has out-links to levels up to l + 1, of which only
 // l + 1 and (some of) l are written, so even levels are kept with a plus sign and odd ones with a minus sign, and a level adds up
 // the entries of the other sign only.  Coefs of unequal demands have any sign: even and odd levels have an array each.
-// The nodes' order goes through memory from one sweep to the other; it is read three pieces ahead, links one piece ahead.  With
-// demands, demand / path count goes with it.  Without, the path count stays in LDS, in the low word of the double that the backward sweep has
-// of a node: below 2^-1022, it changes no sum of coefs, all of which are above 2^-25, and not 1 / count either.  So the forward
-// sweep stores nothing in memory, whose pieces would wait for what the piece before has stored, and 2 bytes a node make the way that took 6:
-// 16384 nodes of degree 4 1646, now 1516 us here; 20011 of degree 5 364, 360.  (All of it read again by node from the output rows 1791,
-// 414; with demands, 8191 of degree 8 774, 938, and with quotients and nodes stored after the sweep 801.)  Rows of the outputs are written from
-// LDS, in node order.
-// Bound by the chain of a piece (links, gathers, sum, barrier at the end of a level), which the four waves of a SIMD hide in part: a
-// source of 16384 nodes of degree 4 takes 57 thousand cycles, sort 9.7, forward 15, backward 23, rows and zeroes 9; vector
-// ALUs and LDS are busy about half of the time each.  Pushing counts to the out-links by LDS additions where that touches fewer
-// nodes took longer (48 for 26 thousand cycles forward, 20011 nodes of degree 5), and so did links asked for three pieces ahead (20
-// for 14 thousand).
+// The nodes' order stays in LDS where there is room (kStays, flow_stays), else it goes through memory; it is read three pieces ahead, links
+// one piece ahead.  With demands, demand / path count goes with it.  Without, the path count stays in LDS, in the low word of the
+// double that the backward sweep has of a node: below 2^-1022, it changes no sum of coefs, all of which are above 2^-25.  So the forward
+// sweep stores nothing in memory: its pieces waited for what the one before had stored, 6 bytes a node.  Whole calls with that, with the order
+// through memory, and with it in LDS: 16384 nodes of a generalized Kautz topology of degree 4 2261, 2120 us, -; 20000 of degree 4 3902, 3706, -;
+// 13000 of a generalized Kautz topology of degree 7 1524, 1463, 1442; 14000 of degree 5 2078, 2066, 2034; 12000 of degree 6 1426, 1442, 1425;
+// 9000 of degree 6 937, 956, 943.  (Path counts read again by node from the output rows: 16384 nodes 1646 us here, then 1791; with
+// demands, quotients stored after the sweep: 8191 of degree 8 774, 801.)  Rows of the outputs are written from LDS, in node order.
+// Bound by the instructions of a piece and its barriers, which the four waves of a SIMD hide in part: 16384 nodes of degree 4 took 1640 us
+// with record stores, forward 490, backward 540, sort 240, rows and zeroes 280; with gathers from the thread's own place in LDS, or
+// without any, 1600 and more, without any access to memory 1410.  Two nodes a thread and piece, their gathers at the same time: 2 to 6 % slower.
+// Pushing counts to the out-links by LDS additions where that touches fewer nodes took longer (48 for 26 thousand cycles
+// forward, 20011 nodes of degree 5), and so did links asked for three pieces ahead (20 for 14 thousand).
 // kScaled: the tables have 8 x id.
-template <int KS, bool kScaled, bool kDemand>
+template <int KS, bool kScaled, bool kDemand, bool kStays>
 __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   extern __shared__ double s_small[];
   using Row = FlowRow<KS, kScaled>;
@@ -232,8 +233,9 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   const int N = fv.N, S = fv.stride, nl = (int)small_level_bytes(N);
   const int words = (N + 4 * kWideThreads - 1) / (4 * kWideThreads), v0 = 4 * words * t;  // this thread's nodes in the sort
   uint32_t* const x = reinterpret_cast<uint32_t*>(s_small);
-  unsigned short* const q = reinterpret_cast<unsigned short*>(x + S);
-  unsigned short* const base = q + S + kFlowSpare;
+  const uint32_t q_at = (kStays ? 8u : 4u) * (uint32_t)S;
+  unsigned short* const q = reinterpret_cast<unsigned short*>(reinterpret_cast<char*>(s_small) + q_at);
+  unsigned short* const base = kStays && flow_gap(N, fv.depth) ? reinterpret_cast<unsigned short*>(x + S) : q + S + kFlowSpare;
   double* const demand = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_demand_at(N, fv.depth));
   // behind all that, so that places in the arrays at the start need no addition
   double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_source_lds(N, fv.depth, kDemand) - kFlowTail);
@@ -288,7 +290,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       b.next(starts);
       c = b;
       c.next(starts);
-      const uint32_t q0 = 4u * (uint32_t)S + 2u * (uint32_t)t, q1 = 4u * (uint32_t)S + 2u * last;
+      const uint32_t q0 = q_at + 2u * (uint32_t)t, q1 = q_at + 2u * last;
       const auto node = [&](const FlowPiece<1>& p) {
         return (uint32_t)lds_get<unsigned short>(min(q0 + 2u * (uint32_t)p.base, q1));
       };
@@ -346,7 +348,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
     // Path counts leave, and a node's waits for it in the low word of its place in the backward sweep: as a double less than 2^-1022 and so
     // nothing beside a coef.
     uint32_t* const count = fv.count + (size_t)s * (size_t)S;
-    for (int i = t; i < S / 8 && !kDemand; i += kWideThreads) reinterpret_cast<FlowWords*>(queue)[i] = reinterpret_cast<const FlowWords*>(q)[i];
+    for (int i = t; i < S / 8 && !kDemand && !kStays; i += kWideThreads) reinterpret_cast<FlowWords*>(queue)[i] = reinterpret_cast<const FlowWords*>(q)[i];
     FlowWords words_of[kFlowWords];
 #pragma unroll
     for (int k = 0; k < kFlowWords; ++k) {
@@ -395,7 +397,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
         const uint32_t at = min((uint32_t)t + (uint32_t)p.base, last);
         Entry e;
         e.value = kDemand ? lds_at(value, 8u * at) : 0.0;
-        e.node = queue[at];
+        e.node = kStays ? lds_get<unsigned short>(q_at + 2u * at) : queue[at];
         return e;
       };
       const auto step = [&](const Entry& here, const Entry& next, Entry& third, Row& row, Row& next_row) {

@@ -270,13 +270,22 @@ constexpr int flow_nodes(int ell_words) { return ell_words == 2 ? 6 : ell_words 
 constexpr int flow_stride(int N) { return (N + 63) / 64 * 64; }
 // LDS of k_flow_sources: in its sort and forward sweep a word and a queue entry per node and positions per thread (one for each
 // level of a word of counters, one for those without), and the demands; in its backward sweep 8 bytes a node, 16 with demands.
-constexpr size_t flow_sort_bytes(int N, int depth) { return (size_t)flow_stride(N) * 6 + 2 * 32 + (depth <= 8 ? 9 : 17) * 2 * kSmallThreads; }
+constexpr size_t flow_places(int depth) { return (size_t)(depth <= 8 ? 9 : 17) * 2 * kSmallThreads; }
+constexpr size_t flow_sort_bytes(int N, int depth) { return (size_t)flow_stride(N) * 6 + 2 * 32 + flow_places(depth); }
 constexpr size_t flow_demand_at(int N, int depth) {
   return flow_sort_bytes(N, depth) > (size_t)flow_stride(N) * 8 ? flow_sort_bytes(N, depth) : (size_t)flow_stride(N) * 8;
 }
 constexpr size_t kFlowTail = kSmallThreads / kSmallWave * (8 + 8 * 4);  // sums of the waves
+// Without demands the queue stays in LDS, behind the 8 bytes a node of the backward sweep, where there is room for it; the positions of the sort
+// then lie between the words and the queue, or behind it.
+constexpr bool flow_gap(int N, int depth) { return flow_places(depth) <= (size_t)flow_stride(N) * 4; }
+constexpr size_t flow_stays_bytes(int N, int depth) {
+  return (size_t)flow_stride(N) * 10 + 2 * 32 + (flow_gap(N, depth) ? 0 : flow_places(depth));
+}
+constexpr bool flow_stays(int N, int depth) { return flow_stays_bytes(N, depth) <= kSmallLds; }
 constexpr size_t flow_source_lds(int N, int depth, bool demand) {
-  return flow_demand_at(N, depth) + (demand ? (size_t)flow_stride(N) * 8 : 0) + kFlowTail;
+  return (!demand && flow_stays(N, depth) ? flow_stays_bytes(N, depth) : flow_demand_at(N, depth)) + (demand ? (size_t)flow_stride(N) * 8 : 0) +
+         kFlowTail;
 }
 // Of k_flow_links: the path counts of two sources.
 constexpr size_t flow_link_lds(int N) { return (size_t)flow_stride(N) * 4 * 2; }

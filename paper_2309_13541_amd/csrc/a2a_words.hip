@@ -140,10 +140,13 @@ template <int KS>
 void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStream_t st) {
   const size_t lds = flow_source_lds(fv.N, fv.depth, demand);
   const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(fv); };
+  static_assert(flow_stays(kScaledNodes, kFlowDeepest));
   if (fv.N <= kScaledNodes)
-    demand ? launch(k_flow_sources<KS, true, true>) : launch(k_flow_sources<KS, true, false>);
+    demand ? launch(k_flow_sources<KS, true, true, false>) : launch(k_flow_sources<KS, true, false, true>);
+  else if (demand)
+    launch(k_flow_sources<KS, false, true, false>);
   else
-    demand ? launch(k_flow_sources<KS, false, true>) : launch(k_flow_sources<KS, false, false>);
+    flow_stays(fv.N, fv.depth) ? launch(k_flow_sources<KS, false, false, true>) : launch(k_flow_sources<KS, false, false, false>);
 }
 
 template <int KS>

@@ -14,6 +14,7 @@ namespace a2a_dev {
 struct SmallPlan {
   SmallView sv{};
   int T = 0, workgroups = 0, nodes = 0;  // threads, workgroups of the whole call, nodes per thread
+  int at_a_time = 0;                     // sources of k_node_loads; 0: another kernel
   size_t lds = 0;
 };
 

@@ -699,11 +699,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
 // Bound by the chain of a level: gathers, sum, store, barrier (hypercube of 1024 nodes: waves wait half of the time, vector ALUs are busy
 // 27, LDS 32 % of it).  Whole calls, k_small_loads and this, in a replayed graph: 8x8 torus 10.3, 6.2 us, 256 nodes of degree 8 12.7, 9.5,
 // 512 of degree 4 16.2, 13.0, 1000 of degree 8 34.7, 31.2; one by one the smallest take as long as the host takes to launch them (8x8 torus
-// 11.5 us for both).  Where k_small_loads is the faster one: node_fits.
-template <int KS, int kNodes, bool kDemand>
+// 11.5 us for both).  Where k_small_loads is the faster one: node_fits.  kSources of them at a time, side by side in LDS (unit demands;
+// where that is faster: node_pairs).
+template <int KS, int kNodes, int kSources, bool kDemand>
 __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   extern __shared__ double s_small[];
-  constexpr uint32_t kApart = node_apart(kNodes);  // sigma of even and odd levels, coefs of even and odd levels
+  typedef double Values __attribute__((ext_vector_type(kSources)));  // of a node, a source each
+  // sigma of even and odd levels, coefs of even and odd levels
+  constexpr uint32_t kApart = node_apart(kNodes, kSources), kBytes = 8 * kSources;
   constexpr int kNever = -2, kNone = -1;
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
@@ -716,45 +719,71 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
     in[k].load(sv.in, 8 * v);
     out[k].load(sv.out, 8 * v);
 #pragma unroll
+    for (int j = 0; j < KS; ++j) {  // places of 16 bits: ids are below 2048
+      in[k].w[j] *= kSources;
+      out[k].w[j] *= kSources;
+    }
+#pragma unroll
     for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
   }
   long long dsum = 0, reached = 0;
   double largest = 0.0, wd = 0.0;
-  for (int s = s_first; s < s_last; ++s) {
-    const int source = sv.src_begin + s;
-    int lvl[kNodes];
-    double own[kNodes], demand[kNodes];
+  for (int s = s_first; s < s_last; s += kSources) {
+    int lvl[kNodes][kSources];
+    double own[kNodes][kSources], demand[kNodes][kSources];
     if (s != s_first) __syncthreads();
+    int n = N;
+    asm volatile("" : "+s"(n));  // what it is compared with is not kept from source to source
 #pragma unroll
     for (int k = 0; k < kNodes; ++k) {
       const int v = t + T * k;
-      lvl[k] = v >= N ? kNever : v == source ? 0 : kNone;
-      own[k] = v == source ? 1.0 : 0.0;
-      demand[k] = 0.0;
-      if (v < N) {
-        lds_put(8 * v, own[k]);
+      Values first = 0.0;
 #pragma unroll
-        for (int a = 1; a < 4; ++a) lds_put(8 * v + a * kApart, 0.0);
-        if (kDemand) demand[k] = sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)s];
+      for (int i = 0; i < kSources; ++i) {
+        const bool there = v < n && s + i < s_last, source = there && v == sv.src_begin + s + i;
+        lvl[k][i] = !there ? kNever : source ? 0 : kNone;
+        first[i] = own[k][i] = source ? 1.0 : 0.0;
+        demand[k][i] = kDemand && there ? sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)(s + i)] : 0.0;
+      }
+      if (v < n) {
+        lds_put(kBytes * v, first);
+#pragma unroll
+        for (int a = 1; a < 4; ++a) lds_put(kBytes * v + a * kApart, (Values)0.0);
       }
     }
-    const auto gather = [&](const SmallRow<KS>& row, uint32_t from, double (&y)[2 * KS]) {
+    // of source i, from what was gathered of a node's links
+    const auto of = [&](const Values (&y)[2 * KS], int i, double (&x)[2 * KS]) {
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<double>(row.at(j) + from);
+      for (int j = 0; j < 2 * KS; ++j) x[j] = y[j][i];
+    };
+    const auto gather = [&](const SmallRow<KS>& row, uint32_t from, Values (&y)[2 * KS]) {
+#pragma unroll
+      for (int j = 0; j < 2 * KS; ++j) y[j] = lds_get<Values>(row.at(j) + from);
+    };
+    const auto any = [&](const int (&l)[kSources], int is) {
+      bool x = false;
+#pragma unroll
+      for (int i = 0; i < kSources; ++i) x |= l[i] == is;
+      return x;
     };
     const auto forward = [&](auto odd, int l) {
       constexpr uint32_t kNow = decltype(odd)::value ? kApart : 0, kBefore = kApart - kNow;
       __syncthreads();
 #pragma unroll
       for (int k = 0; k < kNodes; ++k) {
-        if (lvl[k] != kNone) continue;
-        double y[2 * KS];
+        if (!any(lvl[k], kNone)) continue;
+        Values y[2 * KS];
         gather(in[k], kBefore, y);
-        const double a = SmallNode<KS>::sum_pairs(y);
-        if (a > 0.0) {
-          lvl[k] = l;
-          own[k] = a;
-          lds_put(8 * (t + T * k) + kNow, a);
+#pragma unroll
+        for (int i = 0; i < kSources; ++i) {
+          double x[2 * KS];
+          of(y, i, x);
+          const double a = SmallNode<KS>::sum_pairs(x);
+          if ((kSources == 1 || lvl[k][i] == kNone) && a > 0.0) {
+            lvl[k][i] = l;
+            own[k][i] = a;
+            lds_put(kBytes * (t + T * k) + 8 * i + kNow, a);
+          }
         }
       }
     };
@@ -767,13 +796,19 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
       constexpr uint32_t kNow = 2 * kApart + (decltype(odd)::value ? kApart : 0), kAfter = 5 * kApart - kNow;
 #pragma unroll
       for (int k = 0; k < kNodes; ++k) {
-        if (lvl[k] != l) continue;
-        double y[2 * KS];
+        if (!any(lvl[k], l)) continue;
+        Values y[2 * KS];
         gather(out[k], kAfter, y);
 #pragma unroll
-        for (int j = 0; j < 2 * KS; ++j) acc[k][j] = __builtin_fma(own[k], y[j], acc[k][j]);
-        const double r = recip(own[k]);
-        lds_put(8 * (t + T * k) + kNow, (kDemand ? demand[k] * r : r) + SmallNode<KS>::sum_pairs(y));
+        for (int i = 0; i < kSources; ++i) {
+          if (kSources > 1 && lvl[k][i] != l) continue;
+          double x[2 * KS];
+          of(y, i, x);
+#pragma unroll
+          for (int j = 0; j < 2 * KS; ++j) acc[k][j] = __builtin_fma(own[k][i], x[j], acc[k][j]);
+          const double r = recip(own[k][i]);
+          lds_put(kBytes * (t + T * k) + 8 * i + kNow, (kDemand ? demand[k][i] * r : r) + SmallNode<KS>::sum_pairs(x));
+        }
       }
       __syncthreads();
     };
@@ -784,12 +819,14 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
       backward(std::false_type{}, l - 1);
     }
 #pragma unroll
-    for (int k = 0; k < kNodes; ++k) {
-      dsum += max(lvl[k], 0);
-      reached += lvl[k] > 0 ? 1 : 0;
-      largest = larger(largest, own[k]);
-      if (kDemand && lvl[k] > 0) wd = __builtin_fma((double)lvl[k], demand[k], wd);
-    }
+    for (int k = 0; k < kNodes; ++k)
+#pragma unroll
+      for (int i = 0; i < kSources; ++i) {
+        dsum += max(lvl[k][i], 0);
+        reached += lvl[k][i] > 0 ? 1 : 0;
+        largest = larger(largest, own[k][i]);
+        if (kDemand && lvl[k][i] > 0) wd = __builtin_fma((double)lvl[k][i], demand[k][i], wd);
+      }
   }
 #pragma unroll
   for (int k = 0; k < kNodes; ++k) {
@@ -800,7 +837,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
       for (int j = 0; j < 2 * KS; ++j) to[(size_t)j * (size_t)N] = acc[k][j];
     }
   }
-  small_totals(sv, &lds_at(s_small, 3 * kApart + 8 * (uint32_t)N), dsum, reached, largest >= kTwo53, wd, kDemand);
+  small_totals(sv, &lds_at(s_small, 3 * kApart + kBytes * (uint32_t)N), dsum, reached, largest >= kTwo53, wd, kDemand);
 }
 
 // Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and

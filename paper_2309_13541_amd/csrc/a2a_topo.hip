@@ -759,14 +759,16 @@ SmallPlan small_plan(const a2a_topo* t, int32_t src_count, SmallWhat what) {
 }
 
 // The same for link loads, with a thread per node where that is faster.
-SmallPlan small_loads_plan(const a2a_topo* t, int32_t src_count) {
+SmallPlan small_loads_plan(const a2a_topo* t, int32_t src_count, bool demand) {
   SmallPlan p = small_plan(t, src_count, SmallWhat::kLoads);
-  if (node_fits(t->N, t->ell_words, t->level_bound, src_count)) {
+  const bool pairs = !demand && node_pairs(t->N, t->ell_words, t->level_bound, src_count);
+  if (pairs || node_fits(t->N, t->ell_words, t->level_bound, src_count)) {
     const NodeCut c = node_cut(t->N, src_count);
     p.T = c.threads;
     p.nodes = c.nodes;
     p.workgroups = c.workgroups;
-    p.lds = node_lds_bytes(t->N, c.nodes);
+    p.at_a_time = pairs ? 2 : 1;
+    p.lds = node_lds_bytes(t->N, c.nodes, p.at_a_time);
     p.sv.per = 1;
     p.sv.per_wg = c.per_wg;
   }
@@ -792,17 +794,21 @@ bool small_loads_fit(const a2a_topo* t) {
 // rows; 1.2 MB are what the level kernels take, and in those the rows went in four launches, and as many to add them up: 40.6 us,
 // 13.0 in one.  256 sources of 1000 nodes 70.3, 23.6.)
 size_t small_loads_bytes(const a2a_topo* t, int32_t src_count) {
-  const SmallPlan p = small_loads_plan(t, src_count);
-  const int rows = std::max(p.workgroups, std::min(src_count, kComputeUnits));
-  return 256 + (size_t)rows * small_row_bytes(t, p.sv.per_wg);
+  size_t most = 0;
+  for (const bool demand : {false, true}) {
+    const SmallPlan p = small_loads_plan(t, src_count, demand);
+    const int rows = std::max(p.workgroups, std::min(src_count, kComputeUnits));
+    most = std::max(most, 256 + (size_t)rows * small_row_bytes(t, p.sv.per_wg));
+  }
+  return most;
 }
 
 int small_link_loads(const a2a_topo* t, int32_t src_begin, int32_t src_count, const double* demand, double* load,
                      double* weighted_dist, int64_t* dist_sum_total, int64_t* flags, char* ws, size_t ws_bytes,
                      hipStream_t st) {
   if (ws_bytes < t->min_loads_bytes) return A2A_ERR_WORKSPACE_TOO_SMALL;
-  SmallPlan p = small_loads_plan(t, src_count);
-  const bool by_node = node_fits(t->N, t->ell_words, t->level_bound, src_count);
+  SmallPlan p = small_loads_plan(t, src_count, demand != nullptr);
+  const bool by_node = p.at_a_time > 0;
   p.sv.src_begin = src_begin;
   p.sv.dem = demand;
   p.sv.dem_ld = src_count;

@@ -47,11 +47,13 @@ void launch_small_loads(const SmallPlan& p, bool demand, int workgroups, hipStre
 template <int KS>
 void launch_node_loads(const SmallPlan& p, bool demand, int workgroups, hipStream_t st) {
   const auto launch = [&](auto kernel) { kernel<<<workgroups, p.T, p.lds, st>>>(p.sv); };
-  constexpr int kTwo = KS <= 5 ? 2 : 1;  // (node_fits)
-  if (p.nodes == 1)
-    demand ? launch(k_node_loads<KS, 1, true>) : launch(k_node_loads<KS, 1, false>);
+  constexpr int kTwo = KS <= 5 ? 2 : 1, kTwoPair = KS <= 4 ? 2 : 1, kPair = KS <= 5 ? 2 : 1;  // (node_fits, node_pairs)
+  if (p.at_a_time == 2)
+    p.nodes == 1 ? launch(k_node_loads<KS, 1, kPair, false>) : launch(k_node_loads<KS, kTwoPair, kPair, false>);
+  else if (p.nodes == 1)
+    demand ? launch(k_node_loads<KS, 1, 1, true>) : launch(k_node_loads<KS, 1, 1, false>);
   else
-    demand ? launch(k_node_loads<KS, kTwo, true>) : launch(k_node_loads<KS, kTwo, false>);
+    demand ? launch(k_node_loads<KS, kTwo, 1, true>) : launch(k_node_loads<KS, kTwo, 1, false>);
 }
 
 template <int KS>

@@ -141,9 +141,9 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   long long reached = 0;
   const int groups = (wv.src_count + W - 1) / W;
   // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
-  // time.  The first start is spread over about the length of a search.  Without, with twice and with half the spread, and as
-  // it is, without sums: 65536 nodes of degree 8 5.48, 4.25, 4.71, 4.07 ms; of degree 3 (13 levels) 5.24, 4.30, 4.57, 4.06; 20011
-  // of degree 5 576, 543, 560, 541 us; a 40x40x40 torus (60 levels) 18.9, 18.7, 17.2, 17.7 ms.
+  // time.  The first start is spread over about the length of a search.  Without, with half, with one and a half times the spread, and as
+  // it is: 65536 nodes of degree 8 3.96, 3.89, 3.92, 3.77 ms; of degree 3 (13 levels) 4.11, 3.99, 4.07, 3.79; 40001 of degree 5 1.71, 1.63, 1.52,
+  // 1.49; 20011 of degree 5 518, 473, 442, 427 us; a 40x40x40 torus (60 levels) 15.6, 15.1, 16.0, 15.7 ms.
   if (kOut == kWideDist && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {

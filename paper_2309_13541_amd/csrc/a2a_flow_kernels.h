@@ -17,7 +17,7 @@ namespace a2a_dev {
 struct FlowView {
   const uint32_t *in, *out;    // link tables, as in SmallView
   const unsigned char* level;  // [sources][small_level_bytes(N)]
-  void* record;                // [workgroups of k_flow_sources] nodes of a source, level by level, 16 bits each
+  void* record;                // [workgroups of k_flow_sources] nodes of a source, level by level, 16 bits each (FlowKeep::kMemory)
   uint32_t* count;             // [sources][stride] FlowWord
   double* coef;                // [sources][stride]; demands before (k_flow_demand)
   double* weighted;            // [sources] demand x distance
@@ -211,21 +211,24 @@ struct FlowPiece {
 // the backward sweep a double per node, 0 until it is written: a node of level l has out-links to levels up to l + 1, of which only
 // l + 1 and (some of) l are written, so even levels are kept with a plus sign and odd ones with a minus sign, and a level adds up
 // the entries of the other sign only.  Coefs of unequal demands have any sign: even and odd levels have an array each.
-// The nodes' order stays in LDS where there is room (kStays, flow_stays), else it goes through memory; it is read three pieces ahead, links
-// one piece ahead.  With demands, demand / path count goes with it.  Without, the path count stays in LDS, in the low word of the
-// double that the backward sweep has of a node: below 2^-1022, it changes no sum of coefs, all of which are above 2^-25.  So the forward
-// sweep stores nothing in memory: its pieces waited for what the one before had stored, 6 bytes a node.  Whole calls with that, with the order
-// through memory, and with it in LDS: 16384 nodes of a generalized Kautz topology of degree 4 2261, 2120 us, -; 20000 of degree 4 3902, 3706, -;
-// 13000 of a generalized Kautz topology of degree 7 1524, 1463, 1442; 14000 of degree 5 2078, 2066, 2034; 12000 of degree 6 1426, 1442, 1425;
-// 9000 of degree 6 937, 956, 943.  (Path counts read again by node from the output rows: 16384 nodes 1646 us here, then 1791; with
-// demands, quotients stored after the sweep: 8191 of degree 8 774, 801.)  Rows of the outputs are written from LDS, in node order.
+// The nodes' order and their path counts go from one sweep to the other in LDS as far as there is room (flow_keep has the rule and its times);
+// both are read three pieces ahead, links one piece ahead.  With demands, order and demand / path count go through memory.  Without,
+// the forward sweep stores nothing in memory: its pieces waited for what the one before had stored, 6 bytes a node.  Where path counts do not fit in
+// the queue's order, a node's stays in the low word of the double that the backward sweep has of it: below 2^-1022, it changes no sum of
+// coefs, all of which are above 2^-25; but it is then read in the chain of a backward piece.  All sources, link loads alone in a replayed graph, records
+// through memory and now: 9000 nodes of degree 4 893, 867 us, of degree 8 979, 971; 10000 of a generalized Kautz topology of degree 9 1085, 1033; order
+// in LDS: 13000 of a generalized Kautz topology of degree 7 1523, 1449, of degree 6 1765, 1702; order in memory: 16384 of a generalized Kautz topology of
+// degree 4 2235, 2112; 20000 of degree 4 3893, 3698, of degree 16 6524, 6518.  At the lower end of what has ids and not 8 x id in its tables the old way
+// was the faster one by 0.4 % (8300 of degree 8 855, 859).  With 16 links and path counts by node two registers spill.  (Path counts read again by node from the
+// output rows: 16384 nodes 1646 us here, then 1791; with demands, quotients stored after the sweep: 8191 of degree 8 774, 801.)  Rows
+// of the outputs are written from LDS, in node order.
 // Bound by the instructions of a piece and its barriers, which the four waves of a SIMD hide in part: 16384 nodes of degree 4 took 1640 us
 // with record stores, forward 490, backward 540, sort 240, rows and zeroes 280; with gathers from the thread's own place in LDS, or
 // without any, 1600 and more, without any access to memory 1410.  Two nodes a thread and piece, their gathers at the same time: 2 to 6 % slower.
 // Pushing counts to the out-links by LDS additions where that touches fewer nodes took longer (48 for 26 thousand cycles
 // forward, 20011 nodes of degree 5), and so did links asked for three pieces ahead (20 for 14 thousand).
 // kScaled: the tables have 8 x id.
-template <int KS, bool kScaled, bool kDemand, bool kStays>
+template <int KS, bool kScaled, bool kDemand, FlowKeep kKeep>
 __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   extern __shared__ double s_small[];
   using Row = FlowRow<KS, kScaled>;
@@ -233,12 +236,14 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
   const int N = fv.N, S = fv.stride, nl = (int)small_level_bytes(N);
   const int words = (N + 4 * kWideThreads - 1) / (4 * kWideThreads), v0 = 4 * words * t;  // this thread's nodes in the sort
   uint32_t* const x = reinterpret_cast<uint32_t*>(s_small);
-  const uint32_t q_at = (kStays ? 8u : 4u) * (uint32_t)S;
+  constexpr bool kRecords = kKeep == FlowKeep::kRecords, kStays = kKeep != FlowKeep::kMemory;
+  constexpr bool kByNode = !kDemand && !kRecords;  // path counts wait by node
+  const uint32_t q_at = (kStays ? 8u : 4u) * (uint32_t)S, paths_at = q_at + 2u * (uint32_t)(S + kFlowSpare);
   unsigned short* const q = reinterpret_cast<unsigned short*>(reinterpret_cast<char*>(s_small) + q_at);
-  unsigned short* const base = kStays && flow_gap(N, fv.depth) ? reinterpret_cast<unsigned short*>(x + S) : q + S + kFlowSpare;
+  unsigned short* const base = kStays && flow_gap(N, fv.depth) ? reinterpret_cast<unsigned short*>(x + S) : q + S + kFlowSpare + (kRecords ? 2 * S : 0);
   double* const demand = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_demand_at(N, fv.depth));
   // behind all that, so that places in the arrays at the start need no addition
-  double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_source_lds(N, fv.depth, kDemand) - kFlowTail);
+  double* const s_weighted = reinterpret_cast<double*>(reinterpret_cast<char*>(s_small) + flow_tail_at(N, fv.depth, kKeep, kDemand));
   uint32_t* const s_totals = reinterpret_cast<uint32_t*>(s_weighted + kWideThreads / kWave);
   unsigned short* const queue = reinterpret_cast<unsigned short*>(static_cast<char*>(fv.record) + (size_t)blockIdx.x * flow_record_bytes(S, kDemand));
   double* const value = reinterpret_cast<double*>(queue + S);  // demand / path count, with demands
@@ -316,6 +321,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) sum += flow_count(y[j], before);
           lds_put<uint32_t>(Row::template own<2>(here.node), sum + above);
+          if constexpr (kRecords) lds_put<uint32_t>(paths_at + 4u * (uint32_t)(a.base + t), sum);
           if constexpr (kDemand) {
             const uint32_t at = (uint32_t)(a.base + t);
             value[at] = own * recip((double)sum);
@@ -345,10 +351,10 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       wd = wave_sum_double(wd);
       if (lane == 0) s_weighted[wave] = wd;
     }
-    // Path counts leave, and a node's waits for it in the low word of its place in the backward sweep: as a double less than 2^-1022 and so
-    // nothing beside a coef.
+    // Path counts leave.  By node, a node's waits for it in the low word of its place in the backward sweep: as a double less than 2^-1022
+    // and so nothing beside a coef.
     uint32_t* const count = fv.count + (size_t)s * (size_t)S;
-    for (int i = t; i < S / 8 && !kDemand && !kStays; i += kWideThreads) reinterpret_cast<FlowWords*>(queue)[i] = reinterpret_cast<const FlowWords*>(q)[i];
+    for (int i = t; i < S / 8 && kByNode && !kStays; i += kWideThreads) reinterpret_cast<FlowWords*>(queue)[i] = reinterpret_cast<const FlowWords*>(q)[i];
     FlowWords words_of[kFlowWords];
 #pragma unroll
     for (int k = 0; k < kFlowWords; ++k) {
@@ -364,8 +370,8 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       for (int k = 0; k < kWideThreads / kWave; ++k) wd += s_weighted[k];
       fv.weighted[s] = wd;
     }
-    if (kDemand) {
-      for (int i = t; i < S; i += kWideThreads) reinterpret_cast<double2*>(s_small)[i] = make_double2(0.0, 0.0);
+    if (!kByNode) {
+      for (int i = t; i < (kDemand ? S : S / 2); i += kWideThreads) reinterpret_cast<double2*>(s_small)[i] = make_double2(0.0, 0.0);
     } else {
 #pragma unroll
       for (int k = 0; k < kFlowWords; ++k) {
@@ -377,7 +383,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       }
     }
     lds_barrier();
-    if (!kDemand && t == 0) s_small[fv.source0 + s] = 0.0;
+    if (kByNode && t == 0) s_small[fv.source0 + s] = 0.0;
 
     if (s + (int)gridDim.x < fv.sources) levels(s + (int)gridDim.x);
     if (deep > 0) {  // backward
@@ -390,13 +396,14 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
       d = c;
       d.next(starts);
       struct Entry {
-        uint32_t node;
+        uint32_t node, paths;
         double value;
       };
       const auto read = [&](const FlowPiece<-1>& p) {
         const uint32_t at = min((uint32_t)t + (uint32_t)p.base, last);
         Entry e;
         e.value = kDemand ? lds_at(value, 8u * at) : 0.0;
+        e.paths = kRecords ? lds_get<uint32_t>(paths_at + 4u * at) : 0u;
         e.node = kStays ? lds_get<unsigned short>(q_at + 2u * at) : queue[at];
         return e;
       };
@@ -409,7 +416,7 @@ __global__ void __launch_bounds__(kWideThreads) k_flow_sources(FlowView fv) {
         if (t < a.end - a.base) {
           const bool odd = (a.level & 1) != 0, inner = a.level < deep;  // the last level has no successors
           const uint32_t from = kDemand && !odd ? 8u * (uint32_t)S : 0u, to = kDemand && odd ? 8u * (uint32_t)S : 0u;
-          const uint32_t paths = kDemand ? 0u : lds_get<uint32_t>(Row::template own<3>(here.node));
+          const uint32_t paths = !kByNode ? here.paths : lds_get<uint32_t>(Row::template own<3>(here.node));
           double y[2 * KS];
           if (inner) {
 #pragma unroll

@@ -304,16 +304,30 @@ constexpr size_t flow_demand_at(int N, int depth) {
   return flow_sort_bytes(N, depth) > (size_t)flow_stride(N) * 8 ? flow_sort_bytes(N, depth) : (size_t)flow_stride(N) * 8;
 }
 constexpr size_t kFlowTail = kSmallThreads / kSmallWave * (8 + 8 * 4);  // sums of the waves
-// Without demands the queue stays in LDS, behind the 8 bytes a node of the backward sweep, where there is room for it; the positions of the sort
-// then lie between the words and the queue, or behind it.
+// How k_flow_sources keeps the order of a source's nodes and their path counts from its forward sweep to its backward one, without demands: both
+// in LDS, in that order (kRecords), behind the 8 bytes a node of the backward sweep; the order there, path counts by node in those 8 bytes
+// (kQueue); the order in memory, path counts by node (kMemory; with demands, demand / path count in memory too).  Each where there is no room
+// for the one before.  In the first two the positions of the sort lie between words and queue where they fit, or behind all that.
+// (us, all sources, records through memory / kQueue / kRecords: 5200 nodes of degree 8 414 / 419 / 413, 9000 of degree 8 977 / 993 / 970, of degree 16
+// 1414 / 1427 / 1394, of a generalized Kautz topology of degree 4 752 / 742 / 727; 11200 of degree 6 1265 / 1260 / 1234, of degree 12 2007 / 1948 / 1899.
+// Records through memory / kMemory / kQueue: 13000 of degree 6 1763 / 1748 / 1703, 16200 of degree 12 3989 / 3871 / 3739, of degree 16 4013 / 4020 / 3955.)
+enum class FlowKeep { kRecords, kQueue, kMemory };
 constexpr bool flow_gap(int N, int depth) { return flow_places(depth) <= (size_t)flow_stride(N) * 4; }
-constexpr size_t flow_stays_bytes(int N, int depth) {
-  return (size_t)flow_stride(N) * 10 + 2 * 32 + (flow_gap(N, depth) ? 0 : flow_places(depth));
+constexpr size_t flow_keep_bytes(int N, int depth, FlowKeep keep) {
+  return keep == FlowKeep::kMemory ? flow_demand_at(N, depth)
+                                   : (size_t)flow_stride(N) * (keep == FlowKeep::kRecords ? 14 : 10) + 2 * 32 + (flow_gap(N, depth) ? 0 : flow_places(depth));
 }
-constexpr bool flow_stays(int N, int depth) { return flow_stays_bytes(N, depth) <= kSmallLds; }
+constexpr FlowKeep flow_keep(int N, int depth, bool demand) {
+  if (!demand)
+    for (const FlowKeep keep : {FlowKeep::kRecords, FlowKeep::kQueue})
+      if (flow_keep_bytes(N, depth, keep) <= kSmallLds) return keep;
+  return FlowKeep::kMemory;
+}
+constexpr size_t flow_tail_at(int N, int depth, FlowKeep keep, bool demand) {
+  return flow_keep_bytes(N, depth, keep) + (demand ? (size_t)flow_stride(N) * 8 : 0);
+}
 constexpr size_t flow_source_lds(int N, int depth, bool demand) {
-  return (!demand && flow_stays(N, depth) ? flow_stays_bytes(N, depth) : flow_demand_at(N, depth)) + (demand ? (size_t)flow_stride(N) * 8 : 0) +
-         kFlowTail;
+  return flow_tail_at(N, depth, flow_keep(N, depth, demand), demand) + kFlowTail;
 }
 // Of k_flow_links: the path counts of two sources.
 constexpr size_t flow_link_lds(int N) { return (size_t)flow_stride(N) * 4 * 2; }

@@ -142,13 +142,17 @@ template <int KS>
 void launch_flow_sources(const FlowView& fv, bool demand, int workgroups, hipStream_t st) {
   const size_t lds = flow_source_lds(fv.N, fv.depth, demand);
   const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(fv); };
-  static_assert(flow_stays(kScaledNodes, kFlowDeepest));
-  if (fv.N <= kScaledNodes)
-    demand ? launch(k_flow_sources<KS, true, true, false>) : launch(k_flow_sources<KS, true, false, true>);
-  else if (demand)
-    launch(k_flow_sources<KS, false, true, false>);
-  else
-    flow_stays(fv.N, fv.depth) ? launch(k_flow_sources<KS, false, false, true>) : launch(k_flow_sources<KS, false, false, false>);
+  static_assert(flow_keep(kScaledNodes, kFlowDeepest, false) == FlowKeep::kRecords);
+  if (fv.N <= kScaledNodes) {
+    demand ? launch(k_flow_sources<KS, true, true, FlowKeep::kMemory>) : launch(k_flow_sources<KS, true, false, FlowKeep::kRecords>);
+    return;
+  }
+  switch (flow_keep(fv.N, fv.depth, demand)) {
+    case FlowKeep::kRecords: return launch(k_flow_sources<KS, false, false, FlowKeep::kRecords>);
+    case FlowKeep::kQueue: return launch(k_flow_sources<KS, false, false, FlowKeep::kQueue>);
+    case FlowKeep::kMemory:
+      demand ? launch(k_flow_sources<KS, false, true, FlowKeep::kMemory>) : launch(k_flow_sources<KS, false, false, FlowKeep::kMemory>);
+  }
 }
 
 template <int KS>

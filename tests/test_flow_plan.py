@@ -29,12 +29,25 @@ int main() {
       }
       for (int demand = 0; demand < 2; ++demand)
         if (N <= kFlowNodes && depth <= kFlowDeepest && flow_lds_fits(N, depth, demand)) {
-          const size_t at = flow_demand_at(N, depth), lds = flow_source_lds(N, depth, demand);
-          check(at % 8 == 0 && at >= S * 4 + (S + 32) * 2 + places && at >= S * 8 && lds >= at + (demand ? S * 8 : 0) + 16 * (8 + 32) &&
-                lds <= 160 * 1024 && flow_link_lds(N) <= kSmallLds, "sources", N, depth, demand);
+          // [from, to) of what is in LDS at a time: sort and forward sweep (positions only in the first), backward sweep
+          const FlowKeep keep = flow_keep(N, depth, demand);
+          const bool memory = keep == FlowKeep::kMemory, records = keep == FlowKeep::kRecords;
+          const size_t lds = flow_source_lds(N, depth, demand), tail = flow_tail_at(N, depth, keep, demand);
+          const size_t queue = (memory ? 4 : 8) * S, paths = queue + (S + 32) * 2;
+          const size_t behind = paths + (records ? 4 * S : 0), base = !memory && flow_gap(N, depth) ? 4 * S : behind;
+          const size_t dem = flow_demand_at(N, depth);
+          check(memory || !demand, "demands go through memory", N, depth, demand);
+          check(base >= 4 * S && (base + places <= queue || base >= behind) && base + places <= (demand ? dem : tail), "positions", N, depth, (int)keep);
+          check(behind <= (demand ? dem : tail) && (memory || queue >= 8 * S) && 8 * S <= (demand ? dem : tail), "queue, path counts, doubles", N, depth, (int)keep);
+          check(!demand || (dem % 16 == 0 && dem >= 8 * S && dem + 8 * S <= tail && 16 * S <= tail), "demands", N, depth, demand);
+          check(tail % 8 == 0 && queue % 16 == 0 && paths % 4 == 0 && base % 2 == 0 && lds >= tail + 16 * (8 + 32) && lds <= 160 * 1024 &&
+                flow_link_lds(N) <= kSmallLds, "sources", N, depth, demand);
+          check(N > kScaledNodes || demand || records, "with 8 x id in the tables all of it stays", N, depth, 0);
         }
     }
   }
+  check(flow_keep(11584, 11, false) == FlowKeep::kRecords && flow_keep(11585, 5, false) == FlowKeep::kQueue &&
+        flow_keep(16256, 11, false) == FlowKeep::kQueue && flow_keep(16257, 5, false) == FlowKeep::kMemory, "where the forms change", 0, 0, 0);
   const int nodes[] = {5121, 8191, 8192, 10176, 16384, 20000, kFlowNodes}, words[] = {2, 3, 4, 5, 8};
   for (int N : nodes)
     for (int w : words)

@@ -1,5 +1,5 @@
-"""Link loads of a source at a time in LDS, where the queue of its nodes stays there and where it goes through memory: at the edges of
-that and of where the positions of the sort lie, and from sources without links.  (Needs an MI355X.)"""
+"""Link loads of a source at a time in LDS, where the queue of its nodes and their path counts stay there and where the queue goes through
+memory: at the edges of that and of where the positions of the sort lie, and from sources without links.  (Needs an MI355X.)"""
 import numpy as np
 import pytest
 
@@ -15,15 +15,19 @@ def without_links(csr, every):
 
 
 CASES = {
-    # positions behind the queue; one node on, between the words and the queue (8 levels and fewer, then more)
-    "4608 less one, 9 links": lambda: gen.random_regular(4544, 12, 1),
-    "4609 nodes, 12 links": lambda: gen.random_regular(4609, 12, 2),
+    # positions of the sort behind all that stays, then (one node on) between the words and the queue, which they fill
+    "4544 nodes, 12 links": lambda: gen.random_regular(4544, 12, 1),
+    "4545 nodes, 12 links": lambda: gen.random_regular(4545, 12, 2),
     "8640 nodes, 9 levels": lambda: gen.imase_itoh(8640, 3),
-    "8705 nodes, 9 levels": lambda: gen.imase_itoh(8705, 3),
+    "8641 nodes, 9 levels": lambda: gen.imase_itoh(8641, 3),
+    # most nodes whose path counts stay in the queue's order, and one more
+    "11584 nodes": lambda: gen.random_regular(11584, 5, 7),
+    "11585 nodes": lambda: gen.random_regular(11585, 5, 8),
     # most nodes whose queue stays, and one more
     "16256 nodes": lambda: gen.random_regular(16256, 5, 3),
     "16257 nodes": lambda: gen.random_regular(16257, 5, 4),
-    "sources without links, queue in LDS": lambda: without_links(gen.random_regular(9000, 8, 5), 7),
+    "sources without links, path counts in the queue's order": lambda: without_links(gen.random_regular(9000, 8, 5), 7),
+    "sources without links, queue in LDS": lambda: without_links(gen.random_regular(12500, 6, 9), 7),
     "sources without links, queue in memory": lambda: without_links(gen.random_regular(17000, 6, 6), 7),
 }
 

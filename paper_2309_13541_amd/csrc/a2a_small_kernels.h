@@ -700,9 +700,13 @@ __global__ void __launch_bounds__(kSmallThreads) k_small_loads(SmallView sv) {
 // 27, LDS 32 % of it).  Whole calls, k_small_loads and this, in a replayed graph: 8x8 torus 10.3, 6.2 us, 256 nodes of degree 8 12.7, 9.5,
 // 512 of degree 4 16.2, 13.0, 1000 of degree 8 34.7, 31.2; one by one the smallest take as long as the host takes to launch them (8x8 torus
 // 11.5 us for both).  Where k_small_loads is the faster one: node_fits.  kSources of them at a time, side by side in LDS (unit demands;
-// where that is faster: node_pairs).
+// where that is faster: node_pairs); a link's loads from two sources are then added up level by level, the deepest first, and not source
+// by source.  One at a time has no loop over sources in its backward sweep, not even one of a single pass: with it 10 links of two nodes a
+// thread spilled 12 bytes, with demands 52 where they spill 32, and demands were asked for before the first stores to LDS (1300 nodes of degree 10
+// 30.4, 30.8 us, with demands 31.5, 32.9, of 768 sources 54.2, 57.9; now 30.4, 31.7, 54.3).
 template <int KS, int kNodes, int kSources, bool kDemand>
 __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
+  static_assert(kSources == 1 || !kDemand);
   extern __shared__ double s_small[];
   typedef double Values __attribute__((ext_vector_type(kSources)));  // of a node, a source each
   // sigma of even and odd levels, coefs of even and odd levels
@@ -730,25 +734,26 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   double largest = 0.0, wd = 0.0;
   for (int s = s_first; s < s_last; s += kSources) {
     int lvl[kNodes][kSources];
-    double own[kNodes][kSources], demand[kNodes][kSources];
+    double own[kNodes][kSources], demand[kNodes];
     if (s != s_first) __syncthreads();
     int n = N;
-    asm volatile("" : "+s"(n));  // what it is compared with is not kept from source to source
+    if (kSources > 1) asm volatile("" : "+s"(n));  // what it is compared with is not kept from source to source
 #pragma unroll
     for (int k = 0; k < kNodes; ++k) {
       const int v = t + T * k;
       Values first = 0.0;
 #pragma unroll
       for (int i = 0; i < kSources; ++i) {
-        const bool there = v < n && s + i < s_last, source = there && v == sv.src_begin + s + i;
+        const bool there = v < n && (kSources == 1 || s + i < s_last), source = (kSources == 1 || there) && v == sv.src_begin + s + i;
         lvl[k][i] = !there ? kNever : source ? 0 : kNone;
         first[i] = own[k][i] = source ? 1.0 : 0.0;
-        demand[k][i] = kDemand && there ? sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)(s + i)] : 0.0;
       }
+      demand[k] = 0.0;
       if (v < n) {
         lds_put(kBytes * v, first);
 #pragma unroll
         for (int a = 1; a < 4; ++a) lds_put(kBytes * v + a * kApart, (Values)0.0);
+        if (kDemand) demand[k] = sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)s];
       }
     }
     // of source i, from what was gathered of a node's links
@@ -799,15 +804,20 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
         if (!any(lvl[k], l)) continue;
         Values y[2 * KS];
         gather(out[k], kAfter, y);
-#pragma unroll
-        for (int i = 0; i < kSources; ++i) {
-          if (kSources > 1 && lvl[k][i] != l) continue;
+        const auto add = [&](int i) {
           double x[2 * KS];
           of(y, i, x);
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) acc[k][j] = __builtin_fma(own[k][i], x[j], acc[k][j]);
           const double r = recip(own[k][i]);
-          lds_put(kBytes * (t + T * k) + 8 * i + kNow, (kDemand ? demand[k][i] * r : r) + SmallNode<KS>::sum_pairs(x));
+          lds_put(kBytes * (t + T * k) + 8 * i + kNow, (kDemand ? demand[k] * r : r) + SmallNode<KS>::sum_pairs(x));
+        };
+        if constexpr (kSources == 1) {
+          add(0);
+        } else {  // (not a loop of one pass: see above)
+#pragma unroll
+          for (int i = 0; i < kSources; ++i)
+            if (lvl[k][i] == l) add(i);
         }
       }
       __syncthreads();
@@ -825,7 +835,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
         dsum += max(lvl[k][i], 0);
         reached += lvl[k][i] > 0 ? 1 : 0;
         largest = larger(largest, own[k][i]);
-        if (kDemand && lvl[k][i] > 0) wd = __builtin_fma((double)lvl[k][i], demand[k][i], wd);
+        if (kDemand && lvl[k][i] > 0) wd = __builtin_fma((double)lvl[k][i], demand[k], wd);
       }
   }
 #pragma unroll

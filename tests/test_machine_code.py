@@ -110,6 +110,22 @@ def test_lds_by_address_starts_at_zero(code_objects):
     assert {k: sizes[k] for k in names if sizes[k] != {0}} == {}
 
 
+def test_registers_of_a_thread_per_node(code_objects):
+    """Link loads with a thread per node, a source at a time, keep all of a thread's nodes in registers: only 10 links of two
+    nodes with demands do not fit."""
+    scratch = {}
+    for path in code_objects:
+        notes = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", path], check=True, stdout=subprocess.PIPE, text=True,
+                               timeout=120).stdout
+        for words, nodes, sources, demand, size in re.findall(
+                r"\.name: +_ZN7a2a_dev12k_node_loadsILi(\d)ELi(\d)ELi(\d)ELb(\d)E\w*\n.*\.private_segment_fixed_size: (\d+)", notes):
+            scratch[int(words), int(nodes), int(sources), int(demand)] = int(size)
+    alone = {k: v for k, v in scratch.items() if k[2] == 1}
+    assert len(alone) == 18  # 2 to 5 words: a node or two a thread, 8 words: one
+    assert alone.pop((5, 2, 1, 1)) <= 32
+    assert {k: v for k, v in alone.items() if v} == {}
+
+
 def test_words_in_memory_between_the_sweeps_of_a_strip_source():
     """lds_barrier() waits for LDS only.  Where k_strip_sources begins to read the records that other threads have stored, a
     barrier for memory stands before it, and a record is no place outside the link table whatever it holds."""

@@ -197,12 +197,15 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
   return c;
 }
 
-// Link loads with a thread per node (k_node_loads): LDS of four arrays of a double per node, each where an instruction's constant
-// offset reaches it, and the waves' totals.
+// Link loads with a thread per node (k_node_loads): LDS of four arrays of a double per node and source, a constant apart, and the waves'
+// totals.  The constant is part of an instruction, but for the coefs of two nodes a thread and two sources: 64 KB on, each gather of
+// theirs takes an addition.  Two sources' arrays are not a power of two apart: the compiler made a constant that sets a bit of the place an
+// operation of its own, and kept the results (2 nodes and 8 links: 100 bytes a lane spilled, now 16; 6 links 126 registers, 111).
 constexpr int kNodeMost = 2;  // nodes a thread may have
-constexpr int node_apart(int nodes, int sources = 1) { return nodes * kSmallThreads * 8 * sources; }
+constexpr int node_apart(int nodes, int sources = 1) { return nodes * kSmallThreads * 8 * sources + (sources > 1 ? 16 : 0); }
+constexpr int node_places(int N) { return (N + 15) / 16 * 16; }  // in whole blocks of 16
 constexpr size_t node_lds_bytes(int N, int nodes, int sources = 1) {
-  return 3 * (size_t)node_apart(nodes, sources) + (size_t)N * 8 * sources + kSmallThreads / kSmallWave * 32;
+  return 3 * (size_t)node_apart(nodes, sources) + (size_t)node_places(N) * 8 * sources + kSmallThreads / kSmallWave * 32;
 }
 
 // A thread has a node, or two where the registers allow it (link tables of 8 words spill: 1100 nodes 124 us, k_small_loads 52).  A
@@ -247,23 +250,27 @@ inline bool node_fits(int N, int ell_words, int depth, int src_count) {
 }
 
 // Which calls with unit demands take its sources two at a time, whether or not node_fits has them: 16 bytes a node and gather, a barrier a
-// level for both.  An odd source has such a pass to itself, and more links spill.  (us, the faster of k_small_loads and one at a time, and
-// this.)  A node a thread.  Two sources: 32x32 torus 31.3, 26.5, 10x10x10 24.9, 23.1, 1000 of degree 4 17.3, 16.6, hypercube of 1024
-// 27.6, 26.8.  Four, 16 levels: 1000 of degree 4 26.7, 25.1, 5x5x6x6 torus 31.9, 29.9, 10x10x10 (15) 36.6, 35.6, hypercube of 1024 38.3, 36.7; not
-// 32x32 (32) 41.0, 42.2.  Three not: 1000 of degree 4 20.7, 21.9, 10x10x10 30.8, 32.1.
-// Two nodes.  Two sources: 38x40 torus 47.8, 39.7, 12x13x13 42.1, 40.2, 2000 of degree 8 36.3, 35.6.  Four, 8 levels: 2000 of degree 4 (8)
-// 37.6, 37.1, of degree 8 49.8, 48.6, 1300 of degree 5 34.4, 32.4; not 6x6x6x6 torus (12) 42.4, 45.6.  Five, above 1536 nodes (below,
-// one at a time is the faster one: 1300 of degree 5 39.5, 40.6), and six, 11: 2000 of degree 4 53.7, 47.1 and 54.8, 48.5, of degree 8 71.4, 60.6
-// and 73.5, 62.6; not 11x11x11 (15) with six 59.4, 60.7.  Seven and eight, 5: 2000 of degree 8 75.4, 74.4 and 78.7, 77.9, of a generalized
-// Kautz topology of degree 6 58.4, 43.6 and 61.9, 46.5; not of degree 4 (8) 55.8, 58.7.
+// level for both.  An odd source has such a pass to itself; 10 links of two nodes have no registers for it, 8 spill 16 bytes.  A link's loads are
+// added up in another order than one source at a time has them, so a call's last bits depend on which it takes; not on the
+// workspace.  (us, the faster of k_small_loads and one at a time, and this.)
+// A node a thread.  Two sources: 32x32 torus 31.3, 26.5, 10x10x10 24.9, 23.1, 1000 of degree 4 17.5, 16.5, of degree 8 21.9, 21.7, 1024 of a
+// generalized Kautz topology of degree 8 19.0, 17.5, hypercube of 1024 27.6, 26.8.  Four, 16 levels: 1000 of degree 4 26.9, 25.4, of degree 8 31.4, 30.3,
+// 8x8x16 torus 37.5, 36.8, 10x10x10 (15) 36.8, 35.8, hypercube of 1024 38.3, 36.7; not 32x32 (32) 41.0, 42.2.  Three not: 1000 of degree 4 20.7, 21.9,
+// 10x10x10 30.8, 32.1.
+// Two nodes.  Two sources, up to 6 links: 38x40 torus 47.9, 40.7, 12x13x13 42.0, 40.7, 2000 of degree 4 26.9, 26.1; not with 8: 1300 28.3, 28.9, 1800
+// 31.8, 32.7.  Four, up to 6 links, 8 levels: 2000 of degree 4 (8) 38.1, 37.5, 1300 of degree 5 33.6, 32.2; not 6x6x6x6 torus (12) 42.4, 45.6, nor
+// 8 links, 1800 44.2, 45.1 (but 1368 of a generalized Kautz topology 31.1, 28.0).  Five, above 1536 nodes (below, one at a time is the faster
+// one: 1300 of degree 5 39.5, 40.6), and six, 11: 2000 of degree 4 54.2, 47.9 and 57.9, 51.2, of degree 8 71.1, 61.6 and 76.0, 65.0; not 11x11x11 (15) with
+// six 59.4, 60.7.  Seven and eight, 5: 2000 of degree 8 76.1, 75.0 and 79.3, 78.5, of a generalized Kautz topology of degree 8 75.5, 45.4 and 74.9,
+// 44.6, of degree 6 58.4, 43.6 and 61.9, 46.5; not of degree 4 (8) 55.8, 58.7.
 inline bool node_pairs(int N, int ell_words, int depth, int src_count) {
   if (N > kNodeMost * kSmallThreads) return false;
   const int sources = node_cut(N, src_count).per_wg;
   if (N <= kSmallThreads) return ell_words <= 5 && (sources == 2 || (sources == 4 && depth <= 16));
   if (ell_words > 4) return false;
   switch (sources) {
-    case 2: return true;
-    case 4: return depth <= 8;
+    case 2: return ell_words <= 3;
+    case 4: return ell_words <= 3 && depth <= 8;
     case 5: return N > kSmallThreads * 3 / 2 && depth <= 11;
     case 6: return depth <= 11;
     case 7:

@@ -708,10 +708,19 @@ template <int KS, int kNodes, int kSources, bool kDemand>
 __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   static_assert(kSources == 1 || !kDemand);
   extern __shared__ double s_small[];
-  typedef double Values __attribute__((ext_vector_type(kSources)));  // of a node, a source each
+  typedef double Several __attribute__((ext_vector_type(kSources)));
+  using Values = std::conditional_t<kSources == 1, double, Several>;  // of a node, a source each
   // sigma of even and odd levels, coefs of even and odd levels
   constexpr uint32_t kApart = node_apart(kNodes, kSources), kBytes = 8 * kSources;
   constexpr int kNever = -2, kNone = -1;
+  // A node's place in an array of pairs.  Links of a generalized Kautz topology of degree 8 lead from consecutive nodes to every eighth one: 16
+  // bytes each, those lie in two sixteenths of the banks.  So with 7 and 8 links the nodes of each block of 16 are permuted, another way from
+  // block to block; with fewer that costs other families more than it gives this one.  (us, the faster of k_small_loads and one at a time, pairs with
+  // nodes in order, permuted.  Generalized Kautz of degree 8, 1024 nodes 24.3, 26.5, 21.1, 1368 37.4, 41.3, 33.4, 1800 74.8, 57.8, 44.9, of degree 7, 900 nodes
+  // 20.2, 19.6, 20.3; random, 1000 of degree 8 31.4, 30.3, 30.6; 5x5x6x6 torus, 512 sources, 23.6, 22.8, 23.5.  With up to 6 links, so left in order, 1024
+  // sources of 1800 of a generalized Kautz topology of degree 5 28.2, 27.5, 30.3, 512 of a 38x40 torus 48.1, 39.9, 42.4.)
+  constexpr bool kPermuted = kSources > 1 && KS == 4;
+  const auto place = [](uint32_t v) { return kPermuted ? v ^ (v >> 4 & 15u) : v; };
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
   const int s_last = min(sv.src_count, s_first + sv.per_wg);
@@ -724,8 +733,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
     out[k].load(sv.out, 8 * v);
 #pragma unroll
     for (int j = 0; j < KS; ++j) {  // places of 16 bits: ids are below 2048
-      in[k].w[j] *= kSources;
-      out[k].w[j] *= kSources;
+      const auto places = [&](uint32_t w) { return place(w >> 3 & 0x1fffu) * kBytes | place(w >> 19) * kBytes << 16; };
+      if (kSources > 1) {
+        in[k].w[j] = places(in[k].w[j]);
+        out[k].w[j] = places(out[k].w[j]);
+      }
     }
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;
@@ -746,20 +758,28 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
       for (int i = 0; i < kSources; ++i) {
         const bool there = v < n && (kSources == 1 || s + i < s_last), source = (kSources == 1 || there) && v == sv.src_begin + s + i;
         lvl[k][i] = !there ? kNever : source ? 0 : kNone;
-        first[i] = own[k][i] = source ? 1.0 : 0.0;
+        own[k][i] = source ? 1.0 : 0.0;
+        if constexpr (kSources == 1)
+          first = own[k][i];
+        else
+          first[i] = own[k][i];
       }
       demand[k] = 0.0;
       if (v < n) {
-        lds_put(kBytes * v, first);
+        lds_put(kBytes * place(v), first);
 #pragma unroll
-        for (int a = 1; a < 4; ++a) lds_put(kBytes * v + a * kApart, (Values)0.0);
+        for (int a = 1; a < 4; ++a) lds_put(kBytes * place(v) + a * kApart, (Values)0.0);
         if (kDemand) demand[k] = sv.dem[(size_t)v * (size_t)sv.dem_ld + (size_t)s];
       }
     }
     // of source i, from what was gathered of a node's links
     const auto of = [&](const Values (&y)[2 * KS], int i, double (&x)[2 * KS]) {
 #pragma unroll
-      for (int j = 0; j < 2 * KS; ++j) x[j] = y[j][i];
+      for (int j = 0; j < 2 * KS; ++j)
+        if constexpr (kSources == 1)
+          x[j] = y[j];
+        else
+          x[j] = y[j][i];
     };
     const auto gather = [&](const SmallRow<KS>& row, uint32_t from, Values (&y)[2 * KS]) {
 #pragma unroll
@@ -787,7 +807,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
           if ((kSources == 1 || lvl[k][i] == kNone) && a > 0.0) {
             lvl[k][i] = l;
             own[k][i] = a;
-            lds_put(kBytes * (t + T * k) + 8 * i + kNow, a);
+            lds_put(kBytes * place(t + T * k) + 8 * i + kNow, a);
           }
         }
       }
@@ -810,7 +830,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
 #pragma unroll
           for (int j = 0; j < 2 * KS; ++j) acc[k][j] = __builtin_fma(own[k][i], x[j], acc[k][j]);
           const double r = recip(own[k][i]);
-          lds_put(kBytes * (t + T * k) + 8 * i + kNow, (kDemand ? demand[k] * r : r) + SmallNode<KS>::sum_pairs(x));
+          lds_put(kBytes * place(t + T * k) + 8 * i + kNow, (kDemand ? demand[k] * r : r) + SmallNode<KS>::sum_pairs(x));
         };
         if constexpr (kSources == 1) {
           add(0);
@@ -847,7 +867,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
       for (int j = 0; j < 2 * KS; ++j) to[(size_t)j * (size_t)N] = acc[k][j];
     }
   }
-  small_totals(sv, &lds_at(s_small, 3 * kApart + kBytes * (uint32_t)N), dsum, reached, largest >= kTwo53, wd, kDemand);
+  small_totals(sv, &lds_at(s_small, 3 * kApart + kBytes * (uint32_t)node_places(N)), dsum, reached, largest >= kTwo53, wd, kDemand);
 }
 
 // Distances and path counts of the sources of a workgroup: rows of the outputs (any of them may be null), search and

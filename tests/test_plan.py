@@ -191,24 +191,29 @@ NODES = r"""
 using namespace a2a_dev;
 
 int main() {
-  long long bad = 0, seen = 0;
+  long long bad = 0, seen[2] = {};
   for (int N = 1; N <= kScaledNodes; ++N)
     for (int words : {2, 3, 4, 5, 8})
       for (int depth : {0, 1, 10, 11, 253})
-        for (int n : {1, 2, 255, 256, 257, 511, 512, 513, 1024, 1536, N - 1, N}) {
-          if (n < 1 || n > N || !node_fits(N, words, depth, n)) continue;
-          const NodeCut c = node_cut(N, n);
-          ++seen;
-          const bool ok = c.threads >= kSmallWave && c.threads % kSmallWave == 0 && c.threads <= kSmallThreads &&
-                          c.nodes >= 1 && c.nodes <= (words <= 5 ? kNodeMost : 1) && c.nodes * c.threads >= N &&
-                          N * 8 <= node_apart(c.nodes) &&
-                          node_lds_bytes(N, c.nodes) >= 3 * (size_t)node_apart(c.nodes) + 8 * (size_t)N + c.threads / kSmallWave * 32 &&
-                          node_lds_bytes(N, c.nodes) <= kSmallLds && c.per_wg >= 1 && c.workgroups <= kComputeUnits &&
-                          (long long)c.workgroups * c.per_wg >= n && (long long)(c.workgroups - 1) * c.per_wg < n;
-          if (!ok && ++bad <= 10) std::printf("N %d words %d depth %d sources %d\n", N, words, depth, n);
+        for (int n : {1, 2, 255, 256, 257, 511, 512, 513, 1024, 1280, 1536, N - 1, N}) {
+          for (int sources = 1; sources <= 2; ++sources) {  // at a time
+            if (n < 1 || n > N || !(sources == 2 ? node_pairs(N, words, depth, n) : node_fits(N, words, depth, n))) continue;
+            const NodeCut c = node_cut(N, n);
+            ++seen[sources - 1];
+            const int most = sources == 2 ? (words <= 4 ? kNodeMost : words <= 5 ? 1 : 0) : words <= 5 ? kNodeMost : 1;  // nodes that are built for
+            const size_t lds = node_lds_bytes(N, c.nodes, sources), each = (size_t)node_places(N) * 8 * sources;  // of an array
+            const bool ok = c.threads >= kSmallWave && c.threads % kSmallWave == 0 && c.threads <= kSmallThreads &&
+                            c.nodes >= 1 && c.nodes <= most && c.nodes * c.threads >= N &&
+                            node_places(N) >= N && each <= (size_t)node_apart(c.nodes, sources) && each <= 0x10000 &&  // places have 16 bits
+                            node_apart(c.nodes, sources) % (8 * sources) == 0 &&
+                            lds >= 3 * (size_t)node_apart(c.nodes, sources) + each + c.threads / kSmallWave * 32 &&
+                            lds <= kSmallLds && c.per_wg >= sources && c.workgroups <= kComputeUnits &&
+                            (long long)c.workgroups * c.per_wg >= n && (long long)(c.workgroups - 1) * c.per_wg < n;
+            if (!ok && ++bad <= 10) std::printf("N %d words %d depth %d sources %d, %d at a time\n", N, words, depth, n, sources);
+          }
         }
-  std::printf("%lld cuts, %lld bad\n", seen, bad);
-  return bad != 0 || seen == 0;
+  std::printf("%lld and %lld cuts, %lld bad\n", seen[0], seen[1], bad);
+  return bad != 0 || seen[0] == 0 || seen[1] == 0;
 }
 """
 
@@ -223,7 +228,7 @@ EDGES = r"""
 using namespace a2a_dev;
 
 int main() {
-  // nodes, words of the link table, levels, sources, whether k_node_loads was the faster one when both were timed
+  // nodes, words of the link table, levels, sources, whether k_node_loads was the faster one when both were timed, a source at a time
   const int measured[][5] = {
       {256, 4, 4, 256, 1},   {1024, 2, 68, 512, 1},  {500, 2, 250, 500, 1},  {1000, 3, 15, 768, 1},  {576, 2, 24, 576, 0},
       {702, 2, 26, 702, 0},  {729, 3, 12, 729, 1},   {1024, 5, 10, 1024, 1}, {1024, 4, 12, 1024, 0}, {1000, 3, 15, 1000, 0},
@@ -236,6 +241,18 @@ int main() {
   for (const auto& m : measured)
     if (node_fits(m[0], m[1], m[2], m[3]) != (m[4] != 0)) {
       std::printf("%d nodes, %d words, %d levels, %d sources: not %d\n", m[0], m[1], m[2], m[3], m[4]);
+      ++bad;
+    }
+  const int pairs[][5] = {  // two at a time against the faster of the others
+      {1024, 2, 32, 512, 1}, {1000, 3, 15, 512, 1},  {1000, 4, 5, 512, 1},   {1024, 5, 10, 512, 1},  {1000, 2, 9, 768, 0},
+      {1000, 3, 15, 768, 0}, {1024, 3, 16, 1000, 1}, {1024, 5, 10, 1024, 1}, {1024, 4, 4, 1024, 1},  {1024, 2, 32, 1024, 0},
+      {1520, 2, 39, 512, 1}, {2028, 3, 18, 512, 1},  {1300, 4, 5, 512, 0},   {1800, 4, 5, 512, 0},   {2000, 2, 8, 1024, 1},
+      {1300, 3, 6, 1024, 1}, {1296, 4, 12, 1024, 0}, {1800, 4, 5, 1024, 0},  {1300, 3, 6, 1280, 0},  {2000, 2, 8, 1280, 1},
+      {2000, 4, 5, 1280, 1}, {2000, 2, 8, 1500, 1},  {1368, 4, 4, 1368, 1},  {1331, 3, 15, 1331, 0}, {2000, 4, 5, 1700, 1},
+      {1800, 4, 4, 1800, 1}, {2000, 4, 5, 2000, 1},  {2000, 2, 8, 2000, 0}};
+  for (const auto& m : pairs)
+    if (node_pairs(m[0], m[1], m[2], m[3]) != (m[4] != 0)) {
+      std::printf("%d nodes, %d words, %d levels, %d sources: not %d, two at a time\n", m[0], m[1], m[2], m[3], m[4]);
       ++bad;
     }
   return bad != 0;

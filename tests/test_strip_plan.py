@@ -86,7 +86,8 @@ int main(int argc, char** argv) {  // nodes, words of the link table, deepest le
   if (std::atoi(argv[4]) != 0)
     std::printf("%d", flow_groups(N, words, N, N > kFlowNodes).groups);
   else
-    std::printf("%d", node_fits(N, words, depth, N) ? node_cut(N, N).workgroups : small_cut(N, depth, words, N, SmallWhat::kLoads).workgroups);
+    std::printf("%d", node_pairs(N, words, depth, N) || node_fits(N, words, depth, N) ? node_cut(N, N).workgroups
+                                                                                    : small_cut(N, depth, words, N, SmallWhat::kLoads).workgroups);
 }
 """
 

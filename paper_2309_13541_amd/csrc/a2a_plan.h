@@ -199,13 +199,18 @@ inline SmallCut small_cut(int N, int depth, int ell_words, int src_count, SmallW
 
 // Link loads with a thread per node (k_node_loads): LDS of four arrays of a double per node and source, a constant apart, and the waves'
 // totals.  The constant is part of an instruction, but for the coefs of two nodes a thread and two sources: 64 KB on, each gather of
-// theirs takes an addition.  Two sources' arrays are not a power of two apart: the compiler made a constant that sets a bit of the place an
-// operation of its own, and kept the results (2 nodes and 8 links: 100 bytes a lane spilled, now 16; 6 links 126 registers, 111).
+// theirs takes an addition.  With permuted places the arrays are not a power of two apart: the compiler made a constant that sets a bit of the
+// place an operation of its own, and kept the results (2 nodes and 8 links: 100 bytes a lane spilled, now 16).  In order nothing spills either
+// way, and a power of two is the faster one (us, 16 bytes more and this: 40x40 torus, 512 sources 42.8, 42.1, 12x13x13 41.1, 40.8, 1397 nodes
+// of degree 5 45.1, 44.5, 1500 sources of 2000 of degree 4 51.7, 51.3, 2000 of a generalized Kautz topology of degree 6 47.6, 47.1).
 constexpr int kNodeMost = 2;  // nodes a thread may have
-constexpr int node_apart(int nodes, int sources = 1) { return nodes * kSmallThreads * 8 * sources + (sources > 1 ? 16 : 0); }
+constexpr bool node_permuted(int words, int sources) { return sources > 1 && words == 4; }  // (k_node_loads)
+constexpr int node_apart(int nodes, int sources, int words) {
+  return nodes * kSmallThreads * 8 * sources + (node_permuted(words, sources) ? 16 : 0);
+}
 constexpr int node_places(int N) { return (N + 15) / 16 * 16; }  // in whole blocks of 16
-constexpr size_t node_lds_bytes(int N, int nodes, int sources = 1) {
-  return 3 * (size_t)node_apart(nodes, sources) + (size_t)node_places(N) * 8 * sources + kSmallThreads / kSmallWave * 32;
+constexpr size_t node_lds_bytes(int N, int nodes, int sources, int words) {
+  return 3 * (size_t)node_apart(nodes, sources, words) + (size_t)node_places(N) * 8 * sources + kSmallThreads / kSmallWave * 32;
 }
 
 // A thread has a node, or two where the registers allow it (link tables of 8 words spill: 1100 nodes 124 us, k_small_loads 52).  A

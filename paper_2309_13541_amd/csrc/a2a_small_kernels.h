@@ -711,7 +711,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   typedef double Several __attribute__((ext_vector_type(kSources)));
   using Values = std::conditional_t<kSources == 1, double, Several>;  // of a node, a source each
   // sigma of even and odd levels, coefs of even and odd levels
-  constexpr uint32_t kApart = node_apart(kNodes, kSources), kBytes = 8 * kSources;
+  constexpr uint32_t kApart = node_apart(kNodes, kSources, KS), kBytes = 8 * kSources;
   constexpr int kNever = -2, kNone = -1;
   // A node's place in an array of pairs.  Links of a generalized Kautz topology of degree 8 lead from consecutive nodes to every eighth one: 16
   // bytes each, those lie in two sixteenths of the banks.  So with 7 and 8 links the nodes of each block of 16 are permuted, another way from
@@ -719,7 +719,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
   // nodes in order, permuted.  Generalized Kautz of degree 8, 1024 nodes 24.3, 26.5, 21.1, 1368 37.4, 41.3, 33.4, 1800 74.8, 57.8, 44.9, of degree 7, 900 nodes
   // 20.2, 19.6, 20.3; random, 1000 of degree 8 31.4, 30.3, 30.6; 5x5x6x6 torus, 512 sources, 23.6, 22.8, 23.5.  With up to 6 links, so left in order, 1024
   // sources of 1800 of a generalized Kautz topology of degree 5 28.2, 27.5, 30.3, 512 of a 38x40 torus 48.1, 39.9, 42.4.)
-  constexpr bool kPermuted = kSources > 1 && KS == 4;
+  constexpr bool kPermuted = node_permuted(KS, kSources);
   const auto place = [](uint32_t v) { return kPermuted ? v ^ (v >> 4 & 15u) : v; };
   const int T = (int)blockDim.x, t = (int)threadIdx.x, N = sv.N;
   const int s_first = (sv.wg0 + (int)blockIdx.x) * sv.per_wg;
@@ -733,11 +733,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_node_loads(SmallView sv) {
     out[k].load(sv.out, 8 * v);
 #pragma unroll
     for (int j = 0; j < KS; ++j) {  // places of 16 bits: ids are below 2048
-      const auto places = [&](uint32_t w) { return place(w >> 3 & 0x1fffu) * kBytes | place(w >> 19) * kBytes << 16; };
-      if (kSources > 1) {
-        in[k].w[j] = places(in[k].w[j]);
-        out[k].w[j] = places(out[k].w[j]);
-      }
+      const auto places = [&](uint32_t w) {
+        return kPermuted ? place(w >> 3 & 0x1fffu) * kBytes | place(w >> 19) * kBytes << 16 : w * kSources;
+      };
+      in[k].w[j] = places(in[k].w[j]);
+      out[k].w[j] = places(out[k].w[j]);
     }
 #pragma unroll
     for (int j = 0; j < 2 * KS; ++j) acc[k][j] = 0.0;

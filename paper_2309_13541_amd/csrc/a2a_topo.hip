@@ -768,7 +768,7 @@ SmallPlan small_loads_plan(const a2a_topo* t, int32_t src_count, bool demand) {
     p.nodes = c.nodes;
     p.workgroups = c.workgroups;
     p.at_a_time = pairs ? 2 : 1;
-    p.lds = node_lds_bytes(t->N, c.nodes, p.at_a_time);
+    p.lds = node_lds_bytes(t->N, c.nodes, p.at_a_time, t->ell_words);
     p.sv.per = 1;
     p.sv.per_wg = c.per_wg;
   }

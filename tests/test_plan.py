@@ -201,12 +201,12 @@ int main() {
             const NodeCut c = node_cut(N, n);
             ++seen[sources - 1];
             const int most = sources == 2 ? (words <= 4 ? kNodeMost : words <= 5 ? 1 : 0) : words <= 5 ? kNodeMost : 1;  // nodes that are built for
-            const size_t lds = node_lds_bytes(N, c.nodes, sources), each = (size_t)node_places(N) * 8 * sources;  // of an array
+            const size_t lds = node_lds_bytes(N, c.nodes, sources, words), each = (size_t)node_places(N) * 8 * sources;  // of an array
             const bool ok = c.threads >= kSmallWave && c.threads % kSmallWave == 0 && c.threads <= kSmallThreads &&
                             c.nodes >= 1 && c.nodes <= most && c.nodes * c.threads >= N &&
-                            node_places(N) >= N && each <= (size_t)node_apart(c.nodes, sources) && each <= 0x10000 &&  // places have 16 bits
-                            node_apart(c.nodes, sources) % (8 * sources) == 0 &&
-                            lds >= 3 * (size_t)node_apart(c.nodes, sources) + each + c.threads / kSmallWave * 32 &&
+                            node_places(N) >= N && each <= (size_t)node_apart(c.nodes, sources, words) && each <= 0x10000 &&  // places have 16 bits
+                            node_apart(c.nodes, sources, words) % (8 * sources) == 0 &&
+                            lds >= 3 * (size_t)node_apart(c.nodes, sources, words) + each + c.threads / kSmallWave * 32 &&
                             lds <= kSmallLds && c.per_wg >= sources && c.workgroups <= kComputeUnits &&
                             (long long)c.workgroups * c.per_wg >= n && (long long)(c.workgroups - 1) * c.per_wg < n;
             if (!ok && ++bad <= 10) std::printf("N %d words %d depth %d sources %d, %d at a time\n", N, words, depth, n, sources);

@@ -299,6 +299,26 @@ constexpr size_t wide_words_bytes(int slots) { return (size_t)slots * kSmallThre
 constexpr int wide_list(int N, int W) { return !wide_sparse(W) ? 0 : N / 8 < kWideList ? N / 8 : kWideList; }
 static_assert(wide_words_bytes(32) + kWideList * 2 <= kSmallLds);
 
+// Whether the waves of a workgroup store the same row of distances at a time, a barrier in front of each, and not each a slot of all its rows.
+// What is under way then lies in few pages, and lines that two waves share are written soon after each other; but a wave waits for the others, and
+// one without a slot stays.  So it is for calls of many rows that start within a line of 64 bytes; of rows of whole lines, for the longest, for
+// large calls with little work from row to row (distances of 3 bits), and for many levels, where few workgroups would store at a time.
+// (us, each by itself and together.  Within a line: all of 40001 nodes of degree 3 2037, 1512, 20011 of degree 5 565, 432, 45000 of degree 8 2201, 1863, 9001
+// 139, 124; 190 MB, 8750 nodes of degree 8 91.8, 87.5, 20011 105, 98.6, 30001 131, 122, 25000 116, 117; 213, 44444 nodes of degree 3 158, 160, of degree 8 165,
+// 156.  Not 144 MB, 900 sources of 44444 of degree 3 147, 154, nor 300 of 20011 70.8, 76.5, nor just above 8192 nodes, where the last slot is nearly empty: 8200 of
+// degree 8 105, 109, 8260 119.7, 120.7, but 8488 118, 113.
+// Whole lines: 65536 of degree 8 4000, 3756, 4096 sources 384, 351, of degree 3 403, 364, all 4034, 3848, of degree 4 3624, 3699, 63488 of degree 3 3842, 3625, 4096
+// sources 332, 330, 62000 of degree 8 3348, 3172; 1024 of 65536 of degree 3 196, 208.  Fewer nodes: 50000 of degree 8 2200, 2112, 56000 2654, 2553, 53248 2361,
+// 2301; not 32000 sources of 48000 1300, 1323, 44800 1664, 1710, 36000 1098, 1174, nor 60000 of degree 3 3134, 3281, nor where 64 sources share a word, 16384 of
+// degree 3 284, 333, 8448 of degree 8 98.7, 103.3 (but 9600 124.8, 121.7).  Tori: 36x36x36 7.92, 7.68 ms, 32x32x32 3.22, 3.07, 10922 sources of it 1.36, 1.31;
+// not 4665 of 36x36x36 1325, 1339 us, nor 64 sources a word, 24x24x24 449, 451.)
+inline bool wide_together(int N, int src_count, int W, int depth) {
+  const long long bytes = 4ll * N * src_count;
+  if (N % 16 != 0) return N >= 8400 && src_count >= 1200 && bytes >= 190000000;
+  if (W == 16 && (N >= 62000 ? bytes >= 500000000 : depth < 8 && bytes >= 9000000000)) return true;
+  return W != 64 && depth >= 40 && bytes >= 1400000000;
+}
+
 // ---------------------------------------------------------------------------------------
 // link loads by sources in LDS, links in registers (a2a_flow_kernels.h)
 // ---------------------------------------------------------------------------------------

@@ -896,6 +896,7 @@ int wide_search(const a2a_topo* t, WideView* wv, int out, char* ws, size_t ws_by
   wv->slots = W == 16 ? (t->N + 2 * kWideThreads - 1) / (2 * kWideThreads) : (t->N + kWideThreads - 1) / kWideThreads * (W / 32);
   wv->out = t->d_ell_out;
   wv->list = wide_list(t->N, W);
+  wv->together = wv->dist != nullptr && wide_together(t->N, n, W, t->level_bound);
   const size_t masks = (size_t)(wv->depth / 2 + 1) * wv->slots * kWideThreads * sizeof(uint32_t);
   const size_t room = ws_bytes / (masks + kSmallCounters * sizeof(long long));
   if (room < 1) return A2A_ERR_WORKSPACE_TOO_SMALL;

@@ -31,6 +31,7 @@ struct WideView {
   int32_t* dist;        // [src_count][N], may be null
   unsigned char* level; // [src_count][small_level_bytes(N)]: the same as bytes (instead of dist)
   long long* sums;      // [src_count], may be null
+  int together;         // whether the waves of a workgroup store the same row of dist at a time (wide_together)
   int N, depth, src_begin, src_count;
   int slots;            // words of masks per thread that hold nodes, at most kWideSlots
   int list;             // most entries of a sparse level's list
@@ -105,8 +106,7 @@ __device__ __forceinline__ bool wide_steps_while(F&& f, std::index_sequence<I...
 // The first levels have few new nodes.  While those of the level before fit a list (wide_list), they are what is gone over: their
 // R_{l-1} is ORed into the words of their out-neighbours, those that gain by it are the next list (a node once for every
 // link that brought something), and a thread finds R_l of its own there.  65536 nodes of degree 8: four of seven levels, some 20
-// thousand cycles each where the others take 66; sums alone 3.57, now 2.31 ms, with distances 4.09, now 3.98 into the
-// same buffers, 4.41, now 4.07 into others on every call (the stores).
+// thousand cycles each where the others take 66; sums alone 3.57, 2.31 ms (with distances, then with rows a wave at a time, 4.09, 3.98).
 // kOut: what is wanted.  kWideMasks: the newly reached of every level 1..depth, [groups][depth][slots][kWideThreads].
 // kScaled: the table has 8 x id (up to 8191 nodes; 64 sources a word only).
 enum { kWideDist, kWideBytes, kWideMasks };
@@ -142,8 +142,8 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   const int groups = (wv.src_count + W - 1) / W;
   // All workgroups start together and their phases are equally long: all would search at a time and then all write at a
   // time.  The first start is spread over about the length of a search.  Without, with half, with one and a half times the spread, and as
-  // it is: 65536 nodes of degree 8 3.96, 3.89, 3.92, 3.77 ms; of degree 3 (13 levels) 4.11, 3.99, 4.07, 3.79; 40001 of degree 5 1.71, 1.63, 1.52,
-  // 1.49; 20011 of degree 5 518, 473, 442, 427 us; a 40x40x40 torus (60 levels) 15.6, 15.1, 16.0, 15.7 ms.
+  // it is: 65536 nodes of degree 8 3.96, 3.89, 3.92, 3.77 ms; 40001 of degree 5 1.71, 1.63, 1.52, 1.49; 20011 of degree 5 518, 473, 442, 427 us; a
+  // 40x40x40 torus (60 levels) 15.6, 15.1, 16.0, 15.7 ms; rows not stored together, without, with half, as it is: 65536 of degree 3 (13 levels) 5.24, 4.57, 4.06.
   if (kOut == kWideDist && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
@@ -413,9 +413,9 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
     constexpr int kGroups = kWideThreads / (4 * kWave);
     for (int slot0 = 0; slot0 < wv.slots; slot0 += kGroups) {
       const bool there = slot0 + (wave >> 2) < wv.slots;
-      // Waves without a slot stay for the barriers of the rows only.  (Sums alone, where they stayed too and now: 33000 nodes of degree 4 798, 779 us,
-      // 18000 of degree 5 207, 204, 8300 of degree 4 59.2, 57.5.)
-      if (!there && (kBytes || wv.dist == nullptr)) break;
+      // Waves without a slot stay for the barriers of the rows only.  (33000 nodes of degree 4, sums alone, where they stayed too and now 798, 779 us,
+      // 18000 of degree 5 207, 204; distances of 664 sources of 8300 of degree 3, with barriers and now 55.5, 48.7.)
+      if (!there && (kBytes || !wv.together)) break;
       const int slot = min(slot0 + (wave >> 2), wv.slots - 1);
       const uint32_t at = (uint32_t)slot * kWideThreads + 4 * (t & 255);
       const auto words = [&](const uint32_t* p) { return *reinterpret_cast<const uint4*>(p + at); };
@@ -466,15 +466,18 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
       if (!kBytes && wv.dist == nullptr) continue;
       const int v = slot / kWords * kStride + 4 * (t & 255);  // first of the lane's nodes
       int32_t* out = wv.dist + (size_t)(s_first + first) * (size_t)N;
-      const auto rows = [&](auto part) {
-        // The waves keep to the same row: what is under way then lies in few pages.  65536 nodes of degree 8 3997, now 3731 us, of degree 3
-        // 4436, 3921; 40001 of degree 5 1996, 1511; 20011 of degree 5 546, 432; torus 40x40x40 16.7, 15.4 ms.  Stores alone, without a
-        // search: 4.6 TB/s, 5.7 with the barrier.  (The rows of two slots at a time: 3772, 3789, 1493, 427 us, 15.7 ms.)
+      const auto rows = [&](auto part, auto together) {
+        // Stores alone, without a search: 4.6 TB/s, 5.7 with the barrier (65536 nodes).  (The rows of two slots at a time: 65536 of degree 8 3731, 3772 us,
+        // of degree 3 3921, 3789, 40001 of degree 5 1511, 1493, 20011 432, 427, a 40x40x40 torus 15.4, 15.7 ms.)
 #pragma unroll
         for (int j = 0; j < kLanes; ++j) {
-          if (j >= count) break;  // the same in all threads
-          asm volatile("s_barrier" ::: "memory");
-          if (first + j >= count) continue;
+          if constexpr (decltype(together)::value) {
+            if (j >= count) break;  // the same in all threads
+            asm volatile("s_barrier" ::: "memory");
+            if (first + j >= count) continue;
+          } else {
+            if (first + j >= count) break;
+          }
 #pragma unroll
           for (int n = 0; n < kPerStep; ++n) {
             const Int4 d = number(n * 16 + j);
@@ -507,10 +510,11 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
           }
           row += nl;
         }
-      } else if ((slot0 + kGroups) / kWords * kStride <= N)
-        rows(std::false_type{});
-      else
-        rows(std::true_type{});
+      } else if (wv.together) {
+        (slot0 + kGroups) / kWords * kStride <= N ? rows(std::false_type{}, std::true_type{}) : rows(std::true_type{}, std::true_type{});
+      } else {
+        (slot / kWords + 1) * kStride <= N ? rows(std::false_type{}, std::false_type{}) : rows(std::true_type{}, std::false_type{});
+      }
     }
     if (!kBytes && wv.sums != nullptr) {
 #pragma unroll

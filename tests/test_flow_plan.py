@@ -64,6 +64,14 @@ int main() {
             const bool whole = l.rows == n || (l.rows > 0 && l.rows % g.group == 0) || l.rows < g.group;
             check((l.rows == 0 || l.total <= bytes) && l.rows <= n && whole && (long long)l.parts * g.group >= l.rows &&
                   (part < 64 || l.rows == n), "layout", N, n, part);
+            // pieces: no more than the largest take, and among as many no fewer rounds of 256 sources
+            const auto fits = [&](int k) { return flow_layout_for(N, w, n, demand, std::min(k * g.group, n), k).total <= bytes; };
+            const auto rounds = [&](int rows) { return n / rows * ((rows + 255) / 256) + (n % rows + 255) / 256; };
+            if (part % 8 == 3 && l.rows >= g.group)
+              for (int k = 1; k <= g.groups && fits(k); ++k) {
+                const int rows = std::min(k * g.group, n), pieces = (n + rows - 1) / rows, has = (n + l.rows - 1) / l.rows;
+                check(has < pieces || (has == pieces && rounds(l.rows) <= rounds(rows)), "pieces", N, n, k);
+              }
           }
         }
   std::printf("%lld checks, %lld bad\n", seen, bad);

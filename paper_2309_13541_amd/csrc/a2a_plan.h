@@ -454,8 +454,9 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips =
   const int most = std::max(8, kComputeUnits / g.blocks / 8 * 8);
   g.group = (src_count + most - 1) / most;
   // By strips a source takes up to a megabyte of workspace, and what of a call fits it may be few groups, so they are smaller, at the price of
-  // as many partial loads (65536 nodes of degree 8, with groups as above and these: 4096 sources in 1 GB 11.4, 7.7 ms; groups of 128 for all
-  // 65536 sources 75.9, of 256 74.4 ms, in 1 GB 119 and 152, in 4 GB 82 and 82; of 50000 of a generalized Kautz topology of degree 5, 30.6, 29.6 ms).
+  // as many partial loads (65536 nodes of degree 8, with groups as above and these: 4096 sources in 1 GB 8.33, 6.42 ms; groups of 128 for all
+  // 65536 sources 71.9, of 256 71.3 ms, in 1 GB 100 and 125, in 4 GB 76.6 and 76.7; of 50000 of a generalized Kautz topology of degree 5, groups as above 29.6,
+  // of 128 30.6, these 30.9 ms).
   if (strips) g.group = std::min(g.group, std::min(256, std::max(128, src_count / 128)));
   g.groups = (src_count + g.group - 1) / g.group;
   return g;
@@ -463,10 +464,10 @@ inline FlowGroups flow_groups(int N, int ell_words, int src_count, bool strips =
 
 // Whether k_flow_links after k_strip_sources has two nodes a thread for its usual four or six: where all workgroups of the groups at hand then still
 // run at once.  A group's workgroups share an XCD, so that is a matter of the XCD with the most groups.  A link's load is the same sum.
-// (16384 sources, ms, usual and two nodes, and workgroups of that XCD with two: 65536 nodes of degree 8, 7 groups 30.3, 28.3 (32), 11 groups 24.7, 28.3
-// (64); 45000 of degree 3, 8 groups 21.1, 19.5 (22), 11 groups 19.4, 21.4 (44); 24000 of degree 8, 16 groups 8.48, 7.70 (24), 21 groups 8.14, 8.73 (36); 4096
-// of 33000 of degree 7, 7 groups 4.08, 3.70 (17), 11 groups 3.18, 3.66 (34).  Just above 32 with little left over it is the faster one now and then, too: 20353
-// of degree 6, 25 groups 6.74, 6.45 (40).)
+// (16384 sources, ms, usual and two nodes, and workgroups of that XCD with two: 65536 nodes of degree 8, 7 groups 27.2, 25.1 (32), 8 groups 24.3, 22.6 (32),
+// 11 groups 22.4, 24.7 (64), of degree 4, 8 groups 26.6, 24.6 (32), 9 groups 26.9, 28.5 (64); 50000 of a generalized Kautz topology of degree 5, 8 groups 14.0,
+// 12.7 (25), 10 groups 12.7, 14.8 (50); 45000 of degree 3, 8 groups 19.8, 17.4 (22), 11 groups 18.3, 19.5 (44); 24000 of degree 8, 16 groups 8.40, 7.67 (24),
+// 21 groups 8.08, 8.71 (36); 20353 of degree 6, 25 groups 6.73, 7.18 (40); 4096 of 33000 of degree 7, 7 groups 4.09, 3.72 (17), 11 groups 3.19, 3.67 (34).)
 inline bool strip_links_narrow(int N, int ell_words, int groups) {
   constexpr int kXcds = 8, kNarrow = 2 * kSmallThreads;
   return flow_nodes(ell_words) > 2 && (groups + kXcds - 1) / kXcds * ((N + kNarrow - 1) / kNarrow) <= kComputeUnits / kXcds;

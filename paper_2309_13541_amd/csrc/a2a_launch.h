@@ -32,7 +32,7 @@ template <int KS>
 void launch_flow_sssp(const SmallPlan& p, const SmallSssp& ss, int workgroups, hipStream_t st);
 template <int KS>
 void launch_small_sssp_add(const SmallPlan& p, const SmallSssp& ss, hipStream_t st);
-// W sources a word; out: kWideDist (16, 32 or 64) or kWideBytes (16 or 64).
+// W sources a word; out: kWideDist (16, 32 or 64; without a matrix its sums alone) or kWideBytes (16 or 64).
 template <int KS>
 void launch_wide_search(const WideView& wv, int W, int out, int workgroups, hipStream_t st);
 // Newly reached of every level; W: 16 or 64.

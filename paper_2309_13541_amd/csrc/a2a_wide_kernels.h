@@ -106,10 +106,10 @@ __device__ __forceinline__ bool wide_steps_while(F&& f, std::index_sequence<I...
 // The first levels have few new nodes.  While those of the level before fit a list (wide_list), they are what is gone over: their
 // R_{l-1} is ORed into the words of their out-neighbours, those that gain by it are the next list (a node once for every
 // link that brought something), and a thread finds R_l of its own there.  65536 nodes of degree 8: four of seven levels, some 20
-// thousand cycles each where the others take 66; sums alone 3.57, 2.31 ms (with distances, then with rows a wave at a time, 4.09, 3.98).
-// kOut: what is wanted.  kWideMasks: the newly reached of every level 1..depth, [groups][depth][slots][kWideThreads].
+// thousand cycles each where the others take 66; sums alone, then in the same kernel, 3.57, 2.31 ms (with distances, then with rows a wave at a time, 4.09, 3.98).
+// kOut: what is wanted.  kWideSums: no distances, a kernel of its own (18000 nodes of degree 5 207.8, 204.0 us, 65536 of degree 8 2318, 2266).  kWideMasks: the newly reached of every level 1..depth, [groups][depth][slots][kWideThreads].
 // kScaled: the table has 8 x id (up to 8191 nodes; 64 sources a word only).
-enum { kWideDist, kWideBytes, kWideMasks };
+enum { kWideDist, kWideBytes, kWideMasks, kWideSums };
 template <int W, int KS, int kPlanes, int kOut = kWideDist, bool kScaled = false>
 __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   using Word = typename WideWord<W>::type;
@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
   // time.  The first start is spread over about the length of a search.  Without, with half, with one and a half times the spread, and as
   // it is: 65536 nodes of degree 8 3.96, 3.89, 3.92, 3.77 ms; 40001 of degree 5 1.71, 1.63, 1.52, 1.49; 20011 of degree 5 518, 473, 442, 427 us; a
   // 40x40x40 torus (60 levels) 15.6, 15.1, 16.0, 15.7 ms; rows not stored together, without, with half, as it is: 65536 of degree 3 (13 levels) 5.24, 4.57, 4.06.
-  if (kOut == kWideDist && wv.dist != nullptr && groups > 2 * (int)gridDim.x)
+  if (kOut == kWideDist && groups > 2 * (int)gridDim.x)
     for (int k = ((int)blockIdx.x >> 3) * wv.depth * wv.slots * KS / 64; k > 0; --k) __builtin_amdgcn_s_sleep(16);
   for (int g = (int)blockIdx.x; g < groups; g += (int)gridDim.x) {
     const int s_first = g * W, count = min(W, wv.src_count - s_first), s0 = wv.src_begin + s_first;
@@ -413,9 +413,8 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
     constexpr int kGroups = kWideThreads / (4 * kWave);
     for (int slot0 = 0; slot0 < wv.slots; slot0 += kGroups) {
       const bool there = slot0 + (wave >> 2) < wv.slots;
-      // Waves without a slot stay for the barriers of the rows only.  (33000 nodes of degree 4, sums alone, where they stayed too and now 798, 779 us,
-      // 18000 of degree 5 207, 204; distances of 664 sources of 8300 of degree 3, with barriers and now 55.5, 48.7.)
-      if (!there && (kBytes || !wv.together)) break;
+      // Waves without a slot stay for the barriers of the rows only (664 sources of 8300 nodes of degree 3, with barriers and without 55.5, 48.7 us).
+      if (!there && (kOut != kWideDist || !wv.together)) break;
       const int slot = min(slot0 + (wave >> 2), wv.slots - 1);
       const uint32_t at = (uint32_t)slot * kWideThreads + 4 * (t & 255);
       const auto words = [&](const uint32_t* p) { return *reinterpret_cast<const uint4*>(p + at); };
@@ -463,7 +462,7 @@ __global__ void __launch_bounds__(kWideThreads) k_wide_dist(WideView wv) {
           sum[b % kLanes] += d.x + d.y + d.z + d.w;
         }
       }
-      if (!kBytes && wv.dist == nullptr) continue;
+      if (kOut == kWideSums) continue;
       const int v = slot / kWords * kStride + 4 * (t & 255);  // first of the lane's nodes
       int32_t* out = wv.dist + (size_t)(s_first + first) * (size_t)N;
       const auto rows = [&](auto part, auto together) {

@@ -31,8 +31,8 @@ template <int W, int KS, int kOut>
 void wide_search(const WideView& wv, int workgroups, hipStream_t st) {
   const size_t lds = wide_words_bytes(wv.slots) + (size_t)wv.list * 2;
   const auto launch = [&](auto kernel) { kernel<<<workgroups, kWideThreads, lds, st>>>(wv); };
-  if (kOut == kWideDist && wv.depth < 8)
-    launch(k_wide_dist<W, KS, kOut == kWideDist ? 3 : 6, kOut>);
+  if (kOut != kWideBytes && wv.depth < 8)
+    launch(k_wide_dist<W, KS, kOut != kWideBytes ? 3 : 6, kOut>);
   else
     launch(k_wide_dist<W, KS, 6, kOut>);
 }
@@ -114,10 +114,14 @@ template <int KS>
 void launch_wide_search(const WideView& wv, int W, int out, int workgroups, hipStream_t st) {
   if (out == kWideBytes)
     return W == 16 ? wide_search<16, KS, kWideBytes>(wv, workgroups, st) : wide_search<64, KS, kWideBytes>(wv, workgroups, st);
+  const auto search = [&](auto w) {
+    constexpr int kW = decltype(w)::value;
+    wv.dist != nullptr ? wide_search<kW, KS, kWideDist>(wv, workgroups, st) : wide_search<kW, KS, kWideSums>(wv, workgroups, st);
+  };
   switch (W) {
-    case 16: return wide_search<16, KS, kWideDist>(wv, workgroups, st);
-    case 32: return wide_search<32, KS, kWideDist>(wv, workgroups, st);
-    default: return wide_search<64, KS, kWideDist>(wv, workgroups, st);
+    case 16: return search(std::integral_constant<int, 16>{});
+    case 32: return search(std::integral_constant<int, 32>{});
+    default: return search(std::integral_constant<int, 64>{});
   }
 }
 
